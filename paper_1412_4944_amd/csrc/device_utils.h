@@ -55,7 +55,9 @@ struct Bf16x3Pair {
 };
 __device__ __forceinline__ unsigned pack_bf16(float v0, float v1) {
     const bf16x2 t = {(__bf16)v0, (__bf16)v1};           // v_cvt_pk_bf16_f32: round to nearest even
-    return __builtin_bit_cast(unsigned, t);
+    unsigned r = __builtin_bit_cast(unsigned, t);
+    asm("" : "+v"(r));                                   // or v0 is converted once more for each use of its half
+    return r;
 }
 __device__ __forceinline__ Bf16x3Pair split_bf16x3(float v0, float v1) {
     Bf16x3Pair r;

@@ -85,7 +85,7 @@ hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Wor
         sq.part = ws.sq_partial;
         sq.counter = ws.sq_counter;
         sq.out = sq_out;
-        sq.nb = 128;                           // <= kSqBlocks shares of err
+        sq.nb = (int)(m / 2048 < 1 ? 1 : m / 2048 < 128 ? m / 2048 : 128);   // <= kSqBlocks shares of err
     }
     return launch_polar_ns(p, K, nullptr, ws.partial, ws.offsets, accum_piece(m, K, p), ws.counts, D,
                            write_ops == 1 ? ws.dsw : nullptr, write_ops >= 2 ? ws.dsb : nullptr, write_ops,

@@ -4,37 +4,49 @@
 // U V^T is the orthogonal polar factor of P_j, and for a matrix scaled to singular values in
 // (0, sqrt(3)) the iteration converges to it quadratically; each step is two p x p x p products,
 // which are dense contractions, where the Jacobi SVD is p - 1 dependent rounds of plain ALU
-// work per sweep.  The block matrices P_j = Y_j X_j^T of this method are well conditioned
-// (condition numbers of 3 to 60 on the benchmark workloads), so 4 to 9 steps reach fp32
-// accuracy.  A block that has not converged after max_iters steps (rank-deficient or nearly
+// work per sweep.  A block that has not converged after max_iters steps (rank-deficient or nearly
 // so, zero, NaN) is handed, in the same workgroup, to the one-sided Jacobi SVD (jacobi_block.h),
 // which also supplies the orthonormal completion a vanishing singular value needs.
 //
-// The products run on the bf16 matrix cores at fp32 accuracy: X, its transpose and G = X^T X
-// are kept in LDS as three bf16 parts per entry (their exact sum is the fp32 value, see
-// device_utils.h), row-major, so that every MFMA operand is one 16-byte LDS read, and the six
-// partial products above 2^-24 are accumulated in fp32 (v_mfma_f32_32x32x16_bf16).  Every
-// wavefront owns one 32 x 32 tile of X in fp32 registers.
+// What bounds it: one workgroup on one CU per block, every step waiting for the one before, so
+// the time is the number of steps times the latency of a step.  Both are kept small:
+//   * Steps.  The singular values are pulled towards one by scaling X before a step: with all of
+//     them in [l, 1], X sqrt(3 / (1 + l + l^2)) makes the step's polynomial map [l, 1] to the
+//     smallest possible interval [l', 1].  A smaller singular value is safe (the polynomial never
+//     exceeds one and is positive on (0, sqrt(3))), it only takes longer; l starts at 0.16 (block
+//     matrices of this method have condition numbers of 2 to 10).  The last step is X (I + E/2 + 3/8 E^2), E = I - X^T X: its error is
+//     5/16 E^3 instead of 3/8 E^2.  Five steps where the plain iteration takes seven.
+//   * The step.  A wavefront owns a strip of 16 columns of X (v_mfma_f32_16x16x32_bf16 tiles, four
+//     consecutive rows of one column per lane and tile).  An accumulator tile is at the same time
+//     the B operand of the next product, up to an order of the contraction index that the A
+//     operand shares: X^T X takes its B operand from the registers that hold X, X E takes it from
+//     the registers that hold E, and only the A operands (the other wavefronts' columns of X,
+//     and, transposed by ds_read_b64_tr_b16 on the way out, its rows) go through LDS.
+//   * The products run at fp32 accuracy: every entry is the exact sum of three bf16 parts
+//     (device_utils.h), six partial products with fp32 accumulation; three in the last step, where
+//     they multiply an E below 1e-2 and are added to X.
+// Measured inside sbo_iterate (launch to launch, K = 32, p = 64): 31 us with 32 x 32 tiles, both operands
+// of every product through LDS and the plain iteration, 16 us as it is; p = 32: 21 -> 9 us, p = 16:
+// 22 -> 7 us.  A step at p = 64 is 4800 cycles (matrix work 1650 of them), the sum of eight pieces
+// 5000 (12000 with loads that touch half cache lines).
 //
 // The same launch can (a) sum the per-piece partial matrices of the fused select + accumulate
 // kernel on the way in, in piece order, which saves the separate reduction launch, and (b) form
 // the total squared error of the coding pass in extra workgroups.
 //
-// The stored matrix is atom-major (the transpose of P_j); the polar factor of the transpose is
-// the transpose of the polar factor, so iterating on the stored matrix yields D[j] directly.
+// X is the transpose of the stored, atom-major matrix, so a lane's four consecutive rows are
+// four consecutive dims of an atom (16-byte loads and stores), and X^T X is the Gram matrix of
+// P_j's columns weighted by the codes: nearly diagonal, which makes its row sums a good bound.
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "jacobi_block.h"
 #include "sq_total.h"
 
+#include <type_traits>
+
 namespace sbo {
 
 namespace {
-
-// upper half of a -> low half of the result, upper half of b -> high half
-__device__ __forceinline__ unsigned pack_upper(unsigned a, unsigned b) {
-    return __builtin_amdgcn_perm(b, a, 0x07060302u);
-}
 
 struct NsArgs {
     const float* M;            // [K][p][p] finished matrices, or nullptr: sum the pieces
@@ -59,48 +71,61 @@ struct NsArgs {
     int nb;
 };
 
+// sqrt(3 / (1 + l + l^2)) for l = 0.16 and then the l that the steps leave: 0.16, 0.375, 0.71, 0.96
+__device__ constexpr float kAlpha[4] = {1.5907f, 1.4081f, 1.1601f, 1.0206f};
+
 template <int P>
 constexpr int ns_threads() {
-    return P == 64 ? 256 : 64;
+    return P * 4;                              // a wavefront per strip of 16 columns
 }
+// bytes of one LDS image of X: per strip and contraction step of 32, three parts of 64 lanes x 16 bytes
 template <int P>
-constexpr int ns_pad() {
-    return P == 64 ? 64 : 32;
+constexpr int ns_image_bytes() {
+    return (P / 16) * ((P / 16 + 1) / 2) * 3 * 1024;
 }
-// dynamic LDS: nine bf16 planes [PAD][PAD + 8] (the Jacobi routine reuses this part) | fp32
-// scratch [PAD][PAD + 4] | vec, wec [PAD] | red[8]
+// dynamic LDS: two images (the Jacobi routine reuses this part) | red[2][2][4] floats
 template <int P>
 constexpr size_t ns_front_bytes() {
-    constexpr int PAD = ns_pad<P>();
-    const size_t planes = (size_t)9 * PAD * (PAD + 8) * 2;
-    const size_t jac = (size_t)jacobi_lds_floats<P>() * 4;
-    return ((planes > jac ? planes : jac) + 15) / 16 * 16;
+    const size_t img = (size_t)2 * ns_image_bytes<P>(), jac = (size_t)jacobi_lds_floats<P>() * 4;
+    const size_t sq = (size_t)(ns_threads<P>() + 2) * 8;
+    const size_t a = img > jac ? img : jac;
+    return ((a > sq ? a : sq) + 15) / 16 * 16;
 }
 template <int P>
 constexpr size_t ns_lds_bytes() {
-    constexpr int PAD = ns_pad<P>();
-    return ns_front_bytes<P>() + (size_t)PAD * (PAD + 4) * 4 + (size_t)2 * PAD * 4 + 8 * 4;
+    return ns_front_bytes<P>() + 16 * 4;
+}
+
+// Sums over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (bitwise the same in all of them).
+__device__ __forceinline__ float sum_groups(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a0 = r[0], a1 = r[1];
+    const float y = __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
+    const unsigned w = __builtin_bit_cast(unsigned, y);
+    auto q = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const unsigned b0 = q[0], b1 = q[1];
+    return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+}
+// Maximum over the 16 lanes of a row of non-negative values; a NaN wins (its bits are the largest).
+__device__ __forceinline__ float row_max_nan(float x) {
+    unsigned u = __builtin_bit_cast(unsigned, x);
+    auto step = [&](auto f) { u = max(u, __builtin_bit_cast(unsigned, f(__builtin_bit_cast(float, u)))); };
+    step([](float v) { return dpp_f<kDppXor1>(v); });
+    step([](float v) { return dpp_f<kDppXor2>(v); });
+    step([](float v) { return dpp_f<kDppHalfMirror>(v); });
+    step([](float v) { return dpp_f<kDppRowMirror>(v); });
+    return __builtin_bit_cast(float, u);
 }
 
 template <int P>
 __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
-    constexpr int T = P == 64 ? 2 : 1;         // 32-wide tiles per side
+    constexpr int T = P / 16;                  // tiles per side = strips = wavefronts
+    constexpr int S = (T + 1) / 2;             // contraction steps of 32 (p = 16: half of one)
     constexpr int NTH = ns_threads<P>();
-    constexpr int PAD = ns_pad<P>();           // padded dimension (p = 16 sits in one tile)
-    constexpr int LDB = PAD + 8;               // row stride of a bf16 plane (rows stay 16-byte aligned,
-                                               // eight consecutive rows cover all LDS banks)
-    constexpr int LDF = PAD + 4;               // row stride of the fp32 scratch
-    constexpr int KS16 = PAD / 16;
-    constexpr int PLANE = PAD * LDB;           // bf16 elements per plane
     constexpr int TPP_FALLBACK = NTH / (P / 2);          // the Jacobi routine with this workgroup's threads
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    unsigned short* Xp = reinterpret_cast<unsigned short*>(lds_raw);      // [3][PAD][LDB]
-    unsigned short* Xtp = Xp + 3 * PLANE;
-    unsigned short* Gp = Xtp + 3 * PLANE;                                 // holds G^T
-    float* F = reinterpret_cast<float*>(lds_raw + ns_front_bytes<P>());   // [PAD][LDF]
-    float* vec = F + PAD * LDF;
-    float* wec = vec + PAD;
-    float* red = wec + PAD;
+    float* red = reinterpret_cast<float*>(lds_raw + ns_front_bytes<P>());   // [4 slots][4 wavefronts]
 
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= g.K) {              // uniform: the workgroups of the squared-error total
@@ -111,10 +136,26 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         return;
     }
     const int j = blockIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, n = lane & 31;
-    const int ta = wave / T, tb = wave % T;    // this wavefront's tile of X
-    if (g.counts != nullptr && g.counts[j] == 0) {       // uniform: block keeps its basis
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = lane >> 4, c16 = lane & 15;
+    const int col = wave * 16 + c16;           // this lane's column of X = atom
+    // Where P_j comes from.  Pieces: block j' has ceil(n_j' / piece) of them, in block order.
+    BlockMatrixSource src = {nullptr, g.partial, 0, 1, P * P};
+    bool empty;
+    if (g.M != nullptr) {
+        src.M = g.M + (int64_t)j * P * P;
+        empty = g.counts != nullptr && g.counts[j] == 0;
+    } else {
+        int before = 0;                        // every wavefront for itself
+        for (int jj = lane; jj < j; jj += 64) before += (g.offsets[jj + 1] - g.offsets[jj] + g.piece - 1) / g.piece;
+        const int n_j = g.offsets[j + 1] - g.offsets[j];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+        src.pc_beg = __builtin_amdgcn_readfirstlane(before);
+        src.pc_end = src.pc_beg + (n_j + g.piece - 1) / g.piece;
+        empty = n_j == 0;
+    }
+    if (empty) {                               // uniform: block keeps its basis
         if (tid == 0) {
             g.fallback[j] = 0;
             if (g.iters_out != nullptr) g.iters_out[j] = 0;
@@ -122,240 +163,300 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         return;
     }
 
-    // Where P_j comes from.  Pieces: block j' has ceil(n_j' / piece) of them, in block order.
-    BlockMatrixSource src = {nullptr, g.partial, 0, 0, P * P};
-    if (g.M != nullptr) {
-        src.M = g.M + (int64_t)j * P * P;
-    } else {
-        int before = 0;
-        for (int jj = tid; jj < j; jj += NTH) before += (g.offsets[jj + 1] - g.offsets[jj] + g.piece - 1) / g.piece;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
-        if (lane == 0) red[wave] = __builtin_bit_cast(float, before);
-        __syncthreads();
-        before = 0;
-        for (int w = 0; w < T * T; ++w) before += __builtin_bit_cast(int, red[w]);
-        __syncthreads();
-        src.pc_beg = before;
-        src.pc_end = before + (g.offsets[j + 1] - g.offsets[j] + g.piece - 1) / g.piece;
-    }
-
-    // P_j -> the fp32 scratch, summed over the block's pieces in piece order (the order, and so
-    // the bits, of accum_reduce_kernel; a finished matrix is a single piece).  16-byte loads,
-    // those of kInFlight pieces in flight at a time: one workgroup has to pull a few hundred KiB
-    // that other CUs have just written, and each round of loads is a trip to memory.
+    // xr[t][r] = X[t*16 + grp*4 + r][col], summed over the block's pieces in piece order (the order,
+    // and so the bits, of accum_reduce_kernel; a finished matrix is a single piece).  A wavefront
+    // reads its 16 atoms as whole cache lines, kInFlight pieces at a time (each round of loads is a
+    // trip to memory that other CUs have just written), and turns the sum into its own layout
+    // through LDS.
+    f32x4 xr[T];
     {
-        constexpr int U = (P * P / 4 + NTH - 1) / NTH;     // 16-byte units per thread
         constexpr int kInFlight = 8;
-        const f32x4* base = reinterpret_cast<const f32x4*>(src.M != nullptr ? src.M : src.partial);
-        const int pc_beg = src.M != nullptr ? 0 : src.pc_beg, pc_end = src.M != nullptr ? 1 : src.pc_end;
-        f32x4 sum[U];
+        constexpr int LD = P / 4 + 1;          // 16-byte units per atom (odd: 16 atoms cover all banks)
+        static_assert(16 * LD * 16 * T <= (int)ns_front_bytes<P>(), "the strips fit in front");
+        const f32x4* base = reinterpret_cast<const f32x4*>(src.M != nullptr ? src.M : src.partial) + wave * (4 * P) + lane;
+        f32x4 sum[T];
 #pragma unroll
-        for (int u = 0; u < U; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int pc = pc_beg; pc < pc_end; pc += kInFlight) {
-            f32x4 v[kInFlight][U];
+        for (int t = 0; t < T; ++t) sum[t] = base[(int64_t)src.pc_beg * (P * P / 4) + t * 64];
+        for (int pc = src.pc_beg + 1; pc < src.pc_end; pc += kInFlight) {
+            f32x4 v[kInFlight][T];
 #pragma unroll
             for (int k = 0; k < kInFlight; ++k)
+                if (pc + k < src.pc_end) {                        // uniform
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int e4 = tid + NTH * u;
-                    const int pcc = min(pc + k, pc_end - 1);      // clamped loads are not added
-                    v[k][u] = e4 < P * P / 4 ? base[(int64_t)pcc * (P * P / 4) + e4] : f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int t = 0; t < T; ++t) v[k][t] = base[(int64_t)(pc + k) * (P * P / 4) + t * 64];
                 }
 #pragma unroll
             for (int k = 0; k < kInFlight; ++k)
-                if (pc + k < pc_end) {                            // uniform
+                if (pc + k < src.pc_end) {                        // uniform
 #pragma unroll
-                    for (int u = 0; u < U; ++u) sum[u] += v[k][u];
+                    for (int t = 0; t < T; ++t) sum[t] += v[k][t];
                 }
         }
+        f32x4* strip = reinterpret_cast<f32x4*>(lds_raw) + wave * (16 * LD);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e4 = tid + NTH * u;
-            if (e4 < P * P / 4) *reinterpret_cast<f32x4*>(&F[(e4 / (P / 4)) * LDF + 4 * (e4 % (P / 4))]) = sum[u];
+        for (int t = 0; t < T; ++t) {
+            const int u = t * 64 + lane;
+            strip[(u / (P / 4)) * LD + u % (P / 4)] = sum[t];
         }
-        __syncthreads();
-    }
-    // Register q of lane (h, n) of tile (ta, tb) is row ta*32 + (q/4)*8 + h*4 + q%4, column
-    // tb*32 + n (the accumulator layout of the 32 x 32 matrix instructions).
-    auto row_of = [&](int q) { return ta * 32 + (q >> 2) * 8 + h * 4 + (q & 3); };
-    const int col = tb * 32 + n;
-    float xr[16];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int row = row_of(q);
-        xr[q] = (row < P && col < P) ? F[row * LDF + col] : 0.f;
+        for (int t = 0; t < T; ++t) xr[t] = strip[c16 * LD + t * 4 + grp];
+        __syncthreads();                       // the strips become the images
     }
-    __syncthreads();                           // F is rewritten below
 
-    // tile -> three bf16 planes, transposed: dst[c][r] = v[r][c]; four consecutive rows of a
-    // lane's column are 8 bytes of a plane row
-    auto store_transposed = [&](unsigned short* dst, const float (&v)[16]) {
+    // Three bf16 parts of a strip of tiles as a B operand: lane (grp, c16) holds, for contraction step
+    // s, rows grp*4 .. +3 of tiles 2s and 2s+1.
+    auto split_strip = [&](const f32x4 (&v)[T], u32x4 (&out)[S][3]) {
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const TriWord a = split_trunc(v[4 * q4]), b = split_trunc(v[4 * q4 + 1]);
-            const TriWord c = split_trunc(v[4 * q4 + 2]), d = split_trunc(v[4 * q4 + 3]);
-            const int at = col * LDB + ta * 32 + q4 * 8 + h * 4;
-            *reinterpret_cast<u32x2*>(dst + at) = u32x2{pack_upper(a.hi, b.hi), pack_upper(c.hi, d.hi)};
-            *reinterpret_cast<u32x2*>(dst + PLANE + at) = u32x2{pack_upper(a.mid, b.mid), pack_upper(c.mid, d.mid)};
-            *reinterpret_cast<u32x2*>(dst + 2 * PLANE + at) = u32x2{pack_upper(a.lo, b.lo), pack_upper(c.lo, d.lo)};
+        for (int s = 0; s < S; ++s) {
+            const f32x4 lo = v[2 * s];
+            const f32x4 hi = 2 * s + 1 < T ? v[2 * s + 1 < T ? 2 * s + 1 : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
+            const Bf16x3Pair a = split_bf16x3(lo.x, lo.y), b = split_bf16x3(lo.z, lo.w);
+            const Bf16x3Pair c = split_bf16x3(hi.x, hi.y), d = split_bf16x3(hi.z, hi.w);
+            out[s][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+            out[s][1] = u32x4{a.mid, b.mid, c.mid, d.mid};
+            out[s][2] = u32x4{a.lo, b.lo, c.lo, d.lo};
         }
     };
-    // tile -> three bf16 planes, row-major: dst[r][c] = v[r][c]; neighbouring lanes hold
-    // neighbouring columns, so a lane pair exchanges half of its values and each lane writes
-    // (column pair) words of every other row
-    auto store_rowmajor = [&](unsigned short* dst, const float (&v)[16]) {
-        const bool odd = n & 1;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float e = v[2 * k], o = v[2 * k + 1];
-            const float got = dpp_f<kDppXor1>(odd ? e : o);
-            const TriWord lo = split_trunc(odd ? got : e), hi = split_trunc(odd ? o : got);
-            const int at = row_of(2 * k + (odd ? 1 : 0)) * LDB + tb * 32 + (n & ~1);
-            *reinterpret_cast<unsigned*>(dst + at) = pack_upper(lo.hi, hi.hi);
-            *reinterpret_cast<unsigned*>(dst + PLANE + at) = pack_upper(lo.mid, hi.mid);
-            *reinterpret_cast<unsigned*>(dst + 2 * PLANE + at) = pack_upper(lo.lo, hi.lo);
-        }
+    // The LDS image: per (strip, step, part) 1 KiB, tile 2s in the first half, tile 2s+1 in the
+    // second, 8 bytes per (grp, c16), the upper two groups with their columns exchanged by eights:
+    // 32 consecutive lanes of a write, of a straight and of a transposing read each cover all banks.
+    const int lane_at = (grp * 16 + (c16 ^ ((grp >> 1) * 8))) * 8;
+    auto unit = [&](unsigned char* img, int strip, int s, int pl) { return img + ((strip * S + s) * 3 + pl) * 1024; };
+    auto write_part = [&](unsigned char* img, int s, int pl, u32x4 w) {
+        unsigned char* u = unit(img, wave, s, pl) + lane_at;
+        *reinterpret_cast<u32x2*>(u) = u32x2{w.x, w.y};
+        if (2 * s + 1 < T) *reinterpret_cast<u32x2*>(u + 512) = u32x2{w.z, w.w};
     };
-    // tile (ta, tb) of A B^T for row-major planes A, B: sum over k of A[ta*32 + n][k] B[tb*32 + n][k],
-    // six partial products per 16 dims, smallest first, two accumulators alternating
-    auto abt_tile = [&](const unsigned short* A, const unsigned short* B, float (&out)[16]) {
-        constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
-        constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
-        f32x16 acc[2];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            acc[0][q] = 0.f;
-            acc[1][q] = 0.f;
-        }
-        const unsigned short* ar = A + (ta * 32 + n) * LDB + h * 8;
-        const unsigned short* br = B + (tb * 32 + n) * LDB + h * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS16; ++ks) {
-            u32x4 a[3], b[3];
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                a[pl] = *reinterpret_cast<const u32x4*>(ar + pl * PLANE + ks * 16);
-                b[pl] = *reinterpret_cast<const u32x4*>(br + pl * PLANE + ks * 16);
-            }
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
-                acc[ks & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[TA[t]]),
-                                                                      __builtin_bit_cast(bf16x8, b[TB[t]]),
-                                                                      acc[ks & 1], 0, 0, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < 16; ++q) out[q] = KS16 > 1 ? acc[0][q] + acc[1][q] : acc[0][q];
+    // A operand whose row m is column m of strip `strip` (contraction over rows of X)
+    auto read_cols = [&](unsigned char* img, int strip, int s, int pl) {
+        const unsigned char* u = unit(img, strip, s, pl) + lane_at;
+        const u32x2 a = *reinterpret_cast<const u32x2*>(u);
+        u32x2 b = {0u, 0u};
+        if (2 * s + 1 < T) b = *reinterpret_cast<const u32x2*>(u + 512);
+        return u32x4{a.x, a.y, b.x, b.y};
     };
-    // largest |v - I| over the valid part of the tile
-    auto deviation = [&](const float (&v)[16]) {
-        float dev = 0.f;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int row = row_of(q);
-            if (row < P && col < P) dev = fmaxf(dev, fabsf(v[q] - (row == col ? 1.f : 0.f)));
-        }
-        return dev;
+    // A operand whose row m is row t*16 + m of X (contraction over columns: lane (grp, .) takes
+    // columns grp*4 .. +3 of strips sa and sb).  ds_read_b64_tr_b16: of the 16 lanes of a row, lane
+    // i addresses four consecutive rows (4 (i & 3) ..) of column grp*4 + (i >> 2) and receives row i
+    // of the four columns.
+    const int tr_at = ((c16 & 3) * 16 + ((grp * 4 + (c16 >> 2)) ^ (((c16 & 3) >> 1) * 8))) * 8;
+    auto read_rows = [&](unsigned char* img, int t, int sa, int sb, int pl) {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+        const int at = (t & 1) * 512 + tr_at;
+        const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(unit(img, sa, t >> 1, pl) + at));
+        s16x4 b = {0, 0, 0, 0};
+        if (T > 1) b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(unit(img, sb, t >> 1, pl) + at));
+        const u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
+        return u32x4{ua.x, ua.y, ub.x, ub.y};
     };
-    // maximum over the workgroup of a per-thread value (ends with a barrier)
-    auto wg_max = [&](float v) {
+    auto mfma = [](u32x4 a, u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    };
+    // the six partial products, smallest first: (A part, B part); the last three of them alone
+    // are good for 2^-16 of the product
+    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
+    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    // Row tiles of G (and E) are kept in the order wave, wave + 1, ... (mod T): tile 0 is the one on
+    // the diagonal, and its operand is in this wavefront's registers.
+    int strip_of[T];
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-        __syncthreads();                       // red may still be read from the previous use
-        if (lane == 0) red[wave] = v;
-        __syncthreads();
-        float r = red[0];
+    for (int i = 0; i < T; ++i) strip_of[i] = (wave + i) & (T - 1);
+    f32x4 diag;                                // the diagonal tile of I
 #pragma unroll
-        for (int w = 1; w < T * T; ++w) r = fmaxf(r, red[w]);
-        return r;
+    for (int r = 0; r < 4; ++r) diag[r] = grp * 4 + r == c16 ? 1.f : 0.f;
+    // The A operands of X E, requested in the order in which the products use them, all of them
+    // before the first product (the compiler would otherwise keep only a few in flight, and with
+    // one wavefront per SIMD nothing else covers the wait).
+    auto load_rows = [&](unsigned char* img, u32x4 (&a)[S][3][T]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int pl = k == 0 ? 2 : k - 1;
+                    a[s][pl][t] = read_rows(img, t, strip_of[2 * s], strip_of[T > 1 ? 2 * s + 1 : 0], pl);
+                }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // acc[t] = X E for row tile t from the parts of E: the partial products Q0 .. 5
+    auto times = [&](const u32x4 (&a)[S][3][T], const u32x4 (&eq)[S][3], auto q0, f32x4 (&acc)[T]) {
+        constexpr int Q0 = decltype(q0)::value;
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = zero4;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int q = Q0; q < 6; ++q)
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t] = mfma(a[s][TA[q]][t], eq[s][TB[q]], acc[t]);
+    };
+    // one value per wavefront -> the sum (maximum) over the workgroup; slot: 0 .. 3, a slot is
+    // reused two barriers later at the earliest
+    auto publish = [&](int slot, float v) {
+        if (lane == 0) red[slot * 4 + wave] = v;
     };
 
-    // G0 = X^T X of the unscaled input (X^T X = Xt Xt^T: both operands are rows of Xt), in fp32
-    // in F for the scale estimate.
-    store_transposed(Xtp, xr);
-    __syncthreads();
-    float gt[16];
-    abt_tile(Xtp, Xtp, gt);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) F[row_of(q) * LDF + col] = gt[q];
-    __syncthreads();
-
-    // Scale so that the largest singular value is about one.  sigma_max^2 is the largest
-    // eigenvalue of G = X^T X.  The iteration sends every singular value in (0, sqrt(3)) to +1,
-    // one in (sqrt(3), sqrt(5)) to -1 (an orthogonal matrix that is NOT U V^T, and which the
-    // deviation test cannot tell apart), so the scale must be a guaranteed bound: the largest
-    // absolute row sum of G is at least its largest eigenvalue, and dividing G by that sum / 2.9
-    // keeps every scaled sigma^2 at or below 2.9.  That bound alone is often two to three times
-    // too large, which costs iterations; a Rayleigh quotient after a few power-iteration steps
-    // from the vector of absolute row sums is a lower estimate that is usually tight, so the
-    // scale is the larger of (1.08 x that quotient) and (row-sum bound / 2.9).
-    if (tid < P) {
-        float rs = 0.f;
-        for (int b = 0; b < P; ++b) rs += fabsf(F[tid * LDF + b]);
-        vec[tid] = rs;
-    }
-    __syncthreads();
-    float rsmax = 0.f;                         // every thread, same order: same value
-    for (int a = 0; a < P; ++a) rsmax = fmaxf(rsmax, vec[a]);
-    float s2 = 0.f;
-    for (int round = 0; round < 4; ++round) {
-        if (tid < P) {
-            float w = 0.f;
-            for (int b = 0; b < P; ++b) w += F[tid * LDF + b] * vec[b];
-            wec[tid] = w;
-        }
-        __syncthreads();
-        float vv = 0.f, vw = 0.f, wmax = 0.f;  // every thread, same order: same values
-        for (int a = 0; a < P; ++a) {
-            vv += vec[a] * vec[a];
-            vw += vec[a] * wec[a];
-            wmax = fmaxf(wmax, fabsf(wec[a]));
-        }
-        s2 = 1.08f * vw / vv;                  // NaN for a zero matrix: caught below
-        __syncthreads();
-        if (tid < P) vec[tid] = wec[tid] / wmax;
-        __syncthreads();
-    }
-    const bool rq_ok = s2 > 0.f && s2 < 3e38f; // zero, infinite or NaN input: not for this iteration
-    s2 = fmaxf(s2, rsmax * (1.f / 2.9f));
-    const bool ok = rq_ok && s2 < 3e38f;
-    const float inv = ok ? __builtin_amdgcn_rsqf(s2) : 0.f;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        xr[q] *= inv;
-        gt[q] *= inv * inv;
-    }
-    store_rowmajor(Xp, xr);
-    store_transposed(Xtp, xr);                 // (every wavefront has finished reading the unscaled Xt)
-    store_transposed(Gp, gt);
-    float dev = deviation(gt);
+    unsigned char* img = lds_raw;              // the image of the current X; the other one is free
+    unsigned char* other = lds_raw + ns_image_bytes<P>();
+    u32x4 xq[S][3];
     int it = 0;
     bool converged = false;
-    while (ok) {
-        // d = max |X^T X - I|; below 2e-4 the step that follows is the last (quadratic
-        // convergence leaves about d^2 behind).  The barriers inside also publish the planes.
-        const float d = wg_max(dev);
-        const bool last = d < 2e-4f;
-        if (!(d < 4.f)) break;                 // NaN or diverging: leave it to the Jacobi SVD
-
-        // X <- 1.5 X - 0.5 X G; X G = X (G^T)^T: rows of X against rows of the stored G^T
-        float xg[16];
-        abt_tile(Xp, Gp, xg);
+    while (true) {
+        split_strip(xr, xq);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) xr[q] = 1.5f * xr[q] - 0.5f * xg[q];
-        __syncthreads();                       // every wavefront has read the old planes
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) write_part(img, s, pl, xq[s][pl]);
+        __syncthreads();
+
+        // this wavefront's columns of G = X^T X; the diagonal tile needs no operand from LDS and
+        // covers the wait for the others
+        f32x4 ge[T];
+        {
+            u32x4 a[S][3][T];
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                    for (int i = 1; i < T; ++i) {
+                        const int pl = k == 0 ? 2 : k - 1;     // in the order in which the products use them
+                        a[s][pl][i] = read_cols(img, strip_of[i], s, pl);
+                    }
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 g0[S];
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int s = 0; s < S; ++s) g0[s] = mfma(xq[s][TA[q]], xq[s][TB[q]], q == 0 ? zero4 : g0[s]);
+#pragma unroll
+            for (int i = 1; i < T; ++i) ge[i] = zero4;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int i = 1; i < T; ++i) ge[i] = mfma(a[s][TA[q]][i], xq[s][TB[q]], ge[i]);
+            ge[0] = S > 1 ? g0[0] + g0[S - 1] : g0[0];
+        }
+
+        float alpha = it < 4 ? kAlpha[it] : 1.f;           // X is scaled by this before the step
+        bool last = false;
+        if (it == 0) {
+            // The scale of the input.  The iteration sends every singular value in (0, sqrt(3)) to
+            // +1, one in (sqrt(3), sqrt(5)) to -1 (an orthogonal matrix that is NOT U V^T, and
+            // which no later test can tell apart), so the scale must be a guaranteed bound: the
+            // largest absolute row sum of G is at least its largest eigenvalue sigma_max^2, and
+            // alpha^2 <= 2.9 / that keeps every scaled sigma^2 below 2.9.  Where the bound is tight, the
+            // aim is sigma_max = 1 times the scaling for l, with the largest norm of a column of
+            // G (a lower bound of its largest eigenvalue) as the estimate.
+            float rs = 0.f, r2 = 0.f;
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    rs += fabsf(ge[i][r]);
+                    r2 = fmaf(ge[i][r], ge[i][r], r2);
+                }
+            publish(0, row_max_nan(sum_groups(rs)));
+            publish(1, row_max_nan(sum_groups(r2)));
+            __syncthreads();
+            float rsmax = red[0], r2max = red[4];
+#pragma unroll
+            for (int w = 1; w < T; ++w) {      // as bits: a NaN wins
+                rsmax = __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, rsmax), __builtin_bit_cast(unsigned, red[w])));
+                r2max = __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, r2max), __builtin_bit_cast(unsigned, red[4 + w])));
+            }
+            // zero, infinite, NaN or overflowing input: not for this iteration
+            if (!(rsmax > 1e-37f && rsmax < 3e37f)) break;
+            float b2 = 2.9f * __builtin_amdgcn_rcpf(rsmax);
+            if (r2max > 1e-37f && r2max < 3e37f)
+                b2 = fminf(b2, kAlpha[0] * kAlpha[0] / 1.04f * __builtin_amdgcn_rsqf(r2max));
+            alpha = __builtin_amdgcn_sqrtf(b2);
+        } else {
+            float fr = 0.f;
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float e = i == 0 ? diag[r] - ge[i][r] : ge[i][r];
+                    fr = fmaf(e, e, fr);
+                }
+            publish(2 + (it & 1), sum_groups(group_sum<16>(fr)));
+        }
+        // E = I - alpha^2 G, then X <- alpha (X + X E / 2)
+        auto make_e = [&](float a2) {
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) ge[i][r] = i == 0 ? diag[r] - a2 * ge[i][r] : -a2 * ge[i][r];
+        };
+        u32x4 rows[S][3][T], eq[S][3];
+        load_rows(img, rows);
+        f32x4 g0[T];
+#pragma unroll
+        for (int i = 0; i < T; ++i) g0[i] = ge[i];
+        make_e(alpha * alpha);
+        split_strip(ge, eq);
+        if (it > 0) {                          // has this been the last but one step?  (the split hides the wait)
+            __syncthreads();
+            float fr = red[(2 + (it & 1)) * 4];
+#pragma unroll
+            for (int w = 1; w < T; ++w) fr += red[(2 + (it & 1)) * 4 + w];
+            if (!(fr < 2.f * P)) break;        // NaN or diverging: leave it to the Jacobi SVD
+            last = fr < 1e-4f;                 // |E|_F < 1e-2, a bound on the spectral norm of E
+            if (!last && it >= g.max_iters) break;
+        }
+        f32x4 acc[T];
+        if (last) {                            // uniform
+            alpha = 1.f;
+#pragma unroll
+            for (int i = 0; i < T; ++i) ge[i] = g0[i];
+            make_e(1.f);
+            // E^2 from the leading parts alone: 2^-8 of something below 1e-4
+            split_strip(ge, eq);
+#pragma unroll
+            for (int s = 0; s < S; ++s) write_part(other, s, 0, eq[s][0]);
+            __syncthreads();
+            f32x4 e2[T];
+#pragma unroll
+            for (int i = 0; i < T; ++i) e2[i] = zero4;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    // E is symmetric: its rows are the strips, each with its tiles in its own order
+                    const int pa = (strip_of[2 * s] - strip_of[i]) & (T - 1), pb = (pa + 1) & (T - 1);
+                    const u32x2 a = *reinterpret_cast<const u32x2*>(unit(other, strip_of[i], pa >> 1, 0) + (pa & 1) * 512 + lane_at);
+                    u32x2 b = {0u, 0u};
+                    if (T > 1)
+                        b = *reinterpret_cast<const u32x2*>(unit(other, strip_of[i], pb >> 1, 0) + (pb & 1) * 512 + lane_at);
+                    e2[i] = mfma(u32x4{a.x, a.y, b.x, b.y}, eq[s][0], e2[i]);
+                }
+#pragma unroll
+            for (int i = 0; i < T; ++i) ge[i] += 0.75f * e2[i];        // 2 (E / 2 + 3/8 E^2)
+            split_strip(ge, eq);
+            times(rows, eq, std::integral_constant<int, 3>{}, acc);
+        } else {
+            times(rows, eq, std::integral_constant<int, 0>{}, acc);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) xr[t] = alpha * xr[t] + (0.5f * alpha) * acc[t];
         ++it;
         if (last) {
             converged = true;
             break;
         }
-        if (it >= g.max_iters) break;
-        store_rowmajor(Xp, xr);
-        store_transposed(Xtp, xr);
-        __syncthreads();
-        abt_tile(Xtp, Xtp, gt);
-        store_transposed(Gp, gt);              // G was last read before the barrier above
-        dev = deviation(gt);
+        unsigned char* const done = img;       // (its last readers are behind the barrier after the next writes)
+        img = other;
+        other = done;
     }
 
     if (!converged) {                          // uniform: the Jacobi SVD of this block, right here
@@ -371,18 +472,14 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         if (g.iters_out != nullptr) g.iters_out[j] = -it;   // negative: Newton-Schulz steps, not sweeps
     }
 
-    // D[j][k][:] = row k of X, through the fp32 scratch so that a thread holds four consecutive
-    // dims of a row; the same values in the coding kernels' operand orders
+    // D[j][k][:] = column k of X; the same values in the coding kernels' operand orders
+    f32x4* Dj = reinterpret_cast<f32x4*>(g.D + (int64_t)j * P * P);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) F[row_of(q) * LDF + col] = xr[q];
-    __syncthreads();
-    float* Dj = g.D + (int64_t)j * P * P;
-    for (int u = tid; u < P * P / 4; u += NTH) {
-        const int k = u / (P / 4), d4 = u % (P / 4);
-        const f32x4 row = *reinterpret_cast<const f32x4*>(&F[k * LDF + 4 * d4]);
-        *reinterpret_cast<f32x4*>(&Dj[k * P + 4 * d4]) = row;
-        if (g.dsw != nullptr) store_operand_f32<P>(g.dsw, j * P + k, d4, row);
-        if (g.dsb != nullptr) store_operand_parts<P>(g.dsb, g.dsb_kind, j * P + k, d4, row);
+    for (int t = 0; t < T; ++t) {
+        const int d4 = t * 4 + grp;
+        Dj[col * (P / 4) + d4] = xr[t];
+        if (g.dsw != nullptr) store_operand_f32<P>(g.dsw, j * P + col, d4, xr[t]);
+        if (g.dsb != nullptr) store_operand_parts<P>(g.dsb, g.dsb_kind, j * P + col, d4, xr[t]);
     }
 }
 
