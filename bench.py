@@ -30,19 +30,18 @@ PEAK_HBM_GBS = 8000.0
 SPLIT_PRODUCTS = 6
 
 
-def roofline_kernel_name(p: int, arith: str) -> str:
-    return "energy_kernel" if arith == "f32" else "energy_split_kernel"
+def roofline_kernel_name(p: int, arith: str, s0: int = 8) -> str:
+    """The library's rule: the screened choice for at most p / 2 coefficients, p = 256 only in f16x2."""
+    if 2 * s0 <= p and (p <= 64 or arith == "f16x2"):
+        return "energy_screen_kernel"
+    if arith == "f32":
+        return "energy_kernel"
+    return "energy_split_wide_kernel" if p > 64 else "energy_split_kernel"
 
 
 def arith_value(sbo, arith: str) -> int:
     return {"f32": sbo.SBO_ARITH_F32, "bf16x3": sbo.SBO_ARITH_BF16X3, "screen": sbo.SBO_ARITH_BF16X3_SCREEN,
             "f16x2": sbo.SBO_ARITH_F16X2}[arith]
-
-
-def screening_applies(p: int, m: int) -> bool:
-    """SBO_ARITH_BF16X3_SCREEN screens only for p <= 64 and when the signals fill the chip (the
-    library's rule: at least 192 workgroups of 512 signals); otherwise it is SBO_ARITH_BF16X3."""
-    return p <= 64 and (m + 511) // 512 >= 192
 
 
 def measured_traffic_bytes(workload: str, arith: str):
@@ -132,46 +131,39 @@ def roofline_entry(p, K, m, energy_ms, arith, workload, s0=8):
     """The energy kernel against the matrix roof of the instruction it runs on."""
     flops = 2.0 * K * p * p * m                 # algorithmic: projection onto all K orthobases
     achieved = flops / (energy_ms * 1e-3) / 1e12
-    kernel = roofline_kernel_name(p, arith)
-    if arith == "screen" and screening_applies(p, m):
-        # two launches: three partial products for every signal, then six for the undecided ones
-        peak = PEAK_MFMA_BF16_TFLOPS / 3
-        extra = {"kernel": "energy_split_kernel MODE 1 + MODE 2 (fused Q^T y on the bf16 matrix cores: the three "
-                           "largest bf16 partial products for every signal + top-s0 energy + block argmax, then "
-                           "all six products for the signals that pass leaves undecided)",
-                 "peak_note": "2500 TFLOP/s dense bf16 MFMA / 3 partial products per screened product; the time "
-                              "is that of both launches",
-                 "peak_bf16_tflops": PEAK_MFMA_BF16_TFLOPS,
-                 "vs_six_product_roof": achieved / (PEAK_MFMA_BF16_TFLOPS / SPLIT_PRODUCTS),
-                 "vs_fp32_mfma_peak": achieved / PEAK_MFMA_F32_TFLOPS}
-    elif arith == "f16x2":
-        peak = PEAK_MFMA_BF16_TFLOPS / 3          # fp16 and bf16 MFMA share the 2500 TFLOP/s peak
-        # the selection networks, per tile of 32 signals and block (p = 64, sort width 8): 4 sorts of 8 by
-        # three-input insertion networks (33 instructions each), 3 half-cleaner + bitonic merges (32
-        # each), the lane-pair fold (8 maxima) and 8 squares = 244 vector instructions (the kernel's ISA
-        # agrees: 220 min / max / median per copy of the network + the squares and swaps); one
+    kernel = roofline_kernel_name(p, arith, s0)
+    if kernel == "energy_screen_kernel":
+        # one fp16 product per product for every signal and block, then the context's arithmetic for the
+        # blocks the screening's error bound leaves in (that share of the work depends on the data)
+        peak = PEAK_MFMA_BF16_TFLOPS              # fp16 and bf16 MFMA share the 2500 TFLOP/s peak
+        # vector instructions of the main loop per 64 signals and block (p = 64, s0 = 8, the kernel's ISA):
+        # packed conversion, sorting networks and merges on two signals per instruction, about 300; one
         # lane-operation per lane and instruction, against 256 CUs x 64 lanes x 2.4 GHz
-        sel_ops = 244.0 * 64.0 * (K * m / 32.0)
+        sel_ops = 300.0 * 64.0 * (K * m / 64.0)
         sel_peak = 256 * 64 * 2.4e9
-        extra = {"kernel": "energy_split_kernel MODE 3 (fused Q^T y on the fp16 matrix cores, fp32 operands scaled "
-                           "and written as hi + lo in fp16, three partial products + top-s0 energy + block argmax)",
-                 "peak_note": "2500 TFLOP/s dense fp16 MFMA / 3 partial products per product; the kernel's time is "
-                              "0.70 x (matrix part + selection networks on the vector ALU)",
-                 "executed_f16_tflops": achieved * 3, "peak_f16_tflops": PEAK_MFMA_BF16_TFLOPS,
+        extra = {"kernel": "energy_screen_kernel (screening: Q^T y once on the fp16 matrix cores + packed top-s0 energy "
+                           "of every block; then the blocks within the error bound of the best in " + arith + ")",
+                 "peak_note": "2500 TFLOP/s dense fp16 MFMA, one product per product",
+                 "executed_f16_tflops": achieved, "peak_f16_tflops": PEAK_MFMA_BF16_TFLOPS,
                  "vs_six_product_roof": achieved / (PEAK_MFMA_BF16_TFLOPS / SPLIT_PRODUCTS),
                  "vs_fp32_mfma_peak": achieved / PEAK_MFMA_F32_TFLOPS,
                  "selection_alu": {"lane_ops_per_launch": sel_ops,
                                    "achieved_Tops": sel_ops / (energy_ms * 1e-3) / 1e12,
                                    "peak_Tops": sel_peak / 1e12,
                                    "frac": sel_ops / (energy_ms * 1e-3) / sel_peak}}
-        if p > 64:
-            extra["kernel"] = ("energy_split_wide_kernel (the same on the fp16 matrix cores for p = 256: the two "
-                               "wavefronts of a SIMD each multiply half of the dims)")
-        if p != 64 or not 4 < s0 <= 8:         # the instruction count above is that of p = 64, sort width 8
+        if p != 64 or s0 != 8:                 # the instruction count above is that of p = 64, s0 = 8
             del extra["selection_alu"]
-    elif kernel == "energy_split_kernel":
+    elif arith == "f16x2":
+        peak = PEAK_MFMA_BF16_TFLOPS / 3
+        extra = {"kernel": kernel + " (fused Q^T y on the fp16 matrix cores, fp32 operands scaled and written as "
+                           "hi + lo in fp16, three partial products + top-s0 energy + block argmax)",
+                 "peak_note": "2500 TFLOP/s dense fp16 MFMA / 3 partial products per product",
+                 "executed_f16_tflops": achieved * 3, "peak_f16_tflops": PEAK_MFMA_BF16_TFLOPS,
+                 "vs_six_product_roof": achieved / (PEAK_MFMA_BF16_TFLOPS / SPLIT_PRODUCTS),
+                 "vs_fp32_mfma_peak": achieved / PEAK_MFMA_F32_TFLOPS}
+    elif kernel != "energy_kernel":
         peak = PEAK_MFMA_BF16_TFLOPS / SPLIT_PRODUCTS
-        extra = {"kernel": "energy_split_kernel (fused Q^T y on the bf16 matrix cores, fp32 operands as exact "
+        extra = {"kernel": kernel + " (fused Q^T y on the bf16 matrix cores, fp32 operands as exact "
                            "sums of three bf16, six partial products + top-s0 energy + block argmax)",
                  "peak_note": "2500 TFLOP/s dense bf16 MFMA / 6 partial products per fp32-accurate product",
                  "executed_bf16_tflops": achieved * SPLIT_PRODUCTS, "peak_bf16_tflops": PEAK_MFMA_BF16_TFLOPS,
@@ -183,7 +175,7 @@ def roofline_entry(p, K, m, energy_ms, arith, workload, s0=8):
            "traffic": measured_traffic_bytes(workload, arith), **extra}
     sel = extra.get("selection_alu")
     if sel is not None and sel["frac"] > out["frac"]:
-        # The roofline of a kernel is the highest of its floors.  With three fp16 products the
+        # The roofline of a kernel is the highest of its floors.  With one fp16 product the
         # vector-ALU floor (selection networks) lies above the matrix floor, so that is the roof
         # the kernel is measured against; the matrix side stays in "mfma".
         out = {"bound": "alu", "achieved": sel["achieved_Tops"], "peak": sel["peak_Tops"],
@@ -353,7 +345,7 @@ def main() -> int:
     # comparison: its energy kernel against the fp32 MFMA peak.  Outside the timed region.
     other = []
     for alt in ("f32", "bf16x3", "screen", "f16x2"):
-        if alt == args.arith or (alt == "screen" and not screening_applies(p, m)):
+        if alt in (args.arith, "screen"):         # (screen: as bf16x3)
             continue
         sbo.sbo_set_option(ctx, sbo.SBO_OPT_CODING_ARITH, arith_value(sbo, alt))
         sbo.sbo_set_timing(ctx, 2)
@@ -525,8 +517,6 @@ def main() -> int:
         if "executed_bf16_tflops" in mf or "executed_f16_tflops" in mf:
             ex = mf.get("executed_bf16_tflops", mf.get("executed_f16_tflops"))
             mf["frac_of_measured_random_operand_rate"] = ex / measured["mfma_bf16_tflops_random_operands"]
-        elif out["roofline"]["kernel"].startswith("energy_split"):
-            pass
         else:
             out["roofline"]["frac_of_measured_peak"] = out["roofline"]["achieved"] / measured["mfma_f32_tflops"]
     if next_rows is not None:

@@ -231,20 +231,15 @@ enum {
                               accumulation: per-term error 3 * 2^-22 |a||b|, below the p * 2^-24 sum |a||b|
                               an fp32 dot product of p terms guarantees; half the matrix work of
                               SBO_ARITH_BF16X3.  Supports and coefficients still come from the six bf16
-                              products.  Dictionary entries
+                              products.  (For s0 <= p/2 the choice is screened, under every arithmetic: one
+                              fp16 product and its guaranteed error bound rule out the blocks that cannot
+                              win, only the others are computed as described here; the chosen blocks are
+                              the same.  p = 256: under this arithmetic only.)  Dictionary entries
                               must be below 8 in magnitude (orthonormal atoms: at most 1); a signal whose
                               largest magnitude is below 2^-63 is coded as a zero signal (its energies
                               underflow in fp32 under any arithmetic). */
-    SBO_ARITH_BF16X3_SCREEN = 2  /* as SBO_ARITH_BF16X3, but the choice of the orthobase (eq. (4))
-                              first runs with the three largest partial products only, for all signals; that
-                              decides every signal whose two best kept energies are further apart than twice
-                              the error bound of the shortened product, 2 (2 sqrt(s0) c + s0 c^2) ||y||^2 with
-                              c = 3.01 * 2^-16 + 2e-6, and only the remaining signals get the six products
-                              over all orthobases.  The chosen orthobases are those of SBO_ARITH_BF16X3;
-                              supports and coefficients always come from the six products.  Used for
-                              p <= 64 when the signals fill the chip; otherwise as SBO_ARITH_BF16X3.
-                              Pays when the orthobases are well separated (few undecided signals); with
-                              near-random orthobases it is about as fast as SBO_ARITH_BF16X3. */
+    SBO_ARITH_BF16X3_SCREEN = 2  /* as SBO_ARITH_BF16X3 (kept for callers that name it: the choice is
+                              screened under every arithmetic, see SBO_ARITH_F16X2) */
 };
 
 /* Set an option for every later call on this context (Algorithm 1 steps 6-7 leave the SVD

@@ -16,7 +16,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libsbo.so")
 
-SOURCES = ["sbo_api.hip", "code_energy.hip", "code_select.hip", "select_accum.hip", "group.hip", "accumulate.hip",
+SOURCES = ["sbo_api.hip", "code_energy.hip", "code_screen_16.hip", "code_screen_32.hip", "code_screen_64.hip",
+           "code_screen_256.hip", "code_select.hip", "select_accum.hip", "group.hip", "accumulate.hip",
            "polar_jacobi.hip", "polar_ns.hip", "polar_wide.hip", "polar_wide_ns.hip", "reduce.hip", "worst.hip"]
 # bench.py's achievable-peak probes: a library of their own, not part of libsbo
 PROBE_SOURCE = "bench_probe.hip"
@@ -26,12 +27,13 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
 
-# Per-source additions.  The energy kernel reads its MFMA accumulators with ordinary
+# Per-source additions.  The block-choice kernels read their MFMA accumulators with ordinary
 # vector instructions right after each stage; keeping them in architectural VGPRs saves
-# one accumulator-read instruction per value.  Its compare-exchange networks are built
+# one accumulator-read instruction per value.  Their compare-exchange networks are built
 # from min/max, which need no NaN-quieting pre-pass when NaNs are not honoured (signals
 # or atoms holding NaN give unspecified block choices instead of propagating NaN).
-EXTRA = {"code_energy.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"] for f in SOURCES
+         if f.startswith(("code_energy", "code_screen"))}
 
 
 def hipcc() -> str:

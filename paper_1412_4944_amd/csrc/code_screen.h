@@ -1,0 +1,698 @@
+// Sparse-coding stage 1, the block choice (Section 2, eq. (4); Section 3.1), screened: for every
+// signal the orthobase whose s0 largest coefficients hold the most energy.
+//
+// What bounds the choice is not memory (Y is read once, 256 bytes a signal at p = 64, against
+// 2 K p^2 flop) but the matrix cores AND the vector ALU: with full-precision coefficients, K = 32 and
+// p = 64 take three fp16 products per product (82 us of matrix time for 262144 signals) and 250
+// vector instructions per 32 signals and block for the selection networks (104 us), and the two
+// overlap badly.  Almost all of that precision is spent on blocks that are far from winning.  So:
+//
+//   1. Screening.  One fp16 product per product (the leading fp16 part of the signal, scaled, times
+//      the leading part of the dictionary) gives every coefficient to about 2^-11; the magnitudes
+//      are rounded to fp16, and the selection networks run on two signals per instruction
+//      (energy_networks.h).  The kept energy of every (signal, block) goes to LDS, 16 bits each.
+//   2. Decision.  The s0 largest magnitudes' norm of a block is off by at most
+//          eps = sqrt(s0) (max |q| |y - hi(y)| + |y| max |q - hi(q)| + accumulation)
+//      (Cauchy-Schwarz per coefficient; the two remainders' norms are computed, not bounded) and by
+//      the rounding down of the magnitudes, less than 2^-10 of itself.  A block that is further than that
+//      below the best one cannot win.  A signal with one block left is decided.
+//   3. Resolution.  For the others, the blocks that are left are computed in the context's
+//      arithmetic (SBO_ARITH_*), operand by operand and sum by sum what the kernels in
+//      code_energy.hip do, and compared: the largest energy wins, the lower block on a tie.
+// The chosen blocks are therefore those of the full computation, for every dictionary (nothing is
+// assumed about D; the bound is just wide if its atoms are long).
+//
+// Two shapes of the same work:
+//   energy_screen_kernel<..., false>: a workgroup takes 512 signals, a wavefront 64 of them and all
+//     blocks; dictionary stages go through LDS, double-buffered.
+//   energy_screen_kernel<..., true>: a workgroup takes 64 signals, and its wavefronts share out the
+//     blocks and read their dictionary rows straight from L2: eight times the workgroups, for
+//     signal sets that would not fill the chip otherwise, and for K beyond the LDS table of the other.
+// Measured (MI355X, f16x2 results): K = 32, p = 64, s0 = 8, 262144 signals 229 -> 126 us (155 on a near-random
+// dictionary, where a third of the signals has candidates to resolve), of which 103 k cycles main
+// loop, 13 k loading the signals, 5 k decision; K = 128, s0 = 6, 2^20 signals 3283 -> 1700 us; p = 256, K = 16,
+// 131072 signals 757 -> 288 us; K = 16, 16384 signals (the second shape) 28 -> 9 us.  "Before" is
+// the full-precision projection of every block.
+#pragma once
+
+#include "sbo_internal.h"
+#include "device_utils.h"
+#include "energy_networks.h"
+#include "screen_args.h"
+
+namespace sbo {
+
+namespace {
+
+constexpr int kScrWaves = 8;
+
+// Maximum over the wavefront, in all lanes.
+__device__ __forceinline__ float wave_max(float x) {
+    x = row16_max(x);
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a0 = r[0], a1 = r[1];
+    const float y = fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1));
+    const SwapPair q = swap32(y, y);
+    return fmaxf(q.first, q.second);
+}
+
+template <int P>
+struct ScrGeom {
+    static constexpr bool WIDE = P > 64;
+    static constexpr int KS16 = P / 16;                     // contraction steps of 16 dims
+    static constexpr int NB = WIDE ? 1 : 64 / P;            // blocks per 64-row stage (p <= 64)
+    static constexpr int SPB = WIDE ? P / 32 : 1;           // stages of 32 rows per block (p = 256)
+    static constexpr int MTS = WIDE ? 1 : 2;                // 32-row tiles per stage
+    static constexpr int STAGE_U = MTS * KS16 * 64;         // 16-byte units of a stage (leading parts only)
+    static constexpr int NV = WIDE ? 16 : P / 2;            // coefficients per lane, block and stage
+};
+
+// Kept energy of signal i (-1: none) in block j in the exact arithmetic, up to the signal's scale.
+template <int P, int S, int SX, int ARITH>
+__device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
+    constexpr int KS16 = P / 16, QN = P / 8;
+    constexpr int NPL = ARITH == 3 ? 2 : 3;
+    constexpr int NRT = P >= 32 ? P / 32 : 1;               // 32-row tiles of a block
+    constexpr int NV = P <= 64 ? P / 2 : 16;
+    const int h = lane >> 5;
+    const int tile0 = P >= 32 ? j * NRT : j >> 1;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const float* yrow = g.Y + (i < 0 ? 0 : i) * P;
+    auto load4 = [&](int d) {
+        return i >= 0 ? *reinterpret_cast<const f32x4*>(yrow + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+
+    if constexpr (ARITH == 0) {
+        static_assert(P <= 64, "p = 256 in fp32 is not screened");
+        f32x4 yb[QN];
+#pragma unroll
+        for (int q = 0; q < QN; ++q) yb[q] = load4(h * (P / 2) + 4 * q);
+        const f32x4* D = reinterpret_cast<const f32x4*>(g.Dx) + (int64_t)tile0 * (QN * 64) + lane;
+        f32x16 acc[NRT];
+#pragma unroll
+        for (int q = 0; q < QN; ++q) {
+            f32x4 a[NRT];
+#pragma unroll
+            for (int mt = 0; mt < NRT; ++mt) a[mt] = D[(mt * QN + q) * 64];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int mt = 0; mt < NRT; ++mt)
+                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mt][kk], yb[q][kk],
+                                                                   (q == 0 && kk == 0) ? zero : acc[mt], 0, 0, 0);
+        }
+        float x[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            x[v] = fabsf(P == 16 ? ((j & 1) ? acc[0][(8 + v) & 15] : acc[0][v & 15]) : acc[(v >> 4) % NRT][v & 15]);
+        return pair_top_energy<NV, S, SX>(x, g.s0, h != 0);
+    } else {
+        float scale = 1.f;
+        if constexpr (ARITH == 3) {
+            float vmax = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const f32x4 v = load4(ks * 16 + h * 8 + 4 * e);
+                    vmax = fmaxf(fmaxf(fmaxf(vmax, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
+                }
+            vmax = fmaxf(vmax, other_half(vmax));
+            scale = f16_signal_scale(vmax);
+        }
+        u32x4 yq[KS16][NPL];
+#pragma unroll
+        for (int ks = 0; ks < KS16; ++ks) {
+            const f32x4 v0 = load4(ks * 16 + h * 8), v1 = load4(ks * 16 + h * 8 + 4);
+            if constexpr (ARITH == 3) {
+                const F16x2Pair a = split_f16x2(v0.x * scale, v0.y * scale), b = split_f16x2(v0.z * scale, v0.w * scale);
+                const F16x2Pair c = split_f16x2(v1.x * scale, v1.y * scale), d = split_f16x2(v1.z * scale, v1.w * scale);
+                yq[ks][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+                yq[ks][1] = u32x4{a.lo, b.lo, c.lo, d.lo};
+            } else {
+                const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
+                const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
+                yq[ks][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+                yq[ks][1] = u32x4{a.mid, b.mid, c.mid, d.mid};
+                yq[ks][NPL - 1] = u32x4{a.lo, b.lo, c.lo, d.lo};
+            }
+        }
+        // the partial products, smallest first: (A part, B part)
+        constexpr bool F16 = ARITH == 3;
+        constexpr int TA[6] = {F16 ? 0 : 2, F16 ? 1 : 0, F16 ? 0 : 1, 1, 0, 0};
+        constexpr int TB[6] = {F16 ? 1 : 0, F16 ? 0 : 2, F16 ? 0 : 1, 0, 1, 0};
+        constexpr int T1 = F16 ? 3 : 6;
+        const u32x4* D = reinterpret_cast<const u32x4*>(g.Dx) + (int64_t)tile0 * (KS16 * NPL * 64) + lane;
+        auto step = [&](const u32x4 (&a)[NPL], int ks, int t, f32x16 c) {
+            if constexpr (F16)
+                return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[TA[t]]),
+                                                              __builtin_bit_cast(f16x8, yq[ks][TB[t]]), c, 0, 0, 0);
+            else
+                return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[TA[t]]),
+                                                               __builtin_bit_cast(bf16x8, yq[ks][TB[t]]), c, 0, 0, 0);
+        };
+        if constexpr (P <= 64) {
+            f32x16 acc[NRT];
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks) {
+                u32x4 a[NRT][NPL];
+#pragma unroll
+                for (int mt = 0; mt < NRT; ++mt)
+#pragma unroll
+                    for (int pl = 0; pl < NPL; ++pl) a[mt][pl] = D[((mt * KS16 + ks) * NPL + pl) * 64];
+#pragma unroll
+                for (int t = 0; t < T1; ++t)
+#pragma unroll
+                    for (int mt = 0; mt < NRT; ++mt) acc[mt] = step(a[mt], ks, t, (ks == 0 && t == 0) ? zero : acc[mt]);
+            }
+            float x[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                x[v] = fabsf(P == 16 ? ((j & 1) ? acc[0][(8 + v) & 15] : acc[0][v & 15]) : acc[(v >> 4) % NRT][v & 15]);
+            return pair_top_energy<NV, S, SX>(x, g.s0, h != 0);
+        } else {
+            // the two halves of the contraction are summed separately, as the two wavefronts of
+            // energy_split_wide_kernel do
+            float run[S];
+#pragma unroll 1
+            for (int rt = 0; rt < NRT; ++rt) {
+                f32x16 half[2];
+#pragma unroll
+                for (int ks = 0; ks < KS16; ++ks) {
+                    u32x4 a[NPL];
+#pragma unroll
+                    for (int pl = 0; pl < NPL; ++pl) a[pl] = D[((rt * KS16 + ks) * NPL + pl) * 64];
+                    constexpr int KH = KS16 / 2;
+#pragma unroll
+                    for (int t = 0; t < T1; ++t)
+                        half[ks / KH] = step(a, ks, t, (ks % KH == 0 && t == 0) ? zero : half[ks / KH]);
+                }
+                float x[16], top[S];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) x[v] = fabsf(half[0][v] + half[1][v]);
+                top_sorted<16, S>(x, top);
+                if (rt == 0) {
+#pragma unroll
+                    for (int t = 0; t < S; ++t) run[t] = top[t];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < S; ++t) run[t] = fmaxf(run[t], top[S - 1 - t]);
+                    bitonic_merge_desc<S>(run);
+                }
+            }
+            return pair_list_energy<S, SX>(run, g.s0, h != 0);
+        }
+    }
+}
+
+// LDS of a workgroup:
+//   front       two dictionary stages (SHARED, p = 256: the signals); then the candidate lists, then the
+//               chunk histogram
+//   E16         [K rounded up to whole stages][signals] 16 bits
+//   (front and E16 together first hold the signals while they are converted)
+//   thr, y2, r2 [signals] floats; key [signals] 64 bits; small change
+template <int P, bool SHARED>
+constexpr size_t scr_front_bytes() {
+    const size_t stages = SHARED ? (P > 64 ? (size_t)64 * P * 2 : 0) : (size_t)2 * ScrGeom<P>::STAGE_U * 16;
+    const size_t lists = (size_t)kScrWaves * (SHARED ? 64 : 512) * 2;
+    const size_t a = stages > lists ? stages : lists;
+    return a > 6144 ? a : 6144;                // the wavefronts' results (SHARED), the histogram
+}
+template <int P, bool SHARED>
+constexpr size_t scr_table_bytes(int K) {      // front + E16
+    constexpr int NB = ScrGeom<P>::NB;
+    const size_t rows = (size_t)((K + NB - 1) / NB * NB), sig = SHARED ? 64 : 64 * kScrWaves;
+    const size_t a = scr_front_bytes<P, SHARED>() + ((rows * sig * 2 + 15) & ~(size_t)15);
+    const size_t signals = SHARED ? (size_t)64 * P * 2 : (size_t)kScrWaves * 4096;
+    return a > signals ? a : signals;
+}
+template <int P, bool SHARED>
+constexpr size_t scr_lds_bytes(int K) {
+    return scr_table_bytes<P, SHARED>(K) + (size_t)(SHARED ? 64 : 64 * kScrWaves) * 20 + (2 * kScrWaves + 1) * 4;
+}
+
+// One step of the main loop issues the matrix instructions of the NEXT rows and the selection networks
+// of the present ones, NM and about NVALU instructions; spread them evenly: a matrix instruction
+// occupies its pipe for 32 cycles and the vector ALU runs beside it, but only if the wavefront
+// has something else to issue (measured: 16 matrix and 304 vector instructions, two wavefronts per
+// SIMD, 2940 cycles interleaved; 3830 when the two wavefronts multiply and select in turns).
+template <int NM, int NVALU>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);              // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              // matrix
+        __builtin_amdgcn_sched_group_barrier(0x002, NVALU / NM, 0);     // vector ALU
+    }
+}
+
+template <int P, int S, int SX, int ARITH, bool SHARED>
+__global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g) {
+    using G = ScrGeom<P>;
+    constexpr int KS16 = G::KS16, MTS = G::MTS, NB = G::NB, SPB = G::SPB, NV = G::NV, STAGE_U = G::STAGE_U;
+    constexpr bool WIDE = G::WIDE;
+    constexpr int SIG = SHARED ? 64 : 64 * kScrWaves;      // signals of the workgroup
+    constexpr int NT = 2;                                   // 32-signal tiles of a wavefront
+    const int K = g.K, m = g.m;
+
+    extern __shared__ u32x4 lds_scr[];
+    unsigned char* front = reinterpret_cast<unsigned char*>(lds_scr);
+    unsigned short* E16 = reinterpret_cast<unsigned short*>(front + scr_front_bytes<P, SHARED>());
+    unsigned* thr = reinterpret_cast<unsigned*>(front + scr_table_bytes<P, SHARED>(K));
+    float* y2s = reinterpret_cast<float*>(thr + SIG);
+    float* r2s = y2s + SIG;
+    unsigned long long* key = reinterpret_cast<unsigned long long*>(r2s + SIG);
+    float* wred = reinterpret_cast<float*>(key + SIG);     // [2][kScrWaves], then one flag
+    int* any_flag = reinterpret_cast<int*>(wred + 2 * kScrWaves);
+
+    const int tid = threadIdx.x, NTH = blockDim.x, NW = NTH >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, n = lane & 31;
+    const int64_t wg0 = (int64_t)blockIdx.x * SIG;         // first signal of the workgroup
+    const int loc0 = SHARED ? 0 : wave * 64;               // first signal of the wavefront, in the workgroup
+
+    // the dictionary's norms (most of the time one entry per thread; consumed below)
+    const int n_norm = K * (P / 16);
+    float2 norm = tid < n_norm ? g.dnorm[tid] : float2{0.f, 0.f};
+
+    // Stages of the dictionary (!SHARED: all wavefronts read the same one); the first two are requested
+    // before the signals.
+    constexpr int FPT = (STAGE_U + 64 * kScrWaves - 1) / (64 * kScrWaves);
+    const int n_stage = WIDE ? K * SPB : (K + NB - 1) / NB;
+    u32x4(*Qs)[STAGE_U] = reinterpret_cast<u32x4(*)[STAGE_U]>(lds_scr);
+    u32x4 pre[FPT], pre1[FPT];
+    auto fetch = [&](u32x4 (&p)[FPT], int s) { // past the end: the last stage once more, not used
+        s = min(s, n_stage - 1);
+#pragma unroll
+        for (int r = 0; r < FPT; ++r) {
+            const int u = min(tid + 64 * kScrWaves * r, STAGE_U - 1);
+            p[r] = g.Dh[(int64_t)s * (2 * STAGE_U) + (u >> 6) * 128 + (u & 63)];
+        }
+    };
+    auto stash = [&](const u32x4 (&p)[FPT], int buf) {
+#pragma unroll
+        for (int r = 0; r < FPT; ++r) Qs[buf][min(tid + 64 * kScrWaves * r, STAGE_U - 1)] = p[r];
+    };
+    if constexpr (!SHARED) {
+        fetch(pre, 0);
+        fetch(pre1, 1);
+    }
+
+    // The leading fp16 parts of the signals, every signal scaled by a power of two (largest magnitude
+    // into [1/2, 1), p = 256: [1/4, 1/2), so that coefficients times the dictionary's 2^13 stay inside
+    // fp16).  PARTS consecutive lanes share a signal, so that a load instruction reads whole cache
+    // lines; GS signals at a time.  y2s / r2s: |y|^2 and |y - hi|^2 of the scaled signal; -1 in y2s: the
+    // signal does not fit (infinite, or below 2^-63).
+    constexpr int PARTS = P / 4 < 8 ? P / 4 : 8, GS = 64 / PARTS, L4 = P / 4 / PARTS;
+    const int part = lane % PARTS, sub = lane / PARTS;
+    auto load_group = [&](int first, f32x4 (&raw)[L4]) {   // first: in the workgroup
+        const int64_t i = wg0 + first + sub;
+#pragma unroll
+        for (int e = 0; e < L4; ++e) {
+            raw[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (i < m) raw[e] = *reinterpret_cast<const f32x4*>(g.Y + i * P + (e * PARTS + part) * 4);
+        }
+    };
+    auto over_parts = [&](float x, auto f) {               // over the PARTS lanes of a signal
+        x = f(x, dpp_f<kDppXor1>(x));
+        x = f(x, dpp_f<kDppXor2>(x));
+        if constexpr (PARTS == 8) x = f(x, dpp_f<kDppHalfMirror>(x));
+        return x;
+    };
+    // dest: operand order of a tile of NN signals: ((ks*2 + hh)*NN + signal)*16 bytes, dims ks*16 + hh*8 ..
+    auto convert_group = [&](int first, const f32x4 (&raw)[L4], unsigned char* dest, int NN, int at) {
+        float vmax = 0.f;
+#pragma unroll
+        for (int e = 0; e < L4; ++e)
+            vmax = fmaxf(fmaxf(fmaxf(vmax, fabsf(raw[e].x)), fmaxf(fabsf(raw[e].y), fabsf(raw[e].z))), fabsf(raw[e].w));
+        vmax = over_parts(vmax, [](float a, float b) { return fmaxf(a, b); });
+        const unsigned ex = (__builtin_bit_cast(unsigned, vmax) >> 23) & 0xffu;
+        const bool fits = ex >= 64u && ex <= 240u;
+        const float scale = fits ? __builtin_bit_cast(float, ((WIDE ? 252u : 253u) - ex) << 23) : 0.f;
+        float y2 = 0.f, r2 = 0.f;
+#pragma unroll
+        for (int e = 0; e < L4; ++e) {
+            typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+            const f32x4 v = raw[e] * scale;
+            const unsigned p0 = pack_f16(v.x, v.y), p1 = pack_f16(v.z, v.w);
+            const f16x2 h0 = __builtin_bit_cast(f16x2, p0), h1 = __builtin_bit_cast(f16x2, p1);
+            const float d0 = v.x - (float)h0[0], d1 = v.y - (float)h0[1], d2 = v.z - (float)h1[0], d3 = v.w - (float)h1[1];
+            y2 = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, y2))));
+            r2 = fmaf(d0, d0, fmaf(d1, d1, fmaf(d2, d2, fmaf(d3, d3, r2))));
+            const int d4 = e * PARTS + part;               // (ks, hh, half) = bits of d4
+            *reinterpret_cast<u32x2*>(dest + ((d4 >> 1) * NN + at + sub) * 16 + (d4 & 1) * 8) = u32x2{p0, p1};
+        }
+        y2 = over_parts(y2, [](float a, float b) { return a + b; });
+        r2 = over_parts(r2, [](float a, float b) { return a + b; });
+        if (part == 0) {
+            y2s[first + sub] = fits || vmax == 0.f ? y2 : -1.f;
+            r2s[first + sub] = r2;
+        }
+    };
+    auto wave_fence = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // B operand: dims ks*16 + h*8 .. +7 of this lane's signal in tile nt
+    u32x4 yq[SHARED && WIDE ? 1 : NT][SHARED && WIDE ? 1 : KS16];
+    if constexpr (SHARED) {
+        for (int q = wave; q < 64 / GS; q += NW) {
+            f32x4 raw[L4];
+            load_group(q * GS, raw);
+            convert_group(q * GS, raw, front + (q * GS / 32) * (32 * P * 2), 32, q * GS & 31);
+        }
+    } else if constexpr (!WIDE) {
+        constexpr int NG = 32 / GS;                        // groups of a tile
+        f32x4 raw[NT * NG][L4];
+#pragma unroll
+        for (int q = 0; q < NT * NG; ++q) load_group(loc0 + q * GS, raw[q]);
+        unsigned char* mine = front + wave * 4096;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+            for (int q = 0; q < NG; ++q) convert_group(loc0 + (nt * NG + q) * GS, raw[nt * NG + q], mine, 32, q * GS);
+            wave_fence();
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks) yq[nt][ks] = *reinterpret_cast<const u32x4*>(mine + (ks * 64 + lane) * 16);
+            wave_fence();
+        }
+    } else {
+        static_assert(!WIDE || GS == 8, "eight signals of 512 bytes at a time");
+        unsigned char* mine = front + wave * 4096;
+        f32x4 raw[2][L4];
+        load_group(loc0, raw[0]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (q + 1 < 8) load_group(loc0 + (q + 1) * GS, raw[(q + 1) & 1]);
+            convert_group(loc0 + q * GS, raw[q & 1], mine, GS, 0);
+            wave_fence();
+            if ((n >> 3) == (q & 3)) {
+#pragma unroll
+                for (int ks = 0; ks < KS16; ++ks)
+                    yq[q >> 2][ks] = *reinterpret_cast<const u32x4*>(mine + ((ks * 2 + h) * GS + (n & 7)) * 16);
+            }
+            wave_fence();
+        }
+    }
+    for (int e = tid + NTH; e < n_norm; e += NTH) {
+        const float2 v = g.dnorm[e];
+        norm.x = fmaxf(norm.x, v.x);
+        norm.y = fmaxf(norm.y, v.y);
+    }
+    norm.x = wave_max(norm.x);
+    norm.y = wave_max(norm.y);
+    if (tid == 0) *any_flag = 0;
+    if (lane == 0) {
+        wred[wave] = norm.x;
+        wred[kScrWaves + wave] = norm.y;
+    }
+    __syncthreads();
+    // Lane (h, n) is the owner of signal (tile h, n) = loc0 + lane.  Energies are stored relative to |y|^2.
+    const float y2_own = y2s[loc0 + lane];
+    const float e_scale = y2_own > 0.f ? 0x1p-26f / y2_own : 0.f;
+    if constexpr (SHARED && !WIDE) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+                yq[nt][ks] = *reinterpret_cast<const u32x4*>(front + nt * (32 * P * 2) + (ks * 64 + lane) * 16);
+    }
+
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    constexpr int UT = SHARED ? (P == 64 ? 2 : 1) : MTS;   // 32-row tiles of a step
+    constexpr int UB = WIDE ? 1 : UT * 32 / P;             // blocks of a step
+    using Acc = f32x16[NT][UT];
+    u16x2 run[SX];                             // p = 256: the pair's sorted top of the block so far
+    float bestE = -1.f, secondE = -1.f;        // of the own signal, in stored units
+    int best = 0;
+    auto finish = [&](const u16x2 (&a)[SX], int j) {
+        const float e = pk_pair_energy<SX>(a, h != 0) * e_scale;
+        secondE = fmaxf(secondE, fminf(bestE, e));
+        best = e > bestE ? j : best;
+        bestE = fmaxf(bestE, e);
+        const auto q = __builtin_amdgcn_cvt_pknorm_u16(e, 0.f);
+        E16[j * SIG + loc0 + lane] = (unsigned short)q[0];
+    };
+    // selection from acc: p <= 64: the UB blocks from j0 on; p = 256: 32 atoms of a block (first: of them all)
+    auto select = [&](const Acc& acc, int j0, bool first) {
+#pragma unroll
+        for (int b = 0; b < UB; ++b) {
+            u16x2 x[NV], a[SX];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int f = b * NV + v;
+                const auto p = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[0][(f >> 4) % UT][f & 15]), fabsf(acc[1][(f >> 4) % UT][f & 15]));
+                x[v] = __builtin_bit_cast(u16x2, p);
+            }
+            pk_top_sorted<NV, SX>(x, a);
+            if constexpr (!WIDE) {
+                finish(a, j0 + b);
+            } else {
+                // (zeros below everything: the first list of a block is taken as it is)
+                const unsigned keep = first ? 0u : 0xffffffffu;
+#pragma unroll
+                for (int t = 0; t < SX; ++t) run[t] = __builtin_bit_cast(u16x2, __builtin_bit_cast(unsigned, run[t]) & keep);
+                pk_merge_top<SX>(run, a);
+            }
+        }
+    };
+    auto multiply = [&](Acc& acc, u32x4 a, int ks, int mt) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            u32x4 b;
+            if constexpr (SHARED && WIDE) b = *reinterpret_cast<const u32x4*>(front + nt * (32 * P * 2) + (ks * 64 + lane) * 16);
+            else b = yq[nt][ks];
+            acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b),
+                                                                 ks == 0 ? zero : acc[nt][mt], 0, 0, 0);
+        }
+    };
+    constexpr int kMatrix = NT * UT * KS16;
+    constexpr int kVector = UB * (NV * 7 + 8 * SX);        // about
+
+    Acc acc0, acc1;
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int t = 0; t < SX; ++t) run[t] = u16x2{0, 0};
+    }
+    if constexpr (!SHARED) {
+        // while stage s is selected from the accumulators, stage s + 1 is multiplied from one buffer and
+        // stage s + 2 written to the other
+        auto project = [&](Acc& acc, int buf) {
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < MTS; ++mt) multiply(acc, Qs[buf][(mt * KS16 + ks) * 64 + lane], ks, mt);
+        };
+        auto step = [&](Acc& now, Acc& next, int s) {
+            fetch(pre, s + 2);
+            project(next, (s + 1) & 1);
+            select(now, s * NB, s % SPB == 0);
+            stash(pre, s & 1);
+            interleave<kMatrix, kVector>();
+            if (WIDE && s % SPB == SPB - 1) finish(run, s / SPB);      // uniform
+            __syncthreads();
+        };
+        stash(pre, 0);
+        stash(pre1, 1);
+        __syncthreads();
+        project(acc0, 0);
+        // The signals of the workgroup that will follow on this CU (workgroups go round the XCDs, so it
+        // comes to the same one) into the XCD's L2, one load per 128-byte line, while this one computes.
+        constexpr int kTouch = P == 64 || P == 32 ? P / 32 : 0;
+        float touch[kTouch > 0 ? kTouch : 1] = {0.f};
+        const int64_t line0 = ((wg0 + (int64_t)kNumCU * SIG) * P) / 32 + tid;
+#pragma unroll
+        for (int r = 0; r < kTouch; ++r)
+            touch[r] = g.Y[min(line0 + (int64_t)r * (64 * kScrWaves), ((int64_t)m * P - 1) / 32) * 32];
+        __syncthreads();
+        for (int s = 0; s < n_stage; s += 2) {
+            step(acc0, acc1, s);
+            if (s + 1 < n_stage) step(acc1, acc0, s + 1);              // uniform
+        }
+#pragma unroll
+        for (int r = 0; r < kTouch; ++r) asm volatile("" ::"v"(touch[r]));
+    } else {
+        // A step = UT row tiles of the dictionary, p = 256: one of the SPB tiles of a block; wavefront w takes
+        // the blocks (p < 64: tiles) w, w + NW, .. and reads their rows from L2, one step ahead.
+        const int n_unit = WIDE ? K : (K + UB - 1) / UB;
+        const int n_mine = wave < n_unit ? ((n_unit - 1 - wave) / NW + 1) * SPB : 0;
+        auto tile_of = [&](int t) {            // past the end: the last one once more, not used
+            t = min(t, n_mine - 1);
+            return WIDE ? (wave + (t / SPB) * NW) * SPB + t % SPB : (wave + t * NW) * UT;
+        };
+        u32x4 rows[UT][KS16];
+        auto load = [&](int t) {
+            const u32x4* src = g.Dh + (int64_t)tile_of(t) * (KS16 * 128) + lane;
+#pragma unroll
+            for (int mt = 0; mt < UT; ++mt)
+#pragma unroll
+                for (int ks = 0; ks < KS16; ++ks) rows[mt][ks] = src[(mt * KS16 + ks) * 128];
+        };
+        auto project = [&](Acc& acc) {
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < UT; ++mt) multiply(acc, rows[mt][ks], ks, mt);
+        };
+        auto step = [&](Acc& now, Acc& next, int t) {
+            project(next);
+            load(t + 2);
+            select(now, WIDE ? 0 : (wave + t * NW) * UB, t % SPB == 0);
+            interleave<kMatrix, kVector>();
+            if (WIDE && t % SPB == SPB - 1) finish(run, wave + (t / SPB) * NW);   // uniform
+        };
+        if (n_mine > 0) {                      // uniform over the wavefront
+            load(0);
+            project(acc0);
+            load(1);
+            for (int t = 0; t < n_mine; t += 2) {
+                step(acc0, acc1, t);
+                if (t + 1 < n_mine) step(acc1, acc0, t + 1);
+            }
+        }
+    }
+
+    // Decision: the best block alone at or above the threshold, in stored energies, or not.
+    const bool valid = wg0 + loc0 + lane < m;
+    if constexpr (SHARED) {
+        __syncthreads();                       // the signals in front are dead
+        float* xb = reinterpret_cast<float*>(front);       // best, second, block: [3][NW][64]
+        xb[wave * 64 + lane] = bestE;
+        xb[(NW + wave) * 64 + lane] = secondE;
+        xb[(2 * NW + wave) * 64 + lane] = __builtin_bit_cast(float, best);
+        __syncthreads();
+        bestE = secondE = -1.f;
+        for (int w = 0; w < NW; ++w) {
+            const float e = xb[w * 64 + lane], e2 = xb[(NW + w) * 64 + lane];
+            secondE = fmaxf(fmaxf(secondE, e2), fminf(bestE, e));
+            best = e > bestE ? __builtin_bit_cast(int, xb[(2 * NW + w) * 64 + lane]) : best;
+            bestE = fmaxf(bestE, e);
+        }
+    }
+    float qn = wred[0], dq = wred[kScrWaves];
+    for (int w = 1; w < NW; ++w) {
+        qn = fmaxf(qn, wred[w]);
+        dq = fmaxf(dq, wred[kScrWaves + w]);
+    }
+    auto stored = [](float e) { return (unsigned)(unsigned short)__builtin_amdgcn_cvt_pknorm_u16(e, 0.f)[0]; };
+    unsigned t16 = 0u;                         // 0: every block stays in
+    {
+        const float rel = y2_own > 0.f ? r2s[loc0 + lane] / y2_own : 0.f;
+        const float eps = sqrtf((float)g.s0) * (qn * sqrtf(rel) + 1.001f * dq + qn * (P * 1.2e-7f)) * 1.001f;
+        const float qb = (float)stored(bestE);
+        const float nrm = sqrtf(fmaxf(qb - 0.5f, 0.f) * (1.f / 65535.f));
+        const float t = (nrm - 2.f * eps) * (1.f - 0x1.02p-10f);
+        const float t2 = t > 0.f ? t * t * (65535.f * (1.f - 1e-5f)) - 1.f : 0.f;
+        if (y2_own > 0.f && t2 > 0.f) t16 = (unsigned)t2;
+    }
+    if (!valid || y2_own == 0.f) t16 = 0x10000u;           // a zero signal: block 0 (ties go to the lowest)
+    const bool undecided = stored(secondE) >= t16;
+    if (t16 == 0x10000u) best = 0;
+    if (!SHARED || wave == 0) {
+        thr[loc0 + lane] = undecided ? t16 : 0x10000u;
+        key[loc0 + lane] = 0ull;
+    }
+    if (__ballot(undecided) != 0ull && lane == 0) *any_flag = 1;
+    __syncthreads();
+
+    // Resolution: the candidates of the undecided signals, block by block.
+    if (*any_flag != 0) {                      // uniform
+        unsigned short* list = reinterpret_cast<unsigned short*>(front) + wave * SIG;
+        unsigned tr[SIG / 64];
+#pragma unroll
+        for (int r = 0; r < SIG / 64; ++r) tr[r] = thr[r * 64 + lane];
+        for (int j = wave; j < K; j += NW) {
+            int len = 0;
+#pragma unroll
+            for (int r = 0; r < SIG / 64; ++r) {
+                const bool in = E16[j * SIG + r * 64 + lane] >= tr[r];
+                const unsigned long long mask = __ballot(in);
+                if (in) list[len + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)(r * 64 + lane);
+                len += __popcll(mask);
+            }
+            wave_fence();
+            for (int t0 = 0; t0 < len; t0 += 32) {         // uniform
+                const int id = t0 + n < len ? (int)list[t0 + n] : -1;
+                const float e = exact_energy<P, S, SX, ARITH>(g, id < 0 ? (int64_t)-1 : wg0 + id, j, lane);
+                // the largest energy (bits of a non-negative float), the lower block on a tie
+                if (h == 0 && id >= 0)
+                    atomicMax(&key[id], ((unsigned long long)__builtin_bit_cast(unsigned, e) << 32) | (unsigned)(~j));
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        if (undecided) best = (int)~(unsigned)key[loc0 + lane];
+    }
+    if (valid && (!SHARED || wave == 0)) g.blk[wg0 + loc0 + lane] = best;
+
+    // First step of the grouping (Section 3.3), folded in here: chunk_count[c][j] += number of
+    // this workgroup's signals that chose block j (chunk is a multiple of SIG; the array is zero on
+    // entry).  Integer atomics only: the sums do not depend on the order.
+    if (g.chunk_count != nullptr) {            // uniform
+        int* lh = reinterpret_cast<int*>(front);
+        __syncthreads();                       // the lists are dead
+        for (int j = tid; j < K; j += NTH) lh[j] = 0;
+        __syncthreads();
+        if (valid && (!SHARED || wave == 0)) atomicAdd(&lh[best], 1);
+        __syncthreads();
+        const unsigned cc = (unsigned)wg0 / (unsigned)g.chunk;
+        for (int j = tid; j < K; j += NTH)
+            if (lh[j] != 0) atomicAdd(&g.chunk_count[cc * (unsigned)K + j], lh[j]);
+    }
+}
+
+template <int P, int S, int SX, int ARITH>
+hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
+    constexpr size_t kLdsMax = 160 * 1024;
+    const bool shared = screen_shared(a.m) || scr_lds_bytes<P, false>(a.K) > kLdsMax;
+    const int sig = shared ? 64 : 64 * kScrWaves;
+    const unsigned grid = (unsigned)((a.m + sig - 1) / sig);
+    if (a.chunk % sig != 0) return hipErrorInvalidValue;
+    if (shared) {
+        const size_t lds = scr_lds_bytes<P, true>(a.K);
+        if (lds > kLdsMax) return hipErrorInvalidValue;
+        const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, true>);
+        if (hipError_t e = raised->ensure(fn, kLdsMax); e != hipSuccess) return e;
+        const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
+        hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, true>), dim3(grid),
+                           dim3(64 * (units < kScrWaves ? units : kScrWaves)), lds, st, a);
+    } else {
+        const size_t lds = scr_lds_bytes<P, false>(a.K);
+        const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, false>);
+        if (hipError_t e = raised->ensure(fn, kLdsMax); e != hipSuccess) return e;
+        hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, false>), dim3(grid), dim3(64 * kScrWaves), lds, st, a);
+    }
+    return hipGetLastError();
+}
+
+template <int P, int SX>
+hipError_t launch_s(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
+    constexpr int S = pow2_at_least(SX);
+    if (arith == SBO_ARITH_F16X2) return launch_a<P, S, SX, 3>(a, raised, st);
+    if constexpr (P <= 64) {
+        if (arith == SBO_ARITH_F32) return launch_a<P, S, SX, 0>(a, raised, st);
+        return launch_a<P, S, SX, 1>(a, raised, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int P>
+hipError_t launch_p(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
+    switch (a.s0) {
+#define SBO_CASE(N) \
+    case N:         \
+        if constexpr (screen_applies(P, N, SBO_ARITH_F16X2)) return launch_s<P, N>(a, arith, raised, st); \
+        break;
+        SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
+        SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
+#undef SBO_CASE
+        default: break;
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+}  // namespace sbo

@@ -1,0 +1,10 @@
+// Block choice, screened (code_screen.h), for p = 16.
+#include "code_screen.h"
+
+namespace sbo {
+
+hipError_t launch_screen_16(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
+    return launch_p<16>(a, arith, raised, st);
+}
+
+}  // namespace sbo

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
 // through LDS 32 atoms at a time (48 KiB in the split operand order, double-buffered); each
 // wavefront keeps its signals' three bf16 parts (192 registers) and the whole projection
 // (8 accumulator tiles, 128 registers) in registers and selects from there.  Dsb is the whole
-// dictionary in the split operand order (dict_swizzle_split_kernel).
+// dictionary in the split operand order (dict_parts_kernel).
 // Workgroup ids are dealt out so that the workgroups of one XCD (ids equal modulo 8) take a
 // contiguous run of tiles, that is, few blocks, whose rows then stay in that XCD's L2.
 template <int P, int S>
@@ -437,7 +437,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
                          bool split, hipStream_t st) {
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
-        hipError_t e = split ? launch_dict_swizzle_split(p, K, D, ws.dsb, 2, st)
+        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, st)
                              : launch_dict_swizzle(p, K, D, ws.dsw, st);
         if (e != hipSuccess) return e;
     }

@@ -159,24 +159,46 @@ __device__ __forceinline__ void store_operand_split(unsigned* __restrict__ dsb, 
     out[4 * 64] = u32x2{a.lo, b.lo};
 }
 
+// Four dims of a dictionary row as two fp16 parts, scaled by kF16DictScale; q2 / r2 += their squares and
+// those of what the leading part leaves (both unscaled).
+struct F16x2Quad {
+    u32x2 hi, lo;
+};
+__device__ __forceinline__ F16x2Quad split_f16x2_dict(f32x4 row, float& q2, float& r2) {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    constexpr float sc = kF16DictScale, inv = 1.f / kF16DictScale;
+    const F16x2Pair a = split_f16x2(row.x * sc, row.y * sc), b = split_f16x2(row.z * sc, row.w * sc);
+    const f16x2 ha = __builtin_bit_cast(f16x2, a.hi), hb = __builtin_bit_cast(f16x2, b.hi);
+    const f32x4 rem = {row.x - (float)ha[0] * inv, row.y - (float)ha[1] * inv, row.z - (float)hb[0] * inv,
+                       row.w - (float)hb[1] * inv};
+    q2 += row.x * row.x + row.y * row.y + row.z * row.z + row.w * row.w;
+    r2 += rem.x * rem.x + rem.y * rem.y + rem.z * rem.z + rem.w * rem.w;
+    return {u32x2{a.hi, b.hi}, u32x2{a.lo, b.lo}};
+}
 template <int P>
-__device__ __forceinline__ void store_operand_f16x2(unsigned* __restrict__ dsb, int grow, int d4, f32x4 row) {
+__device__ __forceinline__ void store_operand_f16x2(unsigned* __restrict__ dsh, int grow, int d4, F16x2Quad q) {
     constexpr int KS16 = P / 16;
     const int st = grow >> 6, mt = (grow >> 5) & 1, nn = grow & 31;
     const int ks = d4 >> 2, hh = (d4 >> 1) & 1, half = d4 & 1;
-    const F16x2Pair a = split_f16x2(row.x * kF16DictScale, row.y * kF16DictScale);
-    const F16x2Pair b = split_f16x2(row.z * kF16DictScale, row.w * kF16DictScale);
-    u32x2* out = reinterpret_cast<u32x2*>(dsb) +
+    u32x2* out = reinterpret_cast<u32x2*>(dsh) +
                  ((int64_t)st * (2 * KS16 * 2 * 64) + (int64_t)((mt * KS16 + ks) * 2) * 64 + hh * 32 + nn) * 2 + half;
-    out[0] = u32x2{a.hi, b.hi};
-    out[2 * 64] = u32x2{a.lo, b.lo};
+    out[0] = q.hi;
+    out[2 * 64] = q.lo;
 }
-// kind: 2 = the three-bf16 split order, 3 = the two-fp16 order
-template <int P>
-__device__ __forceinline__ void store_operand_parts(unsigned* __restrict__ dsb, int kind, int grow, int d4,
-                                                    f32x4 row) {
-    if (kind == 3) store_operand_f16x2<P>(dsb, grow, d4, row);
-    else store_operand_split<P>(dsb, grow, d4, row);
+// Where a kernel that writes dictionary rows also leaves them in the coding kernels' operand orders
+// (nullptr: not wanted).
+struct DictOps {
+    float* f32 = nullptr;       // fp32 order
+    unsigned* bf16 = nullptr;   // three bf16 parts
+    unsigned* f16 = nullptr;    // two fp16 parts, and with them
+    float2* dnorm = nullptr;    // per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
+};
+// Maximum over the 16 lanes of a row, in all of them.
+__device__ __forceinline__ float row16_max(float x) {
+    x = fmaxf(x, dpp_f<kDppXor1>(x));
+    x = fmaxf(x, dpp_f<kDppXor2>(x));
+    x = fmaxf(x, dpp_f<kDppHalfMirror>(x));
+    return fmaxf(x, dpp_f<kDppRowMirror>(x));
 }
 
 // Workgroup-wide exclusive scan of n <= 4 * blockDim.x integers produced by f(idx).

@@ -50,7 +50,7 @@ constexpr int jacobi_lds_floats() {
 template <int P, int TPP>
 __device__ __forceinline__ void jacobi_block(const BlockMatrixSource& src, float* __restrict__ Dj,
                                              float* __restrict__ eig_sv, float done,
-                                             float* __restrict__ dsw, unsigned* __restrict__ dsb, int dsb_kind, int j,
+                                             const DictOps& ops, int j,
                                              int32_t* __restrict__ sweeps_out, float* lds) {
     constexpr int LD = P + 4;
     constexpr int NT = (P / 2) * TPP;          // threads: TPP lanes per column pair
@@ -291,6 +291,9 @@ __device__ __forceinline__ void jacobi_block(const BlockMatrixSource& src, float
         }
     }
 
+    // orthonormal atoms: bounds instead of the norms (an fp16 part is good for 2^-11)
+    if (ops.f16 != nullptr && tid < P / 16) ops.dnorm[j * (P / 16) + tid] = float2{1.0001f, 1.0001f / 2048.f};
+
     // Q = U V^T, written atom-major: D[j][k][r] = sum_c U[r][c] V[k][c].
     constexpr int TILES = (P / 4) * (P / 4);
     for (int tile = tid; tile < TILES; tile += NT) {
@@ -309,8 +312,12 @@ __device__ __forceinline__ void jacobi_block(const BlockMatrixSource& src, float
             f32x4 row = {o[a][0], o[a][1], o[a][2], o[a][3]};
             *reinterpret_cast<f32x4*>(&Dj[(k0 + a) * P + q0]) = row;
             // the same four values in the coding kernel's operand orders
-            if (dsw != nullptr) store_operand_f32<P>(dsw, j * P + k0 + a, q0 >> 2, row);
-            if (dsb != nullptr) store_operand_parts<P>(dsb, dsb_kind, j * P + k0 + a, q0 >> 2, row);
+            if (ops.f32 != nullptr) store_operand_f32<P>(ops.f32, j * P + k0 + a, q0 >> 2, row);
+            if (ops.bf16 != nullptr) store_operand_split<P>(ops.bf16, j * P + k0 + a, q0 >> 2, row);
+            if (ops.f16 != nullptr) {
+                float q2 = 0.f, r2 = 0.f;
+                store_operand_f16x2<P>(ops.f16, j * P + k0 + a, q0 >> 2, split_f16x2_dict(row, q2, r2));
+            }
         }
     }
 }

@@ -55,9 +55,7 @@ struct NsArgs {
     int piece;                 // signals per piece
     const int32_t* counts;     // [K] or nullptr
     float* D;
-    float* dsw;
-    unsigned* dsb;
-    int dsb_kind;              // 2 = three bf16 parts, 3 = two fp16 parts (device_utils.h)
+    DictOps ops;               // the new atoms in the coding kernels' operand orders
     int32_t* fallback;         // [K] 1 = the block went to the Jacobi SVD
     int32_t* iters_out;        // [K] minus the Newton-Schulz steps, or the Jacobi sweeps
     int max_iters;
@@ -462,7 +460,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
     if (!converged) {                          // uniform: the Jacobi SVD of this block, right here
         __syncthreads();
         if (tid == 0) g.fallback[j] = 1;
-        jacobi_block<P, TPP_FALLBACK>(src, g.D + (int64_t)j * P * P, nullptr, kPolarDone, g.dsw, g.dsb, g.dsb_kind, j,
+        jacobi_block<P, TPP_FALLBACK>(src, g.D + (int64_t)j * P * P, nullptr, kPolarDone, g.ops, j,
                                       g.iters_out ? g.iters_out + j : nullptr,
                                       reinterpret_cast<float*>(lds_raw));
         return;
@@ -474,12 +472,19 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
 
     // D[j][k][:] = column k of X; the same values in the coding kernels' operand orders
     f32x4* Dj = reinterpret_cast<f32x4*>(g.D + (int64_t)j * P * P);
+    float q2 = 0.f, r2 = 0.f;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int d4 = t * 4 + grp;
         Dj[col * (P / 4) + d4] = xr[t];
-        if (g.dsw != nullptr) store_operand_f32<P>(g.dsw, j * P + col, d4, xr[t]);
-        if (g.dsb != nullptr) store_operand_parts<P>(g.dsb, g.dsb_kind, j * P + col, d4, xr[t]);
+        if (g.ops.f32 != nullptr) store_operand_f32<P>(g.ops.f32, j * P + col, d4, xr[t]);
+        if (g.ops.bf16 != nullptr) store_operand_split<P>(g.ops.bf16, j * P + col, d4, xr[t]);
+        if (g.ops.f16 != nullptr) store_operand_f16x2<P>(g.ops.f16, j * P + col, d4, split_f16x2_dict(xr[t], q2, r2));
+    }
+    if (g.ops.f16 != nullptr) {                // a wavefront holds 16 atoms
+        q2 = row16_max(sum_groups(q2));
+        r2 = row16_max(sum_groups(r2));
+        if (lane == 0) g.ops.dnorm[j * T + wave] = float2{sqrtf(q2), sqrtf(r2)};
     }
 }
 
@@ -502,7 +507,7 @@ hipError_t launch_ns_p(const NsArgs& a, LdsRaised* raised, hipStream_t st) {
 // M == nullptr: P_j = the sum of block j's pieces in partial (cut from offsets with `piece`
 // signals per piece).  sq.out != nullptr: extra workgroups form *sq.out = sum of sq.err[0..m).
 hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, const int32_t* offsets,
-                           int piece, const int32_t* counts, float* D, float* dsw, unsigned* dsb, int dsb_kind,
+                           int piece, const int32_t* counts, float* D, const DictOps& ops,
                            int32_t* fallback, int32_t* iters, const SqTotalArgs& sq, LdsRaised* raised,
                            hipStream_t st) {
     constexpr int kMaxIters = 26;
@@ -513,9 +518,7 @@ hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, c
     a.piece = piece;
     a.counts = counts;
     a.D = D;
-    a.dsw = dsw;
-    a.dsb = dsb;
-    a.dsb_kind = dsb_kind;
+    a.ops = ops;
     a.fallback = fallback;
     a.iters_out = iters;
     a.max_iters = kMaxIters;

@@ -34,8 +34,9 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.energy = (float*)take((size_t)m_max * 4);
     w.dsw = (float*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dsb = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 6);
-    w.dsh = (unsigned*)take(p > 64 ? (size_t)((K * p + 63) / 64) * 64 * p * 4 : 0);
-    const size_t split_m = (size_t)m_max;      // small m: one entry per signal; resolution pass: per list entry
+    w.dsh = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
+    w.dnorm = (float2*)take((size_t)K * (p / 16) * 8);
+    const size_t split_m = (size_t)(m_max < kEnergySplitSignals ? m_max : kEnergySplitSignals);
     w.part_E = (float*)take((size_t)kEnergySplitRows * split_m * 4);
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
     w.partial = (float*)take((size_t)max_pieces_bound(m_max, K, p) * p * p * 4);
@@ -51,8 +52,6 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.sel_ids = (int32_t*)take((size_t)m_max * 4);
     w.sq_out = (double*)take(8);
     w.sq_counter = (int32_t*)take(4);
-    w.flag_ids = (int32_t*)take((size_t)m_max * 4);
-    w.flag_count = (int32_t*)take(4);
     w.sweeps = (int32_t*)take((size_t)K * 4);
     w.ns_fallback = (int32_t*)take((size_t)K * 4);
     w.sq_partial = (double*)take((size_t)kSqBlocks * 8);
@@ -122,37 +121,33 @@ static int run_group(sbo_ctx* c, const int32_t* blk, int64_t m, bool have_hist =
     return SBO_OK;
 }
 
-// The coding kernel reads the split dictionary (bf16 matrix cores) or the fp32 one.
 static bool use_split(const sbo_ctx* c) { return c->coding_arith != SBO_ARITH_F32; }
-// Which operand order the coding kernel of this context reads (the write_ops / kind values of
-// launch_polar and launch_dict_swizzle_split): 1 fp32, 2 three bf16 parts, 3 two fp16 parts.
-static int ops_kind(const sbo_ctx* c) {
-    if (c->coding_arith == SBO_ARITH_F32) return 1;
-    return c->coding_arith == SBO_ARITH_F16X2 ? 3 : 2;
+// The arithmetic of the block choice.  Screening is now part of every arithmetic that allows it, so
+// SBO_ARITH_BF16X3_SCREEN is SBO_ARITH_BF16X3.
+static int choice_arith(const sbo_ctx* c) {
+    return c->coding_arith == SBO_ARITH_BF16X3_SCREEN ? (int)SBO_ARITH_BF16X3 : c->coding_arith;
 }
-// The buffer the energy kernel reads: at p = 256 the fp16 order has a buffer of its own, because
-// the select kernel there reads the three-bf16 order from ws.dsb.
-static unsigned* energy_parts(const sbo_ctx* c) {
-    return c->p > 64 && ops_kind(c) == 3 ? c->ws.dsh : c->ws.dsb;
+// The operand orders that the block choice of this context reads.
+static int energy_ops(const sbo_ctx* c) {
+    const int a = choice_arith(c);
+    const int own = a == SBO_ARITH_F32 ? kOpsF32 : a == SBO_ARITH_F16X2 ? kOpsF16 : kOpsBf16;
+    return screen_applies(c->p, c->s0, a) ? own | kOpsF16 : own;
 }
 
 // D in the operand order(s) the coding kernels of this context read (tiny; outside the stages).
 static int run_swizzle(sbo_ctx* c, const float* D) {
-    if (use_split(c)) {
-        SBO_HIP(launch_dict_swizzle_split(c->p, c->K, D, energy_parts(c), ops_kind(c), c->stream));
-        if (energy_parts(c) != c->ws.dsb)       // p = 256: the select kernel's order as well
-            SBO_HIP(launch_dict_swizzle_split(c->p, c->K, D, c->ws.dsb, 2, c->stream));
-    }
-    else SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, c->stream));
+    int ops = energy_ops(c);
+    if (c->p > 64) ops |= use_split(c) ? kOpsBf16 : kOpsF32;       // what the select kernel reads
+    if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, c->stream));
+    if (ops & (kOpsBf16 | kOpsF16))
+        SBO_HIP(launch_dict_parts(c->p, c->K, D, ops & kOpsBf16 ? c->ws.dsb : nullptr,
+                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm, c->stream));
     return SBO_OK;
 }
 
 static int run_energy(sbo_ctx* c, const float* Y, int64_t m, int32_t* blk) {
     StageTimer t(c, SBO_STAGE_ENERGY);     // also leaves the chunk histograms of the grouping
-    const EnergyScreen scr{c->ws.flag_ids, c->ws.flag_count};
-    SBO_HIP(launch_energy(c->p, c->K, c->s0, Y, m, c->ws.dsw, use_split(c) ? energy_parts(c) : nullptr, ops_kind(c), blk,
-                          c->ws.energy, c->ws.chunk_count, c->ws.part_E, c->ws.part_j, &c->raised,
-                          c->coding_arith == SBO_ARITH_BF16X3_SCREEN ? &scr : nullptr, c->stream));
+    SBO_HIP(launch_energy(c->p, c->K, c->s0, choice_arith(c), Y, m, c->ws, blk, c->ws.chunk_count, c->stream));
     return SBO_OK;
 }
 
@@ -247,7 +242,6 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     // finished-workgroup counter are zero whenever no call is in flight.
     e = hipMemsetAsync(c->ws.chunk_count, 0, (size_t)max_chunks() * K * 4, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->ws.sq_counter, 0, 4, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->ws.flag_count, 0, 4, c->stream);
     if (e != hipSuccess) {
         (void)hipFree(c->ws_base);
         delete c;
@@ -379,7 +373,7 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
             StageTimer t(c, SBO_STAGE_SELECT);  // includes the per-piece accumulation
             SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, c->stream));
         }
-        rc = run_polar_pieces(c, m, D, ops_kind(c), err, sqerr_per_iter ? sqerr_per_iter + it : nullptr);
+        rc = run_polar_pieces(c, m, D, energy_ops(c), err, sqerr_per_iter ? sqerr_per_iter + it : nullptr);
         if (rc) return rc;
     }
     return SBO_OK;

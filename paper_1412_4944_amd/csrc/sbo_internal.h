@@ -11,6 +11,8 @@
 
 namespace sbo {
 
+struct DictOps;                // device_utils.h
+
 constexpr int kWave = 64;
 
 // ---- grouping geometry -----------------------------------------------------
@@ -90,10 +92,10 @@ struct Workspace {
     // coding
     float* energy;         // [m_max] kept energy in the winning block
     float* dsw;            // [ceil(K*p/64)*64][p] dictionary in MFMA operand order
-    unsigned* dsh;         // p > 64 only: the same rows as two fp16 parts (the energy kernel's order there)
-    unsigned* dsb;         // the same rows in parts: three bf16 (6 bytes per entry) or, for the energy kernel at
-                           // p <= 64, two fp16 (4 bytes per entry), in the split operand orders
-    float* part_E;         // [kEnergySplitRows][m_max] split coding / resolution pass: best energy per row
+    unsigned* dsb;         // the same rows as three bf16 parts (6 bytes per entry)
+    unsigned* dsh;         // the same rows as two fp16 parts (4 bytes per entry)
+    float2* dnorm;         // [K*p/16] per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
+    float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row
     int32_t* part_j;       // same shape: its block
     // accumulation
     float* partial;        // [max_pieces][p][p]
@@ -111,8 +113,6 @@ struct Workspace {
     int32_t* ns_fallback;  // [K] 1 = Newton-Schulz left the block to the Jacobi kernel
     int32_t* sq_counter;   // [1] workgroups of the fused squared-error sum that have finished (0 between launches)
     bool parts_accum = false;   // p = 256: the accumulation on the bf16 matrix cores (any coding arithmetic but fp32)
-    int32_t* flag_ids;     // [m_max] signals whose block the screening pass of the coding kernel left undecided
-    int32_t* flag_count;   // [1] how many (0 between calls: the grouping's scan kernel clears it)
     // iterate
     double* sq_partial;    // [kSqBlocks]
     size_t bytes;
@@ -152,32 +152,36 @@ struct sbo_ctx {
 // ---- kernel launchers (each returns a hipError_t from the launch) ----------------
 namespace sbo {
 
-// dsw = D rewritten by launch_dict_swizzle into the energy kernel's operand order.
+// Operand orders of the dictionary that a coding arithmetic reads (bit mask).
+constexpr int kOpsF32 = 1, kOpsBf16 = 2, kOpsF16 = 4;
+
+// Which calls choose the block by screening with leading fp16 parts and full products for the
+// contenders only (code_screen.h).  More than p / 2 coefficients kept: the blocks of a signal all but
+// tie, and almost all of them would be contenders.  p = 256 in the other arithmetics: the full
+// products of three bf16 parts do not fit the registers beside the screening.
+constexpr bool screen_applies(int p, int s0, int arith) {
+    return 2 * s0 <= p && (p <= 64 || arith == SBO_ARITH_F16X2);
+}
+// Which shape of the screening kernel: workgroups of 64 signals (true) or of 512.  The latter reads the
+// dictionary once per 512 signals and is 1.2 times as fast on a full chip, but its time is that of whole
+// rounds of one workgroup per CU: it is taken from 0.65 of its rounds' capacity on (measured, K = 32,
+// p = 64, workgroups of 64 / 512: 65536 signals 82 / 93 us, 81920 94 / 96, 98304 112 / 105, 131072 139 / 116).
+constexpr bool screen_shared(int64_t m) {
+    const int64_t round = (int64_t)kNumCU * 512, rounds = (m + round - 1) / round;
+    return 20 * m < 13 * rounds * round;
+}
+
+// dsw = D in the fp32 operand order of the coding kernels.
 hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStream_t st);
-// dsb = D in the operand order of the split coding kernels; kind 2: three bf16 parts per entry,
-// kind 3 (p <= 64): two fp16 parts per entry (device_utils.h).
-hipError_t launch_dict_swizzle_split(int p, int K, const float* D, unsigned* dsb, int kind, hipStream_t st);
+// dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
+// (device_utils.h); dnorm comes with dsh.
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, hipStream_t st);
+// The block of every signal, from the operand orders in ws that (p, s0, arith) reads (energy_ops in
+// sbo_api.hip).
 // chunk_count != nullptr: also add the per-chunk histograms of the chosen blocks into it (the
 // first step of launch_group; the array must be zero on entry, launch_group leaves it so).
-// part_E / part_j ([kEnergySplitRows][m_max], may be nullptr): scratch for small m (at most
-// kEnergySplitSignals), where the blocks are split over several workgroup rows to fill the chip,
-// and for the resolution pass of the screening (scr), which is always split that way.
-// dsb != nullptr: the projection runs on the bf16 (dsb_kind 2) or fp16 (dsb_kind 3, p <= 64) matrix
-// cores from the split dictionary (dsw is then not read); otherwise on the fp32 matrix instruction
-// from dsw.
-// scr != nullptr (with dsb, p <= 64, enough signals to fill the chip): a screening pass with half
-// the matrix work decides the block of every signal whose two best energies are further apart
-// than the screening error allows, and the full products are formed only for the rest, listed in
-// scr->ids ([m]) / scr->count ([1], zero on entry; launch_group sets it back to zero).  The
-// energies written for decided signals are then the screened ones.
-struct EnergyScreen {
-    int32_t* ids;
-    int32_t* count;
-};
-hipError_t launch_energy(int p, int K, int s0, const float* Y, int64_t m, const float* dsw,
-                         const unsigned* dsb, int dsb_kind, int32_t* blk, float* energy, int32_t* chunk_count,
-                         float* part_E, int32_t* part_j, LdsRaised* raised, const EnergyScreen* scr,
-                         hipStream_t st);
+hipError_t launch_energy(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws, int32_t* blk,
+                         int32_t* chunk_count, hipStream_t st);
 
 hipError_t launch_group(int K, const int32_t* blk, int64_t m, const Workspace& ws, bool have_hist,
                         hipStream_t st);
@@ -216,9 +220,8 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
 // eig_sv != nullptr switches to eigen mode (always Jacobi): M[j] symmetric positive
 // semidefinite, D[j] receives its eigenvectors as atoms by descending eigenvalue and
 // eig_sv[j][p] the square roots of the eigenvalues.
-// write_ops (p <= 64): the rows of every updated block are also written in the coding kernel's
-// operand order: 1 = into ws.dsw (what launch_dict_swizzle would produce from the new D), 2 / 3 =
-// into ws.dsb (launch_dict_swizzle_split with kind 2: three bf16 parts / 3: two fp16 parts), 0 = neither.
+// write_ops (p <= 64): the operand orders (kOps*) in which the rows of every updated block are also
+// left in ws.
 hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, float* D,
                         const Workspace& ws, int jacobi_only, float* eig_sv, int write_ops,
                         hipStream_t st);
@@ -236,7 +239,7 @@ struct SqTotalArgs {
 // converge.  M == nullptr: P_j = the sum of block j's pieces in `partial` (fused select +
 // accumulate, cut from `offsets` with `piece` signals per piece).
 hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, const int32_t* offsets,
-                           int piece, const int32_t* counts, float* D, float* dsw, unsigned* dsb, int dsb_kind,
+                           int piece, const int32_t* counts, float* D, const DictOps& ops,
                            int32_t* fallback, int32_t* iters, const SqTotalArgs& sq, LdsRaised* raised,
                            hipStream_t st);
 // The SVD update straight from the piece results of launch_select_accum (p <= 64, Newton-Schulz

@@ -1,0 +1,28 @@
+// Arguments of the screened block choice (code_screen.h) and its entry points.
+#pragma once
+
+#include "sbo_internal.h"
+#include "device_utils.h"
+
+namespace sbo {
+
+// What the resolution reads, besides Dh: Dx = the dictionary in the exact arithmetic's operand order.
+struct ScrArgs {
+    const float* Y;
+    int m;
+    const u32x4* Dh;           // two fp16 parts per entry (device_utils.h)
+    const void* Dx;            // ARITH 3: Dh, 1: three bf16 parts, 0: fp32 order
+    const float2* dnorm;       // per 16 atoms: largest norm, largest norm of the fp16 remainder
+    int K, s0;
+    int32_t* blk;
+    int32_t* chunk_count;      // or nullptr
+    int chunk;
+};
+
+// One translation unit per p (code_screen_<p>.hip): the kernels are many.
+hipError_t launch_screen_16(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+hipError_t launch_screen_32(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+hipError_t launch_screen_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+hipError_t launch_screen_256(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+
+}  // namespace sbo

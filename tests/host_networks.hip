@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../paper_1412_4944_amd/csrc/device_utils.h"
+#include "../paper_1412_4944_amd/csrc/energy_networks.h"
 
 using namespace sbo;
 
@@ -110,6 +111,46 @@ template <int S> static void test_pair_fold() {
     }
 }
 
+// the packed networks (two 16-bit lists per word): sorts on all 0-1 inputs, top-N lists and their
+// merge against std::sort, with ties
+template <int L> static void test_pk_sort() {
+    for (unsigned b = 0; b < (1u << L); ++b) {
+        u16x2 v[L];
+        for (int i = 0; i < L; ++i) v[i] = u16x2{(unsigned short)((b >> i) & 1), (unsigned short)((~b >> i) & 1)};
+        pk_sort_desc<L>(v);
+        for (int i = 1; i < L; ++i) CHECK(v[i - 1][0] >= v[i][0] && v[i - 1][1] >= v[i][1]);
+    }
+}
+template <int NV, int N> static void test_pk_top() {
+    std::mt19937 g(9000 + NV * 17 + N);
+    for (int rep = 0; rep < 2000; ++rep) {
+        u16x2 x[NV], out[N], more[N];
+        std::vector<int> w[2];
+        const unsigned mask = rep % 3 == 0 ? 1u : rep % 3 == 1 ? 7u : 0xffffu;
+        for (int i = 0; i < NV; ++i)
+            for (int t = 0; t < 2; ++t) {
+                x[i][t] = (unsigned short)(g() & mask);
+                w[t].push_back(x[i][t]);
+            }
+        pk_top_sorted<NV, N>(x, out);
+        for (int t = 0; t < 2; ++t) {
+            std::sort(w[t].rbegin(), w[t].rend());
+            for (int i = 0; i < N; ++i) CHECK(out[i][t] == w[t][i]);
+        }
+        for (int t = 0; t < 2; ++t) {
+            std::vector<int> u;
+            for (int i = 0; i < N; ++i) u.push_back((int)(g() & mask));
+            std::sort(u.rbegin(), u.rend());
+            for (int i = 0; i < N; ++i) more[i][t] = (unsigned short)u[i];
+            w[t].insert(w[t].end(), u.begin(), u.end());
+            std::sort(w[t].rbegin(), w[t].rend());
+        }
+        pk_merge_top<N>(out, more);
+        for (int t = 0; t < 2; ++t)
+            for (int i = 0; i < N; ++i) CHECK(out[i][t] == w[t][i]);
+    }
+}
+
 static void test_slot() {
     std::mt19937 g(7);
     for (int rep = 0; rep < 2000; ++rep) {
@@ -132,6 +173,10 @@ int main() {
     test_top<16, 1>(); test_top<16, 2>(); test_top<16, 4>(); test_top<16, 8>(); test_top<16, 16>();
     test_top<32, 1>(); test_top<32, 2>(); test_top<32, 4>(); test_top<32, 8>(); test_top<32, 16>();
     test_pair_fold<1>(); test_pair_fold<2>(); test_pair_fold<4>(); test_pair_fold<8>(); test_pair_fold<16>();
+    test_pk_sort<2>(); test_pk_sort<4>(); test_pk_sort<8>(); test_pk_sort<16>();
+    test_pk_top<8, 1>(); test_pk_top<8, 3>(); test_pk_top<8, 8>(); test_pk_top<16, 2>(); test_pk_top<16, 5>();
+    test_pk_top<16, 9>(); test_pk_top<16, 12>(); test_pk_top<16, 15>(); test_pk_top<16, 16>(); test_pk_top<32, 1>();
+    test_pk_top<32, 4>(); test_pk_top<32, 6>(); test_pk_top<32, 7>(); test_pk_top<32, 8>(); test_pk_top<32, 13>();
     test_slot();
     if (fails) { std::printf("%d failures\n", fails); return 1; }
     std::printf("ok\n");

@@ -107,6 +107,43 @@ def test_code_over_signal_scales_and_dynamic_range(arith, p, K, s0):
     print(f"  exempt fraction {frac:.5f}", flush=True)
 
 
+SCREEN_EDGES = [                                         # both shapes, their borders and remainders; a table
+                                                         # too large for 512 signals (the last two)
+    (64, 1, 8, 1), (64, 9, 16, 65), (32, 5, 16, 193), (16, 7, 8, 63), (16, 1, 1, 64), (256, 3, 16, 129),
+    (64, 3, 4, 85196), (64, 2, 6, 85197), (32, 7, 3, 86000 + 513), (16, 5, 8, 86016 + 31), (256, 2, 12, 86016 + 1),
+    (64, 4, 3, 131072), (32, 5, 5, 131073), (16, 160, 3, 90001), (64, 130, 2, 86081),
+]
+
+
+@pytest.mark.parametrize("p,K,s0,m", SCREEN_EDGES)
+@pytest.mark.parametrize("close", [False, True], ids=["apart", "close"])
+def test_screened_block_choice(p, K, s0, m, close):
+    """The screened choice at the edges of its shapes; with blocks that differ from one another by
+    about 1e-5, nearly every signal has several candidates left to be resolved in full precision."""
+    rng = np.random.default_rng(17 + p + K)
+    if close:
+        Q = synth.random_onb(rng, p)
+        D = np.stack([np.linalg.qr(Q + 1e-5 * rng.standard_normal((p, p)))[0] for _ in range(K)])
+        D *= np.sign(np.einsum("kij,ij->kj", D, Q))[:, None, :]
+        D = np.ascontiguousarray(D.transpose(0, 2, 1)).astype(np.float32)
+    else:
+        D = np.stack([synth.random_onb(rng, p).T for _ in range(K)]).astype(np.float32)
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    Y[m // 2] = 0.0
+    rows = np.unique(np.r_[0:min(m, 300), max(0, m - 600):m])
+    o = orc.o_code(Y[rows], D, s0)
+    outs = []
+    for arith in ["f16x2"] if p == 256 else ["f32", "bf16x3", "f16x2"]:
+        print(f"case {arith}: p={p} K={K} m={m} s0={s0} close={close}", flush=True)
+        with Sbo(p, K, s0, m, arith=arith) as g:
+            out = g.code(Y, D)
+        compare_code(Y[rows], D, s0, o, tuple(a[rows] for a in out), max_exempt_frac=1.0 if close else 0.01)
+        outs.append(out[0])
+    for blk in outs:
+        assert blk[m // 2] == 0 and blk.min() >= 0 and blk.max() < K
+        assert close or (blk != outs[0]).mean() < 0.01
+
+
 @pytest.mark.parametrize("K,m", [(4, 1024), (32, 5000), (128, 70001), (1, 100), (1000, 3000), (7, 1)])
 def test_group_matches_oracle(K, m):
     rng = np.random.default_rng(K * 1000 + m)
