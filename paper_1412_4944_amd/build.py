@@ -18,7 +18,7 @@ LIB = os.path.join(LIB_DIR, "libsbo.so")
 
 SOURCES = ["sbo_api.hip", "code_energy.hip", "code_screen_16.hip", "code_screen_32.hip", "code_screen_64.hip",
            "code_screen_256.hip", "code_select.hip", "select_accum.hip", "group.hip", "accumulate.hip",
-           "polar_jacobi.hip", "polar_ns.hip", "polar_wide.hip", "polar_wide_ns.hip", "reduce.hip", "worst.hip"]
+           "polar_jacobi.hip", "polar_ns.hip", "polar_wide.hip", "reduce.hip", "worst.hip"]
 # bench.py's achievable-peak probes: a library of their own, not part of libsbo
 PROBE_SOURCE = "bench_probe.hip"
 PROBE_LIB = os.path.join(LIB_DIR, "libsbo_benchprobe.so")

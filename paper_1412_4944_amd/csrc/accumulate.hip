@@ -616,6 +616,7 @@ hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, 
         hipLaunchKernelGGL((accum_wide_kernel<S0, false>), dim3(max_pieces), dim3(256), lds1, st, Y, K, piece,
                            ws.offsets, ws.perm, supp, coef, ws.partial);
     }
+    if (M == nullptr) return hipGetLastError();
     const size_t lds2 = (K + 1 + 16) * sizeof(int);
     hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256), lds2, st,
                        K, piece, ws.offsets, ws.partial, M, nullptr, (int64_t)0, nullptr, nullptr, nullptr, 0);
@@ -722,6 +723,7 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
 
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
                              const float* coef, const Workspace& ws, float* M, hipStream_t st) {
+    if (M == nullptr && p != 256) return hipErrorInvalidValue;
     switch (p) {
         case 16: return launch_p<16>(K, s0, Y, m, supp, coef, ws, M, st);
         case 32: return launch_p<32>(K, s0, Y, m, supp, coef, ws, M, st);

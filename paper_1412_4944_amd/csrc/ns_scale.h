@@ -1,0 +1,68 @@
+// The scaling of the Newton-Schulz iteration X <- X (3 I - X^T X) / 2 for p = 256 (polar_wide.hip).
+//
+// With all singular values in [l, 1], X scaled by alpha(l) = sqrt(3 / (1 + l + l^2)) before a step makes the
+// step's polynomial f(s) = alpha s (3 - (alpha s)^2) / 2 map [l, 1] to the smallest possible interval
+// [l', 1], l' = f(l).  A smaller singular value is safe (f is positive and at most one on
+// (0, sqrt(3))), but it grows by only 3/2 a step once alpha is 1: so l starts at 0.16 (block matrices of a trained
+// dictionary have condition numbers of 2 to 10) and is lowered when a column of X shows it to be
+// wrong: the smallest column norm is an upper bound of the smallest singular value, and where atoms are
+// rarely used it is close to it.  From 0.5 on the values have met and it is left alone.  (Simulated on block
+// matrices of first training rounds, condition 60 to 5000: 9 to 15 steps instead of 11 to 22; condition
+// below 7: as without it.  p <= 64, condition 3 to 14, keeps the fixed scalings for l = 0.16 of
+// polar_ns.hip: a step less in some rounds was what the bookkeeping cost.)
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace sbo {
+
+struct NsScale {
+    float l = 0.16f;           // before the present step
+    float alpha = 1.f, lower = 1.f;            // of the step before: its scaling, its l
+
+    __device__ __forceinline__ float take(float alpha_) {
+        alpha = alpha_;
+        lower = l;
+        l = fminf(map(l), 1.f);
+        return alpha;
+    }
+    __device__ __forceinline__ float map(float s) const {
+        const float a = alpha * s;
+        return a * (1.5f - 0.5f * a * a);
+    }
+    __device__ __forceinline__ static float best(float s) {
+        return s < 0.99f ? __builtin_amdgcn_sqrtf(3.f * __builtin_amdgcn_rcpf(1.f + s + s * s)) : 1.f;
+    }
+    // The first step, which also scales the input: the iteration sends every singular value in (0, sqrt(3))
+    // to +1, one in (sqrt(3), sqrt(5)) to -1 (an orthogonal matrix that is NOT U V^T, and which no later
+    // test can tell apart), so the scale must be a guaranteed bound: the largest absolute row sum of
+    // G = X^T X is at least its largest eigenvalue sigma_max^2, and alpha^2 <= 2.9 / that keeps every
+    // scaled sigma^2 below 2.9.  Where the bound is tight, the aim is sigma_max = 1 times alpha(l), with
+    // the largest norm of a column of G (a lower bound of its largest eigenvalue) as the estimate.
+    // row_sum: the former; col2: the square of the latter; diag: the smallest diagonal entry of G.
+    __device__ __forceinline__ float first(float row_sum, float col2, float diag) {
+        float b2 = 2.9f * __builtin_amdgcn_rcpf(row_sum);
+        float est = row_sum * (1.f / 1.4f);    // of sigma_max^2
+        if (col2 > 1e-37f && col2 < 3e37f) {
+            est = 1.04f * __builtin_amdgcn_sqrtf(col2);
+            const float r = diag > 0.f ? __builtin_amdgcn_sqrtf(diag * __builtin_amdgcn_rcpf(est)) : 0.f;
+            l = fmaxf(fminf(l, r), 1e-3f);
+            const float a = best(l);
+            b2 = fminf(b2, a * a * __builtin_amdgcn_rcpf(est));
+        }
+        const float scale = __builtin_amdgcn_sqrtf(b2);
+        // in units of X / sqrt(est)
+        take(__builtin_amdgcn_sqrtf(b2 * est));
+        alpha = 1.f;                           // (a column norm seen now is of the unscaled X: not used)
+        lower = 0.f;
+        return scale;
+    }
+    __device__ __forceinline__ float next() { return take(best(l)); }
+    // diag: the smallest diagonal entry of X^T X before the step whose alpha was taken last
+    __device__ __forceinline__ void seen(float diag) {
+        const float s = __builtin_amdgcn_sqrtf(fmaxf(diag, 0.f));
+        if (s < lower && s < 0.5f) l = fmaxf(map(s), 1e-3f);
+    }
+};
+
+}  // namespace sbo

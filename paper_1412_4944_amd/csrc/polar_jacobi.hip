@@ -65,17 +65,9 @@ hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, flo
                         const Workspace& ws, int jacobi_only, float* eig_sv, int write_ops,
                         hipStream_t st) {
     const bool ns = eig_sv == nullptr && !jacobi_only;
-    if (p == 256) {
-        if (write_ops) return hipErrorInvalidValue;   // p = 256 rewrites the operand order itself
-        if (!ns)
-            return launch_polar_wide(K, M, counts, D, ws.vwork, ws.jac_a, eig_sv, ws.sweeps, nullptr,
-                                     ws.raised, st);
-        hipError_t e = launch_polar_wide_ns(K, M, counts, D, ws.jac_a, ws.ns_fallback, ws.sweeps,
-                                            ws.raised, st);
-        if (e != hipSuccess) return e;
-        return launch_polar_wide(K, M, counts, D, ws.vwork, ws.jac_a, nullptr, ws.sweeps,
-                                 ws.ns_fallback, ws.raised, st);
-    }
+    if (p == 256)
+        return launch_polar_wide(K, M, nullptr, nullptr, 0, counts, D, dict_ops(ws, eig_sv ? 0 : write_ops), ns, eig_sv,
+                                 ws, SqTotalArgs{}, st);
     const DictOps ops = dict_ops(ws, write_ops);
     if (!ns) return launch_jacobi(p, K, M, counts, D, eig_sv, ops, ws.sweeps, nullptr, st);
     // Newton-Schulz for every block; a block on which it does not converge gets the Jacobi SVD in
@@ -86,7 +78,6 @@ hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, flo
 
 hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Workspace& ws, int write_ops,
                                     const float* err, double* sq_out, hipStream_t st) {
-    if (p > 64) return hipErrorInvalidValue;
     SqTotalArgs sq;
     if (err != nullptr && sq_out != nullptr) {
         sq.err = err;
@@ -96,6 +87,9 @@ hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Wor
         sq.out = sq_out;
         sq.nb = (int)(m / 2048 < 1 ? 1 : m / 2048 < 128 ? m / 2048 : 128);   // <= kSqBlocks shares of err
     }
+    if (p == 256)
+        return launch_polar_wide(K, nullptr, ws.partial, ws.offsets, accum_piece(m, K, p), ws.counts, D,
+                                 dict_ops(ws, write_ops), true, nullptr, ws, sq, st);
     return launch_polar_ns(p, K, nullptr, ws.partial, ws.offsets, accum_piece(m, K, p), ws.counts, D,
                            dict_ops(ws, write_ops), ws.ns_fallback, ws.sweeps, sq, ws.raised, st);
 }

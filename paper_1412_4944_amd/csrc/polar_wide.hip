@@ -1,376 +1,839 @@
-// Batched SVD update Q_j = U V^T (Algorithm 1, steps 6-7) for p = 256.
+// Batched SVD update Q_j = U V^T (Algorithm 1, steps 6-7) for p = 256: a team of 16 workgroups per
+// block, one launch for everything.
 //
-// The same one-sided Jacobi as for p <= 64 (round-robin tournament, p/2 disjoint column
-// pairs per round, eight lanes per pair, DPP dot-product reductions), but A = P_j and V
-// (2 x 256 KiB per block) do not fit the LDS of one CU.  The work is therefore split:
+// A 256 x 256 matrix in the three bf16 parts that fp32 accuracy takes is 384 KiB: more than the LDS of
+// a CU, and one CU alone would need 80 us of matrix time for a block.  So 16 workgroups share a block
+// and meet at barriers in memory (2-3 us each); the alternative, a launch per product, pays 5 us per
+// launch and has to launch as many steps as the worst matrix might need.
 //
-//   1. wide_jacobi_kernel, one workgroup of 1024 threads per block, orthogonalises the
-//      columns of A only.  Rows 0..127 of A live in LDS (132 KiB), rows 128..255 in global
-//      memory (L2); every round streams each column pair through registers.  The rotation
-//      (cos, sin) of every pair and round is appended to a log.
-//   2. wide_replay_kernel applies the logged rotations to V.  Rows of V are independent,
-//      so this spreads over the whole chip: a wavefront keeps four rows in LDS and walks
-//      the log.
-//   3. wide_finish_kernel: sigma = column norms, U = A / sigma, completion of vanished
-//      columns, Q = U V^T.
+//   Newton-Schulz (polar_ns.hip has the iteration and its last step, ns_scale.h the scaling).  A
+//   workgroup owns a strip of 16 columns of X, in registers.  Per step it multiplies G = X^T X (its 16
+//   columns), then X E (its 16 columns), six bf16 products each; the A operands are ALL of X, by
+//   columns for the first product and by rows for the second, read straight from L2 in operand order,
+//   each exactly once: every workgroup leaves its strip in both orders when it has updated it, and that
+//   is the only exchange, hence one barrier per step (two in the first and the last).  A wavefront
+//   makes two 16 x 16 tiles of both products; its loads run four contraction steps ahead and through from
+//   the first product into the second.
 //
-// Keeping V out of the tournament halves the data each round has to move through one CU,
-// which is what bounds step 1.
+//   A block on which that does not converge (rank-deficient, zero, NaN), every block under
+//   SBO_SVD_JACOBI, and the eigenvectors of a Gram matrix: one-sided Jacobi with eight of the
+//   workgroups.  Columns in 16 sets of 16; a workgroup rotates all pairs of two sets (one set's columns of A
+//   and V in registers, half a wavefront each, the other's in LDS), then the sets move on: all
+//   pairs of sets in 15 rounds, seven of them keeping one of the two sets in place.  A set is
+//   handed over through memory with a version number; there is no barrier but one per sweep.
+//
+// What bounds it: Newton-Schulz by the 768 KiB of operands per workgroup and step from L2 (40 to 46 bytes a
+// cycle arrive; a step is 27000 cycles, 6600 of them matrix work, 3000 the barrier); Jacobi by the vector ALU
+// of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.
+// Measured: K = 16 inside sbo_iterate 347 us (a launch per product and step, fp32 matrix instruction,
+// 20 steps enqueued, plus launches for the sum of the pieces, the Jacobi SVD that has nothing to do,
+// the operand order and the squared error: 46 launches, 400 us) -> 125 us and nothing else; K = 1 in a
+// first training round 300 -> 125 us; eigenvectors of a Gram matrix (10 sweeps) 12.1 -> 1.8 ms.
+//
+// Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups, one per CU, and
+// workgroups start in order, so whatever else runs, the first team that is not done is or will be
+// complete.  Every wait is bounded all the same, and a team that gives up leaves NaN.
 #include "sbo_internal.h"
 #include "device_utils.h"
+#include "ns_scale.h"
+#include "sq_total.h"
+
+#include <type_traits>
 
 namespace sbo {
 
 namespace {
 
 constexpr int P = 256;
-constexpr int kPairs = P / 2;
-constexpr int kSteps = P - 1;
-constexpr int kMaxSweeps = 24;    // rounds logged per block: kMaxSweeps * kSteps
-constexpr float kTol = 1e-6f;     // rotate while |a_i . a_j| > kTol |a_i| |a_j|
-constexpr int LDA = 132;          // LDS leading dimension of the 128 on-chip rows
-constexpr int kRowsLds = 128;
+constexpr int kTeam = 16;                      // workgroups per block
+constexpr int kJacTeam = 8;
+constexpr int kMaxTeams = 16;                  // blocks at a time
+constexpr int kNT = 512;
+constexpr int kWaves = kNT / 64;
+constexpr int kSpin = 1 << 22;                 // polls of a wait: seconds
+constexpr int kMaxSweeps = 24;
+constexpr float kTol = 1e-6f;                  // rotate while |a_i . a_j| > kTol |a_i| |a_j|
 
-constexpr size_t kLogFloatsPerBlock = (size_t)kMaxSweeps * kSteps * kPairs * 2;
+constexpr int kImage = 8 * 3 * 1024;           // a strip's operand image: [contraction step][part][64 lanes][16 bytes]
+constexpr int kLdStrip = P + 4;
 
-// Scratch layout per launch: A[K][P][P] | log[K][kLogFloatsPerBlock] | nsweeps[K] (ints)
-struct WideScratch {
-    float* A;
-    float* log;
-    int* nsweeps;
+// A team's memory
+constexpr size_t kColAt = 0;                                   // [2][16 strips] images by columns
+constexpr size_t kRowAt = kColAt + 2 * (size_t)kTeam * kImage; // [2][16 row tiles][8][part][half][64 lanes][8 bytes]
+constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [16 strips][8][64 lanes][16 bytes] leading parts of E
+constexpr size_t kJaAt = kEAt + (size_t)kTeam * 8 * 1024;      // [256 columns][256] A
+constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
+constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][3][16] | sigma[256] | 1/|v|[256]
+constexpr size_t kTeamBytes = kSmallAt + 4096;
+// and its counters (ints, zero between launches), each on a cache line of its own
+constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kVersionAt = 160, kMeetAt = 192, kSyncInts = 224;
+
+// LDS
+constexpr int kEimgAt = kImage;
+constexpr int kStripAt = 2 * kImage;                           // [16][kLdStrip] floats
+constexpr int kSmallLds = 4 * P * 16 * 4 > kStripAt + 16 * kLdStrip * 4 ? 4 * P * 16 * 4 : kStripAt + 16 * kLdStrip * 4;
+constexpr size_t kLds = kSmallLds + 6144;                      // 256 floats of reductions, then 5 x 256 words
+
+struct WideArgs {
+    const float* M;            // [K][p][p] finished matrices, or nullptr: sum the pieces
+    const float* partial;      // [pieces][p][p] (M == nullptr)
+    const int32_t* offsets;    // [K+1] (M == nullptr): the grouping the pieces were cut from
+    int piece;
+    const int32_t* counts;     // [K] or nullptr
+    float* D;
+    DictOps ops;
+    float* eig_sv;             // eigen mode
+    int32_t* fallback;
+    int32_t* iters_out;
+    int max_iters, K, teams;
+    unsigned char* data;       // [teams][kTeamBytes]
+    int* sync;                 // [teams][kSyncInts]
+    SqTotalArgs sq;
 };
-__host__ __device__ inline WideScratch carve(float* base, int K) {
-    WideScratch s;
-    s.A = base;
-    s.log = base + (size_t)K * P * P;
-    s.nsweeps = reinterpret_cast<int*>(s.log + (size_t)K * kLogFloatsPerBlock);
-    return s;
+
+__device__ __forceinline__ float half_sum(float x) {           // over 32 lanes
+    x = group_sum<16>(x);
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a0 = r[0], a1 = r[1];
+    return __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
 }
 
-// Tournament schedule: player P-1 stays, the others advance by one (mod P-1) per round.
-__device__ __forceinline__ void pair_init(int pi, int& ca, int& cb) {
-    ca = pi == 0 ? P - 1 : pi;
-    cb = pi == 0 ? 0 : P - 1 - pi;
+// Handing data from one workgroup to another: every thread waits for its own stores, then thread 0
+// releases for all; the other side polls, acquires and lets its workgroup go on.
+//
+// near: both workgroups run on the same XCD (HW_REG_XCC_ID, compared when the team first meets), so
+// its L2 is where they meet: a store that has been waited for is in it (L1 writes through), and a load
+// finds it there once L1 is invalidated; counters are atomics without a scope bit, which L2
+// executes.  That is how the workgroup scope works for a workgroup spread over several CUs.  Otherwise the
+// fences of the agent scope, which write L2 back and invalidate it: 3 us a barrier, 5 to 10 when all
+// CUs do it, against 1.
+__device__ __forceinline__ void stores_done() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
 }
-__device__ __forceinline__ void pair_next(int pi, int& ca, int& cb) {
-    if (pi == 0) {
-        cb = cb + 1;
-    } else {
-        ca = ca + 1 == P - 1 ? 0 : ca + 1;
-        cb = cb + 1 == P - 1 ? 0 : cb + 1;
-    }
+__device__ __forceinline__ int peek(int* p, bool near) {
+    if (!near) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int v = -1;                                // (an atomic that changes nothing: a load could be served by L1)
+    __hip_atomic_compare_exchange_strong(p, &v, -1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return v;
 }
-
-__global__ __launch_bounds__(1024) void wide_jacobi_kernel(const float* __restrict__ M,
-                                                           const int32_t* __restrict__ counts,
-                                                           float* scratch, int K, float done,
-                                                           int32_t* __restrict__ sweeps_out,
-                                                           const int32_t* __restrict__ only) {
-    constexpr int NT = 1024;
-    constexpr int TPP = 8;
-    constexpr int RPT = P / TPP;               // 32 rows per lane: 16 on chip, 16 in global memory
-    constexpr int HALF = RPT / 2;
-    static_assert(HALF * TPP == kRowsLds, "row split");
-    extern __shared__ float AL[];              // [P][LDA]: rows 0..127 of every column
-    __shared__ float red[NT / 64];
-
-    const WideScratch ws = carve(scratch, K);
-    const int j = blockIdx.x;
-    const int tid = threadIdx.x;
-    if (only != nullptr && only[j] == 0) return;   // uniform: another kernel has done this block
-    if (counts != nullptr && counts[j] == 0) { // uniform: block keeps its basis
-        if (tid == 0) {
-            ws.nsweeps[j] = 0;
-            if (sweeps_out != nullptr) sweeps_out[j] = 0;
+template <class F>
+__device__ __forceinline__ bool poll(bool near, F ready) {
+    for (int k = 0; k < kSpin; ++k) {
+        if (ready()) {
+            if (near) asm volatile("buffer_inv sc0" ::: "memory");
+            else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            return true;
         }
-        return;
+        __builtin_amdgcn_s_sleep(1);
     }
-    float* A = ws.A + (int64_t)j * P * P;      // column c = A[c*P .. c*P+P); rows >= 128 used here
-    float* log = ws.log + (int64_t)j * kLogFloatsPerBlock;
+    return false;
+}
+__device__ __forceinline__ void raise_to(int* p, int v, bool near) {
+    if (near) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A barrier of `size` workgroups that carries three floats of each of them.
+struct Team {
+    int* arrive;               // the counters: of the agent scope, then (a cache line on) near ones
+    float* red;                // [4][3][16]
+    int* ok;                   // LDS
+    int size, q;
+    int epoch, arrived;        // barriers so far; of this kind
+    bool near;
+
+    __device__ __forceinline__ bool sync(float a, float b = 0.f, float c = 0.f) {      // a, b, c: of thread 0
+        ++epoch;
+        ++arrived;
+        if (threadIdx.x == 0) {
+            float* slot = red + (epoch & 3) * 48 + q;
+            slot[0] = a;
+            slot[16] = b;
+            slot[32] = c;
+        }
+        stores_done();
+        if (threadIdx.x == 0) {
+            int* count = arrive + (near ? 32 : 0);
+            if (near) __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            else __hip_atomic_fetch_add(count, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            const int target = size * arrived;
+            *ok = poll(near, [&]() { return peek(count, near) >= target; });
+        }
+        __syncthreads();
+        return *ok != 0;
+    }
+    // The first barrier of a launch, which finds out whether the team is near: a counter of five bits per XCD.
+    // If it is, what was stored before is where the others look; if not, a barrier of the other kind follows.
+    __device__ __forceinline__ bool meet(unsigned long long* count) {
+        stores_done();
+        if (threadIdx.x == 0) {
+            int xcc;
+            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
+            const int field = 5 * (xcc < 8 ? xcc : 8);
+            __hip_atomic_fetch_add(count, 1ull << field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long v = 0;
+            const bool here = poll(true, [&]() {
+                v = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int n = 0;
+                for (int f = 0; f <= 40; f += 5) n += (int)(v >> f) & 31;
+                return n == size;
+            });
+            *ok = !here ? 0 : xcc < 8 && (int)(v >> field & 31) == size ? 2 : 1;
+        }
+        __syncthreads();
+        const int how = *ok;
+        near = how == 2;
+        if (how == 1) return sync(0.f);        // (begins with a barrier: *ok has been read)
+        return how != 0;
+    }
+    // value k of workgroup lane % size, from the last sync
+    __device__ __forceinline__ float value(int k) const {
+        return __hip_atomic_load(red + (epoch & 3) * 48 + k * 16 + (threadIdx.x & (size - 1)), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+// Maximum over the 16 lanes of a row of non-negative values; a NaN wins (its bits are the largest).
+__device__ __forceinline__ float row_max_nan(float x) {
+    unsigned u = __builtin_bit_cast(unsigned, x);
+    auto step = [&](auto f) { u = max(u, __builtin_bit_cast(unsigned, f(__builtin_bit_cast(float, u)))); };
+    step([](float v) { return dpp_f<kDppXor1>(v); });
+    step([](float v) { return dpp_f<kDppXor2>(v); });
+    step([](float v) { return dpp_f<kDppHalfMirror>(v); });
+    step([](float v) { return dpp_f<kDppRowMirror>(v); });
+    return __builtin_bit_cast(float, u);
+}
+// Sums over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (bitwise the same in all of them).
+__device__ __forceinline__ float sum_groups(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a0 = r[0], a1 = r[1];
+    const float y = __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
+    const unsigned w = __builtin_bit_cast(unsigned, y);
+    auto q = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const unsigned b0 = q[0], b1 = q[1];
+    return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+}
+
+// Where P_j comes from: a finished matrix, or the pieces [beg, end) summed in piece order.
+struct Source {
+    const float* base;         // of the first piece
+    int n;
+};
+// 16-byte units tid and tid + 512 of the 16 columns of strip s (16 KiB in one run)
+__device__ __forceinline__ void load_strip(const Source& src, int s, f32x4 (&v)[2]) {
+    constexpr int kInFlight = 8;
+    const f32x4* b = reinterpret_cast<const f32x4*>(src.base) + s * (16 * P / 4) + threadIdx.x;
+    for (int pc = 0; pc < src.n; pc += kInFlight) {
+        f32x4 w[kInFlight][2];
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+            if (pc + k < src.n) {              // uniform
+#pragma unroll
+                for (int u = 0; u < 2; ++u) w[k][u] = b[(int64_t)(pc + k) * (P * P / 4) + u * kNT];
+            }
+        if (pc == 0) v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+            if (pc + k < src.n) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) v[u] += w[k][u];
+            }
+    }
+}
+
+// D[j] rows of strip s from LDS ([16][kLdStrip]), and the same rows in the operand orders.  dn: 256 floats of LDS.
+__device__ __forceinline__ void emit_strip(const WideArgs& g, int j, int s, const float* strip, float* dn) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    f32x4* Dj = reinterpret_cast<f32x4*>(g.D + ((int64_t)j * P + s * 16) * P);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int e = tid + u * kNT;
+        Dj[e] = *reinterpret_cast<const f32x4*>(strip + (e >> 6) * kLdStrip + 4 * (e & 63));
+    }
+    if (g.ops.f32 == nullptr && g.ops.bf16 == nullptr && g.ops.f16 == nullptr) return;     // uniform
+    const int col = tid & 15, d8 = tid >> 4, grow = j * P + s * 16 + col;
+    float q2 = 0.f, r2 = 0.f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(strip + col * kLdStrip + 8 * d8 + 4 * u);
+        if (g.ops.f32 != nullptr) store_operand_f32<P>(g.ops.f32, grow, 2 * d8 + u, v);
+        if (g.ops.bf16 != nullptr) store_operand_split<P>(g.ops.bf16, grow, 2 * d8 + u, v);
+        if (g.ops.f16 != nullptr) store_operand_f16x2<P>(g.ops.f16, grow, 2 * d8 + u, split_f16x2_dict(v, q2, r2));
+    }
+    if (g.ops.f16 == nullptr) return;          // uniform
+    q2 = sum_groups(q2);
+    r2 = sum_groups(r2);
+    if (lane < 16) {
+        dn[wave * 16 + lane] = q2;
+        dn[128 + wave * 16 + lane] = r2;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        q2 = r2 = 0.f;
+        for (int w = 0; w < kWaves; ++w) {
+            q2 += dn[w * 16 + (lane & 15)];
+            r2 += dn[128 + w * 16 + (lane & 15)];
+        }
+        q2 = row16_max(q2);
+        r2 = row16_max(r2);
+        if (lane == 0) g.ops.dnorm[j * (P / 16) + s] = float2{sqrtf(q2), sqrtf(r2)};
+    }
+    __syncthreads();
+}
+
+enum class Outcome { done, left, dead };       // left: to the Jacobi SVD
+
+// Newton-Schulz for a block; strip `t.q` of the result is left in LDS at kStripAt.  first != nullptr: the team
+// has not met yet.
+__device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source& src, Team& t,
+                                                 unsigned long long* first, unsigned char* mem, unsigned char* lds,
+                                                 float* red, int& steps) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = lane >> 4, c16 = lane & 15;
+    unsigned char* ximg = lds;
+    unsigned char* eimg = lds + kEimgAt;
+    float* strip = reinterpret_cast<float*>(lds + kStripAt);
+
+    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};  // the six partial products, smallest first
+    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int kAhead = 4;
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(mem, 0, (int)kTeamBytes, 0x00027000);
+    auto mfma = [](u32x4 a, u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    };
+    auto at16 = [](const unsigned char* p) { return *reinterpret_cast<const u32x4*>(p); };
+    auto split = [](f32x4 lo, f32x4 hi, u32x4 (&out)[3]) {
+        const Bf16x3Pair a = split_bf16x3(lo.x, lo.y), b = split_bf16x3(lo.z, lo.w);
+        const Bf16x3Pair c = split_bf16x3(hi.x, hi.y), d = split_bf16x3(hi.z, hi.w);
+        out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+        out[1] = u32x4{a.mid, b.mid, c.mid, d.mid};
+        out[2] = u32x4{a.lo, b.lo, c.lo, d.lo};
+    };
+    // sum over the workgroup, the same in all threads; red: 256 floats, slot 0 .. 3
+    auto wg_sum = [&](float v, int slot) {
+        v = sum_groups(group_sum<16>(v));
+        if (lane == 0) red[slot * 8 + wave] = v;
+        __syncthreads();
+        float s = 0.f;
+        for (int w = 0; w < kWaves; ++w) s += red[slot * 8 + w];
+        return s;
+    };
+
+    // xr[k]: rows (2 wave + k) * 16 + grp * 4 .. +3 of column t.q * 16 + c16
+    f32x4 xr[2];
+    {
+        f32x4 v[2];
+        load_strip(src, t.q, v);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = tid + u * kNT;
+            *reinterpret_cast<f32x4*>(strip + (e >> 6) * kLdStrip + 4 * (e & 63)) = v[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            xr[k] = *reinterpret_cast<const f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4);
+    }
+    // Leaves the strip for the others (buffer buf) and in ximg.  Contraction step s of 32 = tiles 2s and
+    // 2s + 1: a lane holds rows grp * 4 .. of both, which is what an accumulator leaves it; the rows
+    // by ds_read_b64_tr_b16 (see polar_ns.hip), 4 columns of a row per lane.
+    auto publish = [&](int buf) {
+        u32x4 part[3];
+        split(xr[0], xr[1], part);
+        unsigned char* cols = mem + kColAt + ((size_t)buf * kTeam + t.q) * kImage;
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+            const int at = (wave * 3 + pl) * 1024 + lane * 16;
+            *reinterpret_cast<u32x4*>(ximg + at) = part[pl];
+            *reinterpret_cast<u32x4*>(cols + at) = part[pl];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+        unsigned char* rows = mem + kRowAt + (size_t)buf * kTeam * kImage;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds_ptr)(ximg + (wave * 3 + pl) * 1024 + (4 * grp + (c16 >> 2) + 16 * (c16 & 3)) * 16 + k * 8));
+                const int td = 2 * wave + k;
+                *reinterpret_cast<u32x2*>(rows + (size_t)((td * 8 + (t.q >> 1)) * 3 + pl) * 1024 + (t.q & 1) * 512 +
+                                          lane * 8) = __builtin_bit_cast(u32x2, r);
+            }
+    };
+    // smallest diagonal entry of G in this workgroup's columns, in thread 0 (two tiles lie on the diagonal;
+    // both in the wavefront of tile t.q)
+    auto least_diag = [&](const f32x4 (&gm)[2]) {
+        float v = 3e38f;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) v = gm[k][r];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
+        if (wave == (t.q >> 1) && lane == 0) red[255] = v;
+        __syncthreads();
+        return red[255];
+    };
+    // E = I - a2 G
+    auto make_e = [&](const f32x4 (&gm)[2], float a2, f32x4 (&e)[2]) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                e[k][r] = ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16 ? 1.f : 0.f) - a2 * gm[k][r];
+    };
+
+    // A product: contraction steps S0 .. S0 + 7, their A operands requested kAhead steps before, the B operands
+    // from an image in LDS one step before; two sums per tile, so that four matrix instructions are independent.
+    auto product = [&](auto& a, auto& request, auto& turn, const unsigned char* img, auto first_step, f32x4 (&out)[2]) {
+        constexpr int S0 = decltype(first_step)::value;
+        f32x4 sum[2][2] = {{zero4, zero4}, {zero4, zero4}};
+        u32x4 b[2][3];
+        auto read = [&](int s) {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) b[s & 1][pl] = at16(img + (turn(s) * 3 + pl) * 1024 + lane * 16);
+        };
+        read(S0);
+#pragma unroll
+        for (int s = S0; s < S0 + 8; ++s) {
+            if (s + 1 < S0 + 8) read(s + 1);
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    sum[k][q & 1] = mfma(a[s % kAhead][k][TA[q]], b[s & 1][TB[q]], sum[k][q & 1]);
+            if (s + kAhead < 16) request(s + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) out[k] = sum[k][0] + sum[k][1];
+    };
+
+    publish(0);
+    if (!(first != nullptr ? t.meet(first) : t.sync(0.f))) return Outcome::dead;
+    float prev = 3e38f;                        // |I - X^T X|_F^2 before the step before
+    NsScale scale;
+    for (int it = 0;; ) {
+        // A operands, contraction steps 0 .. 7 of X^T X, then 8 .. 15 = 0 .. 7 of X E.  Buffer loads: one
+        // descriptor, a scalar offset per load (as pointers the addresses alone take 100 registers).  Every
+        // wavefront of the team starts at another step: in step, they would all ask the same L2
+        // channels at a time.
+        const int cols = (int)kColAt + ((it & 1) * kTeam + 2 * wave) * kImage;
+        const int rows = (int)kRowAt + ((it & 1) * kTeam + 2 * wave) * kImage;
+        u32x4 a[kAhead][2][3];
+        auto turn = [&](int s) { return (s + wave + t.q) & 7; };
+        auto request = [&](int s) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    const int at = k * kImage + (turn(s) * 3 + pl) * 1024;
+                    if (s < 8) {
+                        a[s % kAhead][k][pl] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, cols + at, 0);
+                    } else {
+                        const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane * 8, rows + at, 0);
+                        const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane * 8 + 512, rows + at, 0);
+                        a[s % kAhead][k][pl] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    }
+                }
+        };
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) request(s);
+        f32x4 gm[2];
+        product(a, request, turn, ximg, std::integral_constant<int, 0>{}, gm);
+
+        float alpha = 1.f, fr = 0.f, least = 0.f;
+        bool last = false, known = false;
+        f32x4 e[2];
+        if (it == 0) {
+            float rs = 0.f, r2 = 0.f;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    rs += fabsf(gm[k][r]);
+                    r2 = fmaf(gm[k][r], gm[k][r], r2);
+                }
+            rs = sum_groups(rs);
+            r2 = sum_groups(r2);
+            if (lane < 16) {
+                red[wave * 16 + lane] = rs;
+                red[128 + wave * 16 + lane] = r2;
+            }
+            __syncthreads();
+            rs = r2 = 0.f;
+            for (int w = 0; w < kWaves; ++w) {
+                rs += red[w * 16 + c16];
+                r2 += red[128 + w * 16 + c16];
+            }
+            if (!t.sync(row_max_nan(rs), row_max_nan(r2), least_diag(gm))) return Outcome::dead;
+            const float rsmax = row_max_nan(t.value(0)), r2max = row_max_nan(t.value(1));
+            // zero, infinite, NaN or overflowing input: not for this iteration
+            if (!(rsmax > 1e-37f && rsmax < 3e37f)) return Outcome::left;
+            alpha = scale.first(rsmax, r2max, -row16_max(-t.value(2)));
+        } else {
+            make_e(gm, 1.f, e);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) fr = fmaf(e[k][r], e[k][r], fr);
+            fr = wg_sum(fr, it & 1);
+            least = least_diag(gm);
+            alpha = scale.next();
+            // Close to the end the team meets here to learn whether this is the last step, and exchanges the
+            // leading parts of E for its square.
+            if (prev < 4.f || it >= g.max_iters) {           // uniform over the team
+                u32x4 part[3];
+                split(e[0], e[1], part);
+                *reinterpret_cast<u32x4*>(eimg + wave * 3 * 1024 + lane * 16) = part[0];
+                *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)t.q * 8 + wave) * 1024 + lane * 16) = part[0];
+                if (!t.sync(fr)) return Outcome::dead;
+                prev = group_sum<16>(t.value(0));
+                known = true;
+                if (!(prev < 2.f * P)) return Outcome::left;   // NaN or diverging
+                last = prev < 1e-4f;           // |E|_F < 1e-2
+                if (!last && it >= g.max_iters) return Outcome::left;
+            }
+        }
+        u32x4 eq[3];
+        if (last) {                            // uniform: X (I + E / 2 + 3/8 E^2), E^2 from leading parts
+            alpha = 1.f;
+            f32x4 e2[2] = {zero4, zero4};
+            const int er = (int)kEAt + 2 * wave * 8 * 1024;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                u32x4 ea[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + (k * 8 + s) * 1024, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) e2[k] = mfma(ea[s], at16(eimg + s * 3 * 1024 + lane * 16), e2[k]);
+            }
+            __syncthreads();                   // eimg is rewritten
+#pragma unroll
+            for (int k = 0; k < 2; ++k) e[k] += 0.75f * e2[k];
+        } else {
+            make_e(gm, alpha * alpha, e);
+        }
+        split(e[0], e[1], eq);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(eimg + (wave * 3 + pl) * 1024 + lane * 16) = eq[pl];
+        __syncthreads();
+        f32x4 acc[2];
+        product(a, request, turn, eimg, std::integral_constant<int, 8>{}, acc);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) xr[k] = alpha * xr[k] + (0.5f * alpha) * acc[k];
+        ++it;
+        if (last) {
+            steps = it;
+            break;
+        }
+        publish(it & 1);
+        if (!t.sync(fr, least)) return Outcome::dead;
+        if (!known && it > 1) {
+            prev = group_sum<16>(t.value(0));
+            if (!(prev < 2.f * P)) return Outcome::left;
+            scale.seen(-row16_max(-t.value(1)));
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4) = xr[k];
+    __syncthreads();
+    return Outcome::done;
+}
+
+// One-sided Jacobi for block j by the workgroups q < 8 of a team (t: their barrier); version: the
+// numbers the column sets have reached, tbase what they all stand at.  Writes D.
+__device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source& src, Team& t, int* version, int& tbase,
+                                          unsigned char* mem, unsigned char* lds, float* red, int* flag) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hw = tid >> 5, l32 = tid & 31, q = t.q;
+    float* XA = reinterpret_cast<float*>(lds);  // [16 columns][256] each
+    float* XV = XA + 16 * P;
+    float* YA = XV + 16 * P;
+    float* YV = YA + 16 * P;
+    float* GA = reinterpret_cast<float*>(mem + kJaAt);         // [256 columns][256]
+    float* GV = reinterpret_cast<float*>(mem + kJvAt);
+    float* Gsig = reinterpret_cast<float*>(mem + kSmallAt) + 384;
+    float* Gvinv = Gsig + P;
+    auto copy4 = [&](float* dst, const float* from) {          // 16 columns
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            reinterpret_cast<f32x4*>(dst)[tid + u * kNT] = reinterpret_cast<const f32x4*>(from)[tid + u * kNT];
+    };
 
     // scale by 1 / max|entry| (the orthogonal factor does not depend on scale)
-    const float* Mj = M + (int64_t)j * P * P;
-    float mx = 0.f;
-    for (int e = tid; e < P * P; e += NT) mx = fmaxf(mx, fabsf(Mj[e]));
+    float mx = 0.f, scale;
+    {
+        f32x4 v[2][2];
+        load_strip(src, q, v[0]);
+        load_strip(src, q + 8, v[1]);
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if ((tid & 63) == 0) red[tid >> 6] = mx;
-    __syncthreads();
-    mx = 0.f;
-    for (int w = 0; w < NT / 64; ++w) mx = fmaxf(mx, red[w]);
-    const float scale = mx > 0.f ? 1.f / mx : 0.f;
-
-    // A = scale * P_j
-    for (int o = tid; o < P * P / 4; o += NT) {
-        const int c = o / (P / 4), r4 = (o % (P / 4)) * 4;
-        f32x4 s4 = *reinterpret_cast<const f32x4*>(&Mj[c * P + r4]);
-        s4 *= scale;
-        if (r4 < kRowsLds) *reinterpret_cast<f32x4*>(&AL[c * LDA + r4]) = s4;
-        else *reinterpret_cast<f32x4*>(&A[c * P + r4]) = s4;
-    }
-    __threadfence_block();
-    __syncthreads();
-
-    // lane `sub` of a pair owns rows sub*16..+15 (LDS) and 128 + sub*16..+15 (global), so
-    // every lane has both kinds of access in flight at once
-    const int pi = tid / TPP, sub = tid % TPP;
-    const int rl = sub * HALF;                 // first on-chip row
-    const int rg = kRowsLds + sub * HALF;      // first global row
-    int sweeps_done = 0;
-    for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-        int rotated = 0;
-        int ca, cb;
-        pair_init(pi, ca, cb);
-        float* lg = log + ((size_t)sweep * kSteps * kPairs + pi) * 2;
-        for (int step = 0; step < kSteps; ++step, lg += kPairs * 2) {
-            const int ci = min(ca, cb), cj = max(ca, cb);
-            float* gi = A + ci * P + rg;
-            float* gj = A + cj * P + rg;
-            float* li = AL + ci * LDA + rl;
-            float* lj = AL + cj * LDA + rl;
-            float x[RPT], y[RPT];
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int t = 0; t < HALF; t += 4) {
-                const f32x4 a4 = *reinterpret_cast<const f32x4*>(gi + t);
-                const f32x4 b4 = *reinterpret_cast<const f32x4*>(gj + t);
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    x[HALF + t + e] = a4[e];
-                    y[HALF + t + e] = b4[e];
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < HALF; t += 4) {
-                const f32x4 a4 = *reinterpret_cast<const f32x4*>(li + t);
-                const f32x4 b4 = *reinterpret_cast<const f32x4*>(lj + t);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    x[t + e] = a4[e];
-                    y[t + e] = b4[e];
-                }
-            }
-            float alpha = 0.f, beta = 0.f, gamma = 0.f;
-#pragma unroll
-            for (int t = 0; t < RPT; ++t) {
-                alpha += x[t] * x[t];
-                beta += y[t] * y[t];
-                gamma += x[t] * y[t];
-            }
-            alpha = group_sum<TPP>(alpha);
-            beta = group_sum<TPP>(beta);
-            gamma = group_sum<TPP>(gamma);
-            const float d = beta - alpha, g2 = 2.f * gamma;
-            const float hh = d * d + g2 * g2;
-            const float g2ab = gamma * gamma, ab = alpha * beta;
-            if (g2ab > (done * done) * ab) rotated = 1;
-            float cs = 1.f, sn = 0.f;
-            if (g2ab > (kTol * kTol) * ab && hh > 1e-36f) {
-                // cos(2 theta) = |d| / hypot(d, 2 gamma), |theta| <= pi/4
-                const float r = __builtin_amdgcn_rsqf(hh);
-                const float w = 0.5f + 0.5f * (fabsf(d) * r);
-                const float rc = __builtin_amdgcn_rsqf(w);
-                cs = w * rc;
-                sn = copysignf(0.5f * rc * r, d) * g2;
-#pragma unroll
-                for (int t = 0; t < HALF; t += 4) {
-                    f32x4 na, nb;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        na[e] = cs * x[HALF + t + e] - sn * y[HALF + t + e];
-                        nb[e] = sn * x[HALF + t + e] + cs * y[HALF + t + e];
-                    }
-                    *reinterpret_cast<f32x4*>(gi + t) = na;
-                    *reinterpret_cast<f32x4*>(gj + t) = nb;
-                }
-#pragma unroll
-                for (int t = 0; t < HALF; t += 4) {
-                    f32x4 na, nb;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        na[e] = cs * x[t + e] - sn * y[t + e];
-                        nb[e] = sn * x[t + e] + cs * y[t + e];
-                    }
-                    *reinterpret_cast<f32x4*>(li + t) = na;
-                    *reinterpret_cast<f32x4*>(lj + t) = nb;
-                }
-            }
-            if (sub == 0) {                    // (ci, cj) of a round follow from the schedule
-                lg[0] = cs;
-                lg[1] = sn;
-            }
-            pair_next(pi, ca, cb);
-            __threadfence_block();
-            __syncthreads();
-        }
-        sweeps_done = sweep + 1;
-        if (!__syncthreads_or(rotated)) break;
-    }
-    if (tid == 0) {
-        ws.nsweeps[j] = sweeps_done;
-        if (sweeps_out != nullptr) sweeps_out[j] = sweeps_done;
-    }
-
-    // the on-chip rows go back next to the others for the finishing kernel
-    for (int o = tid; o < P * kRowsLds / 4; o += NT) {
-        const int c = o / (kRowsLds / 4), r4 = (o % (kRowsLds / 4)) * 4;
-        *reinterpret_cast<f32x4*>(&A[c * P + r4]) = *reinterpret_cast<const f32x4*>(&AL[c * LDA + r4]);
-    }
-}
-
-// V <- I * (logged rotations), four rows per wavefront.
-constexpr int kReplayRows = 4;
-
-__global__ __launch_bounds__(256) void wide_replay_kernel(const int32_t* __restrict__ counts,
-                                                          float* Vst,
-                                                          const float* scratch, int K,
-                                                          const int32_t* __restrict__ only) {
-    __shared__ float rows_all[4][kReplayRows][P];
-    const WideScratch ws = carve(const_cast<float*>(scratch), K);
-    const int j = blockIdx.x;
-    if (only != nullptr && only[j] == 0) return;   // uniform
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row0 = (blockIdx.y * 4 + wave) * kReplayRows;
-    float* V = Vst + (int64_t)j * P * P;       // column-major: V[c*P + r]
-    float(*rows)[P] = rows_all[wave];
-
-    if (counts != nullptr && counts[j] == 0) return;   // uniform: block keeps its basis, V unused
-#pragma unroll
-    for (int rr = 0; rr < kReplayRows; ++rr)
-        for (int c = lane; c < P; c += 64) rows[rr][c] = c == row0 + rr ? 1.f : 0.f;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
-    const int ns = ws.nsweeps[j];
-    const float* log = ws.log + (int64_t)j * kLogFloatsPerBlock;
-    const int p0 = lane, p1 = lane + 64;       // this lane's pairs (neighbouring lanes touch
-                                               // neighbouring columns: no bank conflicts)
-    for (int sweep = 0; sweep < ns; ++sweep) {
-        int ca0, cb0, ca1, cb1;
-        pair_init(p0, ca0, cb0);
-        pair_init(p1, ca1, cb1);
-        const float2* lg = reinterpret_cast<const float2*>(log + (size_t)sweep * kSteps * kPairs * 2);
-        float2 n0 = lg[p0], n1 = lg[p1];
-        for (int step = 0; step < kSteps; ++step) {
-            const float2 r0 = n0, r1 = n1;     // (cos, sin) of this lane's two pairs
-            if (step + 1 < kSteps) {
-                n0 = lg[(size_t)(step + 1) * kPairs + p0];
-                n1 = lg[(size_t)(step + 1) * kPairs + p1];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            {
-                const int ci = min(ca0, cb0), cj = max(ca0, cb0);
-#pragma unroll
-                for (int rr = 0; rr < kReplayRows; ++rr) {
-                    const float pv = rows[rr][ci], qv = rows[rr][cj];
-                    rows[rr][ci] = r0.x * pv - r0.y * qv;
-                    rows[rr][cj] = r0.y * pv + r0.x * qv;
-                }
-            }
-            {
-                const int ci = min(ca1, cb1), cj = max(ca1, cb1);
-#pragma unroll
-                for (int rr = 0; rr < kReplayRows; ++rr) {
-                    const float pv = rows[rr][ci], qv = rows[rr][cj];
-                    rows[rr][ci] = r1.x * pv - r1.y * qv;
-                    rows[rr][cj] = r1.y * pv + r1.x * qv;
-                }
-            }
-            pair_next(p0, ca0, cb0);
-            pair_next(p1, ca1, cb1);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();   // the next round pairs other columns
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int rr = 0; rr < kReplayRows; ++rr)
-        for (int c = lane; c < P; c += 64) V[c * P + row0 + rr] = rows[rr][c];
-}
-
-__global__ __launch_bounds__(1024) void wide_finish_kernel(const float* __restrict__ M,
-                                                           const int32_t* __restrict__ counts,
-                                                           float* __restrict__ D, float* Vst,
-                                                           float* scratch, int K,
-                                                           float* __restrict__ eig_sv,
-                                                           const int32_t* __restrict__ only) {
-    constexpr int NT = 1024;
-    __shared__ float sig[P];
-    __shared__ float coefs[P];
-    __shared__ float vec[P];
-    __shared__ int isbad[P];
-    __shared__ int shared_i[2];
-
-    const WideScratch ws = carve(scratch, K);
-    const int j = blockIdx.x;
-    const int tid = threadIdx.x;
-    if (only != nullptr && only[j] == 0) return;       // uniform
-    if (counts != nullptr && counts[j] == 0) return;   // uniform: block keeps its basis
-    float* A = ws.A + (int64_t)j * P * P;
-    float* V = Vst + (int64_t)j * P * P;
-
-    // sigma = column norms, U = A / sigma, V columns renormalised
-    if (tid < P) {
-        float s = 0.f, v = 0.f;
-        for (int r = 0; r < P; ++r) {
-            s += A[tid * P + r] * A[tid * P + r];
-            v += V[tid * P + r] * V[tid * P + r];
-        }
-        sig[tid] = sqrtf(s);
-        vec[tid] = 1.f / sqrtf(v);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        float smax = 0.f;
-        for (int c = 0; c < P; ++c) smax = fmaxf(smax, sig[c]);
-        int nb = 0;
-        const float thr = smax * 1e-6f;
-        for (int c = 0; c < P; ++c) {
-            isbad[c] = !(sig[c] > thr);
-            nb += isbad[c];
-        }
-        shared_i[0] = nb;
-    }
-    __syncthreads();
-    for (int e = tid; e < P * P; e += NT) {
-        const int c = e / P;
-        A[e] = isbad[c] ? 0.f : A[e] / sig[c];
-        V[e] *= vec[c];
-    }
-    __threadfence_block();
-    __syncthreads();
-
-    // Eigen mode (see polar_kernel): atoms = eigenvectors (columns of V) by descending
-    // eigenvalue, eig_sv = square roots of the eigenvalues.  The scale the Jacobi kernel
-    // applied (1 / max|entry| of P_j) is recomputed here.
-    if (eig_sv != nullptr) {
-        const float* Mj = M + (int64_t)j * P * P;
-        float mx = 0.f;
-        for (int e = tid; e < P * P; e += NT) mx = fmaxf(mx, fabsf(Mj[e]));
+                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(v[s][u][e]));
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-        if ((tid & 63) == 0) coefs[tid >> 6] = mx;
+        if (lane == 0) red[wave] = mx;
         __syncthreads();
-        mx = 0.f;
-        for (int w = 0; w < NT / 64; ++w) mx = fmaxf(mx, coefs[w]);
-        __syncthreads();
-        if (tid < P) {
-            int rank = 0;
-            for (int c = 0; c < P; ++c) rank += sig[c] > sig[tid] || (sig[c] == sig[tid] && c < tid);
-            isbad[tid] = rank;
-            eig_sv[(int64_t)j * P + rank] = sqrtf(sig[tid] * vec[tid] * mx);   // |A_c| / |V_c|, rescaled
+        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, red[w]);
+        if (!t.sync(mx)) return Outcome::dead;
+        mx = row16_max(t.value(0));
+        scale = mx > 0.f ? 1.f / mx : 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = tid + u * kNT, c = e >> 6, r = 4 * (e & 63);
+            reinterpret_cast<f32x4*>(XA)[e] = v[0][u] * scale;
+            reinterpret_cast<f32x4*>(YA)[e] = v[1][u] * scale;
+            f32x4 ix, iy;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ix[k] = r + k == 16 * q + c ? 1.f : 0.f;
+                iy[k] = r + k == 16 * (q + 8) + c ? 1.f : 0.f;
+            }
+            reinterpret_cast<f32x4*>(XV)[e] = ix;
+            reinterpret_cast<f32x4*>(YV)[e] = iy;
         }
-        __syncthreads();
-        float* Dj = D + (int64_t)j * P * P;
-        for (int e = tid; e < P * P; e += NT) Dj[isbad[e / P] * P + (e % P)] = V[e];
-        return;                                // uniform
     }
 
-    if (shared_i[0] > 0) {                     // uniform: complete the vanished columns
+    // half a wavefront rotates one pair of columns: rows 2 l32 + 64 k + {0, 1}
+    int rotated = 0;
+    auto get = [&](const float* col, float (&v)[8]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float2 w = *reinterpret_cast<const float2*>(col + 2 * l32 + 64 * k);
+            v[2 * k] = w.x;
+            v[2 * k + 1] = w.y;
+        }
+    };
+    auto put = [&](float* col, const float (&v)[8]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) *reinterpret_cast<float2*>(col + 2 * l32 + 64 * k) = float2{v[2 * k], v[2 * k + 1]};
+    };
+    auto rotate = [&](float (&x)[8], float (&y)[8], float (&u)[8], float (&v)[8]) {
+        float al = 0.f, be = 0.f, ga = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            al += x[k] * x[k];
+            be += y[k] * y[k];
+            ga += x[k] * y[k];
+        }
+        al = half_sum(al);
+        be = half_sum(be);
+        ga = half_sum(ga);
+        const float d = be - al, g2 = 2.f * ga, hh = d * d + g2 * g2, gg = ga * ga, ab = al * be;
+        if (gg > (kPolarDone * kPolarDone) * ab) rotated = 1;
+        if (!(gg > (kTol * kTol) * ab && hh > 1e-36f)) return false;
+        // cos(2 theta) = |d| / hypot(d, 2 gamma), |theta| <= pi/4
+        const float r = __builtin_amdgcn_rsqf(hh), w = 0.5f + 0.5f * (fabsf(d) * r), rc = __builtin_amdgcn_rsqf(w);
+        const float cs = w * rc, sn = copysignf(0.5f * rc * r, d) * g2;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float a = x[k], b = y[k];
+            x[k] = cs * a - sn * b;
+            y[k] = sn * a + cs * b;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float a = u[k], b = v[k];
+            u[k] = cs * a - sn * b;
+            v[k] = sn * a + cs * b;
+        }
+        return true;
+    };
+    // the two sets of a round: si stays while si is the same
+    auto sets = [&](int r, int& si, int& sj) {
+        if (r < 8) {
+            si = q;
+            sj = 8 + ((q + r) & 7);
+        } else if (r < 12) {
+            si = 8 * (q >> 2) + (q & 3);
+            sj = 8 * (q >> 2) + 4 + ((q + r) & 3);
+        } else if (r < 14) {
+            si = 4 * (q >> 1) + (q & 1);
+            sj = 4 * (q >> 1) + 2 + ((q + r) & 1);
+        } else {
+            si = 2 * q;
+            sj = 2 * q + 1;
+        }
+    };
+    auto moves = [](int r) { return r == 0 || r == 8 || r == 12 || r == 14; };     // si is new in round r
+
+    float x[8], u[8];
+    int sweeps = 0;
+    for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+        rotated = 0;
+        for (int r = 0; r < 15; ++r) {
+            int si, sj;
+            sets(r, si, sj);
+            const int now = tbase + sweep * 15 + r;
+            if (sweep > 0 || r > 0) {
+                if (tid == 0)
+                    *flag = poll(t.near, [&]() {
+                        return peek(version + sj, t.near) >= now && (!moves(r) || peek(version + si, t.near) >= now);
+                    });
+                __syncthreads();
+                if (*flag == 0) return Outcome::dead;
+                copy4(YA, GA + sj * 16 * P);
+                copy4(YV, GV + sj * 16 * P);
+                if (r == 0) {
+                    copy4(XA, GA + si * 16 * P);
+                    copy4(XV, GV + si * 16 * P);
+                } else if (moves(r)) {
+                    get(GA + (si * 16 + hw) * P, x);
+                    get(GV + (si * 16 + hw) * P, u);
+                }
+            }
+            __syncthreads();
+            if (r == 0) {                      // the pairs inside the sets, a tournament of 16
+                const int pi = hw & 7;
+                float* A = hw < 8 ? XA : YA;
+                float* V = hw < 8 ? XV : YV;
+                for (int s = 0; s < 15; ++s) {
+                    const int ca = pi == 0 ? 15 : (pi + s) % 15, cb = pi == 0 ? s : (15 - pi + s) % 15;
+                    const int lo = min(ca, cb), hi = max(ca, cb);
+                    float y[8], v[8];
+                    get(A + lo * P, x);
+                    get(A + hi * P, y);
+                    get(V + lo * P, u);
+                    get(V + hi * P, v);
+                    if (rotate(x, y, u, v)) {
+                        put(A + lo * P, x);
+                        put(A + hi * P, y);
+                        put(V + lo * P, u);
+                        put(V + hi * P, v);
+                    }
+                    __syncthreads();
+                }
+                get(XA + hw * P, x);
+                get(XV + hw * P, u);
+            }
+            for (int s = 0; s < 16; ++s) {     // the pairs across the sets
+                const int cy = (hw + s) & 15;
+                float y[8], v[8];
+                get(YA + cy * P, y);
+                get(YV + cy * P, v);
+                if (rotate(x, y, u, v)) {
+                    put(YA + cy * P, y);
+                    put(YV + cy * P, v);
+                }
+                __syncthreads();
+            }
+            copy4(GA + sj * 16 * P, YA);
+            copy4(GV + sj * 16 * P, YV);
+            const bool leaves = moves(r == 14 ? 0 : r + 1);
+            if (leaves) {
+                put(GA + (si * 16 + hw) * P, x);
+                put(GV + (si * 16 + hw) * P, u);
+            }
+            stores_done();
+            if (tid == 0) {
+                raise_to(version + sj, now + 1, t.near);
+                if (leaves) raise_to(version + si, now + 1, t.near);
+            }
+        }
+        sweeps = sweep + 1;
+        if (tid == 0) *flag = 0;
+        __syncthreads();
+        if (rotated) *flag = 1;
+        __syncthreads();
+        const float mine = *flag ? 1.f : 0.f;
+        if (!t.sync(mine)) return Outcome::dead;
+        if (!(row16_max(t.value(0)) > 0.f)) break;             // uniform over the team
+    }
+    tbase += sweeps * 15;
+    if (tid == 0 && q == 0 && g.iters_out != nullptr) g.iters_out[j] = sweeps;
+
+    // sigma = column norms; columns of V renormalised.  Sets 2q (x, u) and 2q + 1 (LDS).
+    float y[8], v[8];
+    get(YA + hw * P, y);
+    get(YV + hw * P, v);
+    auto norm2 = [&](const float (&w)[8]) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += w[k] * w[k];
+        return half_sum(s);
+    };
+    const int cx = 32 * q + hw, cyy = 32 * q + 16 + hw;        // their columns
+    const float sx = sqrtf(norm2(x)), sy = sqrtf(norm2(y)), ix = 1.f / sqrtf(norm2(u)), iy = 1.f / sqrtf(norm2(v));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        u[k] *= ix;
+        v[k] *= iy;
+    }
+    if (l32 == 0) {
+        Gsig[cx] = sx;
+        Gsig[cyy] = sy;
+        Gvinv[cx] = ix;
+        Gvinv[cyy] = iy;
+    }
+    const bool eig = g.eig_sv != nullptr;
+    if (!eig) {                                // (A stands in memory already)
+        put(GV + cx * P, u);
+        put(GV + cyy * P, v);
+    }
+    if (!t.sync(0.f)) return Outcome::dead;
+    float* sig = red + 256;                    // [256] words each
+    int* isbad = reinterpret_cast<int*>(red + 512);
+    float* vec = red + 768;
+    float* coefs = red + 1024;
+    if (tid < P) sig[tid] = Gsig[tid];
+    __syncthreads();
+
+    if (eig) {
+        // atoms = eigenvectors (columns of V) by descending eigenvalue, eig_sv = square roots of the
+        // eigenvalues: |A_c| / |V_c|, rescaled
+        auto rank_of = [&](float s, int c) {
+            float n = 0.f;
+            for (int k = 0; k < 8; ++k) {
+                const int o = l32 + 32 * k;
+                n += sig[o] > s || (sig[o] == s && o < c) ? 1.f : 0.f;
+            }
+            return min(max((int)half_sum(n), 0), P - 1);
+        };
+        const int rx = rank_of(sx, cx), ry = rank_of(sy, cyy);
+        if (l32 == 0) {
+            g.eig_sv[(int64_t)j * P + rx] = sqrtf(sx * ix * mx);
+            g.eig_sv[(int64_t)j * P + ry] = sqrtf(sy * iy * mx);
+        }
+        put(g.D + ((int64_t)j * P + rx) * P, u);
+        put(g.D + ((int64_t)j * P + ry) * P, v);
+        return Outcome::done;
+    }
+
+    float smax = 0.f;
+    for (int c = 0; c < P; ++c) smax = fmaxf(smax, sig[c]);
+    const float thr = smax * 1e-6f;
+    if (tid == 0) *flag = 0;
+    __syncthreads();
+    if (tid < P) {
+        isbad[tid] = !(sig[tid] > thr);
+        if (isbad[tid]) *flag = 1;
+    }
+    __syncthreads();
+    const bool bad = *flag != 0;               // uniform over the team
+    if (bad && q != 0) return Outcome::done;
+    if (bad) {                                 // one workgroup completes the vanished columns
+        for (int e = tid; e < P * P; e += kNT) GA[e] = isbad[e / P] ? 0.f : GA[e] / sig[e / P];
+        __syncthreads();
         for (int c = 0; c < P; ++c) {
             if (!isbad[c]) continue;           // uniform
             if (tid < P) {
                 float s = 0.f;
-                for (int cc = 0; cc < P; ++cc) s += A[cc * P + tid] * A[cc * P + tid];
+                for (int cc = 0; cc < P; ++cc) s += GA[cc * P + tid] * GA[cc * P + tid];
                 vec[tid] = s;
             }
             __syncthreads();
@@ -378,26 +841,26 @@ __global__ __launch_bounds__(1024) void wide_finish_kernel(const float* __restri
                 int best = 0;
                 for (int r = 1; r < P; ++r)
                     if (vec[r] < vec[best]) best = r;
-                shared_i[1] = best;
+                *flag = best;
             }
             __syncthreads();
-            const int rs = shared_i[1];
+            const int rs = *flag;
             float w = 0.f;
             if (tid < P) {
                 float s = (tid == rs) ? 1.f : 0.f;
-                for (int cc = 0; cc < P; ++cc) s -= A[cc * P + rs] * A[cc * P + tid];
+                for (int cc = 0; cc < P; ++cc) s -= GA[cc * P + rs] * GA[cc * P + tid];
                 w = s;
                 vec[tid] = s;
             }
             __syncthreads();
             if (tid < P) {
                 float dsum = 0.f;
-                for (int r = 0; r < P; ++r) dsum += A[tid * P + r] * vec[r];
+                for (int r = 0; r < P; ++r) dsum += GA[tid * P + r] * vec[r];
                 coefs[tid] = dsum;
             }
             __syncthreads();
             if (tid < P) {
-                for (int cc = 0; cc < P; ++cc) w -= coefs[cc] * A[cc * P + tid];
+                for (int cc = 0; cc < P; ++cc) w -= coefs[cc] * GA[cc * P + tid];
             }
             __syncthreads();
             if (tid < P) vec[tid] = w;
@@ -405,53 +868,158 @@ __global__ __launch_bounds__(1024) void wide_finish_kernel(const float* __restri
             if (tid < P) {
                 float nrm = 0.f;
                 for (int r = 0; r < P; ++r) nrm += vec[r] * vec[r];
-                A[c * P + tid] = w / sqrtf(nrm);
+                GA[c * P + tid] = w / sqrtf(nrm);
             }
-            __threadfence_block();
             __syncthreads();
         }
     }
-
-    // Q = U V^T, atom-major: D[j][k][r] = sum_c U[r][c] V[k][c]
-    float* Dj = D + (int64_t)j * P * P;
-    for (int tile = tid; tile < (P / 4) * (P / 4); tile += NT) {
-        const int q0 = 4 * (tile % (P / 4)), k0 = 4 * (tile / (P / 4));
+    // Q = U V^T, atom-major: D[j][k][r] = sum_c U[r][c] V[k][c]; 32 rows k at a time
+    if (tid < P) sig[tid] = bad ? 1.f : 1.f / sig[tid];
+    __syncthreads();
+    float* strip = reinterpret_cast<float*>(lds);              // [2][16][kLdStrip] (X and Y are dead)
+    for (int sl = bad ? 0 : q; sl < (bad ? kJacTeam : q + 1); ++sl) {
+        const int q0 = 4 * lane, k0 = 4 * wave;
         float o[4][4] = {};
         for (int c = 0; c < P; ++c) {
-            const f32x4 u = *reinterpret_cast<const f32x4*>(&A[c * P + q0]);
-            const f32x4 v = *reinterpret_cast<const f32x4*>(&V[c * P + k0]);
+            const f32x4 uu = *reinterpret_cast<const f32x4*>(GA + c * P + q0) * sig[c];
+            const f32x4 vv = *reinterpret_cast<const f32x4*>(GV + c * P + 32 * sl + k0);
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) o[a][b] += v[a] * u[b];
+                for (int b = 0; b < 4; ++b) o[a][b] += vv[a] * uu[b];
         }
+        __syncthreads();
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            f32x4 row = {o[a][0], o[a][1], o[a][2], o[a][3]};
-            *reinterpret_cast<f32x4*>(&Dj[(k0 + a) * P + q0]) = row;
+        for (int a = 0; a < 4; ++a)
+            *reinterpret_cast<f32x4*>(strip + (k0 + a) * kLdStrip + q0) = f32x4{o[a][0], o[a][1], o[a][2], o[a][3]};
+        __syncthreads();
+        emit_strip(g, j, 2 * sl, strip, red);
+        emit_strip(g, j, 2 * sl + 1, strip + 16 * kLdStrip, red);
+    }
+    return Outcome::done;
+}
+
+// NS: Newton-Schulz first; otherwise Jacobi for every block.
+template <bool NS>
+__global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    // The 16 workgroups of a team lie eight apart: workgroups go round the eight XCDs, so a team shares an L2.
+    const int team_wgs = (g.teams + 7) / 8 * 128;
+    if ((int)blockIdx.x >= team_wgs) {         // uniform: the workgroups of the squared-error total
+        const int b = (int)blockIdx.x - team_wgs;
+        if (g.sq.out != nullptr && b < g.sq.nb)
+            sq_total_part<kNT>(g.sq.err, g.sq.m, b, g.sq.nb, g.sq.part, g.sq.counter, g.sq.out,
+                               reinterpret_cast<double*>(lds));
+        return;
+    }
+    const int team = (int)blockIdx.x / 128 * 8 + (int)blockIdx.x % 8, q = (int)blockIdx.x % 128 / 8;
+    if (team >= g.teams) return;               // uniform
+    float* red = reinterpret_cast<float*>(lds + kSmallLds);
+    int* flag = reinterpret_cast<int*>(red + 1280);
+    unsigned char* mem = g.data + (size_t)team * kTeamBytes;
+    int* sync = g.sync + team * kSyncInts;
+    float* small = reinterpret_cast<float*>(mem + kSmallAt);
+    Team all = {sync + kArriveAt, small, flag, kTeam, q, 0, 0, false};
+    Team eight = {sync + kArriveJacAt, small + 192, flag + 1, kJacTeam, q, 0, 0, false};
+    int tbase = 0;
+
+    unsigned long long* count = reinterpret_cast<unsigned long long*>(sync + kMeetAt);
+    bool alive = NS || all.meet(count), met = !NS;
+    eight.near = all.near;
+
+    for (int j = team; alive && j < g.K; j += g.teams) {
+        Source src;
+        bool empty;
+        if (g.M != nullptr) {
+            src = {g.M + (int64_t)j * P * P, 1};
+            empty = g.counts != nullptr && g.counts[j] == 0;
+        } else {
+            int before = 0, own = 0;           // every wavefront for itself; one trip for up to 64 blocks
+            for (int jj = lane; jj <= j; jj += 64) {
+                own = g.offsets[jj + 1] - g.offsets[jj];
+                before += (own + g.piece - 1) / g.piece;
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+            const int n_j = __builtin_amdgcn_readlane(own, j & 63), pieces = (n_j + g.piece - 1) / g.piece;
+            src = {g.partial + (int64_t)(__builtin_amdgcn_readfirstlane(before) - pieces) * P * P, pieces};
+            empty = n_j == 0;
         }
+        if (empty) {                           // uniform over the team: block keeps its basis
+            if (q == 0 && tid == 0) {
+                g.fallback[j] = 0;
+                if (g.iters_out != nullptr) g.iters_out[j] = 0;
+            }
+            continue;
+        }
+        Outcome how = Outcome::left;
+        if constexpr (NS) {
+            int steps = 0;
+            how = newton_schulz(g, src, all, met ? nullptr : count, mem, lds, red, steps);
+            met = true;
+            eight.near = all.near;
+            if (q == 0 && tid == 0) {
+                g.fallback[j] = how == Outcome::left;
+                if (g.iters_out != nullptr && how == Outcome::done) g.iters_out[j] = -steps;
+            }
+            if (how == Outcome::done) emit_strip(g, j, q, reinterpret_cast<const float*>(lds + kStripAt), red);
+        }
+        if (how == Outcome::left) {
+            __syncthreads();
+            how = q < kJacTeam ? jacobi(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag) : Outcome::done;
+        }
+        if (how == Outcome::dead) {            // nothing to be had from the others: say so
+            for (int e = tid; e < 16 * P; e += kNT) g.D[((int64_t)j * P + q * 16) * P + e] = __builtin_nanf("");
+            alive = false;
+        }
+        __syncthreads();
+    }
+    // the last workgroup of the team to leave sets the counters back
+    __syncthreads();
+    if (tid == 0) *flag = __hip_atomic_fetch_add(sync + kExitAt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == kTeam - 1;
+    __syncthreads();
+    if (*flag != 0 && tid < kSyncInts) {
+        if (all.near && tid != kArriveAt && tid != kExitAt && tid < kMeetAt)
+            __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else
+            __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 }  // namespace
 
-size_t polar_wide_scratch_bytes(int K) {
-    return ((size_t)K * P * P + (size_t)K * kLogFloatsPerBlock) * sizeof(float) + (size_t)K * sizeof(int);
-}
+size_t polar_wide_scratch_bytes(int K) { return (size_t)(K < kMaxTeams ? K : kMaxTeams) * kTeamBytes; }
+size_t polar_wide_sync_bytes(int K) { return (size_t)(K < kMaxTeams ? K : kMaxTeams) * kSyncInts * sizeof(int); }
 
-hipError_t launch_polar_wide(int K, const float* M, const int32_t* counts, float* D, float* vwork,
-                             float* jac_a, float* eig_sv, int32_t* sweeps, const int32_t* only,
-                             LdsRaised* raised, hipStream_t st) {
-    if (vwork == nullptr || jac_a == nullptr || raised == nullptr) return hipErrorInvalidValue;
-    const size_t lds = (size_t)P * LDA * sizeof(float);
-    hipError_t e = raised->ensure(reinterpret_cast<const void*>(&wide_jacobi_kernel), lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(wide_jacobi_kernel, dim3(K), dim3(1024), lds, st, M, counts, jac_a, K, kPolarDone,
-                       sweeps, only);
-    hipLaunchKernelGGL(wide_replay_kernel, dim3(K, P / (4 * kReplayRows)), dim3(256), 0, st, counts,
-                       vwork, jac_a, K, only);
-    hipLaunchKernelGGL(wide_finish_kernel, dim3(K), dim3(1024), 0, st, M, counts, D, vwork, jac_a, K,
-                       eig_sv, only);
+hipError_t launch_polar_wide(int K, const float* M, const float* partial, const int32_t* offsets, int piece,
+                             const int32_t* counts, float* D, const DictOps& ops, bool newton_schulz_first,
+                             float* eig_sv, const Workspace& ws, const SqTotalArgs& sq, hipStream_t st) {
+    constexpr int kMaxIters = 26;
+    if (ws.wide == nullptr || ws.wide_sync == nullptr || ws.raised == nullptr) return hipErrorInvalidValue;
+    WideArgs a;
+    a.M = M;
+    a.partial = partial;
+    a.offsets = offsets;
+    a.piece = piece;
+    a.counts = counts;
+    a.D = D;
+    a.ops = ops;
+    a.eig_sv = eig_sv;
+    a.fallback = ws.ns_fallback;
+    a.iters_out = ws.sweeps;
+    a.max_iters = kMaxIters;
+    a.K = K;
+    a.teams = K < kMaxTeams ? K : kMaxTeams;
+    a.data = reinterpret_cast<unsigned char*>(ws.wide);
+    a.sync = ws.wide_sync;
+    a.sq = sq;
+    const unsigned grid = (unsigned)((a.teams + 7) / 8 * 128 + (sq.out != nullptr ? sq.nb : 0));
+    const void* fn = newton_schulz_first ? reinterpret_cast<const void*>(&wide_polar_kernel<true>)
+                                         : reinterpret_cast<const void*>(&wide_polar_kernel<false>);
+    if (hipError_t e = ws.raised->ensure(fn, kLds); e != hipSuccess) return e;
+    if (newton_schulz_first) hipLaunchKernelGGL(wide_polar_kernel<true>, dim3(grid), dim3(kNT), kLds, st, a);
+    else hipLaunchKernelGGL(wide_polar_kernel<false>, dim3(grid), dim3(kNT), kLds, st, a);
     return hipGetLastError();
 }
 

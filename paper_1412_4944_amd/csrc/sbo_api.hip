@@ -41,9 +41,8 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
     w.partial = (float*)take((size_t)max_pieces_bound(m_max, K, p) * p * p * 4);
     w.M = (float*)take((size_t)K * p * p * 4);
-    w.vwork = (float*)take(p > 64 ? (size_t)K * p * p * 4 : 0);
-    const size_t wide_a = polar_wide_scratch_bytes(K), wide_b = polar_wide_ns_scratch_bytes(K);
-    w.jac_a = (float*)take(p > 64 ? (wide_a > wide_b ? wide_a : wide_b) : 0);
+    w.wide = (float*)take(p > 64 ? polar_wide_scratch_bytes(K) : 0);
+    w.wide_sync = (int*)take(p > 64 ? polar_wide_sync_bytes(K) : 0);
     const size_t sel_chunks = (size_t)((m_max + kSelChunk - 1) / kSelChunk);
     w.sel_hist = (int32_t*)take((size_t)4 * 256 * 4);
     w.sel_state = (int32_t*)take((size_t)4 * 2 * 4);
@@ -134,10 +133,13 @@ static int energy_ops(const sbo_ctx* c) {
     return screen_applies(c->p, c->s0, a) ? own | kOpsF16 : own;
 }
 
+// ... that its select kernel reads (p <= 64: D itself), and both.
+static int select_ops(const sbo_ctx* c) { return c->p <= 64 ? 0 : use_split(c) ? kOpsBf16 : kOpsF32; }
+static int code_ops(const sbo_ctx* c) { return energy_ops(c) | select_ops(c); }
+
 // D in the operand order(s) the coding kernels of this context read (tiny; outside the stages).
 static int run_swizzle(sbo_ctx* c, const float* D) {
-    int ops = energy_ops(c);
-    if (c->p > 64) ops |= use_split(c) ? kOpsBf16 : kOpsF32;       // what the select kernel reads
+    const int ops = code_ops(c);
     if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, c->stream));
     if (ops & (kOpsBf16 | kOpsF16))
         SBO_HIP(launch_dict_parts(c->p, c->K, D, ops & kOpsBf16 ? c->ws.dsb : nullptr,
@@ -151,9 +153,10 @@ static int run_energy(sbo_ctx* c, const float* Y, int64_t m, int32_t* blk) {
     return SBO_OK;
 }
 
+// have_ops: the workspace holds D in those orders already.
 static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32_t* blk,
-                    int32_t* supp, float* coef, float* err) {
-    int rc = run_swizzle(c, D);
+                    int32_t* supp, float* coef, float* err, bool have_ops = false) {
+    int rc = have_ops ? SBO_OK : run_swizzle(c, D);
     if (rc) return rc;
     rc = run_energy(c, Y, m, blk);
     if (rc) return rc;
@@ -166,24 +169,9 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
     return SBO_OK;
 }
 
-// Accumulate + SVD for signals already grouped in the workspace.
-static int run_update_grouped(sbo_ctx* c, const float* Y, int64_t m, const int32_t* supp,
-                              const float* coef, float* D) {
-    {
-        StageTimer t(c, SBO_STAGE_ACCUM);
-        SBO_HIP(launch_accumulate(c->p, c->K, c->s0, Y, m, supp, coef, c->ws, c->ws.M, c->stream));
-    }
-    {
-        StageTimer t(c, SBO_STAGE_SVD);
-        SBO_HIP(launch_polar(c->p, c->K, c->ws.M, c->ws.counts, D, c->ws, c->svd_method, nullptr, 0,
-                             c->stream));
-    }
-    return SBO_OK;
-}
-
-// The SVD update from the piece results of launch_select_accum (p <= 64); err / sq_out: also
-// the squared-error total of the coding pass.  One launch on the default path; with the Jacobi
-// SVD for every block the pieces are summed by their own launch first.
+// The SVD update from the piece results of launch_select_accum (p <= 64) or launch_accumulate (p = 256);
+// err / sq_out: also the squared-error total of the coding pass.  One launch on the default path;
+// with the Jacobi SVD for every block the pieces are summed by their own launch first.
 static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, const float* err, double* sq_out,
                             int K = -1) {
     if (K < 0) K = c->K;
@@ -198,6 +186,21 @@ static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, cons
     }
     StageTimer t(c, SBO_STAGE_SVD);
     SBO_HIP(launch_polar_from_pieces(c->p, K, m, D, c->ws, write_ops, err, sq_out, c->stream));
+    return SBO_OK;
+}
+
+// Accumulate + SVD of K orthobases (-1: all) from codes, for signals already grouped in the workspace.
+// p <= 64 sums the pieces of the stand-alone accumulation (which cuts them its own way) by a launch.
+static int run_update_grouped(sbo_ctx* c, const float* Y, int64_t m, const int32_t* supp, const float* coef, float* D,
+                              int write_ops = 0, const float* err = nullptr, double* sq_out = nullptr, int K = -1) {
+    if (K < 0) K = c->K;
+    {
+        StageTimer t(c, SBO_STAGE_ACCUM);
+        SBO_HIP(launch_accumulate(c->p, K, c->s0, Y, m, supp, coef, c->ws, c->p > 64 ? nullptr : c->ws.M, c->stream));
+    }
+    if (c->p > 64) return run_polar_pieces(c, m, D, write_ops, err, sq_out, K);
+    StageTimer t(c, SBO_STAGE_SVD);
+    SBO_HIP(launch_polar(c->p, K, c->ws.M, c->ws.counts, D, c->ws, c->svd_method, nullptr, 0, c->stream));
     return SBO_OK;
 }
 
@@ -238,10 +241,11 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     workspace_layout(p, K, s0, m_max, &c->ws, c->ws_base);
     c->ws.raised = &c->raised;
     c->ws.parts_accum = c->coding_arith != SBO_ARITH_F32;
-    // Two pieces of the workspace carry an invariant between calls: the chunk histograms and the
-    // finished-workgroup counter are zero whenever no call is in flight.
+    // Three pieces of the workspace carry an invariant between calls: the chunk histograms, the
+    // finished-workgroup counter and the counters of polar_wide.hip are zero whenever no call is in flight.
     e = hipMemsetAsync(c->ws.chunk_count, 0, (size_t)max_chunks() * K * 4, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->ws.sq_counter, 0, 4, c->stream);
+    if (e == hipSuccess && p > 64) e = hipMemsetAsync(c->ws.wide_sync, 0, polar_wide_sync_bytes(K), c->stream);
     if (e != hipSuccess) {
         (void)hipFree(c->ws_base);
         delete c;
@@ -352,10 +356,10 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
     const bool fused = c->p <= 64;             // select and accumulate share one pass over Y
     for (int it = 0; it < n_iter; ++it) {
         if (!fused) {
-            rc = run_code(c, Y, m, D, blk, supp, coef, err);
+            rc = run_code(c, Y, m, D, blk, supp, coef, err, it > 0);
             if (rc) return rc;
-            if (sqerr_per_iter) SBO_HIP(launch_sqerr(err, nullptr, m, c->ws, sqerr_per_iter + it, c->stream));
-            rc = run_update_grouped(c, Y, m, supp, coef, D);   // grouping reused
+            rc = run_update_grouped(c, Y, m, supp, coef, D, code_ops(c), err,      // grouping reused
+                                    sqerr_per_iter ? sqerr_per_iter + it : nullptr);
             if (rc) return rc;
             continue;
         }
@@ -396,15 +400,12 @@ static int run_train_rounds(sbo_ctx* c, const float* Y, int64_t m, const int32_t
         } else {
             {
                 StageTimer t(c, SBO_STAGE_SELECT);
-                SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, false,
+                SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, r > 0,
                                       use_split(c), c->stream));
             }
-            StageTimer t(c, SBO_STAGE_ACCUM);
-            SBO_HIP(launch_accumulate(c->p, c->K, c->s0, Y, m, supp, coef, c->ws, c->ws.M, c->stream));
+            rc = run_update_grouped(c, Y, m, supp, coef, D, select_ops(c));
+            if (rc) return rc;
         }
-        StageTimer t(c, SBO_STAGE_SVD);
-        SBO_HIP(launch_polar(c->p, c->K, c->ws.M, c->ws.counts, D, c->ws, c->svd_method, nullptr, 0,
-                             c->stream));
     }
     return SBO_OK;
 }
@@ -470,18 +471,13 @@ static int run_new_base(sbo_ctx* c, const float* Y, int64_t n, int R, int have_q
         if (c->p <= 64) {
             SBO_HIP(launch_select_accum(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, c->stream));
         } else {
-            SBO_HIP(launch_select(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, false, use_split(c), c->stream));
-            SBO_HIP(launch_accumulate(c->p, 1, c->s0, Y, n, supp, coef, c->ws, c->ws.M, c->stream));
+            SBO_HIP(launch_select(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, r > 0, use_split(c), c->stream));
         }
         if (sqerr_per_round)
             SBO_HIP(launch_sqerr(err, c->ws.perm, n, c->ws, sqerr_per_round + r, c->stream));
-        if (c->p <= 64) {
-            int rc = run_polar_pieces(c, n, Q, 0, nullptr, nullptr, 1);
-            if (rc) return rc;
-        } else {
-            SBO_HIP(launch_polar(c->p, 1, c->ws.M, c->ws.counts, Q, c->ws, c->svd_method, nullptr, 0,
-                                 c->stream));
-        }
+        int rc = c->p <= 64 ? run_polar_pieces(c, n, Q, 0, nullptr, nullptr, 1)
+                            : run_update_grouped(c, Y, n, supp, coef, Q, select_ops(c), nullptr, nullptr, 1);
+        if (rc) return rc;
     }
     return SBO_OK;
 }

@@ -100,8 +100,8 @@ struct Workspace {
     // accumulation
     float* partial;        // [max_pieces][p][p]
     float* M;              // [K][p][p]
-    float* vwork;          // p > 64 only: [K][p][p] the V of the wide Jacobi SVD
-    float* jac_a;          // p > 64 only: scratch of the wide Jacobi (polar_wide_scratch_bytes)
+    float* wide;           // p > 64 only: exchange memory of polar_wide.hip (polar_wide_scratch_bytes)
+    int* wide_sync;        // p > 64 only: its counters (0 between launches)
     // worst-W selection
     int32_t* sel_hist;     // [4][256] digit histograms of the radix select
     int32_t* sel_state;    // [4][2] (key prefix, entries still to take) after each pass
@@ -198,6 +198,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
                          bool split, hipStream_t st);
 
+// M == nullptr (p = 256): the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
                              const float* coef, const Workspace& ws, float* M, hipStream_t st);
 
@@ -211,17 +212,16 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
                                const float* err, double* sq_out, hipStream_t st);
 
 // The SVD update Q_j = U V^T of every block with counts[j] > 0 (counts == nullptr: all).
-// p <= 64: Newton-Schulz on the matrix cores (polar_ns.hip) first, then the Jacobi SVD for the
-// blocks it leaves flagged (rank-deficient ones); p = 256: the same two steps spread over the whole
-// chip (polar_wide_ns.hip, polar_wide.hip).
+// Newton-Schulz on the matrix cores (polar_ns.hip; p = 256: polar_wide.hip), in the same launch the
+// Jacobi SVD for the blocks on which it does not converge (rank-deficient ones).
 // jacobi_only != 0: the Jacobi SVD for every block (SBO_SVD_JACOBI).
-// Uses ws.vwork and ws.jac_a (p = 256), ws.sweeps (per block: Jacobi sweeps, or minus the
+// Uses ws.wide and ws.wide_sync (p = 256), ws.sweeps (per block: Jacobi sweeps, or minus the
 // Newton-Schulz steps), ws.ns_fallback.
 // eig_sv != nullptr switches to eigen mode (always Jacobi): M[j] symmetric positive
 // semidefinite, D[j] receives its eigenvectors as atoms by descending eigenvalue and
 // eig_sv[j][p] the square roots of the eigenvalues.
-// write_ops (p <= 64): the operand orders (kOps*) in which the rows of every updated block are also
-// left in ws.
+// write_ops: the operand orders (kOps*) in which the rows of every updated block are also left in
+// ws (not in eigen mode).
 hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, float* D,
                         const Workspace& ws, int jacobi_only, float* eig_sv, int write_ops,
                         hipStream_t st);
@@ -242,23 +242,19 @@ hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, c
                            int piece, const int32_t* counts, float* D, const DictOps& ops,
                            int32_t* fallback, int32_t* iters, const SqTotalArgs& sq, LdsRaised* raised,
                            hipStream_t st);
-// The SVD update straight from the piece results of launch_select_accum (p <= 64, Newton-Schulz
-// path): what launch_accum_reduce + launch_polar do, in one launch.  err / sq_out as for
-// launch_accum_reduce.
+// The SVD update straight from the piece results (launch_select_accum, p = 256: launch_accumulate
+// without its sum; Newton-Schulz path): what launch_accum_reduce + launch_polar do, in one launch.
+// err / sq_out as for launch_accum_reduce.
 hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Workspace& ws, int write_ops,
                                     const float* err, double* sq_out, hipStream_t st);
 
-// p = 256 variant of launch_polar (polar_wide.hip) and the size of its scratch (working
-// copy of P_j, rotation log, sweep counts).
+// p = 256 (polar_wide.hip): source and squared-error total as launch_polar_ns; newton_schulz_first ==
+// false or eig_sv != nullptr: the Jacobi SVD for every block.  And the sizes of ws.wide, ws.wide_sync.
 size_t polar_wide_scratch_bytes(int K);
-// only != nullptr: blocks with only[j] == 0 are skipped.
-hipError_t launch_polar_wide(int K, const float* M, const int32_t* counts, float* D, float* vwork,
-                             float* jac_a, float* eig_sv, int32_t* sweeps, const int32_t* only,
-                             LdsRaised* raised, hipStream_t st);
-// p = 256 Newton-Schulz over the whole chip (polar_wide_ns.hip); scratch as for the Jacobi variant.
-size_t polar_wide_ns_scratch_bytes(int K);
-hipError_t launch_polar_wide_ns(int K, const float* M, const int32_t* counts, float* D, float* scratch,
-                                int32_t* fallback, int32_t* iters, LdsRaised* raised, hipStream_t st);
+size_t polar_wide_sync_bytes(int K);
+hipError_t launch_polar_wide(int K, const float* M, const float* partial, const int32_t* offsets, int piece,
+                             const int32_t* counts, float* D, const DictOps& ops, bool newton_schulz_first,
+                             float* eig_sv, const Workspace& ws, const SqTotalArgs& sq, hipStream_t st);
 
 // ids == nullptr: sum over all m signals; otherwise over the m listed ones.
 hipError_t launch_sqerr(const float* err, const int32_t* ids, int64_t m, const Workspace& ws,

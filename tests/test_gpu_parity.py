@@ -413,6 +413,29 @@ def test_polar_condition_sweep_and_both_paths(p):
     assert np.abs(out["default"][good] - out["jacobi"][good]).max() <= 1e-4
 
 
+@pytest.mark.parametrize("K", [1, 9, 33])               # one team; two groups of eight; teams with three blocks in turn
+@pytest.mark.parametrize("jacobi_only", [False, True], ids=["auto", "jacobi"])
+def test_polar_p256_teams_of_workgroups(K, jacobi_only):
+    """p = 256: blocks of every kind in one launch (a team passes from Newton-Schulz on one block to
+    the Jacobi SVD on the next, to an empty one), twice in a row on one context."""
+    p = 256
+    rng = np.random.default_rng(29 + K)
+    M = np.stack([(synth.random_onb(rng, p) * np.geomspace(1, 10.0 ** -(j % 3), p)) @ synth.random_onb(rng, p)
+                  for j in range(K)])
+    for j in range(4, K, 9):
+        M[j][:, 200:] = M[j][:, :56]                     # rank 200: left to the Jacobi SVD
+    counts = np.ones(K, np.int32)
+    counts[5::7] = 0
+    M32 = M.astype(np.float32)
+    D_old = synth.random_dictionary(rng, K, p).astype(np.float32)
+    Dn = np.stack([orc.o_polar(M32[j].astype(np.float64)) if counts[j] else D_old[j] for j in range(K)])
+    with Sbo(p, K, 4, 256, jacobi_only=jacobi_only) as g:
+        a, b = g.polar(M32, D_old, counts), g.polar(M32, D_old, counts)
+    np.testing.assert_array_equal(a, b)
+    w = compare_Q(a, Dn, M32.astype(np.float64), counts > 0)
+    print(f"  K={K} jacobi={jacobi_only}: worst |Q - Q_oracle| {w:.2e}", flush=True)
+
+
 JACOBI_CASES = [("tiny", dict(), 12), ("patch8", dict(m=4096 + 77), 10),
                 ("p256", dict(p=256, K=2, m=1300, s0=12, snr_db=25.0), 2)]
 
