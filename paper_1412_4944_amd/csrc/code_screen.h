@@ -9,13 +9,22 @@
 //
 //   1. Screening.  One fp16 product per product (the leading fp16 part of the signal, scaled, times
 //      the leading part of the dictionary) gives every coefficient to about 2^-11; the magnitudes
-//      are rounded to fp16, and the selection networks run on two signals per instruction
-//      (energy_networks.h).  The kept energy of every (signal, block) goes to LDS, 16 bits each.
+//      are rounded down to fp16.
+//        p = 64, s0 >= 5: the kept energy is only bounded from above.  For any t,
+//            sum of the s0 largest c^2  <=  sum over all of max(c^2, t) - (p - s0) t,
+//      with equality at the s0-th largest one: two instructions per pair of magnitudes (a maximum and a dot
+//      product) instead of the six or more of a selection network.  t is the s0-th largest c^2 of
+//      the first block: the other blocks that are far from the signal look alike, and where the coefficients of
+//      the right one stand out the bound is nearly exact.  The magnitudes of the block that is ahead
+//      stay in registers, and at the end one selection network gives its kept energy.
+//        Otherwise: the networks for every block, on two signals per instruction (energy_networks.h).
+//      The bound or kept energy of every (signal, block) goes to LDS, 16 bits each.
 //   2. Decision.  The s0 largest magnitudes' norm of a block is off by at most
 //          eps = sqrt(s0) (max |q| |y - hi(y)| + |y| max |q - hi(q)| + accumulation)
 //      (Cauchy-Schwarz per coefficient; the two remainders' norms are computed, not bounded) and by
-//      the rounding down of the magnitudes, less than 2^-10 of itself.  A block that is further than that
-//      below the best one cannot win.  A signal with one block left is decided.
+//      the rounding down of the magnitudes, less than 2^-10 of itself.  A block that is (whose bound is) further
+//      than that below the kept energy of the one ahead cannot win.  A signal with one block left is
+//      decided.
 //   3. Resolution.  For the others, the blocks that are left are computed in the context's
 //      arithmetic (SBO_ARITH_*), operand by operand and sum by sum what the kernels in
 //      code_energy.hip do, and compared: the largest energy wins, the lower block on a tie.
@@ -23,16 +32,18 @@
 // assumed about D; the bound is just wide if its atoms are long).
 //
 // Two shapes of the same work:
-//   energy_screen_kernel<..., false>: a workgroup takes 512 signals, a wavefront 64 of them and all
-//     blocks; dictionary stages go through LDS, double-buffered.
-//   energy_screen_kernel<..., true>: a workgroup takes 64 signals, and its wavefronts share out the
-//     blocks and read their dictionary rows straight from L2: eight times the workgroups, for
-//     signal sets that would not fill the chip otherwise, and for K beyond the LDS table of the other.
-// Measured (MI355X, f16x2 results): K = 32, p = 64, s0 = 8, 262144 signals 229 -> 126 us (155 on a near-random
-// dictionary, where a third of the signals has candidates to resolve), of which 103 k cycles main
-// loop, 13 k loading the signals, 5 k decision; K = 128, s0 = 6, 2^20 signals 3283 -> 1700 us; p = 256, K = 16,
-// 131072 signals 757 -> 288 us; K = 16, 16384 signals (the second shape) 28 -> 9 us.  "Before" is
-// the full-precision projection of every block.
+//   energy_screen_kernel<..., false, W>: a workgroup takes 64 W signals, a wavefront 64 of them and all
+//     blocks; dictionary stages go through LDS, double-buffered.  W = 4 where two workgroups fit the LDS of a
+//     CU: one loads or decides while the other multiplies.
+//   energy_screen_kernel<..., true, 8>: a workgroup takes 64 signals, and its wavefronts share out the
+//     blocks and read their dictionary rows straight from L2: more workgroups, for signal sets that
+//     would not fill the chip otherwise, and for K beyond the LDS table of the other.
+//
+// Measured (MI355X, f16x2 results; "before" is the full-precision projection of every block): K = 32, p = 64,
+// s0 = 8, 262144 signals 229 us before, 126 with networks for every block, 100 with bounds; K = 128, s0 = 6, 2^20
+// signals 3283, 1712, 1400 us; p = 256, K = 16, 131072 signals 757 -> 288 us; K = 16, 16384 signals (the second
+// shape) 28 -> 9 us.  Of the 100 us, 66 are the main loop at 45 us of matrix work (at the 1530 TFLOP/s that the
+// chip sustains on such operands) and 40 of vector work, which share the power budget.
 #pragma once
 
 #include "sbo_internal.h"
@@ -44,7 +55,8 @@ namespace sbo {
 
 namespace {
 
-constexpr int kScrWaves = 8;
+constexpr int kScrWaves = 8;                   // at most
+constexpr size_t kScrLdsMax = 160 * 1024;
 
 // Maximum over the wavefront, in all lanes.
 __device__ __forceinline__ float wave_max(float x) {
@@ -67,6 +79,10 @@ struct ScrGeom {
     static constexpr int STAGE_U = MTS * KS16 * 64;         // 16-byte units of a stage (leading parts only)
     static constexpr int NV = WIDE ? 16 : P / 2;            // coefficients per lane, block and stage
 };
+
+// Which sizes screen with bounds from above (the header): where a wavefront meets enough blocks to pay
+// for its two selections, and these are long.
+constexpr bool scr_bound(int P, int SX, bool shared) { return P == 64 && SX >= 5 && !shared; }
 
 // Kept energy of signal i (-1: none) in block j in the exact arithmetic, up to the signal's scale.
 template <int P, int S, int SX, int ARITH>
@@ -212,24 +228,24 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
 //   E16         [K rounded up to whole stages][signals] 16 bits
 //   (front and E16 together first hold the signals while they are converted)
 //   thr, y2, r2 [signals] floats; key [signals] 64 bits; small change
-template <int P, bool SHARED>
+template <int P, bool SHARED, int W>
 constexpr size_t scr_front_bytes() {
     const size_t stages = SHARED ? (P > 64 ? (size_t)64 * P * 2 : 0) : (size_t)2 * ScrGeom<P>::STAGE_U * 16;
-    const size_t lists = (size_t)kScrWaves * (SHARED ? 64 : 512) * 2;
+    const size_t lists = (size_t)W * (SHARED ? 64 : 64 * W) * 2;
     const size_t a = stages > lists ? stages : lists;
-    return a > 6144 ? a : 6144;                // the wavefronts' results (SHARED), the histogram
+    return a > 8192 ? a : 8192;                // the wavefronts' results (SHARED), the histogram
 }
-template <int P, bool SHARED>
+template <int P, bool SHARED, int W>
 constexpr size_t scr_table_bytes(int K) {      // front + E16
     constexpr int NB = ScrGeom<P>::NB;
-    const size_t rows = (size_t)((K + NB - 1) / NB * NB), sig = SHARED ? 64 : 64 * kScrWaves;
-    const size_t a = scr_front_bytes<P, SHARED>() + ((rows * sig * 2 + 15) & ~(size_t)15);
-    const size_t signals = SHARED ? (size_t)64 * P * 2 : (size_t)kScrWaves * 4096;
+    const size_t rows = (size_t)((K + NB - 1) / NB * NB), sig = SHARED ? 64 : 64 * W;
+    const size_t a = scr_front_bytes<P, SHARED, W>() + ((rows * sig * 2 + 15) & ~(size_t)15);
+    const size_t signals = SHARED ? (size_t)64 * P * 2 : (size_t)W * 4096;
     return a > signals ? a : signals;
 }
-template <int P, bool SHARED>
+template <int P, bool SHARED, int W>
 constexpr size_t scr_lds_bytes(int K) {
-    return scr_table_bytes<P, SHARED>(K) + (size_t)(SHARED ? 64 : 64 * kScrWaves) * 20 + (2 * kScrWaves + 1) * 4;
+    return scr_table_bytes<P, SHARED, W>(K) + (size_t)(SHARED ? 64 : 64 * W) * 20 + (2 * W + 1) * 4;
 }
 
 // One step of the main loop issues the matrix instructions of the NEXT rows and the selection networks
@@ -239,32 +255,36 @@ constexpr size_t scr_lds_bytes(int K) {
 // SIMD, 2940 cycles interleaved; 3830 when the two wavefronts multiply and select in turns).
 template <int NM, int NVALU>
 __device__ __forceinline__ void interleave() {
+    constexpr int kFirst = NVALU / NM;         // while the first operands come from LDS
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                  // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x002, kFirst, 0);             // vector ALU
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);              // LDS read
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              // matrix
-        __builtin_amdgcn_sched_group_barrier(0x002, NVALU / NM, 0);     // vector ALU
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (NVALU - kFirst) / NM, 0);
     }
 }
 
-template <int P, int S, int SX, int ARITH, bool SHARED>
-__global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g) {
+template <int P, int S, int SX, int ARITH, bool SHARED, int W>
+__global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     using G = ScrGeom<P>;
     constexpr int KS16 = G::KS16, MTS = G::MTS, NB = G::NB, SPB = G::SPB, NV = G::NV, STAGE_U = G::STAGE_U;
-    constexpr bool WIDE = G::WIDE;
-    constexpr int SIG = SHARED ? 64 : 64 * kScrWaves;      // signals of the workgroup
+    constexpr bool WIDE = G::WIDE, BOUND = scr_bound(P, SX, SHARED);
+    constexpr bool YLDS = SHARED && P >= 64;               // B operands from LDS (registers: 32 less at p = 64)
+    constexpr int SIG = SHARED ? 64 : 64 * W;      // signals of the workgroup
     constexpr int NT = 2;                                   // 32-signal tiles of a wavefront
     const int K = g.K, m = g.m;
 
     extern __shared__ u32x4 lds_scr[];
     unsigned char* front = reinterpret_cast<unsigned char*>(lds_scr);
-    unsigned short* E16 = reinterpret_cast<unsigned short*>(front + scr_front_bytes<P, SHARED>());
-    unsigned* thr = reinterpret_cast<unsigned*>(front + scr_table_bytes<P, SHARED>(K));
+    unsigned short* E16 = reinterpret_cast<unsigned short*>(front + scr_front_bytes<P, SHARED, W>());
+    unsigned* thr = reinterpret_cast<unsigned*>(front + scr_table_bytes<P, SHARED, W>(K));
     float* y2s = reinterpret_cast<float*>(thr + SIG);
     float* r2s = y2s + SIG;
     unsigned long long* key = reinterpret_cast<unsigned long long*>(r2s + SIG);
-    float* wred = reinterpret_cast<float*>(key + SIG);     // [2][kScrWaves], then one flag
-    int* any_flag = reinterpret_cast<int*>(wred + 2 * kScrWaves);
+    float* wred = reinterpret_cast<float*>(key + SIG);     // [2][W], then one flag
+    int* any_flag = reinterpret_cast<int*>(wred + 2 * W);
 
     const int tid = threadIdx.x, NTH = blockDim.x, NW = NTH >> 6;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -278,26 +298,25 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
 
     // Stages of the dictionary (!SHARED: all wavefronts read the same one); the first two are requested
     // before the signals.
-    constexpr int FPT = (STAGE_U + 64 * kScrWaves - 1) / (64 * kScrWaves);
+    constexpr int FPT = (STAGE_U + 64 * W - 1) / (64 * W);
     const int n_stage = WIDE ? K * SPB : (K + NB - 1) / NB;
     u32x4(*Qs)[STAGE_U] = reinterpret_cast<u32x4(*)[STAGE_U]>(lds_scr);
-    u32x4 pre[FPT], pre1[FPT];
+    u32x4 pre[FPT];
+    const __amdgpu_buffer_rsrc_t dict =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(g.Dh), 0, n_stage * (2 * STAGE_U) * 16, 0x00027000);
     auto fetch = [&](u32x4 (&p)[FPT], int s) { // past the end: the last stage once more, not used
         s = min(s, n_stage - 1);
 #pragma unroll
         for (int r = 0; r < FPT; ++r) {
-            const int u = min(tid + 64 * kScrWaves * r, STAGE_U - 1);
-            p[r] = g.Dh[(int64_t)s * (2 * STAGE_U) + (u >> 6) * 128 + (u & 63)];
+            const int u = min(tid + 64 * W * r, STAGE_U - 1);
+            p[r] = __builtin_amdgcn_raw_buffer_load_b128(dict, ((u >> 6) * 128 + (u & 63)) * 16, s * (2 * STAGE_U * 16), 0);
         }
     };
     auto stash = [&](const u32x4 (&p)[FPT], int buf) {
 #pragma unroll
-        for (int r = 0; r < FPT; ++r) Qs[buf][min(tid + 64 * kScrWaves * r, STAGE_U - 1)] = p[r];
+        for (int r = 0; r < FPT; ++r) Qs[buf][min(tid + 64 * W * r, STAGE_U - 1)] = p[r];
     };
-    if constexpr (!SHARED) {
-        fetch(pre, 0);
-        fetch(pre1, 1);
-    }
+    if constexpr (!SHARED) fetch(pre, 0);
 
     // The leading fp16 parts of the signals, every signal scaled by a power of two (largest magnitude
     // into [1/2, 1), p = 256: [1/4, 1/2), so that coefficients times the dictionary's 2^13 stay inside
@@ -356,7 +375,7 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     // B operand: dims ks*16 + h*8 .. +7 of this lane's signal in tile nt
-    u32x4 yq[SHARED && WIDE ? 1 : NT][SHARED && WIDE ? 1 : KS16];
+    u32x4 yq[YLDS ? 1 : NT][YLDS ? 1 : KS16];
     if constexpr (SHARED) {
         for (int q = wave; q < 64 / GS; q += NW) {
             f32x4 raw[L4];
@@ -406,13 +425,13 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
     if (tid == 0) *any_flag = 0;
     if (lane == 0) {
         wred[wave] = norm.x;
-        wred[kScrWaves + wave] = norm.y;
+        wred[W + wave] = norm.y;
     }
     __syncthreads();
     // Lane (h, n) is the owner of signal (tile h, n) = loc0 + lane.  Energies are stored relative to |y|^2.
     const float y2_own = y2s[loc0 + lane];
     const float e_scale = y2_own > 0.f ? 0x1p-26f / y2_own : 0.f;
-    if constexpr (SHARED && !WIDE) {
+    if constexpr (SHARED && !YLDS) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -425,36 +444,113 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
     constexpr int UB = WIDE ? 1 : UT * 32 / P;             // blocks of a step
     using Acc = f32x16[NT][UT];
     u16x2 run[SX];                             // p = 256: the pair's sorted top of the block so far
-    float bestE = -1.f, secondE = -1.f;        // of the own signal, in stored units
+    // of the own signal, in stored units (BOUND: bounds from above)
+    float bestE = -1.f, secondE = -1.f;
     int best = 0;
-    auto finish = [&](const u16x2 (&a)[SX], int j) {
-        const float e = pk_pair_energy<SX>(a, h != 0) * e_scale;
+    auto offer = [&](float e, int j) {
+        const bool better = e > bestE;
         secondE = fmaxf(secondE, fminf(bestE, e));
-        best = e > bestE ? j : best;
+        best = better ? j : best;
         bestE = fmaxf(bestE, e);
         const auto q = __builtin_amdgcn_cvt_pknorm_u16(e, 0.f);
         E16[j * SIG + loc0 + lane] = (unsigned short)q[0];
+        return better;
     };
-    // selection from acc: p <= 64: the UB blocks from j0 on; p = 256: 32 atoms of a block (first: of them all)
+    auto finish = [&](const u16x2 (&a)[SX], int j) { offer(pk_pair_energy<SX>(a, h != 0) * e_scale, j); };
+    // BOUND.  keep: the best block's magnitudes (two of a signal per word); tau: the s0-th largest of the
+    // first block, twice; slope: (p - s0) tau^2
+    constexpr int NK = BOUND ? NV / 2 : 1;
+    u16x2 keep[NT][NK], tau[NT];
+    float slope[NT];
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    auto magnitudes = [&](const Acc& acc, int b, int nt, u16x2 (&x)[NK]) {
+#pragma unroll
+        for (int v = 0; v < NK; ++v) {
+            const int f = b * NV + 2 * v;
+            const auto p = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[nt][(f >> 4) % UT][f & 15]), fabsf(acc[nt][(f >> 4) % UT][(f + 1) & 15]));
+            x[v] = __builtin_bit_cast(u16x2, p);
+        }
+    };
+    auto sorted_top = [&](const u16x2 (&x)[NT][NK], u16x2 (&a)[SX]) {          // of both signals, packed
+        u16x2 t[2 * NK];
+#pragma unroll
+        for (int v = 0; v < NK; ++v) {
+            const unsigned x0 = __builtin_bit_cast(unsigned, x[0][v]), x1 = __builtin_bit_cast(unsigned, x[1][v]);
+            t[2 * v] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(x1, x0, 0x05040100u));
+            t[2 * v + 1] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(x1, x0, 0x07060302u));
+        }
+        pk_top_sorted<2 * NK, SX>(t, a);
+    };
+    auto first_block = [&](const Acc& acc) {
+        u16x2 x[NT][NK], a[SX];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) magnitudes(acc, 0, nt, x[nt]);
+        sorted_top(x, a);
+        const u16x2 least = pk_pair_least<SX>(a, h != 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            tau[nt] = u16x2{least[nt], least[nt]};
+            const float t = (float)__builtin_bit_cast(f16x2, tau[nt])[0];
+            slope[nt] = (float)(P - SX) * 0.5f * (t * t);                  // (each lane of a pair takes half)
+#pragma unroll
+            for (int v = 0; v < NK; ++v) keep[nt][v] = u16x2{0, 0};
+        }
+    };
+    // selection from acc, p <= 64: the UB blocks from j0 on; p = 256: 32 atoms of a block (first: of them all)
     auto select = [&](const Acc& acc, int j0, bool first) {
+        if constexpr (BOUND) {
 #pragma unroll
-        for (int b = 0; b < UB; ++b) {
-            u16x2 x[NV], a[SX];
+            for (int b = 0; b < UB; ++b) {
+                u16x2 x[NT][NK];
+                float up[NT][2];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const int f = b * NV + v;
-                const auto p = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[0][(f >> 4) % UT][f & 15]), fabsf(acc[1][(f >> 4) % UT][f & 15]));
-                x[v] = __builtin_bit_cast(u16x2, p);
+                for (int nt = 0; nt < NT; ++nt) {
+                    magnitudes(acc, b, nt, x[nt]);
+                    up[nt][0] = -slope[nt];
+                    up[nt][1] = 0.f;
+                }
+#pragma unroll
+                for (int v = 0; v < NK; v += 2) {          // four sums, so that no instruction waits for the one before
+                    f16x2 w[NT][2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) w[nt][k] = __builtin_bit_cast(f16x2, pk_max(x[nt][v + k], tau[nt]));
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) up[nt][k] = __builtin_amdgcn_fdot2(w[nt][k], w[nt][k], up[nt][k], false);
+                }
+                const SwapPair t = swap32(up[0][0] + up[0][1], up[1][0] + up[1][1]);
+                const unsigned long long better = __ballot(offer((t.first + t.second) * e_scale, j0 + b));
+                const unsigned long long lo = better & 0xffffffffull, hi = better >> 32;
+                const bool b0 = __builtin_amdgcn_inverse_ballot_w64(lo | lo << 32), b1 = __builtin_amdgcn_inverse_ballot_w64(hi | hi << 32);
+#pragma unroll
+                for (int v = 0; v < NK; ++v) {
+                    keep[0][v] = b0 ? x[0][v] : keep[0][v];
+                    keep[1][v] = b1 ? x[1][v] : keep[1][v];
+                }
             }
-            pk_top_sorted<NV, SX>(x, a);
-            if constexpr (!WIDE) {
-                finish(a, j0 + b);
-            } else {
-                // (zeros below everything: the first list of a block is taken as it is)
-                const unsigned keep = first ? 0u : 0xffffffffu;
+        } else {
 #pragma unroll
-                for (int t = 0; t < SX; ++t) run[t] = __builtin_bit_cast(u16x2, __builtin_bit_cast(unsigned, run[t]) & keep);
-                pk_merge_top<SX>(run, a);
+            for (int b = 0; b < UB; ++b) {
+                u16x2 x[NV], a[SX];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int f = b * NV + v;
+                    const auto p = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[0][(f >> 4) % UT][f & 15]), fabsf(acc[1][(f >> 4) % UT][f & 15]));
+                    x[v] = __builtin_bit_cast(u16x2, p);
+                }
+                pk_top_sorted<NV, SX>(x, a);
+                if constexpr (!WIDE) {
+                    finish(a, j0 + b);
+                } else {
+                    // (zeros below everything: the first list of a block is taken as it is)
+                    const unsigned keep_run = first ? 0u : 0xffffffffu;
+#pragma unroll
+                    for (int t = 0; t < SX; ++t) run[t] = __builtin_bit_cast(u16x2, __builtin_bit_cast(unsigned, run[t]) & keep_run);
+                    pk_merge_top<SX>(run, a);
+                }
             }
         }
     };
@@ -462,14 +558,14 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             u32x4 b;
-            if constexpr (SHARED && WIDE) b = *reinterpret_cast<const u32x4*>(front + nt * (32 * P * 2) + (ks * 64 + lane) * 16);
+            if constexpr (YLDS) b = *reinterpret_cast<const u32x4*>(front + nt * (32 * P * 2) + (ks * 64 + lane) * 16);
             else b = yq[nt][ks];
             acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b),
                                                                  ks == 0 ? zero : acc[nt][mt], 0, 0, 0);
         }
     };
     constexpr int kMatrix = NT * UT * KS16;
-    constexpr int kVector = UB * (NV * 7 + 8 * SX);        // about
+    constexpr int kVector = UB * (BOUND ? NV * 4 + 16 : NV * 7 + 8 * SX);      // about
 
     Acc acc0, acc1;
     if constexpr (WIDE) {
@@ -478,7 +574,7 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
     }
     if constexpr (!SHARED) {
         // while stage s is selected from the accumulators, stage s + 1 is multiplied from one buffer and
-        // stage s + 2 written to the other
+        // stage s + 2 written to the other (requested a stage earlier, it makes no difference)
         auto project = [&](Acc& acc, int buf) {
 #pragma unroll
             for (int ks = 0; ks < KS16; ++ks)
@@ -495,24 +591,16 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
             __syncthreads();
         };
         stash(pre, 0);
-        stash(pre1, 1);
+        fetch(pre, 1);
+        stash(pre, 1);
         __syncthreads();
         project(acc0, 0);
-        // The signals of the workgroup that will follow on this CU (workgroups go round the XCDs, so it
-        // comes to the same one) into the XCD's L2, one load per 128-byte line, while this one computes.
-        constexpr int kTouch = P == 64 || P == 32 ? P / 32 : 0;
-        float touch[kTouch > 0 ? kTouch : 1] = {0.f};
-        const int64_t line0 = ((wg0 + (int64_t)kNumCU * SIG) * P) / 32 + tid;
-#pragma unroll
-        for (int r = 0; r < kTouch; ++r)
-            touch[r] = g.Y[min(line0 + (int64_t)r * (64 * kScrWaves), ((int64_t)m * P - 1) / 32) * 32];
+        if constexpr (BOUND) first_block(acc0);
         __syncthreads();
         for (int s = 0; s < n_stage; s += 2) {
             step(acc0, acc1, s);
             if (s + 1 < n_stage) step(acc1, acc0, s + 1);              // uniform
         }
-#pragma unroll
-        for (int r = 0; r < kTouch; ++r) asm volatile("" ::"v"(touch[r]));
     } else {
         // A step = UT row tiles of the dictionary, p = 256: one of the SPB tiles of a block; wavefront w takes
         // the blocks (p < 64: tiles) w, w + NW, .. and reads their rows from L2, one step ahead.
@@ -547,6 +635,7 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
             load(0);
             project(acc0);
             load(1);
+            if constexpr (BOUND) first_block(acc0);
             for (int t = 0; t < n_mine; t += 2) {
                 step(acc0, acc1, t);
                 if (t + 1 < n_mine) step(acc1, acc0, t + 1);
@@ -554,37 +643,49 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
         }
     }
 
-    // Decision: the best block alone at or above the threshold, in stored energies, or not.
+    // Decision: the best block alone at or above the threshold, in stored energies, or not.  below: the kept
+    // energy of block `best`; secondE: the largest bound of the others.
     const bool valid = wg0 + loc0 + lane < m;
+    float below = bestE;
+    if constexpr (BOUND) {
+        u16x2 a[SX];
+        sorted_top(keep, a);
+        below = bestE >= 0.f ? pk_pair_energy<SX>(a, h != 0) * e_scale : -1.f;
+    }
     if constexpr (SHARED) {
         __syncthreads();                       // the signals in front are dead
-        float* xb = reinterpret_cast<float*>(front);       // best, second, block: [3][NW][64]
-        xb[wave * 64 + lane] = bestE;
-        xb[(NW + wave) * 64 + lane] = secondE;
-        xb[(2 * NW + wave) * 64 + lane] = __builtin_bit_cast(float, best);
+        float* xb = reinterpret_cast<float*>(front);       // kept, best bound, second, block: [4][NW][64]
+        xb[wave * 64 + lane] = below;
+        xb[(NW + wave) * 64 + lane] = bestE;
+        xb[(2 * NW + wave) * 64 + lane] = secondE;
+        xb[(3 * NW + wave) * 64 + lane] = __builtin_bit_cast(float, best);
         __syncthreads();
-        bestE = secondE = -1.f;
-        for (int w = 0; w < NW; ++w) {
-            const float e = xb[w * 64 + lane], e2 = xb[(NW + w) * 64 + lane];
-            secondE = fmaxf(fmaxf(secondE, e2), fminf(bestE, e));
-            best = e > bestE ? __builtin_bit_cast(int, xb[(2 * NW + w) * 64 + lane]) : best;
-            bestE = fmaxf(bestE, e);
+        below = bestE = secondE = -1.f;
+        for (int w = 0; w < NW; ++w) {         // bestE: the bound of the block that is ahead
+            const float e = xb[w * 64 + lane], u = xb[(NW + w) * 64 + lane];
+            const bool ahead = e > below;
+            secondE = fmaxf(fmaxf(secondE, xb[(2 * NW + w) * 64 + lane]), ahead ? bestE : u);
+            best = ahead ? __builtin_bit_cast(int, xb[(3 * NW + w) * 64 + lane]) : best;
+            bestE = ahead ? u : bestE;
+            below = fmaxf(below, e);
         }
     }
-    float qn = wred[0], dq = wred[kScrWaves];
+    float qn = wred[0], dq = wred[W];
     for (int w = 1; w < NW; ++w) {
         qn = fmaxf(qn, wred[w]);
-        dq = fmaxf(dq, wred[kScrWaves + w]);
+        dq = fmaxf(dq, wred[W + w]);
     }
     auto stored = [](float e) { return (unsigned)(unsigned short)__builtin_amdgcn_cvt_pknorm_u16(e, 0.f)[0]; };
     unsigned t16 = 0u;                         // 0: every block stays in
     {
         const float rel = y2_own > 0.f ? r2s[loc0 + lane] / y2_own : 0.f;
         const float eps = sqrtf((float)g.s0) * (qn * sqrtf(rel) + 1.001f * dq + qn * (P * 1.2e-7f)) * 1.001f;
-        const float qb = (float)stored(bestE);
+        const float qb = (float)stored(below);
         const float nrm = sqrtf(fmaxf(qb - 0.5f, 0.f) * (1.f / 65535.f));
         const float t = (nrm - 2.f * eps) * (1.f - 0x1.02p-10f);
-        const float t2 = t > 0.f ? t * t * (65535.f * (1.f - 1e-5f)) - 1.f : 0.f;
+        // one unit for the rounding of the table; BOUND: what the sum of a bound may lose to rounding
+        constexpr float kUnits = 1.f + (!BOUND ? 0.f : 65535.f * P * 0x1p-25f * (1.f + (float)P / SX));
+        const float t2 = t > 0.f ? t * t * (65535.f * (1.f - 1e-5f)) - kUnits : 0.f;
         if (y2_own > 0.f && t2 > 0.f) t16 = (unsigned)t2;
     }
     if (!valid || y2_own == 0.f) t16 = 0x10000u;           // a zero signal: block 0 (ties go to the lowest)
@@ -643,28 +744,29 @@ __global__ __launch_bounds__(64 * kScrWaves) void energy_screen_kernel(ScrArgs g
     }
 }
 
+template <int P, int S, int SX, int ARITH, bool SHARED, int W>
+hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t st) {
+    constexpr int sig = SHARED ? 64 : 64 * W;
+    const size_t lds = scr_lds_bytes<P, SHARED, W>(a.K);
+    if (lds > kScrLdsMax || a.chunk % sig != 0) return hipErrorInvalidValue;
+    const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W>);
+    if (hipError_t e = raised->ensure(fn, kScrLdsMax); e != hipSuccess) return e;
+    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W>), dim3((unsigned)((a.m + sig - 1) / sig)),
+                       dim3(64 * waves), lds, st, a);
+    return hipGetLastError();
+}
+
 template <int P, int S, int SX, int ARITH>
 hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
-    constexpr size_t kLdsMax = 160 * 1024;
-    const bool shared = screen_shared(a.m) || scr_lds_bytes<P, false>(a.K) > kLdsMax;
-    const int sig = shared ? 64 : 64 * kScrWaves;
-    const unsigned grid = (unsigned)((a.m + sig - 1) / sig);
-    if (a.chunk % sig != 0) return hipErrorInvalidValue;
-    if (shared) {
-        const size_t lds = scr_lds_bytes<P, true>(a.K);
-        if (lds > kLdsMax) return hipErrorInvalidValue;
-        const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, true>);
-        if (hipError_t e = raised->ensure(fn, kLdsMax); e != hipSuccess) return e;
+    const bool half = P <= 64 && scr_lds_bytes<P, false, kScrWaves / 2>(a.K) <= kScrLdsMax / 2;
+    if (screen_shared(a.m, P == 64 && half) || scr_lds_bytes<P, false, kScrWaves>(a.K) > kScrLdsMax) {
         const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
-        hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, true>), dim3(grid),
-                           dim3(64 * (units < kScrWaves ? units : kScrWaves)), lds, st, a);
-    } else {
-        const size_t lds = scr_lds_bytes<P, false>(a.K);
-        const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, false>);
-        if (hipError_t e = raised->ensure(fn, kLdsMax); e != hipSuccess) return e;
-        hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, false>), dim3(grid), dim3(64 * kScrWaves), lds, st, a);
+        return launch_w<P, S, SX, ARITH, true, kScrWaves>(a, units < kScrWaves ? units : kScrWaves, raised, st);
     }
-    return hipGetLastError();
+    if constexpr (P <= 64)
+        if (half)
+            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2>(a, kScrWaves / 2, raised, st);
+    return launch_w<P, S, SX, ARITH, false, kScrWaves>(a, kScrWaves, raised, st);
 }
 
 template <int P, int SX>

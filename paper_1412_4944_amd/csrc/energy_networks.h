@@ -212,18 +212,11 @@ __host__ __device__ __forceinline__ void pk_top_sorted(const u16x2 (&x)[NV], u16
 }
 
 // Packed sorted lists (low half: signal of tile 0, high half: of tile 1), one per lane of a lane
-// pair -> sum of squares of the N largest of the pair's union: lanes 0-31 receive that of their
-// signal in tile 0, lanes 32-63 that of their signal in tile 1.
-template <int N>
-__device__ __forceinline__ float pk_pair_energy(const u16x2 (&a)[N], bool hi) {
+// pair -> f(the N largest of the pair's union, packed): the low lane of the pair gets the even ones, the high lane
+// the odd ones, and if N is odd both get the last one (second argument of f: it is that one).
+template <int N, class F>
+__device__ __forceinline__ void pk_pair_top(const u16x2 (&a)[N], bool hi, F f) {
     const unsigned msk = hi ? 0xffffffffu : 0u;
-    float s0 = 0.f, s1 = 0.f;
-    auto add = [&](unsigned w) {
-        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-        const f16x2 v = __builtin_bit_cast(f16x2, w);
-        s0 = fmaf((float)v[0], (float)v[0], s0);
-        s1 = fmaf((float)v[1], (float)v[1], s1);
-    };
     unsigned r[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {              // the high lanes list theirs in reverse
@@ -233,16 +226,40 @@ __device__ __forceinline__ float pk_pair_energy(const u16x2 (&a)[N], bool hi) {
 #pragma unroll
     for (int i = 0; i + 1 < N; i += 2) {       // low lanes: maximum i, high lanes: maximum i + 1
         auto t = __builtin_amdgcn_permlane32_swap(r[i], r[i + 1], false, false);
-        const unsigned f = t[0], s = t[1];
-        add(__builtin_bit_cast(unsigned, pk_max(__builtin_bit_cast(u16x2, f), __builtin_bit_cast(u16x2, s))));
+        const unsigned p = t[0], q = t[1];
+        f(pk_max(__builtin_bit_cast(u16x2, p), __builtin_bit_cast(u16x2, q)), false);
     }
-    if constexpr (N % 2 == 1) {                // the middle one: the same in both lanes, counted once
+    if constexpr (N % 2 == 1) {
         auto t = __builtin_amdgcn_permlane32_swap(r[N - 1], r[N - 1], false, false);
-        const unsigned f = t[0], s = t[1];
-        add(__builtin_bit_cast(unsigned, pk_max(__builtin_bit_cast(u16x2, f), __builtin_bit_cast(u16x2, s))) & ~msk);
+        const unsigned p = t[0], q = t[1];
+        f(pk_max(__builtin_bit_cast(u16x2, p), __builtin_bit_cast(u16x2, q)), true);
     }
+}
+
+// Sum of squares of the N largest: lanes 0-31 receive that of their signal in tile 0, lanes 32-63
+// that of their signal in tile 1.
+template <int N>
+__device__ __forceinline__ float pk_pair_energy(const u16x2 (&a)[N], bool hi) {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    float s0 = 0.f, s1 = 0.f;
+    pk_pair_top<N>(a, hi, [&](u16x2 v, bool both) {
+        const f16x2 w = __builtin_bit_cast(f16x2, __builtin_bit_cast(unsigned, v) & (both && hi ? 0u : 0xffffffffu));
+        s0 = fmaf((float)w[0], (float)w[0], s0);
+        s1 = fmaf((float)w[1], (float)w[1], s1);
+    });
     const SwapPair t = swap32(s0, s1);
     return t.first + t.second;
+}
+
+// The N-th largest, packed, in both lanes of the pair.
+template <int N>
+__device__ __forceinline__ u16x2 pk_pair_least(const u16x2 (&a)[N], bool hi) {
+    u16x2 least = {0xffff, 0xffff};
+    pk_pair_top<N>(a, hi, [&](u16x2 v, bool) { least = __builtin_elementwise_min(least, v); });
+    const unsigned u = __builtin_bit_cast(unsigned, least);
+    auto t = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const unsigned p = t[0], q = t[1];
+    return __builtin_elementwise_min(__builtin_bit_cast(u16x2, p), __builtin_bit_cast(u16x2, q));
 }
 
 }  // namespace sbo

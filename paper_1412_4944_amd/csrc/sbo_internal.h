@@ -162,13 +162,14 @@ constexpr int kOpsF32 = 1, kOpsBf16 = 2, kOpsF16 = 4;
 constexpr bool screen_applies(int p, int s0, int arith) {
     return 2 * s0 <= p && (p <= 64 || arith == SBO_ARITH_F16X2);
 }
-// Which shape of the screening kernel: workgroups of 64 signals (true) or of 512.  The latter reads the
-// dictionary once per 512 signals and is 1.2 times as fast on a full chip, but its time is that of whole
-// rounds of one workgroup per CU: it is taken from 0.65 of its rounds' capacity on (measured, K = 32,
-// p = 64, workgroups of 64 / 512: 65536 signals 82 / 93 us, 81920 94 / 96, 98304 112 / 105, 131072 139 / 116).
-constexpr bool screen_shared(int64_t m) {
+// Which shape of the screening kernel: workgroups of 64 signals (true), or of 512 or 256, which read the
+// dictionary once for all of them and are up to 1.4 times as fast on a full chip.  The time of the larger ones is
+// that of whole rounds of one (512) or two (256) workgroups per CU.  Measured, p = 64, K = 32, workgroups of 64 /
+// 256: 32768 signals 55 / 61 us, 49152 69 / 65, 65536 84 / 71, 131072 145 / 107; p = 256, K = 16, 64 / 512: 81920
+// signals 385 / 394 us, 98304 466 / 446, 131072 603 / 527, 150000 675 / 738, 196608 853 / 823.
+constexpr bool screen_shared(int64_t m, bool p64_by_256) {
     const int64_t round = (int64_t)kNumCU * 512, rounds = (m + round - 1) / round;
-    return 20 * m < 13 * rounds * round;
+    return p64_by_256 ? 5 * m < 2 * round : 20 * m < 13 * rounds * round;
 }
 
 // dsw = D in the fp32 operand order of the coding kernels.
