@@ -10,13 +10,13 @@
 //   1. Screening.  One fp16 product per product (the leading fp16 part of the signal, scaled, times
 //      the leading part of the dictionary) gives every coefficient to about 2^-11; the magnitudes
 //      are rounded down to fp16.
-//        p = 64, s0 >= 5: the kept energy is only bounded from above.  For any t,
+//        p = 64, s0 >= 4: the kept energy is only bounded from above.  For any t,
 //            sum of the s0 largest c^2  <=  sum over all of max(c^2, t) - (p - s0) t,
 //      with equality at the s0-th largest one: two instructions per pair of magnitudes (a maximum and a dot
-//      product) instead of the six or more of a selection network.  t is the s0-th largest c^2 of
-//      the first block: the other blocks that are far from the signal look alike, and where the coefficients of
-//      the right one stand out the bound is nearly exact.  The magnitudes of the block that is ahead
-//      stay in registers, and at the end one selection network gives its kept energy.
+//      product) instead of the six or more of a selection network.  t is where the s0-th largest of p normal
+//      values of the signal's energy lies: blocks that are far from the signal look like that, and where the
+//      coefficients of the right one stand out the bound is nearly exact.  The magnitudes of the block that
+//      is ahead stay in registers, and at the end one selection network gives its kept energy.
 //        Otherwise: the networks for every block, on two signals per instruction (energy_networks.h).
 //      The bound or kept energy of every (signal, block) goes to LDS, 16 bits each.
 //   2. Decision.  The s0 largest magnitudes' norm of a block is off by at most
@@ -33,8 +33,8 @@
 //
 // Two shapes of the same work:
 //   energy_screen_kernel<..., false, W>: a workgroup takes 64 W signals, a wavefront 64 of them and all
-//     blocks; dictionary stages go through LDS, double-buffered.  W = 4 where two workgroups fit the LDS of a
-//     CU: one loads or decides while the other multiplies.
+//     blocks; dictionary stages go through LDS, double-buffered.  W = 8; W = 4, two workgroups per CU, for a last
+//     round that W = 8 would not fill.
 //   energy_screen_kernel<..., true, 8>: a workgroup takes 64 signals, and its wavefronts share out the
 //     blocks and read their dictionary rows straight from L2: more workgroups, for signal sets that
 //     would not fill the chip otherwise, and for K beyond the LDS table of the other.
@@ -80,13 +80,31 @@ struct ScrGeom {
     static constexpr int NV = WIDE ? 16 : P / 2;            // coefficients per lane, block and stage
 };
 
-// Which sizes screen with bounds from above (the header): where a wavefront meets enough blocks to pay
-// for its two selections, and these are long.
-constexpr bool scr_bound(int P, int SX, bool shared) { return P == 64 && SX >= 5 && !shared; }
+// Which sizes screen with bounds from above (the header): where a wavefront meets enough blocks to pay for
+// the selection at the end, and where that is long (p = 64, K = 32, 262144 signals: s0 = 2 176 us with bounds,
+// 166 with networks; s0 = 8 181, 195; p = 32, s0 = 12 107, 102).
+constexpr bool scr_bound(int P, int SX, bool shared) { return P == 64 && SX >= 4 && !shared; }
 
-// Kept energy of signal i (-1: none) in block j in the exact arithmetic, up to the signal's scale.
+// A lane's half of signal i (-1: none), as exact_energy takes it (p = 256: it reads the signal itself).
+template <int P, int ARITH>
+struct ExactRow {
+    static constexpr int N = P <= 64 ? P / 8 : 1;
+    f32x4 v[N];
+    __device__ __forceinline__ void load(const ScrArgs& g, int64_t i, int h) {
+        if constexpr (P <= 64) {
+            const f32x4* row = reinterpret_cast<const f32x4*>(g.Y + (i < 0 ? 0 : i) * P);
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                v[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (i >= 0) v[k] = row[ARITH == 0 ? h * N + k : (k >> 1) * 4 + h * 2 + (k & 1)];
+            }
+        }
+    }
+};
+
+// Kept energy of signal i (-1: none; y: its row) in block j in the exact arithmetic, up to the signal's scale.
 template <int P, int S, int SX, int ARITH>
-__device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
+__device__ float exact_energy(const ScrArgs& g, const ExactRow<P, ARITH>& y, int64_t i, int j, int lane) {
     constexpr int KS16 = P / 16, QN = P / 8;
     constexpr int NPL = ARITH == 3 ? 2 : 3;
     constexpr int NRT = P >= 32 ? P / 32 : 1;               // 32-row tiles of a block
@@ -95,27 +113,27 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
     const int tile0 = P >= 32 ? j * NRT : j >> 1;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const float* yrow = g.Y + (i < 0 ? 0 : i) * P;
-    auto load4 = [&](int d) {
-        return i >= 0 ? *reinterpret_cast<const f32x4*>(yrow + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    auto part = [&](int ks, int e) {           // dims ks*16 + h*8 + 4 e .. +3
+        if constexpr (P <= 64) return y.v[2 * ks + e];
+        else return i >= 0 ? *reinterpret_cast<const f32x4*>(yrow + ks * 16 + h * 8 + 4 * e) : f32x4{0.f, 0.f, 0.f, 0.f};
     };
 
     if constexpr (ARITH == 0) {
         static_assert(P <= 64, "p = 256 in fp32 is not screened");
-        f32x4 yb[QN];
-#pragma unroll
-        for (int q = 0; q < QN; ++q) yb[q] = load4(h * (P / 2) + 4 * q);
         const f32x4* D = reinterpret_cast<const f32x4*>(g.Dx) + (int64_t)tile0 * (QN * 64) + lane;
+        f32x4 a[QN][NRT];                      // (all on their way at once)
+#pragma unroll
+        for (int q = 0; q < QN; ++q)
+#pragma unroll
+            for (int mt = 0; mt < NRT; ++mt) a[q][mt] = D[(mt * QN + q) * 64];
         f32x16 acc[NRT];
 #pragma unroll
         for (int q = 0; q < QN; ++q) {
-            f32x4 a[NRT];
-#pragma unroll
-            for (int mt = 0; mt < NRT; ++mt) a[mt] = D[(mt * QN + q) * 64];
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
                 for (int mt = 0; mt < NRT; ++mt)
-                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mt][kk], yb[q][kk],
+                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][mt][kk], y.v[q][kk],
                                                                    (q == 0 && kk == 0) ? zero : acc[mt], 0, 0, 0);
         }
         float x[NV];
@@ -124,6 +142,17 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
             x[v] = fabsf(P == 16 ? ((j & 1) ? acc[0][(8 + v) & 15] : acc[0][v & 15]) : acc[(v >> 4) % NRT][v & 15]);
         return pair_top_energy<NV, S, SX>(x, g.s0, h != 0);
     } else {
+        const u32x4* D = reinterpret_cast<const u32x4*>(g.Dx) + (int64_t)tile0 * (KS16 * NPL * 64) + lane;
+        constexpr bool AHEAD = P <= 64;        // the dictionary rows on their way before anything else
+        u32x4 a_all[AHEAD ? KS16 : 1][AHEAD ? NRT : 1][NPL];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < NRT; ++mt)
+#pragma unroll
+                    for (int pl = 0; pl < NPL; ++pl) a_all[ks][mt][pl] = D[((mt * KS16 + ks) * NPL + pl) * 64];
+        }
         float scale = 1.f;
         if constexpr (ARITH == 3) {
             float vmax = 0.f;
@@ -131,7 +160,7 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
             for (int ks = 0; ks < KS16; ++ks)
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    const f32x4 v = load4(ks * 16 + h * 8 + 4 * e);
+                    const f32x4 v = part(ks, e);
                     vmax = fmaxf(fmaxf(fmaxf(vmax, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
                 }
             vmax = fmaxf(vmax, other_half(vmax));
@@ -140,7 +169,7 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
         u32x4 yq[KS16][NPL];
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks) {
-            const f32x4 v0 = load4(ks * 16 + h * 8), v1 = load4(ks * 16 + h * 8 + 4);
+            const f32x4 v0 = part(ks, 0), v1 = part(ks, 1);
             if constexpr (ARITH == 3) {
                 const F16x2Pair a = split_f16x2(v0.x * scale, v0.y * scale), b = split_f16x2(v0.z * scale, v0.w * scale);
                 const F16x2Pair c = split_f16x2(v1.x * scale, v1.y * scale), d = split_f16x2(v1.z * scale, v1.w * scale);
@@ -159,7 +188,6 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
         constexpr int TA[6] = {F16 ? 0 : 2, F16 ? 1 : 0, F16 ? 0 : 1, 1, 0, 0};
         constexpr int TB[6] = {F16 ? 1 : 0, F16 ? 0 : 2, F16 ? 0 : 1, 0, 1, 0};
         constexpr int T1 = F16 ? 3 : 6;
-        const u32x4* D = reinterpret_cast<const u32x4*>(g.Dx) + (int64_t)tile0 * (KS16 * NPL * 64) + lane;
         auto step = [&](const u32x4 (&a)[NPL], int ks, int t, f32x16 c) {
             if constexpr (F16)
                 return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[TA[t]]),
@@ -172,15 +200,10 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
             f32x16 acc[NRT];
 #pragma unroll
             for (int ks = 0; ks < KS16; ++ks) {
-                u32x4 a[NRT][NPL];
-#pragma unroll
-                for (int mt = 0; mt < NRT; ++mt)
-#pragma unroll
-                    for (int pl = 0; pl < NPL; ++pl) a[mt][pl] = D[((mt * KS16 + ks) * NPL + pl) * 64];
 #pragma unroll
                 for (int t = 0; t < T1; ++t)
 #pragma unroll
-                    for (int mt = 0; mt < NRT; ++mt) acc[mt] = step(a[mt], ks, t, (ks == 0 && t == 0) ? zero : acc[mt]);
+                    for (int mt = 0; mt < NRT; ++mt) acc[mt] = step(a_all[ks][mt], ks, t, (ks == 0 && t == 0) ? zero : acc[mt]);
             }
             float x[NV];
 #pragma unroll
@@ -223,17 +246,15 @@ __device__ float exact_energy(const ScrArgs& g, int64_t i, int j, int lane) {
 }
 
 // LDS of a workgroup:
-//   front       two dictionary stages (SHARED, p = 256: the signals); then the candidate lists, then the
-//               chunk histogram
+//   front       two dictionary stages (SHARED, p = 256: the signals); then the tasks of the resolution, then
+//               the chunk histogram
 //   E16         [K rounded up to whole stages][signals] 16 bits
 //   (front and E16 together first hold the signals while they are converted)
 //   thr, y2, r2 [signals] floats; key [signals] 64 bits; small change
 template <int P, bool SHARED, int W>
 constexpr size_t scr_front_bytes() {
     const size_t stages = SHARED ? (P > 64 ? (size_t)64 * P * 2 : 0) : (size_t)2 * ScrGeom<P>::STAGE_U * 16;
-    const size_t lists = (size_t)W * (SHARED ? 64 : 64 * W) * 2;
-    const size_t a = stages > lists ? stages : lists;
-    return a > 8192 ? a : 8192;                // the wavefronts' results (SHARED), the histogram
+    return stages > 8192 ? stages : 8192;      // the wavefronts' results (SHARED), the tasks, the histogram
 }
 template <int P, bool SHARED, int W>
 constexpr size_t scr_table_bytes(int K) {      // front + E16
@@ -245,7 +266,7 @@ constexpr size_t scr_table_bytes(int K) {      // front + E16
 }
 template <int P, bool SHARED, int W>
 constexpr size_t scr_lds_bytes(int K) {
-    return scr_table_bytes<P, SHARED, W>(K) + (size_t)(SHARED ? 64 : 64 * W) * 20 + (2 * W + 1) * 4;
+    return scr_table_bytes<P, SHARED, W>(K) + (size_t)(SHARED ? 64 : 64 * W) * 20 + (2 * W + 2) * 4;
 }
 
 // One step of the main loop issues the matrix instructions of the NEXT rows and the selection networks
@@ -283,8 +304,9 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     float* y2s = reinterpret_cast<float*>(thr + SIG);
     float* r2s = y2s + SIG;
     unsigned long long* key = reinterpret_cast<unsigned long long*>(r2s + SIG);
-    float* wred = reinterpret_cast<float*>(key + SIG);     // [2][W], then one flag
+    float* wred = reinterpret_cast<float*>(key + SIG);     // [2][W], then a flag and a count
     int* any_flag = reinterpret_cast<int*>(wred + 2 * W);
+    int* n_tasks = any_flag + 1;
 
     const int tid = threadIdx.x, NTH = blockDim.x, NW = NTH >> 6;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -422,7 +444,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     }
     norm.x = wave_max(norm.x);
     norm.y = wave_max(norm.y);
-    if (tid == 0) *any_flag = 0;
+    if (tid == 0) any_flag[0] = any_flag[1] = 0;
     if (lane == 0) {
         wred[wave] = norm.x;
         wred[W + wave] = norm.y;
@@ -457,8 +479,8 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         return better;
     };
     auto finish = [&](const u16x2 (&a)[SX], int j) { offer(pk_pair_energy<SX>(a, h != 0) * e_scale, j); };
-    // BOUND.  keep: the best block's magnitudes (two of a signal per word); tau: the s0-th largest of the
-    // first block, twice; slope: (p - s0) tau^2
+    // BOUND.  keep: the best block's magnitudes (two of a signal per word); tau: sqrt(t), twice; slope:
+    // (p - s0) t
     constexpr int NK = BOUND ? NV / 2 : 1;
     u16x2 keep[NT][NK], tau[NT];
     float slope[NT];
@@ -481,21 +503,21 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         }
         pk_top_sorted<2 * NK, SX>(t, a);
     };
-    auto first_block = [&](const Acc& acc) {
-        u16x2 x[NT][NK], a[SX];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) magnitudes(acc, 0, nt, x[nt]);
-        sorted_top(x, a);
-        const u16x2 least = pk_pair_least<SX>(a, h != 0);
+    if constexpr (BOUND) {
+        // two-sided normal tail of SX / P (a fit): where a block that has nothing to do with the signal has its
+        // SX-th largest coefficient
+        const float tail = __builtin_logf((float)P / SX), q2 = tail * (0.859f + 0.1314f * tail);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            tau[nt] = u16x2{least[nt], least[nt]};
-            const float t = (float)__builtin_bit_cast(f16x2, tau[nt])[0];
+            const float y2 = y2s[loc0 + nt * 32 + n];
+            const _Float16 t16 = (_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2, 0.f) * (q2 / P)));
+            const float t = (float)t16;
+            tau[nt] = __builtin_bit_cast(u16x2, f16x2{t16, t16});
             slope[nt] = (float)(P - SX) * 0.5f * (t * t);                  // (each lane of a pair takes half)
 #pragma unroll
             for (int v = 0; v < NK; ++v) keep[nt][v] = u16x2{0, 0};
         }
-    };
+    }
     // selection from acc, p <= 64: the UB blocks from j0 on; p = 256: 32 atoms of a block (first: of them all)
     auto select = [&](const Acc& acc, int j0, bool first) {
         if constexpr (BOUND) {
@@ -595,7 +617,6 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         stash(pre, 1);
         __syncthreads();
         project(acc0, 0);
-        if constexpr (BOUND) first_block(acc0);
         __syncthreads();
         for (int s = 0; s < n_stage; s += 2) {
             step(acc0, acc1, s);
@@ -635,7 +656,6 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             load(0);
             project(acc0);
             load(1);
-            if constexpr (BOUND) first_block(acc0);
             for (int t = 0; t < n_mine; t += 2) {
                 step(acc0, acc1, t);
                 if (t + 1 < n_mine) step(acc1, acc0, t + 1);
@@ -700,28 +720,57 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
 
     // Resolution: the candidates of the undecided signals, block by block.
     if (*any_flag != 0) {                      // uniform
-        unsigned short* list = reinterpret_cast<unsigned short*>(front) + wave * SIG;
+        // every row of the table becomes the list of its candidates, padded to whole tiles of 32 with 0xffff, and
+        // the tiles of all rows one list of tasks
+        unsigned short* tasks = reinterpret_cast<unsigned short*>(front);
         unsigned tr[SIG / 64];
 #pragma unroll
         for (int r = 0; r < SIG / 64; ++r) tr[r] = thr[r * 64 + lane];
         for (int j = wave; j < K; j += NW) {
+            unsigned short* row = E16 + j * SIG;
+            unsigned v[SIG / 64];
+#pragma unroll
+            for (int r = 0; r < SIG / 64; ++r) v[r] = row[r * 64 + lane];
             int len = 0;
 #pragma unroll
             for (int r = 0; r < SIG / 64; ++r) {
-                const bool in = E16[j * SIG + r * 64 + lane] >= tr[r];
+                const bool in = v[r] >= tr[r];
                 const unsigned long long mask = __ballot(in);
-                if (in) list[len + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)(r * 64 + lane);
+                if (in) row[len + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)(r * 64 + lane);
                 len += __popcll(mask);
             }
-            wave_fence();
-            for (int t0 = 0; t0 < len; t0 += 32) {         // uniform
-                const int id = t0 + n < len ? (int)list[t0 + n] : -1;
-                const float e = exact_energy<P, S, SX, ARITH>(g, id < 0 ? (int64_t)-1 : wg0 + id, j, lane);
-                // the largest energy (bits of a non-negative float), the lower block on a tie
-                if (h == 0 && id >= 0)
-                    atomicMax(&key[id], ((unsigned long long)__builtin_bit_cast(unsigned, e) << 32) | (unsigned)(~j));
+            if (len == 0) continue;            // uniform
+            const int tiles = (len + 31) >> 5;
+            if (len + lane < tiles * 32) row[len + lane] = 0xffff;
+            int at = 0;
+            if (lane == 0) at = atomicAdd(n_tasks, tiles);
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (lane < tiles) tasks[at + lane] = (unsigned short)(j * (SIG / 32) + lane);
+        }
+        __syncthreads();
+        const int n_task = *n_tasks;
+        // (the signals of the next task are on their way while the present one is computed)
+        int id_next = -1, j_next = 0;
+        ExactRow<P, ARITH> y_next;
+        auto look_up = [&](int t) {
+            id_next = -1;
+            if (t < n_task) {                  // uniform
+                const int task = __builtin_amdgcn_readfirstlane((int)tasks[t]);
+                j_next = task / (SIG / 32);
+                const int id = (int)E16[task * 32 + n];
+                id_next = id == 0xffff ? -1 : id;
             }
-            __builtin_amdgcn_wave_barrier();
+            y_next.load(g, id_next < 0 ? (int64_t)-1 : wg0 + id_next, h);
+        };
+        look_up(wave);
+        for (int t = wave; t < n_task; t += NW) {
+            const int id = id_next, j = j_next;
+            const ExactRow<P, ARITH> y = y_next;
+            look_up(t + NW);
+            const float e = exact_energy<P, S, SX, ARITH>(g, y, id < 0 ? (int64_t)-1 : wg0 + id, j, lane);
+            // the largest energy (bits of a non-negative float), the lower block on a tie
+            if (h == 0 && id >= 0)
+                atomicMax(&key[id], ((unsigned long long)__builtin_bit_cast(unsigned, e) << 32) | (unsigned)(~j));
         }
         __syncthreads();
         if (undecided) best = (int)~(unsigned)key[loc0 + lane];
@@ -758,7 +807,7 @@ hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t 
 
 template <int P, int S, int SX, int ARITH>
 hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
-    const bool half = P <= 64 && scr_lds_bytes<P, false, kScrWaves / 2>(a.K) <= kScrLdsMax / 2;
+    const bool half = P <= 64 && scr_lds_bytes<P, false, kScrWaves / 2>(a.K) <= kScrLdsMax / 2 && screen_by_256(a.m);
     if (screen_shared(a.m, P == 64 && half) || scr_lds_bytes<P, false, kScrWaves>(a.K) > kScrLdsMax) {
         const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
         return launch_w<P, S, SX, ARITH, true, kScrWaves>(a, units < kScrWaves ? units : kScrWaves, raised, st);

@@ -251,15 +251,4 @@ __device__ __forceinline__ float pk_pair_energy(const u16x2 (&a)[N], bool hi) {
     return t.first + t.second;
 }
 
-// The N-th largest, packed, in both lanes of the pair.
-template <int N>
-__device__ __forceinline__ u16x2 pk_pair_least(const u16x2 (&a)[N], bool hi) {
-    u16x2 least = {0xffff, 0xffff};
-    pk_pair_top<N>(a, hi, [&](u16x2 v, bool) { least = __builtin_elementwise_min(least, v); });
-    const unsigned u = __builtin_bit_cast(unsigned, least);
-    auto t = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    const unsigned p = t[0], q = t[1];
-    return __builtin_elementwise_min(__builtin_bit_cast(u16x2, p), __builtin_bit_cast(u16x2, q));
-}
-
 }  // namespace sbo

@@ -162,11 +162,19 @@ constexpr int kOpsF32 = 1, kOpsBf16 = 2, kOpsF16 = 4;
 constexpr bool screen_applies(int p, int s0, int arith) {
     return 2 * s0 <= p && (p <= 64 || arith == SBO_ARITH_F16X2);
 }
-// Which shape of the screening kernel: workgroups of 64 signals (true), or of 512 or 256, which read the
-// dictionary once for all of them and are up to 1.4 times as fast on a full chip.  The time of the larger ones is
-// that of whole rounds of one (512) or two (256) workgroups per CU.  Measured, p = 64, K = 32, workgroups of 64 /
-// 256: 32768 signals 55 / 61 us, 49152 69 / 65, 65536 84 / 71, 131072 145 / 107; p = 256, K = 16, 64 / 512: 81920
-// signals 385 / 394 us, 98304 466 / 446, 131072 603 / 527, 150000 675 / 738, 196608 853 / 823.
+// Which shape of the screening kernel (p <= 64): workgroups of 256 signals, two per CU, instead of 512 where the
+// last round of the latter would be at most 0.65 full (196608 signals, p = 64, K = 32: 141 us instead of 160); on
+// full rounds they are equal, but with fewer signals per list of candidates the resolution costs more (262144
+// signals, near-random dictionary: 164 us instead of 142).
+constexpr bool screen_by_256(int64_t m) {
+    const int64_t round = (int64_t)kNumCU * 512, rest = m % round;
+    return rest != 0 && 20 * rest < 13 * round;
+}
+// And whether workgroups of 64 signals are better than both: the larger ones read the dictionary once for
+// all of theirs and are up to 1.4 times as fast on a full chip, but their time is that of whole rounds.
+// Measured, p = 64, K = 32, workgroups of 64 / 256: 32768 signals 55 / 61 us, 49152 69 / 65, 65536 84 / 71, 131072
+// 145 / 107; p = 256, K = 16, 64 / 512: 81920 signals 385 / 394 us, 98304 466 / 446, 131072 603 / 527, 150000 675 /
+// 738, 196608 853 / 823.
 constexpr bool screen_shared(int64_t m, bool p64_by_256) {
     const int64_t round = (int64_t)kNumCU * 512, rounds = (m + round - 1) / round;
     return p64_by_256 ? 5 * m < 2 * round : 20 * m < 13 * rounds * round;

@@ -110,7 +110,7 @@ def test_code_over_signal_scales_and_dynamic_range(arith, p, K, s0):
 SCREEN_EDGES = [                                         # both shapes, their borders and remainders; a table
                                                          # too large for 512 signals (the last two)
     (64, 1, 8, 1), (64, 9, 16, 65), (32, 5, 16, 193), (16, 7, 8, 63), (16, 1, 1, 64), (256, 3, 16, 129),
-    (64, 3, 4, 52428), (64, 2, 6, 52429), (64, 119, 8, 85197), (32, 7, 3, 86000 + 513), (16, 5, 8, 86016 + 31), (256, 2, 12, 86016 + 1),
+    (64, 3, 4, 52428), (64, 2, 6, 52429), (64, 119, 8, 85196), (64, 3, 8, 85197), (32, 7, 3, 86000 + 513), (16, 5, 8, 86016 + 31), (256, 2, 12, 86016 + 1),
     (64, 4, 3, 131072), (32, 5, 5, 131073), (16, 160, 3, 90001), (64, 130, 2, 86081),
 ]
 
