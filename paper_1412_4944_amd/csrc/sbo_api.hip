@@ -31,6 +31,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.counts = (int32_t*)take((size_t)K * 4);
     w.offsets = (int32_t*)take((size_t)(K + 1) * 4);
     w.perm = (int32_t*)take((size_t)m_max * 4);
+    w.group_done = (int*)take(4);
     w.energy = (float*)take((size_t)m_max * 4);
     w.dsw = (float*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dsb = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 6);
@@ -241,10 +242,11 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     workspace_layout(p, K, s0, m_max, &c->ws, c->ws_base);
     c->ws.raised = &c->raised;
     c->ws.parts_accum = c->coding_arith != SBO_ARITH_F32;
-    // Three pieces of the workspace carry an invariant between calls: the chunk histograms, the
-    // finished-workgroup counter and the counters of polar_wide.hip are zero whenever no call is in flight.
+    // Some pieces of the workspace carry an invariant between calls: the chunk histograms, the two
+    // finished-workgroup counters and the counters of polar_wide.hip are zero whenever no call is in flight.
     e = hipMemsetAsync(c->ws.chunk_count, 0, (size_t)max_chunks() * K * 4, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->ws.sq_counter, 0, 4, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws.group_done, 0, 4, c->stream);
     if (e == hipSuccess && p > 64) e = hipMemsetAsync(c->ws.wide_sync, 0, polar_wide_sync_bytes(K), c->stream);
     if (e != hipSuccess) {
         (void)hipFree(c->ws_base);

@@ -89,6 +89,7 @@ struct Workspace {
     int32_t* counts;       // [K]
     int32_t* offsets;      // [K+1]
     int32_t* perm;         // [m_max]
+    int* group_done;       // [1] workgroups of the scatter that have read the histograms (0 between launches)
     // coding
     float* energy;         // [m_max] kept energy in the winning block
     float* dsw;            // [ceil(K*p/64)*64][p] dictionary in MFMA operand order

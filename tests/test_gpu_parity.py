@@ -144,6 +144,20 @@ def test_screened_block_choice(p, K, s0, m, close):
         assert close or (blk != outs[0]).mean() < 0.01
 
 
+@pytest.mark.parametrize("K,m", [(256, 3000), (200, 20001), (257, 3000), (32, 131072), (32, 131073), (1, 262145)])
+def test_group_scan_inside_scatter(K, m):
+    """Both sides of the rule by which the scan over the chunks is part of the scatter; twice on one
+    context (the histograms are set back)."""
+    rng = np.random.default_rng(K + m)
+    with Sbo(16, K, 2, m) as g:
+        for _ in range(2):
+            blk = rng.integers(0, K, m).astype(np.int32)
+            counts, offsets, perm = g.group(blk)
+            assert np.array_equal(counts, np.bincount(blk, minlength=K))
+            assert np.array_equal(offsets, np.r_[0, np.cumsum(counts)])
+            assert np.array_equal(perm, np.argsort(blk, kind="stable"))
+
+
 @pytest.mark.parametrize("K,m", [(4, 1024), (32, 5000), (128, 70001), (1, 100), (1000, 3000), (7, 1)])
 def test_group_matches_oracle(K, m):
     rng = np.random.default_rng(K * 1000 + m)
