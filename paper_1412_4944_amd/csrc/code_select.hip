@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
         }
     }
 
-    tile_select<P, S, false>(acc, h, n, active, i, s0, ctile_all + wave * 32 * LDC,
+    tile_select<P, S>(acc, h, n, active, i, s0, ctile_all + wave * 32 * LDC,
                              stage_all + wave * kSelectStageWords, supp, coef, err);
 }
 
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256) void select_wide_split_kernel(const float* __r
         __syncthreads();
     }
 
-    tile_select<P, S, false>(acc, h, n, active, i, s0, nullptr, stage_all + wave * kSelectStageWords, supp, coef,
+    tile_select<P, S>(acc, h, n, active, i, s0, nullptr, stage_all + wave * kSelectStageWords, supp, coef,
                              err);
 }
 

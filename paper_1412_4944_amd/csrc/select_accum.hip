@@ -15,12 +15,16 @@
 //   selection   (select_tile.h) from the accumulators;
 //   product     P_j += x y^T: atoms on M, dims on N, SIGNALS contracted, so both operands are
 //                             needed with eight consecutive signals per lane: the split parts of
-//                             y go through a wave-private LDS tile [dim][signal] (lane pairs
-//                             exchange halves so that every write is a whole word), the s0 kept
-//                             coefficients of every signal are scattered into a zeroed tile
+//                             y go through a wave-private LDS tile [signal][dim], from which
+//                             ds_read_b64_tr_b16 takes them transposed, the s0 kept coefficients of every signal are scattered into a zeroed tile
 //                             [atom][signal] and wiped again after use; 16 signals at a time.
 // Accumulators stay in registers across the tiles of the piece; the wavefronts are added in
 // wavefront order, the pieces of a block in piece order by the kernel that consumes them.
+//
+// What bounds it: instruction issue and LDS round trips of two wavefronts per SIMD, not memory (Y is
+// read once).  Measured, 262144 signals, K = 32, p = 64, s0 = 8: 61 us with y transposed word by word through
+// lane exchanges and the copies of the accumulators stored entry by entry, 49 us as it is (with the shorter
+// selection of select_tile.h); 2^20 signals, K = 128: 265 -> 190 us.
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "select_tile.h"
@@ -30,7 +34,6 @@ namespace sbo {
 namespace {
 
 constexpr int kSaWaves = 8;
-
 
 template <int P, int S>
 __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
@@ -48,6 +51,8 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     constexpr int OPS_B = 6 * PLANE_B;         // x tile (3 parts) + y tile (3 parts)
     constexpr int REGION_B = (OPS_B > CT_B ? OPS_B : CT_B);
     constexpr int WAVE_B = kSelectStageWords * 4 + REGION_B;
+    constexpr int YU = P / 8 - 1 < 7 ? P / 8 - 1 : 7;      // of a signal's 16-byte units
+    constexpr int NE = (S + 3) / 4;            // kept entries per lane and half tile
 
     // piece_start[K+1] | tmp[16] | pad | Qs[Q_U] | per wavefront: stage | region
     extern __shared__ int lds[];
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     int* stage = reinterpret_cast<int*>(waves_base + (size_t)wave * WAVE_B);
     unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords);
     unsigned char* xt = region;                // [3 parts][ROWS atoms][16 signals] bf16
-    unsigned char* yt = region + 3 * PLANE_B;  // [3 parts][ROWS dims][16 signals] bf16
+    unsigned char* yt = region + 3 * PLANE_B;  // [3 parts][16 signals][P dims] bf16
     // the x tile starts out zero (and is left zero by every tile)
     for (int e = lane; e < 3 * PLANE_B / 16; e += 64) reinterpret_cast<u32x4*>(xt)[e] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
@@ -178,7 +183,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
         // product below.
         // The tie-breaking scratch is the operand region: the x tile is zeroed again if it was used.
         bool ties = false;
-        tile_select<P, S, false>(acc, h, n, active, i, s0, reinterpret_cast<float*>(region), stage, supp, coef,
+        tile_select<P, S>(acc, h, n, active, i, s0, reinterpret_cast<float*>(region), stage, supp, coef,
                                  err, &ties);
         if (ties) {                            // uniform (rare): the scratch overwrote the zeroed x tile
             for (int e = lane; e < 3 * PLANE_B / 16; e += 64)
@@ -194,52 +199,58 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // y parts -> [dim][signal]: a lane holds (dim pair, own signal) words; the lanes of
-            // neighbouring signals swap halves, so that the even one writes (signal pair, even dim)
-            // and the odd one (signal pair, odd dim)
-            {
-                const bool odd = n & 1;
-                const unsigned sel = odd ? 0x03020706u : 0x05040100u;
+            // y parts: rows of signals as they are, 16-byte units (8 dims) of a row in an order that depends
+            // on the row; they are transposed on the way out
+            if (mine) {
 #pragma unroll
                 for (int ks = 0; ks < KS16; ++ks)
 #pragma unroll
                     for (int pl = 0; pl < 3; ++pl)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            const unsigned own = yq[ks][pl][c];
-                            const unsigned oth =
-                                (unsigned)__builtin_amdgcn_update_dpp(0, (int)own, kDppXor1, 0xf, 0xf, true);
-                            const unsigned w = __builtin_amdgcn_perm(oth, own, sel);
-                            const int dim = ks * 16 + h * 8 + 2 * c + (odd ? 1 : 0);
-                            if (mine) *reinterpret_cast<unsigned*>(yt + pl * PLANE_B + tr_off(dim, sc & ~1)) = w;
-                        }
+                        *reinterpret_cast<u32x4*>(yt + pl * PLANE_B + sc * (P * 2) + (((ks * 2 + h) ^ (sc & YU)) << 4)) = yq[ks][pl];
             }
-            // kept coefficients -> [atom][signal]; the two lanes of a signal share its entries
+            // kept coefficients -> [atom][signal]; four lanes of a signal share its entries
             // (entries that do not exist go to the dummy row instead of a branch)
-            int at_[(S + 1) / 2];
+            int at_[NE];
+            {
+                const int sx = lane & 15, row = 16 * half + sx;
 #pragma unroll
-            for (int t = 0; t < (S + 1) / 2; ++t) {
-                const int pos = 2 * t + h;
-                const bool have = mine && active && pos < s0;
-                const int atom = stage[stage_idx(n, 0, have ? pos : 0)];
-                const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx(n, 1, have ? pos : 0)]));
-                at_[t] = tr_off(have ? (atom & (ROWS - 1)) : ROWS, sc);   // row ROWS: nobody reads it
-                *reinterpret_cast<unsigned short*>(xt + at_[t]) = (unsigned short)(w.hi >> 16);
-                *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = (unsigned short)(w.mid >> 16);
-                *reinterpret_cast<unsigned short*>(xt + 2 * PLANE_B + at_[t]) = (unsigned short)(w.lo >> 16);
+                for (int t = 0; t < NE; ++t) {
+                    const int pos = 4 * t + (lane >> 4);
+                    const bool have = row < cnt_t && pos < s0;
+                    const int atom = stage[stage_idx(row, 0, have ? pos : 0)];
+                    const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx(row, 1, have ? pos : 0)]));
+                    at_[t] = tr_off(have ? (atom & (ROWS - 1)) : ROWS, sx);   // row ROWS: nobody reads it
+                    *reinterpret_cast<unsigned short*>(xt + at_[t]) = (unsigned short)(w.hi >> 16);
+                    *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = (unsigned short)(w.mid >> 16);
+                    *reinterpret_cast<unsigned short*>(xt + 2 * PLANE_B + at_[t]) = (unsigned short)(w.lo >> 16);
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // operands: lane (h, n) takes signals 8h .. 8h+7 of atom resp. dim t*32 + n
+            // operands: lane (h, n) takes signals 8h .. 8h+7 of atom resp. dim t*32 + n; the dims by
+            // ds_read_b64_tr_b16 (of 16 lanes, lane i addresses four dims, 4 (i & 3) .., of signal i >> 2 and
+            // receives dim i of the four signals)
             u32x4 xa[MT][3], yb[MT][3];
 #pragma unroll
-            for (int t = 0; t < MT; ++t)
+            for (int t = 0; t < MT; ++t) {
+                int ya[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int sig = 8 * h + 4 * k + ((lane & 15) >> 2), d = (t * 32 + (lane & 16) + 4 * (lane & 3)) & (P - 1);
+                    ya[k] = sig * (P * 2) + (((d >> 3) ^ (sig & YU)) << 4) + (d & 4) * 2;
+                }
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) {
+                    typedef short s16x4 __attribute__((ext_vector_type(4)));
+                    typedef __attribute__((address_space(3))) s16x4* lds_ptr;
                     xa[t][pl] = *reinterpret_cast<const u32x4*>(xt + pl * PLANE_B + tr_off(t * 32 + n, 8 * h));
-                    yb[t][pl] = *reinterpret_cast<const u32x4*>(yt + pl * PLANE_B + tr_off(t * 32 + n, 8 * h));
+                    const s16x4 y0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(yt + pl * PLANE_B + ya[0]));
+                    const s16x4 y1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(yt + pl * PLANE_B + ya[1]));
+                    const u32x2 u0 = __builtin_bit_cast(u32x2, y0), u1 = __builtin_bit_cast(u32x2, y1);
+                    yb[t][pl] = u32x4{u0.x, u0.y, u1.x, u1.y};
                 }
+            }
 #pragma unroll
             for (int t = 0; t < 6; ++t)
 #pragma unroll
@@ -252,7 +263,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();   // the operands have been read: wipe the x entries again
 #pragma unroll
-            for (int t = 0; t < (S + 1) / 2; ++t) {
+            for (int t = 0; t < NE; ++t) {
                 *reinterpret_cast<unsigned short*>(xt + at_[t]) = 0;
                 *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = 0;
                 *reinterpret_cast<unsigned short*>(xt + 2 * PLANE_B + at_[t]) = 0;
@@ -263,32 +274,35 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     }
     __syncthreads();                           // all tiles done: their LDS becomes the exchange area
 
-    // The wavefronts' accumulators are added in wavefront order: every wavefront stores its own
-    // copy atom-major (register r of tile (mt, nt) in lane (h, n) is atom mt*32 + (r/4)*8 + h*4 +
-    // r%4, dimension nt*32 + n), then every thread adds the NW copies of four consecutive entries
-    // and writes them to the piece result.
-    static_assert((size_t)PP * 4 <= (size_t)WAVE_B, "a copy fits the wave's own area");
+    // The wavefronts' accumulators are added in wavefront order: every wavefront stores its own copy as it
+    // holds it, 16 bytes per lane (register r of tile (mt, nt) in lane (h, n) is atom mt*32 + (r/4)*8 + h*4 +
+    // r%4, dimension nt*32 + n), then every thread adds the NW copies of a unit, four atoms of one
+    // dimension, and writes them to the piece result.
+    constexpr int UNITS = MT * MT * 4 * 64;
+    static_assert((size_t)UNITS * 16 <= (size_t)WAVE_B, "a copy fits the wave's own area");
     {
-        float* mine = reinterpret_cast<float*>(waves_base + (size_t)wave * WAVE_B);
+        f32x4* mine = reinterpret_cast<f32x4*>(waves_base + (size_t)wave * WAVE_B) + lane;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < MT; ++nt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int atom = mt * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-                    const int dim = nt * 32 + n;
-                    if (atom < P && dim < P) mine[atom * P + dim] = accM[mt][nt][r];
-                }
+                for (int q = 0; q < 4; ++q)
+                    mine[((mt * MT + nt) * 4 + q) * 64] = f32x4{accM[mt][nt][4 * q], accM[mt][nt][4 * q + 1],
+                                                                accM[mt][nt][4 * q + 2], accM[mt][nt][4 * q + 3]};
     }
     __syncthreads();
-    f32x4* out = reinterpret_cast<f32x4*>(partial + (int64_t)id * PP);
-    for (int e4 = tid; e4 < PP / 4; e4 += NTH) {
+    float* out = partial + (int64_t)id * PP;
+    for (int u = tid; u < UNITS; u += NTH) {
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < NW; ++w)
-            sum += reinterpret_cast<const f32x4*>(waves_base + (size_t)w * WAVE_B)[e4];
-        out[e4] = sum;
+            sum += reinterpret_cast<const f32x4*>(waves_base + (size_t)w * WAVE_B)[u];
+        const int tile = u >> 8, atom = (tile / MT) * 32 + ((u >> 6) & 3) * 8 + ((u >> 5) & 1) * 4;
+        const int dim = (tile % MT) * 32 + (u & 31);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (atom + k < P && dim < P) out[(atom + k) * P + dim] = sum[k];
     }
 }
 

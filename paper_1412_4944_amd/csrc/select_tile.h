@@ -14,26 +14,34 @@ namespace sbo {
 // signal).  Exact magnitude ties beyond the trivial one are resolved by a sequential
 // per-signal pass through the wave-private LDS tile ct[32][P+1] (p <= 64; for larger p by
 // running counts over the registers, and ct is not used: pass nullptr).  The (atom, coefficient)
-// rows are first compacted in the wave-private LDS area stage[32][2][16] (words) and then
+// rows are first compacted in the wave-private LDS area stage[2][16][32] (words) and then
 // written with one or a few wide stores per lane (lane half 0: supp row, half 1: coef row),
 // because scattered 4-byte stores to rows in original signal order are what this step
-// would otherwise wait on.
-// KEEP_X: on return ct[n][atom] holds the sparse code x of every signal of the tile
-// (kept coefficients, zeros elsewhere).  Without KEEP_X ct is touched only on the tie path
-// (*used_ct is then set).  On return the compacted rows are still in `stage`: entry pos of
-// signal n at stage_idx(n, 0, pos) (atom) and stage_idx(n, 1, pos) (coefficient bits).
+// would otherwise wait on.  ct is touched only on the tie path (*used_ct is then set).  On return the compacted rows
+// are still in `stage`: entry pos of signal n at stage_idx(n, 0, pos) (atom) and stage_idx(n, 1, pos)
+// (coefficient bits).
+//
+// What bounds it: instruction issue (it was 7500 cycles a tile of 32 signals for a wavefront, most of them for a
+// branch and two swizzled addresses per entry; positions now come from packed counts, and an entry is a
+// comparison, an address and two predicated stores).  select_kernel, 100003 signals, p = 64: 32.8 -> 29.4 us.
 constexpr int kSelectStageWords = 32 * 2 * 16;
 
 // Word index of entry `pos` (< 16) of signal row n in the stage area; kind 0 = atom, 1 =
-// coefficient bits.  A row is 32 words = 8 groups of 4 (groups 0-3 atoms, 4-7 coefficients);
-// the group index is XORed with the row number so that lanes writing the same entry of
-// different rows do not all land in one LDS bank (a plain [n][32] layout would put them there),
-// while the four words of a group stay together for the 16-byte copy out.
-__device__ __forceinline__ int stage_idx(int n, int kind, int pos) {
-    return n * 32 + ((((kind << 2) | (pos >> 2)) ^ (n & 7)) << 2) + (pos & 3);
-}
+// coefficient bits.  All lanes n of one entry are neighbours.
+__device__ __forceinline__ int stage_idx(int n, int kind, int pos) { return kind * 512 + pos * 32 + n; }
 
-template <int P, int S, bool KEEP_X>
+// The value in the other lane of the pair (all lanes active).
+__device__ __forceinline__ unsigned pair_other(unsigned x, int h) {
+    auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const unsigned lo = r[0], hi = r[1];
+    return h ? lo : hi;
+}
+__device__ __forceinline__ float pair_other(float x, int h) {
+    return __builtin_bit_cast(float, pair_other(__builtin_bit_cast(unsigned, x), h));
+}
+__device__ __forceinline__ int pair_other(int x, int h) { return (int)pair_other((unsigned)x, h); }
+
+template <int P, int S>
 __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, bool active, int64_t i,
                                             int s0, float* ct, int* stage,
                                             int32_t* __restrict__ supp, float* __restrict__ coef,
@@ -55,7 +63,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     float top[S], oth[S], mrg[S];
     top_sorted<NVL, S>(mag, top);
 #pragma unroll
-    for (int t = 0; t < S; ++t) oth[t] = other_half(top[t]);
+    for (int t = 0; t < S; ++t) oth[t] = pair_other(top[t], h);
 #pragma unroll
     for (int t = 0; t < S; ++t) mrg[t] = fmaxf(top[t], oth[S - 1 - t]);
     bitonic_merge_desc<S>(mrg);
@@ -64,44 +72,55 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     for (int t = 1; t < S; ++t) tau = (t == s0 - 1) ? mrg[t] : tau;
 
     // Entries with |c| >= tau, per group of 4 consecutive atoms (the groups alternate
-    // between the two lanes of a signal).  Exactly s0 of them: no tie at tau to break.
-    int own[NVL / 4], par[NVL / 4], total = 0;
+    // between the two lanes of a signal), four groups to a word.  Exactly s0 of them: no tie at tau to
+    // break.  (A lane without a signal keeps nothing.)
+    constexpr int NG = NVL / 4, NWD = NG / 4;
+    const float keep_from = active ? tau : __builtin_inff();
+    unsigned own[NWD], par[NWD], total = 0;
 #pragma unroll
-    for (int g = 0; g < NVL / 4; ++g) {
-        own[g] = 0;
+    for (int w = 0; w < NWD; ++w) {
+        own[w] = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) own[g] += mag[4 * g + e] >= tau;
-        par[g] = other_half(own[g]);
-        total += own[g] + par[g];
+        for (int g = 0; g < 4; ++g) {
+            unsigned k = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k += mag[16 * w + 4 * g + e] >= keep_from;
+            own[w] |= k << (8 * g);
+        }
+        par[w] = pair_other(own[w], h);
+        total = __builtin_amdgcn_sad_u8(own[w], 0u, __builtin_amdgcn_sad_u8(par[w], 0u, total));
     }
-    const bool simple = !active || total == s0;
+    const bool simple = !active || (int)total == s0;
 
     if (__all(simple)) {
         // Every entry with |c| >= tau is kept.  Emit in ascending atom order.
-        int run = 0;
+        unsigned before = 0;                   // entries of earlier words
         float dropped = 0.f;
 #pragma unroll
-        for (int g = 0; g < NVL / 4; ++g) {
-            int pos = run + (h ? par[g] : 0);
-            run += own[g] + par[g];
+        for (int w = 0; w < NWD; ++w) {
+            const unsigned both = own[w] + par[w], upto = both * 0x01010101u;      // inclusive sums, per byte
+            const unsigned start = upto - both + (h ? par[w] : 0u) + before * 0x01010101u;
+            before += upto >> 24;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int f = 4 * g + e;
-                const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + h * 4 + (f & 3);
-                if (mag[f] >= tau) {
-                    if (active) {             // (a lane without a signal keeps "everything")
-                        stage[stage_idx(n, 0, pos)] = atom;
-                        stage[stage_idx(n, 1, pos)] = __builtin_bit_cast(int, c[f]);
+            for (int g = 0; g < 4; ++g) {
+                unsigned pos = (start >> (8 * g)) & 0xffu;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int f = 16 * w + 4 * g + e;
+                    const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + h * 4 + (f & 3);
+                    const bool keep = mag[f] >= keep_from;
+                    if (keep) {
+                        int* at = stage + stage_idx(n, 0, (int)pos);
+                        at[0] = atom;
+                        at[512] = __builtin_bit_cast(int, c[f]);
                     }
-                    ++pos;
-                } else if (atom < P) {
-                    dropped += c[f] * c[f];
+                    pos += keep;
+                    const float rest = keep || atom >= P ? 0.f : c[f];
+                    dropped = fmaf(rest, rest, dropped);
                 }
-                if constexpr (KEEP_X)
-                    if (atom < P) ct[n * LDC + atom] = mag[f] >= tau ? c[f] : 0.f;
             }
         }
-        dropped += other_half(dropped);
+        dropped += pair_other(dropped, h);
         if (active && h == 0) err[i] = dropped;
     } else if constexpr (P > 64) {
         // Exact magnitude ties, in registers (a [32][P] scratch tile per wavefront would not fit
@@ -113,7 +132,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
         int gt = 0;
 #pragma unroll
         for (int f = 0; f < NVL; ++f) gt += mag[f] > tau;
-        gt += other_half(gt);
+        gt += pair_other(gt, h);
         const int need = s0 - gt;              // entries equal to tau still to take (>= 1)
         int run_eq = 0, run_keep = 0;
         float dropped = 0.f;
@@ -122,7 +141,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
             int eq_own = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) eq_own += mag[4 * g + e] == tau;
-            const int eq_par = other_half(eq_own);
+            const int eq_par = pair_other(eq_own, h);
             int eq_rank = run_eq + (h ? eq_par : 0);
             run_eq += eq_own + eq_par;
             bool keep[4];
@@ -134,7 +153,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                 eq_rank += is_eq;
                 keep_own += keep[e];
             }
-            const int keep_par = other_half(keep_own);
+            const int keep_par = pair_other(keep_own, h);
             int pos = run_keep + (h ? keep_par : 0);
             run_keep += keep_own + keep_par;
 #pragma unroll
@@ -152,7 +171,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                 }
             }
         }
-        dropped += other_half(dropped);
+        dropped += pair_other(dropped, h);
         if (active && h == 0) err[i] = dropped;
     } else {
         // Exact magnitude ties: walk each signal's coefficients in atom order.
@@ -168,7 +187,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
         int gt = 0;
 #pragma unroll
         for (int f = 0; f < NVL; ++f) gt += mag[f] > tau;
-        gt += other_half(gt);
+        gt += pair_other(gt, h);
         const int need = s0 - gt;              // entries equal to tau still to take (>= 1)
         if (active && h == 0) {
             int pos = 0, taken_eq = 0;
@@ -187,7 +206,6 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                     ++pos;
                 } else {
                     dropped += v * v;
-                    if constexpr (KEEP_X) ct[n * LDC + k] = 0.f;
                 }
             }
             err[i] = dropped;
@@ -200,16 +218,16 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (active) {
         int* dst = (h ? reinterpret_cast<int*>(coef) : supp) + i * s0;
+        const int* row = stage + stage_idx(n, h, 0);
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         typedef int i32x2 __attribute__((ext_vector_type(2)));
         if ((s0 & 3) == 0) {
             for (int t = 0; t < s0; t += 4)
-                *reinterpret_cast<i32x4*>(dst + t) = *reinterpret_cast<const i32x4*>(stage + stage_idx(n, h, t));
+                *reinterpret_cast<i32x4*>(dst + t) = i32x4{row[t * 32], row[t * 32 + 32], row[t * 32 + 64], row[t * 32 + 96]};
         } else if ((s0 & 1) == 0) {
-            for (int t = 0; t < s0; t += 2)
-                *reinterpret_cast<i32x2*>(dst + t) = *reinterpret_cast<const i32x2*>(stage + stage_idx(n, h, t));
+            for (int t = 0; t < s0; t += 2) *reinterpret_cast<i32x2*>(dst + t) = i32x2{row[t * 32], row[t * 32 + 32]};
         } else {
-            for (int t = 0; t < s0; ++t) dst[t] = stage[stage_idx(n, h, t)];
+            for (int t = 0; t < s0; ++t) dst[t] = row[t * 32];
         }
     }
     __builtin_amdgcn_wave_barrier();           // stage is reused by the caller's next tile
