@@ -7,8 +7,7 @@
 // Plane rotations are applied from the right to the columns of A = P_j and to V (starting at I)
 // until all columns of A are mutually orthogonal; then A = U diag(sigma) and
 // P_j = U diag(sigma) V^T, so Q_j = sum_c (A_c / sigma_c) V_c^T.  p/2 disjoint column pairs
-// (round-robin tournament) are rotated concurrently, TPP lanes per pair, one barrier per
-// tournament round.  Columns whose norm vanishes (rank-deficient P_j) are replaced by an
+// are rotated concurrently, TPP lanes per pair, one barrier per round.  Columns whose norm vanishes (rank-deficient P_j) are replaced by an
 // orthonormal completion, which is a valid choice of U there.
 #pragma once
 
@@ -87,106 +86,93 @@ __device__ __forceinline__ void jacobi_block(const BlockMatrixSource& src, float
     }
     __syncthreads();
 
-    // Round-robin tournament on P players: player P-1 stays, the others rotate; group pi
-    // meets columns ca, cb, which advance by one (mod P-1) every round.
+    // All pairs of P columns in P - 1 rounds of P / 2 disjoint pairs: the columns in two halves, every
+    // column of one against every one of the other, then each half likewise, and so on.  A group
+    // of lanes keeps its column of the first half in registers for the h rounds of a level, and only the
+    // others go round through LDS: half the LDS traffic of a tournament in which both columns move (p = 64,
+    // eigenvectors of a Gram matrix: 207 -> 187 us; what is left of a round, 900 cycles, is mostly the issue
+    // of 90 vector instructions by two wavefronts per SIMD; 8 lanes per pair: 15 % slower).
     const int pi = tid / TPP, sub = tid % TPP;
     const int r0 = sub * RPT;
+    auto get = [&](const float* col, float (&v)[RPT]) {
+        if constexpr (RPT % 4 == 0) {
+#pragma unroll
+            for (int t = 0; t < RPT; t += 4) {
+                const f32x4 w = *reinterpret_cast<const f32x4*>(col + r0 + t);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[t + e] = w[e];
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < RPT; ++t) v[t] = col[r0 + t];
+        }
+    };
+    auto put = [&](float* col, const float (&v)[RPT]) {
+        if constexpr (RPT % 4 == 0) {
+#pragma unroll
+            for (int t = 0; t < RPT; t += 4)
+                *reinterpret_cast<f32x4*>(col + r0 + t) = f32x4{v[t], v[t + 1], v[t + 2], v[t + 3]};
+        } else {
+#pragma unroll
+            for (int t = 0; t < RPT; ++t) col[r0 + t] = v[t];
+        }
+    };
     int sweeps_done = 0;
     for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
         int rotated = 0;
-        // columns as LDS offsets (column * LD), advanced by additions only
-        constexpr int WRAP = (P - 1) * LD;
-        int oa = (pi == 0 ? P - 1 : pi) * LD;
-        int ob = (pi == 0 ? 0 : P - 1 - pi) * LD;
-        for (int step = 0; step < P - 1; ++step) {
-            const int oi = min(oa, ob), oj = max(oa, ob);
-            float* ai = A + oi + r0;
-            float* aj = A + oj + r0;
-            float* vi = V + oi + r0;
-            float* vj = V + oj + r0;
-            float x[RPT], y[RPT], vx[RPT], vy[RPT];
-            if constexpr (RPT % 4 == 0) {
-#pragma unroll
-                for (int t = 0; t < RPT; t += 4) {
-                    const f32x4 a4 = *reinterpret_cast<const f32x4*>(ai + t);
-                    const f32x4 b4 = *reinterpret_cast<const f32x4*>(aj + t);
-                    const f32x4 c4 = *reinterpret_cast<const f32x4*>(vi + t);
-                    const f32x4 d4 = *reinterpret_cast<const f32x4*>(vj + t);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        x[t + e] = a4[e];
-                        y[t + e] = b4[e];
-                        vx[t + e] = c4[e];
-                        vy[t + e] = d4[e];
-                    }
-                }
-            } else {
+        for (int half = P / 2; half >= 1; half >>= 1) {
+            const int q = pi & (half - 1), first = (pi - q) * 2;         // the first column of the pair of halves
+            float x[RPT], vx[RPT];
+            get(A + (first + q) * LD, x);
+            get(V + (first + q) * LD, vx);
+            for (int step = 0; step < half; ++step) {
+                const int oj = (first + half + ((q + step) & (half - 1))) * LD;
+                float y[RPT], vy[RPT];
+                get(A + oj, y);
+                get(V + oj, vy);
+                float alpha = 0.f, beta = 0.f, gamma = 0.f;
 #pragma unroll
                 for (int t = 0; t < RPT; ++t) {
-                    x[t] = ai[t];
-                    y[t] = aj[t];
-                    vx[t] = vi[t];
-                    vy[t] = vj[t];
+                    alpha += x[t] * x[t];
+                    beta += y[t] * y[t];
+                    gamma += x[t] * y[t];
                 }
-            }
-            float alpha = 0.f, beta = 0.f, gamma = 0.f;
+                alpha = group_sum<TPP>(alpha);
+                beta = group_sum<TPP>(beta);
+                gamma = group_sum<TPP>(gamma);
+                // Rotation by theta with tan(2 theta) = 2 gamma / (beta - alpha), |theta| <= pi/4,
+                // from cos(2 theta) = |d| / hypot(d, 2 gamma).  One-ulp reciprocal square roots
+                // suffice: the iteration corrects itself.
+                const float d = beta - alpha, g2 = 2.f * gamma;
+                const float hh = d * d + g2 * g2;
+                // keep the V loads issued together with the A loads, ahead of the decision
 #pragma unroll
-            for (int t = 0; t < RPT; ++t) {
-                alpha += x[t] * x[t];
-                beta += y[t] * y[t];
-                gamma += x[t] * y[t];
-            }
-            alpha = group_sum<TPP>(alpha);
-            beta = group_sum<TPP>(beta);
-            gamma = group_sum<TPP>(gamma);
-            // Rotation by theta with tan(2 theta) = 2 gamma / (beta - alpha), |theta| <= pi/4,
-            // from cos(2 theta) = |d| / hypot(d, 2 gamma).  One-ulp reciprocal square roots
-            // suffice: the iteration corrects itself.
-            const float d = beta - alpha, g2 = 2.f * gamma;
-            const float hh = d * d + g2 * g2;
-            // keep the V loads issued together with the A loads, ahead of the decision
+                for (int t = 0; t < RPT; ++t) asm volatile("" : "+v"(vy[t]));
+                const float g2ab = gamma * gamma, ab = alpha * beta;
+                if (g2ab > (done * done) * ab) rotated = 1;      // another sweep is needed
+                if (g2ab > (kTol * kTol) * ab && hh > 1e-36f) {
+                    const float r = __builtin_amdgcn_rsqf(hh);
+                    const float w = 0.5f + 0.5f * (fabsf(d) * r);
+                    const float rc = __builtin_amdgcn_rsqf(w);
+                    const float cs = w * rc;
+                    const float sn = copysignf(0.5f * rc * r, d) * g2;
 #pragma unroll
-            for (int t = 0; t < RPT; ++t) asm volatile("" : "+v"(vx[t]), "+v"(vy[t]));
-            const float g2ab = gamma * gamma, ab = alpha * beta;
-            if (g2ab > (done * done) * ab) rotated = 1;          // another sweep is needed
-            if (g2ab > (kTol * kTol) * ab && hh > 1e-36f) {
-                const float r = __builtin_amdgcn_rsqf(hh);
-                const float w = 0.5f + 0.5f * (fabsf(d) * r);
-                const float rc = __builtin_amdgcn_rsqf(w);
-                const float cs = w * rc;
-                const float sn = copysignf(0.5f * rc * r, d) * g2;
-                float nx[RPT], ny[RPT], nvx[RPT], nvy[RPT];
-#pragma unroll
-                for (int t2 = 0; t2 < RPT; ++t2) {
-                    nx[t2] = cs * x[t2] - sn * y[t2];
-                    ny[t2] = sn * x[t2] + cs * y[t2];
-                    nvx[t2] = cs * vx[t2] - sn * vy[t2];
-                    nvy[t2] = sn * vx[t2] + cs * vy[t2];
-                }
-                if constexpr (RPT % 4 == 0) {
-#pragma unroll
-                    for (int t = 0; t < RPT; t += 4) {
-                        *reinterpret_cast<f32x4*>(ai + t) = f32x4{nx[t], nx[t + 1], nx[t + 2], nx[t + 3]};
-                        *reinterpret_cast<f32x4*>(aj + t) = f32x4{ny[t], ny[t + 1], ny[t + 2], ny[t + 3]};
-                        *reinterpret_cast<f32x4*>(vi + t) = f32x4{nvx[t], nvx[t + 1], nvx[t + 2], nvx[t + 3]};
-                        *reinterpret_cast<f32x4*>(vj + t) = f32x4{nvy[t], nvy[t + 1], nvy[t + 2], nvy[t + 3]};
+                    for (int t = 0; t < RPT; ++t) {
+                        const float xa = x[t], ya = y[t], xv = vx[t], yv = vy[t];
+                        x[t] = cs * xa - sn * ya;
+                        y[t] = sn * xa + cs * ya;
+                        vx[t] = cs * xv - sn * yv;
+                        vy[t] = sn * xv + cs * yv;
                     }
-                } else {
-#pragma unroll
-                    for (int t2 = 0; t2 < RPT; ++t2) {
-                        ai[t2] = nx[t2];
-                        aj[t2] = ny[t2];
-                        vi[t2] = nvx[t2];
-                        vj[t2] = nvy[t2];
-                    }
+                    put(A + oj, y);
+                    put(V + oj, vy);
                 }
+                if (step == half - 1) {        // uniform: the next level takes other columns
+                    put(A + (first + q) * LD, x);
+                    put(V + (first + q) * LD, vx);
+                }
+                __syncthreads();
             }
-            {
-                const int na = oa + LD, nb = ob + LD;
-                oa = pi == 0 ? oa : (na == WRAP ? 0 : na);        // player P-1 stays
-                ob = (pi == 0 || nb != WRAP) ? nb : 0;            // pi == 0: 0, 1, ..., P-2
-            }
-            __syncthreads();
         }
         sweeps_done = sweep + 1;
         if (!__syncthreads_or(rotated)) break;
