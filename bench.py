@@ -136,13 +136,13 @@ def roofline_entry(p, K, m, energy_ms, arith, workload, s0=8):
         # one fp16 product per product for every signal and block, then the context's arithmetic for the
         # blocks the screening's error bound leaves in (that share of the work depends on the data)
         peak = PEAK_MFMA_BF16_TFLOPS              # fp16 and bf16 MFMA share the 2500 TFLOP/s peak
-        # vector instructions of the main loop per 64 signals and block (p = 64, s0 = 8, the kernel's ISA):
-        # packed conversion, sorting networks and merges on two signals per instruction, about 300; one
+        # vector instructions of the main loop per 64 signals and block (p = 64, s0 >= 4, the kernel's ISA):
+        # packed conversion, maximum and dot product of the bound, the block ahead kept: 141; one
         # lane-operation per lane and instruction, against 256 CUs x 64 lanes x 2.4 GHz
-        sel_ops = 300.0 * 64.0 * (K * m / 64.0)
+        sel_ops = 141.0 * 64.0 * (K * m / 64.0)
         sel_peak = 256 * 64 * 2.4e9
-        extra = {"kernel": "energy_screen_kernel (screening: Q^T y once on the fp16 matrix cores + packed top-s0 energy "
-                           "of every block; then the blocks within the error bound of the best in " + arith + ")",
+        extra = {"kernel": "energy_screen_kernel (screening: Q^T y once on the fp16 matrix cores + a bound on the top-s0 "
+                           "energy of every block; then the blocks within the error bound of the best in " + arith + ")",
                  "peak_note": "2500 TFLOP/s dense fp16 MFMA, one product per product",
                  "executed_f16_tflops": achieved, "peak_f16_tflops": PEAK_MFMA_BF16_TFLOPS,
                  "vs_six_product_roof": achieved / (PEAK_MFMA_BF16_TFLOPS / SPLIT_PRODUCTS),
@@ -151,7 +151,7 @@ def roofline_entry(p, K, m, energy_ms, arith, workload, s0=8):
                                    "achieved_Tops": sel_ops / (energy_ms * 1e-3) / 1e12,
                                    "peak_Tops": sel_peak / 1e12,
                                    "frac": sel_ops / (energy_ms * 1e-3) / sel_peak}}
-        if p != 64 or s0 != 8:                 # the instruction count above is that of p = 64, s0 = 8
+        if p != 64 or s0 < 4:                  # the instruction count above is that of the bound
             del extra["selection_alu"]
     elif arith == "f16x2":
         peak = PEAK_MFMA_BF16_TFLOPS / 3
