@@ -30,9 +30,12 @@
 // the operand order and the squared error: 46 launches, 400 us) -> 125 us and nothing else; K = 1 in a
 // first training round 300 -> 125 us; eigenvectors of a Gram matrix (10 sweeps) 12.1 -> 1.8 ms.
 //
-// Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups, one per CU, and
-// workgroups start in order, so whatever else runs, the first team that is not done is or will be
-// complete.  Every wait is bounded all the same, and a team that gives up leaves NaN.
+// Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups, one per CU, and workgroups
+// start in order.  A launch that does not have the chip to itself can hold at most 15 workgroups of an
+// incomplete team on an XCD (32 CUs), so two launches at a time always leave room for one to complete a
+// team.  With contexts of this size on more than two streams the teams lie in consecutive workgroups instead
+// ("spread": at most 15 waiting ones on the whole chip per launch, barriers of the slower kind).  Every wait is
+// bounded all the same, and a team that gives up leaves NaN.
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "ns_scale.h"
@@ -86,10 +89,15 @@ struct WideArgs {
     int32_t* fallback;
     int32_t* iters_out;
     int max_iters, K, teams;
+    int spread;
     unsigned char* data;       // [teams][kTeamBytes]
     int* sync;                 // [teams][kSyncInts]
     SqTotalArgs sq;
 };
+
+__host__ __device__ inline int wide_team_wgs(int teams, int spread) {
+    return spread ? teams * kTeam : (teams + 7) / 8 * 128;
+}
 
 __device__ __forceinline__ float half_sum(float x) {           // over 32 lanes
     x = group_sum<16>(x);
@@ -904,8 +912,9 @@ template <bool NS>
 __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
-    // The 16 workgroups of a team lie eight apart: workgroups go round the eight XCDs, so a team shares an L2.
-    const int team_wgs = (g.teams + 7) / 8 * 128;
+    // The 16 workgroups of a team lie eight apart: workgroups go round the eight XCDs, so a team shares an L2
+    // (spread: next to each other).
+    const int team_wgs = wide_team_wgs(g.teams, g.spread);
     if ((int)blockIdx.x >= team_wgs) {         // uniform: the workgroups of the squared-error total
         const int b = (int)blockIdx.x - team_wgs;
         if (g.sq.out != nullptr && b < g.sq.nb)
@@ -913,7 +922,8 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
                                reinterpret_cast<double*>(lds));
         return;
     }
-    const int team = (int)blockIdx.x / 128 * 8 + (int)blockIdx.x % 8, q = (int)blockIdx.x % 128 / 8;
+    const int team = g.spread ? (int)blockIdx.x / 16 : (int)blockIdx.x / 128 * 8 + (int)blockIdx.x % 8;
+    const int q = g.spread ? (int)blockIdx.x % 16 : (int)blockIdx.x % 128 / 8;
     if (team >= g.teams) return;               // uniform
     float* red = reinterpret_cast<float*>(lds + kSmallLds);
     int* flag = reinterpret_cast<int*>(red + 1280);
@@ -1014,7 +1024,8 @@ hipError_t launch_polar_wide(int K, const float* M, const float* partial, const 
     a.data = reinterpret_cast<unsigned char*>(ws.wide);
     a.sync = ws.wide_sync;
     a.sq = sq;
-    const unsigned grid = (unsigned)((a.teams + 7) / 8 * 128 + (sq.out != nullptr ? sq.nb : 0));
+    a.spread = wide_streams() > 2;
+    const unsigned grid = (unsigned)(wide_team_wgs(a.teams, a.spread) + (sq.out != nullptr ? sq.nb : 0));
     const void* fn = newton_schulz_first ? reinterpret_cast<const void*>(&wide_polar_kernel<true>)
                                          : reinterpret_cast<const void*>(&wide_polar_kernel<false>);
     if (hipError_t e = ws.raised->ensure(fn, kLds); e != hipSuccess) return e;

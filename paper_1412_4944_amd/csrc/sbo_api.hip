@@ -2,6 +2,9 @@
 // All arithmetic is in the kernels; this file only enqueues them.
 #include "sbo_internal.h"
 
+#include <algorithm>
+#include <mutex>
+
 #include <cmath>
 #include <new>
 #include <string>
@@ -69,6 +72,25 @@ static bool shape_ok(int p, int K, int s0, int64_t m_max) {
     const int64_t lim = ((int64_t)1 << 31) / (p > s0 ? p : s0);
     if (m_max >= lim) return false;
     return true;
+}
+
+// The streams of the live contexts of p = 256.
+static std::mutex g_wide_mutex;
+static std::vector<hipStream_t> g_wide;
+int wide_streams() {
+    std::lock_guard<std::mutex> lock(g_wide_mutex);
+    int n = 0;
+    for (size_t i = 0; i < g_wide.size(); ++i) n += std::find(g_wide.begin(), g_wide.begin() + i, g_wide[i]) == g_wide.begin() + i;
+    return n;
+}
+static void wide_context(hipStream_t st, bool live) {
+    std::lock_guard<std::mutex> lock(g_wide_mutex);
+    if (live) {
+        g_wide.push_back(st);
+    } else {
+        auto it = std::find(g_wide.begin(), g_wide.end(), st);
+        if (it != g_wide.end()) g_wide.erase(it);
+    }
 }
 
 static thread_local std::string g_hip_text = "no HIP error recorded";
@@ -253,6 +275,7 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
         delete c;
         return hip_fail(e);
     }
+    if (p > 64) wide_context(c->stream, true);
     *out = c;
     return SBO_OK;
 }
@@ -260,6 +283,7 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
 int sbo_destroy(sbo_ctx* c) {
     if (!c) return SBO_EINVAL;
     hipError_t e = hipStreamSynchronize(c->stream);
+    if (c->p > 64) wide_context(c->stream, false);
     for (auto& s : c->spans) {
         (void)hipEventDestroy(s.beg);
         (void)hipEventDestroy(s.end);

@@ -450,6 +450,35 @@ def test_polar_p256_teams_of_workgroups(K, jacobi_only):
     print(f"  K={K} jacobi={jacobi_only}: worst |Q - Q_oracle| {w:.2e}", flush=True)
 
 
+def test_polar_p256_on_three_streams():
+    """Contexts on more than two streams: the teams take the other workgroup order; their launches overlap."""
+    import torch
+    p, K = 256, 9
+    rng = np.random.default_rng(31)
+    M32 = np.stack([(synth.random_onb(rng, p) * np.geomspace(1, 0.1, p)) @ synth.random_onb(rng, p)
+                    for _ in range(K)]).astype(np.float32)
+    M32[4][:, 200:] = M32[4][:, :56]                     # left to the Jacobi SVD
+    Dn = np.stack([orc.o_polar(M32[j].astype(np.float64)) for j in range(K)])
+    M = torch.from_numpy(M32).cuda()
+    D = [torch.zeros_like(M) for _ in range(3)]
+    torch.cuda.synchronize()
+    ctxs = []
+    for _ in range(3):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ctxs.append((s, sbo.sbo_create(p, K, 4, 256)))
+    for _ in range(3):
+        for (s, c), d in zip(ctxs, D):
+            with torch.cuda.stream(s):
+                sbo.sbo_polar(c, M, None, d)
+    torch.cuda.synchronize()
+    for s, c in ctxs:
+        sbo.sbo_destroy(c)
+    for d in D:
+        compare_Q(d.cpu().numpy(), Dn, M32.astype(np.float64), np.ones(K, bool))
+        assert torch.equal(d, D[0])
+
+
 JACOBI_CASES = [("tiny", dict(), 12), ("patch8", dict(m=4096 + 77), 10),
                 ("p256", dict(p=256, K=2, m=1300, s0=12, snr_db=25.0), 2)]
 
