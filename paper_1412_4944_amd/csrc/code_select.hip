@@ -17,14 +17,25 @@ namespace sbo {
 
 namespace {
 
-template <int P, int S>
+// What select_kernel needs to group the signals itself: the choices in, the results of the grouping out.
+struct GroupInSelect {
+    const int32_t* blk;
+    int m;
+    int32_t *counts, *offsets, *perm, *chunk_count;
+};
+
+// GROUP: the grouping of a small set (m <= kGroupInSelect) without a launch of its own.  Every workgroup sorts all
+// choices in its own LDS (the stable order of group.hip: each wavefront a quarter, counts, scan, scatter); the
+// first one also leaves counts, offsets and perm in memory and sets the histograms of the block choice back to zero.
+// A launch in a stream costs 4.5 us whatever it does, the sort in LDS less than that.
+template <int P, int S, bool GROUP>
 __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y,
                                                      const float* __restrict__ D, int K, int s0,
                                                      const int32_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ perm,
                                                      int32_t* __restrict__ supp,
                                                      float* __restrict__ coef,
-                                                     float* __restrict__ err) {
+                                                     float* __restrict__ err, GroupInSelect g) {
     constexpr int KS = P / 2;
     constexpr int QN = P / 8;
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-row tiles per block
@@ -43,6 +54,38 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, n = lane & 31;
 
+    if constexpr (GROUP) {                     // behind the tiles: off[K+1] | run[4][K] | list[m]
+        int* off = reinterpret_cast<int*>(ctile_all + 4 * 32 * LDC);
+        int *run = off + (K + 1), *list = run + 4 * K;
+        const int per = (g.m + 3) >> 2, beg = min(g.m, wave * per), end = min(g.m, beg + per);
+        for (int j = tid; j < 4 * K; j += 256) run[j] = 0;
+        __syncthreads();
+        for (int i = beg + lane; i < end; i += 64) {
+            const int b = g.blk[i];
+            if ((unsigned)b < (unsigned)K) atomicAdd(&run[wave * K + b], 1);
+        }
+        __syncthreads();
+        wg_exclusive_scan4([&](int j) { return run[j] + run[K + j] + run[2 * K + j] + run[3 * K + j]; }, K, off, tmp);
+        for (int j = tid; j < K; j += 256) {   // counts of the wavefronts -> where each one's signals start
+            int at = off[j];
+            for (int w = 0; w < 4; ++w) {
+                const int v = run[w * K + j];
+                run[w * K + j] = at;
+                at += v;
+            }
+        }
+        __syncthreads();
+        scatter_chunk(g.blk, beg, end, K, run + wave * K, list);
+        if (blockIdx.x == 0) {
+            for (int j = tid; j <= K; j += 256) g.offsets[j] = off[j];
+            for (int j = tid; j < K; j += 256) g.counts[j] = off[j + 1] - off[j];
+            for (int e = tid; e < (g.m + 511) / 512 * K; e += 256) g.chunk_count[e] = 0;
+            __syncthreads();                   // list
+            for (int i = tid; i < off[K]; i += 256) g.perm[i] = list[i];
+        }
+        offsets = off;
+        perm = list;
+    }
     wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + 31) >> 5; }, K,
                        tile_start, tmp);
     const int wt = blockIdx.x * 4 + wave;
@@ -411,40 +454,47 @@ hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int 
 
 template <int P, int S>
 hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws,
-                     int32_t* supp, float* coef, float* err, hipStream_t st) {
+                     int32_t* supp, float* coef, float* err, const int32_t* blk, hipStream_t st) {
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
-    const size_t lds = ((((K + 1 + 16) + 3) & ~3) + 4 * kSelectStageWords) * sizeof(int) +
-                       4 * 32 * (P + 1) * sizeof(float);
-    hipLaunchKernelGGL((select_kernel<P, S>), grid, dim3(256), lds, st, Y, D, K, s0, ws.offsets,
-                       ws.perm, supp, coef, err);
+    size_t lds = ((((K + 1 + 16) + 3) & ~3) + 4 * kSelectStageWords) * sizeof(int) +
+                 4 * 32 * (P + 1) * sizeof(float);
+    if (blk != nullptr) {
+        lds += (5 * K + 1 + m) * sizeof(int);      // at most 60 KiB in all
+        hipLaunchKernelGGL((select_kernel<P, S, true>), grid, dim3(256), lds, st, Y, D, K, s0, nullptr, nullptr, supp,
+                           coef, err, GroupInSelect{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count});
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((select_kernel<P, S, false>), grid, dim3(256), lds, st, Y, D, K, s0, ws.offsets,
+                       ws.perm, supp, coef, err, GroupInSelect{});
     return hipGetLastError();
 }
 
 template <int P>
 hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
-                    int32_t* supp, float* coef, float* err, hipStream_t st) {
-    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, st);
-    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, st);
-    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, st);
-    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, st);
-    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, st);
+                    int32_t* supp, float* coef, float* err, const int32_t* blk, hipStream_t st) {
+    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
+    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
+    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
+    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
+    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
 }
 
 }  // namespace
 
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st) {
+                         bool split, hipStream_t st, const int32_t* blk) {
+    if (blk != nullptr && !group_in_select(p, K, m)) return hipErrorInvalidValue;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
         hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, st)
                              : launch_dict_swizzle(p, K, D, ws.dsw, st);
         if (e != hipSuccess) return e;
     }
     switch (p) {
-        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, st);
-        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, st);
-        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, st);
+        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, st);
+        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, st);
+        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, st);
         case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, st);
         default: return hipErrorInvalidValue;
     }

@@ -242,6 +242,38 @@ __device__ __forceinline__ void wg_exclusive_scan4(F f, int n, int* out, int* tm
     __syncthreads();
 }
 
+// One wavefront puts the signals [beg, end), in order, into the lists of their blocks: run[j] (LDS, its own) is
+// where the next signal of block j goes in perm.  Ids outside [0, K) are dropped.
+__device__ __forceinline__ void scatter_chunk(const int32_t* __restrict__ blk, int beg, int end, int K, int* run,
+                                              int32_t* perm) {
+    const int lane = threadIdx.x & 63;
+    int nbits = 0;
+    while ((1 << nbits) < K) ++nbits;
+    for (int i0 = beg; i0 < end; i0 += 64) {
+        const int i = i0 + lane;
+        int b = i < end ? blk[i] : -1;
+        const bool valid = (unsigned)b < (unsigned)K;
+        if (!valid) b = 0;
+        // lanes holding the same block as this lane
+        unsigned long long same = __ballot(valid);
+        for (int bit = 0; bit < nbits; ++bit) {
+            const bool one = (b >> bit) & 1;
+            const unsigned long long bal = __ballot(valid && one);
+            same &= one ? bal : ~bal;
+        }
+        const unsigned long long below = same & ((1ull << lane) - 1ull);
+        const int rank = __popcll(below);
+        int base = 0;
+        if (valid) {
+            base = run[b];
+            perm[base + rank] = i;
+        }
+        __builtin_amdgcn_wave_barrier();   // every lane has read run[] before a leader updates it
+        if (valid && rank == 0) run[b] = base + __popcll(same);
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // Largest j in [0, n) with start[j] <= x, for a non-decreasing start[0..n].
 __host__ __device__ __forceinline__ int upper_slot(const int* start, int n, int x) {
     int lo = 0, hi = n;  // invariant: start[lo] <= x, answer in [lo, hi)

@@ -162,33 +162,8 @@ __global__ __launch_bounds__(256) void group_scatter_kernel(const int32_t* __res
     if (c >= n_chunks) return;             // no workgroup barrier below this line
     __builtin_amdgcn_wave_barrier();
 
-    int nbits = 0;
-    while ((1 << nbits) < K) ++nbits;
     const int beg = c * chunk;
-    const int end = min(m, beg + chunk);
-    for (int i0 = beg; i0 < end; i0 += 64) {
-        const int i = i0 + lane;
-        int b = i < end ? blk[i] : -1;
-        const bool valid = (unsigned)b < (unsigned)K;
-        if (!valid) b = 0;
-        // lanes holding the same block as this lane
-        unsigned long long same = __ballot(valid);
-        for (int bit = 0; bit < nbits; ++bit) {
-            const bool one = (b >> bit) & 1;
-            const unsigned long long bal = __ballot(valid && one);
-            same &= one ? bal : ~bal;
-        }
-        const unsigned long long below = same & ((1ull << lane) - 1ull);
-        const int rank = __popcll(below);
-        int base = 0;
-        if (valid) {
-            base = run[b];
-            perm[base + rank] = i;
-        }
-        __builtin_amdgcn_wave_barrier();   // every lane has read run[] before a leader updates it
-        if (valid && rank == 0) run[b] = base + __popcll(same);
-        __builtin_amdgcn_wave_barrier();
-    }
+    scatter_chunk(blk, beg, min(m, beg + chunk), K, run, perm);
 }
 
 // scan + scatter from the histograms in chunk_count

@@ -183,11 +183,13 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
     if (rc) return rc;
     rc = run_energy(c, Y, m, blk);
     if (rc) return rc;
-    rc = run_group(c, blk, m, true);           // the energy kernel left the chunk histograms
+    const bool in_select = group_in_select(c->p, c->K, m);
+    if (!in_select) rc = run_group(c, blk, m, true);   // the energy kernel left the chunk histograms
     if (rc) return rc;
     {
         StageTimer t(c, SBO_STAGE_SELECT);         // p = 256 reads the operand order run_swizzle wrote
-        SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, true, use_split(c), c->stream));
+        SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, true, use_split(c), c->stream,
+                              in_select ? blk : nullptr));
     }
     return SBO_OK;
 }

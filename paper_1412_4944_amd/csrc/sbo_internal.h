@@ -204,9 +204,13 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // p = 256 reads Q in operand order: ws.dsb (split: the bf16 matrix cores) or ws.dsw (fp32 matrix
 // instruction).  ops_valid: that buffer already holds this D (launch_dict_swizzle[_split]);
 // otherwise it is rewritten first.  p <= 64 reads D itself and ignores both flags.
+// blk: nullptr, or the choices of the signals, which the kernel then groups itself (where group_in_select says so;
+// launch_group is not called, and what it leaves in ws is left there too).  The line: every workgroup sorts the whole
+// set, so it has to be small, and its lists have to fit 64 KiB of LDS beside the tiles.
+inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st);
+                         bool split, hipStream_t st, const int32_t* blk = nullptr);
 
 // M == nullptr (p = 256): the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
