@@ -234,7 +234,8 @@ enum {
                               products.  (For s0 <= p/2 the choice is screened, under every arithmetic: one
                               fp16 product and its guaranteed error bound rule out the blocks that cannot
                               win, only the others are computed as described here; the chosen blocks are
-                              the same.  p = 256: under this arithmetic only.)  Dictionary entries
+                              the same.  p = 256: under this arithmetic only, and for K <= 1013; with more
+                              orthobases the choice is made as under SBO_ARITH_BF16X3.)  Dictionary entries
                               must be below 8 in magnitude (orthonormal atoms: at most 1); a signal whose
                               largest magnitude is below 2^-63 is coded as a zero signal (its energies
                               underflow in fp32 under any arithmetic). */

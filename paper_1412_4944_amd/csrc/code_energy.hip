@@ -767,7 +767,8 @@ __global__ __launch_bounds__(256) void energy_merge_kernel(const float* __restri
 }
 
 // The kernels of this file, for what code_screen.h does not screen: p = 16 with s0 > 8 (all arithmetics) and
-// p = 256 in SBO_ARITH_F32 and SBO_ARITH_BF16X3.  arith: SBO_ARITH_*.
+// p = 256 in SBO_ARITH_F32 and SBO_ARITH_BF16X3 (as which SBO_ARITH_F16X2 with K > kScreenWideMaxK comes here).
+// arith: SBO_ARITH_*.
 template <int P, int S, int SX>
 hipError_t launch_pse(const float* Y, int64_t m, int K, int s0, int arith, const Workspace& ws, int32_t* blk,
                       int32_t* chunk_count, hipStream_t st) {
@@ -875,7 +876,7 @@ hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsign
 
 static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws,
                                 int32_t* blk, int32_t* chunk_count, hipStream_t st) {
-    if (!screen_applies(p, s0, arith) || ws.raised == nullptr) return hipErrorInvalidValue;
+    if (!screen_applies(p, K, s0, arith) || ws.raised == nullptr) return hipErrorInvalidValue;
     ScrArgs a;
     a.Y = Y;
     a.m = (int)m;
@@ -898,7 +899,7 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
 
 hipError_t launch_energy(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws, int32_t* blk,
                          int32_t* chunk_count, hipStream_t st) {
-    if (screen_applies(p, s0, arith)) return launch_energy_screen(p, K, s0, arith, Y, m, ws, blk, chunk_count, st);
+    if (screen_applies(p, K, s0, arith)) return launch_energy_screen(p, K, s0, arith, Y, m, ws, blk, chunk_count, st);
     if (p == 16) return launch_pse<16, 16, 0>(Y, m, K, s0, arith, ws, blk, chunk_count, st);
     if (p != 256) return hipErrorInvalidValue;
     if (s0 <= 1) return launch_wide_s<1>(Y, m, K, s0, arith, ws, blk, chunk_count, st);

@@ -269,6 +269,14 @@ constexpr size_t scr_lds_bytes(int K) {
     return scr_table_bytes<P, SHARED, W>(K) + (size_t)(SHARED ? 64 : 64 * W) * 20 + (2 * W + 2) * 4;
 }
 
+// The workgroups of 64 signals take every K that the boundary accepts; p = 256: up to the line of screen_applies.
+static_assert(scr_lds_bytes<16, true, kScrWaves>(1024) <= kScrLdsMax && scr_lds_bytes<32, true, kScrWaves>(1024) <= kScrLdsMax &&
+                  scr_lds_bytes<64, true, kScrWaves>(1024) <= kScrLdsMax,
+              "p <= 64: K up to 1024");
+static_assert(scr_lds_bytes<256, true, kScrWaves>(kScreenWideMaxK) <= kScrLdsMax &&
+                  scr_lds_bytes<256, true, kScrWaves>(kScreenWideMaxK + 1) > kScrLdsMax,
+              "p = 256: K up to kScreenWideMaxK");
+
 // One step of the main loop issues the matrix instructions of the NEXT rows and the selection networks
 // of the present ones, NM and about NVALU instructions; spread them evenly: a matrix instruction
 // occupies its pipe for 32 cycles and the vector ALU runs beside it, but only if the wavefront
@@ -834,7 +842,7 @@ hipError_t launch_p(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t 
     switch (a.s0) {
 #define SBO_CASE(N) \
     case N:         \
-        if constexpr (screen_applies(P, N, SBO_ARITH_F16X2)) return launch_s<P, N>(a, arith, raised, st); \
+        if constexpr (screen_applies(P, 1, N, SBO_ARITH_F16X2)) return launch_s<P, N>(a, arith, raised, st); \
         break;
         SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
         SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)

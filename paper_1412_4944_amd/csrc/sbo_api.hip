@@ -145,15 +145,17 @@ static int run_group(sbo_ctx* c, const int32_t* blk, int64_t m, bool have_hist =
 
 static bool use_split(const sbo_ctx* c) { return c->coding_arith != SBO_ARITH_F32; }
 // The arithmetic of the block choice.  Screening is now part of every arithmetic that allows it, so
-// SBO_ARITH_BF16X3_SCREEN is SBO_ARITH_BF16X3.
+// SBO_ARITH_BF16X3_SCREEN is SBO_ARITH_BF16X3.  At p = 256 only the screening kernel works with two fp16 parts:
+// where it does not apply (K beyond its table), three bf16 parts, the finer of the two.
 static int choice_arith(const sbo_ctx* c) {
-    return c->coding_arith == SBO_ARITH_BF16X3_SCREEN ? (int)SBO_ARITH_BF16X3 : c->coding_arith;
+    const int a = c->coding_arith == SBO_ARITH_BF16X3_SCREEN ? (int)SBO_ARITH_BF16X3 : c->coding_arith;
+    return a == SBO_ARITH_F16X2 && c->p > 64 && !screen_applies(c->p, c->K, c->s0, a) ? (int)SBO_ARITH_BF16X3 : a;
 }
 // The operand orders that the block choice of this context reads.
 static int energy_ops(const sbo_ctx* c) {
     const int a = choice_arith(c);
     const int own = a == SBO_ARITH_F32 ? kOpsF32 : a == SBO_ARITH_F16X2 ? kOpsF16 : kOpsBf16;
-    return screen_applies(c->p, c->s0, a) ? own | kOpsF16 : own;
+    return screen_applies(c->p, c->K, c->s0, a) ? own | kOpsF16 : own;
 }
 
 // ... that its select kernel reads (p <= 64: D itself), and both.

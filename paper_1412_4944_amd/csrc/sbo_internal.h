@@ -159,9 +159,11 @@ constexpr int kOpsF32 = 1, kOpsBf16 = 2, kOpsF16 = 4;
 // Which calls choose the block by screening with leading fp16 parts and full products for the
 // contenders only (code_screen.h).  More than p / 2 coefficients kept: the blocks of a signal all but
 // tie, and almost all of them would be contenders.  p = 256 in the other arithmetics: the full
-// products of three bf16 parts do not fit the registers beside the screening.
-constexpr bool screen_applies(int p, int s0, int arith) {
-    return 2 * s0 <= p && (p <= 64 || arith == SBO_ARITH_F16X2);
+// products of three bf16 parts do not fit the registers beside the screening; and with more blocks than
+// kScreenWideMaxK the table of 64 signals (128 bytes a block) does not fit LDS beside them.
+constexpr int kScreenWideMaxK = 1013;
+constexpr bool screen_applies(int p, int K, int s0, int arith) {
+    return 2 * s0 <= p && (p <= 64 || (arith == SBO_ARITH_F16X2 && K <= kScreenWideMaxK));
 }
 // Which shape of the screening kernel (p <= 64): workgroups of 256 signals, two per CU, instead of 512 where the
 // last round of the latter would be at most 0.65 full (196608 signals, p = 64, K = 32: 141 us instead of 160); on

@@ -385,6 +385,32 @@ def test_largest_K_and_context_reuse(arith):
         compare_code(Y, Dg, 2, orc.o_code(Y, Dg, 2), g.code(Y, Dg))
 
 
+@pytest.mark.parametrize("K", [1013, 1014, 1024])
+def test_largest_K_at_p256(K):
+    """Both sides of the line up to which the table of the screening kernel holds all blocks, and the largest K:
+    coding against the oracle; beyond the line it is the coding in three bf16 parts, bit for bit, also inside
+    sbo_iterate (which rereads the operand orders that the SVD kernel leaves)."""
+    p, s0, m = 256, 12, 70
+    rng = np.random.default_rng(K)
+    Q = synth.random_onb(rng, p).T
+    v = rng.standard_normal((K, p))
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    D = (Q - 2 * (v @ Q.T)[:, :, None] * v[:, None, :]).astype(np.float32)       # atoms reflected at K hyperplanes
+    Y = np.einsum("ik,ikd->id", rng.standard_normal((m, s0)), D[rng.integers(0, K, m)][:, :s0].astype(np.float64))
+    Y = (Y + 0.05 * rng.standard_normal(Y.shape)).astype(np.float32)
+    o = orc.o_code(Y, D, s0)
+    codes, dicts = {}, {}
+    for arith in ("f16x2", "bf16x3"):
+        print(f"case {arith}: K={K}", flush=True)
+        with Sbo(p, K, s0, m, arith=arith) as g:
+            codes[arith] = g.code(Y, D)
+            compare_code(Y, D, s0, o, codes[arith])
+            dicts[arith] = g.iterate(Y[:24], D, 2)[:2] if K == 1014 else ()
+    if K > 1013:
+        for a, b in zip(codes["f16x2"] + tuple(dicts["f16x2"]), codes["bf16x3"] + tuple(dicts["bf16x3"])):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("p", [16, 32, 64, 256])
 def test_polar_condition_sweep_and_both_paths(p):
     """The SVD update over a range of condition numbers, once with the default path
