@@ -210,8 +210,13 @@ int sbo_svd_sweeps(sbo_ctx* c, int32_t* sweeps);
 /* Options of a context (sbo_set_option). */
 enum {
     SBO_OPT_SVD_METHOD   = 0,  /* how Q_j = U V^T is computed: SBO_SVD_AUTO or SBO_SVD_JACOBI */
-    SBO_OPT_CODING_ARITH = 1   /* how the projection Q_j^T y onto all K orthobases is multiplied out:
+    SBO_OPT_CODING_ARITH = 1,  /* how the projection Q_j^T y onto all K orthobases is multiplied out:
                                   SBO_ARITH_F32, SBO_ARITH_BF16X3, SBO_ARITH_BF16X3_SCREEN or SBO_ARITH_F16X2 */
+    SBO_OPT_SVD_WAIT     = 2   /* p = 256: how often, at most, one of the 16 workgroups that share the SVD of an
+                                  orthobase looks whether the others have arrived (>= 0; default 4194304: seconds).
+                                  They run side by side unless other work holds the GPU for that long; then the
+                                  wait ends and one workgroup computes the orthobase by the Jacobi SVD: the same
+                                  Q_j up to rounding, in tens of milliseconds. */
 };
 enum {
     SBO_SVD_AUTO   = 0,  /* default: Newton-Schulz polar factor on the matrix cores, the one-sided

@@ -218,7 +218,7 @@ def sbo_svd_sweeps(ctx, K: int) -> list:
     return list(buf)
 
 
-SBO_OPT_SVD_METHOD, SBO_OPT_CODING_ARITH = 0, 1
+SBO_OPT_SVD_METHOD, SBO_OPT_CODING_ARITH, SBO_OPT_SVD_WAIT = 0, 1, 2
 SBO_SVD_AUTO, SBO_SVD_JACOBI = 0, 1
 SBO_ARITH_F32, SBO_ARITH_BF16X3, SBO_ARITH_BF16X3_SCREEN, SBO_ARITH_F16X2 = 0, 1, 2, 3
 

@@ -34,8 +34,12 @@
 // start in order.  A launch that does not have the chip to itself can hold at most 15 workgroups of an
 // incomplete team on an XCD (32 CUs), so two launches at a time always leave room for one to complete a
 // team.  With contexts of this size on more than two streams the teams lie in consecutive workgroups instead
-// ("spread": at most 15 waiting ones on the whole chip per launch, barriers of the slower kind).  Every wait is
-// bounded all the same, and a team that gives up leaves NaN.
+// ("spread": at most 15 waiting ones on the whole chip per launch, barriers of the slower kind).  That is about
+// speed only: other processes or kernels may still hold the CUs that a team needs, so every wait is bounded
+// (WideArgs::polls), a workgroup whose wait ends gives the team up (gone), and the workgroup that leaves the team
+// last, which by then waits for nobody, computes from their sources all blocks that one of the 16 did not
+// finish (jacobi_alone).  The result is what it would have been, up to rounding; sbo_svd_sweeps shows such a block
+// as one of the Jacobi SVD.
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "ns_scale.h"
@@ -53,7 +57,6 @@ constexpr int kJacTeam = 8;
 constexpr int kMaxTeams = 16;                  // blocks at a time
 constexpr int kNT = 512;
 constexpr int kWaves = kNT / 64;
-constexpr int kSpin = 1 << 22;                 // polls of a wait: seconds
 constexpr int kMaxSweeps = 24;
 constexpr float kTol = 1e-6f;                  // rotate while |a_i . a_j| > kTol |a_i| |a_j|
 
@@ -69,7 +72,10 @@ constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
 constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][3][16] | sigma[256] | 1/|v|[256]
 constexpr size_t kTeamBytes = kSmallAt + 4096;
 // and its counters (ints, zero between launches), each on a cache line of its own
-constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kVersionAt = 160, kMeetAt = 192, kSyncInts = 224;
+constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kUndoneAt = 129, kVersionAt = 160, kMeetAt = 192, kSyncInts = 224;
+// Added to a barrier's counter by a workgroup that gives up (no barrier counts as far, and 16 times it fits an int).
+constexpr int kGone = 1 << 24;
+constexpr unsigned long long kGoneMeet = 1ull << 62;
 
 // LDS
 constexpr int kEimgAt = kImage;
@@ -90,6 +96,7 @@ struct WideArgs {
     int32_t* iters_out;
     int max_iters, K, teams;
     int spread;
+    int polls;                 // of one wait, at most
     unsigned char* data;       // [teams][kTeamBytes]
     int* sync;                 // [teams][kSyncInts]
     SqTotalArgs sq;
@@ -127,8 +134,8 @@ __device__ __forceinline__ int peek(int* p, bool near) {
     return v;
 }
 template <class F>
-__device__ __forceinline__ bool poll(bool near, F ready) {
-    for (int k = 0; k < kSpin; ++k) {
+__device__ __forceinline__ bool poll(int polls, bool near, F ready) {
+    for (int k = 0; k < polls; ++k) {
         if (ready()) {
             if (near) asm volatile("buffer_inv sc0" ::: "memory");
             else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -148,9 +155,15 @@ struct Team {
     int* arrive;               // the counters: of the agent scope, then (a cache line on) near ones
     float* red;                // [4][3][16]
     int* ok;                   // LDS
-    int size, q;
+    int size, q, polls;
     int epoch, arrived;        // barriers so far; of this kind
     bool near;
+
+    // So that the others need not wait for as long.
+    __device__ __forceinline__ void gone() const {             // thread 0
+        if (near) __hip_atomic_fetch_add(arrive + 32, kGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else __hip_atomic_fetch_add(arrive, kGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 
     __device__ __forceinline__ bool sync(float a, float b = 0.f, float c = 0.f) {      // a, b, c: of thread 0
         ++epoch;
@@ -167,7 +180,9 @@ struct Team {
             if (near) __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             else __hip_atomic_fetch_add(count, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             const int target = size * arrived;
-            *ok = poll(near, [&]() { return peek(count, near) >= target; });
+            int v = 0;
+            const bool here = poll(polls, near, [&]() { return (v = peek(count, near)) >= target; });
+            *ok = here && v < kGone;
         }
         __syncthreads();
         return *ok != 0;
@@ -182,13 +197,14 @@ struct Team {
             const int field = 5 * (xcc < 8 ? xcc : 8);
             __hip_atomic_fetch_add(count, 1ull << field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             unsigned long long v = 0;
-            const bool here = poll(true, [&]() {
+            const bool here = poll(polls, true, [&]() {
                 v = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 int n = 0;
                 for (int f = 0; f <= 40; f += 5) n += (int)(v >> f) & 31;
-                return n == size;
+                return n == size || v >= kGoneMeet;
             });
-            *ok = !here ? 0 : xcc < 8 && (int)(v >> field & 31) == size ? 2 : 1;
+            if (!here) __hip_atomic_fetch_or(count, kGoneMeet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *ok = !here || v >= kGoneMeet ? 0 : xcc < 8 && (int)(v >> field & 31) == size ? 2 : 1;
         }
         __syncthreads();
         const int how = *ok;
@@ -292,7 +308,7 @@ __device__ __forceinline__ void emit_strip(const WideArgs& g, int j, int s, cons
     __syncthreads();
 }
 
-enum class Outcome { done, left, dead };       // left: to the Jacobi SVD
+enum class Outcome { done, left, dead };       // left: to the Jacobi SVD; dead: a wait has ended
 
 // Newton-Schulz for a block; strip `t.q` of the result is left in LDS at kStripAt.  first != nullptr: the team
 // has not met yet.
@@ -561,6 +577,165 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
     return Outcome::done;
 }
 
+// Columns in half a wavefront: rows 2 l32 + 64 k + {0, 1}
+__device__ __forceinline__ void get_column(const float* col, float (&v)[8]) {
+    const int l32 = threadIdx.x & 31;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float2 w = *reinterpret_cast<const float2*>(col + 2 * l32 + 64 * k);
+        v[2 * k] = w.x;
+        v[2 * k + 1] = w.y;
+    }
+}
+__device__ __forceinline__ void put_column(float* col, const float (&v)[8]) {
+    const int l32 = threadIdx.x & 31;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) *reinterpret_cast<float2*>(col + 2 * l32 + 64 * k) = float2{v[2 * k], v[2 * k + 1]};
+}
+__device__ __forceinline__ float column_norm(const float (&w)[8]) {
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += w[k] * w[k];
+    return sqrtf(half_sum(s));
+}
+// Rotates the columns x, y of A and u, v of V if x and y are not orthogonal enough (false: left as they are).
+__device__ __forceinline__ bool rotate(float (&x)[8], float (&y)[8], float (&u)[8], float (&v)[8], int& rotated) {
+    float al = 0.f, be = 0.f, ga = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        al += x[k] * x[k];
+        be += y[k] * y[k];
+        ga += x[k] * y[k];
+    }
+    al = half_sum(al);
+    be = half_sum(be);
+    ga = half_sum(ga);
+    const float d = be - al, g2 = 2.f * ga, hh = d * d + g2 * g2, gg = ga * ga, ab = al * be;
+    if (gg > (kPolarDone * kPolarDone) * ab) rotated = 1;
+    if (!(gg > (kTol * kTol) * ab && hh > 1e-36f)) return false;
+    // cos(2 theta) = |d| / hypot(d, 2 gamma), |theta| <= pi/4
+    const float r = __builtin_amdgcn_rsqf(hh), w = 0.5f + 0.5f * (fabsf(d) * r), rc = __builtin_amdgcn_rsqf(w);
+    const float cs = w * rc, sn = copysignf(0.5f * rc * r, d) * g2;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float a = x[k], b = y[k];
+        x[k] = cs * a - sn * b;
+        y[k] = sn * a + cs * b;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float a = u[k], b = v[k];
+        u[k] = cs * a - sn * b;
+        v[k] = sn * a + cs * b;
+    }
+    return true;
+}
+// Place of the eigenvector c among the 256 by descending sig (LDS), the lower index first.
+__device__ __forceinline__ int rank_of(const float* sig, float s, int c) {
+    float n = 0.f;
+    for (int k = 0; k < 8; ++k) {
+        const int o = (threadIdx.x & 31) + 32 * k;
+        n += sig[o] > s || (sig[o] == s && o < c) ? 1.f : 0.f;
+    }
+    return min(max((int)half_sum(n), 0), P - 1);
+}
+
+// Q = U V^T of block j from A = U S and V in memory (the norms S of A's columns in LDS, 256 words at red + 256), its 32
+// atoms q of 8, or all of them: alone, and where columns have vanished, which one workgroup completes.
+__device__ __forceinline__ void write_factor(const WideArgs& g, int j, unsigned char* mem, unsigned char* lds, float* red,
+                                             int* flag, int q, bool alone) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float* GA = reinterpret_cast<float*>(mem + kJaAt);
+    const float* GV = reinterpret_cast<const float*>(mem + kJvAt);
+    float* sig = red + 256;                    // [256] words each
+    int* isbad = reinterpret_cast<int*>(red + 512);
+    float* vec = red + 768;
+    float* coefs = red + 1024;
+    float smax = 0.f;
+    for (int c = 0; c < P; ++c) smax = fmaxf(smax, sig[c]);
+    const float thr = smax * 1e-6f;
+    if (tid == 0) *flag = 0;
+    __syncthreads();
+    if (tid < P) {
+        isbad[tid] = !(sig[tid] > thr);
+        if (isbad[tid]) *flag = 1;
+    }
+    __syncthreads();
+    const bool bad = *flag != 0;               // uniform over the team
+    if (bad && q != 0) return;
+    if (bad) {                                 // one workgroup completes the vanished columns
+        for (int e = tid; e < P * P; e += kNT) GA[e] = isbad[e / P] ? 0.f : GA[e] / sig[e / P];
+        __syncthreads();
+        for (int c = 0; c < P; ++c) {
+            if (!isbad[c]) continue;           // uniform
+            if (tid < P) {
+                float s = 0.f;
+                for (int cc = 0; cc < P; ++cc) s += GA[cc * P + tid] * GA[cc * P + tid];
+                vec[tid] = s;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                int best = 0;
+                for (int r = 1; r < P; ++r)
+                    if (vec[r] < vec[best]) best = r;
+                *flag = best;
+            }
+            __syncthreads();
+            const int rs = *flag;
+            float w = 0.f;
+            if (tid < P) {
+                float s = (tid == rs) ? 1.f : 0.f;
+                for (int cc = 0; cc < P; ++cc) s -= GA[cc * P + rs] * GA[cc * P + tid];
+                w = s;
+                vec[tid] = s;
+            }
+            __syncthreads();
+            if (tid < P) {
+                float dsum = 0.f;
+                for (int r = 0; r < P; ++r) dsum += GA[tid * P + r] * vec[r];
+                coefs[tid] = dsum;
+            }
+            __syncthreads();
+            if (tid < P) {
+                for (int cc = 0; cc < P; ++cc) w -= coefs[cc] * GA[cc * P + tid];
+            }
+            __syncthreads();
+            if (tid < P) vec[tid] = w;
+            __syncthreads();
+            if (tid < P) {
+                float nrm = 0.f;
+                for (int r = 0; r < P; ++r) nrm += vec[r] * vec[r];
+                GA[c * P + tid] = w / sqrtf(nrm);
+            }
+            __syncthreads();
+        }
+    }
+    // Q = U V^T, atom-major: D[j][k][r] = sum_c U[r][c] V[k][c]; 32 rows k at a time
+    if (tid < P) sig[tid] = bad ? 1.f : 1.f / sig[tid];
+    __syncthreads();
+    float* strip = reinterpret_cast<float*>(lds);              // [2][16][kLdStrip] (X and Y are dead)
+    alone = alone || bad;
+    for (int sl = alone ? 0 : q; sl < (alone ? kJacTeam : q + 1); ++sl) {
+        const int q0 = 4 * lane, k0 = 4 * wave;
+        float o[4][4] = {};
+        for (int c = 0; c < P; ++c) {
+            const f32x4 uu = *reinterpret_cast<const f32x4*>(GA + c * P + q0) * sig[c];
+            const f32x4 vv = *reinterpret_cast<const f32x4*>(GV + c * P + 32 * sl + k0);
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) o[a][b] += vv[a] * uu[b];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+            *reinterpret_cast<f32x4*>(strip + (k0 + a) * kLdStrip + q0) = f32x4{o[a][0], o[a][1], o[a][2], o[a][3]};
+        __syncthreads();
+        emit_strip(g, j, 2 * sl, strip, red);
+        emit_strip(g, j, 2 * sl + 1, strip + 16 * kLdStrip, red);
+    }
+}
+
 // One-sided Jacobi for block j by the workgroups q < 8 of a team (t: their barrier); version: the
 // numbers the column sets have reached, tbase what they all stand at.  Writes D.
 __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source& src, Team& t, int* version, int& tbase,
@@ -617,51 +792,7 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
         }
     }
 
-    // half a wavefront rotates one pair of columns: rows 2 l32 + 64 k + {0, 1}
     int rotated = 0;
-    auto get = [&](const float* col, float (&v)[8]) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float2 w = *reinterpret_cast<const float2*>(col + 2 * l32 + 64 * k);
-            v[2 * k] = w.x;
-            v[2 * k + 1] = w.y;
-        }
-    };
-    auto put = [&](float* col, const float (&v)[8]) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) *reinterpret_cast<float2*>(col + 2 * l32 + 64 * k) = float2{v[2 * k], v[2 * k + 1]};
-    };
-    auto rotate = [&](float (&x)[8], float (&y)[8], float (&u)[8], float (&v)[8]) {
-        float al = 0.f, be = 0.f, ga = 0.f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            al += x[k] * x[k];
-            be += y[k] * y[k];
-            ga += x[k] * y[k];
-        }
-        al = half_sum(al);
-        be = half_sum(be);
-        ga = half_sum(ga);
-        const float d = be - al, g2 = 2.f * ga, hh = d * d + g2 * g2, gg = ga * ga, ab = al * be;
-        if (gg > (kPolarDone * kPolarDone) * ab) rotated = 1;
-        if (!(gg > (kTol * kTol) * ab && hh > 1e-36f)) return false;
-        // cos(2 theta) = |d| / hypot(d, 2 gamma), |theta| <= pi/4
-        const float r = __builtin_amdgcn_rsqf(hh), w = 0.5f + 0.5f * (fabsf(d) * r), rc = __builtin_amdgcn_rsqf(w);
-        const float cs = w * rc, sn = copysignf(0.5f * rc * r, d) * g2;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float a = x[k], b = y[k];
-            x[k] = cs * a - sn * b;
-            y[k] = sn * a + cs * b;
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float a = u[k], b = v[k];
-            u[k] = cs * a - sn * b;
-            v[k] = sn * a + cs * b;
-        }
-        return true;
-    };
     // the two sets of a round: si stays while si is the same
     auto sets = [&](int r, int& si, int& sj) {
         if (r < 8) {
@@ -690,7 +821,7 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
             const int now = tbase + sweep * 15 + r;
             if (sweep > 0 || r > 0) {
                 if (tid == 0)
-                    *flag = poll(t.near, [&]() {
+                    *flag = poll(t.polls, t.near, [&]() {
                         return peek(version + sj, t.near) >= now && (!moves(r) || peek(version + si, t.near) >= now);
                     });
                 __syncthreads();
@@ -701,8 +832,8 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
                     copy4(XA, GA + si * 16 * P);
                     copy4(XV, GV + si * 16 * P);
                 } else if (moves(r)) {
-                    get(GA + (si * 16 + hw) * P, x);
-                    get(GV + (si * 16 + hw) * P, u);
+                    get_column(GA + (si * 16 + hw) * P, x);
+                    get_column(GV + (si * 16 + hw) * P, u);
                 }
             }
             __syncthreads();
@@ -714,29 +845,29 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
                     const int ca = pi == 0 ? 15 : (pi + s) % 15, cb = pi == 0 ? s : (15 - pi + s) % 15;
                     const int lo = min(ca, cb), hi = max(ca, cb);
                     float y[8], v[8];
-                    get(A + lo * P, x);
-                    get(A + hi * P, y);
-                    get(V + lo * P, u);
-                    get(V + hi * P, v);
-                    if (rotate(x, y, u, v)) {
-                        put(A + lo * P, x);
-                        put(A + hi * P, y);
-                        put(V + lo * P, u);
-                        put(V + hi * P, v);
+                    get_column(A + lo * P, x);
+                    get_column(A + hi * P, y);
+                    get_column(V + lo * P, u);
+                    get_column(V + hi * P, v);
+                    if (rotate(x, y, u, v, rotated)) {
+                        put_column(A + lo * P, x);
+                        put_column(A + hi * P, y);
+                        put_column(V + lo * P, u);
+                        put_column(V + hi * P, v);
                     }
                     __syncthreads();
                 }
-                get(XA + hw * P, x);
-                get(XV + hw * P, u);
+                get_column(XA + hw * P, x);
+                get_column(XV + hw * P, u);
             }
             for (int s = 0; s < 16; ++s) {     // the pairs across the sets
                 const int cy = (hw + s) & 15;
                 float y[8], v[8];
-                get(YA + cy * P, y);
-                get(YV + cy * P, v);
-                if (rotate(x, y, u, v)) {
-                    put(YA + cy * P, y);
-                    put(YV + cy * P, v);
+                get_column(YA + cy * P, y);
+                get_column(YV + cy * P, v);
+                if (rotate(x, y, u, v, rotated)) {
+                    put_column(YA + cy * P, y);
+                    put_column(YV + cy * P, v);
                 }
                 __syncthreads();
             }
@@ -744,8 +875,8 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
             copy4(GV + sj * 16 * P, YV);
             const bool leaves = moves(r == 14 ? 0 : r + 1);
             if (leaves) {
-                put(GA + (si * 16 + hw) * P, x);
-                put(GV + (si * 16 + hw) * P, u);
+                put_column(GA + (si * 16 + hw) * P, x);
+                put_column(GV + (si * 16 + hw) * P, u);
             }
             stores_done();
             if (tid == 0) {
@@ -767,16 +898,10 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
 
     // sigma = column norms; columns of V renormalised.  Sets 2q (x, u) and 2q + 1 (LDS).
     float y[8], v[8];
-    get(YA + hw * P, y);
-    get(YV + hw * P, v);
-    auto norm2 = [&](const float (&w)[8]) {
-        float s = 0.f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s += w[k] * w[k];
-        return half_sum(s);
-    };
+    get_column(YA + hw * P, y);
+    get_column(YV + hw * P, v);
     const int cx = 32 * q + hw, cyy = 32 * q + 16 + hw;        // their columns
-    const float sx = sqrtf(norm2(x)), sy = sqrtf(norm2(y)), ix = 1.f / sqrtf(norm2(u)), iy = 1.f / sqrtf(norm2(v));
+    const float sx = column_norm(x), sy = column_norm(y), ix = 1.f / column_norm(u), iy = 1.f / column_norm(v);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         u[k] *= ix;
@@ -790,121 +915,130 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
     }
     const bool eig = g.eig_sv != nullptr;
     if (!eig) {                                // (A stands in memory already)
-        put(GV + cx * P, u);
-        put(GV + cyy * P, v);
+        put_column(GV + cx * P, u);
+        put_column(GV + cyy * P, v);
     }
     if (!t.sync(0.f)) return Outcome::dead;
-    float* sig = red + 256;                    // [256] words each
-    int* isbad = reinterpret_cast<int*>(red + 512);
-    float* vec = red + 768;
-    float* coefs = red + 1024;
+    float* sig = red + 256;
     if (tid < P) sig[tid] = Gsig[tid];
     __syncthreads();
-
     if (eig) {
         // atoms = eigenvectors (columns of V) by descending eigenvalue, eig_sv = square roots of the
         // eigenvalues: |A_c| / |V_c|, rescaled
-        auto rank_of = [&](float s, int c) {
-            float n = 0.f;
-            for (int k = 0; k < 8; ++k) {
-                const int o = l32 + 32 * k;
-                n += sig[o] > s || (sig[o] == s && o < c) ? 1.f : 0.f;
-            }
-            return min(max((int)half_sum(n), 0), P - 1);
-        };
-        const int rx = rank_of(sx, cx), ry = rank_of(sy, cyy);
+        const int rx = rank_of(sig, sx, cx), ry = rank_of(sig, sy, cyy);
         if (l32 == 0) {
             g.eig_sv[(int64_t)j * P + rx] = sqrtf(sx * ix * mx);
             g.eig_sv[(int64_t)j * P + ry] = sqrtf(sy * iy * mx);
         }
-        put(g.D + ((int64_t)j * P + rx) * P, u);
-        put(g.D + ((int64_t)j * P + ry) * P, v);
-        return Outcome::done;
-    }
-
-    float smax = 0.f;
-    for (int c = 0; c < P; ++c) smax = fmaxf(smax, sig[c]);
-    const float thr = smax * 1e-6f;
-    if (tid == 0) *flag = 0;
-    __syncthreads();
-    if (tid < P) {
-        isbad[tid] = !(sig[tid] > thr);
-        if (isbad[tid]) *flag = 1;
-    }
-    __syncthreads();
-    const bool bad = *flag != 0;               // uniform over the team
-    if (bad && q != 0) return Outcome::done;
-    if (bad) {                                 // one workgroup completes the vanished columns
-        for (int e = tid; e < P * P; e += kNT) GA[e] = isbad[e / P] ? 0.f : GA[e] / sig[e / P];
-        __syncthreads();
-        for (int c = 0; c < P; ++c) {
-            if (!isbad[c]) continue;           // uniform
-            if (tid < P) {
-                float s = 0.f;
-                for (int cc = 0; cc < P; ++cc) s += GA[cc * P + tid] * GA[cc * P + tid];
-                vec[tid] = s;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                int best = 0;
-                for (int r = 1; r < P; ++r)
-                    if (vec[r] < vec[best]) best = r;
-                *flag = best;
-            }
-            __syncthreads();
-            const int rs = *flag;
-            float w = 0.f;
-            if (tid < P) {
-                float s = (tid == rs) ? 1.f : 0.f;
-                for (int cc = 0; cc < P; ++cc) s -= GA[cc * P + rs] * GA[cc * P + tid];
-                w = s;
-                vec[tid] = s;
-            }
-            __syncthreads();
-            if (tid < P) {
-                float dsum = 0.f;
-                for (int r = 0; r < P; ++r) dsum += GA[tid * P + r] * vec[r];
-                coefs[tid] = dsum;
-            }
-            __syncthreads();
-            if (tid < P) {
-                for (int cc = 0; cc < P; ++cc) w -= coefs[cc] * GA[cc * P + tid];
-            }
-            __syncthreads();
-            if (tid < P) vec[tid] = w;
-            __syncthreads();
-            if (tid < P) {
-                float nrm = 0.f;
-                for (int r = 0; r < P; ++r) nrm += vec[r] * vec[r];
-                GA[c * P + tid] = w / sqrtf(nrm);
-            }
-            __syncthreads();
-        }
-    }
-    // Q = U V^T, atom-major: D[j][k][r] = sum_c U[r][c] V[k][c]; 32 rows k at a time
-    if (tid < P) sig[tid] = bad ? 1.f : 1.f / sig[tid];
-    __syncthreads();
-    float* strip = reinterpret_cast<float*>(lds);              // [2][16][kLdStrip] (X and Y are dead)
-    for (int sl = bad ? 0 : q; sl < (bad ? kJacTeam : q + 1); ++sl) {
-        const int q0 = 4 * lane, k0 = 4 * wave;
-        float o[4][4] = {};
-        for (int c = 0; c < P; ++c) {
-            const f32x4 uu = *reinterpret_cast<const f32x4*>(GA + c * P + q0) * sig[c];
-            const f32x4 vv = *reinterpret_cast<const f32x4*>(GV + c * P + 32 * sl + k0);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) o[a][b] += vv[a] * uu[b];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-            *reinterpret_cast<f32x4*>(strip + (k0 + a) * kLdStrip + q0) = f32x4{o[a][0], o[a][1], o[a][2], o[a][3]};
-        __syncthreads();
-        emit_strip(g, j, 2 * sl, strip, red);
-        emit_strip(g, j, 2 * sl + 1, strip + 16 * kLdStrip, red);
+        put_column(g.D + ((int64_t)j * P + rx) * P, u);
+        put_column(g.D + ((int64_t)j * P + ry) * P, v);
+    } else {
+        write_factor(g, j, mem, lds, red, flag, q, false);
     }
     return Outcome::done;
+}
+
+// The same by one workgroup that waits for nobody, for what a team has given up: all pairs of columns in 255 rounds
+// of 128, straight from memory (31 ms for a block that takes 11 sweeps).  The matrices are the team's, whose other workgroups have left.
+__device__ __forceinline__ void jacobi_alone(const WideArgs& g, int j, const Source& src, unsigned char* mem,
+                                             unsigned char* lds, float* red, int* flag) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hw = tid >> 5, l32 = tid & 31;
+    float* GA = reinterpret_cast<float*>(mem + kJaAt);
+    float* GV = reinterpret_cast<float*>(mem + kJvAt);
+    float* sig = red + 256;
+    float* vinv = red + 768;
+    float mx = 0.f;
+#pragma unroll 1
+    for (int s = 0; s < kTeam; ++s) {
+        f32x4 v[2];
+        load_strip(src, s, v);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(v[u][e]));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, red[w]);
+    const float scale = mx > 0.f ? 1.f / mx : 0.f;
+#pragma unroll 1
+    for (int s = 0; s < kTeam; ++s) {
+        f32x4 v[2];
+        load_strip(src, s, v);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = s * (16 * P / 4) + tid + u * kNT, c = e >> 6, r = 4 * (e & 63);
+            f32x4 one;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) one[k] = r + k == c ? 1.f : 0.f;
+            reinterpret_cast<f32x4*>(GA)[e] = v[u] * scale;
+            reinterpret_cast<f32x4*>(GV)[e] = one;
+        }
+    }
+    stores_done();
+    int sweeps = 0;
+    bool again = true;
+    while (again && sweeps < kMaxSweeps) {
+        int rotated = 0;
+#pragma unroll 1
+        for (int r = 0; r < P - 1; ++r) {
+#pragma unroll 1
+            for (int i = hw; i < P / 2; i += 2 * kWaves) {     // a tournament of 256
+                const int ca = i == 0 ? P - 1 : (r + i) % (P - 1), cb = i == 0 ? r : (r + P - 1 - i) % (P - 1);
+                const int lo = min(ca, cb), hi = max(ca, cb);
+                float x[8], y[8], u[8], v[8];
+                get_column(GA + lo * P, x);
+                get_column(GA + hi * P, y);
+                get_column(GV + lo * P, u);
+                get_column(GV + hi * P, v);
+                if (rotate(x, y, u, v, rotated)) {
+                    put_column(GA + lo * P, x);
+                    put_column(GA + hi * P, y);
+                    put_column(GV + lo * P, u);
+                    put_column(GV + hi * P, v);
+                }
+            }
+            stores_done();
+        }
+        ++sweeps;
+        if (tid == 0) *flag = 0;
+        __syncthreads();
+        if (rotated) *flag = 1;
+        __syncthreads();
+        again = *flag != 0;                    // uniform
+        __syncthreads();
+    }
+    if (tid == 0) {
+        g.fallback[j] = 1;
+        if (g.iters_out != nullptr) g.iters_out[j] = sweeps;
+    }
+    for (int c = hw; c < P; c += 2 * kWaves) { // sigma = column norms; columns of V renormalised
+        float x[8], u[8];
+        get_column(GA + c * P, x);
+        get_column(GV + c * P, u);
+        const float sc = column_norm(x), ic = 1.f / column_norm(u);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) u[k] *= ic;
+        put_column(GV + c * P, u);
+        if (l32 == 0) {
+            sig[c] = sc;
+            vinv[c] = ic;
+        }
+    }
+    stores_done();
+    if (g.eig_sv == nullptr) {
+        write_factor(g, j, mem, lds, red, flag, 0, true);
+        return;
+    }
+    for (int c = hw; c < P; c += 2 * kWaves) {
+        float u[8];
+        get_column(GV + c * P, u);
+        const int rc = rank_of(sig, sig[c], c);
+        if (l32 == 0) g.eig_sv[(int64_t)j * P + rc] = sqrtf(sig[c] * vinv[c] * mx);
+        put_column(g.D + ((int64_t)j * P + rc) * P, u);
+    }
 }
 
 // NS: Newton-Schulz first; otherwise Jacobi for every block.
@@ -930,37 +1064,41 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
     unsigned char* mem = g.data + (size_t)team * kTeamBytes;
     int* sync = g.sync + team * kSyncInts;
     float* small = reinterpret_cast<float*>(mem + kSmallAt);
-    Team all = {sync + kArriveAt, small, flag, kTeam, q, 0, 0, false};
-    Team eight = {sync + kArriveJacAt, small + 192, flag + 1, kJacTeam, q, 0, 0, false};
+    Team all = {sync + kArriveAt, small, flag, kTeam, q, g.polls, 0, 0, false};
+    Team eight = {sync + kArriveJacAt, small + 192, flag + 1, kJacTeam, q, g.polls, 0, 0, false};
     int tbase = 0;
+    const int blocks = (g.K - 1 - team) / g.teams + 1;         // of this team
+    int undone = blocks;
 
     unsigned long long* count = reinterpret_cast<unsigned long long*>(sync + kMeetAt);
     bool alive = NS || all.meet(count), met = !NS;
     eight.near = all.near;
 
-    for (int j = team; alive && j < g.K; j += g.teams) {
-        Source src;
-        bool empty;
+    // where P_j comes from; false: no signals, the block keeps its basis
+    auto source = [&](int j, Source& src) {
         if (g.M != nullptr) {
             src = {g.M + (int64_t)j * P * P, 1};
-            empty = g.counts != nullptr && g.counts[j] == 0;
-        } else {
-            int before = 0, own = 0;           // every wavefront for itself; one trip for up to 64 blocks
-            for (int jj = lane; jj <= j; jj += 64) {
-                own = g.offsets[jj + 1] - g.offsets[jj];
-                before += (own + g.piece - 1) / g.piece;
-            }
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
-            const int n_j = __builtin_amdgcn_readlane(own, j & 63), pieces = (n_j + g.piece - 1) / g.piece;
-            src = {g.partial + (int64_t)(__builtin_amdgcn_readfirstlane(before) - pieces) * P * P, pieces};
-            empty = n_j == 0;
+            return g.counts == nullptr || g.counts[j] != 0;
         }
-        if (empty) {                           // uniform over the team: block keeps its basis
+        int before = 0, own = 0;           // every wavefront for itself; one trip for up to 64 blocks
+        for (int jj = lane; jj <= j; jj += 64) {
+            own = g.offsets[jj + 1] - g.offsets[jj];
+            before += (own + g.piece - 1) / g.piece;
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+        const int n_j = __builtin_amdgcn_readlane(own, j & 63), pieces = (n_j + g.piece - 1) / g.piece;
+        src = {g.partial + (int64_t)(__builtin_amdgcn_readfirstlane(before) - pieces) * P * P, pieces};
+        return n_j != 0;
+    };
+    for (int j = team; alive && j < g.K; j += g.teams) {
+        Source src;
+        if (!source(j, src)) {                 // uniform over the team
             if (q == 0 && tid == 0) {
                 g.fallback[j] = 0;
                 if (g.iters_out != nullptr) g.iters_out[j] = 0;
             }
+            --undone;
             continue;
         }
         Outcome how = Outcome::left;
@@ -979,22 +1117,44 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
             __syncthreads();
             how = q < kJacTeam ? jacobi(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag) : Outcome::done;
         }
-        if (how == Outcome::dead) {            // nothing to be had from the others: say so
-            for (int e = tid; e < 16 * P; e += kNT) g.D[((int64_t)j * P + q * 16) * P + e] = __builtin_nanf("");
-            alive = false;
+        alive = how != Outcome::dead;
+        if (alive) {
+            --undone;
+        } else if (tid == 0) {
+            all.gone();
+            eight.gone();
         }
         __syncthreads();
     }
-    // the last workgroup of the team to leave sets the counters back
-    __syncthreads();
-    if (tid == 0) *flag = __hip_atomic_fetch_add(sync + kExitAt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == kTeam - 1;
-    __syncthreads();
-    if (*flag != 0 && tid < kSyncInts) {
-        if (all.near && tid != kArriveAt && tid != kExitAt && tid < kMeetAt)
-            __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else
-            __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The last workgroup of the team to leave (the release and acquire of the agent scope hand it what the others
+    // have written) does what there is left to do and sets the counters back.
+    stores_done();
+    if (tid == 0) {
+        if (undone > 0) __hip_atomic_fetch_max(sync + kUndoneAt, undone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = __hip_atomic_fetch_add(sync + kExitAt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == kTeam - 1;
+        flag[1] = flag[0] ? __hip_atomic_load(sync + kUndoneAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     }
+    __syncthreads();
+    if (flag[0] == 0) return;                  // uniform
+    const int rest = flag[1];
+    for (int n = blocks - rest; n < blocks; ++n) {
+        const int j = team + n * g.teams;
+        Source src;
+        __syncthreads();                       // flag and the reductions are read
+        if (source(j, src)) {
+            jacobi_alone(g, j, src, mem, lds, red, flag);
+        } else if (tid == 0) {
+            g.fallback[j] = 0;
+            if (g.iters_out != nullptr) g.iters_out[j] = 0;
+        }
+    }
+    if (tid >= kSyncInts) return;
+    const bool in_l2 = all.near && tid != kArriveAt && tid < kMeetAt && tid != kExitAt && tid != kUndoneAt;
+    if (in_l2 || rest > 0) {                   // (rest > 0: this workgroup may have left without knowing that it is near)
+        __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    if (!in_l2 || rest > 0) __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
@@ -1025,6 +1185,7 @@ hipError_t launch_polar_wide(int K, const float* M, const float* partial, const 
     a.sync = ws.wide_sync;
     a.sq = sq;
     a.spread = wide_streams() > 2;
+    a.polls = ws.wide_polls;
     const unsigned grid = (unsigned)(wide_team_wgs(a.teams, a.spread) + (sq.out != nullptr ? sq.nb : 0));
     const void* fn = newton_schulz_first ? reinterpret_cast<const void*>(&wide_polar_kernel<true>)
                                          : reinterpret_cast<const void*>(&wide_polar_kernel<false>);

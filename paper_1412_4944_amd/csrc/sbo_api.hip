@@ -630,6 +630,10 @@ int sbo_set_option(sbo_ctx* c, int option, int value) {
             c->coding_arith = value;
             c->ws.parts_accum = value != SBO_ARITH_F32;
             return SBO_OK;
+        case SBO_OPT_SVD_WAIT:
+            if (value < 0) return SBO_EINVAL;
+            c->ws.wide_polls = value;
+            return SBO_OK;
         default: return SBO_EINVAL;
     }
 }

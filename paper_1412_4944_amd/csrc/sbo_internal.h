@@ -81,6 +81,9 @@ struct LdsRaised {
     }
 };
 
+// Polls of one wait between the workgroups of a p = 256 SVD team: seconds.
+constexpr int kWidePolls = 1 << 22;
+
 // ---- device workspace layout ---------------------------------------------------
 struct Workspace {
     // grouping
@@ -119,6 +122,7 @@ struct Workspace {
     size_t bytes;
     // host side: launch state of the owning context (not device memory)
     LdsRaised* raised;
+    int wide_polls = kWidePolls;           // p > 64: how long the workgroups of an SVD team wait for one another
 };
 constexpr int kSqBlocks = 256;
 constexpr int kEnergySplitBelow = 192;       // coding launches with fewer workgroups split the blocks

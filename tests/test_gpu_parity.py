@@ -505,6 +505,63 @@ def test_polar_p256_on_three_streams():
         assert torch.equal(d, D[0])
 
 
+@pytest.mark.parametrize("polls", [0, 1, 8, 60, 400])
+@pytest.mark.parametrize("K", [1, 9, 33])
+def test_polar_p256_teams_that_give_up(K, polls):
+    """Waits between the workgroups of a p = 256 team that end early (none at all, or somewhere on the way): every
+    block is finished all the same, empty ones keep their basis, and the next call finds the counters set back."""
+    p = 256
+    rng = np.random.default_rng(37 + K)
+    M = np.stack([(synth.random_onb(rng, p) * np.geomspace(1, 10.0 ** -(j % 3), p)) @ synth.random_onb(rng, p)
+                  for j in range(K)])
+    for j in range(4, K, 9):
+        M[j][:, 200:] = M[j][:, :56]                     # rank 200
+    counts = np.ones(K, np.int32)
+    counts[5::7] = 0
+    M32 = M.astype(np.float32)
+    D_old = synth.random_dictionary(rng, K, p).astype(np.float32)
+    Dn = np.stack([orc.o_polar(M32[j].astype(np.float64)) if counts[j] else D_old[j] for j in range(K)])
+    with Sbo(p, K, 4, 256) as g:
+        for jacobi_only in (False, True):
+            print(f"case K={K} polls={polls} jacobi={jacobi_only}", flush=True)
+            g.svd_jacobi(jacobi_only)
+            before = g.polar(M32, D_old, counts)
+            sbo.sbo_set_option(g.ctx, sbo.SBO_OPT_SVD_WAIT, polls)
+            D = g.polar(M32, D_old, counts)
+            work = np.array(sbo.sbo_svd_sweeps(g.ctx, K))
+            sbo.sbo_set_option(g.ctx, sbo.SBO_OPT_SVD_WAIT, 1 << 22)
+            np.testing.assert_array_equal(g.polar(M32, D_old, counts), before)
+            compare_Q(D, Dn, M32.astype(np.float64), counts > 0)
+            np.testing.assert_array_equal(D[counts == 0], D_old[counts == 0])
+            assert (work[counts == 0] == 0).all() and (work[counts > 0] != 0).all()
+            if polls == 0:
+                assert (work[counts > 0] > 0).all(), "no team can have met"
+
+
+def test_iterate_and_base_at_p256_with_teams_that_give_up():
+    """The same inside sbo_iterate: the next coding pass reads the operand orders of what was finished; and the
+    eigenvectors of a Gram matrix."""
+    pr = _problem("giveup", p=256, K=2, m=1500, s0=12, snr_db=25.0)
+    m = pr.Y.shape[0]
+    ids = np.arange(0, m, 2).astype(np.int32)
+    with Sbo(256, 2, 12, m) as g:
+        sbo.sbo_set_option(g.ctx, sbo.SBO_OPT_SVD_WAIT, 0)
+        D1, blk, supp, coef, err, sq = g.iterate(pr.Y, pr.D_init, 1)
+        Dn, M = orc.o_update(pr.Y, blk, supp, coef, pr.D_init)
+        compare_Q(D1, Dn, M, np.bincount(blk, minlength=2) > 0)
+        D2, b2, s2, c2, e2, sq2 = g.iterate(pr.Y, pr.D_init, 2)
+        compare_code(pr.Y, D1, 12, orc.o_code(pr.Y, D1, 12), (b2, s2, c2, e2))
+        assert sq2[0] == sq[0] and sq2[1] <= sq2[0] * (1 + 1e-6)
+        Q, sv = g.init_base(pr.Y, ids)
+    G = pr.Y[ids].astype(np.float64).T @ pr.Y[ids].astype(np.float64)
+    lam = np.linalg.eigvalsh(G)[::-1]
+    Q64 = Q.astype(np.float64)
+    assert np.abs(Q64 @ Q64.T - np.eye(256)).max() <= 1e-5
+    H = Q64 @ G @ Q64.T                                   # (2e-5: the bound of the tests of sbo_init_base)
+    assert np.abs(H - np.diag(np.diag(H))).max() <= 2e-5 * lam[0]
+    assert np.abs(sv.astype(np.float64) ** 2 - lam).max() <= 2e-5 * lam[0]
+
+
 JACOBI_CASES = [("tiny", dict(), 12), ("patch8", dict(m=4096 + 77), 10),
                 ("p256", dict(p=256, K=2, m=1300, s0=12, snr_db=25.0), 2)]
 
