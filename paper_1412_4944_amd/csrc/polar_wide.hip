@@ -1184,7 +1184,7 @@ hipError_t launch_polar_wide(int K, const float* M, const float* partial, const 
     a.data = reinterpret_cast<unsigned char*>(ws.wide);
     a.sync = ws.wide_sync;
     a.sq = sq;
-    a.spread = wide_streams() > 2;
+    a.spread = wide_streams(ws.device) > 2;
     a.polls = ws.wide_polls;
     const unsigned grid = (unsigned)(wide_team_wgs(a.teams, a.spread) + (sq.out != nullptr ? sq.nb : 0));
     const void* fn = newton_schulz_first ? reinterpret_cast<const void*>(&wide_polar_kernel<true>)

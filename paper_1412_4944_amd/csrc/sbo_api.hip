@@ -1,9 +1,7 @@
 // C-ABI of libsbo: argument checks, workspace, stage sequencing and timing.
 // All arithmetic is in the kernels; this file only enqueues them.
 #include "sbo_internal.h"
-
-#include <algorithm>
-#include <mutex>
+#include "stream_count.h"
 
 #include <cmath>
 #include <new>
@@ -60,6 +58,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.sq_partial = (double*)take((size_t)kSqBlocks * 8);
     w.bytes = off;
     w.raised = nullptr;
+    w.device = 0;
     if (ws) *ws = w;
     return off;
 }
@@ -74,24 +73,9 @@ static bool shape_ok(int p, int K, int s0, int64_t m_max) {
     return true;
 }
 
-// The streams of the live contexts of p = 256.
-static std::mutex g_wide_mutex;
-static std::vector<hipStream_t> g_wide;
-int wide_streams() {
-    std::lock_guard<std::mutex> lock(g_wide_mutex);
-    int n = 0;
-    for (size_t i = 0; i < g_wide.size(); ++i) n += std::find(g_wide.begin(), g_wide.begin() + i, g_wide[i]) == g_wide.begin() + i;
-    return n;
-}
-static void wide_context(hipStream_t st, bool live) {
-    std::lock_guard<std::mutex> lock(g_wide_mutex);
-    if (live) {
-        g_wide.push_back(st);
-    } else {
-        auto it = std::find(g_wide.begin(), g_wide.end(), st);
-        if (it != g_wide.end()) g_wide.erase(it);
-    }
-}
+// The live contexts of p = 256.
+static StreamCount g_wide;
+int wide_streams(int device) { return g_wide.streams(device); }
 
 static thread_local std::string g_hip_text = "no HIP error recorded";
 
@@ -258,7 +242,9 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     c->n_spans = 0;
     const size_t bytes = workspace_layout(p, K, s0, m_max, nullptr, nullptr);
     void* base = nullptr;
-    hipError_t e = hipMalloc(&base, bytes);
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipMalloc(&base, bytes);
     if (e != hipSuccess) {
         delete c;
         if (e == hipErrorOutOfMemory) return SBO_ENOMEM;
@@ -267,6 +253,7 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     c->ws_base = (char*)base;
     workspace_layout(p, K, s0, m_max, &c->ws, c->ws_base);
     c->ws.raised = &c->raised;
+    c->ws.device = device;
     c->ws.parts_accum = c->coding_arith != SBO_ARITH_F32;
     // Some pieces of the workspace carry an invariant between calls: the chunk histograms, the two
     // finished-workgroup counters and the counters of polar_wide.hip are zero whenever no call is in flight.
@@ -279,7 +266,7 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
         delete c;
         return hip_fail(e);
     }
-    if (p > 64) wide_context(c->stream, true);
+    if (p > 64) g_wide.add(device, c->stream);
     *out = c;
     return SBO_OK;
 }
@@ -287,7 +274,7 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
 int sbo_destroy(sbo_ctx* c) {
     if (!c) return SBO_EINVAL;
     hipError_t e = hipStreamSynchronize(c->stream);
-    if (c->p > 64) wide_context(c->stream, false);
+    if (c->p > 64) g_wide.remove(c->ws.device, c->stream);
     for (auto& s : c->spans) {
         (void)hipEventDestroy(s.beg);
         (void)hipEventDestroy(s.end);

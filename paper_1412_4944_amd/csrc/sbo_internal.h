@@ -122,6 +122,7 @@ struct Workspace {
     size_t bytes;
     // host side: launch state of the owning context (not device memory)
     LdsRaised* raised;
+    int device;                            // that was current when the context was created
     int wide_polls = kWidePolls;           // p > 64: how long the workgroups of an SVD team wait for one another
 };
 constexpr int kSqBlocks = 256;
@@ -272,8 +273,8 @@ hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Wor
 // false or eig_sv != nullptr: the Jacobi SVD for every block.  And the sizes of ws.wide, ws.wide_sync.
 size_t polar_wide_scratch_bytes(int K);
 size_t polar_wide_sync_bytes(int K);
-// Streams with live contexts of p = 256 (how many of these launches may run at a time).
-int wide_streams();
+// Streams of a GPU with live contexts of p = 256 (how many of these launches may run at a time there).
+int wide_streams(int device);
 hipError_t launch_polar_wide(int K, const float* M, const float* partial, const int32_t* offsets, int piece,
                              const int32_t* counts, float* D, const DictOps& ops, bool newton_schulz_first,
                              float* eig_sv, const Workspace& ws, const SqTotalArgs& sq, hipStream_t st);

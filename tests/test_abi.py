@@ -61,6 +61,17 @@ def test_compare_exchange_networks_on_host(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:]
 
 
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_streams_are_counted_by_device(tmp_path):
+    exe = str(tmp_path / "host_stream_count")
+    r = subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-pthread",
+                        os.path.join(ROOT, "tests", "host_stream_count.cpp"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:]
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     """No CPU fallback: with the shared library absent the binding raises instead of
     computing anything some other way."""
