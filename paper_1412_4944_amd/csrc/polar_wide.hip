@@ -81,7 +81,8 @@ constexpr unsigned long long kGoneMeet = 1ull << 62;
 constexpr int kEimgAt = kImage;
 constexpr int kStripAt = 2 * kImage;                           // [16][kLdStrip] floats
 constexpr int kSmallLds = 4 * P * 16 * 4 > kStripAt + 16 * kLdStrip * 4 ? 4 * P * 16 * 4 : kStripAt + 16 * kLdStrip * 4;
-constexpr size_t kLds = kSmallLds + 6144;                      // 256 floats of reductions, then 5 x 256 words
+constexpr size_t kLds = kSmallLds + 6144;                      // 256 floats of reductions, 4 x 256 words, two flags, ..
+constexpr int kDiagAt = 1282;                                  // .. and a word beside the reductions
 
 struct WideArgs {
     const float* M;            // [K][p][p] finished matrices, or nullptr: sum the pieces
@@ -404,9 +405,9 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
                 if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) v = gm[k][r];
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
-        if (wave == (t.q >> 1) && lane == 0) red[255] = v;
+        if (wave == (t.q >> 1) && lane == 0) red[kDiagAt] = v;
         __syncthreads();
-        return red[255];
+        return red[kDiagAt];
     };
     // E = I - a2 G
     auto make_e = [&](const f32x4 (&gm)[2], float a2, f32x4 (&e)[2]) {
