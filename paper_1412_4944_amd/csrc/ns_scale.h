@@ -1,4 +1,4 @@
-// The scaling of the Newton-Schulz iteration X <- X (3 I - X^T X) / 2 for p = 256 (polar_wide.hip).
+// The Newton-Schulz iteration X <- X (3 I - X^T X) / 2: its last step, and its scaling for p = 256 (polar_wide.hip).
 //
 // With all singular values in [l, 1], X scaled by alpha(l) = sqrt(3 / (1 + l + l^2)) before a step makes the
 // step's polynomial f(s) = alpha s (3 - (alpha s)^2) / 2 map [l, 1] to the smallest possible interval
@@ -15,6 +15,14 @@
 #include <hip/hip_runtime.h>
 
 namespace sbo {
+
+// The last step is X (I + c1 E + c2 E^2), E = I - X^T X, for |E|_F < 1e-2: (1 - e)^(-1/2) on [0, eps] (no step leaves a
+// singular value above one, so E has no negative eigenvalue to speak of).  The third term of the series, 5/16 e^3
+// (3e-7 where one singular value lags behind the others: more than fp32 rounding), is interpolated: 5/16 times
+// e^3 - 3/2 eps e^2 + 9/16 eps^2 e lies between 0 and eps^3 / 16, 2e-8 off at most.  kLastLinear = 2 c1,
+// kLastSquare = 2 c2.
+constexpr float kLastEps = 1e-2f;
+constexpr float kLastLinear = 1.f - 5.f / 8 * 9 / 16 * kLastEps * kLastEps, kLastSquare = 0.75f + 5.f / 8 * 3 / 2 * kLastEps;
 
 struct NsScale {
     float l = 0.16f;           // before the present step

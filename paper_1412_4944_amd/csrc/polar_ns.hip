@@ -14,8 +14,8 @@
 //     them in [l, 1], X sqrt(3 / (1 + l + l^2)) makes the step's polynomial map [l, 1] to the
 //     smallest possible interval [l', 1].  A smaller singular value is safe (the polynomial never
 //     exceeds one and is positive on (0, sqrt(3))), it only takes longer; l starts at 0.16 (block
-//     matrices of this method have condition numbers of 2 to 10).  The last step is X (I + E/2 + 3/8 E^2), E = I - X^T X: its error is
-//     5/16 E^3 instead of 3/8 E^2.  Five steps where the plain iteration takes seven.
+//     matrices of this method have condition numbers of 2 to 10).  The last step is quintic, X (I + c1 E + c2 E^2),
+//     E = I - X^T X (ns_scale.h).  Five steps where the plain iteration takes seven.
 //   * The step.  A wavefront owns a strip of 16 columns of X (v_mfma_f32_16x16x32_bf16 tiles, four
 //     consecutive rows of one column per lane and tile).  An accumulator tile is at the same time
 //     the B operand of the next product, up to an order of the contraction index that the A
@@ -23,8 +23,9 @@
 //     the registers that hold E, and only the A operands (the other wavefronts' columns of X,
 //     and, transposed by ds_read_b64_tr_b16 on the way out, its rows) go through LDS.
 //   * The products run at fp32 accuracy: every entry is the exact sum of three bf16 parts
-//     (device_utils.h), six partial products with fp32 accumulation; three in the last step, where
-//     they multiply an E below 1e-2 and are added to X.
+//     (device_utils.h), six partial products with fp32 accumulation; three for E^2 in the last step, which is
+//     below 1e-4 and added to E.  (With its leading parts alone, three products for X E and the plain series, a
+//     signed permutation with one late singular value came out up to 4.2e-7 off; now exactly, in the same time.)
 // Measured inside sbo_iterate (launch to launch, K = 32, p = 64): 31 us with 32 x 32 tiles, both operands
 // of every product through LDS and the plain iteration, 16 us as it is; p = 32: 21 -> 9 us, p = 16:
 // 22 -> 7 us.  A step at p = 64 is 4800 cycles (matrix work 1650 of them), the sum of eight pieces
@@ -40,9 +41,8 @@
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "jacobi_block.h"
+#include "ns_scale.h"
 #include "sq_total.h"
-
-#include <type_traits>
 
 namespace sbo {
 
@@ -255,8 +255,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
                                                        0, 0, 0);
     };
-    // the six partial products, smallest first: (A part, B part); the last three of them alone
-    // are good for 2^-16 of the product
+    // the six partial products, smallest first: (A part, B part)
     constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
     constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -283,15 +282,14 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
                 }
         __builtin_amdgcn_sched_barrier(0);
     };
-    // acc[t] = X E for row tile t from the parts of E: the partial products Q0 .. 5
-    auto times = [&](const u32x4 (&a)[S][3][T], const u32x4 (&eq)[S][3], auto q0, f32x4 (&acc)[T]) {
-        constexpr int Q0 = decltype(q0)::value;
+    // acc[t] = X E for row tile t from the parts of E
+    auto times = [&](const u32x4 (&a)[S][3][T], const u32x4 (&eq)[S][3], f32x4 (&acc)[T]) {
 #pragma unroll
         for (int t = 0; t < T; ++t) acc[t] = zero4;
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int q = Q0; q < 6; ++q)
+            for (int q = 0; q < 6; ++q)
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc[t] = mfma(a[s][TA[q]][t], eq[s][TB[q]], acc[t]);
     };
@@ -409,7 +407,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
 #pragma unroll
             for (int w = 1; w < T; ++w) fr += red[(2 + (it & 1)) * 4 + w];
             if (!(fr < 2.f * P)) break;        // NaN or diverging: leave it to the Jacobi SVD
-            last = fr < 1e-4f;                 // |E|_F < 1e-2, a bound on the spectral norm of E
+            last = fr < kLastEps * kLastEps;   // |E|_F, a bound on the spectral norm of E
             if (!last && it >= g.max_iters) break;
         }
         f32x4 acc[T];
@@ -418,10 +416,12 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
 #pragma unroll
             for (int i = 0; i < T; ++i) ge[i] = g0[i];
             make_e(1.f);
-            // E^2 from the leading parts alone: 2^-8 of something below 1e-4
+            // E^2 from the three largest partial products: 2^-16 of something below 1e-4
             split_strip(ge, eq);
 #pragma unroll
-            for (int s = 0; s < S; ++s) write_part(other, s, 0, eq[s][0]);
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int pl = 0; pl < 2; ++pl) write_part(other, s, pl, eq[s][pl]);
             __syncthreads();
             f32x4 e2[T];
 #pragma unroll
@@ -432,19 +432,24 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
                 for (int i = 0; i < T; ++i) {
                     // E is symmetric: its rows are the strips, each with its tiles in its own order
                     const int pa = (strip_of[2 * s] - strip_of[i]) & (T - 1), pb = (pa + 1) & (T - 1);
-                    const u32x2 a = *reinterpret_cast<const u32x2*>(unit(other, strip_of[i], pa >> 1, 0) + (pa & 1) * 512 + lane_at);
-                    u32x2 b = {0u, 0u};
-                    if (T > 1)
-                        b = *reinterpret_cast<const u32x2*>(unit(other, strip_of[i], pb >> 1, 0) + (pb & 1) * 512 + lane_at);
-                    e2[i] = mfma(u32x4{a.x, a.y, b.x, b.y}, eq[s][0], e2[i]);
+                    u32x4 a[2];
+#pragma unroll
+                    for (int pl = 0; pl < 2; ++pl) {
+                        const u32x2 lo = *reinterpret_cast<const u32x2*>(unit(other, strip_of[i], pa >> 1, pl) + (pa & 1) * 512 + lane_at);
+                        u32x2 hi = {0u, 0u};
+                        if (T > 1)
+                            hi = *reinterpret_cast<const u32x2*>(unit(other, strip_of[i], pb >> 1, pl) + (pb & 1) * 512 + lane_at);
+                        a[pl] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    }
+                    e2[i] = mfma(a[1], eq[s][0], e2[i]);
+                    e2[i] = mfma(a[0], eq[s][1], e2[i]);
+                    e2[i] = mfma(a[0], eq[s][0], e2[i]);
                 }
 #pragma unroll
-            for (int i = 0; i < T; ++i) ge[i] += 0.75f * e2[i];        // 2 (E / 2 + 3/8 E^2)
+            for (int i = 0; i < T; ++i) ge[i] = kLastLinear * ge[i] + kLastSquare * e2[i];
             split_strip(ge, eq);
-            times(rows, eq, std::integral_constant<int, 3>{}, acc);
-        } else {
-            times(rows, eq, std::integral_constant<int, 0>{}, acc);
         }
+        times(rows, eq, acc);
 #pragma unroll
         for (int t = 0; t < T; ++t) xr[t] = alpha * xr[t] + (0.5f * alpha) * acc[t];
         ++it;

@@ -66,8 +66,8 @@ constexpr int kLdStrip = P + 4;
 // A team's memory
 constexpr size_t kColAt = 0;                                   // [2][16 strips] images by columns
 constexpr size_t kRowAt = kColAt + 2 * (size_t)kTeam * kImage; // [2][16 row tiles][8][part][half][64 lanes][8 bytes]
-constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [16 strips][8][64 lanes][16 bytes] leading parts of E
-constexpr size_t kJaAt = kEAt + (size_t)kTeam * 8 * 1024;      // [256 columns][256] A
+constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [2 parts][16 strips][8][64 lanes][16 bytes] of E
+constexpr size_t kJaAt = kEAt + 2 * (size_t)kTeam * 8 * 1024;  // [256 columns][256] A
 constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
 constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][3][16] | sigma[256] | 1/|v|[256]
 constexpr size_t kTeamBytes = kSmallAt + 4096;
@@ -515,38 +515,47 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             fr = wg_sum(fr, it & 1);
             least = least_diag(gm);
             alpha = scale.next();
-            // Close to the end the team meets here to learn whether this is the last step, and exchanges the
-            // leading parts of E for its square.
+            // Close to the end the team meets here to learn whether this is the last step, and exchanges two
+            // parts of E for its square.
             if (prev < 4.f || it >= g.max_iters) {           // uniform over the team
                 u32x4 part[3];
                 split(e[0], e[1], part);
-                *reinterpret_cast<u32x4*>(eimg + wave * 3 * 1024 + lane * 16) = part[0];
-                *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)t.q * 8 + wave) * 1024 + lane * 16) = part[0];
+#pragma unroll
+                for (int pl = 0; pl < 2; ++pl) {
+                    *reinterpret_cast<u32x4*>(eimg + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
+                    *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)(pl * kTeam + t.q) * 8 + wave) * 1024 + lane * 16) = part[pl];
+                }
                 if (!t.sync(fr)) return Outcome::dead;
                 prev = group_sum<16>(t.value(0));
                 known = true;
                 if (!(prev < 2.f * P)) return Outcome::left;   // NaN or diverging
-                last = prev < 1e-4f;           // |E|_F < 1e-2
+                last = prev < kLastEps * kLastEps;
                 if (!last && it >= g.max_iters) return Outcome::left;
             }
         }
         u32x4 eq[3];
-        if (last) {                            // uniform: X (I + E / 2 + 3/8 E^2), E^2 from leading parts
+        if (last) {                            // uniform.  E^2 from the three largest partial products
             alpha = 1.f;
             f32x4 e2[2] = {zero4, zero4};
             const int er = (int)kEAt + 2 * wave * 8 * 1024;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                u32x4 ea[8];
 #pragma unroll
-                for (int s = 0; s < 8; ++s) ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + (k * 8 + s) * 1024, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int pl = 1; pl >= 0; --pl) {
+                    u32x4 ea[8];
 #pragma unroll
-                for (int s = 0; s < 8; ++s) e2[k] = mfma(ea[s], at16(eimg + s * 3 * 1024 + lane * 16), e2[k]);
+                    for (int s = 0; s < 8; ++s)
+                        ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + pl * (kTeam * 8 * 1024) + (k * 8 + s) * 1024, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int s = 0; s < 8; ++s)
+#pragma unroll
+                        for (int o = 1 - pl; o >= 0; --o) e2[k] = mfma(ea[s], at16(eimg + (s * 3 + o) * 1024 + lane * 16), e2[k]);
+                }
             }
             __syncthreads();                   // eimg is rewritten
 #pragma unroll
-            for (int k = 0; k < 2; ++k) e[k] += 0.75f * e2[k];
+            for (int k = 0; k < 2; ++k) e[k] = kLastLinear * e[k] + kLastSquare * e2[k];
         } else {
             make_e(gm, alpha * alpha, e);
         }

@@ -453,6 +453,24 @@ def test_polar_condition_sweep_and_both_paths(p):
     assert np.abs(out["default"][good] - out["jacobi"][good]).max() <= 1e-4
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+@pytest.mark.parametrize("cond", [3.0, 40.0, 150.0])
+def test_polar_last_step_is_accurate(p, cond):
+    """Signed permutations with random singular values: often one of them converges last, alone, and the error of
+    the last step's polynomial and products all goes into one entry of size one.  Bound: two roundings of
+    2^-24 (the Gram matrix, the result) and 2e-8 of the polynomial, with a margin of a quarter."""
+    K = 16 if p == 256 else 96
+    rng = np.random.default_rng(41 + p + int(cond))
+    perm = np.stack([np.eye(p)[rng.permutation(p)] * rng.choice([-1.0, 1.0], p) for _ in range(K)])
+    M = (perm * rng.uniform(1 / cond, 1, (K, 1, p)) * 10.0 ** rng.uniform(-3, 3, (K, 1, 1))).astype(np.float32)
+    with Sbo(p, K, 4, 256) as g:
+        D = g.polar(M, np.zeros_like(M), None)
+        assert all(x < 0 for x in sbo.sbo_svd_sweeps(g.ctx, K))
+    worst = np.abs(D.astype(np.float64) - perm).max()
+    print(f"  p={p} cond={cond}: worst |Q - exact| {worst:.2e}", flush=True)
+    assert worst <= 1.25 * (2 * 2.0 ** -24 + 2e-8)
+
+
 @pytest.mark.parametrize("K", [1, 9, 33])               # one team; two groups of eight; teams with three blocks in turn
 @pytest.mark.parametrize("jacobi_only", [False, True], ids=["auto", "jacobi"])
 def test_polar_p256_teams_of_workgroups(K, jacobi_only):
