@@ -10,6 +10,16 @@
 // matrices of first training rounds, condition 60 to 5000: 9 to 15 steps instead of 11 to 22; condition
 // below 7: as without it.  p <= 64, condition 3 to 14, keeps the fixed scalings for l = 0.16 of
 // polar_ns.hip: a step less in some rounds was what the bookkeeping cost.)
+//
+// A narrow spectrum (atoms used equally often, over many signals) is the exception, for every p: alpha(0.16) would send
+// singular values that are all near one down to 0.375 first, where the rounding of the step weighs 1 / 0.375 as
+// much (condition 1.02: |Q - exact|_F / sqrt(p) 2.0e-7 in five steps at p = 64, 4.0e-7 in six at p = 256; with alpha = 1
+// 4.5e-8 in two, 1.0e-7 in three; p = 256, condition 1.2 2.7e-7, 9.9e-8).  The
+// eigenvalues of G have the mean mu = tr G / p and the mean square |G|_F^2 / p, so their spread is known after the
+// first product, and the scale that centres them needs no estimate of the largest.  The line (spread below
+// kNarrow mu): p <= 64 0.1, condition up to 1.2 where all singular values share in it, which one small value among
+// 64 (0.125) does not meet.  p = 256 0.25 (condition 1.5; the rounding of more products weighs more), and no
+// column below half the mean.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,6 +33,14 @@ namespace sbo {
 // kLastSquare = 2 c2.
 constexpr float kLastEps = 1e-2f;
 constexpr float kLastLinear = 1.f - 5.f / 8 * 9 / 16 * kLastEps * kLastEps, kLastSquare = 0.75f + 5.f / 8 * 3 / 2 * kLastEps;
+
+template <int P>
+__device__ constexpr float kNarrow = P <= 64 ? 0.1f : 0.25f;
+// sum2 = |G|_F^2
+template <int P>
+__device__ __forceinline__ bool narrow_spectrum(float sum2, float mu) {
+    return sum2 < P * (1.f + kNarrow<P> * kNarrow<P>) * (mu * mu);
+}
 
 struct NsScale {
     float l = 0.16f;           // before the present step
@@ -47,9 +65,14 @@ struct NsScale {
     // G = X^T X is at least its largest eigenvalue sigma_max^2, and alpha^2 <= 2.9 / that keeps every
     // scaled sigma^2 below 2.9.  Where the bound is tight, the aim is sigma_max = 1 times alpha(l), with
     // the largest norm of a column of G (a lower bound of its largest eigenvalue) as the estimate.
-    // row_sum: the former; col2: the square of the latter; diag: the smallest diagonal entry of G.
-    __device__ __forceinline__ float first(float row_sum, float col2, float diag) {
+    // row_sum: the former; col2: the square of the latter; diag: the smallest diagonal entry of G; sum2, mu: above.
+    __device__ __forceinline__ float first(float row_sum, float col2, float diag, float sum2, float mu) {
         float b2 = 2.9f * __builtin_amdgcn_rcpf(row_sum);
+        if (narrow_spectrum<256>(sum2, mu) && diag > 0.5f * mu) {
+            l = 1.f;
+            lower = 0.f;
+            return __builtin_amdgcn_sqrtf(fminf(b2, __builtin_amdgcn_rcpf(mu)));
+        }
         float est = row_sum * (1.f / 1.4f);    // of sigma_max^2
         if (col2 > 1e-37f && col2 < 3e37f) {
             est = 1.04f * __builtin_amdgcn_sqrtf(col2);

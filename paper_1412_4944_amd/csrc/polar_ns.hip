@@ -81,7 +81,7 @@ template <int P>
 constexpr int ns_image_bytes() {
     return (P / 16) * ((P / 16 + 1) / 2) * 3 * 1024;
 }
-// dynamic LDS: two images (the Jacobi routine reuses this part) | red[2][2][4] floats
+// dynamic LDS: two images (the Jacobi routine reuses this part) | red[4 slots][4 wavefronts] floats
 template <int P>
 constexpr size_t ns_front_bytes() {
     const size_t img = (size_t)2 * ns_image_bytes<P>(), jac = (size_t)jacobi_lds_floats<P>() * 4;
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
     unsigned char* other = lds_raw + ns_image_bytes<P>();
     u32x4 xq[S][3];
     int it = 0;
-    bool converged = false;
+    bool converged = false, narrow = false;
     while (true) {
         split_strip(xr, xq);
 #pragma unroll
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
             ge[0] = S > 1 ? g0[0] + g0[S - 1] : g0[0];
         }
 
-        float alpha = it < 4 ? kAlpha[it] : 1.f;           // X is scaled by this before the step
+        float alpha = it < 4 && !narrow ? kAlpha[it] : 1.f;            // X is scaled by this before the step
         bool last = false;
         if (it == 0) {
             // The scale of the input.  The iteration sends every singular value in (0, sqrt(3)) to
@@ -352,8 +352,11 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
             // largest absolute row sum of G is at least its largest eigenvalue sigma_max^2, and
             // alpha^2 <= 2.9 / that keeps every scaled sigma^2 below 2.9.  Where the bound is tight, the
             // aim is sigma_max = 1 times the scaling for l, with the largest norm of a column of
-            // G (a lower bound of its largest eigenvalue) as the estimate.
-            float rs = 0.f, r2 = 0.f;
+            // G (a lower bound of its largest eigenvalue) as the estimate; a narrow spectrum (ns_scale.h) is
+            // centred at one.
+            float rs = 0.f, r2 = 0.f, tr = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tr = fmaf(diag[r], ge[0][r], tr);
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll
@@ -362,18 +365,27 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
                     r2 = fmaf(ge[i][r], ge[i][r], r2);
                 }
             publish(0, row_max_nan(sum_groups(rs)));
-            publish(1, row_max_nan(sum_groups(r2)));
+            r2 = sum_groups(r2);
+            publish(1, row_max_nan(r2));
+            publish(2, group_sum<16>(r2));
+            publish(3, sum_groups(group_sum<16>(tr)));
             __syncthreads();
-            float rsmax = red[0], r2max = red[4];
+            float rsmax = red[0], r2max = red[4], sum2 = red[8], mu = red[12];
 #pragma unroll
             for (int w = 1; w < T; ++w) {      // as bits: a NaN wins
                 rsmax = __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, rsmax), __builtin_bit_cast(unsigned, red[w])));
                 r2max = __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, r2max), __builtin_bit_cast(unsigned, red[4 + w])));
+                sum2 += red[8 + w];
+                mu += red[12 + w];
             }
+            mu *= 1.f / P;
             // zero, infinite, NaN or overflowing input: not for this iteration
             if (!(rsmax > 1e-37f && rsmax < 3e37f)) break;
             float b2 = 2.9f * __builtin_amdgcn_rcpf(rsmax);
-            if (r2max > 1e-37f && r2max < 3e37f)
+            narrow = narrow_spectrum<P>(sum2, mu);
+            if (narrow)
+                b2 = fminf(b2, __builtin_amdgcn_rcpf(mu));
+            else if (r2max > 1e-37f && r2max < 3e37f)
                 b2 = fminf(b2, kAlpha[0] * kAlpha[0] / 1.04f * __builtin_amdgcn_rsqf(r2max));
             alpha = __builtin_amdgcn_sqrtf(b2);
         } else {

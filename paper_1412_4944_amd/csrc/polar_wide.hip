@@ -69,8 +69,11 @@ constexpr size_t kRowAt = kColAt + 2 * (size_t)kTeam * kImage; // [2][16 row til
 constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [2 parts][16 strips][8][64 lanes][16 bytes] of E
 constexpr size_t kJaAt = kEAt + 2 * (size_t)kTeam * 8 * 1024;  // [256 columns][256] A
 constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
-constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][3][16] | sigma[256] | 1/|v|[256]
-constexpr size_t kTeamBytes = kSmallAt + 4096;
+constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][kCarried][16] | sigma[256] | 1/|v|[256]
+constexpr int kCarried = 5;                                    // floats of each workgroup that a barrier carries
+constexpr int kRedSize = 4 * kCarried * 16;
+constexpr size_t kTeamBytes = kSmallAt + 5120;
+static_assert((2 * kRedSize + 2 * P) * 4 <= 5120, "the team's small memory");
 // and its counters (ints, zero between launches), each on a cache line of its own
 constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kUndoneAt = 129, kVersionAt = 160, kMeetAt = 192, kSyncInts = 224;
 // Added to a barrier's counter by a workgroup that gives up (no barrier counts as far, and 16 times it fits an int).
@@ -82,7 +85,7 @@ constexpr int kEimgAt = kImage;
 constexpr int kStripAt = 2 * kImage;                           // [16][kLdStrip] floats
 constexpr int kSmallLds = 4 * P * 16 * 4 > kStripAt + 16 * kLdStrip * 4 ? 4 * P * 16 * 4 : kStripAt + 16 * kLdStrip * 4;
 constexpr size_t kLds = kSmallLds + 6144;                      // 256 floats of reductions, 4 x 256 words, two flags, ..
-constexpr int kDiagAt = 1282;                                  // .. and a word beside the reductions
+constexpr int kDiagAt = 1282;                                  // .. and two words beside the reductions
 
 struct WideArgs {
     const float* M;            // [K][p][p] finished matrices, or nullptr: sum the pieces
@@ -151,10 +154,10 @@ __device__ __forceinline__ void raise_to(int* p, int v, bool near) {
     else __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A barrier of `size` workgroups that carries three floats of each of them.
+// A barrier of `size` workgroups that carries kCarried floats of each of them.
 struct Team {
     int* arrive;               // the counters: of the agent scope, then (a cache line on) near ones
-    float* red;                // [4][3][16]
+    float* red;                // [4][kCarried][16]
     int* ok;                   // LDS
     int size, q, polls;
     int epoch, arrived;        // barriers so far; of this kind
@@ -166,14 +169,17 @@ struct Team {
         else __hip_atomic_fetch_add(arrive, kGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 
-    __device__ __forceinline__ bool sync(float a, float b = 0.f, float c = 0.f) {      // a, b, c: of thread 0
+    // a .. e: of thread 0
+    __device__ __forceinline__ bool sync(float a, float b = 0.f, float c = 0.f, float d = 0.f, float e = 0.f) {
         ++epoch;
         ++arrived;
         if (threadIdx.x == 0) {
-            float* slot = red + (epoch & 3) * 48 + q;
+            float* slot = red + (epoch & 3) * (16 * kCarried) + q;
             slot[0] = a;
             slot[16] = b;
             slot[32] = c;
+            slot[48] = d;
+            slot[64] = e;
         }
         stores_done();
         if (threadIdx.x == 0) {
@@ -215,7 +221,7 @@ struct Team {
     }
     // value k of workgroup lane % size, from the last sync
     __device__ __forceinline__ float value(int k) const {
-        return __hip_atomic_load(red + (epoch & 3) * 48 + k * 16 + (threadIdx.x & (size - 1)), __ATOMIC_RELAXED,
+        return __hip_atomic_load(red + (epoch & 3) * (16 * kCarried) + k * 16 + (threadIdx.x & (size - 1)), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
@@ -501,11 +507,21 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
                 rs += red[w * 16 + c16];
                 r2 += red[128 + w * 16 + c16];
             }
-            if (!t.sync(row_max_nan(rs), row_max_nan(r2), least_diag(gm))) return Outcome::dead;
+            float tr = 0.f;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) tr = gm[k][r];
+            tr = sum_groups(group_sum<16>(tr));
+            if (wave == (t.q >> 1) && lane == 0) red[kDiagAt + 1] = tr;
+            least = least_diag(gm);            // (a barrier)
+            if (!t.sync(row_max_nan(rs), row_max_nan(r2), least, group_sum<16>(r2), red[kDiagAt + 1])) return Outcome::dead;
             const float rsmax = row_max_nan(t.value(0)), r2max = row_max_nan(t.value(1));
             // zero, infinite, NaN or overflowing input: not for this iteration
             if (!(rsmax > 1e-37f && rsmax < 3e37f)) return Outcome::left;
-            alpha = scale.first(rsmax, r2max, -row16_max(-t.value(2)));
+            alpha = scale.first(rsmax, r2max, -row16_max(-t.value(2)), group_sum<16>(t.value(3)),
+                                group_sum<16>(t.value(4)) * (1.f / P));
         } else {
             make_e(gm, 1.f, e);
 #pragma unroll
@@ -758,7 +774,7 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
     float* YV = YA + 16 * P;
     float* GA = reinterpret_cast<float*>(mem + kJaAt);         // [256 columns][256]
     float* GV = reinterpret_cast<float*>(mem + kJvAt);
-    float* Gsig = reinterpret_cast<float*>(mem + kSmallAt) + 384;
+    float* Gsig = reinterpret_cast<float*>(mem + kSmallAt) + 2 * kRedSize;
     float* Gvinv = Gsig + P;
     auto copy4 = [&](float* dst, const float* from) {          // 16 columns
 #pragma unroll
@@ -1075,7 +1091,7 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
     int* sync = g.sync + team * kSyncInts;
     float* small = reinterpret_cast<float*>(mem + kSmallAt);
     Team all = {sync + kArriveAt, small, flag, kTeam, q, g.polls, 0, 0, false};
-    Team eight = {sync + kArriveJacAt, small + 192, flag + 1, kJacTeam, q, g.polls, 0, 0, false};
+    Team eight = {sync + kArriveJacAt, small + kRedSize, flag + 1, kJacTeam, q, g.polls, 0, 0, false};
     int tbase = 0;
     const int blocks = (g.K - 1 - team) / g.teams + 1;         // of this team
     int undone = blocks;

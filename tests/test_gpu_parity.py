@@ -471,6 +471,31 @@ def test_polar_last_step_is_accurate(p, cond):
     assert worst <= 1.25 * (2 * 2.0 ** -24 + 2e-8)
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+@pytest.mark.parametrize("kind", ["spread", "one low", "one high"])
+def test_polar_of_narrow_spectra_is_accurate(p, kind):
+    """Singular values within 2 % (atoms used equally often): the iteration has nothing to do but to round twice, so
+    the error per singular value is that of a sum of p terms in fp32, 2^-24 max(1, sqrt(p / 64)), with a margin
+    of a half.  And on both sides of the line below which a spectrum counts as narrow, the same to 1e-6."""
+    K = 16
+    rng = np.random.default_rng(43 + p)
+    def spectrum(low):
+        if kind == "spread":
+            return rng.uniform(low, 1, p)
+        return np.r_[np.full(p - 1, low if kind == "one high" else 1.0), 1.0 if kind == "one high" else low]
+    low = np.r_[np.full(8, 1 / 1.02), np.geomspace(1 / 1.1, 1 / 3, 8)]
+    M32 = np.stack([(synth.random_onb(rng, p) * spectrum(l)) @ synth.random_onb(rng, p) * 10.0 ** rng.uniform(-3, 3)
+                    for l in low]).astype(np.float32)
+    with Sbo(p, K, 4, 256) as g:
+        D = g.polar(M32, np.zeros_like(M32), None)
+        steps = sbo.sbo_svd_sweeps(g.ctx, K)
+    Q = np.stack([orc.o_polar(m.astype(np.float64)) for m in M32])
+    err = np.sqrt(((D - Q) ** 2).sum((1, 2)) / p)
+    print(f"  p={p} {kind}: worst {err[:8].max():.2e}, then {err[8:].max():.2e}, steps {steps}", flush=True)
+    assert err[:8].max() <= 1.5 * 2.0 ** -24 * max(1.0, np.sqrt(p / 64))
+    assert err.max() <= 1e-6
+
+
 @pytest.mark.parametrize("K", [1, 9, 33])               # one team; two groups of eight; teams with three blocks in turn
 @pytest.mark.parametrize("jacobi_only", [False, True], ids=["auto", "jacobi"])
 def test_polar_p256_teams_of_workgroups(K, jacobi_only):
