@@ -174,6 +174,32 @@ def test_group_matches_oracle(K, m):
     np.testing.assert_array_equal(perm, op)
 
 
+@pytest.mark.parametrize("p", [16, 32, 64])
+@pytest.mark.parametrize("K,m", [(256, 1024), (256, 1025), (257, 1024), (1, 1024), (256, 1), (5, 513)])
+def test_code_groups_small_sets_in_the_select_kernel(p, K, m):
+    """Both sides of the rule by which sbo_code leaves the grouping of a small set to the select kernel (m <= 1024,
+    K <= 256: at (256, 1024) its lists and the tiles fill LDS), on one context in turn with calls that group by a
+    launch: what either leaves in the workspace is what the other needs."""
+    pr = synth.generate(synth.custom(f"small_p{p}", p=p, K=K, m=max(m, 1100), s0=4, snr_db=20.0))
+    Y, D = pr.Y[:m], pr.D_planted
+    with Sbo(p, K, 4, pr.Y.shape[0]) as g:
+        sbo.sbo_set_timing(g.ctx, 1)
+        for n in (m, pr.Y.shape[0], m):
+            out = g.code(pr.Y[:n], D)
+            ms = sbo.sbo_stage_ms(g.ctx)
+            assert (ms["group"] > 0) == (n > 1024 or K > 256)
+            compare_code(pr.Y[:n], D, 4, orc.o_code(pr.Y[:n], D, 4), out)
+        sbo.sbo_set_timing(g.ctx, 0)
+        # the histograms of the choice are zero again: a grouping that adds to them, and one that counts itself
+        D1, blk, supp, coef, err, sq = g.iterate(Y, D, 1)
+        np.testing.assert_array_equal(blk, out[0])
+        np.testing.assert_array_equal(supp, out[1])
+        counts, offsets, perm = g.group(blk)
+        oc, oo, op = orc.o_group(blk, K)
+        np.testing.assert_array_equal(counts, oc)
+        np.testing.assert_array_equal(perm, op)
+
+
 UPDATE_CASES = [
     ("tiny", dict()),
     ("patch8", dict(m=4096 + 77)),
