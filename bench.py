@@ -176,11 +176,14 @@ def roofline_entry(p, K, m, energy_ms, arith, workload, s0=8):
     sel = extra.get("selection_alu")
     if sel is not None and sel["frac"] > out["frac"]:
         # The roofline of a kernel is the highest of its floors.  With one fp16 product the
-        # vector-ALU floor (selection networks) lies above the matrix floor, so that is the roof
-        # the kernel is measured against; the matrix side stays in "mfma".
+        # vector-ALU floor (the bounds) lies above the matrix floor, so that is the roof
+        # the kernel is measured against; the matrix side stays in "mfma".  Neither floor alone holds
+        # it: both run on one power budget, so their times add up (0.7 to 0.8 of the sum), and the
+        # load and conversion of the signals and the contenders' resolution overlap neither.
         out = {"bound": "alu", "achieved": sel["achieved_Tops"], "peak": sel["peak_Tops"],
-               "unit": "Tops/s (vector lane operations: one min / max / median per lane and instruction; "
-                       "256 CUs x 64 lanes x 2.4 GHz)",
+               "unit": "Tops/s (vector lane operations: one per lane and instruction; 256 CUs x 64 lanes x 2.4 GHz)",
+               "bound_note": "the higher of two floors that add up rather than overlap: matrix and vector work share the "
+                             "power budget, and the load of the signals and the contenders' resolution overlap neither",
                "frac": sel["frac"], "traffic": out["traffic"], "kernel": extra["kernel"],
                "mfma": {"achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                         **{k: v for k, v in extra.items() if k not in ("kernel", "selection_alu")}},

@@ -220,9 +220,10 @@ enum {
                                   Q_j up to rounding, in tens of milliseconds. */
 };
 enum {
-    SBO_SVD_AUTO   = 0,  /* default: Newton-Schulz polar factor on the matrix cores, the one-sided
-                            Jacobi SVD for the orthobases it flags (rank-deficient P_j) */
-    SBO_SVD_JACOBI = 1   /* the one-sided Jacobi SVD (one workgroup per orthobase) for every orthobase */
+    SBO_SVD_AUTO   = 0,  /* default: Newton-Schulz polar factor on the matrix cores (six bf16 partial products of exact
+                            three-part splits, rounding at the fp32 level, whatever SBO_OPT_CODING_ARITH is), the
+                            one-sided Jacobi SVD for the orthobases it flags (rank-deficient P_j) */
+    SBO_SVD_JACOBI = 1   /* the one-sided Jacobi SVD for every orthobase (one workgroup each, p = 256: eight) */
 };
 
 enum {

@@ -173,7 +173,10 @@ constexpr bool screen_applies(int p, int K, int s0, int arith) {
 // Which shape of the screening kernel (p <= 64): workgroups of 256 signals, two per CU, instead of 512 where the
 // last round of the latter would be at most 0.65 full (196608 signals, p = 64, K = 32: 141 us instead of 160); on
 // full rounds they are equal, but with fewer signals per list of candidates the resolution costs more (262144
-// signals, near-random dictionary: 164 us instead of 142).
+// signals, near-random dictionary: 164 us instead of 142).  The line was found at p = 64, K = 32 and depends on m
+// alone; measured over K (trained dictionary), it costs up to 4 % at K >= 32.  Where a workgroup has fewer stages to
+// multiply, 256 signals are better on full rounds too: p = 64, K = 4 393216 signals 48.5 us, by 256 41.3; K = 16
+// 524288 signals 110.7, 100.9; p = 16, K = 32 393216 signals 46.0, 38.6.
 constexpr bool screen_by_256(int64_t m) {
     const int64_t round = (int64_t)kNumCU * 512, rest = m % round;
     return rest != 0 && 20 * rest < 13 * round;
@@ -182,7 +185,10 @@ constexpr bool screen_by_256(int64_t m) {
 // all of theirs and are up to 1.4 times as fast on a full chip, but their time is that of whole rounds.
 // Measured, p = 64, K = 32, workgroups of 64 / 256: 32768 signals 55 / 61 us, 49152 69 / 65, 65536 84 / 71, 131072
 // 145 / 107; p = 256, K = 16, 64 / 512: 81920 signals 385 / 394 us, 98304 466 / 446, 131072 603 / 527, 150000 675 /
-// 738, 196608 853 / 823.
+// 738, 196608 853 / 823.  The lines depend on m alone.  Measured over K: within 9 % of the best shape at p = 64, K >= 32,
+// and p = 256, K = 4 to 64; not at p = 64, K = 16 (40960 signals 26.7 us, by 256 22.0), and p = 16 and 32, which share the
+// line of p = 256, are better with 64 signals for longer where K is large (p = 32, K = 128, 98304 signals 84.3 us,
+// by 64 64.6) and with 256 for sooner where it is small (p = 16, K = 32, 163840 signals 30.7, 21.9).
 constexpr bool screen_shared(int64_t m, bool p64_by_256) {
     const int64_t round = (int64_t)kNumCU * 512, rounds = (m + round - 1) / round;
     return p64_by_256 ? 5 * m < 2 * round : 20 * m < 13 * rounds * round;
