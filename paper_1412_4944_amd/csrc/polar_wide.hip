@@ -25,7 +25,7 @@
 // What bounds it: Newton-Schulz by the 768 KiB of operands per workgroup and step from L2 (40 to 46 bytes a
 // cycle arrive; a step is 27000 cycles, 6600 of them matrix work, 3000 the barrier); Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  The kernel that has
-// both needs more registers than a lane of 512 threads has: 99 of them are spilled (none in the one that has Jacobi
+// both needs more registers than a lane of 512 threads has: 100 of them are spilled (none in the one that has Jacobi
 // alone), 400 bytes a lane, which with 80 MB of strips is what 142 MiB written per launch are (K = 16).
 // Measured: K = 16 inside sbo_iterate 347 us (a launch per product and step, fp32 matrix instruction,
 // 20 steps enqueued, plus launches for the sum of the pieces, the Jacobi SVD that has nothing to do,
@@ -68,8 +68,9 @@ constexpr int kLdStrip = P + 4;
 // A team's memory
 constexpr size_t kColAt = 0;                                   // [2][16 strips] images by columns
 constexpr size_t kRowAt = kColAt + 2 * (size_t)kTeam * kImage; // [2][16 row tiles][8][part][half][64 lanes][8 bytes]
-constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [2 parts][16 strips][8][64 lanes][16 bytes] of E
-constexpr size_t kJaAt = kEAt + 2 * (size_t)kTeam * 8 * 1024;  // [256 columns][256] A
+constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [16 strips][8][64 lanes][16 bytes] fp16 parts of E
+constexpr size_t kJaAt = kEAt + (size_t)kTeam * 8 * 1024;      // [256 columns][256] A
+constexpr float kEScale = 8192.f;                              // of those: 1e-2 is in the middle of fp16's range
 constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
 constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][kCarried][16] | sigma[256] | 1/|v|[256]
 constexpr int kCarried = 5;                                    // floats of each workgroup that a barrier carries
@@ -533,16 +534,16 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             fr = wg_sum(fr, it & 1);
             least = least_diag(gm);
             alpha = scale.next();
-            // Close to the end the team meets here to learn whether this is the last step, and exchanges two
-            // parts of E for its square.
+            // Close to the end the team meets here to learn whether this is the last step, and exchanges the
+            // leading fp16 parts of E for its square.
             if (prev < 4.f || it >= g.max_iters) {           // uniform over the team
-                u32x4 part[3];
-                split(e[0], e[1], part);
-#pragma unroll
-                for (int pl = 0; pl < 2; ++pl) {
-                    *reinterpret_cast<u32x4*>(eimg + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
-                    *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)(pl * kTeam + t.q) * 8 + wave) * 1024 + lane * 16) = part[pl];
-                }
+                const f32x4 lo = kEScale * e[0], hi = kEScale * e[1];
+                const F16x2Pair a0 = split_f16x2(lo.x, lo.y), a1 = split_f16x2(lo.z, lo.w);
+                const F16x2Pair a2 = split_f16x2(hi.x, hi.y), a3 = split_f16x2(hi.z, hi.w);
+                const u32x4 lead = {a0.hi, a1.hi, a2.hi, a3.hi};
+                *reinterpret_cast<u32x4*>(eimg + wave * 3 * 1024 + lane * 16) = lead;
+                *reinterpret_cast<u32x4*>(eimg + (wave * 3 + 1) * 1024 + lane * 16) = u32x4{a0.lo, a1.lo, a2.lo, a3.lo};
+                *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)t.q * 8 + wave) * 1024 + lane * 16) = lead;
                 if (!t.sync(fr)) return Outcome::dead;
                 prev = group_sum<16>(t.value(0));
                 known = true;
@@ -552,28 +553,30 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             }
         }
         u32x4 eq[3];
-        if (last) {                            // uniform.  E^2 from the three largest partial products
+        // uniform.  E^2: one operand in its leading fp16 part (off by 2^-11, of a term below 4e-5: 2e-8 at most, as
+        // the polynomial), the other in two.  As three bf16 products it takes a second exchange and two more rounds
+        // of loads, 3 us of 97 at K = 16, for an error that is the same in all digits measured.
+        if (last) {
             alpha = 1.f;
             f32x4 e2[2] = {zero4, zero4};
             const int er = (int)kEAt + 2 * wave * 8 * 1024;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
+                u32x4 ea[8];
 #pragma unroll
-                for (int pl = 1; pl >= 0; --pl) {
-                    u32x4 ea[8];
+                for (int s = 0; s < 8; ++s) ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + (k * 8 + s) * 1024, 0);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int s = 0; s < 8; ++s)
-                        ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + pl * (kTeam * 8 * 1024) + (k * 8 + s) * 1024, 0);
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int s = 0; s < 8; ++s)
 #pragma unroll
-                    for (int s = 0; s < 8; ++s)
-#pragma unroll
-                        for (int o = 1 - pl; o >= 0; --o) e2[k] = mfma(ea[s], at16(eimg + (s * 3 + o) * 1024 + lane * 16), e2[k]);
-                }
+                    for (int pl = 1; pl >= 0; --pl)
+                        e2[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            __builtin_bit_cast(f16x8, ea[s]),
+                            __builtin_bit_cast(f16x8, at16(eimg + (s * 3 + pl) * 1024 + lane * 16)), e2[k], 0, 0, 0);
             }
             __syncthreads();                   // eimg is rewritten
 #pragma unroll
-            for (int k = 0; k < 2; ++k) e[k] = kLastLinear * e[k] + kLastSquare * e2[k];
+            for (int k = 0; k < 2; ++k) e[k] = kLastLinear * e[k] + (kLastSquare / (kEScale * kEScale)) * e2[k];
         } else {
             make_e(gm, alpha * alpha, e);
         }
