@@ -116,7 +116,7 @@ int sbo_accumulate(sbo_ctx* c, const float* Y, int64_t m, const int32_t* blk,
  * matrix cores where that converges (condition numbers up to about 3000) and by a
  * one-sided Jacobi SVD otherwise (or always: sbo_set_option).  A block with counts[j] == 0 is left untouched
  * (counts may be NULL = all blocks updated).  Rank-deficient M_j: the null directions
- * are completed to an orthonormal basis (any completion is a valid U V^T).
+ * are completed to an orthonormal basis (any completion is a valid U V^T).  M and D must not overlap.
  * in : M[K][p][p], counts[K] or NULL in/out: D[K][p][p] */
 int sbo_polar(sbo_ctx* c, const float* M, const int32_t* counts, float* D);
 

@@ -26,10 +26,10 @@
 // cycle arrive; a step is 27000 cycles, 6600 of them matrix work, 3000 the barrier); Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  The kernel that has
 // both needs more registers than a lane of 512 threads has: 100 of them are spilled (none in the one that has Jacobi
-// alone), 400 bytes a lane, which with 80 MB of strips is what 142 MiB written per launch are (K = 16).
+// alone), 400 bytes a lane, which with 80 MB of strips is what 145 MiB written per launch are (K = 16).
 // Measured: K = 16 inside sbo_iterate 347 us (a launch per product and step, fp32 matrix instruction,
 // 20 steps enqueued, plus launches for the sum of the pieces, the Jacobi SVD that has nothing to do,
-// the operand order and the squared error: 46 launches, 400 us) -> 125 us and nothing else; K = 1 in a
+// the operand order and the squared error: 46 launches, 400 us) -> 136 us and nothing else; K = 1 in a
 // first training round 300 -> 125 us; eigenvectors of a Gram matrix (10 sweeps) 12.1 -> 1.8 ms.
 //
 // Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups, one per CU, and workgroups
