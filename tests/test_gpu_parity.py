@@ -607,6 +607,36 @@ def test_polar_p256_teams_that_give_up(K, polls):
                 assert (work[counts > 0] > 0).all(), "no team can have met"
 
 
+@pytest.mark.parametrize("polls", [0, 100])
+def test_polar_p256_teams_that_give_up_on_three_streams(polls):
+    """The same with the workgroup order of more than two streams, whose launches overlap."""
+    import torch
+    p, K = 256, 9
+    rng = np.random.default_rng(53)
+    M32 = np.stack([(synth.random_onb(rng, p) * np.geomspace(1, 0.1, p)) @ synth.random_onb(rng, p)
+                    for _ in range(K)]).astype(np.float32)
+    M32[4][:, 200:] = M32[4][:, :56]                     # left to the Jacobi SVD
+    Dn = np.stack([orc.o_polar(M32[j].astype(np.float64)) for j in range(K)])
+    M = torch.from_numpy(M32).cuda()
+    D = [torch.zeros_like(M) for _ in range(3)]
+    torch.cuda.synchronize()
+    ctxs = []
+    for _ in range(3):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ctxs.append((s, sbo.sbo_create(p, K, 4, 256)))
+        sbo.sbo_set_option(ctxs[-1][1], sbo.SBO_OPT_SVD_WAIT, polls)
+    for _ in range(2):
+        for (s, c), d in zip(ctxs, D):
+            with torch.cuda.stream(s):
+                sbo.sbo_polar(c, M, None, d)
+    torch.cuda.synchronize()
+    for s, c in ctxs:
+        sbo.sbo_destroy(c)
+    for d in D:
+        compare_Q(d.cpu().numpy(), Dn, M32.astype(np.float64), np.ones(K, bool))
+
+
 def test_iterate_and_base_at_p256_with_teams_that_give_up():
     """The same inside sbo_iterate: the next coding pass reads the operand orders of what was finished; and the
     eigenvectors of a Gram matrix."""
