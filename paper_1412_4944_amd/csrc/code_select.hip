@@ -58,10 +58,12 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
         int* off = reinterpret_cast<int*>(ctile_all + 4 * 32 * LDC);
         int *run = off + (K + 1), *list = run + 4 * K;
         const int per = (g.m + 3) >> 2, beg = min(g.m, wave * per), end = min(g.m, beg + per);
+        int key[1];
+        load_keys(g.blk, beg, end, key);
         for (int j = tid; j < 4 * K; j += 256) run[j] = 0;
         __syncthreads();
         for (int i = beg + lane; i < end; i += 64) {
-            const int b = g.blk[i];
+            const int b = i < beg + 64 ? key[0] : g.blk[i];
             if ((unsigned)b < (unsigned)K) atomicAdd(&run[wave * K + b], 1);
         }
         __syncthreads();
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
             }
         }
         __syncthreads();
-        scatter_chunk(g.blk, beg, end, K, run + wave * K, list);
+        scatter_chunk(g.blk, key, beg, end, K, run + wave * K, list);
         if (blockIdx.x == 0) {
             for (int j = tid; j <= K; j += 256) g.offsets[j] = off[j];
             for (int j = tid; j < K; j += 256) g.counts[j] = off[j + 1] - off[j];

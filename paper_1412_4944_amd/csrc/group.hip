@@ -116,8 +116,12 @@ __global__ __launch_bounds__(256) void group_scatter_kernel(const int32_t* __res
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = blockIdx.x * 4 + wave;
     int* run = runs + wave * K;
+    const int beg = min(m, c * chunk), end = min(m, beg + chunk);
+    int key[8];                                // on their way while the offsets are formed
+    load_keys(blk, beg, end, key);
+    int ticket = 0;
     if constexpr (SCAN) {
-        int *total = runs + 4 * K, *before = total + K, *last = before + K;
+        int *total = runs + 4 * K, *before = total + K;
         for (int j = threadIdx.x; j < 2 * K; j += 256) total[j] = 0;
         __syncthreads();
         const int rows = 256 / K, j = (int)threadIdx.x % K, c0 = (int)blockIdx.x * 4;
@@ -140,14 +144,7 @@ __global__ __launch_bounds__(256) void group_scatter_kernel(const int32_t* __res
             run[jj] = v;
         }
         __syncthreads();
-        if (done != nullptr) {                 // uniform
-            if (threadIdx.x == 0) *last = atomicAdd(done, 1) == (int)gridDim.x - 1;
-            __syncthreads();
-            if (*last) {
-                for (int e = threadIdx.x; e < n_chunks * K; e += 256) chunk_count[e] = 0;
-                if (threadIdx.x == 0) *done = 0;
-            }
-        }
+        if (done != nullptr && threadIdx.x == 0) ticket = atomicAdd(done, 1);      // (looked at when all else is done)
         wg_exclusive_scan4([&](int idx) { return total[idx]; }, K, off, tmp);
         if (blockIdx.x == 0)
             for (int jj = threadIdx.x; jj < K; jj += 256) counts[jj] = total[jj];
@@ -159,11 +156,18 @@ __global__ __launch_bounds__(256) void group_scatter_kernel(const int32_t* __res
     }
     if (blockIdx.x == 0)
         for (int j = threadIdx.x; j <= K; j += 256) offsets[j] = off[j];
-    if (c >= n_chunks) return;             // no workgroup barrier below this line
     __builtin_amdgcn_wave_barrier();
-
-    const int beg = c * chunk;
-    scatter_chunk(blk, beg, min(m, beg + chunk), K, run, perm);
+    if (c < n_chunks) scatter_chunk(blk, key, beg, end, K, run, perm);
+    if constexpr (SCAN)
+        if (done != nullptr) {                 // uniform
+            int* last = runs + 6 * K;
+            if (threadIdx.x == 0) *last = ticket == (int)gridDim.x - 1;
+            __syncthreads();
+            if (*last) {
+                for (int e = threadIdx.x; e < n_chunks * K; e += 256) chunk_count[e] = 0;
+                if (threadIdx.x == 0) *done = 0;
+            }
+        }
 }
 
 // scan + scatter from the histograms in chunk_count
