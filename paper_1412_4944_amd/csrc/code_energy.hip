@@ -53,20 +53,25 @@ __global__ __launch_bounds__(256) void dict_swizzle_kernel(const float* __restri
 
 // The same dictionary in parts, 8 consecutive dims of a row per 16-byte unit and part (see
 // device_utils.h): three bf16 (Dsb) and / or two fp16 (Dsh; then also dnorm, per 16 atoms the largest
-// norm of an atom and of what its leading fp16 part leaves).  One launch for both orders.
+// norm of an atom and of what its leading fp16 part leaves).  One launch for both orders.  Latency is all it is
+// (a trip to memory each way), so a thread takes one or two units: p = 256, K = 16 13.3 us with 64 rows to
+// a workgroup, 9.4 with 16.
 template <int P>
+constexpr int dict_rows() {
+    return P == 256 ? 16 : P == 64 ? 32 : 64;
+}template <int P>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
                                                          float2* __restrict__ dnorm) {
-    constexpr int KS16 = P / 16;
-    __shared__ float qs[64][P / 8 + 1], rs[64][P / 8 + 1];
+    constexpr int KS16 = P / 16, R = dict_rows<P>();
+    __shared__ float qs[R][P / 8 + 1], rs[R][P / 8 + 1];
     const f32x4* D4 = reinterpret_cast<const f32x4*>(D);
     const int rows = K * P;
-    const int s = blockIdx.x;
-    for (int g = threadIdx.x; g < 2 * KS16 * 64; g += 256) {       // (mt, ks, lane)
-        const int lane = g & 63, mk = g >> 6;
-        const int nn = lane & 31, hh = lane >> 5, ks = mk % KS16, mt = mk / KS16;
-        const int grow = s * 64 + mt * 32 + nn;
+    const int row0 = blockIdx.x * R;
+    for (int g = threadIdx.x; g < R * (P / 8); g += 256) {         // (ks, hh, row)
+        const int r = g % R, kh = g / R, ks = kh >> 1, hh = kh & 1;
+        const int grow = row0 + r, lane = hh * 32 + (grow & 31);
+        const int64_t mk = (int64_t)(grow >> 5) * KS16 + ks;       // 64 rows: two tiles of 32
         f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
         if (grow < rows) {
             v0 = D4[(int64_t)grow * (P / 4) + ks * 4 + hh * 2];
@@ -75,7 +80,7 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
         if (Dsb != nullptr) {
             const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
             const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
-            u32x4* out = Dsb + ((int64_t)s * (2 * KS16) + mk) * (3 * 64) + lane;
+            u32x4* out = Dsb + mk * (3 * 64) + lane;
             out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
             out[64] = u32x4{a.mid, b.mid, c.mid, d.mid};
             out[128] = u32x4{a.lo, b.lo, c.lo, d.lo};
@@ -83,16 +88,16 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
         if (Dsh != nullptr) {
             float q2 = 0.f, r2 = 0.f;
             const F16x2Quad a = split_f16x2_dict(v0, q2, r2), b = split_f16x2_dict(v1, q2, r2);
-            u32x4* out = Dsh + ((int64_t)s * (2 * KS16) + mk) * (2 * 64) + lane;
+            u32x4* out = Dsh + mk * (2 * 64) + lane;
             out[0] = u32x4{a.hi.x, a.hi.y, b.hi.x, b.hi.y};
             out[64] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
-            qs[mt * 32 + nn][ks * 2 + hh] = q2;
-            rs[mt * 32 + nn][ks * 2 + hh] = r2;
+            qs[r][kh] = q2;
+            rs[r][kh] = r2;
         }
     }
     if (Dsh != nullptr) {                      // uniform
         __syncthreads();
-        if (threadIdx.x < 64) {
+        if (threadIdx.x < R) {
             float q2 = 0.f, r2 = 0.f;
             for (int e = 0; e < P / 8; ++e) {
                 q2 += qs[threadIdx.x][e];
@@ -100,7 +105,7 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
             }
             q2 = row16_max(q2);
             r2 = row16_max(r2);
-            const int at = s * 4 + (threadIdx.x >> 4);
+            const int at = (row0 + (int)threadIdx.x) >> 4;
             if ((threadIdx.x & 15) == 0 && at < K * (P / 16)) dnorm[at] = float2{sqrtf(q2), sqrtf(r2)};
         }
     }
@@ -863,12 +868,12 @@ hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStre
 
 hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, hipStream_t st) {
     u32x4 *b = reinterpret_cast<u32x4*>(dsb), *h = reinterpret_cast<u32x4*>(dsh);
-    const dim3 grid((K * p + 63) / 64);
+    const unsigned stages = (unsigned)(K * p + 63) / 64;           // (the last one is filled up with zeros)
     switch (p) {
-        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), grid, dim3(256), 0, st, D, K, b, h, dnorm); break;
-        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), grid, dim3(256), 0, st, D, K, b, h, dnorm); break;
-        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), grid, dim3(256), 0, st, D, K, b, h, dnorm); break;
-        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), grid, dim3(256), 0, st, D, K, b, h, dnorm); break;
+        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
+        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
+        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
+        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
