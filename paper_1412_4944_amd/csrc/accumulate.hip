@@ -569,8 +569,18 @@ __global__ __launch_bounds__(256) void accum_reduce_kernel(int K, int piece,
     const int j = blockIdx.x;
     const int e = blockIdx.y * 256 + threadIdx.x;
     if (e >= PP) return;
+    // eight pieces on their way at a time (every round is a trip to memory), added in piece order
+    constexpr int A = 8;
+    const int pc1 = piece_start[j + 1];
     float s = 0.f;
-    for (int pc = piece_start[j]; pc < piece_start[j + 1]; ++pc) s += partial[(int64_t)pc * PP + e];
+    for (int pc = piece_start[j]; pc < pc1; pc += A) {
+        float v[A];
+#pragma unroll
+        for (int k = 0; k < A; ++k) v[k] = pc + k < pc1 ? partial[(int64_t)(pc + k) * PP + e] : 0.f;
+#pragma unroll
+        for (int k = 0; k < A; ++k)
+            if (pc + k < pc1) s += v[k];
+    }
     M[(int64_t)j * PP + e] = s;
 }
 

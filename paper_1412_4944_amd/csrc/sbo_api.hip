@@ -13,9 +13,12 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static int max_chunks() { return 1025; }
 
-static int max_pieces_bound(int64_t m_max, int K, int p) {
-    const int min_piece = p <= 64 ? 64 : 256;  // smallest piece size accum_piece() can return
-    return (int)((m_max + min_piece - 1) / min_piece) + K + 1;
+// At least what accum_piece() and accum_tall_piece() make of any m <= m_max and at most K blocks.
+static int64_t max_pieces_bound(int64_t m_max, int K, int p) {
+    const int64_t smallest = (m_max + kMinPiece - 1) / kMinPiece;
+    if (p <= 64) return smallest + K + 1;
+    const int64_t most = (m_max + kMaxPiece - 1) / kMaxPiece;      // (they only grow beyond kNumCU when that many are largest)
+    return (smallest < most + kNumCU ? smallest : most + kNumCU) + K + 1;
 }
 
 size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char* base) {
