@@ -18,7 +18,7 @@ LIB = os.path.join(LIB_DIR, "libsbo.so")
 
 SOURCES = ["sbo_api.hip", "code_energy.hip", "code_screen_16.hip", "code_screen_32.hip", "code_screen_64.hip",
            "code_screen_256.hip", "code_select.hip", "select_accum.hip", "group.hip", "accumulate.hip",
-           "polar_jacobi.hip", "polar_ns.hip", "polar_wide.hip", "reduce.hip", "worst.hip"]
+           "polar_jacobi.hip", "polar_ns.hip", "polar_wide.hip", "eigen.hip", "reduce.hip", "worst.hip"]
 # bench.py's achievable-peak probes: a library of their own, not part of libsbo
 PROBE_SOURCE = "bench_probe.hip"
 PROBE_LIB = os.path.join(LIB_DIR, "libsbo_benchprobe.so")
@@ -34,6 +34,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # or atoms holding NaN give unspecified block choices instead of propagating NaN).
 EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"] for f in SOURCES
          if f.startswith(("code_energy", "code_screen"))}
+# (the same reason: the accumulators are read by vector instructions after every product)
+EXTRA["eigen.hip"] = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 
 
 def hipcc() -> str:

@@ -65,6 +65,10 @@ hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, flo
                         const Workspace& ws, int jacobi_only, float* eig_sv, int write_ops,
                         hipStream_t st) {
     const bool ns = eig_sv == nullptr && !jacobi_only;
+    if (eig_sv != nullptr && !jacobi_only) {   // what it leaves: "no signals" to the Jacobi kernels is "done"
+        if (hipError_t e = launch_eigen(p, K, M, D, eig_sv, ws, st); e != hipSuccess) return e;
+        counts = ws.eig_left;
+    }
     if (p == 256)
         return launch_polar_wide(K, M, nullptr, nullptr, 0, counts, D, dict_ops(ws, eig_sv ? 0 : write_ops), ns, eig_sv,
                                  ws, SqTotalArgs{}, st);

@@ -48,6 +48,8 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.M = (float*)take((size_t)K * p * p * 4);
     w.wide = (float*)take(p > 64 ? polar_wide_scratch_bytes(K) : 0);
     w.wide_sync = (int*)take(p > 64 ? polar_wide_sync_bytes(K) : 0);
+    w.eig = (unsigned char*)take((size_t)K * eigen_scratch_bytes(p));
+    w.eig_left = (int32_t*)take((size_t)K * 4);
     const size_t sel_chunks = (size_t)((m_max + kSelChunk - 1) / kSelChunk);
     w.sel_hist = (int32_t*)take((size_t)4 * 256 * 4);
     w.sel_state = (int32_t*)take((size_t)4 * 2 * 4);
@@ -464,8 +466,8 @@ int sbo_worst(sbo_ctx* c, const float* err, int64_t m, int64_t W, int32_t* ids) 
 // Gram matrix of the set -> its eigenvectors by descending eigenvalue (ws.perm etc. hold the set).
 static int run_init_base(sbo_ctx* c, const float* Y, int64_t n, float* Q, float* sv) {
     SBO_HIP(launch_gram(c->p, 1, Y, n, c->ws, c->ws.M, c->stream));
-    SBO_HIP(launch_polar(c->p, 1, c->ws.M, nullptr, Q, c->ws, 0, sv ? sv : c->ws.energy, 0,
-                         c->stream));              // energy[m_max >= p] as a sink
+    SBO_HIP(launch_polar(c->p, 1, c->ws.M, nullptr, Q, c->ws, c->svd_method == SBO_SVD_JACOBI,
+                         sv ? sv : c->ws.energy, 0, c->stream));   // energy[m_max >= p] as a sink
     return SBO_OK;
 }
 
@@ -552,7 +554,8 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
     if (c->p <= 64 && n_init <= c->m_max && (int64_t)K0 * c->p <= c->m_max) {
         SBO_HIP(launch_equal_blocks(init_ids, K0, P0, m, c->ws, c->stream));
         SBO_HIP(launch_gram(c->p, K0, Y, n_init, c->ws, c->ws.M, c->stream));
-        SBO_HIP(launch_polar(c->p, K0, c->ws.M, nullptr, D, c->ws, 0, c->ws.energy, 0, c->stream));
+        SBO_HIP(launch_polar(c->p, K0, c->ws.M, nullptr, D, c->ws, c->svd_method == SBO_SVD_JACOBI, c->ws.energy, 0,
+                             c->stream));
         for (int r = 0; r < R; ++r) {
             SBO_HIP(launch_select_accum(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, c->stream));
             rc = run_polar_pieces(c, n_init, D, 0, nullptr, nullptr, K0);

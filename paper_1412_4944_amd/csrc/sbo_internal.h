@@ -109,6 +109,9 @@ struct Workspace {
     float* M;              // [K][p][p]
     float* wide;           // p > 64 only: exchange memory of polar_wide.hip (polar_wide_scratch_bytes)
     int* wide_sync;        // p > 64 only: its counters (0 between launches)
+    // eigenvectors of Gram matrices
+    unsigned char* eig;    // [K] x eigen_scratch_bytes
+    int32_t* eig_left;     // [K] not 0: left to the Jacobi SVD
     // worst-W selection
     int32_t* sel_hist;     // [4][256] digit histograms of the radix select
     int32_t* sel_state;    // [4][2] (key prefix, entries still to take) after each pass
@@ -247,14 +250,19 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
 // jacobi_only != 0: the Jacobi SVD for every block (SBO_SVD_JACOBI).
 // Uses ws.wide and ws.wide_sync (p = 256), ws.sweeps (per block: Jacobi sweeps, or minus the
 // Newton-Schulz steps), ws.ns_fallback.
-// eig_sv != nullptr switches to eigen mode (always Jacobi): M[j] symmetric positive
-// semidefinite, D[j] receives its eigenvectors as atoms by descending eigenvalue and
-// eig_sv[j][p] the square roots of the eigenvalues.
+// eig_sv != nullptr switches to eigen mode: M[j] symmetric positive semidefinite, D[j] receives its
+// eigenvectors as atoms by descending eigenvalue and eig_sv[j][p] the square roots of the eigenvalues
+// (launch_eigen, then Jacobi for the matrices that it leaves; jacobi_only: Jacobi for all of them).
 // write_ops: the operand orders (kOps*) in which the rows of every updated block are also left in
 // ws (not in eigen mode).
 hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, float* D,
                         const Workspace& ws, int jacobi_only, float* eig_sv, int write_ops,
                         hipStream_t st);
+
+// Eigenvectors by tridiagonalisation (eigen.hip), as eigen mode above; ws.eig_left[j] != 0 where D[j] and sv[j] are
+// not to be used.
+size_t eigen_scratch_bytes(int p);
+hipError_t launch_eigen(int p, int K, const float* M, float* D, float* sv, const Workspace& ws, hipStream_t st);
 
 // Total squared error riding along in a launch (sq_total.h): out == nullptr = none.
 struct SqTotalArgs {

@@ -102,6 +102,30 @@ def test_init_base_matches_oracle(name, kw, n):
         assert checked >= cfg.p // 4
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+@pytest.mark.parametrize("kind", ["noise", "equal", "pairs", "zero", "scaled"])
+def test_init_base_spectra(p, kind):
+    """Spectra at both ends of what the tridiagonal eigenvectors take: well separated ones (noise, also far from
+    unit scale), and equal, pairwise equal and vanishing eigenvalues, which the Jacobi kernels have to finish."""
+    rng = np.random.default_rng(47 + p)
+    n = p if kind in ("equal", "pairs") else 3 * p
+    if kind in ("noise", "scaled"):
+        Y = rng.standard_normal((n, p)) * (1e9 if kind == "scaled" else 1.0)
+    else:
+        Y = np.zeros((n, p))
+        if kind != "zero":
+            Y[np.arange(p), np.arange(p)] = 1.0 if kind == "equal" else 1.0 + np.arange(p) // 2
+    Y = Y.astype(np.float32)
+    ids = np.arange(n, dtype=np.int32)
+    print(f"case p={p} {kind}", flush=True)
+    with Sbo(p, 2, 4, n) as g:
+        Qg, svg = g.init_base(Y, ids)
+        if kind == "zero":
+            assert (svg == 0).all() and np.abs(Qg @ Qg.T - np.eye(p)).max() <= ORTHO_TOL
+            return
+        _check_init_base(Y, ids, Qg, svg)
+
+
 # ------------------------------------------------------------------- new base
 @pytest.mark.parametrize("name,kw,n,R", [("tiny", dict(), 400, 3), ("patch8", dict(m=5000), 1800, 3),
                                          ("p256", dict(p=256, K=2, m=1200, s0=12, snr_db=25.0), 700, 2)])
