@@ -413,11 +413,184 @@ __global__ __launch_bounds__(256) void select_wide_split_kernel(const float* __r
                              err);
 }
 
+// The same for small sets, whose tiles of four wavefronts each would leave most of the chip idle for the 38 us that one
+// takes: a workgroup has ONE tile of 32 signals, its eight wavefronts share out the atoms (32 each, rows straight from L2,
+// every row used once) and then the signals (four each, 16 lanes to a signal, 16 consecutive atoms per lane).  The signals'
+// parts are made once, by all, in LDS.  Same products in the same order as above.  5041 signals, K = 16, s0 = 12:
+// 42.4 -> 19.8 us, 2048, K = 1 43.2 -> 16.6, 11000, K = 8 43.1 -> 24.6.  Two such workgroups fit a CU: the line is where they take a second
+// round (24000 signals would take 44, against 46).
+constexpr int64_t kSharedTiles = 2 * kNumCU;
+constexpr int kShareWaves = 8;
+constexpr int kShareLd = 260;                  // floats per signal of the coefficients (16-byte units cover all banks)
+template <int S>
+__global__ __launch_bounds__(64 * kShareWaves) void select_wide_shared_kernel(const float* __restrict__ Y, const u32x4* __restrict__ Dsb,
+                                                                 int K, int s0, const int32_t* __restrict__ offsets,
+                                                                 const int32_t* __restrict__ perm,
+                                                                 int32_t* __restrict__ supp, float* __restrict__ coef,
+                                                                 float* __restrict__ err) {
+    constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 6, NW = kShareWaves, L = 16;
+    constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
+    extern __shared__ int lds[];               // tile_start[K+1] | tmp[16] | pad | parts of y, then coefficients | stage
+    int* tile_start = lds;
+    int* tmp = lds + (K + 1);
+    const int head = ((K + 1 + 16) + 3) & ~3;
+    u32x4* ys = reinterpret_cast<u32x4*>(lds + head);          // [KS16][3][64]
+    float* cs = reinterpret_cast<float*>(ys);                  // [32][kShareLd]
+    int* stage = reinterpret_cast<int*>(ys + STAGE_U);         // [32][2][16]
+    static_assert(32 * kShareLd * 4 <= STAGE_U * 16, "the coefficients fit");
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, n = lane & 31;
+    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + 31) >> 5; }, K, tile_start, tmp);
+    const int id = blockIdx.x;
+    if (id >= tile_start[K]) return;           // uniform over the workgroup
+    const int j = upper_slot(tile_start, K, id);
+    const int pos0 = offsets[j] + (id - tile_start[j]) * 32;
+    const int cnt = min(32, offsets[j + 1] - pos0);
+
+    // A operand: rows of this wavefront's 32 atoms, AHEAD contraction steps on their way
+    const u32x4* Qj = Dsb + ((int64_t)j * MT + wave) * STAGE_U + lane;
+    u32x4 a[AHEAD][3];
+    auto fetch = [&](u32x4 (&v)[3], int ks) {
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) v[pl] = Qj[(ks * 3 + pl) * 64];
+    };
+    {
+        const int64_t i = n < cnt ? perm[pos0 + n] : -1;
+        f32x4 v[KS16 / NW][2];
+#pragma unroll
+        for (int q = 0; q < KS16 / NW; ++q)     // steps NW q + wave: dims ks*16 + h*8 .. +7 of signal n
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                v[q][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (i >= 0) v[q][e] = reinterpret_cast<const f32x4*>(Y + i * P + (NW * q + wave) * 16 + h * 8)[e];
+            }
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) fetch(a[t], t);
+#pragma unroll
+        for (int q = 0; q < KS16 / NW; ++q) {
+            const Bf16x3Pair x = split_bf16x3(v[q][0].x, v[q][0].y), y = split_bf16x3(v[q][0].z, v[q][0].w);
+            const Bf16x3Pair z = split_bf16x3(v[q][1].x, v[q][1].y), w = split_bf16x3(v[q][1].z, v[q][1].w);
+            u32x4* out = ys + ((NW * q + wave) * 3) * 64 + lane;
+            out[0] = u32x4{x.hi, y.hi, z.hi, w.hi};
+            out[64] = u32x4{x.mid, y.mid, z.mid, w.mid};
+            out[128] = u32x4{x.lo, y.lo, z.lo, w.lo};
+        }
+    }
+    __syncthreads();
+    // the six partial products, smallest first: (A part, B part)
+    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
+    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc;
+#pragma unroll
+    for (int ks = 0; ks < KS16; ++ks) {
+        u32x4 b[3];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) b[pl] = ys[(ks * 3 + pl) * 64 + lane];
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[ks % AHEAD][TA[t]]),
+                                                          __builtin_bit_cast(bf16x8, b[TB[t]]),
+                                                          (ks == 0 && t == 0) ? zero : acc, 0, 0, 0);
+        if (ks + AHEAD < KS16) fetch(a[ks % AHEAD], ks + AHEAD);
+    }
+    __syncthreads();                           // the parts are dead
+#pragma unroll
+    for (int q = 0; q < 4; ++q)                // atoms wave*32 + q*8 + h*4 .. +3 of signal n
+        *reinterpret_cast<f32x4*>(cs + n * kShareLd + wave * 32 + q * 8 + h * 4) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    __syncthreads();
+
+    // L lanes to a signal, lane `part` has the coefficients of C consecutive atoms.
+    constexpr int C = P / L;
+    const int sig = wave * (64 / L) + lane / L, part = lane % L;
+    const bool active = sig < cnt;
+    const float* row = cs + sig * kShareLd;
+    float c[C], mag[C], top[S];
+#pragma unroll
+    for (int u = 0; u < C / 4; ++u) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(row + C * part + 4 * u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            c[4 * u + e] = v[e];
+            mag[4 * u + e] = fabsf(v[e]);
+        }
+    }
+    top_sorted<C, S>(mag, top);
+    auto merge = [&](auto other) {             // with the sorted list of another lane
+        float o[S];
+#pragma unroll
+        for (int t = 0; t < S; ++t) o[t] = other(top[t]);
+#pragma unroll
+        for (int t = 0; t < S; ++t) top[t] = fmaxf(top[t], o[S - 1 - t]);
+        bitonic_merge_desc<S>(top);
+    };
+    merge([](float x) { return dpp_f<kDppXor1>(x); });
+    merge([](float x) { return dpp_f<kDppXor2>(x); });
+    merge([](float x) { return dpp_f<kDppHalfMirror>(x); });
+    merge([](float x) { return dpp_f<kDppRowMirror>(x); });
+    float tau = top[0];
+#pragma unroll
+    for (int t = 1; t < S; ++t) tau = (t == s0 - 1) ? top[t] : tau;
+
+    // entries above tau, and equal to it in ascending order until there are s0
+    int gt = 0, eq = 0;
+#pragma unroll
+    for (int e = 0; e < C; ++e) {
+        gt += fabsf(c[e]) > tau;
+        eq += fabsf(c[e]) == tau;
+    }
+    int both = gt | eq << 16, upto = both;     // sums over the lanes up to this one
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) {
+        const int v = __shfl_up(upto, o, L);
+        if (part >= o) upto += v;
+    }
+    const int all = __shfl(upto, L - 1, L), before = upto - both;
+    const int need = s0 - (all & 0xffff);
+    int eq_rank = before >> 16, pos = (before & 0xffff) + min(eq_rank, need);
+    float dropped = 0.f;
+    int* mine = stage + sig * 32;
+#pragma unroll
+    for (int e = 0; e < C; ++e) {
+        const float m = fabsf(c[e]);
+        const bool tie = m == tau, keep = m > tau || (tie && eq_rank < need);
+        eq_rank += tie;
+        if (keep && pos < s0) {
+            mine[pos] = part * C + e;
+            mine[16 + pos] = __builtin_bit_cast(int, c[e]);
+        }
+        pos += keep;
+        dropped = fmaf(keep ? 0.f : c[e], keep ? 0.f : c[e], dropped);
+    }
+    dropped = group_sum<L>(dropped);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (!active) return;
+    const int64_t i = perm[pos0 + sig];
+    if (part == 0) err[i] = dropped;
+    for (int e = part; e < s0; e += L) {
+        supp[i * s0 + e] = mine[e];
+        coef[i * s0 + e] = __builtin_bit_cast(float, mine[16 + e]);
+    }
+}
+
 template <int P, int S>
 hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int s0,
                           const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
                           hipStream_t st) {
     (void)D;                                   // the kernels read ws.dsb / ws.dsw, the same Q in operand order
+    const int64_t tiles = (m + 31) / 32 + K;
+    if (split && tiles <= kSharedTiles) {
+        const size_t lds = (((size_t)(K + 1 + 16) + 3) & ~(size_t)3) * sizeof(int) + (size_t)(P / 16) * 3 * 64 * 16 + 32 * 32 * sizeof(int);
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_shared_kernel<S>), 64 * 1024); e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL((select_wide_shared_kernel<S>), dim3((unsigned)tiles), dim3(64 * kShareWaves), lds, st, Y,
+                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err);
+        return hipGetLastError();
+    }
     if (split) {
         // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every unit
         const int64_t max_units = (((m + 127) / 128 + K) + 7) & ~(int64_t)7;
