@@ -50,8 +50,8 @@ typedef struct sbo_ctx sbo_ctx;   /* opaque: shapes, stream, device workspace */
 /* Stages timed by sbo_stage_ms, in this order. */
 enum {
     SBO_STAGE_ENERGY = 0,  /* projection onto all K blocks + top-s0 energy + block argmax */
-    SBO_STAGE_GROUP  = 1,  /* counting-sort bucketing of signals by block (0 where sbo_code leaves it to the select
-                              kernel: p <= 64, K <= 256 and m <= 1024) */
+    SBO_STAGE_GROUP  = 1,  /* counting-sort bucketing of signals by block (0 where sbo_code and sbo_iterate leave it
+                              to the select kernel: p <= 64, K <= 256 and m <= 1024) */
     SBO_STAGE_SELECT = 2,  /* support/coefficients/error in the winning block */
     SBO_STAGE_ACCUM  = 3,  /* P_j = Y_j X_j^T */
     SBO_STAGE_SVD    = 4,  /* Q_j = U V^T of each P_j (Algorithm 1, steps 6-7) */

@@ -17,13 +17,6 @@ namespace sbo {
 
 namespace {
 
-// What select_kernel needs to group the signals itself: the choices in, the results of the grouping out.
-struct GroupInSelect {
-    const int32_t* blk;
-    int m;
-    int32_t *counts, *offsets, *perm, *chunk_count;
-};
-
 // GROUP: the grouping of a small set (m <= kGroupInSelect) without a launch of its own.  Every workgroup sorts all
 // choices in its own LDS (the stable order of group.hip: each wavefront a quarter, counts, scan, scatter); the
 // first one also leaves counts, offsets and perm in memory and sets the histograms of the block choice back to zero.
@@ -35,7 +28,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
                                                      const int32_t* __restrict__ perm,
                                                      int32_t* __restrict__ supp,
                                                      float* __restrict__ coef,
-                                                     float* __restrict__ err, GroupInSelect g) {
+                                                     float* __restrict__ err, GroupInKernel g) {
     constexpr int KS = P / 2;
     constexpr int QN = P / 8;
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-row tiles per block
@@ -57,33 +50,10 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     if constexpr (GROUP) {                     // behind the tiles: off[K+1] | run[4][K] | list[m]
         int* off = reinterpret_cast<int*>(ctile_all + 4 * 32 * LDC);
         int *run = off + (K + 1), *list = run + 4 * K;
-        const int per = (g.m + 3) >> 2, beg = min(g.m, wave * per), end = min(g.m, beg + per);
-        int key[1];
-        load_keys(g.blk, beg, end, key);
-        for (int j = tid; j < 4 * K; j += 256) run[j] = 0;
-        __syncthreads();
-        for (int i = beg + lane; i < end; i += 64) {
-            const int b = i < beg + 64 ? key[0] : g.blk[i];
-            if ((unsigned)b < (unsigned)K) atomicAdd(&run[wave * K + b], 1);
-        }
-        __syncthreads();
-        wg_exclusive_scan4([&](int j) { return run[j] + run[K + j] + run[2 * K + j] + run[3 * K + j]; }, K, off, tmp);
-        for (int j = tid; j < K; j += 256) {   // counts of the wavefronts -> where each one's signals start
-            int at = off[j];
-            for (int w = 0; w < 4; ++w) {
-                const int v = run[w * K + j];
-                run[w * K + j] = at;
-                at += v;
-            }
-        }
-        __syncthreads();
-        scatter_chunk(g.blk, key, beg, end, K, run + wave * K, list);
+        group_in_lds<4>(g.blk, g.m, K, off, run, list, [&](auto f) { wg_exclusive_scan4(f, K, off, tmp); });
         if (blockIdx.x == 0) {
-            for (int j = tid; j <= K; j += 256) g.offsets[j] = off[j];
-            for (int j = tid; j < K; j += 256) g.counts[j] = off[j + 1] - off[j];
-            for (int e = tid; e < (g.m + 511) / 512 * K; e += 256) g.chunk_count[e] = 0;
-            __syncthreads();                   // list
-            for (int i = tid; i < off[K]; i += 256) g.perm[i] = list[i];
+            __syncthreads();
+            g.leave(K, off, list);
         }
         offsets = off;
         perm = list;
@@ -637,11 +607,11 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
     if (blk != nullptr) {
         lds += (5 * K + 1 + m) * sizeof(int);      // at most 60 KiB in all
         hipLaunchKernelGGL((select_kernel<P, S, true>), grid, dim3(256), lds, st, Y, D, K, s0, nullptr, nullptr, supp,
-                           coef, err, GroupInSelect{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count});
+                           coef, err, GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count});
         return hipGetLastError();
     }
     hipLaunchKernelGGL((select_kernel<P, S, false>), grid, dim3(256), lds, st, Y, D, K, s0, ws.offsets,
-                       ws.perm, supp, coef, err, GroupInSelect{});
+                       ws.perm, supp, coef, err, GroupInKernel{});
     return hipGetLastError();
 }
 

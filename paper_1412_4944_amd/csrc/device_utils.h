@@ -295,6 +295,54 @@ __device__ __forceinline__ void scatter_chunk(const int32_t* __restrict__ blk, i
     }
 }
 
+// The grouping of a small set by one workgroup of NW wavefronts, in LDS (the stable order of group.hip: each wavefront
+// its share of the signals, counts, scan, scatter): off[K+1], list[m], run[NW][K], tmp[16].  list is there after the
+// caller's next barrier.
+template <int NW, class Scan>
+__device__ __forceinline__ void group_in_lds(const int32_t* __restrict__ blk, int m, int K, int* off, int* run, int* list,
+                                             Scan scan) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (m + NW - 1) / NW, beg = min(m, wave * per), end = min(m, beg + per);
+    int key[1];
+    load_keys(blk, beg, end, key);
+    for (int j = tid; j < NW * K; j += 64 * NW) run[j] = 0;
+    __syncthreads();
+    for (int i = beg + lane; i < end; i += 64) {
+        const int b = i < beg + 64 ? key[0] : blk[i];
+        if ((unsigned)b < (unsigned)K) atomicAdd(&run[wave * K + b], 1);
+    }
+    __syncthreads();
+    scan([&](int j) {
+        int v = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += run[w * K + j];
+        return v;
+    });
+    for (int j = tid; j < K; j += 64 * NW) {   // counts of the wavefronts -> where each one's signals start
+        int at = off[j];
+        for (int w = 0; w < NW; ++w) {
+            const int v = run[w * K + j];
+            run[w * K + j] = at;
+            at += v;
+        }
+    }
+    __syncthreads();
+    scatter_chunk(blk, key, beg, end, K, run + wave * K, list);
+}
+// ... and what launch_group would have left in memory, by one workgroup of the launch (after a barrier).
+struct GroupInKernel {
+    const int32_t* blk;
+    int m;
+    int32_t *counts, *offsets, *perm, *chunk_count;
+    __device__ __forceinline__ void leave(int K, const int* off, const int* list) const {
+        const int tid = threadIdx.x, n = blockDim.x;
+        for (int j = tid; j <= K; j += n) offsets[j] = off[j];
+        for (int j = tid; j < K; j += n) counts[j] = off[j + 1] - off[j];
+        for (int e = tid; e < (m + 511) / 512 * K; e += n) chunk_count[e] = 0;
+        for (int i = tid; i < off[K]; i += n) perm[i] = list[i];
+    }
+};
+
 // Largest j in [0, n) with start[j] <= x, for a non-decreasing start[0..n].
 __host__ __device__ __forceinline__ int upper_slot(const int* start, int n, int x) {
     int lo = 0, hi = n;  // invariant: start[lo] <= x, answer in [lo, hi)

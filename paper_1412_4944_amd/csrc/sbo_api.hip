@@ -393,11 +393,13 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
         }
         rc = run_energy(c, Y, m, blk);
         if (rc) return rc;
-        rc = run_group(c, blk, m, true);
+        const bool in_select = group_in_select(c->p, c->K, m);
+        if (!in_select) rc = run_group(c, blk, m, true);
         if (rc) return rc;
         {
             StageTimer t(c, SBO_STAGE_SELECT);  // includes the per-piece accumulation
-            SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, c->stream));
+            SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, c->stream,
+                                        in_select ? blk : nullptr));
         }
         rc = run_polar_pieces(c, m, D, energy_ops(c), err, sqerr_per_iter ? sqerr_per_iter + it : nullptr);
         if (rc) return rc;

@@ -226,6 +226,27 @@ def test_code_groups_small_sets_in_the_select_kernel(p, K, m):
         np.testing.assert_array_equal(perm, op)
 
 
+@pytest.mark.parametrize("p,K,m", [(16, 4, 1024), (32, 3, 1024), (64, 2, 1024), (64, 5, 257), (16, 2, 1)])
+def test_iterate_groups_small_sets_in_the_select_kernel(p, K, m):
+    """sbo_iterate on both sides of the rule (m <= 1024): filled up with zero signals, which go to the end of block 0 and
+    add nothing, a set is grouped by a launch; codes and dictionary have to be the same, and what either leaves behind
+    is what the other needs."""
+    pr = synth.generate(synth.custom(f"small_it_p{p}", p=p, K=K, m=m, s0=4, snr_db=20.0))
+    full = np.concatenate([pr.Y, np.zeros((1025 - m, p), np.float32)])
+    with Sbo(p, K, 4, 1025) as g:
+        for _ in range(2):
+            a = g.iterate(pr.Y, pr.D_init, 3)
+            b = g.iterate(full, pr.D_init, 3)
+            np.testing.assert_array_equal(a[1], b[1][:m])
+            np.testing.assert_array_equal(a[2], b[2][:m])
+            np.testing.assert_allclose(a[3], b[3][:m], atol=2e-5 * np.abs(pr.Y).max())
+            if m > 100:                                    # (every block of full rank)
+                np.testing.assert_allclose(a[0], b[0], atol=2e-5)
+            np.testing.assert_allclose(a[5], b[5], rtol=1e-5)
+            counts, offsets, perm = g.group(a[1])
+            np.testing.assert_array_equal(perm, orc.o_group(a[1], K)[2])
+
+
 UPDATE_CASES = [
     ("tiny", dict()),
     ("patch8", dict(m=4096 + 77)),
