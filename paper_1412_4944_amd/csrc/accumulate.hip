@@ -8,7 +8,7 @@
 // No floating-point atomics are used anywhere.
 //
 // The piece kernel (p <= 64: one workgroup of 8 wavefronts per piece, as few pieces as keep
-// every CU busy in one round (accum_tall_piece), each wavefront keeping the operands of several
+// every CU busy in one round (accum_piece), each wavefront keeping the operands of several
 // steps in flight) forms the product on the matrix cores: with atoms on the M axis, the
 // dimensions on the N axis and the signal index as the contraction index, one fp32 MFMA
 // 32x32x2 adds two signals to a 32x32 tile of P_j.  Its A operand is the dense x_i, which
@@ -44,14 +44,14 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
     constexpr int EPS = S0 <= 1 ? 1 : S0 <= 2 ? 2 : S0 <= 4 ? 4 : S0 <= 8 ? 8 : 16;
     constexpr int SPI = 64 / EPS;              // signals covered by one such fetch
     constexpr int NI = (SPS + SPI - 1) / SPI;  // fetches per step
-    // piece_start[K+1] | tmp[16] | pad | ids[kTallMaxPiece] | buf: xd[NW][SPS][64] while the
+    // piece_start[K+1] | tmp[16] | pad | ids[kMaxPiece] | buf: xd[NW][SPS][64] while the
     // piece is walked, then [NW/2][ACC_F4] 16-byte units while the wavefronts are summed
     extern __shared__ int lds[];
     int* piece_start = lds;
     int* tmp = lds + (K + 1);
     const int head = ((K + 1 + 16) + 3) & ~3;
     int* ids = lds + head;
-    float* buf = reinterpret_cast<float*>(ids + kTallMaxPiece);
+    float* buf = reinterpret_cast<float*>(ids + kMaxPiece);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
 
     const int j = upper_slot(piece_start, K, id);
     const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kTallMaxPiece (launcher)
+    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
 
     for (int q = tid; q < cnt; q += 64 * NW) ids[q] = perm[pos0 + q];
     __syncthreads();
@@ -230,7 +230,6 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
 // wavefront densifies only its own 64 atoms of x_i; the wave results are disjoint slabs of
 // the piece's partial matrix, so no cross-wave reduction is needed.
 constexpr int kWidePairs = 4;
-constexpr int kWideMaxPiece = 4096;            // accum_piece() never returns more
 
 template <int S0, bool GRAM>
 __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict__ Y, int K,
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
                                                          float* __restrict__ partial) {
     constexpr int P = 256;
     constexpr int NTL = 8;                     // 32-wide tiles along the dimensions
-    // piece_start[K+1] | tmp[16] | xd[4][kWidePairs][2][64] | ids[kWideMaxPiece]
+    // piece_start[K+1] | tmp[16] | xd[4][kWidePairs][2][64] | ids[kMaxPiece]
     extern __shared__ int lds[];
     int* piece_start = lds;
     int* tmp = lds + (K + 1);
@@ -261,7 +260,7 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
 
     const int j = upper_slot(piece_start, K, id);
     const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kWideMaxPiece (launcher)
+    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
     for (int q = tid; q < cnt; q += 256) ids[q] = perm[pos0 + q];
     __syncthreads();
 
@@ -391,13 +390,13 @@ __global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __re
     constexpr int XPLANE = (P + 1) * 32;       // bytes of one part of the x tile (+ the extra row)
     constexpr int SET_B = 3 * YPLANE + 3 * XPLANE;
     static_assert(G * S0 <= 256, "one thread per (signal, entry)");
-    // piece_start[K+1] | tmp[16] | pad | ids[kWideMaxPiece] | two sets of (y tile, x tile)
+    // piece_start[K+1] | tmp[16] | pad | ids[kMaxPiece] | two sets of (y tile, x tile)
     extern __shared__ int lds[];
     int* piece_start = lds;
     int* tmp = lds + (K + 1);
     const int head = ((K + 1 + 16) + 3) & ~3;
     int* ids = lds + head;
-    unsigned char* sets = reinterpret_cast<unsigned char*>(ids + kWideMaxPiece);
+    unsigned char* sets = reinterpret_cast<unsigned char*>(ids + kMaxPiece);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -410,7 +409,7 @@ __global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __re
 
     const int j = upper_slot(piece_start, K, id);
     const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kWideMaxPiece (launcher)
+    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
     for (int q = tid; q < cnt; q += 256) ids[q] = perm[pos0 + q];
     __syncthreads();
 
@@ -588,18 +587,19 @@ template <int P, int S0>
 hipError_t launch_ps(int K, const float* Y, int64_t m, const int32_t* supp, const float* coef,
                      const Workspace& ws, float* M, hipStream_t st) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    const int piece = accum_tall_piece(m, K);
-    const int max_pieces = (int)((m + piece - 1) / piece) + K;
+    const int piece = accum_piece(m, K, P);
+    const int max_pieces = accum_max_pieces(m, K, P);
     const size_t head = ((size_t)(K + 1 + 16) + 3) & ~(size_t)3;
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
-    const size_t lds1 = (head + kTallMaxPiece + (walk > xch ? walk : xch)) * 4;
+    const size_t lds1 = (head + kMaxPiece + (walk > xch ? walk : xch)) * 4;
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, S0, false>),
                                          144 * 1024);
         e != hipSuccess)
         return e;
     hipLaunchKernelGGL((accum_piece_kernel<P, S0, false>), dim3(max_pieces), dim3(64 * kTallWaves), lds1, st,
                        Y, K, piece, ws.offsets, ws.perm, supp, coef, ws.partial);
+    if (M == nullptr) return hipGetLastError();
     const size_t lds2 = (K + 1 + 16) * sizeof(int);
     hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256), lds2, st,
                        K, piece, ws.offsets, ws.partial, M, nullptr, (int64_t)0, nullptr, nullptr, nullptr, 0);
@@ -612,10 +612,10 @@ hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, 
     constexpr int P = 256;
     const int piece = accum_piece(m, K, P);
     const int max_pieces = accum_max_pieces(m, K, P);
-    const size_t lds1 = (K + 1 + 16 + kWideMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
+    const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
     if (split) {
         const int head = ((K + 1 + 16) + 3) & ~3;
-        const size_t lds = (size_t)(head + kWideMaxPiece) * sizeof(int) +
+        const size_t lds = (size_t)(head + kMaxPiece) * sizeof(int) +
                            (size_t)2 * (3 * P * 32 + 3 * (P + 1) * 32);
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_wide_split_kernel<S0>), lds);
             e != hipSuccess)
@@ -665,12 +665,12 @@ template <int P>
 hipError_t launch_gram_p(int K, const float* Y, int64_t n, const Workspace& ws, float* G,
                          hipStream_t st) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    const int piece = accum_tall_piece(n, K);
-    const int max_pieces = (int)((n + piece - 1) / piece) + K;
+    const int piece = accum_piece(n, K, P);
+    const int max_pieces = accum_max_pieces(n, K, P);
     const size_t head = ((size_t)(K + 1 + 16) + 3) & ~(size_t)3;
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
-    const size_t lds1 = (head + kTallMaxPiece + (walk > xch ? walk : xch)) * 4;
+    const size_t lds1 = (head + kMaxPiece + (walk > xch ? walk : xch)) * 4;
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, 1, true>),
                                          144 * 1024);
         e != hipSuccess)
@@ -694,8 +694,8 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
         case 256: {
             constexpr int P = 256;
             const int piece = accum_piece(n, K, P);
-            const int max_pieces = (int)((n + piece - 1) / piece) + K;
-            const size_t lds1 = (K + 1 + 16 + kWideMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
+            const int max_pieces = accum_max_pieces(n, K, P);
+            const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
             hipLaunchKernelGGL((accum_wide_kernel<1, true>), dim3(max_pieces), dim3(256), lds1, st, Y, K,
                                piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial);
             hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256),
@@ -733,7 +733,6 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
 
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
                              const float* coef, const Workspace& ws, float* M, hipStream_t st) {
-    if (M == nullptr && p != 256) return hipErrorInvalidValue;
     switch (p) {
         case 16: return launch_p<16>(K, s0, Y, m, supp, coef, ws, M, st);
         case 32: return launch_p<32>(K, s0, Y, m, supp, coef, ws, M, st);

@@ -13,7 +13,7 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static int max_chunks() { return 1025; }
 
-// At least what accum_piece() and accum_tall_piece() make of any m <= m_max and at most K blocks.
+// At least what accum_piece() makes of any m <= m_max and at most K blocks.
 static int64_t max_pieces_bound(int64_t m_max, int K, int p) {
     const int64_t smallest = (m_max + kMinPiece - 1) / kMinPiece;
     if (p <= 64) return smallest + K + 1;
@@ -185,7 +185,7 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
     return SBO_OK;
 }
 
-// The SVD update from the piece results of launch_select_accum (p <= 64) or launch_accumulate (p = 256);
+// The SVD update from the piece results of launch_select_accum or launch_accumulate;
 // err / sq_out: also the squared-error total of the coding pass.  One launch on the default path;
 // with the Jacobi SVD for every block the pieces are summed by their own launch first.
 static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, const float* err, double* sq_out,
@@ -206,18 +206,14 @@ static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, cons
 }
 
 // Accumulate + SVD of K orthobases (-1: all) from codes, for signals already grouped in the workspace.
-// p <= 64 sums the pieces of the stand-alone accumulation (which cuts them its own way) by a launch.
 static int run_update_grouped(sbo_ctx* c, const float* Y, int64_t m, const int32_t* supp, const float* coef, float* D,
                               int write_ops = 0, const float* err = nullptr, double* sq_out = nullptr, int K = -1) {
     if (K < 0) K = c->K;
     {
         StageTimer t(c, SBO_STAGE_ACCUM);
-        SBO_HIP(launch_accumulate(c->p, K, c->s0, Y, m, supp, coef, c->ws, c->p > 64 ? nullptr : c->ws.M, c->stream));
+        SBO_HIP(launch_accumulate(c->p, K, c->s0, Y, m, supp, coef, c->ws, nullptr, c->stream));
     }
-    if (c->p > 64) return run_polar_pieces(c, m, D, write_ops, err, sq_out, K);
-    StageTimer t(c, SBO_STAGE_SVD);
-    SBO_HIP(launch_polar(c->p, K, c->ws.M, c->ws.counts, D, c->ws, c->svd_method, nullptr, 0, c->stream));
-    return SBO_OK;
+    return run_polar_pieces(c, m, D, write_ops, err, sq_out, K);
 }
 
 }  // namespace sbo

@@ -50,17 +50,6 @@ inline int accum_piece(int64_t m, int K, int p) {
     if (c > kMaxPiece) c = kMaxPiece;
     return (int)c;
 }
-// Piece size of the stand-alone accumulation for p <= 64, whose workgroups fill a whole CU:
-// as few pieces as keep every CU busy in a single round (pieces <= CUs where K allows), capped
-// because the kernel keeps a piece's signal ids in LDS.
-constexpr int kTallMaxPiece = 4096;
-inline int accum_tall_piece(int64_t m, int K) {
-    const int target = K < kNumCU / 2 ? kNumCU - K : kNumCU / 2;
-    int64_t c = (m + target - 1) / target;
-    c = ((c + 63) / 64) * 64;
-    if (c > kTallMaxPiece) c = kTallMaxPiece;
-    return (int)(c < 64 ? 64 : c);
-}
 inline int accum_max_pieces(int64_t m, int K, int p) {
     int piece = accum_piece(m, K, p);
     return (int)((m + piece - 1) / piece) + K;
@@ -231,7 +220,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
                          bool split, hipStream_t st, const int32_t* blk = nullptr);
 
-// M == nullptr (p = 256): the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
+// M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
                              const float* coef, const Workspace& ws, float* M, hipStream_t st);
 
@@ -280,7 +269,7 @@ hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, c
                            int piece, const int32_t* counts, float* D, const DictOps& ops,
                            int32_t* fallback, int32_t* iters, const SqTotalArgs& sq, LdsRaised* raised,
                            hipStream_t st);
-// The SVD update straight from the piece results (launch_select_accum, p = 256: launch_accumulate
+// The SVD update straight from the piece results (launch_select_accum, or launch_accumulate
 // without its sum; Newton-Schulz path): what launch_accum_reduce + launch_polar do, in one launch.
 // err / sq_out as for launch_accum_reduce.
 hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Workspace& ws, int write_ops,
