@@ -902,6 +902,23 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
     }
 }
 
+hipError_t launch_energy_direct(int p, int K, int s0, int arith, const float* Y, int64_t m, const float* D,
+                                const Workspace& ws, hipStream_t st) {
+    if (!choose_in_select(p, K, s0, m, arith)) return hipErrorInvalidValue;
+    ScrArgs a = {};
+    a.Y = Y;
+    a.m = (int)m;
+    a.K = K;
+    a.s0 = s0;
+    a.D = D;
+    a.E = ws.part_E;
+    switch (p) {
+        case 16: return launch_direct_16(a, arith, st);
+        case 32: return launch_direct_32(a, arith, st);
+        default: return launch_direct_64(a, arith, st);
+    }
+}
+
 hipError_t launch_energy(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws, int32_t* blk,
                          int32_t* chunk_count, hipStream_t st) {
     if (screen_applies(p, K, s0, arith)) return launch_energy_screen(p, K, s0, arith, Y, m, ws, blk, chunk_count, st);

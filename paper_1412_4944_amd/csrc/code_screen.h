@@ -103,8 +103,9 @@ struct ExactRow {
 };
 
 // Kept energy of signal i (-1: none; y: its row) in block j in the exact arithmetic, up to the signal's scale.
-template <int P, int S, int SX, int ARITH>
-__device__ float exact_energy(const ScrArgs& g, const ExactRow<P, ARITH>& y, int64_t i, int j, int lane) {
+// DIRECT: the operands are made from the rows of D here (p <= 64), bit by bit what dict_parts_kernel makes of them.
+template <int P, int S, int SX, int ARITH, bool DIRECT = false>
+__device__ __forceinline__ float exact_energy(const ScrArgs& g, const ExactRow<P, ARITH>& y, int64_t i, int j, int lane) {
     constexpr int KS16 = P / 16, QN = P / 8;
     constexpr int NPL = ARITH == 3 ? 2 : 3;
     constexpr int NRT = P >= 32 ? P / 32 : 1;               // 32-row tiles of a block
@@ -118,6 +119,11 @@ __device__ float exact_energy(const ScrArgs& g, const ExactRow<P, ARITH>& y, int
         else return i >= 0 ? *reinterpret_cast<const f32x4*>(yrow + ks * 16 + h * 8 + 4 * e) : f32x4{0.f, 0.f, 0.f, 0.f};
     };
 
+    // dims 4 d4 .. +3 of this lane's row of tile mt (DIRECT)
+    auto row = [&](int mt, int d4) {
+        const int r = (tile0 + mt) * 32 + (lane & 31);
+        return r < g.K * P ? *reinterpret_cast<const f32x4*>(g.D + (int64_t)r * P + 4 * d4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
     if constexpr (ARITH == 0) {
         static_assert(P <= 64, "p = 256 in fp32 is not screened");
         const f32x4* D = reinterpret_cast<const f32x4*>(g.Dx) + (int64_t)tile0 * (QN * 64) + lane;
@@ -125,7 +131,7 @@ __device__ float exact_energy(const ScrArgs& g, const ExactRow<P, ARITH>& y, int
 #pragma unroll
         for (int q = 0; q < QN; ++q)
 #pragma unroll
-            for (int mt = 0; mt < NRT; ++mt) a[q][mt] = D[(mt * QN + q) * 64];
+            for (int mt = 0; mt < NRT; ++mt) a[q][mt] = DIRECT ? row(mt, h * QN + q) : D[(mt * QN + q) * 64];
         f32x16 acc[NRT];
 #pragma unroll
         for (int q = 0; q < QN; ++q) {
@@ -145,7 +151,33 @@ __device__ float exact_energy(const ScrArgs& g, const ExactRow<P, ARITH>& y, int
         const u32x4* D = reinterpret_cast<const u32x4*>(g.Dx) + (int64_t)tile0 * (KS16 * NPL * 64) + lane;
         constexpr bool AHEAD = P <= 64;        // the dictionary rows on their way before anything else
         u32x4 a_all[AHEAD ? KS16 : 1][AHEAD ? NRT : 1][NPL];
-        if constexpr (AHEAD) {
+        if constexpr (AHEAD && DIRECT) {
+            f32x4 raw[KS16][NRT][2];
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < NRT; ++mt)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) raw[ks][mt][e] = row(mt, ks * 4 + h * 2 + e);
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < NRT; ++mt) {
+                    const f32x4 v0 = raw[ks][mt][0], v1 = raw[ks][mt][1];
+                    if constexpr (ARITH == 3) {
+                        float q2 = 0.f, r2 = 0.f;
+                        const F16x2Quad a = split_f16x2_dict(v0, q2, r2), b = split_f16x2_dict(v1, q2, r2);
+                        a_all[ks][mt][0] = u32x4{a.hi.x, a.hi.y, b.hi.x, b.hi.y};
+                        a_all[ks][mt][1] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
+                    } else {
+                        const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
+                        const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
+                        a_all[ks][mt][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+                        a_all[ks][mt][1] = u32x4{a.mid, b.mid, c.mid, d.mid};
+                        a_all[ks][mt][NPL - 1] = u32x4{a.lo, b.lo, c.lo, d.lo};
+                    }
+                }
+        } else if constexpr (AHEAD) {
 #pragma unroll
             for (int ks = 0; ks < KS16; ++ks)
 #pragma unroll
@@ -813,6 +845,20 @@ hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t 
     return hipGetLastError();
 }
 
+// Small sets (choose_in_select): no screening.  What a call on a few hundred signals waits for is launches and trips to
+// memory, not products, so a wavefront takes one block for 32 signals at full precision, with operands made from D itself
+// (no launch for them), and leaves the energies; the select kernel compares them.  225 signals, K = 32, p = 64: operand
+// orders 2.8 us + screened choice 11.2 -> 4.5, and 2 us in the select kernel.
+template <int P, int S, int SX, int ARITH>
+__global__ __launch_bounds__(64) void energy_direct_kernel(ScrArgs g) {
+    const int lane = threadIdx.x, h = lane >> 5, i = (int)blockIdx.x * 32 + (lane & 31), j = (int)blockIdx.y;
+    const int64_t id = i < g.m ? i : -1;
+    ExactRow<P, ARITH> y;
+    y.load(g, id, h);
+    const float e = exact_energy<P, S, SX, ARITH, true>(g, y, id, j, lane);
+    if (h == 0 && i < g.m) g.E[(int64_t)j * g.m + i] = e;
+}
+
 template <int P, int S, int SX, int ARITH>
 hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
     const bool half = P <= 64 && scr_lds_bytes<P, false, kScrWaves / 2>(a.K) <= kScrLdsMax / 2 && screen_by_256(a.m);
@@ -836,6 +882,28 @@ hipError_t launch_s(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t 
     if constexpr (P <= 64) {
         if (arith == SBO_ARITH_F32) return launch_a<P, S, SX, 0>(a, raised, st);
         return launch_a<P, S, SX, 1>(a, raised, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int P>
+hipError_t launch_direct_p(const ScrArgs& a, int arith, hipStream_t st) {
+    const dim3 grid((unsigned)(a.m + 31) / 32, (unsigned)a.K);
+    switch (a.s0) {
+#define SBO_CASE(N) \
+    case N:         \
+        if constexpr (screen_applies(P, 1, N, SBO_ARITH_F16X2)) { \
+            constexpr int S = pow2_at_least(N); \
+            if (arith == SBO_ARITH_F16X2) hipLaunchKernelGGL((energy_direct_kernel<P, S, N, 3>), grid, dim3(64), 0, st, a); \
+            else if (arith == SBO_ARITH_F32) hipLaunchKernelGGL((energy_direct_kernel<P, S, N, 0>), grid, dim3(64), 0, st, a); \
+            else hipLaunchKernelGGL((energy_direct_kernel<P, S, N, 1>), grid, dim3(64), 0, st, a); \
+            return hipGetLastError(); \
+        } \
+        break;
+        SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
+        SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
+#undef SBO_CASE
+        default: break;
     }
     return hipErrorInvalidValue;
 }

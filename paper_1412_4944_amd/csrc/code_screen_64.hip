@@ -7,4 +7,6 @@ hipError_t launch_screen_64(const ScrArgs& a, int arith, LdsRaised* raised, hipS
     return launch_p<64>(a, arith, raised, st);
 }
 
+hipError_t launch_direct_64(const ScrArgs& a, int arith, hipStream_t st) { return launch_direct_p<64>(a, arith, st); }
+
 }  // namespace sbo

@@ -50,6 +50,11 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     if constexpr (GROUP) {                     // behind the tiles: off[K+1] | run[4][K] | list[m]
         int* off = reinterpret_cast<int*>(ctile_all + 4 * 32 * LDC);
         int *run = off + (K + 1), *list = run + 4 * K;
+        if (g.E != nullptr) {                  // uniform
+            int* choice = list + g.m;
+            g.choose<256>(K, choice);
+            g.blk = choice;
+        }
         group_in_lds<4>(g.blk, g.m, K, off, run, list, [&](auto f) { wg_exclusive_scan4(f, K, off, tmp); });
         if (blockIdx.x == 0) {
             __syncthreads();
@@ -599,15 +604,16 @@ hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int 
 
 template <int P, int S>
 hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws,
-                     int32_t* supp, float* coef, float* err, const int32_t* blk, hipStream_t st) {
+                     int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, hipStream_t st) {
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
     size_t lds = ((((K + 1 + 16) + 3) & ~3) + 4 * kSelectStageWords) * sizeof(int) +
                  4 * 32 * (P + 1) * sizeof(float);
     if (blk != nullptr) {
-        lds += (5 * K + 1 + m) * sizeof(int);      // at most 60 KiB in all
+        lds += (5 * K + 1 + (choose ? 2 : 1) * m) * sizeof(int);       // at most 60 KiB in all (choose: K <= 64)
         hipLaunchKernelGGL((select_kernel<P, S, true>), grid, dim3(256), lds, st, Y, D, K, s0, nullptr, nullptr, supp,
-                           coef, err, GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count});
+                           coef, err,
+                           GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count, choose ? ws.part_E : nullptr, blk});
         return hipGetLastError();
     }
     hipLaunchKernelGGL((select_kernel<P, S, false>), grid, dim3(256), lds, st, Y, D, K, s0, ws.offsets,
@@ -617,29 +623,29 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
 
 template <int P>
 hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
-                    int32_t* supp, float* coef, float* err, const int32_t* blk, hipStream_t st) {
-    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
-    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
-    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
-    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
-    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, blk, st);
+                    int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, hipStream_t st) {
+    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
+    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
+    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
+    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
+    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
 }
 
 }  // namespace
 
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, const int32_t* blk) {
-    if (blk != nullptr && !group_in_select(p, K, m)) return hipErrorInvalidValue;
+                         bool split, hipStream_t st, int32_t* blk, bool choose) {
+    if (blk != nullptr ? !group_in_select(p, K, m) : choose) return hipErrorInvalidValue;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
         hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, st)
                              : launch_dict_swizzle(p, K, D, ws.dsw, st);
         if (e != hipSuccess) return e;
     }
     switch (p) {
-        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, st);
-        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, st);
-        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, st);
+        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
+        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
+        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
         case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, st);
         default: return hipErrorInvalidValue;
     }

@@ -334,6 +334,30 @@ struct GroupInKernel {
     const int32_t* blk;
     int m;
     int32_t *counts, *offsets, *perm, *chunk_count;
+    const float* E = nullptr;                  // [K][m] energies to choose from first
+    int32_t* chosen = nullptr;                 // where the choice goes
+    // The block of largest energy of every signal (the lowest on a tie) -> choice[m] in LDS; N threads.
+    template <int N>
+    __device__ __forceinline__ void choose(int K, int* choice) const {
+        constexpr int A = 16;                  // energies on their way at a time
+        for (int i = threadIdx.x; i < m; i += N) {
+            float top = -1.f;
+            int best = 0;
+            for (int j0 = 0; j0 < K; j0 += A) {
+                float e[A];
+#pragma unroll
+                for (int a = 0; a < A; ++a) e[a] = j0 + a < K ? E[(int64_t)(j0 + a) * m + i] : -1.f;
+#pragma unroll
+                for (int a = 0; a < A; ++a) {
+                    best = e[a] > top ? j0 + a : best;
+                    top = fmaxf(top, e[a]);
+                }
+            }
+            choice[i] = best;
+            if (blockIdx.x == 0) chosen[i] = best;
+        }
+        __syncthreads();
+    }
     __device__ __forceinline__ void leave(int K, const int* off, const int* list) const {
         const int tid = threadIdx.x, n = blockDim.x;
         for (int j = tid; j <= K; j += n) offsets[j] = off[j];

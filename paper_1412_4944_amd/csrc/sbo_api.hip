@@ -42,7 +42,8 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.dsh = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dnorm = (float2*)take((size_t)K * (p / 16) * 8);
     const size_t split_m = (size_t)(m_max < kEnergySplitSignals ? m_max : kEnergySplitSignals);
-    w.part_E = (float*)take((size_t)kEnergySplitRows * split_m * 4);
+    const size_t direct = (size_t)(K < kDirectMaxK ? K : kDirectMaxK) * (size_t)(m_max < kDirectMaxSignals ? m_max : kDirectMaxSignals);
+    w.part_E = (float*)take((direct > kEnergySplitRows * split_m ? direct : kEnergySplitRows * split_m) * 4);
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
     w.partial = (float*)take((size_t)max_pieces_bound(m_max, K, p) * p * p * 4);
     w.M = (float*)take((size_t)K * p * p * 4);
@@ -170,17 +171,24 @@ static int run_energy(sbo_ctx* c, const float* Y, int64_t m, int32_t* blk) {
 // have_ops: the workspace holds D in those orders already.
 static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32_t* blk,
                     int32_t* supp, float* coef, float* err, bool have_ops = false) {
-    int rc = have_ops ? SBO_OK : run_swizzle(c, D);
-    if (rc) return rc;
-    rc = run_energy(c, Y, m, blk);
-    if (rc) return rc;
+    int rc = SBO_OK;
+    const bool direct = choose_in_select(c->p, c->K, c->s0, m, choice_arith(c));
+    if (direct) {
+        StageTimer t(c, SBO_STAGE_ENERGY);
+        SBO_HIP(launch_energy_direct(c->p, c->K, c->s0, choice_arith(c), Y, m, D, c->ws, c->stream));
+    } else {
+        if (!have_ops) rc = run_swizzle(c, D);
+        if (rc) return rc;
+        rc = run_energy(c, Y, m, blk);
+        if (rc) return rc;
+    }
     const bool in_select = group_in_select(c->p, c->K, m);
     if (!in_select) rc = run_group(c, blk, m, true);   // the energy kernel left the chunk histograms
     if (rc) return rc;
     {
         StageTimer t(c, SBO_STAGE_SELECT);         // p = 256 reads the operand order run_swizzle wrote
         SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, true, use_split(c), c->stream,
-                              in_select ? blk : nullptr));
+                              in_select ? blk : nullptr, direct));
     }
     return SBO_OK;
 }

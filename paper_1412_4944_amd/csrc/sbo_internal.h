@@ -91,7 +91,8 @@ struct Workspace {
     unsigned* dsb;         // the same rows as three bf16 parts (6 bytes per entry)
     unsigned* dsh;         // the same rows as two fp16 parts (4 bytes per entry)
     float2* dnorm;         // [K*p/16] per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
-    float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row
+    float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row; or
+                           // [<= kDirectMaxK][<= kDirectMaxSignals]: energies of small sets
     int32_t* part_j;       // same shape: its block
     // accumulation
     float* partial;        // [max_pieces][p][p]
@@ -189,6 +190,14 @@ constexpr bool screen_shared(int64_t m, bool p64_by_256) {
     return p64_by_256 ? 5 * m < 2 * round : 20 * m < 13 * rounds * round;
 }
 
+// Which calls of sbo_code leave the choice among full-precision energies to the select kernel (energy_direct_kernel): those
+// whose grouping is left to it, with few blocks, since every one of its workgroups compares the energies of all signals.
+constexpr int kDirectMaxK = 64;
+constexpr int64_t kDirectMaxSignals = 1024;    // (group_in_select allows no more)
+inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
+    return p <= 64 && K <= kDirectMaxK && m <= kDirectMaxSignals && screen_applies(p, K, s0, arith);
+}
+
 // dsw = D in the fp32 operand order of the coding kernels.
 hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStream_t st);
 // dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
@@ -200,6 +209,10 @@ hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsign
 // first step of launch_group; the array must be zero on entry, launch_group leaves it so).
 hipError_t launch_energy(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws, int32_t* blk,
                          int32_t* chunk_count, hipStream_t st);
+
+// Small sets (choose_in_select): ws.part_E[j * m + i] = the energy of signal i in block j, for launch_select.
+hipError_t launch_energy_direct(int p, int K, int s0, int arith, const float* Y, int64_t m, const float* D,
+                                const Workspace& ws, hipStream_t st);
 
 hipError_t launch_group(int K, const int32_t* blk, int64_t m, const Workspace& ws, bool have_hist,
                         hipStream_t st);
@@ -215,10 +228,11 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // blk: nullptr, or the choices of the signals, which the kernel then groups itself (where group_in_select says so;
 // launch_group is not called, and what it leaves in ws is left there too).  The line: every workgroup sorts the whole
 // set, so it has to be small, and its lists have to fit 64 KiB of LDS beside the tiles.
+// choose: blk is written first, from the energies in ws.part_E (launch_energy_direct).
 inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, const int32_t* blk = nullptr);
+                         bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false);
 
 // M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,

@@ -17,6 +17,9 @@ struct ScrArgs {
     int32_t* blk;
     int32_t* chunk_count;      // or nullptr
     int chunk;
+    // energy_direct_kernel only
+    const float* D = nullptr;
+    float* E = nullptr;        // [K][m]
 };
 
 // One translation unit per p (code_screen_<p>.hip): the kernels are many.
@@ -24,5 +27,9 @@ hipError_t launch_screen_16(const ScrArgs& a, int arith, LdsRaised* raised, hipS
 hipError_t launch_screen_32(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
 hipError_t launch_screen_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
 hipError_t launch_screen_256(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+// The full-precision energies of every (signal, block), from D itself.
+hipError_t launch_direct_16(const ScrArgs& a, int arith, hipStream_t st);
+hipError_t launch_direct_32(const ScrArgs& a, int arith, hipStream_t st);
+hipError_t launch_direct_64(const ScrArgs& a, int arith, hipStream_t st);
 
 }  // namespace sbo

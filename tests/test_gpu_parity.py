@@ -226,6 +226,32 @@ def test_code_groups_small_sets_in_the_select_kernel(p, K, m):
         np.testing.assert_array_equal(perm, op)
 
 
+@pytest.mark.parametrize("p,K,m,s0", [(64, 64, 1024, 8), (64, 65, 1024, 8), (64, 32, 225, 8), (64, 3, 33, 16), (32, 64, 1000, 1),
+                                      (32, 7, 500, 16), (16, 63, 1024, 8), (16, 5, 31, 3), (16, 1, 1, 2)])
+@pytest.mark.parametrize("arith", ARITH)
+def test_code_small_sets_without_screening(p, K, m, s0, arith):
+    """Small sets (m <= 1024, K <= 64) compare full-precision energies in the select kernel; in a larger set the same
+    signals go through the screened choice.  Blocks and codes are the same, bit by bit; zero signals, ties between equal
+    blocks and a near-random dictionary among them."""
+    rng = np.random.default_rng(59 + p + K)
+    pr = synth.generate(synth.custom(f"direct_p{p}", p=p, K=K, m=m, s0=s0, snr_db=15.0))
+    Y, D = pr.Y.copy(), (pr.D_planted if K % 2 else pr.D_init).astype(np.float32)
+    if K > 4:
+        D[K - 1] = D[2]                                    # ties go to the lower block
+    Y[m // 2] = 0.0
+    Y[m // 3] *= 1e-20                                     # (squares underflow in fp32: not for the oracle)
+    full = np.concatenate([Y, rng.standard_normal((1025 - m, p)).astype(np.float32)])
+    print(f"case {arith}: p={p} K={K} m={m} s0={s0}", flush=True)
+    with Sbo(p, K, s0, 1025, arith=arith) as g:
+        for _ in range(2):
+            a = g.code(Y, D)
+            b = g.code(full, D)
+            for x, y in zip(a, b):
+                np.testing.assert_array_equal(x, y[:m])
+    keep = np.arange(m) != (m // 3 if m > 1 else -1)
+    compare_code(Y[keep], D, s0, orc.o_code(Y[keep], D, s0), tuple(x[keep] for x in a), max_exempt_frac=1.0)
+
+
 @pytest.mark.parametrize("p,K,m", [(16, 4, 1024), (32, 3, 1024), (64, 2, 1024), (64, 5, 257), (16, 2, 1)])
 def test_iterate_groups_small_sets_in_the_select_kernel(p, K, m):
     """sbo_iterate on both sides of the rule (m <= 1024): filled up with zero signals, which go to the end of block 0 and
