@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
                                                          const int32_t* __restrict__ perm,
                                                          const int32_t* __restrict__ supp,
                                                          const float* __restrict__ coef,
-                                                         float* __restrict__ partial) {
+                                                         float* __restrict__ partial, int by_pos) {
     constexpr int P = 256;
     constexpr int NTL = 8;                     // 32-wide tiles along the dimensions
     // piece_start[K+1] | tmp[16] | xd[4][kWidePairs][2][64] | ids[kMaxPiece]
@@ -292,8 +292,9 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
 #pragma unroll
             for (int nt = 0; nt < NTL; ++nt) o.yv[u][nt] = Y[i * P + nt * 32 + n];
             if constexpr (!GRAM) {
-                o.k[u] = supp[i * S0 + t_lane];
-                o.c[u] = coef[i * S0 + t_lane];
+                const int64_t at = by_pos ? pos0 + min(2 * (g + u) + h, cnt - 1) : i;
+                o.k[u] = supp[at * S0 + t_lane];
+                o.c[u] = coef[at * S0 + t_lane];
             }
         }
     };
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __re
                                                                const int32_t* __restrict__ perm,
                                                                const int32_t* __restrict__ supp,
                                                                const float* __restrict__ coef,
-                                                               float* __restrict__ partial) {
+                                                               float* __restrict__ partial, int by_pos) {
     constexpr int P = 256;
     constexpr int NTL = 8;                     // 32-wide tiles along the dimensions
     constexpr int G = kAwsSignals;
@@ -439,7 +440,8 @@ __global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __re
             const int64_t i = ids[min(g * G + u, cnt - 1)];
             f.y[u] = Y[i * P + tid];
         }
-        const int64_t i = ids[min(g * G + min(e_sig, G - 1), cnt - 1)];
+        const int e = min(g * G + min(e_sig, G - 1), cnt - 1);
+        const int64_t i = by_pos ? pos0 + e : ids[e];
         f.k = supp[i * S0 + e_ent];
         f.c = coef[i * S0 + e_ent];
     };
@@ -608,7 +610,7 @@ hipError_t launch_ps(int K, const float* Y, int64_t m, const int32_t* supp, cons
 
 template <int S0>
 hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, const float* coef,
-                         const Workspace& ws, float* M, bool split, hipStream_t st) {
+                         const Workspace& ws, float* M, bool split, bool by_pos, hipStream_t st) {
     constexpr int P = 256;
     const int piece = accum_piece(m, K, P);
     const int max_pieces = accum_max_pieces(m, K, P);
@@ -621,10 +623,10 @@ hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, 
             e != hipSuccess)
             return e;
         hipLaunchKernelGGL((accum_wide_split_kernel<S0>), dim3(max_pieces), dim3(256), lds, st, Y, K, piece,
-                           ws.offsets, ws.perm, supp, coef, ws.partial);
+                           ws.offsets, ws.perm, supp, coef, ws.partial, (int)by_pos);
     } else {
         hipLaunchKernelGGL((accum_wide_kernel<S0, false>), dim3(max_pieces), dim3(256), lds1, st, Y, K, piece,
-                           ws.offsets, ws.perm, supp, coef, ws.partial);
+                           ws.offsets, ws.perm, supp, coef, ws.partial, (int)by_pos);
     }
     if (M == nullptr) return hipGetLastError();
     const size_t lds2 = (K + 1 + 16) * sizeof(int);
@@ -634,10 +636,10 @@ hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, 
 }
 
 hipError_t launch_wide(int K, int s0, const float* Y, int64_t m, const int32_t* supp,
-                       const float* coef, const Workspace& ws, float* M, bool split, hipStream_t st) {
+                       const float* coef, const Workspace& ws, float* M, bool split, bool by_pos, hipStream_t st) {
     switch (s0) {
 #define SBO_CASE(N) \
-    case N: return launch_wide_s<N>(K, Y, m, supp, coef, ws, M, split, st);
+    case N: return launch_wide_s<N>(K, Y, m, supp, coef, ws, M, split, by_pos, st);
         SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7)
         SBO_CASE(8) SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13)
         SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
@@ -697,7 +699,7 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
             const int max_pieces = accum_max_pieces(n, K, P);
             const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
             hipLaunchKernelGGL((accum_wide_kernel<1, true>), dim3(max_pieces), dim3(256), lds1, st, Y, K,
-                               piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial);
+                               piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial, 0);
             hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256),
                                (K + 1 + 16) * sizeof(int), st, K, piece, ws.offsets, ws.partial, G, nullptr,
                                (int64_t)0, nullptr, nullptr, nullptr, 0);
@@ -732,12 +734,13 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
 }
 
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
-                             const float* coef, const Workspace& ws, float* M, hipStream_t st) {
+                             const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos) {
+    if (by_pos && p != 256) return hipErrorInvalidValue;
     switch (p) {
         case 16: return launch_p<16>(K, s0, Y, m, supp, coef, ws, M, st);
         case 32: return launch_p<32>(K, s0, Y, m, supp, coef, ws, M, st);
         case 64: return launch_p<64>(K, s0, Y, m, supp, coef, ws, M, st);
-        case 256: return launch_wide(K, s0, Y, m, supp, coef, ws, M, ws.parts_accum, st);
+        case 256: return launch_wide(K, s0, Y, m, supp, coef, ws, M, ws.parts_accum, by_pos, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
                                                           const int32_t* __restrict__ perm,
                                                           int32_t* __restrict__ supp,
                                                           float* __restrict__ coef,
-                                                          float* __restrict__ err) {
+                                                          float* __restrict__ err, int by_pos) {
     constexpr int KS = P / 2;
     constexpr int QN = P / 8;
     constexpr int MT = P / 32;
@@ -252,6 +252,7 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
         gt_own += a > tau;
         eq_own += a == tau;
     }
+    const int64_t at = by_pos ? pos0 + n : i;
     const int gt_oth = other_half(gt_own), eq_oth = other_half(eq_own);
     const int need = s0 - (gt_own + gt_oth);   // entries equal to tau to take, lowest index first
     const int gt_lo = h ? gt_oth : gt_own, eq_lo = h ? eq_oth : eq_own;
@@ -270,8 +271,8 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
         }
         if (take) {
             if (active && pos < s0) {
-                supp[i * s0 + pos] = h * (P / 2) + k;
-                coef[i * s0 + pos] = v;
+                supp[at * s0 + pos] = h * (P / 2) + k;
+                coef[at * s0 + pos] = v;
             }
             ++pos;
         } else {
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
         }
     }
     dropped += other_half(dropped);
-    if (active && h == 0) err[i] = dropped;
+    if (active && h == 0) err[at] = dropped;
 }
 
 // p = 256 on the bf16 matrix cores (see energy_split_kernel for the arithmetic): the four
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(256) void select_wide_split_kernel(const float* __r
                                                                 const int32_t* __restrict__ perm,
                                                                 int32_t* __restrict__ supp,
                                                                 float* __restrict__ coef,
-                                                                float* __restrict__ err) {
+                                                                float* __restrict__ err, int by_pos) {
     constexpr int KS16 = P / 16;
     constexpr int MT = P / 32;
     constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(256) void select_wide_split_kernel(const float* __r
         __syncthreads();
     }
 
-    tile_select<P, S>(acc, h, n, active, i, s0, nullptr, stage_all + wave * kSelectStageWords, supp, coef,
+    tile_select<P, S>(acc, h, n, active, by_pos ? pos0 + n : i, s0, nullptr, stage_all + wave * kSelectStageWords, supp, coef,
                              err);
 }
 
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(64 * kShareWaves) void select_wide_shared_kernel(co
                                                                  int K, int s0, const int32_t* __restrict__ offsets,
                                                                  const int32_t* __restrict__ perm,
                                                                  int32_t* __restrict__ supp, float* __restrict__ coef,
-                                                                 float* __restrict__ err) {
+                                                                 float* __restrict__ err, int by_pos) {
     constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 6, NW = kShareWaves, L = 16;
     constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
     extern __shared__ int lds[];               // tile_start[K+1] | tmp[16] | pad | parts of y, then coefficients | stage
@@ -544,7 +545,7 @@ __global__ __launch_bounds__(64 * kShareWaves) void select_wide_shared_kernel(co
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (!active) return;
-    const int64_t i = perm[pos0 + sig];
+    const int64_t i = by_pos ? pos0 + sig : perm[pos0 + sig];
     if (part == 0) err[i] = dropped;
     for (int e = part; e < s0; e += L) {
         supp[i * s0 + e] = mine[e];
@@ -555,7 +556,7 @@ __global__ __launch_bounds__(64 * kShareWaves) void select_wide_shared_kernel(co
 template <int P, int S>
 hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int s0,
                           const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
-                          hipStream_t st) {
+                          bool by_pos, hipStream_t st) {
     (void)D;                                   // the kernels read ws.dsb / ws.dsw, the same Q in operand order
     const int64_t tiles = (m + 31) / 32 + K;
     if (split && tiles <= kSharedTiles) {
@@ -563,7 +564,7 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_shared_kernel<S>), 64 * 1024); e != hipSuccess)
             return e;
         hipLaunchKernelGGL((select_wide_shared_kernel<S>), dim3((unsigned)tiles), dim3(64 * kShareWaves), lds, st, Y,
-                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err);
+                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos);
         return hipGetLastError();
     }
     if (split) {
@@ -577,7 +578,7 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
             e != hipSuccess)
             return e;
         hipLaunchKernelGGL((select_wide_split_kernel<P, S>), dim3((unsigned)max_units), dim3(256), lds, st, Y,
-                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err);
+                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos);
         return hipGetLastError();
     }
     const int64_t max_tiles = (m + 31) / 32 + K;
@@ -587,19 +588,19 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
         e != hipSuccess)
         return e;
     hipLaunchKernelGGL((select_wide_kernel<P, S>), grid, dim3(256), lds, st, Y,
-                       reinterpret_cast<const f32x4*>(ws.dsw), K, s0, ws.offsets, ws.perm, supp, coef, err);
+                       reinterpret_cast<const f32x4*>(ws.dsw), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos);
     return hipGetLastError();
 }
 
 template <int P>
 hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int K,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
-                         hipStream_t st) {
-    if (s0 <= 1) return launch_wide_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, split, st);
-    if (s0 <= 2) return launch_wide_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, split, st);
-    if (s0 <= 4) return launch_wide_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, split, st);
-    if (s0 <= 8) return launch_wide_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, split, st);
-    return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, split, st);
+                         bool by_pos, hipStream_t st) {
+    if (s0 <= 1) return launch_wide_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
+    if (s0 <= 2) return launch_wide_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
+    if (s0 <= 4) return launch_wide_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
+    if (s0 <= 8) return launch_wide_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
+    return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
 }
 
 template <int P, int S>
@@ -635,8 +636,8 @@ hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, co
 
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, int32_t* blk, bool choose) {
-    if (blk != nullptr ? !group_in_select(p, K, m) : choose) return hipErrorInvalidValue;
+                         bool split, hipStream_t st, int32_t* blk, bool choose, bool by_pos) {
+    if ((blk != nullptr ? !group_in_select(p, K, m) : choose) || (by_pos && p != 256)) return hipErrorInvalidValue;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
         hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, st)
                              : launch_dict_swizzle(p, K, D, ws.dsw, st);
@@ -646,7 +647,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
         case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
         case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
         case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
-        case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, st);
+        case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, by_pos, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -215,11 +215,12 @@ static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, cons
 
 // Accumulate + SVD of K orthobases (-1: all) from codes, for signals already grouped in the workspace.
 static int run_update_grouped(sbo_ctx* c, const float* Y, int64_t m, const int32_t* supp, const float* coef, float* D,
-                              int write_ops = 0, const float* err = nullptr, double* sq_out = nullptr, int K = -1) {
+                              int write_ops = 0, const float* err = nullptr, double* sq_out = nullptr, int K = -1,
+                              bool by_pos = false) {
     if (K < 0) K = c->K;
     {
         StageTimer t(c, SBO_STAGE_ACCUM);
-        SBO_HIP(launch_accumulate(c->p, K, c->s0, Y, m, supp, coef, c->ws, nullptr, c->stream));
+        SBO_HIP(launch_accumulate(c->p, K, c->s0, Y, m, supp, coef, c->ws, nullptr, c->stream, by_pos));
     }
     return run_polar_pieces(c, m, D, write_ops, err, sq_out, K);
 }
@@ -551,20 +552,26 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
     };
 
     // Initialisation: K0 orthobases, each trained on its own signal set; then represent.
-    // p <= 64: all K0 at once, the sets as K0 blocks of one grouping (eq. (5) for every block,
-    // then R rounds of the fused select + accumulate and the SVD update over K0 blocks; a
-    // signal that sits in two sets only has its scratch rows of supp / coef / err written
-    // twice, which nothing reads).  Otherwise, and when the sets do not fit the workspace, one
-    // after the other.
+    // All K0 at once, the sets as K0 blocks of one grouping: eq. (5) for every block, then R rounds of selection,
+    // accumulation and the SVD update over K0 blocks.  A signal that sits in two sets has its scratch rows of supp /
+    // coef / err written twice, which nothing reads at p <= 64, where the codes do not go through memory; at p = 256
+    // their rows are those of the positions in the grouping.  Sets that do not fit the workspace (p = 256: those
+    // rows) are trained one after the other.
     const int64_t n_init = (int64_t)K0 * P0;
-    if (c->p <= 64 && n_init <= c->m_max && (int64_t)K0 * c->p <= c->m_max) {
+    if (n_init <= (c->p <= 64 ? c->m_max : m) && (int64_t)K0 * c->p <= c->m_max) {
         SBO_HIP(launch_equal_blocks(init_ids, K0, P0, m, c->ws, c->stream));
         SBO_HIP(launch_gram(c->p, K0, Y, n_init, c->ws, c->ws.M, c->stream));
         SBO_HIP(launch_polar(c->p, K0, c->ws.M, nullptr, D, c->ws, c->svd_method == SBO_SVD_JACOBI, c->ws.energy, 0,
                              c->stream));
         for (int r = 0; r < R; ++r) {
-            SBO_HIP(launch_select_accum(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, c->stream));
-            rc = run_polar_pieces(c, n_init, D, 0, nullptr, nullptr, K0);
+            if (c->p <= 64) {
+                SBO_HIP(launch_select_accum(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, c->stream));
+                rc = run_polar_pieces(c, n_init, D, 0, nullptr, nullptr, K0);
+            } else {
+                SBO_HIP(launch_select(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, r > 0, use_split(c), c->stream,
+                                      nullptr, false, true));
+                rc = run_update_grouped(c, Y, n_init, supp, coef, D, select_ops(c), nullptr, nullptr, K0, true);
+            }
             if (rc) return fail(rc);
         }
     } else {

@@ -229,14 +229,16 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // launch_group is not called, and what it leaves in ws is left there too).  The line: every workgroup sorts the whole
 // set, so it has to be small, and its lists have to fit 64 KiB of LDS beside the tiles.
 // choose: blk is written first, from the energies in ws.part_E (launch_energy_direct).
+// by_pos (p = 256): the codes of the signal at position q of ws.perm go to row q, not to the row of the signal: where a
+// signal is in several blocks (sbo_learn's initial sets).  launch_accumulate reads them likewise.
 inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false);
+                         bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false);
 
 // M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
-                             const float* coef, const Workspace& ws, float* M, hipStream_t st);
+                             const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos = false);
 
 // Fused select + per-piece accumulation (p <= 64); the piece results land in ws.partial
 // and launch_accum_reduce sums them into M.  blk: as launch_select.

@@ -4,6 +4,7 @@ squared-error total (Section 4), and the growth step composed from them."""
 import numpy as np
 import pytest
 
+import paper_1412_4944_amd as sbo
 import sbo_synth as synth
 from oracle import sbo_oracle as orc
 from gpu_util import Sbo, compare_assigned_code, compare_Q, ORTHO_TOL
@@ -178,6 +179,27 @@ def test_new_base_free_running(name, kw, n, R):
     _Qo, sqo = orc.o_new_base(pr.Y, ids, cfg.s0, R)
     print(f"  gpu {sq}\n  oracle {sqo}", flush=True)
     assert np.abs(sq - sqo).max() <= 2e-3 * sqo[0]
+
+
+@pytest.mark.parametrize("p,m,P0,arith", [(16, 900, 300, "f16x2"), (64, 1500, 500, "f16x2"), (256, 2100, 700, "f16x2"),
+                                          (256, 2100, 700, "f32"), (256, 1000, 400, "f16x2")])
+def test_learn_initial_sets_as_one_batch(p, m, P0, arith):
+    """sbo_learn trains its initial orthobases as one batch (at p = 256 with the codes by position, and one after the
+    other where 3 P0 > m): the same as sbo_new_base on each set, also where the sets share signals."""
+    pr = synth.generate(synth.custom(f"batch_p{p}", p=p, K=3, m=m, s0=4, snr_db=20.0))
+    rng = np.random.default_rng(61)
+    sets = np.stack([np.sort(rng.choice(m, P0, replace=False)) for _ in range(3)]).astype(np.int32)
+    sets[2] = sets[0]
+    with Sbo(p, 3, 4, m, arith=arith) as g:
+        t = g.torch
+        D = t.zeros((3, p, p), dtype=t.float32, device=g.dev)
+        sbo.sbo_learn(g.ctx, g.dev_f32(pr.Y), D, g.dev_i32(sets), 3, 100, 3, 0.0, *g.outputs(m))
+        t.cuda.synchronize()
+        D = D.cpu().numpy()
+        assert np.array_equal(D[0], D[2])
+        for j in range(3):
+            Q = g.new_base(pr.Y, sets[j], 3)[0]
+            np.testing.assert_allclose(D[j], Q, atol=2e-5)
 
 
 def test_growth_step_reduces_error():
