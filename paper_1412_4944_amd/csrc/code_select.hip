@@ -283,143 +283,43 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
     if (active && h == 0) err[at] = dropped;
 }
 
-// p = 256 on the bf16 matrix cores (see energy_split_kernel for the arithmetic): the four
-// wavefronts of a workgroup take four 32-signal tiles of ONE block and share its rows, staged
-// through LDS 32 atoms at a time (48 KiB in the split operand order, double-buffered); each
-// wavefront keeps its signals' three bf16 parts (192 registers) and the whole projection
-// (8 accumulator tiles, 128 registers) in registers and selects from there.  Dsb is the whole
-// dictionary in the split operand order (dict_parts_kernel).
-// Workgroup ids are dealt out so that the workgroups of one XCD (ids equal modulo 8) take a
-// contiguous run of tiles, that is, few blocks, whose rows then stay in that XCD's L2.
-template <int P, int S>
-__global__ __launch_bounds__(256) void select_wide_split_kernel(const float* __restrict__ Y,
-                                                                const u32x4* __restrict__ Dsb, int K, int s0,
-                                                                const int32_t* __restrict__ offsets,
-                                                                const int32_t* __restrict__ perm,
-                                                                int32_t* __restrict__ supp,
-                                                                float* __restrict__ coef,
-                                                                float* __restrict__ err, int by_pos) {
-    constexpr int KS16 = P / 16;
-    constexpr int MT = P / 32;
-    constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
-    constexpr int FPT = STAGE_U / 256;
-    static_assert(STAGE_U % 256 == 0 && S <= 16, "shape");
-
-    extern __shared__ int lds[];               // unit_start[K+1] | tmp[16] | pad | Qs[2][STAGE_U] | stage[4][..]
-    int* unit_start = lds;
-    int* tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    u32x4(*Qs)[STAGE_U] = reinterpret_cast<u32x4(*)[STAGE_U]>(lds + head);
-    int* stage_all = reinterpret_cast<int*>(Qs + 2);
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = lane >> 5, n = lane & 31;
-
-    // units of four tiles per block
-    wg_exclusive_scan4([&](int j) { return (((offsets[j + 1] - offsets[j] + 31) >> 5) + 3) >> 2; }, K,
-                       unit_start, tmp);
-    const int per_xcd = gridDim.x >> 3;        // the grid is a multiple of 8 (launcher)
-    const int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (id >= unit_start[K]) return;           // uniform over the workgroup
-
-    const int j = upper_slot(unit_start, K, id);
-    const int pos0 = offsets[j] + ((id - unit_start[j]) * 4 + wave) * 32;
-    const int cnt = min(32, offsets[j + 1] - pos0);        // <= 0: this wavefront has no tile (it still
-    const bool active = n < cnt;                           // takes part in the staging and the barriers)
-    const int64_t i = active ? perm[pos0 + n] : -1;
-
-    u32x4 pre[FPT];
-    const u32x4* Qj = Dsb + (int64_t)j * MT * STAGE_U;
-    auto fetch = [&](int s) {
-#pragma unroll
-        for (int r = 0; r < FPT; ++r) pre[r] = Qj[(int64_t)s * STAGE_U + tid + 256 * r];
-    };
-    auto stash = [&](int buf) {
-#pragma unroll
-        for (int r = 0; r < FPT; ++r) Qs[buf][tid + 256 * r] = pre[r];
-    };
-    fetch(0);
-
-    // B operand: the three bf16 parts of this lane's dims (ks*16 + h*8 .. +7) of its signal
-    u32x4 yq[KS16][3];
-#pragma unroll
-    for (int ks = 0; ks < KS16; ++ks) {
-        f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
-        if (active) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(Y + i * P + ks * 16 + h * 8);
-            v0 = src[0];
-            v1 = src[1];
-        }
-        const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
-        const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
-        yq[ks][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
-        yq[ks][1] = u32x4{a.mid, b.mid, c.mid, d.mid};
-        yq[ks][2] = u32x4{a.lo, b.lo, c.lo, d.lo};
-    }
-    stash(0);
-    __syncthreads();
-
-    // the six partial products, smallest first: (A part, B part)
-    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
-    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
-                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 acc[MT];
-#pragma unroll
-    for (int s = 0; s < MT; ++s) {
-        const int cur = s & 1;
-        if (s + 1 < MT) fetch(s + 1);
-#pragma unroll
-        for (int ks = 0; ks < KS16; ++ks) {
-            u32x4 a[3];
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) a[pl] = Qs[cur][(ks * 3 + pl) * 64 + lane];
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
-                acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[TA[t]]),
-                                                                 __builtin_bit_cast(bf16x8, yq[ks][TB[t]]),
-                                                                 (ks == 0 && t == 0) ? zero : acc[s], 0, 0, 0);
-        }
-        if (s + 1 < MT) stash(cur ^ 1);
-        __syncthreads();
-    }
-
-    tile_select<P, S>(acc, h, n, active, by_pos ? pos0 + n : i, s0, nullptr, stage_all + wave * kSelectStageWords, supp, coef,
-                             err);
-}
-
-// The same for small sets, whose tiles of four wavefronts each would leave most of the chip idle for the 38 us that one
-// takes: a workgroup has ONE tile of 32 signals, its eight wavefronts share out the atoms (32 each, rows straight from L2,
-// every row used once) and then the signals (four each, 16 lanes to a signal, 16 consecutive atoms per lane).  The signals'
-// parts are made once, by all, in LDS.  Same products in the same order as above.  5041 signals, K = 16, s0 = 12:
-// 42.4 -> 19.8 us, 2048, K = 1 43.2 -> 16.6, 11000, K = 8 43.1 -> 24.6.  Two such workgroups fit a CU: the line is where they take a second
-// round (24000 signals would take 44, against 46).
-constexpr int64_t kSharedTiles = 2 * kNumCU;
-constexpr int kShareWaves = 8;
-constexpr int kShareLd = 260;                  // floats per signal of the coefficients (16-byte units cover all banks)
+// p = 256 on the bf16 matrix cores (see energy_split_kernel for the arithmetic): a workgroup has one tile of 32 signals of
+// ONE block.  Its eight wavefronts share out the atoms (32 each; rows of Dsb, the dictionary in the split operand order of
+// dict_parts_kernel, straight from L2, every row used once) and then the signals (four each, 16 lanes to a signal, 16
+// consecutive atoms per lane).  The signals' parts are made once, by all, in LDS, whose place the coefficients take.
+// What bounds it: nothing alone.  A tile's products take a CU 6100 cycles, its selection 5000 cycles of vector issue, and its
+// rows and signals come in several trips; three workgroups on a CU (three contraction steps ahead, 80 registers) fill one another's gaps.
+// With a tile per wavefront, four to a workgroup and one workgroup per CU (projection and signal in 320 registers, rows
+// through LDS) a tile took 38 us however few there were, and nothing hid its selection.  Before and now: 2048 signals, K = 1
+// 43.2 -> 17 us, 5041, K = 16 42.4 -> 19, 16384 46 -> 33, 32768 86 -> 55, 131072 212 -> 159 (two workgroups per CU, six steps
+// ahead 172).
+// Workgroup ids are dealt out so that the workgroups of one XCD (ids equal modulo 8) take a contiguous run of tiles, that is,
+// few blocks, whose rows then stay in that XCD's L2 (131072 signals, K = 16: 190 -> 172 us).
+constexpr int kTileWaves = 8;
+constexpr int kTileLd = 260;                  // floats per signal of the coefficients (16-byte units cover all banks)
 template <int S>
-__global__ __launch_bounds__(64 * kShareWaves) void select_wide_shared_kernel(const float* __restrict__ Y, const u32x4* __restrict__ Dsb,
+__global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(const float* __restrict__ Y, const u32x4* __restrict__ Dsb,
                                                                  int K, int s0, const int32_t* __restrict__ offsets,
                                                                  const int32_t* __restrict__ perm,
                                                                  int32_t* __restrict__ supp, float* __restrict__ coef,
                                                                  float* __restrict__ err, int by_pos) {
-    constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 6, NW = kShareWaves, L = 16;
+    constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 3, NW = kTileWaves, L = 16;
     constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
     extern __shared__ int lds[];               // tile_start[K+1] | tmp[16] | pad | parts of y, then coefficients | stage
     int* tile_start = lds;
     int* tmp = lds + (K + 1);
     const int head = ((K + 1 + 16) + 3) & ~3;
     u32x4* ys = reinterpret_cast<u32x4*>(lds + head);          // [KS16][3][64]
-    float* cs = reinterpret_cast<float*>(ys);                  // [32][kShareLd]
+    float* cs = reinterpret_cast<float*>(ys);                  // [32][kTileLd]
     int* stage = reinterpret_cast<int*>(ys + STAGE_U);         // [32][2][16]
-    static_assert(32 * kShareLd * 4 <= STAGE_U * 16, "the coefficients fit");
+    static_assert(32 * kTileLd * 4 <= STAGE_U * 16, "the coefficients fit");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
     wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + 31) >> 5; }, K, tile_start, tmp);
-    const int id = blockIdx.x;
+    const int per_xcd = gridDim.x >> 3;        // the grid is a multiple of 8 (launcher)
+    const int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (id >= tile_start[K]) return;           // uniform over the workgroup
     const int j = upper_slot(tile_start, K, id);
     const int pos0 = offsets[j] + (id - tile_start[j]) * 32;
@@ -475,14 +375,14 @@ __global__ __launch_bounds__(64 * kShareWaves) void select_wide_shared_kernel(co
     __syncthreads();                           // the parts are dead
 #pragma unroll
     for (int q = 0; q < 4; ++q)                // atoms wave*32 + q*8 + h*4 .. +3 of signal n
-        *reinterpret_cast<f32x4*>(cs + n * kShareLd + wave * 32 + q * 8 + h * 4) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        *reinterpret_cast<f32x4*>(cs + n * kTileLd + wave * 32 + q * 8 + h * 4) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
     __syncthreads();
 
     // L lanes to a signal, lane `part` has the coefficients of C consecutive atoms.
     constexpr int C = P / L;
     const int sig = wave * (64 / L) + lane / L, part = lane % L;
     const bool active = sig < cnt;
-    const float* row = cs + sig * kShareLd;
+    const float* row = cs + sig * kTileLd;
     float c[C], mag[C], top[S];
 #pragma unroll
     for (int u = 0; u < C / 4; ++u) {
@@ -558,26 +458,13 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
                           const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
                           bool by_pos, hipStream_t st) {
     (void)D;                                   // the kernels read ws.dsb / ws.dsw, the same Q in operand order
-    const int64_t tiles = (m + 31) / 32 + K;
-    if (split && tiles <= kSharedTiles) {
-        const size_t lds = (((size_t)(K + 1 + 16) + 3) & ~(size_t)3) * sizeof(int) + (size_t)(P / 16) * 3 * 64 * 16 + 32 * 32 * sizeof(int);
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_shared_kernel<S>), 64 * 1024); e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((select_wide_shared_kernel<S>), dim3((unsigned)tiles), dim3(64 * kShareWaves), lds, st, Y,
-                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos);
-        return hipGetLastError();
-    }
     if (split) {
-        // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every unit
-        const int64_t max_units = (((m + 127) / 128 + K) + 7) & ~(int64_t)7;
-        const int head = ((K + 1 + 16) + 3) & ~3;
-        const size_t lds = (size_t)head * sizeof(int) + (size_t)2 * (P / 16) * 3 * 64 * 16 +
-                           (size_t)4 * kSelectStageWords * sizeof(int);
-        if (hipError_t e =
-                ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_split_kernel<P, S>), lds);
-            e != hipSuccess)
+        // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every tile
+        const int64_t tiles = (((m + 31) / 32 + K) + 7) & ~(int64_t)7;
+        const size_t lds = (((size_t)(K + 1 + 16) + 3) & ~(size_t)3) * sizeof(int) + (size_t)(P / 16) * 3 * 64 * 16 + 32 * 32 * sizeof(int);
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_split_kernel<S>), 64 * 1024); e != hipSuccess)
             return e;
-        hipLaunchKernelGGL((select_wide_split_kernel<P, S>), dim3((unsigned)max_units), dim3(256), lds, st, Y,
+        hipLaunchKernelGGL((select_wide_split_kernel<S>), dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
                            reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos);
         return hipGetLastError();
     }

@@ -84,29 +84,28 @@ def test_code_ties_zero_signal_and_duplicates(arith, p):
 
 
 @pytest.mark.parametrize("s0", [1, 3, 8, 12, 16])
-def test_code_p256_selection_shapes(s0):
-    """p = 256 takes one tile of 32 signals per workgroup up to 512 tiles and four beyond: the same signals on both
-    sides of the line (K = 4: 16256 signals are 512 tiles) get the same supports and bitwise the same coefficients,
-    exact magnitude ties, zero signals and ragged blocks among them; the residual is summed in another order."""
-    p, K, m = 256, 4, 16256
+def test_code_p256_selection(s0):
+    """p = 256 selects with 16 lanes to a signal: exact magnitude ties, zero signals and ragged blocks against the oracle,
+    and the same signals as part of a larger set, where they share tiles with others."""
+    p, K, m = 256, 4, 700
     rng = np.random.default_rng(53)
     D = np.stack([np.eye(p)] + [synth.random_onb(rng, p).T for _ in range(K - 1)]).astype(np.float32)
-    Y = rng.standard_normal((m + 32, p)).astype(np.float32)
+    Y = rng.standard_normal((2 * m, p)).astype(np.float32)
     Y[0] = 0.0
     Y[1:40] = rng.integers(-2, 3, size=(39, p))           # many ties in the first block
     Y[40] = 1.0
     print(f"case s0={s0}", flush=True)
     out = []
-    for n in (m, m + 32):
+    for n in (m, 2 * m):
         with Sbo(p, K, s0, n) as g:
             out.append(g.code(Y[:n], D))
     a, b = out[0], [v[:m] for v in out[1]]
-    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
-    assert np.abs(a[3] - b[3]).max() <= 1e-5 * (Y ** 2).sum(1).max()
-    pick = np.r_[0:64, m - 40:m]
-    o = orc.o_code(Y[pick], D, s0)
-    compare_code(Y[pick], D, s0, o, tuple(v[pick] for v in a), max_exempt_frac=0.5)
-    assert a[1][40].tolist() == list(range(s0)) if a[0][40] == 0 else True
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+    o = orc.o_code(Y[:m], D, s0)
+    compare_code(Y[:m], D, s0, o, a, max_exempt_frac=0.5)
+    if a[0][40] == 0:
+        assert a[1][40].tolist() == list(range(s0)) and (a[2][40] == 1.0).all()
 
 
 @pytest.mark.parametrize("p,K,s0", [(64, 5, 8), (16, 3, 4), (256, 2, 12)])
