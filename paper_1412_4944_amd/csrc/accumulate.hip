@@ -364,40 +364,46 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
 }
 
 // p = 256 on the bf16 matrix cores (three-part split of both operands, six partial products,
-// fp32 accumulation: device_utils.h).  Same division of the work as accum_wide_kernel (a piece per
-// workgroup, 64 atoms per wavefront, 256 accumulator registers), but a step covers 16 signals, the
-// contraction length of v_mfma_f32_32x32x16_bf16, and both operands go through LDS tiles with the
-// signals along the rows' 32 bytes, built by the whole workgroup while the matrix cores work on
-// the previous step's tiles (two sets of tiles):
-//   y tile [3 parts][256 dims][16 signals]: thread t loads dim t of the 16 signals (each load of a
-//          wavefront is 256 contiguous bytes), splits pairs of signals and stores two 16-byte units;
-//   x tile [3 parts][256 atoms + 1][16 signals]: zero-filled, then one thread per (signal, entry)
-//          scatters the three parts of a kept coefficient (entries that do not exist go to the
-//          extra row, which nobody reads).
+// fp32 accumulation: device_utils.h).  A workgroup per piece, 32 atoms per wavefront (8 tiles, 128 accumulator registers); a
+// step covers 16 signals, the contraction length of v_mfma_f32_32x32x16_bf16, and both operands go through LDS tiles with
+// the signals along the rows' 32 bytes, built by the whole workgroup while the matrix cores work on
+// the previous step's tiles:
+//   y tile [3 parts][256 dims][16 signals], two sets: thread t loads dim t % 256 of 8 signals (each load of a
+//          wavefront is 256 contiguous bytes), splits pairs of signals and stores a 16-byte unit per part;
+//   x tile [3 parts][256 atoms + 1][16 signals], three sets, zero but for what one thread per (signal, entry) scatters, the
+//          three parts of a kept coefficient (entries that do not exist go to the extra row, which nobody reads), and
+//          wipes again a step after the tile has been used: one barrier a step.
 // The loads of a step are issued two steps ahead.
+// What bounds it: the products, 1270 TFLOP/s while they run (the chip sustains 1530 on such operands), and the 256 KiB that a piece
+// leaves (15 us of it).  131072 signals, K = 16, s0 = 12: 110 -> 98 us with eight wavefronts, two on a SIMD, where
+// four with 64 atoms each split and multiplied in turn, zero-filled the x tile and met twice a step; 2048 signals 21 -> 19.
 constexpr int kAwsSignals = 16;
+constexpr int kAwsWaves = 8;
+constexpr size_t aws_lds_bytes(int head) {
+    return (size_t)(head + kMaxPiece) * sizeof(int) + (size_t)2 * 3 * 256 * 32 + (size_t)3 * 3 * 257 * 32;
+}
 
 template <int S0>
-__global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __restrict__ Y, int K, int piece,
-                                                               const int32_t* __restrict__ offsets,
-                                                               const int32_t* __restrict__ perm,
-                                                               const int32_t* __restrict__ supp,
-                                                               const float* __restrict__ coef,
-                                                               float* __restrict__ partial, int by_pos) {
-    constexpr int P = 256;
+__global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const float* __restrict__ Y, int K, int piece,
+                                                                          const int32_t* __restrict__ offsets,
+                                                                          const int32_t* __restrict__ perm,
+                                                                          const int32_t* __restrict__ supp,
+                                                                          const float* __restrict__ coef,
+                                                                          float* __restrict__ partial, int by_pos) {
+    constexpr int P = 256, NT = 64 * kAwsWaves;
     constexpr int NTL = 8;                     // 32-wide tiles along the dimensions
-    constexpr int G = kAwsSignals;
+    constexpr int G = kAwsSignals, GH = G / 2;
     constexpr int YPLANE = P * 32;             // bytes of one part of the y tile
     constexpr int XPLANE = (P + 1) * 32;       // bytes of one part of the x tile (+ the extra row)
-    constexpr int SET_B = 3 * YPLANE + 3 * XPLANE;
-    static_assert(G * S0 <= 256, "one thread per (signal, entry)");
-    // piece_start[K+1] | tmp[16] | pad | ids[kMaxPiece] | two sets of (y tile, x tile)
+    static_assert(G * S0 <= NT, "one thread per (signal, entry)");
+    // piece_start[K+1] | tmp[16] | pad | ids[kMaxPiece] | two y tiles | three x tiles
     extern __shared__ int lds[];
     int* piece_start = lds;
     int* tmp = lds + (K + 1);
     const int head = ((K + 1 + 16) + 3) & ~3;
     int* ids = lds + head;
-    unsigned char* sets = reinterpret_cast<unsigned char*>(ids + kMaxPiece);
+    unsigned char* ytiles = reinterpret_cast<unsigned char*>(ids + kMaxPiece);
+    unsigned char* xtiles = ytiles + 2 * 3 * YPLANE;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -411,83 +417,76 @@ __global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __re
     const int j = upper_slot(piece_start, K, id);
     const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
     const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
-    for (int q = tid; q < cnt; q += 256) ids[q] = perm[pos0 + q];
+    for (int q = tid; q < cnt; q += NT) ids[q] = perm[pos0 + q];
+    for (int e = tid; e < 9 * XPLANE / 16; e += NT) reinterpret_cast<u32x4*>(xtiles)[e] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
 
-    f32x16 acc[2][NTL];
+    f32x16 acc[NTL];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int b = 0; b < NTL; ++b)
 #pragma unroll
-        for (int b = 0; b < NTL; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
 
-    const int atom0 = 64 * wave;               // this wavefront's atoms: atom0 .. atom0+63
+    const int atom0 = 32 * wave;               // this wavefront's atoms: atom0 .. atom0+31
     const int n_steps = (cnt + G - 1) / G;
 
-    // What a thread fetches for a step: dim `tid` of its 16 signals, and one (atom, coefficient)
+    // What a thread fetches for a step: one dim of half of its 16 signals, and one (atom, coefficient)
     // of one signal (threads below 16 * S0).  Positions past the end of the piece are clamped
     // for the loads and masked when the tiles are built.
     struct Fetched {
-        float y[G];
+        float y[GH];
         int k;
         float c;
     };
+    const int dim = tid & (P - 1), u0 = __builtin_amdgcn_readfirstlane(tid / P) * GH;
     const int e_sig = tid / S0, e_ent = tid % S0;
     auto fetch = [&](Fetched& f, int g) {
 #pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int64_t i = ids[min(g * G + u, cnt - 1)];
-            f.y[u] = Y[i * P + tid];
+        for (int u = 0; u < GH; ++u) {
+            const int64_t i = ids[min(g * G + u0 + u, cnt - 1)];
+            f.y[u] = Y[i * P + dim];
         }
         const int e = min(g * G + min(e_sig, G - 1), cnt - 1);
         const int64_t i = by_pos ? pos0 + e : ids[e];
         f.k = supp[i * S0 + e_ent];
         f.c = coef[i * S0 + e_ent];
     };
-    auto zero_x = [&](int set) {
-        u32x4* xt = reinterpret_cast<u32x4*>(sets + (size_t)set * SET_B + 3 * YPLANE);
-        for (int e = tid; e < 3 * XPLANE / 16; e += 256) xt[e] = u32x4{0u, 0u, 0u, 0u};
-    };
-    auto build = [&](const Fetched& f, int g, int set) {
-        unsigned char* yt = sets + (size_t)set * SET_B;
-        unsigned char* xt = yt + 3 * YPLANE;
-        const int left = cnt - g * G;          // signals of this step (uniform)
-        unsigned w[3][8];
-#pragma unroll
-        for (int u = 0; u < G; u += 2) {
-            const Bf16x3Pair s = split_bf16x3(u < left ? f.y[u] : 0.f, u + 1 < left ? f.y[u + 1] : 0.f);
-            w[0][u >> 1] = s.hi;
-            w[1][u >> 1] = s.mid;
-            w[2][u >> 1] = s.lo;
-        }
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl) {
-            *reinterpret_cast<u32x4*>(yt + pl * YPLANE + tr_off(tid, 0)) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
-            *reinterpret_cast<u32x4*>(yt + pl * YPLANE + tr_off(tid, 8)) = u32x4{w[pl][4], w[pl][5], w[pl][6], w[pl][7]};
-        }
-        const bool have = tid < G * S0 && e_sig < left && (unsigned)f.k < (unsigned)P;
-        const TriWord t = split_trunc(f.c);
-        const int at = tr_off(have ? f.k : P, e_sig & (G - 1));
+    auto scatter = [&](unsigned char* xt, int at, TriWord t) {
         if (tid < G * S0) {
             *reinterpret_cast<unsigned short*>(xt + at) = (unsigned short)(t.hi >> 16);
             *reinterpret_cast<unsigned short*>(xt + XPLANE + at) = (unsigned short)(t.mid >> 16);
             *reinterpret_cast<unsigned short*>(xt + 2 * XPLANE + at) = (unsigned short)(t.lo >> 16);
         }
     };
+    auto build = [&](const Fetched& f, int g) {            // returns where this thread's entry went
+        unsigned char* yt = ytiles + (g & 1) * (3 * YPLANE);
+        const int left = cnt - g * G;          // signals of this step (uniform)
+        unsigned w[3][GH / 2];
+#pragma unroll
+        for (int u = 0; u < GH; u += 2) {
+            const Bf16x3Pair s = split_bf16x3(u0 + u < left ? f.y[u] : 0.f, u0 + u + 1 < left ? f.y[u + 1] : 0.f);
+            w[0][u >> 1] = s.hi;
+            w[1][u >> 1] = s.mid;
+            w[2][u >> 1] = s.lo;
+        }
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+            *reinterpret_cast<u32x4*>(yt + pl * YPLANE + tr_off(dim, u0)) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
+        const bool have = tid < G * S0 && e_sig < left && (unsigned)f.k < (unsigned)P;
+        const int at = tr_off(have ? f.k : P, e_sig & (G - 1));
+        scatter(xtiles + (g % 3) * (3 * XPLANE), at, split_trunc(f.c));
+        return at;
+    };
     // the six partial products, smallest first: (A part, B part)
     constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
     constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
-    auto multiply = [&](int set) {
-        const unsigned char* yt = sets + (size_t)set * SET_B;
-        const unsigned char* xt = yt + 3 * YPLANE;
+    auto multiply = [&](int g) {
+        const unsigned char* yt = ytiles + (g & 1) * (3 * YPLANE);
+        const unsigned char* xt = xtiles + (g % 3) * (3 * XPLANE);
         // operands: lane (h, n) takes signals 8h .. 8h+7 of atom resp. dim tile*32 + n
-        u32x4 xa[2][3];
+        u32x4 xa[3];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
-                xa[mt][pl] = *reinterpret_cast<const u32x4*>(xt + pl * XPLANE + tr_off(atom0 + mt * 32 + n, 8 * h));
+        for (int pl = 0; pl < 3; ++pl) xa[pl] = *reinterpret_cast<const u32x4*>(xt + pl * XPLANE + tr_off(atom0 + n, 8 * h));
 #pragma unroll
         for (int nt = 0; nt < NTL; ++nt) {
             u32x4 yb[3];
@@ -496,51 +495,44 @@ __global__ __launch_bounds__(256) void accum_wide_split_kernel(const float* __re
                 yb[pl] = *reinterpret_cast<const u32x4*>(yt + pl * YPLANE + tr_off(nt * 32 + n, 8 * h));
 #pragma unroll
             for (int t = 0; t < 6; ++t)
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8, xa[mt][TA[t]]), __builtin_bit_cast(bf16x8, yb[TB[t]]), acc[mt][nt],
-                        0, 0, 0);
+                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[TA[t]]),
+                                                                  __builtin_bit_cast(bf16x8, yb[TB[t]]), acc[nt], 0, 0, 0);
         }
     };
 
-    // step g: its tiles are built during the multiplication of step g - 1 and its loads were issued
-    // during that of step g - 2
+    // phase g: the products of step g; the tiles of step g + 1 are built (their loads were issued two phases ago), and the
+    // entries of step g - 1 wiped, whose x tile is that of step g + 2
     Fetched fa, fb;
     fetch(fa, 0);
     fetch(fb, 1);
-    zero_x(0);
-    __syncthreads();
-    build(fa, 0, 0);
+    int now = build(fa, 0), old = tr_off(P, 0);
     fetch(fa, 2);
     __syncthreads();
+    auto phase = [&](Fetched& f, int g) {
+        // one wavefront of a SIMD builds first, the other multiplies first: between two barriers they would otherwise
+        // want the vector ALU together, and then the matrix cores
+        if (wave >= kAwsWaves / 2) multiply(g);
+        const int next = build(f, g + 1);
+        fetch(f, g + 3);
+        scatter(xtiles + ((g + 2) % 3) * (3 * XPLANE), old, TriWord{0u, 0u, 0u});
+        if (wave < kAwsWaves / 2) multiply(g);
+        old = now;
+        now = next;
+        __syncthreads();
+    };
     for (int g = 0; g < n_steps; g += 2) {
-        // even step g from set 0; meanwhile the tiles of step g + 1 in set 1
-        zero_x(1);
-        __syncthreads();
-        build(fb, g + 1, 1);
-        fetch(fb, g + 3);
-        multiply(0);
-        __syncthreads();
-        // odd step g + 1 from set 1; meanwhile the tiles of step g + 2 in set 0
-        zero_x(0);
-        __syncthreads();
-        build(fa, g + 2, 0);
-        fetch(fa, g + 4);
-        multiply(1);                           // past the end: its tiles hold zeros
-        __syncthreads();
+        phase(fb, g);
+        if (g + 1 < n_steps) phase(fa, g + 1); // uniform
     }
 
     float* out = partial + (int64_t)id * P * P;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
-        for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int atom = atom0 + mt * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-                out[atom * P + nt * 32 + n] = acc[mt][nt][r];
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int atom = atom0 + (r >> 2) * 8 + h * 4 + (r & 3);
+            out[atom * P + nt * 32 + n] = acc[nt][r];
+        }
 }
 
 // Besides the sums over pieces (blockIdx.x < K), nb workgroups in the grid columns from K on form
@@ -616,13 +608,11 @@ hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, 
     const int max_pieces = accum_max_pieces(m, K, P);
     const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
     if (split) {
-        const int head = ((K + 1 + 16) + 3) & ~3;
-        const size_t lds = (size_t)(head + kMaxPiece) * sizeof(int) +
-                           (size_t)2 * (3 * P * 32 + 3 * (P + 1) * 32);
+        const size_t lds = aws_lds_bytes(((K + 1 + 16) + 3) & ~3);
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_wide_split_kernel<S0>), lds);
             e != hipSuccess)
             return e;
-        hipLaunchKernelGGL((accum_wide_split_kernel<S0>), dim3(max_pieces), dim3(256), lds, st, Y, K, piece,
+        hipLaunchKernelGGL((accum_wide_split_kernel<S0>), dim3(max_pieces), dim3(64 * kAwsWaves), lds, st, Y, K, piece,
                            ws.offsets, ws.perm, supp, coef, ws.partial, (int)by_pos);
     } else {
         hipLaunchKernelGGL((accum_wide_kernel<S0, false>), dim3(max_pieces), dim3(256), lds1, st, Y, K, piece,
