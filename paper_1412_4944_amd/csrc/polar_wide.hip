@@ -23,13 +23,13 @@
 //   handed over through memory with a version number; there is no barrier but one per sweep.
 //
 // What bounds it: Newton-Schulz by the 768 KiB of operands per workgroup and step from L2 (40 to 46 bytes a
-// cycle arrive; a step is 27000 cycles, 6600 of them matrix work, 3000 the barrier); Jacobi by the vector ALU
-// of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  The kernel that has
-// both needs more registers than a lane of 512 threads has: 100 of them are spilled (none in the one that has Jacobi
-// alone), 400 bytes a lane, which with 80 MB of strips is what 145 MiB written per launch are (K = 16).
+// cycle arrive; a step is 25000 cycles, 6600 of them matrix work, 3000 the barrier); Jacobi by the vector ALU
+// of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  Jacobi is called, not inlined,
+// where a block may need it after Newton-Schulz, whose operands take all registers (inlined: 100 of them spilled, K = 16 147 us
+// instead of 130); the norm and the smallest diagonal entry of a step share a barrier (130 -> 126).
 // Measured: K = 16 inside sbo_iterate 347 us (a launch per product and step, fp32 matrix instruction,
 // 20 steps enqueued, plus launches for the sum of the pieces, the Jacobi SVD that has nothing to do,
-// the operand order and the squared error: 46 launches, 400 us) -> 136 us and nothing else; K = 1 in a
+// the operand order and the squared error: 46 launches, 400 us) -> 126 us and nothing else; K = 1 in a
 // first training round 300 -> 125 us; eigenvectors of a Gram matrix (10 sweeps) 12.1 -> 1.8 ms.
 //
 // Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups, one per CU, and workgroups
@@ -239,6 +239,16 @@ __device__ __forceinline__ float row_max_nan(float x) {
     step([](float v) { return dpp_f<kDppRowMirror>(v); });
     return __builtin_bit_cast(float, u);
 }
+// Maximum over the wavefront, in all lanes.
+__device__ __forceinline__ float wave_max(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, row16_max(x));
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a0 = r[0], a1 = r[1];
+    const unsigned w = __builtin_bit_cast(unsigned, fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
+    auto q = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const unsigned b0 = q[0], b1 = q[1];
+    return fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
+}
 // Sums over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (bitwise the same in all of them).
 __device__ __forceinline__ float sum_groups(float x) {
     const unsigned u = __builtin_bit_cast(unsigned, x);
@@ -348,16 +358,6 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         out[1] = u32x4{a.mid, b.mid, c.mid, d.mid};
         out[2] = u32x4{a.lo, b.lo, c.lo, d.lo};
     };
-    // sum over the workgroup, the same in all threads; red: 256 floats, slot 0 .. 3
-    auto wg_sum = [&](float v, int slot) {
-        v = sum_groups(group_sum<16>(v));
-        if (lane == 0) red[slot * 8 + wave] = v;
-        __syncthreads();
-        float s = 0.f;
-        for (int w = 0; w < kWaves; ++w) s += red[slot * 8 + w];
-        return s;
-    };
-
     // xr[k]: rows (2 wave + k) * 16 + grp * 4 .. +3 of column t.q * 16 + c16
     f32x4 xr[2];
     {
@@ -403,20 +403,18 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
                                           lane * 8) = __builtin_bit_cast(u32x2, r);
             }
     };
-    // smallest diagonal entry of G in this workgroup's columns, in thread 0 (two tiles lie on the diagonal;
-    // both in the wavefront of tile t.q)
+    // Smallest diagonal entry of G in this workgroup's columns (two tiles lie on the diagonal, both in the wavefront of
+    // tile t.q, which leaves it in red[kDiagAt]: there after the next barrier).
     auto least_diag = [&](const f32x4 (&gm)[2]) {
+        if (wave != (t.q >> 1)) return;        // uniform
         float v = 3e38f;
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) v = gm[k][r];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
-        if (wave == (t.q >> 1) && lane == 0) red[kDiagAt] = v;
-        __syncthreads();
-        return red[kDiagAt];
+        v = -wave_max(-v);
+        if (lane == 0) red[kDiagAt] = v;
     };
     // E = I - a2 G
     auto make_e = [&](const f32x4 (&gm)[2], float a2, f32x4 (&e)[2]) {
@@ -518,7 +516,9 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
                     if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) tr = gm[k][r];
             tr = sum_groups(group_sum<16>(tr));
             if (wave == (t.q >> 1) && lane == 0) red[kDiagAt + 1] = tr;
-            least = least_diag(gm);            // (a barrier)
+            least_diag(gm);
+            __syncthreads();
+            least = red[kDiagAt];
             if (!t.sync(row_max_nan(rs), row_max_nan(r2), least, group_sum<16>(r2), red[kDiagAt + 1])) return Outcome::dead;
             const float rsmax = row_max_nan(t.value(0)), r2max = row_max_nan(t.value(1));
             // zero, infinite, NaN or overflowing input: not for this iteration
@@ -531,8 +531,13 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             for (int k = 0; k < 2; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) fr = fmaf(e[k][r], e[k][r], fr);
-            fr = wg_sum(fr, it & 1);
-            least = least_diag(gm);
+            fr = sum_groups(group_sum<16>(fr));
+            if (lane == 0) red[(it & 1) * 8 + wave] = fr;
+            least_diag(gm);
+            __syncthreads();
+            fr = 0.f;
+            for (int w = 0; w < kWaves; ++w) fr += red[(it & 1) * 8 + w];
+            least = red[kDiagAt];
             alpha = scale.next();
             // Close to the end the team meets here to learn whether this is the last step, and exchanges the
             // leading fp16 parts of E for its square.
@@ -1072,6 +1077,23 @@ __device__ __forceinline__ void jacobi_alone(const WideArgs& g, int j, const Sou
     }
 }
 
+// The same two, called: inlined beside Newton-Schulz, whose operands take all registers, they cost it 100 spilled ones.
+// Everything by value (what a call could change through a pointer would live in memory from the start).
+struct JacobiResult {
+    Outcome how;
+    Team t;
+    int tbase;
+};
+__device__ __attribute__((noinline)) JacobiResult jacobi_called(WideArgs g, int j, Source src, Team t, int* version, int tbase,
+                                                                unsigned char* mem, unsigned char* lds, float* red, int* flag) {
+    const Outcome how = jacobi(g, j, src, t, version, tbase, mem, lds, red, flag);
+    return {how, t, tbase};
+}
+__device__ __attribute__((noinline)) void jacobi_alone_called(WideArgs g, int j, Source src, unsigned char* mem,
+                                                              unsigned char* lds, float* red, int* flag) {
+    jacobi_alone(g, j, src, mem, lds, red, flag);
+}
+
 // NS: Newton-Schulz first; otherwise Jacobi for every block.
 template <bool NS>
 __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
@@ -1146,7 +1168,16 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
         }
         if (how == Outcome::left) {
             __syncthreads();
-            how = q < kJacTeam ? jacobi(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag) : Outcome::done;
+            how = Outcome::done;
+            if (q < kJacTeam) {
+                if constexpr (NS) {
+                    const JacobiResult r = jacobi_called(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag);
+                    how = r.how;
+                    eight = r.t;
+                    tbase = r.tbase;
+                } else
+                    how = jacobi(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag);
+            }
         }
         alive = how != Outcome::dead;
         if (alive) {
@@ -1173,7 +1204,8 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
         Source src;
         __syncthreads();                       // flag and the reductions are read
         if (source(j, src)) {
-            jacobi_alone(g, j, src, mem, lds, red, flag);
+            if constexpr (NS) jacobi_alone_called(g, j, src, mem, lds, red, flag);
+            else jacobi_alone(g, j, src, mem, lds, red, flag);
         } else if (tid == 0) {
             g.fallback[j] = 0;
             if (g.iters_out != nullptr) g.iters_out[j] = 0;
