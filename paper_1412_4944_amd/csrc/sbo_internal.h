@@ -149,6 +149,8 @@ struct sbo_ctx {
     int timing;
     std::vector<sbo_span> spans;     // event pool; the first n_spans are in use
     size_t n_spans;
+    double* host_sq = nullptr;       // sbo_learn: the squared error on its way to the host (pinned), from the first call on,
+    hipEvent_t sq_here = nullptr;    // and when it has arrived
 };
 
 // ---- kernel launchers (each returns a hipError_t from the launch) ----------------

@@ -202,6 +202,32 @@ def test_learn_initial_sets_as_one_batch(p, m, P0, arith):
             np.testing.assert_allclose(D[j], Q, atol=2e-5)
 
 
+@pytest.mark.parametrize("p,m", [(16, 700), (256, 1200)])
+def test_learn_stops_on_the_error(p, m):
+    """The worst-W set is prepared before the host knows whether it is wanted: a run that stops on the error returns
+    what one without room to grow does, and the context's next run is a first one."""
+    pr = synth.generate(synth.custom(f"stop_p{p}", p=p, K=3, m=m, s0=4, snr_db=20.0))
+    sets = np.arange(2 * 300, dtype=np.int32).reshape(2, 300)
+    with Sbo(p, 4, 4, m) as g:
+        t = g.torch
+        Y, ids = g.dev_f32(pr.Y), g.dev_i32(sets)
+
+        def run(K_max, target):
+            D, out = t.zeros((K_max, p, p), dtype=t.float32, device=g.dev), g.outputs(m)
+            K, hist = sbo.sbo_learn(g.ctx, Y, D, ids, 2, 200, K_max, target, *out)
+            return [K, np.asarray(hist), D[:K].cpu().numpy()] + [o.cpu().numpy() for o in out]
+
+        want, free = run(2, 0.0), run(4, 0.0)
+        assert (want[0], len(want[1]), free[0], len(free[1])) == (2, 1, 4, 3)
+        for K, target in ((2, 1e9), (3, float(free[1][:2].mean())), (4, 0.0)):
+            got = run(4, target)
+            assert got[0] == K and len(got[1]) == K - 1
+            np.testing.assert_allclose(got[1], free[1][:K - 1], rtol=1e-6)
+            if K != 3:
+                for a, b in zip(got, want if K == 2 else free):
+                    np.testing.assert_allclose(a, b, atol=2e-5)
+
+
 def test_growth_step_reduces_error():
     """Algorithm 2 steps 3-4 composed from the entry points: worst-W set -> new orthobase ->
     appended to the dictionary -> recoding.  Every signal keeps its old blocks to choose
