@@ -91,26 +91,45 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
         __syncthreads();                       // the lists are dead
     }
 
-    // Q_j -> LDS, split: unit ((mt*KS16 + ks)*3 + part)*64 + hh*32 + nn = the 8 bf16 of that part
-    // of dims ks*16 + hh*8 .. +7 of atom mt*32 + nn (atoms >= P: zeros)
-    {
-        const f32x4* D4 = reinterpret_cast<const f32x4*>(D + (int64_t)j * PP);
-        for (int g = tid; g < MT * KS16 * 64; g += NTH) {
-            const int ln = g & 63, mk = g >> 6;
-            const int nn = ln & 31, hh = ln >> 5, ks = mk % KS16, mt = mk / KS16;
-            const int atom = mt * 32 + nn;
-            f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
-            if (atom < P) {
-                v0 = D4[atom * (P / 4) + ks * 4 + hh * 2];
-                v1 = D4[atom * (P / 4) + ks * 4 + hh * 2 + 1];
-            }
-            const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
-            const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
-            u32x4* out = Qs + (mk * 3) * 64 + ln;
-            out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
-            out[64] = u32x4{a.mid, b.mid, c.mid, d.mid};
-            out[128] = u32x4{a.lo, b.lo, c.lo, d.lo};
+    const int n_tiles = (cnt + 31) >> 5;
+    // Signal ids are fetched two tiles ahead and the rows of Y one tile ahead: the loads of
+    // the next tile are issued as soon as the current rows have been split, and land while
+    // the matrix work and the selection run.  The loads are unconditional (lanes past the end
+    // of the piece read the row of signal 0 and are zeroed when consumed).  Those of the first tile are on their way
+    // before Q_j is split (50021 signals, K = 24, p = 32: 10.0 -> 9.4 us; 262144, p = 64: no difference).
+    auto tile_id = [&](int t) -> int {
+        if (t >= n_tiles || n >= min(32, cnt - t * 32)) return -1;
+        return GROUP ? ids[t * 32 + n] : perm[pos0 + t * 32 + n];
+    };
+    f32x4 raw[KS16][2];                        // this lane's dims ks*16 + h*8 .. +7 of its signal
+    auto load_rows = [&](int sid) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)max(sid, 0) * P + h * 8);
+#pragma unroll
+        for (int ks = 0; ks < KS16; ++ks) {
+            raw[ks][0] = src[ks * 4];
+            raw[ks][1] = src[ks * 4 + 1];
         }
+    };
+    int i_cur = tile_id(wave), i_next = tile_id(wave + NW);
+
+    // Q_j -> LDS, split: unit ((mt*KS16 + ks)*3 + part)*64 + hh*32 + nn = the 8 bf16 of that part
+    // of dims ks*16 + hh*8 .. +7 of atom mt*32 + nn (atoms >= P: zeros); one unit per thread
+    static_assert(MT * KS16 * 64 <= NTH, "one unit per thread");
+    const int q_ks = (tid >> 6) % KS16, q_mt = (tid >> 6) / KS16, q_atom = q_mt * 32 + n;
+    f32x4 q0 = {0.f, 0.f, 0.f, 0.f}, q1 = q0;
+    if (q_mt < MT && q_atom < P) {
+        const f32x4* D4 = reinterpret_cast<const f32x4*>(D + (int64_t)j * PP);
+        q0 = D4[q_atom * (P / 4) + q_ks * 4 + h * 2];
+        q1 = D4[q_atom * (P / 4) + q_ks * 4 + h * 2 + 1];
+    }
+    load_rows(i_cur);
+    if (q_mt < MT) {
+        const Bf16x3Pair a = split_bf16x3(q0.x, q0.y), b = split_bf16x3(q0.z, q0.w);
+        const Bf16x3Pair c = split_bf16x3(q1.x, q1.y), d = split_bf16x3(q1.z, q1.w);
+        u32x4* out = Qs + ((tid >> 6) * 3) * 64 + lane;
+        out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+        out[64] = u32x4{a.mid, b.mid, c.mid, d.mid};
+        out[128] = u32x4{a.lo, b.lo, c.lo, d.lo};
     }
     int* stage = reinterpret_cast<int*>(waves_base + (size_t)wave * WAVE_B);
     unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords);
@@ -131,26 +150,6 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
     constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
 
-    const int n_tiles = (cnt + 31) >> 5;
-    // Signal ids are fetched two tiles ahead and the rows of Y one tile ahead: the loads of
-    // the next tile are issued as soon as the current rows have been split, and land while
-    // the matrix work and the selection run.  The loads are unconditional (lanes past the end
-    // of the piece read the row of signal 0 and are zeroed when consumed).
-    auto tile_id = [&](int t) -> int {
-        if (t >= n_tiles || n >= min(32, cnt - t * 32)) return -1;
-        return GROUP ? ids[t * 32 + n] : perm[pos0 + t * 32 + n];
-    };
-    f32x4 raw[KS16][2];                        // this lane's dims ks*16 + h*8 .. +7 of its signal
-    auto load_rows = [&](int sid) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)max(sid, 0) * P + h * 8);
-#pragma unroll
-        for (int ks = 0; ks < KS16; ++ks) {
-            raw[ks][0] = src[ks * 4];
-            raw[ks][1] = src[ks * 4 + 1];
-        }
-    };
-    int i_cur = tile_id(wave), i_next = tile_id(wave + NW);
-    load_rows(i_cur);
     for (int tile = wave; tile < n_tiles; tile += NW) {
         const int64_t i = i_cur;
         const bool active = i >= 0;
