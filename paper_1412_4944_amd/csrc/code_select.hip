@@ -9,6 +9,8 @@
 // in stage 1, and the support {|c| > tau} plus the lowest-index entries equal to tau is
 // written in ascending atom order.  Exact ties in magnitude beyond the trivial one are
 // resolved by a sequential per-signal pass (rare).
+#include <algorithm>
+
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "select_tile.h"
@@ -33,22 +35,21 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     constexpr int QN = P / 8;
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-row tiles per block
     constexpr int NVL = MT * 16;               // accumulator values per lane
-    constexpr int LDC = P + 1;
     static_assert(S <= NVL, "sort width exceeds the values of one lane");
 
-    extern __shared__ int lds[];   // tile_start[K+1] | tmp[16] | pad | stage[4][...] | ctile[4][32][LDC]
+    extern __shared__ int lds[];   // tile_start[K+1] | tmp[16] | pad | stage[4][...] | ties[4][...]
     int* tile_start = lds;
     int* tmp = lds + (K + 1);
     const int head = ((K + 1 + 16) + 3) & ~3;
     int* stage_all = lds + head;
-    float* ctile_all = reinterpret_cast<float*>(stage_all + 4 * kSelectStageWords);
+    float* ties_all = reinterpret_cast<float*>(stage_all + 4 * kSelectStageWords<S>);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, n = lane & 31;
 
     if constexpr (GROUP) {                     // behind the tiles: off[K+1] | run[4][K] | list[m]
-        int* off = reinterpret_cast<int*>(ctile_all + 4 * 32 * LDC);
+        int* off = reinterpret_cast<int*>(ties_all + 4 * kSelectTieWords);
         int *run = off + (K + 1), *list = run + 4 * K;
         if (g.E != nullptr) {                  // uniform
             int* choice = list + g.m;
@@ -110,8 +111,97 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
         }
     }
 
-    tile_select<P, S>(acc, h, n, active, i, s0, ctile_all + wave * 32 * LDC,
-                             stage_all + wave * kSelectStageWords, supp, coef, err);
+    tile_select<P, S>(acc, h, n, active, i, s0, ties_all + wave * kSelectTieWords,
+                             stage_all + wave * kSelectStageWords<S>, supp, coef, err);
+}
+
+// The same with the six bf16 products (every arithmetic but SBO_ARITH_F32), for larger sets.  A workgroup takes a piece of
+// one block, whose Q_j it splits into LDS, in operand order, once; its NW wavefronts take every NW-th tile of 32 signals.
+// What bounds select_kernel is not its matrix work (4100 cycles a tile) but that every lane reads its own row of Q_j:
+// 64 lines an instruction, 16 instructions a tile, and few of them in flight; here a tile reads LDS and has 1500 cycles
+// of matrix work, and what is left is the selection's instructions (select_tile.h).  Coefficients against 64 bits, of
+// |y|: rms 2.3e-8 to 5.5e-8 (select_kernel 3.1e-8 to 8.5e-8), at most 3.1e-7 (4.6e-7).
+template <int P, int S, int NW>
+__global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* __restrict__ Y, const float* __restrict__ D,
+                                                                  int K, int s0, int piece,
+                                                                  const int32_t* __restrict__ offsets,
+                                                                  const int32_t* __restrict__ perm,
+                                                                  int32_t* __restrict__ supp, float* __restrict__ coef,
+                                                                  float* __restrict__ err) {
+    constexpr int KS16 = P / 16, MT = P / 32, Q_U = MT * KS16 * 3 * 64;
+
+    extern __shared__ int lds[];               // piece_start[K+1] | tmp[16] | pad | Qs[Q_U] | stage[NW][..] | ties[NW][..]
+    int *piece_start = lds, *tmp = lds + (K + 1);
+    const int head = ((K + 1 + 16) + 3) & ~3;
+    u32x4* Qs = reinterpret_cast<u32x4*>(lds + head);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, n = lane & 31;
+
+    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + piece - 1) / piece; }, K, piece_start, tmp);
+    const int id = blockIdx.x;
+    if (id >= piece_start[K]) return;          // uniform over the workgroup
+    const int j = upper_slot(piece_start, K, id);
+    const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
+    const int cnt = min(piece, offsets[j + 1] - pos0), n_tiles = (cnt + 31) >> 5;
+
+    // Ids two tiles ahead, rows one tile ahead (lanes past the end read the row of signal 0 and are zeroed when consumed).
+    auto tile_id = [&](int t) -> int { return t * 32 + n < cnt ? perm[pos0 + t * 32 + n] : -1; };
+    f32x4 raw[KS16][2];                        // this lane's dims ks*16 + h*8 .. +7 of its signal
+    auto load_rows = [&](int sid) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)max(sid, 0) * P + h * 8);
+#pragma unroll
+        for (int ks = 0; ks < KS16; ++ks) {
+            raw[ks][0] = src[ks * 4];
+            raw[ks][1] = src[ks * 4 + 1];
+        }
+    };
+    int i_cur = tile_id(wave), i_next = tile_id(wave + NW);
+    load_rows(i_cur);
+#pragma unroll
+    for (int g = wave; g < MT * KS16; g += NW) {
+        const int ks = g % KS16, atom = (g / KS16) * 32 + n;
+        const f32x4* src = reinterpret_cast<const f32x4*>(D + ((int64_t)j * P + atom) * P + ks * 16 + h * 8);
+        const f32x4 v[2] = {src[0], src[1]};
+        split_unit(v, Qs + g * 3 * 64 + lane, 64);
+    }
+    __syncthreads();
+
+    int* stage = lds + head + Q_U * 4 + wave * kSelectStageWords<S>;
+    float* ties = reinterpret_cast<float*>(lds + head + Q_U * 4 + NW * kSelectStageWords<S>) + wave * kSelectTieWords;
+    for (int tile = wave; tile < n_tiles; tile += NW) {
+        const int64_t i = i_cur;
+        u32x4 yq[KS16][3];
+#pragma unroll
+        for (int ks = 0; ks < KS16; ++ks) {
+            if (i < 0) raw[ks][0] = raw[ks][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            split_unit(raw[ks], yq[ks], 1);
+        }
+        i_cur = i_next;
+        i_next = tile_id(tile + 2 * NW);
+        load_rows(i_cur);
+
+        constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0};      // smallest products first
+        f32x16 acc[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x16{};
+#pragma unroll
+        for (int ks = 0; ks < KS16; ++ks) {
+            u32x4 a[MT][3];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) a[mt][pl] = Qs[((mt * KS16 + ks) * 3 + pl) * 64 + lane];
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[mt][TA[t]]),
+                                                                      __builtin_bit_cast(bf16x8, yq[ks][TB[t]]),
+                                                                      acc[mt], 0, 0, 0);
+        }
+        tile_select<P, S>(acc, h, n, i >= 0, i, s0, ties, stage, supp, coef, err);
+    }
 }
 
 // Variant for p > 64.  The p coefficients of a signal no longer fit the registers of a
@@ -490,18 +580,37 @@ hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int 
     return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
 }
 
+// From here on select_split_kernel (p = 32, 64), four wavefronts and up to 4 tiles for each: the fewest with which all
+// workgroups are there at once.  Against select_kernel (us): p = 64, 20000 signals 9.6 / 9.4, 65537 16.3 / 19.0, 100003
+// (K = 64) 21.6 / 26.4, 262144 33.5 / 48.9, 2^20 (K = 128) 140 / 215; p = 32, 50000 - 60000 the same, 300000 21 / 24.5, 10^6
+// 53 / 64; p = 16 no faster at any size.  With one tile for each wavefront 262144 signals took 43 us, with eight of them
+// (two workgroups on a CU) 36.6 to 43.
+constexpr int64_t kSplitMinSignals = 32768;
+
 template <int P, int S>
 hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws,
-                     int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, hipStream_t st) {
+                     int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
-    size_t lds = ((((K + 1 + 16) + 3) & ~3) + 4 * kSelectStageWords) * sizeof(int) +
-                 4 * 32 * (P + 1) * sizeof(float);
+    size_t lds = ((((K + 1 + 16) + 3) & ~3) + 4 * (kSelectStageWords<S> + kSelectTieWords)) * sizeof(int);
     if (blk != nullptr) {
         lds += (5 * K + 1 + (choose ? 2 : 1) * m) * sizeof(int);       // at most 60 KiB in all (choose: K <= 64)
         hipLaunchKernelGGL((select_kernel<P, S, true>), grid, dim3(256), lds, st, Y, D, K, s0, nullptr, nullptr, supp,
                            coef, err,
                            GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count, choose ? ws.part_E : nullptr, blk});
+        return hipGetLastError();
+    }
+    if constexpr (P >= 32) if (split && m >= kSplitMinSignals) {
+        constexpr int NW = 4, Q_U = P / 32 * (P / 16) * 3 * 64;
+        const int64_t resident = 256 * (P == 64 ? 3 : 4) - K / 2;          // less the blocks' unfinished pieces
+        const int tiles = (int)std::min<int64_t>(4, (m + 32 * NW * resident - 1) / (32 * NW * resident));
+        const int piece = 32 * NW * tiles;
+        lds = ((((K + 1 + 16) + 3) & ~3) + 4 * Q_U + NW * (kSelectStageWords<S> + kSelectTieWords)) * sizeof(int);
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_split_kernel<P, S, NW>), 160 * 1024);
+            e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL((select_split_kernel<P, S, NW>), dim3((unsigned)((m + piece - 1) / piece + K)), dim3(64 * NW), lds,
+                           st, Y, D, K, s0, piece, ws.offsets, ws.perm, supp, coef, err);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((select_kernel<P, S, false>), grid, dim3(256), lds, st, Y, D, K, s0, ws.offsets,
@@ -511,12 +620,12 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
 
 template <int P>
 hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
-                    int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, hipStream_t st) {
-    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
-    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
-    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
-    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
-    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, st);
+                    int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
+    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
+    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
+    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
+    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
+    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
 }
 
 }  // namespace
@@ -531,9 +640,9 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
         if (e != hipSuccess) return e;
     }
     switch (p) {
-        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
-        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
-        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, st);
+        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
+        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
+        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
         case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, by_pos, st);
         default: return hipErrorInvalidValue;
     }

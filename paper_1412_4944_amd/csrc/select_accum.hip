@@ -35,6 +35,14 @@ namespace {
 
 constexpr int kSaWaves = 8;
 
+// LDS of a wavefront: the stage and the operand tiles (or the scratch for ties); at the end a copy of its accumulators.
+template <int P, int S>
+constexpr int sa_wave_bytes() {
+    constexpr int MT = P >= 32 ? P / 32 : 1, ops = 6 * (MT * 32 + 1) * 32, ct = kSelectTieWords * 4;
+    constexpr int use = kSelectStageWords<S> * 4 + (ops > ct ? ops : ct), copy = MT * MT * 4 * 64 * 16;
+    return use > copy ? use : copy;
+}
+
 // GROUP: every workgroup groups the (small) set itself, as select_kernel does: no launch for it (1024 signals, K = 4,
 // p = 16: 5.4 + 6.6 us -> 9.2).
 template <int P, int S, bool GROUP>
@@ -49,10 +57,11 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     constexpr int PP = P * P;
     constexpr int Q_U = MT * KS16 * 3 * 64;    // Q_j in split operand order, 16-byte units
     constexpr int PLANE_B = (ROWS + 1) * 32;   // bytes of one part of a transposed operand tile (+ a dummy row)
-    constexpr int CT_B = 32 * (P + 1) * 4;     // tie-breaking scratch of tile_select
+    constexpr int CT_B = kSelectTieWords * 4;           // tie-breaking scratch of tile_select
     constexpr int OPS_B = 6 * PLANE_B;         // x tile (3 parts) + y tile (3 parts)
     constexpr int REGION_B = (OPS_B > CT_B ? OPS_B : CT_B);
-    constexpr int WAVE_B = kSelectStageWords * 4 + REGION_B;
+    constexpr int WAVE_B = sa_wave_bytes<P, S>();
+    static_assert(kSelectStageWords<S> * 4 + REGION_B <= WAVE_B, "stage and region");
     constexpr int YU = P / 8 - 1 < 7 ? P / 8 - 1 : 7;      // of a signal's 16-byte units
     constexpr int NE = (S + 3) / 4;            // kept entries per lane and half tile
 
@@ -132,7 +141,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
         out[128] = u32x4{a.lo, b.lo, c.lo, d.lo};
     }
     int* stage = reinterpret_cast<int*>(waves_base + (size_t)wave * WAVE_B);
-    unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords);
+    unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords<S>);
     unsigned char* xt = region;                // [3 parts][ROWS atoms][16 signals] bf16
     unsigned char* yt = region + 3 * PLANE_B;  // [3 parts][16 signals][P dims] bf16
     // the x tile starts out zero (and is left zero by every tile)
@@ -232,8 +241,8 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
                 for (int t = 0; t < NE; ++t) {
                     const int pos = 4 * t + (lane >> 4);
                     const bool have = row < cnt_t && pos < s0;
-                    const int atom = stage[stage_idx(row, 0, have ? pos : 0)];
-                    const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx(row, 1, have ? pos : 0)]));
+                    const int atom = stage[stage_idx<S>(row, 0, have ? pos : 0)];
+                    const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx<S>(row, 1, have ? pos : 0)]));
                     at_[t] = tr_off(have ? (atom & (ROWS - 1)) : ROWS, sx);   // row ROWS: nobody reads it
                     *reinterpret_cast<unsigned short*>(xt + at_[t]) = (unsigned short)(w.hi >> 16);
                     *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = (unsigned short)(w.mid >> 16);
@@ -325,9 +334,7 @@ template <int P, int S>
 hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws,
                      int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    constexpr int ROWS = MT * 32;
-    constexpr size_t ct_b = (size_t)32 * (P + 1) * 4, ops_b = (size_t)6 * (ROWS + 1) * 32;
-    constexpr size_t wave_b = (size_t)kSelectStageWords * 4 + (ops_b > ct_b ? ops_b : ct_b);
+    constexpr size_t wave_b = sa_wave_bytes<P, S>();
     const int piece = accum_piece(m, K, P);
     const int max_pieces = accum_max_pieces(m, K, P);
     const int head = ((K + 1 + 16) + 3) & ~3;

@@ -12,8 +12,8 @@ namespace sbo {
 // lowest-index entries equal to tau in ascending atom order, the coefficients and the
 // residual (sum of the dropped c^2) of signal i (original index; active = lane has a
 // signal).  Exact magnitude ties beyond the trivial one are resolved by a sequential
-// per-signal pass through the wave-private LDS tile ct[32][P+1].  The (atom, coefficient)
-// rows are first compacted in the wave-private LDS area stage[2][16][32] (words) and then
+// per-signal pass through the wave-private LDS tile ct, 16 atoms at a time.  The (atom, coefficient)
+// rows are first compacted in the wave-private LDS area stage[2][S][32] (words) and then
 // written with one or a few wide stores per lane (lane half 0: supp row, half 1: coef row),
 // because scattered 4-byte stores to rows in original signal order are what this step
 // would otherwise wait on.  ct is touched only on the tie path (*used_ct is then set).  On return the compacted rows
@@ -22,12 +22,26 @@ namespace sbo {
 //
 // What bounds it: instruction issue (it was 7500 cycles a tile of 32 signals for a wavefront, most of them for a
 // branch and two swizzled addresses per entry; positions now come from packed counts, and an entry is a
-// comparison, an address and two predicated stores).  select_kernel, 100003 signals, p = 64: 32.8 -> 29.4 us.
-constexpr int kSelectStageWords = 32 * 2 * 16;
+// comparison, an address and two predicated stores: 100003 signals, p = 64: 32.8 -> 29.4 us).
+// Both areas are as small as that: with 16 entries and all p coefficients of a signal in them (12 KiB a wavefront at
+// p = 64) LDS held three wavefronts of select_kernel on a SIMD, and a few workgroups a second round (29.8 -> 26.3 us).
+template <int S>
+constexpr int kSelectStageWords = 32 * 2 * S;
+constexpr int kSelectTieWords = 32 * (16 + 1);         // [signal][atom], a column of padding
 
-// Word index of entry `pos` (< 16) of signal row n in the stage area; kind 0 = atom, 1 =
+// 8 consecutive values as the three bf16 parts of an operand unit: out[0], out[step], out[2 step].
+__device__ __forceinline__ void split_unit(const f32x4* v, u32x4* out, int step) {
+    const Bf16x3Pair a = split_bf16x3(v[0].x, v[0].y), b = split_bf16x3(v[0].z, v[0].w);
+    const Bf16x3Pair c = split_bf16x3(v[1].x, v[1].y), d = split_bf16x3(v[1].z, v[1].w);
+    out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+    out[step] = u32x4{a.mid, b.mid, c.mid, d.mid};
+    out[2 * step] = u32x4{a.lo, b.lo, c.lo, d.lo};
+}
+
+// Word index of entry `pos` (< S) of signal row n in the stage area; kind 0 = atom, 1 =
 // coefficient bits.  All lanes n of one entry are neighbours.
-__device__ __forceinline__ int stage_idx(int n, int kind, int pos) { return kind * 512 + pos * 32 + n; }
+template <int S>
+__device__ __forceinline__ int stage_idx(int n, int kind, int pos) { return (kind * S + pos) * 32 + n; }
 
 // The value in the other lane of the pair (all lanes active).
 __device__ __forceinline__ unsigned pair_other(unsigned x, int h) {
@@ -47,7 +61,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                                             float* __restrict__ err, bool* used_ct = nullptr) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
     constexpr int NVL = MT * 16;
-    constexpr int LDC = P + 1;
+    constexpr int LDC = kSelectTieWords / 32;
     static_assert(P <= 64, "p = 256 selects in select_wide_split_kernel");
     static_assert(S <= NVL, "sort width exceeds the values of one lane");
     float c[NVL], mag[NVL];
@@ -110,9 +124,9 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                     const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + h * 4 + (f & 3);
                     const bool keep = mag[f] >= keep_from;
                     if (keep) {
-                        int* at = stage + stage_idx(n, 0, (int)pos);
+                        int* at = stage + stage_idx<S>(n, 0, (int)pos);
                         at[0] = atom;
-                        at[512] = __builtin_bit_cast(int, c[f]);
+                        at[S * 32] = __builtin_bit_cast(int, c[f]);
                     }
                     pos += keep;
                     const float rest = keep || atom >= P ? 0.f : c[f];
@@ -125,40 +139,43 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     } else {
         // Exact magnitude ties: walk each signal's coefficients in atom order.
         if (used_ct != nullptr) *used_ct = true;
-#pragma unroll
-        for (int f = 0; f < NVL; ++f) {
-            const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + h * 4 + (f & 3);
-            if (atom < P) ct[n * LDC + atom] = c[f];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         int gt = 0;
 #pragma unroll
         for (int f = 0; f < NVL; ++f) gt += mag[f] > tau;
         gt += pair_other(gt, h);
         const int need = s0 - gt;              // entries equal to tau still to take (>= 1)
-        if (active && h == 0) {
-            int pos = 0, taken_eq = 0;
-            float dropped = 0.f;
-            for (int k = 0; k < P; ++k) {
-                const float v = ct[n * LDC + k];
-                const float a = fabsf(v);
-                bool take = a > tau;
-                if (!take && a == tau && taken_eq < need) {
-                    take = true;
-                    ++taken_eq;
-                }
-                if (take && pos < s0) {
-                    stage[stage_idx(n, 0, pos)] = k;
-                    stage[stage_idx(n, 1, pos)] = __builtin_bit_cast(int, v);
-                    ++pos;
-                } else {
-                    dropped += v * v;
+        int pos = 0, taken_eq = 0;
+        float dropped = 0.f;
+#pragma unroll
+        for (int k0 = 0; k0 < P; k0 += 16) {
+            __builtin_amdgcn_wave_barrier();   // the atoms before these have been walked
+#pragma unroll
+            for (int r = 0; r < 8; ++r) ct[n * LDC + (r >> 2) * 8 + h * 4 + (r & 3)] = c[k0 / 2 + r];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (active && h == 0) {
+#pragma unroll 4
+                for (int k = 0; k < 16; ++k) {
+                    const float v = ct[n * LDC + k];
+                    const float a = fabsf(v);
+                    bool take = a > tau;
+                    if (!take && a == tau && taken_eq < need) {
+                        take = true;
+                        ++taken_eq;
+                    }
+                    if (take && pos < s0) {
+                        stage[stage_idx<S>(n, 0, pos)] = k0 + k;
+                        stage[stage_idx<S>(n, 1, pos)] = __builtin_bit_cast(int, v);
+                        ++pos;
+                    } else {
+                        dropped += v * v;
+                    }
                 }
             }
-            err[i] = dropped;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         }
+        if (active && h == 0) err[i] = dropped;
     }
 
     // compact rows -> global memory
@@ -167,7 +184,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (active) {
         int* dst = (h ? reinterpret_cast<int*>(coef) : supp) + i * s0;
-        const int* row = stage + stage_idx(n, h, 0);
+        const int* row = stage + stage_idx<S>(n, h, 0);
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         typedef int i32x2 __attribute__((ext_vector_type(2)));
         if ((s0 & 3) == 0) {

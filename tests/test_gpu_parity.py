@@ -108,6 +108,31 @@ def test_code_p256_selection(s0):
         assert a[1][40].tolist() == list(range(s0)) and (a[2][40] == 1.0).all()
 
 
+@pytest.mark.parametrize("p,K,s0,m", [(64, 3, 5, 32768), (64, 8, 1, 33001), (64, 4, 8, 100003), (64, 1024, 12, 100003),
+                                      (32, 5, 16, 32768), (32, 3, 2, 150001)])
+def test_code_larger_sets_selection(p, K, s0, m):
+    """From 32768 signals on the support is selected by workgroups that share a block, one to four tiles to a wavefront:
+    601 signals (zero ones, exact ties) over and over, each copy the same and the first as the oracle has it."""
+    n = 601
+    rng = np.random.default_rng(57)
+    D = np.stack([np.eye(p)] + [synth.random_onb(rng, p).T for _ in range(K - 1)]).astype(np.float32)
+    base = rng.standard_normal((n, p)).astype(np.float32)
+    base[0] = 0.0
+    base[1:40] = rng.integers(-2, 3, size=(39, p))        # many ties in the first block
+    base[40] = 1.0
+    base[41:60] *= np.float32(1e-12)
+    idx = np.arange(m) % n
+    print(f"case p={p} K={K} s0={s0} m={m}", flush=True)
+    with Sbo(p, K, s0, m) as g:
+        out = g.code(base[idx], D)
+    first = [v[:n] for v in out]
+    for x, y in zip(out[:3], first):
+        assert np.array_equal(x, y[idx])
+    # (a tile with a tie adds the up to p squares up in another order: each sum is off by at most p 2^-24 of itself)
+    np.testing.assert_allclose(out[3], first[3][idx], rtol=2 * p * 2.0 ** -24)
+    compare_code(base, D, s0, orc.o_code(base, D, s0), first, max_exempt_frac=0.5 if K < 1024 else 0.9)
+
+
 @pytest.mark.parametrize("p,K,s0", [(64, 5, 8), (16, 3, 4), (256, 2, 12)])
 @pytest.mark.parametrize("arith", ARITH)
 def test_code_over_signal_scales_and_dynamic_range(arith, p, K, s0):
