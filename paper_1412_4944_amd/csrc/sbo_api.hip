@@ -56,7 +56,6 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.sel_state = (int32_t*)take((size_t)4 * 2 * 4);
     w.sel_cnt = (int32_t*)take(sel_chunks * 2 * 4);
     w.sel_base = (int32_t*)take(sel_chunks * 2 * 4);
-    w.sel_ids = (int32_t*)take((size_t)m_max * 4);
     w.sq_out = (double*)take(8);
     w.sq_counter = (int32_t*)take(4);
     w.sweeps = (int32_t*)take((size_t)K * 4);
@@ -544,8 +543,7 @@ static int wait_rmse(sbo_ctx* c, int64_t m, double* out) {
 
 // What a new orthobase starts from, in the workspace: the worst-W set as one block and its Gram matrix.
 static int prepare_growth(sbo_ctx* c, const float* Y, const float* err, int64_t m, int64_t W) {
-    SBO_HIP(launch_worst(err, m, W, c->ws, c->ws.sel_ids, c->stream));
-    SBO_HIP(launch_single_block(c->ws.sel_ids, W, m, c->ws, c->stream));
+    SBO_HIP(launch_worst(err, m, W, c->ws, c->ws.perm, c->stream, true));
     SBO_HIP(launch_gram(c->p, 1, Y, W, c->ws, c->ws.M, c->stream));
     return SBO_OK;
 }
@@ -607,8 +605,8 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
     rc = run_code(c, Y, m, D, blk, supp, coef, err);
     if (rc) return fail(rc);
     // The GPU goes on with the next growth step's worst-W set while the error travels to the host, which decides whether
-    // there is to be one.  p = 64, m = 65,536, K 8 -> 20: 6,958 -> 6,408 us, a wait for the host and for the first of
-    // ten small launches less per orthobase; a call that stops on the error pays some 40 us for a set it does not use.
+    // there is to be one.  p = 64, m = 32768, K = 5 to 16: 6958 -> 6408 us (the host's answer, and the launches after
+    // it, were waited for once per orthobase); a call that stops on the error pays some 40 us for a set it does not use.
     int n = 0;
     auto next_error = [&]() {
         int e = send_sq(c, err, m);

@@ -107,7 +107,6 @@ struct Workspace {
     int32_t* sel_state;    // [4][2] (key prefix, entries still to take) after each pass
     int32_t* sel_cnt;      // [ceil(m_max / kSelChunk)][2] entries above / equal to the threshold
     int32_t* sel_base;     // same shape: exclusive sums of sel_cnt over the chunks
-    int32_t* sel_ids;      // [m_max] worst-W set inside sbo_learn
     double* sq_out;        // [1] squared-error total inside sbo_learn
     int32_t* sweeps;       // [K] most recent SVD stage: Jacobi sweeps, or minus the Newton-Schulz steps
     int32_t* ns_fallback;  // [K] 1 = Newton-Schulz left the block to the Jacobi kernel
@@ -323,6 +322,6 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
 
 // ids[0..W) = the W signals with the largest err (ties: lower index), ascending.
 hipError_t launch_worst(const float* err, int64_t m, int64_t W, const Workspace& ws, int32_t* ids,
-                        hipStream_t st);
+                        hipStream_t st, bool block = false);
 
 }  // namespace sbo

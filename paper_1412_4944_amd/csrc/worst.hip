@@ -12,6 +12,10 @@
 // No kernel waits on another workgroup: the digit found by pass k is recomputed from the
 // finished histogram of pass k by every workgroup of the next launch (and stored once for
 // the launch after that).
+//
+// Up to kOneMax entries one workgroup does all of it in one launch, the keys in its registers (us a
+// call, one launch / eight: 1000 entries 8.8 / 24.1, 5000 9.0 / 27.4, 16384 13.8 / 28.8, 32768 22.6 / 29.4; with 64 keys to a
+// lane, which do not fit the registers, 65536 49 / 29).
 #include "sbo_internal.h"
 #include "device_utils.h"
 
@@ -209,10 +213,131 @@ __global__ __launch_bounds__(kSelThreads) void worst_emit_kernel(const float* __
     }
 }
 
+// The same by one workgroup.  Wavefront w holds the entries 64 Q w .. 64 Q (w + 1) - 1, 64 consecutive ones per q, so that
+// ballots count them in index order.  Lanes l and l + 32 count in a copy of their own of the 256 bins, in a bank of its
+// own: the leading digits (sign and exponent) are nearly all the same.
+// offsets != nullptr: also the set as the grouping of one block (launch_single_block).
+constexpr int kOneWaves = 16;
+constexpr int64_t kOneMax = 64 * 32 * kOneWaves;
+
+template <int Q>
+__global__ __launch_bounds__(64 * kOneWaves) void worst_one_kernel(const float* __restrict__ err, int m, int W,
+                                                                   int32_t* __restrict__ ids, int32_t* __restrict__ counts,
+                                                                   int32_t* __restrict__ offsets) {
+    constexpr int NTH = 64 * kOneWaves;
+    __shared__ int hist[kBins * 32];
+    __shared__ int bin[kBins];
+    __shared__ int st[2];
+    __shared__ int n_gt[kOneWaves], n_eq[kOneWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = wave * 64 * Q + lane;       // entry q of this lane: i0 + 64 q
+
+    uint32_t key[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) key[q] = order_key(err[min(i0 + 64 * q, m - 1)]);
+    if (offsets != nullptr && tid == 0) {
+        counts[0] = W;
+        offsets[0] = 0;
+        offsets[1] = W;
+    }
+
+    uint32_t prefix = 0;
+    int remaining = W;
+#pragma unroll 1
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 24 - 8 * pass;
+        for (int e = tid; e < kBins * 32; e += NTH) hist[e] = 0;
+        if (tid < 2) st[tid] = tid;            // defined whatever happens
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const bool in = i0 + 64 * q < m && (pass == 0 || (key[q] >> 8 >> shift) == prefix);
+            if (in) atomicAdd(&hist[((key[q] >> shift) & 255u) * 32 + (lane & 31)], 1);
+        }
+        __syncthreads();
+        {                                      // four threads to a bin, each in other banks than its neighbours
+            const int b = tid >> 2;
+            int s = 0;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) s += hist[b * 32 + (tid & 3) * 8 + ((c + b) & 7)];
+            s += __shfl_xor(s, 1, 64);
+            s += __shfl_xor(s, 2, 64);
+            if ((tid & 3) == 0) bin[b] = s;
+        }
+        __syncthreads();
+        if (wave == 0) {                       // digits 255 - 4 lane .. 252 - 4 lane
+            int own[4], sum = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum += own[e] = bin[kBins - 1 - 4 * lane - e];
+            int above = sum;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(above, o, 64);
+                if (lane >= o) above += x;
+            }
+            above -= sum;                      // entries with a higher digit
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (above < remaining && remaining <= above + own[e]) {
+                    st[0] = (int)((prefix << 8) | (uint32_t)(kBins - 1 - 4 * lane - e));
+                    st[1] = remaining - above;
+                }
+                above += own[e];
+            }
+        }
+        __syncthreads();
+        prefix = (uint32_t)st[0];
+        remaining = st[1];
+        __syncthreads();                       // (st is set anew by the next pass)
+    }
+
+    // the keys above `prefix` and the first `remaining` equal to it, in index order
+    int gt = 0, eq = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const bool in = i0 + 64 * q < m;
+        gt += __popcll(__ballot(in && key[q] > prefix));
+        eq += __popcll(__ballot(in && key[q] == prefix));
+    }
+    if (lane == 0) {
+        n_gt[wave] = gt;
+        n_eq[wave] = eq;
+    }
+    __syncthreads();
+    int pos = 0, eq_before = 0;
+    for (int w = 0; w < wave; ++w) {
+        pos += n_gt[w];
+        eq_before += n_eq[w];
+    }
+    pos += min(eq_before, remaining);
+    const unsigned long long before = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const bool in = i0 + 64 * q < m, is_eq = in && key[q] == prefix;
+        const unsigned long long eqs = __ballot(is_eq);
+        const bool take = (in && key[q] > prefix) || (is_eq && eq_before + __popcll(eqs & before) < remaining);
+        const unsigned long long takes = __ballot(take);
+        const int at = pos + __popcll(takes & before);
+        if (take && at < W) ids[at] = i0 + 64 * q;         // at < W always (as in worst_emit_kernel)
+        pos += __popcll(takes);
+        eq_before += __popcll(eqs);
+    }
+}
+
 }  // namespace
 
+// block: the set also becomes the grouping of one block (ids: ws.perm), as launch_single_block would make it.
 hipError_t launch_worst(const float* err, int64_t m, int64_t W, const Workspace& ws, int32_t* ids,
-                        hipStream_t st) {
+                        hipStream_t st, bool block) {
+    if (block && ids != ws.perm) return hipErrorInvalidValue;
+    if (m <= kOneMax) {
+        int32_t *counts = block ? ws.counts : nullptr, *offsets = block ? ws.offsets : nullptr;
+        const auto one = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(64 * kOneWaves), 0, st, err, (int)m, (int)W, ids, counts, offsets);
+            return hipGetLastError();
+        };
+        return m <= kOneMax / 4 ? one(worst_one_kernel<8>) : m <= kOneMax / 2 ? one(worst_one_kernel<16>) : one(worst_one_kernel<32>);
+    }
     const int n_chunks = (int)((m + kSelChunk - 1) / kSelChunk);
     const int hist_grid = n_chunks < 1024 ? n_chunks : 1024;
     hipLaunchKernelGGL(worst_clear_kernel, dim3(1), dim3(kSelThreads), 0, st, ws.sel_hist);
@@ -225,6 +350,7 @@ hipError_t launch_worst(const float* err, int64_t m, int64_t W, const Workspace&
                        ws.sel_base);
     hipLaunchKernelGGL(worst_emit_kernel, dim3(n_chunks), dim3(kSelThreads), 0, st, err, (int)m, (int)W,
                        ws.sel_state, ws.sel_base, ids);
+    if (block) return launch_single_block(ids, W, m, ws, st);
     return hipGetLastError();
 }
 

@@ -36,6 +36,24 @@ def test_worst_set_bit_exact(m):
     assert abs(total - err.astype(np.float64).sum()) <= 1e-12 * max(total, 1e-300)
 
 
+@pytest.mark.parametrize("m", [2, 8191, 8192, 8193, 16384, 16385, 32768, 32769])
+def test_worst_set_at_the_sizes_of_its_kernels(m):
+    """One workgroup up to 32768 entries, 8, 16 or 32 of them to a lane; infinities, both zeros and runs of ties."""
+    rng = np.random.default_rng(43 + m)
+    err = rng.standard_normal(m).astype(np.float32) ** 2
+    err[rng.integers(0, m, m // 3)] = err[m // 2]
+    err[::97] = 0.0
+    err[1::97] = -0.0
+    err[m - 1] = np.inf
+    # descending by the order of the bits (-0 below +0), ascending index among equals
+    bits = err.view(np.uint32).astype(np.int64)
+    order = np.argsort(-np.where(bits >> 31, 0xffffffff - bits, bits + 0x80000000), kind="stable")
+    print(f"case m={m}", flush=True)
+    with Sbo(16, 2, 2, max(m, 16)) as g:
+        for W in sorted({1, m // 2, m // 2 + 1, m - 1, m}):
+            assert np.array_equal(g.worst(err, W), np.sort(order[:W])), f"m={m} W={W}"
+
+
 def test_worst_set_all_equal_and_real_residuals():
     pr = _problem("patch8", m=9000)
     cfg = pr.cfg
