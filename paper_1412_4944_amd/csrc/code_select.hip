@@ -200,6 +200,21 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
                                                                       __builtin_bit_cast(bf16x8, yq[ks][TB[t]]),
                                                                       acc[mt], 0, 0, 0);
         }
+        // An infinite entry has no three parts (infinity less itself): the coefficients of such a signal in fp32.
+        const bool bad = acc[0][0] != acc[0][0];
+        if (__any(bad)) {                      // uniform, rare
+            const float* row = Y + max(i, (int64_t)0) * P;
+#pragma unroll 1
+            for (int d = 0; d < P; ++d) {
+                const float y = row[d];
+#pragma unroll
+                for (int f = 0; f < MT * 16; ++f) {
+                    const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + h * 4 + (f & 3);
+                    const float c = fmaf(D[((int64_t)j * P + atom) * P + d], y, d == 0 ? 0.f : acc[f >> 4][f & 15]);
+                    acc[f >> 4][f & 15] = bad ? c : acc[f >> 4][f & 15];
+                }
+            }
+        }
         tile_select<P, S>(acc, h, n, i >= 0, i, s0, ties, stage, supp, coef, err);
     }
 }

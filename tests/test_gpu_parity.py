@@ -125,9 +125,16 @@ def test_code_larger_sets_selection(p, K, s0, m):
     print(f"case p={p} K={K} s0={s0} m={m}", flush=True)
     with Sbo(p, K, s0, m) as g:
         out = g.code(base[idx], D)
+        Y = base[idx]
+        Y[70, p - 1] = np.inf
+        inf = g.code(Y, D)
     first = [v[:n] for v in out]
     for x, y in zip(out[:3], first):
         assert np.array_equal(x, y[idx])
+    # an infinite entry: all products of that signal are infinite (the identity's others 0 * inf), the others as before
+    assert all(np.array_equal(np.delete(x, 70, 0), np.delete(y, 70, 0)) for x, y in zip(inf[:3], out))
+    if inf[0][70] != 0:
+        assert inf[1][70].tolist() == list(range(s0)) and np.isinf(inf[2][70]).all() and (p == s0 or np.isinf(inf[3][70]))
     # (a tile with a tie adds the up to p squares up in another order: each sum is off by at most p 2^-24 of itself)
     np.testing.assert_allclose(out[3], first[3][idx], rtol=2 * p * 2.0 ** -24)
     compare_code(base, D, s0, orc.o_code(base, D, s0), first, max_exempt_frac=0.5 if K < 1024 else 0.9)
