@@ -52,6 +52,19 @@ def test_worst_set_at_the_sizes_of_its_kernels(m):
     with Sbo(16, 2, 2, max(m, 16)) as g:
         for W in sorted({1, m // 2, m // 2 + 1, m - 1, m}):
             assert np.array_equal(g.worst(err, W), np.sort(order[:W])), f"m={m} W={W}"
+        err[m - 1] = 1.0
+        assert abs(g.sqerr(err) - err.astype(np.float64).sum()) <= 1e-12 * err.astype(np.float64).sum()
+
+
+@pytest.mark.parametrize("n", [1, 4096, 4097])
+def test_new_base_error_total_at_the_sizes_of_its_kernels(n):
+    """The error total of a round over a listed set, by one workgroup up to 4096 signals: the sum of the set's errors."""
+    pr = synth.generate(synth.custom("sq", p=16, K=2, m=6000, s0=3, snr_db=20.0))
+    ids = np.random.default_rng(71).permutation(6000)[:n].astype(np.int32)
+    with Sbo(16, 2, 3, 6000) as g:
+        Q, supp, coef, err, sq = g.new_base(pr.Y, ids, 1)
+        total = err[ids].astype(np.float64).sum()
+    assert abs(sq[0] - total) <= 1e-12 * max(total, 1e-300)
 
 
 def test_worst_set_all_equal_and_real_residuals():
