@@ -686,15 +686,22 @@ size_t eigen_scratch_bytes(int p) {
     }
 }
 
+// As many matrices at a time as the scratch holds.
 hipError_t launch_eigen(int p, int K, const float* M, float* D, float* sv, const Workspace& ws, hipStream_t st) {
-    const EigScratch s = {ws.eig, ws.eig_left};
-    switch (p) {
-        case 16: return launch_eigen_p<16>(K, M, D, sv, s, st);
-        case 32: return launch_eigen_p<32>(K, M, D, sv, s, st);
-        case 64: return launch_eigen_p<64>(K, M, D, sv, s, st);
-        case 256: return launch_eigen_p<256>(K, M, D, sv, s, st);
-        default: return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    for (int j = 0; j < K && e == hipSuccess; j += ws.eig_room) {
+        const int n = K - j < ws.eig_room ? K - j : ws.eig_room;
+        const size_t at = (size_t)j * p * p;
+        const EigScratch s = {ws.eig, ws.eig_left + j};
+        switch (p) {
+            case 16: e = launch_eigen_p<16>(n, M + at, D + at, sv + (size_t)j * p, s, st); break;
+            case 32: e = launch_eigen_p<32>(n, M + at, D + at, sv + (size_t)j * p, s, st); break;
+            case 64: e = launch_eigen_p<64>(n, M + at, D + at, sv + (size_t)j * p, s, st); break;
+            case 256: e = launch_eigen_p<256>(n, M + at, D + at, sv + (size_t)j * p, s, st); break;
+            default: return hipErrorInvalidValue;
+        }
     }
+    return e;
 }
 
 }  // namespace sbo

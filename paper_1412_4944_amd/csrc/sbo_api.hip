@@ -45,11 +45,15 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     const size_t direct = (size_t)(K < kDirectMaxK ? K : kDirectMaxK) * (size_t)(m_max < kDirectMaxSignals ? m_max : kDirectMaxSignals);
     w.part_E = (float*)take((direct > kEnergySplitRows * split_m ? direct : kEnergySplitRows * split_m) * 4);
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
-    w.partial = (float*)take((size_t)max_pieces_bound(m_max, K, p) * p * p * 4);
+    // The eigenvectors of a Gram matrix are computed when the pieces of that matrix have been summed: same memory.
+    size_t partial = (size_t)max_pieces_bound(m_max, K, p) * p * p * 4;
+    if (partial < eigen_scratch_bytes(p)) partial = eigen_scratch_bytes(p);
+    w.partial = (float*)take(partial);
+    w.eig = (unsigned char*)w.partial;
+    w.eig_room = (int)(partial / eigen_scratch_bytes(p) < (size_t)K ? partial / eigen_scratch_bytes(p) : (size_t)K);
     w.M = (float*)take((size_t)K * p * p * 4);
     w.wide = (float*)take(p > 64 ? polar_wide_scratch_bytes(K) : 0);
     w.wide_sync = (int*)take(p > 64 ? polar_wide_sync_bytes(K) : 0);
-    w.eig = (unsigned char*)take((size_t)K * eigen_scratch_bytes(p));
     w.eig_left = (int32_t*)take((size_t)K * 4);
     const size_t sel_chunks = (size_t)((m_max + kSelChunk - 1) / kSelChunk);
     w.sel_hist = (int32_t*)take((size_t)4 * 256 * 4);

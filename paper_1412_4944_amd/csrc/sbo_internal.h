@@ -100,7 +100,8 @@ struct Workspace {
     float* wide;           // p > 64 only: exchange memory of polar_wide.hip (polar_wide_scratch_bytes)
     int* wide_sync;        // p > 64 only: its counters (0 between launches)
     // eigenvectors of Gram matrices
-    unsigned char* eig;    // [K] x eigen_scratch_bytes
+    unsigned char* eig;    // [eig_room] x eigen_scratch_bytes, in the memory of `partial`
+    int eig_room;          // matrices at a time (>= 1)
     int32_t* eig_left;     // [K] not 0: left to the Jacobi SVD
     // worst-W selection
     int32_t* sel_hist;     // [4][256] digit histograms of the radix select
@@ -266,7 +267,7 @@ hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, flo
                         hipStream_t st);
 
 // Eigenvectors by tridiagonalisation (eigen.hip), as eigen mode above; ws.eig_left[j] != 0 where D[j] and sv[j] are
-// not to be used.
+// not to be used.  Overwrites ws.partial.
 size_t eigen_scratch_bytes(int p);
 hipError_t launch_eigen(int p, int K, const float* M, float* D, float* sv, const Workspace& ws, hipStream_t st);
 

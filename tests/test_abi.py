@@ -39,6 +39,14 @@ def test_workspace_bytes_and_shape_rejection():
     assert sbo.lib().sbo_create(None, 64, 4, 3, 100, None) == sbo.binding.SBO_EINVAL
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+def test_workspace_of_an_orthobase(p):
+    """What one more orthobase adds: the dictionary in three operand orders (14 bytes an entry), M, a piece of the
+    accumulation and two rows of the grouping's histograms; nothing for calls that the context may never see."""
+    grown = sbo.sbo_workspace_bytes(p, 1024, 4, 4096) - sbo.sbo_workspace_bytes(p, 512, 4, 4096)
+    assert grown <= 512 * (22 * p * p + 2 * 4 * 1025 + p + 64)
+
+
 def test_strerror_and_null_context():
     assert sbo.sbo_strerror(0) == "success"
     assert "invalid" in sbo.sbo_strerror(-1)

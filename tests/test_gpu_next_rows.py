@@ -233,6 +233,25 @@ def test_learn_initial_sets_as_one_batch(p, m, P0, arith):
             np.testing.assert_allclose(D[j], Q, atol=2e-5)
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+def test_learn_more_initial_sets_than_the_eigenvectors_have_room_for(p):
+    """The scratch of the eigenvectors is that of the accumulation's pieces, which small sets have few of: the initial
+    orthobases of sbo_learn in several goes, each as sbo_new_base makes it."""
+    K0 = 7 if p == 256 else 19
+    P0 = min(2 * p, 300)
+    m = K0 * P0
+    pr = synth.generate(synth.custom(f"room_p{p}", p=p, K=2, m=m, s0=4, snr_db=20.0))
+    sets = np.random.default_rng(67).permutation(m).reshape(K0, P0).astype(np.int32)
+    with Sbo(p, K0, 4, m) as g:
+        t = g.torch
+        D = t.zeros((K0, p, p), dtype=t.float32, device=g.dev)
+        sbo.sbo_learn(g.ctx, g.dev_f32(pr.Y), D, g.dev_i32(sets), 1, 100, K0, 0.0, *g.outputs(m))
+        t.cuda.synchronize()
+        D = D.cpu().numpy()
+        for j in range(K0):
+            np.testing.assert_allclose(D[j], g.new_base(pr.Y, sets[j], 1)[0], atol=2e-5)
+
+
 @pytest.mark.parametrize("p,m", [(16, 700), (256, 1200)])
 def test_learn_stops_on_the_error(p, m):
     """The worst-W set is prepared before the host knows whether it is wanted: a run that stops on the error returns
