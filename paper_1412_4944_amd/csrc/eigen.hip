@@ -12,21 +12,30 @@
 //      almost no reduction.  A x does not wait for the reflector (A v = A x - alpha A e), and the next x not for
 //      the accumulators (it is row k + 1 less v w^T + w v^T): one barrier a step, p = 256 two.
 //   2. eig_vectors_kernel (one workgroup per eigenvector).  Eigenvalue k by bisection in 256 points at a time (Sturm
-//      counts; six rounds end at 2^-47 of the largest), eigenvector of the tridiagonal matrix from a twisted factorisation at
+//      counts; five rounds end at 2^-39 of the largest), eigenvector of the tridiagonal matrix from a twisted factorisation at
 //      the index where the residual is smallest, p - 2 reflectors back; all in fp64, and beta = 2 / v^T v of the v
 //      that is stored, so that the rounding of 1 does not touch orthogonality.
-//   3. A matrix for which this is not good enough (eigenvalues closer than 1e-8 of the largest, as the zeros of a
-//      set with fewer than p signals; a residual above 1e-13; not finite) goes to the Jacobi kernels, which compute
-//      all of its eigenvectors.
-// Measured (inside sbo_learn; Jacobi before): p = 64 186 us -> 46 + 24 (+ 5 for the launch that finds nothing left to do),
-// p = 256 1830 -> 320 + 94 (+ 8), any number of matrices at a time.  Against eigenvectors in fp64, signal sets of the
-// method, 500 to 8192 signals, p = 16 to 256: entries off by at most 6e-8 / gap (Jacobi: 2e-7), Q Q^T - I 3e-8 (4e-7 to
-// 2.4e-6), eigenvalues 1.7e-7 of the largest (4.5e-7); with amplitudes falling over two decades the same, but single
-// directions among eigenvalues of 1e-4 of the largest with gaps of 4e-7 are less exact (all of them 2e-3 against 4e-4).
+//   3. refine_kernel, twice (one workgroup per eigenvector, fp64).  1 rounds at 2^-24 of the largest eigenvalue, which is
+//      a lot for eigenvalues that are small: a first-order correction from the matrix itself takes an error E to E^2.
+//      Without it, sets whose amplitudes fall over the coordinates lost what fp32 still holds of them: Q G Q^T off its
+//      diagonal by up to 1e-4 of sqrt(lambda_i lambda_j) (p = 256, three decades), where the Jacobi kernels leave 2e-6.
+//   4. A matrix for which this is not good enough (eigenvalues closer than 1e-8 of the largest, as the zeros of a
+//      set with fewer than p signals; a residual above 2e-11; a correction above 0.1, or above 1e-3 the second time; not
+//      finite) goes to the Jacobi kernels, which compute all of its eigenvectors.
+// Measured (sbo_init_base, 2048 signals; in brackets without 3): p = 16 46 us (37), p = 32 64 (52), p = 64 95 (84), p = 256
+// 493 (455); by Jacobi p = 64 0.2 ms, p = 256 1.8.  Launches inside sbo_learn: p = 64 46, 23, 5, 5 (+ 5 for the one that finds
+// nothing left to do), p = 256 320, 91, 21, 19 (+ 7).  Against eigenvectors in fp64 of the set, amplitudes equal or falling
+// over one to four decades, along the coordinates or across them, p = 16 to 256: the error of the vectors 0.02 to 0.8 of
+// that of the Jacobi kernels wherever 3 is not skipped (equal: 3 to 5e-6 against 2e-5 to 2.5e-4; two decades along the
+// coordinates 2e-8 to 3e-6 against 3e-7 to 3e-5, without 3 1e-6 to 2e-4), Q G Q^T off its diagonal by at most 2e-7 of
+// sqrt(lambda_i lambda_j) there, Q Q^T - I 2e-8 to 7e-7 (Jacobi 3e-7 to 5e-6), eigenvalues 2e-7 of the largest.  To the Jacobi
+// kernels go: four decades from p = 32 on, and three across the coordinates at p = 256, where the Gram matrix in fp32 no
+// longer determines the last directions.
 //
 // What bounds it: the steps of 1 depend on one another (p = 64: 1700 cycles, of which A x 420, sums over the lanes and
 // scalars 500; p = 256: 3000, of which A x on the vector ALU 1300 and one wavefront's scalars 700); 2: a chain of p fused
-// multiply-adds in fp64 per count, 80 cycles a link, six times over, and p - 2 reflectors of 220 to 330 cycles each.
+// multiply-adds in fp64 per count, 80 cycles a link, five times over, and p - 2 reflectors of 220 to 330 cycles each; 3: launches,
+// and at p = 256 the 1.3 MB that every workgroup reads from L2.
 #include "sbo_internal.h"
 #include "device_utils.h"
 
@@ -34,27 +43,30 @@ namespace sbo {
 
 namespace {
 
-// What the first kernel leaves for the second, per matrix.
+// Per matrix, in the order of the kernels: reflectors v (gone once the first eigenvectors are there), tridiagonal matrix,
+// eigenvectors z (one set per step of the refinement), A z and eigenvalues.
 struct EigScratch {
-    unsigned char* base;       // [matrix]{ v[p][p] | (d_i, e_{i-1}^2)[p] | e[p] | beta[p] | scale }
-    int32_t* flag;             // [matrix] 1: left to the Jacobi SVD
+    unsigned char* base;       // [matrix]{ z0[p][p] | z1[p][p], v[p][p] | A z[p][p] | (d_i, e_{i-1}^2)[p] | e[p] | beta[p] | lambda[2][p] }
+    int32_t* flag;             // [matrix] left to the Jacobi SVD by kernel 1, 2, .. (0: by none)
     template <int P>
-    __device__ __forceinline__ float* v(int b) const {
-        return reinterpret_cast<float*>(base + b * bytes<P>());
+    __device__ __forceinline__ double* z(int b, int set) const {
+        return reinterpret_cast<double*>(base + b * bytes<P>()) + (size_t)set * P * P;
     }
     template <int P>
-    __device__ __forceinline__ double* de(int b) const {
-        return reinterpret_cast<double*>(base + b * bytes<P>() + (size_t)P * P * 4);
-    }
+    __device__ __forceinline__ float* v(int b) const { return reinterpret_cast<float*>(z<P>(b, 1)); }
+    template <int P>
+    __device__ __forceinline__ double* az(int b) const { return z<P>(b, 2); }
+    template <int P>
+    __device__ __forceinline__ double* de(int b) const { return z<P>(b, 3); }
     template <int P>
     __device__ __forceinline__ double* e(int b) const { return de<P>(b) + 2 * P; }
     template <int P>
     __device__ __forceinline__ double* beta(int b) const { return de<P>(b) + 3 * P; }
     template <int P>
-    __device__ __forceinline__ double* scale(int b) const { return de<P>(b) + 4 * P; }
+    __device__ __forceinline__ double* lambda(int b, int set) const { return de<P>(b) + (4 + set) * P; }
     template <int P>
     __host__ __device__ static constexpr size_t bytes() {
-        return ((size_t)P * P * 4 + (4 * (size_t)P + 1) * sizeof(double) + 255) / 256 * 256;
+        return (3 * (size_t)P * P + 6 * (size_t)P) * sizeof(double);
     }
 };
 
@@ -146,7 +158,7 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// The flag and the scale (a power of two: exact) of matrix b, from the largest magnitude of a thread's entries; false: it
+// The flag of matrix b and 1 / its scale (a power of two: exact), from the largest magnitude of a thread's entries; false: it
 // is zero or not finite.
 template <int P, int WAVES>
 __device__ __forceinline__ bool tridiag_scale(const EigScratch& s, int b, float mx, unsigned* red, float& inv) {
@@ -154,10 +166,7 @@ __device__ __forceinline__ bool tridiag_scale(const EigScratch& s, int b, float 
     const bool good = mx > 1e-30f && mx < 1e37f;
     const int ex = good ? (int)(__builtin_bit_cast(unsigned, mx) >> 23) - 127 : 0;
     inv = __builtin_bit_cast(float, (unsigned)(127 - ex) << 23);
-    if (threadIdx.x == 0) {
-        s.flag[b] = !good;
-        *s.scale<P>(b) = 1.0 / (double)inv;
-    }
+    if (threadIdx.x == 0) s.flag[b] = !good;
     return good;
 }
 
@@ -465,11 +474,51 @@ __device__ __forceinline__ int sturm_count(const double* __restrict__ de, double
     return n;
 }
 
+// y = A^T x by a workgroup of NTH threads, x and y in LDS; part: NTH doubles.  Every workgroup begins at a row of its
+// own, or all of them want the same lines of L2 at a time (p = 256: 24 us a refine_kernel, 19).
+template <int P, int NTH, class T>
+__device__ __forceinline__ void transposed_times(const T* __restrict__ A, const double* x, double* part, double* y) {
+    constexpr int R = P * P / NTH;             // rows of a group of P threads (a power of two)
+    const int tid = threadIdx.x, t = tid % P, r0 = tid / P * R, off = blockIdx.x;
+    double sum = 0.0;
+#pragma unroll 16
+    for (int i = 0; i < R; ++i) {
+        const int row = r0 + ((i + off) & (R - 1));
+        sum = fma((double)A[row * P + t], x[row], sum);
+    }
+    part[tid] = sum;
+    __syncthreads();
+    if (tid < P) {
+        for (int g = 1; g < NTH / P; ++g) sum += part[g * P + tid];
+        y[tid] = sum;
+    }
+    __syncthreads();
+}
+// x, y = A x -> z, az, and the Rayleigh quotient; x, y in LDS, tid < 64 at least.
+template <int P>
+__device__ __forceinline__ void keep_vector(const double* x, const double* y, double* z, double* az, double* lambda) {
+    const int tid = threadIdx.x;
+    if (tid < P) {
+        z[tid] = x[tid];
+        az[tid] = y[tid];
+    }
+    if (tid < 64) {
+        double xy = 0.0, xx = 0.0;
+        for (int t = tid; t < P; t += 64) {
+            xy = fma(x[t], y[t], xy);
+            xx = fma(x[t], x[t], xx);
+        }
+        xy = lanes_sum<64>(xy);
+        xx = lanes_sum<64>(xx);
+        if (tid == 0) *lambda = xy / xx;
+    }
+}
+
 // 2. Eigenvector blockIdx.x (by descending eigenvalue) of matrix blockIdx.y.
 template <int P>
-__global__ __launch_bounds__(256) void eig_vectors_kernel(EigScratch s, float* __restrict__ D, float* __restrict__ sv) {
+__global__ __launch_bounds__(256) void eig_vectors_kernel(const float* __restrict__ G, EigScratch s) {
     constexpr int E = P > 64 ? P / 64 : 1;     // entries of a lane in the last part
-    constexpr double kGap = 1e-8, kResidual = 1e-13;
+    constexpr double kGap = 1e-8, kResidual = 2e-11;           // (at most sqrt(p) times what the bisection leaves, 1e-12)
     __shared__ double dl[P], el[P], Q[2][P], redd[4];
     __shared__ int redi[8];
     const int b = blockIdx.y, k = blockIdx.x, idx = P - 1 - k, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -490,7 +539,7 @@ __global__ __launch_bounds__(256) void eig_vectors_kernel(EigScratch s, float* _
 
     double lo = -bound * 1.0001, hi = bound * 1.0001;
     bool alone = true;
-    constexpr int kRounds = 6;                 // (to 2^-47 of the bound)
+    constexpr int kRounds = 5;                 // (to 1e-12 of the bound: 1e-4 of a neighbour at most, which the refinement takes out)
     for (int it = 0; it < kRounds; ++it) {
         const bool last = it == kRounds - 1;   // two of its points ask whether another eigenvalue is near
         const int points = last ? 254 : 256;
@@ -591,87 +640,151 @@ __global__ __launch_bounds__(256) void eig_vectors_kernel(EigScratch s, float* _
             r = redi[4 + w];
         }
     // z: products of ratios outwards from the twist, two scans
-    if (wave != 0) return;                     // (no workgroup barrier below this line)
-    double z[E];
-    {
-        double up[E], down[E];                 // of entry t of this lane and what lies between it and the twist in the lane
+    __shared__ double zs[P], ys[P], part[256];
+    if (wave == 0) {
+        double z[E];
+        {
+            double up[E], down[E];                 // of entry t of this lane and what lies between it and the twist in the lane
 #pragma unroll
-        for (int t = 0; t < E; ++t) {
-            const int i = E * lane + t;
-            up[t] = i < r ? -el[i] * recip(Q[0][i]) : 1.0;
-            down[t] = i > r && i < P ? -el[i - 1] * recip(Q[1][i]) : 1.0;
+            for (int t = 0; t < E; ++t) {
+                const int i = E * lane + t;
+                up[t] = i < r ? -el[i] * recip(Q[0][i]) : 1.0;
+                down[t] = i > r && i < P ? -el[i - 1] * recip(Q[1][i]) : 1.0;
+            }
+#pragma unroll
+            for (int t = E - 2; t >= 0; --t) up[t] *= up[t + 1];
+#pragma unroll
+            for (int t = 1; t < E; ++t) down[t] *= down[t - 1];
+            double u = up[0], d = down[E - 1];     // of the lane; then of all lanes up to it
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const double ou = __shfl_down(u, o, 64), od = __shfl_up(d, o, 64);
+                u *= lane + o < 64 ? ou : 1.0;
+                d *= lane >= o ? od : 1.0;
+            }
+            const double ou = __shfl_down(u, 1, 64), od = __shfl_up(d, 1, 64);
+#pragma unroll
+            for (int t = 0; t < E; ++t)
+                z[t] = E * lane + t >= P ? 0.0 : up[t] * (lane < 63 ? ou : 1.0) * down[t] * (lane > 0 ? od : 1.0);
         }
+        double n2 = 0.0;
 #pragma unroll
-        for (int t = E - 2; t >= 0; --t) up[t] *= up[t + 1];
+        for (int t = 0; t < E; ++t) n2 = fma(z[t], z[t], n2);
+        n2 = lanes_sum<64>(n2);
+        const double inv = 1.0 / sqrt(n2);
+        if (!(gamma * inv <= kResidual * bound) && lane == 0) s.flag[b] = 2;       // (also where it is a NaN)
 #pragma unroll
-        for (int t = 1; t < E; ++t) down[t] *= down[t - 1];
-        double u = up[0], d = down[E - 1];     // of the lane; then of all lanes up to it
+        for (int t = 0; t < E; ++t) z[t] *= inv;
+        // Q row = H_0 H_1 .. z; eight reflectors requested at a time
+        constexpr int A = 8;
+        const float* V = s.v<P>(b);
+        const double* beta = s.beta<P>(b);
+        float cur[A][E], next[A][E];
+        double bc[A], bn[A];
+        const int at0 = E * lane < P ? E * lane : 0;
+        auto load = [&](float (&v)[A][E], double (&bv)[A], int row) { // rows row .. row + A - 1
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double ou = __shfl_down(u, o, 64), od = __shfl_up(d, o, 64);
-            u *= lane + o < 64 ? ou : 1.0;
-            d *= lane >= o ? od : 1.0;
+            for (int a = 0; a < A; ++a) {
+                bv[a] = beta[row + a];
+#pragma unroll
+                for (int t = 0; t < E; ++t) v[a][t] = V[(row + a) * P + at0 + t];
+            }
+        };
+        load(cur, bc, P - A);
+#pragma unroll 1
+        for (int row = P - A; row >= 0; row -= A) {
+            load(next, bn, row >= A ? row - A : 0);
+#pragma unroll
+            for (int a = A - 1; a >= 0; --a) {
+                double dot = 0.0;
+#pragma unroll
+                for (int t = 0; t < E; ++t) dot = fma((double)cur[a][t], z[t], dot);
+                dot = lanes_sum<64>(dot) * -bc[a];
+#pragma unroll
+                for (int t = 0; t < E; ++t) z[t] = fma(dot, E * lane < P ? (double)cur[a][t] : 0.0, z[t]);
+            }
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                bc[a] = bn[a];
+#pragma unroll
+                for (int t = 0; t < E; ++t) cur[a][t] = next[a][t];
+            }
         }
-        const double ou = __shfl_down(u, 1, 64), od = __shfl_up(d, 1, 64);
 #pragma unroll
         for (int t = 0; t < E; ++t)
-            z[t] = E * lane + t >= P ? 0.0 : up[t] * (lane < 63 ? ou : 1.0) * down[t] * (lane > 0 ? od : 1.0);
+            if (E * lane + t < P) zs[E * lane + t] = z[t];
     }
-    double n2 = 0.0;
+    __syncthreads();
+    transposed_times<P, 256>(G + (int64_t)b * P * P, zs, part, ys);
+    keep_vector<P>(zs, ys, s.z<P>(b, 0) + k * P, s.az<P>(b) + k * P, s.lambda<P>(b, 0) + k);
+}
+
+// 3. Step STEP of the refinement of eigenvector blockIdx.x of matrix blockIdx.y: from all vectors z_i of the step before,
+// z_k += sum_i E_i z_i with E_i = (z_i^T A z_k - lambda_k z_i^T z_k) / (lambda_k - lambda_i), E_k = (1 - z_k^T z_k) / 2 (first order
+// in the error of the z).  Step 2 writes the result.
+template <int P>
+constexpr int refine_threads() { return P == 256 ? 1024 : P == 64 ? 256 : 64; }
+template <int P, int STEP>
+__global__ __launch_bounds__(refine_threads<P>()) void refine_kernel(const float* __restrict__ G, EigScratch s, float* __restrict__ D,
+                                                                     float* __restrict__ sv) {
+    constexpr int NTH = refine_threads<P>(), E = P / 16;
+    constexpr double kTurn = STEP == 1 ? 0.1 : 1e-3;
+    __shared__ double zs[P], ys[P], turn[P], part[NTH];
+    const int b = blockIdx.y, k = blockIdx.x, tid = threadIdx.x, l = tid & 15;
+    // uniform: this launch writes no flag but STEP + 2
+    const int left = s.flag[b];
+    if (left != 0 && left != STEP + 2) return;
+    const double* __restrict__ Z = s.z<P>(b, STEP - 1);
+    const double* __restrict__ L = s.lambda<P>(b, STEP - 1);
+    const double lambda = L[k];
+    const auto at = [&](int e) { return E == 1 ? l : (e >> 1) * 32 + 2 * l + (e & 1); };   // entries of a lane of 16
+    double zk[E], yk[E];
 #pragma unroll
-    for (int t = 0; t < E; ++t) n2 = fma(z[t], z[t], n2);
-    n2 = lanes_sum<64>(n2);
-    const double inv = 1.0 / sqrt(n2);
-    if (!(gamma * inv <= kResidual * bound) && lane == 0) s.flag[b] = 2;       // (also where it is a NaN)
+    for (int e = 0; e < E; ++e) {
+        zk[e] = Z[k * P + at(e)];
+        yk[e] = s.az<P>(b)[k * P + at(e)];
+    }
+    if (tid < P) zs[tid] = Z[k * P + tid];
+#pragma unroll 2
+    for (int q = 0; q < P * 16 / NTH; ++q) {
+        const int i = (q * (NTH / 16) + (tid >> 4) + k * 4) & (P - 1);
+        double zy = 0.0, zz = 0.0;
 #pragma unroll
-    for (int t = 0; t < E; ++t) z[t] *= inv;
-    // Q row = H_0 H_1 .. z; eight reflectors requested at a time
-    constexpr int A = 8;
-    const float* V = s.v<P>(b);
-    const double* beta = s.beta<P>(b);
-    float cur[A][E], next[A][E];
-    double bc[A], bn[A];
-    const int at0 = E * lane < P ? E * lane : 0;
-    auto load = [&](float (&v)[A][E], double (&bv)[A], int row) { // rows row .. row + A - 1
-#pragma unroll
-        for (int a = 0; a < A; ++a) {
-            bv[a] = beta[row + a];
-#pragma unroll
-            for (int t = 0; t < E; ++t) v[a][t] = V[(row + a) * P + at0 + t];
+        for (int e = 0; e < E; ++e) {
+            const double z = Z[i * P + at(e)];
+            zy = fma(z, yk[e], zy);
+            zz = fma(z, zk[e], zz);
         }
-    };
-    load(cur, bc, P - A);
-#pragma unroll 1
-    for (int row = P - A; row >= 0; row -= A) {
-        load(next, bn, row >= A ? row - A : 0);
-#pragma unroll
-        for (int a = A - 1; a >= 0; --a) {
-            double dot = 0.0;
-#pragma unroll
-            for (int t = 0; t < E; ++t) dot = fma((double)cur[a][t], z[t], dot);
-            dot = lanes_sum<64>(dot) * -bc[a];
-#pragma unroll
-            for (int t = 0; t < E; ++t) z[t] = fma(dot, E * lane < P ? (double)cur[a][t] : 0.0, z[t]);
-        }
-#pragma unroll
-        for (int a = 0; a < A; ++a) {
-            bc[a] = bn[a];
-#pragma unroll
-            for (int t = 0; t < E; ++t) cur[a][t] = next[a][t];
+        zy = lanes_sum<16>(zy);
+        zz = lanes_sum<16>(zz);
+        if (l == 0) {
+            const double t = i == k ? 0.5 * (1.0 - zz) : fma(-lambda, zz, zy) / (lambda - L[i]);
+            if (!(fabs(t) <= kTurn)) s.flag[b] = STEP + 2;     // (also where it is a NaN)
+            turn[i] = t;
         }
     }
-    float* out = D + ((int64_t)b * P + k) * P;
-#pragma unroll
-    for (int t = 0; t < E; ++t)
-        if (E * lane + t < P) out[E * lane + t] = (float)z[t];
-    if (lane == 0) sv[(int64_t)b * P + k] = (float)sqrt(fmax(lambda, 0.0) * *s.scale<P>(b));
+    __syncthreads();
+    transposed_times<P, NTH>(Z, turn, part, ys);
+    if constexpr (STEP == 1) {
+        if (tid < P) zs[tid] += ys[tid];
+        __syncthreads();
+        transposed_times<P, NTH>(G + (int64_t)b * P * P, zs, part, ys);
+        keep_vector<P>(zs, ys, s.z<P>(b, 1) + k * P, s.az<P>(b) + k * P, s.lambda<P>(b, 1) + k);
+    } else {
+        // refined eigenvalues may have changed places
+        const int rank = __syncthreads_count(tid < P && (L[tid] > lambda || (L[tid] == lambda && tid < k)));
+        if (tid < P) D[((int64_t)b * P + rank) * P + tid] = (float)(zs[tid] + ys[tid]);
+        if (tid == 0) sv[(int64_t)b * P + rank] = (float)sqrt(fmax(lambda, 0.0));
+    }
 }
 
 template <int P>
 hipError_t launch_eigen_p(int K, const float* M, float* D, float* sv, const EigScratch& s, hipStream_t st) {
     if constexpr (P > 64) hipLaunchKernelGGL(tridiag_wide_kernel, dim3(K), dim3(1024), 0, st, M, s);
     else hipLaunchKernelGGL((tridiag_kernel<P>), dim3(K), dim3(64 * tri_waves<P>()), 0, st, M, s);
-    hipLaunchKernelGGL((eig_vectors_kernel<P>), dim3(P, K), dim3(256), 0, st, s, D, sv);
+    hipLaunchKernelGGL((eig_vectors_kernel<P>), dim3(P, K), dim3(256), 0, st, M, s);
+    hipLaunchKernelGGL((refine_kernel<P, 1>), dim3(P, K), dim3(refine_threads<P>()), 0, st, M, s, D, sv);
+    hipLaunchKernelGGL((refine_kernel<P, 2>), dim3(P, K), dim3(refine_threads<P>()), 0, st, M, s, D, sv);
     return hipGetLastError();
 }
 

@@ -158,6 +158,38 @@ def test_init_base_spectra(p, kind):
         _check_init_base(Y, ids, Qg, svg)
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+@pytest.mark.parametrize("decades", [1, 2, 3, 4])
+@pytest.mark.parametrize("across", [False, True], ids=["along", "across"])
+def test_init_base_falling_spectra(p, decades, across):
+    """Amplitudes that fall, as those of image patches do.  Along the coordinates every entry of the Gram matrix is
+    known to a rounding of sqrt(G_ii G_jj), and the eigenvectors have to be that good: Q G Q^T off its diagonal by
+    that much of sqrt(lambda_i lambda_j); across them, of the largest eigenvalue.  Bounds: a rounding for each of the
+    two vectors and some more for the fp32 sums of the Gram matrix, 8 * 2^-24 in all; where the matrix was left to the
+    Jacobi kernels, what their sweeps add up to, up to fourteen of p rotations, which round the columns of two matrices:
+    2 * 2^-24 sqrt(14 p)."""
+    rng = np.random.default_rng(73 + p + decades)
+    n = 4 * p
+    Y = rng.standard_normal((n, p)) * np.logspace(0, -decades, p)
+    if across:
+        Y = Y @ synth.random_onb(rng, p)
+    Y = Y.astype(np.float32)
+    ids = np.arange(n, dtype=np.int32)
+    print(f"case p={p} decades={decades} across={across}", flush=True)
+    with Sbo(p, 2, 4, n) as g:
+        Qg, svg = g.init_base(Y, ids)
+        sweeps = sbo.sbo_svd_sweeps(g.ctx, 2)[0]
+    _check_init_base(Y, ids, Qg, svg)
+    G = Y.astype(np.float64).T @ Y.astype(np.float64)
+    Q = Qg.astype(np.float64)
+    H = Q @ G @ Q.T
+    lam = np.linalg.eigvalsh(G)[::-1]
+    off = np.abs(H - np.diag(np.diag(H))) / (lam[0] if across else np.sqrt(np.outer(lam, lam)))
+    print(f"  off the diagonal {off.max():.1e}, sweeps {sweeps}", flush=True)
+    assert off.max() <= (8 * 2.0 ** -24 if sweeps == 0 else 2 * 2.0 ** -24 * np.sqrt(14 * p))
+    assert decades > 2 or sweeps == 0, "left to the Jacobi kernels"
+
+
 # ------------------------------------------------------------------- new base
 @pytest.mark.parametrize("name,kw,n,R", [("tiny", dict(), 400, 3), ("patch8", dict(m=5000), 1800, 3),
                                          ("p256", dict(p=256, K=2, m=1200, s0=12, snr_db=25.0), 700, 2)])
