@@ -8,8 +8,9 @@
  *
  * Conventions for every call
  *   - Every array pointer is a DEVICE pointer owned by the caller.  The library
- *     never frees or reallocates caller memory.  It owns only the workspace it
- *     allocates in sbo_create and frees in sbo_destroy.
+ *     never frees or reallocates caller memory.  It owns the workspace it
+ *     allocates in sbo_create, the events of sbo_set_timing and what sbo_learn keeps
+ *     (stated there), all freed in sbo_destroy.
  *   - Y    [m][p]     float : signal-major (row i = y_i; same bytes as a
  *                             column-major p x m matrix with ld = p).  Read only.
  *   - D    [K][p][p]  float : atom-major, D[j][k][:] = atom k of Q_j (same bytes
@@ -198,7 +199,12 @@ int sbo_set_blocks(sbo_ctx* c, int K);
  *      blk/supp/coef/err (device): the last representation and the codes of the last round;
  *      K_final, n_hist (HOST ints); rmse_hist (HOST double[K_max - K0 + 1]): entry 0 after the
  *      initial representation, then one per iteration, *n_hist entries.
- * Synchronises the stream once per iteration (the stopping rule reads the error). */
+ * Waits for the stream once per iteration (the stopping rule reads the error on the host); the worst-W
+ * set of the next iteration is on its way meanwhile.  A run that stops on the error waits for that
+ * set too, which it does not use: when the call returns with *K_final < K_max, nothing reads Y or err
+ * any more; otherwise the work up to the last rmse_hist entry is done.
+ * The first call on a context allocates 8 bytes of pinned host memory and an event, which the context
+ * keeps.  Not possible under stream capture: SBO_EHIP, and nothing is enqueued. */
 int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* init_ids, int K0,
               int64_t P0, int R, int64_t W, int K_max, double target_rmse, int32_t* blk,
               int32_t* supp, float* coef, float* err, int* K_final, double* rmse_hist, int* n_hist);

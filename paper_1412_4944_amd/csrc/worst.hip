@@ -170,11 +170,13 @@ __global__ __launch_bounds__(kSelThreads) void worst_scan_kernel(const int* __re
     }
 }
 
+// offsets != nullptr: also the set as the grouping of one block (as launch_single_block).
 __global__ __launch_bounds__(kSelThreads) void worst_emit_kernel(const float* __restrict__ err,
                                                                  int m, int W,
                                                                  const int* __restrict__ state,
                                                                  const int* __restrict__ base,
-                                                                 int32_t* __restrict__ ids) {
+                                                                 int32_t* __restrict__ ids, int32_t* __restrict__ counts,
+                                                                 int32_t* __restrict__ offsets) {
     __shared__ int cg[kSelThreads], cq[kSelThreads];
     __shared__ int og[kSelThreads + 1], oq[kSelThreads + 1];
     __shared__ int tmp[16];
@@ -182,6 +184,11 @@ __global__ __launch_bounds__(kSelThreads) void worst_emit_kernel(const float* __
     const int need = state[3 * 2 + 1];
 
     const int tid = threadIdx.x;
+    if (offsets != nullptr && blockIdx.x == 0 && tid == 0) {
+        counts[0] = W;
+        offsets[0] = 0;
+        offsets[1] = W;
+    }
     const int i0 = blockIdx.x * kSelChunk + tid * kSelPerThread;
     uint32_t key[kSelPerThread];
     int gt = 0, eq = 0;
@@ -216,7 +223,7 @@ __global__ __launch_bounds__(kSelThreads) void worst_emit_kernel(const float* __
 // The same by one workgroup.  Wavefront w holds the entries 64 Q w .. 64 Q (w + 1) - 1, 64 consecutive ones per q, so that
 // ballots count them in index order.  Lanes l and l + 32 count in a copy of their own of the 256 bins, in a bank of its
 // own: the leading digits (sign and exponent) are nearly all the same.
-// offsets != nullptr: also the set as the grouping of one block (launch_single_block).
+// counts, offsets: as worst_emit_kernel.
 constexpr int kOneWaves = 16;
 constexpr int64_t kOneMax = 64 * 32 * kOneWaves;
 
@@ -330,8 +337,8 @@ __global__ __launch_bounds__(64 * kOneWaves) void worst_one_kernel(const float* 
 hipError_t launch_worst(const float* err, int64_t m, int64_t W, const Workspace& ws, int32_t* ids,
                         hipStream_t st, bool block) {
     if (block && ids != ws.perm) return hipErrorInvalidValue;
+    int32_t *counts = block ? ws.counts : nullptr, *offsets = block ? ws.offsets : nullptr;
     if (m <= kOneMax) {
-        int32_t *counts = block ? ws.counts : nullptr, *offsets = block ? ws.offsets : nullptr;
         const auto one = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(1), dim3(64 * kOneWaves), 0, st, err, (int)m, (int)W, ids, counts, offsets);
             return hipGetLastError();
@@ -349,8 +356,7 @@ hipError_t launch_worst(const float* err, int64_t m, int64_t W, const Workspace&
     hipLaunchKernelGGL(worst_scan_kernel, dim3(1), dim3(kSelThreads), 0, st, ws.sel_cnt, n_chunks,
                        ws.sel_base);
     hipLaunchKernelGGL(worst_emit_kernel, dim3(n_chunks), dim3(kSelThreads), 0, st, err, (int)m, (int)W,
-                       ws.sel_state, ws.sel_base, ids);
-    if (block) return launch_single_block(ids, W, m, ws, st);
+                       ws.sel_state, ws.sel_base, ids, counts, offsets);
     return hipGetLastError();
 }
 

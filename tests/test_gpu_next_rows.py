@@ -310,6 +310,31 @@ def test_learn_stops_on_the_error(p, m):
                     np.testing.assert_allclose(a, b, atol=2e-5)
 
 
+@pytest.mark.parametrize("m", [32768, 32769])
+def test_learn_grows_by_the_worst_set(m):
+    """One growth step of sbo_learn on both sides of the line up to which its worst-W set comes from one workgroup:
+    what sbo_code, sbo_worst, sbo_new_base, sbo_code and sbo_train_rounds make of the same initial orthobases."""
+    p, s0, W, R = 16, 3, 700, 2
+    pr = synth.generate(synth.custom("grow", p=p, K=3, m=m, s0=s0, snr_db=20.0))
+    sets = np.random.default_rng(79).permutation(m)[:2 * 400].reshape(2, 400).astype(np.int32)
+    with Sbo(p, 3, s0, m) as g:
+        t = g.torch
+        Y, D, out = g.dev_f32(pr.Y), t.zeros((3, p, p), dtype=t.float32, device=g.dev), g.outputs(m)
+        _K, hist = sbo.sbo_learn(g.ctx, Y, D, g.dev_i32(sets), R, W, 2, 0.0, *out)
+        D2 = D[:2].cpu().numpy()
+        _K, hist = sbo.sbo_learn(g.ctx, Y, D, g.dev_i32(sets), R, W, 3, 0.0, *out)
+        t.cuda.synchronize()
+        D, err = D.cpu().numpy(), out[3].cpu().numpy()
+        with Sbo(p, 2, s0, m) as g2:
+            e2 = g2.code(pr.Y, D2)[3]
+        Q = g.new_base(pr.Y, g.worst(e2, W), R)[0]
+        D3 = np.concatenate([D2, Q[None]])
+        Dr, _s, _c, er = g.train_rounds(pr.Y, g.code(pr.Y, D3)[0], D3, R)
+    np.testing.assert_array_equal(D, Dr)
+    np.testing.assert_array_equal(err, er)
+    np.testing.assert_allclose(hist, [orc.rmse(e.astype(np.float64).sum(), p, m) for e in (e2, er)], rtol=1e-9)
+
+
 def test_growth_step_reduces_error():
     """Algorithm 2 steps 3-4 composed from the entry points: worst-W set -> new orthobase ->
     appended to the dictionary -> recoding.  Every signal keeps its old blocks to choose
