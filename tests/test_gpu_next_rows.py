@@ -310,6 +310,37 @@ def test_learn_stops_on_the_error(p, m):
                     np.testing.assert_allclose(a, b, atol=2e-5)
 
 
+def test_learn_is_refused_under_capture():
+    """The host decides inside sbo_learn: a capturing stream gets an error and nothing in its graph, and the context
+    works as before."""
+    p, m = 16, 600
+    pr = synth.generate(synth.custom("capture", p=p, K=3, m=m, s0=3, snr_db=20.0))
+    import torch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream), Sbo(p, 3, 3, m) as g:
+        Y, D, out = g.dev_f32(pr.Y), torch.zeros((3, p, p), device=g.dev), g.outputs(m)
+        sets = g.dev_i32(np.arange(400).reshape(2, 200))
+        args = (g.ctx, Y, D, sets, 2, 100, 3, 0.0, *out)
+        K, hist = sbo.sbo_learn(*args)
+        torch.cuda.synchronize()
+        D1 = D.clone()
+        D.zero_()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            D.add_(1.0)                                  # (something for the graph to hold)
+            with pytest.raises(sbo.SboError) as e:
+                sbo.sbo_learn(*args)
+        assert e.value.code == sbo.binding.SBO_EHIP
+        for n in (1, 2):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert (D == n).all()
+        assert sbo.sbo_learn(*args) == (K, hist)
+        torch.cuda.synchronize()
+        assert torch.equal(D, D1)
+
+
 @pytest.mark.parametrize("m", [32768, 32769])
 def test_learn_grows_by_the_worst_set(m):
     """One growth step of sbo_learn on both sides of the line up to which its worst-W set comes from one workgroup:
