@@ -581,8 +581,8 @@ template <int P, int S0>
 hipError_t launch_ps(int K, const float* Y, int64_t m, const int32_t* supp, const float* coef,
                      const Workspace& ws, float* M, hipStream_t st) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    const int piece = accum_piece(m, K, P);
-    const int max_pieces = accum_max_pieces(m, K, P);
+    const int piece = accum_piece(m, K);
+    const int max_pieces = accum_max_pieces(m, K);
     const size_t head = ((size_t)(K + 1 + 16) + 3) & ~(size_t)3;
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
@@ -604,8 +604,8 @@ template <int S0>
 hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, const float* coef,
                          const Workspace& ws, float* M, bool split, bool by_pos, hipStream_t st) {
     constexpr int P = 256;
-    const int piece = accum_piece(m, K, P);
-    const int max_pieces = accum_max_pieces(m, K, P);
+    const int piece = accum_piece(m, K);
+    const int max_pieces = accum_max_pieces(m, K);
     const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
     if (split) {
         const size_t lds = aws_lds_bytes(((K + 1 + 16) + 3) & ~3);
@@ -657,8 +657,8 @@ template <int P>
 hipError_t launch_gram_p(int K, const float* Y, int64_t n, const Workspace& ws, float* G,
                          hipStream_t st) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    const int piece = accum_piece(n, K, P);
-    const int max_pieces = accum_max_pieces(n, K, P);
+    const int piece = accum_piece(n, K);
+    const int max_pieces = accum_max_pieces(n, K);
     const size_t head = ((size_t)(K + 1 + 16) + 3) & ~(size_t)3;
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
@@ -685,8 +685,8 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
         case 64: return launch_gram_p<64>(K, Y, n, ws, G, st);
         case 256: {
             constexpr int P = 256;
-            const int piece = accum_piece(n, K, P);
-            const int max_pieces = accum_max_pieces(n, K, P);
+            const int piece = accum_piece(n, K);
+            const int max_pieces = accum_max_pieces(n, K);
             const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
             hipLaunchKernelGGL((accum_wide_kernel<1, true>), dim3(max_pieces), dim3(256), lds1, st, Y, K,
                                piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial, 0);
@@ -703,7 +703,7 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
 // *sq_out = sum of err[0..m) (same launch, extra workgroups).
 hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, float* M,
                                const float* err, double* sq_out, hipStream_t st) {
-    const int piece = accum_piece(m, K, p);
+    const int piece = accum_piece(m, K);
     const size_t lds = (K + 1 + 16) * sizeof(int);
     const int gy = (p * p + 255) / 256;
     const bool sq = err != nullptr && sq_out != nullptr;

@@ -59,7 +59,9 @@ __global__ __launch_bounds__(256) void dict_swizzle_kernel(const float* __restri
 template <int P>
 constexpr int dict_rows() {
     return P == 256 ? 16 : P == 64 ? 32 : 64;
-}template <int P>
+}
+
+template <int P>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
                                                          float2* __restrict__ dnorm) {

@@ -37,12 +37,11 @@ inline GroupGeom group_geom(int64_t m) {
 // workgroup reduces one piece into a partial p x p matrix.
 constexpr int kNumCU = 256;
 constexpr int kMinPiece = 64, kMaxPiece = 4096;
-inline int accum_piece(int64_t m, int K, int p) {
+inline int accum_piece(int64_t m, int K) {
     // One workgroup per CU for every p (8 wavefronts with 150 KiB of LDS for p <= 64, 512
     // registers per lane for p = 256), and all pieces resident in one round: pieces <= CUs where
     // K allows.  At least 64 signals: p = 256, K = 1, 2048 signals with 256 / 128 / 64: accumulation 49 / 30 / 21 us,
     // SVD update that sums the pieces 135 / 139 / 142.
-    (void)p;
     const int target = K < kNumCU / 2 ? kNumCU - K : kNumCU / 2;
     int64_t c = (m + target - 1) / target;
     c = ((c + 63) / 64) * 64;
@@ -50,8 +49,8 @@ inline int accum_piece(int64_t m, int K, int p) {
     if (c > kMaxPiece) c = kMaxPiece;
     return (int)c;
 }
-inline int accum_max_pieces(int64_t m, int K, int p) {
-    int piece = accum_piece(m, K, p);
+inline int accum_max_pieces(int64_t m, int K) {
+    int piece = accum_piece(m, K);
     return (int)((m + piece - 1) / piece) + K;
 }
 

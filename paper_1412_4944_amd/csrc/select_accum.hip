@@ -335,8 +335,8 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
                      int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
     constexpr size_t wave_b = sa_wave_bytes<P, S>();
-    const int piece = accum_piece(m, K, P);
-    const int max_pieces = accum_max_pieces(m, K, P);
+    const int piece = accum_piece(m, K);
+    const int max_pieces = accum_max_pieces(m, K);
     const int head = ((K + 1 + 16) + 3) & ~3;
     const size_t lds = (size_t)head * sizeof(int) + (size_t)MT * (P / 16) * 3 * 64 * sizeof(u32x4) + kSaWaves * wave_b +
                        (blk != nullptr ? kMinPiece * sizeof(int) : 0);
