@@ -42,7 +42,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.dsh = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dnorm = (float2*)take((size_t)K * (p / 16) * 8);
     const size_t split_m = (size_t)(m_max < kEnergySplitSignals ? m_max : kEnergySplitSignals);
-    const size_t direct = (size_t)(K < kDirectMaxK ? K : kDirectMaxK) * (size_t)(m_max < kDirectMaxSignals ? m_max : kDirectMaxSignals);
+    const size_t direct = m_max < kDirectMaxEnergies / K ? (size_t)K * m_max : (size_t)kDirectMaxEnergies;
     w.part_E = (float*)take((direct > kEnergySplitRows * split_m ? direct : kEnergySplitRows * split_m) * 4);
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
     // The eigenvectors of a Gram matrix are computed when the pieces of that matrix have been summed: same memory.

@@ -91,7 +91,7 @@ struct Workspace {
     unsigned* dsh;         // the same rows as two fp16 parts (4 bytes per entry)
     float2* dnorm;         // [K*p/16] per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
     float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row; or
-                           // [<= kDirectMaxK][<= kDirectMaxSignals]: energies of small sets
+                           // the energies of a small set, [K][m] (at most kDirectMaxEnergies)
     int32_t* part_j;       // same shape: its block
     // accumulation
     float* partial;        // [max_pieces][p][p]
@@ -192,11 +192,16 @@ constexpr bool screen_shared(int64_t m, bool p64_by_256) {
 }
 
 // Which calls of sbo_code leave the choice among full-precision energies to the select kernel (energy_direct_kernel): those
-// whose grouping is left to it, with few blocks, since every one of its workgroups compares the energies of all signals.
+// whose grouping is left to it, with few energies, since every one of its workgroups compares those of all signals.
+// sbo_code, screened / direct (us): K = 64, 512 signals p = 16 16.8 / 16.4, p = 32 20.1 / 18.3, p = 64 30.8 / 23.9; K = 32, 1024
+// signals 17.9 / 17.8, 19.5 / 19.4, 26.4 / 25.2; K = 64, 1024 signals 18.5 / 24.6, 22.0 / 27.0, 32.8 / 34.3; fewer energies 3 to 12
+// less (K = 4, 64 signals 13.4 / 9.8, 14.7 / 10.9, 18.7 / 15.2).  K = 96 up to 225 signals would gain too (p = 64 35 / 20.7), up to
+// 512 not everywhere.
 constexpr int kDirectMaxK = 64;
-constexpr int64_t kDirectMaxSignals = 1024;    // (group_in_select allows no more)
+constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than group_in_select allows)
+inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
-    return p <= 64 && K <= kDirectMaxK && m <= kDirectMaxSignals && screen_applies(p, K, s0, arith);
+    return group_in_select(p, K, m) && K <= kDirectMaxK && K * m <= kDirectMaxEnergies && screen_applies(p, K, s0, arith);
 }
 
 // dsw = D in the fp32 operand order of the coding kernels.
@@ -232,7 +237,6 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // choose: blk is written first, from the energies in ws.part_E (launch_energy_direct).
 // by_pos (p = 256): the codes of the signal at position q of ws.perm go to row q, not to the row of the signal: where a
 // signal is in several blocks (sbo_learn's initial sets).  launch_accumulate reads them likewise.
-inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
                          bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false);

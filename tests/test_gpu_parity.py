@@ -257,11 +257,12 @@ def test_code_groups_small_sets_in_the_select_kernel(p, K, m):
         np.testing.assert_array_equal(perm, op)
 
 
-@pytest.mark.parametrize("p,K,m,s0", [(64, 64, 1024, 8), (64, 65, 1024, 8), (64, 32, 225, 8), (64, 3, 33, 16), (32, 64, 1000, 1),
+@pytest.mark.parametrize("p,K,m,s0", [(64, 64, 1024, 8), (64, 65, 1024, 8), (64, 64, 512, 8), (64, 64, 513, 8), (64, 65, 500, 8),
+                                      (32, 32, 1024, 4), (32, 33, 993, 4), (64, 32, 225, 8), (64, 3, 33, 16), (32, 64, 1000, 1),
                                       (32, 7, 500, 16), (16, 63, 1024, 8), (16, 5, 31, 3), (16, 1, 1, 2)])
 @pytest.mark.parametrize("arith", ARITH)
 def test_code_small_sets_without_screening(p, K, m, s0, arith):
-    """Small sets (m <= 1024, K <= 64) compare full-precision energies in the select kernel; in a larger set the same
+    """Small sets (K <= 64, m <= 1024 and K m <= 32768) compare full-precision energies in the select kernel; in a larger set the same
     signals go through the screened choice.  Blocks and codes are the same, bit by bit; zero signals, ties between equal
     blocks and a near-random dictionary among them."""
     rng = np.random.default_rng(59 + p + K)
