@@ -596,10 +596,12 @@ hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int 
 }
 
 // From here on select_split_kernel (p = 32, 64), four wavefronts and up to 4 tiles for each: the fewest with which all
-// workgroups are there at once.  Against select_kernel (us): p = 64, 20000 signals 9.6 / 9.4, 65537 16.3 / 19.0, 100003
-// (K = 64) 21.6 / 26.4, 262144 33.5 / 48.9, 2^20 (K = 128) 140 / 215; p = 32, 50000 - 60000 the same, 300000 21 / 24.5, 10^6
-// 53 / 64; p = 16 no faster at any size.  With one tile for each wavefront 262144 signals took 43 us, with eight of them
-// (two workgroups on a CU) 36.6 to 43.
+// workgroups are there at once.  Select stage by select_kernel / select_split_kernel (us): p = 64, K = 32, 12000 signals 11.0 /
+// 11.2, 24576 11.4 / 11.6, 32768 14.8 / 13.9, 40960 15.5 / 14.2, 65537 19.4 / 17.5, 98304 22.9 / 20.1 (K = 4 and 128, s0 = 5 alike);
+// the kernels alone 262144 48.9 / 33.5, 2^20 (K = 128) 215 / 140.  p = 32, K = 4 to 128: 24576 8.4 / 8.7, 32768 9.3 / 9.6,
+// 40960 9.8 / 9.8, 65537 11.1 / 11.1, 98304 12.9 / 12.7; 300000 24.5 / 21, 10^6 64 / 53: one line for both, as its coefficients
+// are the more exact ones.  p = 16 no faster at any size.  With one tile for each wavefront 262144 signals took 43 us, with
+// eight of them (two workgroups on a CU) 36.6 to 43.
 constexpr int64_t kSplitMinSignals = 32768;
 
 template <int P, int S>
