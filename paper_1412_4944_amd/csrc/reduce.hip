@@ -36,10 +36,11 @@ __global__ __launch_bounds__(256) void sq_final_kernel(const double* __restrict_
 }
 
 // Up to kSqOneMax entries (kSqOneMaxIds through a list, whose gather one CU takes longer over): one workgroup, one launch, the
-// order of the sum as fixed.  Two launches / one (us): 4096 to 16384 entries 8.0 / 4.6, 24576 7.8 / 5.0, 32768 7.7 / 6.1, 40960
-// 7.6 / 7.1, 49152 7.7 / 8.2, 65536 7.7 / 10.3, 131072 7.7 / 19.  A round of sbo_new_base (p = 16), which has one launch behind
-// it: 1024 signals 16.7 / 16.1, 2048 18.2 / 17.4, 4096 20.0 / 19.9, 6000 22.1 / 22.7, 8192 23.8 / 25.5.
-constexpr int64_t kSqOneMax = 32768, kSqOneMaxIds = 4096;
+// order of the sum as fixed.  Two launches / one (us), entries that a coding kernel has just written, so that one CU fetches
+// all of them from beyond its L2: 4096 6.0 / 3.6, 8192 5.7 / 4.5, 16384 7.3 / 6.3, 24576 5.7 / 8.3, 32768 5.8 / 10.7 (inside sbo_learn 9.9
+// / 11.1; a total repeated over the same 32768 entries 7.7 / 6.1).  A round of sbo_new_base (p = 16), which has one launch
+// behind it: 1024 signals 16.7 / 16.1, 2048 18.2 / 17.4, 4096 20.0 / 19.9, 6000 22.1 / 22.7, 8192 23.8 / 25.5.
+constexpr int64_t kSqOneMax = 16384, kSqOneMaxIds = 4096;
 
 __global__ __launch_bounds__(1024) void sq_one_kernel(const float* __restrict__ err, const int32_t* __restrict__ ids,
                                                       int m, double* __restrict__ out) {

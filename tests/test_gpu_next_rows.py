@@ -38,7 +38,8 @@ def test_worst_set_bit_exact(m):
 
 @pytest.mark.parametrize("m", [2, 8191, 8192, 8193, 16384, 16385, 32768, 32769])
 def test_worst_set_at_the_sizes_of_its_kernels(m):
-    """One workgroup up to 32768 entries, 8, 16 or 32 of them to a lane; infinities, both zeros and runs of ties."""
+    """One workgroup up to 32768 entries, 8, 16 or 32 of them to a lane; infinities, both zeros and runs of ties.  And the
+    error total, by one workgroup up to 16384."""
     rng = np.random.default_rng(43 + m)
     err = rng.standard_normal(m).astype(np.float32) ** 2
     err[rng.integers(0, m, m // 3)] = err[m // 2]
