@@ -64,7 +64,8 @@ constexpr int dict_rows() {
 template <int P>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
-                                                         float2* __restrict__ dnorm) {
+                                                         float2* __restrict__ dnorm, int* __restrict__ weak) {
+    if (weak != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *weak = 0;       // the first count of the iterations that follow (code_screen.h)
     constexpr int KS16 = P / 16, R = dict_rows<P>();
     __shared__ float qs[R][P / 8 + 1], rs[R][P / 8 + 1];
     const f32x4* D4 = reinterpret_cast<const f32x4*>(D);
@@ -868,21 +869,22 @@ hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, hipStream_t st) {
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, int* weak,
+                             hipStream_t st) {
     u32x4 *b = reinterpret_cast<u32x4*>(dsb), *h = reinterpret_cast<u32x4*>(dsh);
     const unsigned stages = (unsigned)(K * p + 63) / 64;           // (the last one is filled up with zeros)
     switch (p) {
-        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
-        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
-        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
-        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm); break;
+        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
+        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
+        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
+        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws,
-                                int32_t* blk, int32_t* chunk_count, hipStream_t st) {
+                                int32_t* blk, int32_t* chunk_count, int turn, bool orthobases, hipStream_t st) {
     if (!screen_applies(p, K, s0, arith) || ws.raised == nullptr) return hipErrorInvalidValue;
     ScrArgs a;
     a.Y = Y;
@@ -895,6 +897,16 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
     a.blk = blk;
     a.chunk_count = chunk_count;
     a.chunk = group_geom(m).chunk;
+    if (turn >= 0 && (p == 64 ? home_takes_64(a) : p == 256 && home_takes_256(a))) {
+        a.weak = ws.weak;
+        a.turn = turn;
+        if (turn > 0 && orthobases) {
+            a.perm = ws.perm;
+            a.offsets = ws.offsets;
+            a.sweeps = ws.sweeps;
+            return p == 64 ? launch_home_64(a, arith, ws.raised, st) : launch_home_256(a, arith, ws.raised, st);
+        }
+    }
     switch (p) {
         case 16: return launch_screen_16(a, arith, ws.raised, st);
         case 32: return launch_screen_32(a, arith, ws.raised, st);
@@ -922,8 +934,9 @@ hipError_t launch_energy_direct(int p, int K, int s0, int arith, const float* Y,
 }
 
 hipError_t launch_energy(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws, int32_t* blk,
-                         int32_t* chunk_count, hipStream_t st) {
-    if (screen_applies(p, K, s0, arith)) return launch_energy_screen(p, K, s0, arith, Y, m, ws, blk, chunk_count, st);
+                         int32_t* chunk_count, hipStream_t st, int turn, bool orthobases) {
+    if (screen_applies(p, K, s0, arith))
+        return launch_energy_screen(p, K, s0, arith, Y, m, ws, blk, chunk_count, turn, orthobases, st);
     if (p == 16) return launch_pse<16, 16, 0>(Y, m, K, s0, arith, ws, blk, chunk_count, st);
     if (p != 256) return hipErrorInvalidValue;
     if (s0 <= 1) return launch_wide_s<1>(Y, m, K, s0, arith, ws, blk, chunk_count, st);

@@ -32,10 +32,10 @@
 // assumed about D; the bound is just wide if its atoms are long).
 //
 // Two shapes of the same work:
-//   energy_screen_kernel<..., false, W>: a workgroup takes 64 W signals, a wavefront 64 of them and all
+//   energy_screen_kernel<..., false, W, HOME>: a workgroup takes 64 W signals, a wavefront 64 of them and all
 //     blocks; dictionary stages go through LDS, double-buffered.  W = 8; W = 4, two workgroups per CU, for a last
 //     round that W = 8 would not fill.
-//   energy_screen_kernel<..., true, 8>: a workgroup takes 64 signals, and its wavefronts share out the
+//   energy_screen_kernel<..., true, 8, false>: a workgroup takes 64 signals, and its wavefronts share out the
 //     blocks and read their dictionary rows straight from L2: more workgroups, for signal sets that
 //     would not fill the chip otherwise, and for K beyond the LDS table of the other.
 //
@@ -50,6 +50,8 @@
 #include "device_utils.h"
 #include "energy_networks.h"
 #include "screen_args.h"
+
+#include <type_traits>
 
 namespace sbo {
 
@@ -298,7 +300,7 @@ constexpr size_t scr_table_bytes(int K) {      // front + E16
 }
 template <int P, bool SHARED, int W>
 constexpr size_t scr_lds_bytes(int K) {
-    return scr_table_bytes<P, SHARED, W>(K) + (size_t)(SHARED ? 64 : 64 * W) * 20 + (2 * W + 2) * 4;
+    return scr_table_bytes<P, SHARED, W>(K) + (size_t)(SHARED ? 64 : 64 * W) * 20 + (2 * W + (SHARED ? 2 : 4)) * 4;
 }
 
 // The workgroups of 64 signals take every K that the boundary accepts; p = 256: up to the line of screen_applies.
@@ -327,7 +329,44 @@ __device__ __forceinline__ void interleave() {
     }
 }
 
-template <int P, int S, int SX, int ARITH, bool SHARED, int W>
+// Home blocks (sbo_iterate from its second iteration on, where it takes more than 64 signals per workgroup): the signals are taken in the order of the previous grouping, so
+// that most of the signals of a workgroup belong to one block, their home.  That block is screened first, in full.  For every other
+// one, of which the update has just made an orthobase (sweeps), kHomeRows atoms decide: with R = the part of the signal's energy that
+// they leave, and for any t,
+//     kept energy  <=  R + s0 t + sum over them of (c^2 - min(c^2, t))  =  |y|^2 + s0 t - sum of min(c^2, t),
+// which a block that has nothing to do with the signal does not bring near the kept energy of the home block of a signal that the
+// dictionary represents well.  What comes near is resolved like all other candidates, so that the chosen blocks remain those of the
+// full computation.  Where more than one signal in kHomeFew is not represented well (kept energy below home_line), or a block
+// is no orthobase, everything is screened in full: in the order of the signals if the last iteration says so, or by the workgroup that
+// finds it.  Half of the products and of the selection (p = 64; p = 256: a quarter of the products, and no networks), with
+// trained dictionaries: K = 32, s0 = 8, 262144 signals 104 -> 78 us, K = 128, s0 = 6, 2^20 signals 1380 -> 760, p = 256,
+// K = 16, s0 = 12, 131072 signals 302 -> 115.  What is left: the products at the power limit (1.2 us a step of 16 matrix
+// instructions and 130 vector instructions a wavefront), the load of the signals (7 us a workgroup of 512, p = 256 21: HBM), p = 256
+// the home block (16 us).
+template <int P>
+constexpr int kHomeRows = P > 64 ? 64 : 32;
+// t, in units of |y|^2 / P, and mean and spread of the sum over kHomeRows<P> of the P coefficients of a random direction.
+constexpr float kHomeT = 0.8f;
+template <int P>
+constexpr float kHomeSum = 0.447f * kHomeRows<P> / P;
+template <int P>
+constexpr float kHomeSpread = P > 64 ? 0.010f : 0.026f;
+// A signal is weak if the kept energy of its best block, relative to its own, is below this line: there such bounds leave
+// one block in 160 in (mean + 2.5 spreads, and what the arithmetic may lose).
+template <int P>
+constexpr float home_line(int s0) {
+    return 1.f + kHomeT * s0 / P - kHomeSum<P> + 2.5f * kHomeSpread<P> + 0.006f;
+}
+// Which sizes have a kernel for home blocks: where signals at 20 dB are above the line (p = 64: s0 <= 9, p = 256: all).
+template <int P>
+constexpr bool home_applies(int s0) {
+    return (P == 64 || P == 256) && home_line<P>(s0) < 0.97f;
+}
+// One signal in kHomeFew may be weak: of a workgroup, and of those counted, which are the first 64 of every kWeakEvery-th
+// workgroup (all of them: 4096 atomic additions to one address, 262144 signals 125 -> 152 us).
+constexpr int kHomeFew = 16, kWeakEvery = 4;
+
+template <int P, int S, int SX, int ARITH, bool SHARED, int W, bool HOME>
 __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     using G = ScrGeom<P>;
     constexpr int KS16 = G::KS16, MTS = G::MTS, NB = G::NB, SPB = G::SPB, NV = G::NV, STAGE_U = G::STAGE_U;
@@ -347,12 +386,35 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     float* wred = reinterpret_cast<float*>(key + SIG);     // [2][W], then a flag and a count
     int* any_flag = reinterpret_cast<int*>(wred + 2 * W);
     int* n_tasks = any_flag + 1;
+    int* n_weak = n_tasks + 1;                 // HOME: weak signals, then blocks left in
 
     const int tid = threadIdx.x, NTH = blockDim.x, NW = NTH >> 6;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
     const int64_t wg0 = (int64_t)blockIdx.x * SIG;         // first signal of the workgroup
     const int loc0 = SHARED ? 0 : wave * 64;               // first signal of the wavefront, in the workgroup
+
+    // HOME: whether the dictionary represents the signals well enough (what the coding of the last iteration left in
+    // weak, three counts in turn) and all its blocks are orthobases; the signals are then those at positions wg0 .. of perm.
+    bool by_home = false;
+    int id_own = 0, home_lo = 0, home_hi = 0;  // own signal; the home blocks of the workgroup
+    if constexpr (HOME) {
+        by_home = g.weak[(g.turn + 2) % 3] * kHomeFew <= (int)((gridDim.x + kWeakEvery - 1) / kWeakEvery) * 64;
+        int lo = 0, hi = 0, other = 0;
+        const int last = (int)min(wg0 + SIG, (int64_t)m) - 1;
+        for (int j0 = 0; j0 < K; j0 += 64) {
+            const int jj = j0 + lane;
+            const int end = jj < K ? g.offsets[jj + 1] : 0x7fffffff, sw = jj < K ? g.sweeps[jj] : -1;
+            lo += __popcll(__ballot(end <= (int)wg0));
+            hi += __popcll(__ballot(end <= last));
+            other += __popcll(__ballot(sw >= 0));
+        }
+        by_home = by_home && other == 0;
+        home_lo = min(lo, K - 1);
+        home_hi = min(hi, K - 1);
+        const int64_t pos = wg0 + loc0 + lane;
+        id_own = pos < m ? (by_home ? g.perm[pos] : (int)pos) : -1;
+    }
 
     // the dictionary's norms (most of the time one entry per thread; consumed below)
     const int n_norm = K * (P / 16);
@@ -378,7 +440,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
 #pragma unroll
         for (int r = 0; r < FPT; ++r) Qs[buf][min(tid + 64 * W * r, STAGE_U - 1)] = p[r];
     };
-    if constexpr (!SHARED) fetch(pre, 0);
+    if constexpr (!SHARED) fetch(pre, HOME && by_home ? home_lo * SPB : 0);
 
     // The leading fp16 parts of the signals, every signal scaled by a power of two (largest magnitude
     // into [1/2, 1), p = 256: [1/4, 1/2), so that coefficients times the dictionary's 2^13 stay inside
@@ -388,11 +450,11 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     constexpr int PARTS = P / 4 < 8 ? P / 4 : 8, GS = 64 / PARTS, L4 = P / 4 / PARTS;
     const int part = lane % PARTS, sub = lane / PARTS;
     auto load_group = [&](int first, f32x4 (&raw)[L4]) {   // first: in the workgroup
-        const int64_t i = wg0 + first + sub;
+        const int64_t i = HOME ? (int64_t)__shfl(id_own, first - loc0 + sub, 64) : wg0 + first + sub;
 #pragma unroll
         for (int e = 0; e < L4; ++e) {
             raw[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (i < m) raw[e] = *reinterpret_cast<const f32x4*>(g.Y + i * P + (e * PARTS + part) * 4);
+            if (HOME ? i >= 0 : i < m) raw[e] = *reinterpret_cast<const f32x4*>(g.Y + i * P + (e * PARTS + part) * 4);
         }
     };
     auto over_parts = [&](float x, auto f) {               // over the PARTS lanes of a signal
@@ -484,7 +546,10 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     }
     norm.x = wave_max(norm.x);
     norm.y = wave_max(norm.y);
-    if (tid == 0) any_flag[0] = any_flag[1] = 0;
+    if (tid == 0) {
+        any_flag[0] = any_flag[1] = 0;
+        if constexpr (!SHARED) n_weak[0] = n_weak[1] = 0;
+    }
     if (lane == 0) {
         wred[wave] = norm.x;
         wred[W + wave] = norm.y;
@@ -558,9 +623,10 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             for (int v = 0; v < NK; ++v) keep[nt][v] = u16x2{0, 0};
         }
     }
-    // selection from acc, p <= 64: the UB blocks from j0 on; p = 256: 32 atoms of a block (first: of them all)
-    auto select = [&](const Acc& acc, int j0, bool first) {
-        if constexpr (BOUND) {
+    // selection from acc, p <= 64: the UB blocks from j0 on; p = 256: 32 atoms of a block (first: of them all).  In full: by
+    // networks also where bounds would do.
+    auto select_as = [&](const Acc& acc, int j0, bool first, auto in_full) {
+        if constexpr (BOUND && !decltype(in_full)::value) {
 #pragma unroll
             for (int b = 0; b < UB; ++b) {
                 u16x2 x[NT][NK];
@@ -616,6 +682,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             }
         }
     };
+    auto select = [&](const Acc& acc, int j0, bool first) { select_as(acc, j0, first, std::false_type{}); };
     auto multiply = [&](Acc& acc, u32x4 a, int ks, int mt) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -626,6 +693,34 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                                                                  ks == 0 ? zero : acc[nt][mt], 0, 0, 0);
         }
     };
+    // norms of the dictionary's rows, largest: whole, and of what the leading parts leave
+    auto norms = [&]() {
+        float2 v = {wred[0], wred[W]};
+        for (int w = 1; w < NW; ++w) v = {fmaxf(v.x, wred[w]), fmaxf(v.y, wred[W + w])};
+        return v;
+    };
+    auto stored = [](float e) { return (unsigned)(unsigned short)__builtin_amdgcn_cvt_pknorm_u16(e, 0.f)[0]; };
+    const bool valid = wg0 + loc0 + lane < m;
+    // The error of a coefficient, relative to |y|.
+    auto coef_error = [&](float2 nrm) {
+        const float rel = y2_own > 0.f ? r2s[loc0 + lane] / y2_own : 0.f;
+        return (nrm.x * sqrtf(rel) + 1.001f * nrm.y + nrm.x * (P * 1.2e-7f)) * 1.001f;
+    };
+    // What a block has to reach, in stored energies, beside one that keeps `below`; 0: every block stays in, 0x10000: none
+    // does (a zero signal).  units: of rounding.
+    auto threshold = [&](float below, float2 nrm, float units) {
+        unsigned t16 = 0u;
+        const float eps = sqrtf((float)g.s0) * coef_error(nrm);
+        const float qb = (float)stored(below);
+        const float kept = sqrtf(fmaxf(qb - 0.5f, 0.f) * (1.f / 65535.f));
+        const float t = (kept - 2.f * eps) * (1.f - 0x1.02p-10f);
+        const float t2 = t > 0.f ? t * t * (65535.f * (1.f - 1e-5f)) - units : 0.f;
+        if (y2_own > 0.f && t2 > 0.f) t16 = (unsigned)t2;
+        return !valid || y2_own == 0.f ? 0x10000u : t16;
+    };
+    constexpr unsigned kWeakBelow = (unsigned)(65535.f * (home_line<P>(SX) < 1.f ? home_line<P>(SX) : 1.f));
+    bool halves = false;                       // HOME: only the home blocks have been screened in full
+    unsigned t_home = 0u;
     constexpr int kMatrix = NT * UT * KS16;
     constexpr int kVector = UB * (BOUND ? NV * 4 + 16 : NV * 7 + 8 * SX);      // about
 
@@ -652,15 +747,154 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             if (WIDE && s % SPB == SPB - 1) finish(run, s / SPB);      // uniform
             __syncthreads();
         };
-        stash(pre, 0);
-        fetch(pre, 1);
-        stash(pre, 1);
-        __syncthreads();
-        project(acc0, 0);
-        __syncthreads();
-        for (int s = 0; s < n_stage; s += 2) {
-            step(acc0, acc1, s);
-            if (s + 1 < n_stage) step(acc1, acc0, s + 1);              // uniform
+        if constexpr (HOME) {
+            if (by_home) {                     // uniform
+                // the home blocks, those of its own signals by every wavefront
+                int lo = 0, hi = 0;
+                const int first = (int)wg0 + loc0, last = min(first + 63, m - 1);
+                for (int j0 = 0; j0 < K; j0 += 64) {
+                    const int end = j0 + lane < K ? g.offsets[j0 + lane + 1] : 0x7fffffff;
+                    lo += __popcll(__ballot(end <= first));
+                    hi += __popcll(__ballot(end <= last));
+                }
+                const int n_home = (home_hi - home_lo + 1) * SPB;
+                stash(pre, 0);
+                for (int s = 0; s < n_home; ++s) {
+                    const int j = home_lo + s / SPB;
+                    fetch(pre, home_lo * SPB + min(s + 1, n_home - 1));
+                    __syncthreads();
+                    if (j >= lo && j <= hi) {  // uniform over the wavefront
+                        project(acc0, s & 1);
+                        select_as(acc0, j, s % SPB == 0, std::true_type{});
+                        if (WIDE && s % SPB == SPB - 1) finish(run, j);
+                    }
+                    stash(pre, (s + 1) & 1);
+                }
+                const float2 nrm = norms();
+                t_home = threshold(bestE, nrm, 1.f);
+                const int weak = __popcll(__ballot(t_home < kWeakBelow));
+                if (lane == 0 && weak != 0) atomicAdd(n_weak, weak);
+                __syncthreads();
+                halves = *n_weak * kHomeFew <= SIG;
+
+                // and bounds from kHomeRows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the
+                // atoms of one
+                if (halves) {                  // uniform
+                    u16x2 top[NT];             // sqrt(t), twice
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const _Float16 t = (_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2s[loc0 + nt * 32 + n], 0.f) * (kHomeT / P)));
+                        top[nt] = __builtin_bit_cast(u16x2, f16x2{t, t});
+                    }
+                    const float t_own = (float)(_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2_own, 0.f) * (kHomeT / P)));
+                    // Orthobases to 1e-4, sums to a few 2^-24; and |a - b| <= d gives a^2 >= b^2 - 2 d b for the root of the sum, b <= |y|.
+                    constexpr float root = P > 64 ? 8.f : 5.657f;                        // of kHomeRows
+                    const float most = 1.0003f + (float)g.s0 * (t_own * t_own) * e_scale + 2.f * root * coef_error(nrm);
+                    const int n_step = WIDE ? 2 * K : (K + 1) / 2;
+                    auto fetch_home = [&](u32x4 (&q)[FPT], int s) {
+                        s = min(s, n_step - 1);
+                        if constexpr (WIDE) {
+                            fetch(q, (s >> 1) * SPB + (s & 1));
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < FPT; ++r) {
+                                const int u = min(tid + 64 * W * r, STAGE_U - 1), v = u & (STAGE_U / 2 - 1);
+                                const int j = min(2 * s + u / (STAGE_U / 2), K - 1);
+                                q[r] = __builtin_amdgcn_raw_buffer_load_b128(dict, (j * (2 * STAGE_U) + (v >> 6) * 128 + (v & 63)) * 16, 0, 0);
+                            }
+                        }
+                    };
+                    int n_left = 0;            // blocks that the bounds leave in, besides the best one, of the own signal
+                    auto leave = [&](float sum, int j) {
+                        const float e = most - sum * e_scale;
+                        const bool other = j != best;
+                        secondE = fmaxf(secondE, other ? e : -1.f);
+                        const unsigned q = stored(e);
+                        E16[j * SIG + loc0 + lane] = (unsigned short)q;
+                        n_left += other && q >= t_home;
+                    };
+                    float part_sum[NT] = {0.f, 0.f};
+                    auto bound = [&](const Acc& acc, int s, auto second_half) {
+#pragma unroll
+                        for (int b = 0; b < UT; ++b) {
+                            float up[NT][2] = {{0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll
+                            for (int v = 0; v < 16; v += 4) {
+                                f16x2 w[NT][2];
+#pragma unroll
+                                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                                    for (int nt = 0; nt < NT; ++nt) {
+                                        const auto x = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[nt][b][v + 2 * k]), fabsf(acc[nt][b][v + 2 * k + 1]));
+                                        w[nt][k] = __builtin_bit_cast(f16x2, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x), top[nt]));
+                                    }
+#pragma unroll
+                                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                                    for (int nt = 0; nt < NT; ++nt) up[nt][k] = __builtin_amdgcn_fdot2(w[nt][k], w[nt][k], up[nt][k], false);
+                            }
+                            float sum[NT];
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) sum[nt] = up[nt][0] + up[nt][1];
+                            if constexpr (WIDE && !decltype(second_half)::value) {
+#pragma unroll
+                                for (int nt = 0; nt < NT; ++nt) part_sum[nt] = sum[nt];
+                            } else if constexpr (WIDE) {
+                                const SwapPair t = swap32(part_sum[0] + sum[0], part_sum[1] + sum[1]);
+                                leave(t.first + t.second, s >> 1);
+                            } else {
+                                const SwapPair t = swap32(sum[0], sum[1]);
+                                leave(t.first + t.second, min(2 * s + b, K - 1));
+                            }
+                        }
+                    };
+                    auto home_step = [&](Acc& now, Acc& next, int s, auto second_half) {
+                        stash(pre, s & 1);     // stage s + 2, requested a step ago (two steps ago: no better)
+                        fetch_home(pre, s + 3);
+                        project(next, (s + 1) & 1);
+                        bound(now, s, second_half);
+                        interleave<kMatrix, UT * 60>();
+                        __syncthreads();
+                    };
+                    fetch_home(pre, 0);
+                    stash(pre, 0);
+                    fetch_home(pre, 1);
+                    stash(pre, 1);
+                    fetch_home(pre, 2);
+                    __syncthreads();
+                    project(acc0, 0);
+                    __syncthreads();
+                    for (int s = 0; s < n_step && halves; s += 2) {
+                        home_step(acc0, acc1, s, std::false_type{});
+                        if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});     // uniform
+                        if ((s & 14) == 14) {  // too many to be resolved one by one: all over again, in full
+                            if (n_left != 0) atomicAdd(&n_weak[1], n_left);
+                            n_left = 0;
+                            __syncthreads();
+                            halves = n_weak[1] <= 2 * SIG;
+                            __syncthreads();
+                        }
+                    }
+                }
+                if (!halves) {                 // uniform
+                    bestE = secondE = -1.f;
+                    best = 0;
+                    fetch(pre, 0);
+                    __syncthreads();
+                }
+            }
+        }
+        if (!halves) {                         // uniform
+            stash(pre, 0);
+            fetch(pre, 1);
+            stash(pre, 1);
+            __syncthreads();
+            project(acc0, 0);
+            __syncthreads();
+            for (int s = 0; s < n_stage; s += 2) {
+                step(acc0, acc1, s);
+                if (s + 1 < n_stage) step(acc1, acc0, s + 1);          // uniform
+            }
         }
     } else {
         // A step = UT row tiles of the dictionary, p = 256: one of the SPB tiles of a block; wavefront w takes
@@ -705,12 +939,13 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
 
     // Decision: the best block alone at or above the threshold, in stored energies, or not.  below: the kept
     // energy of block `best`; secondE: the largest bound of the others.
-    const bool valid = wg0 + loc0 + lane < m;
     float below = bestE;
     if constexpr (BOUND) {
-        u16x2 a[SX];
-        sorted_top(keep, a);
-        below = bestE >= 0.f ? pk_pair_energy<SX>(a, h != 0) * e_scale : -1.f;
+        if (!halves) {                         // uniform
+            u16x2 a[SX];
+            sorted_top(keep, a);
+            below = bestE >= 0.f ? pk_pair_energy<SX>(a, h != 0) * e_scale : -1.f;
+        }
     }
     if constexpr (SHARED) {
         __syncthreads();                       // the signals in front are dead
@@ -730,30 +965,21 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             below = fmaxf(below, e);
         }
     }
-    float qn = wred[0], dq = wred[W];
-    for (int w = 1; w < NW; ++w) {
-        qn = fmaxf(qn, wred[w]);
-        dq = fmaxf(dq, wred[W + w]);
-    }
-    auto stored = [](float e) { return (unsigned)(unsigned short)__builtin_amdgcn_cvt_pknorm_u16(e, 0.f)[0]; };
-    unsigned t16 = 0u;                         // 0: every block stays in
-    {
-        const float rel = y2_own > 0.f ? r2s[loc0 + lane] / y2_own : 0.f;
-        const float eps = sqrtf((float)g.s0) * (qn * sqrtf(rel) + 1.001f * dq + qn * (P * 1.2e-7f)) * 1.001f;
-        const float qb = (float)stored(below);
-        const float nrm = sqrtf(fmaxf(qb - 0.5f, 0.f) * (1.f / 65535.f));
-        const float t = (nrm - 2.f * eps) * (1.f - 0x1.02p-10f);
-        // one unit for the rounding of the table; BOUND: what the sum of a bound may lose to rounding
-        constexpr float kUnits = 1.f + (!BOUND ? 0.f : 65535.f * P * 0x1p-25f * (1.f + (float)P / SX));
-        const float t2 = t > 0.f ? t * t * (65535.f * (1.f - 1e-5f)) - kUnits : 0.f;
-        if (y2_own > 0.f && t2 > 0.f) t16 = (unsigned)t2;
-    }
-    if (!valid || y2_own == 0.f) t16 = 0x10000u;           // a zero signal: block 0 (ties go to the lowest)
+    // one unit for the rounding of the table; BOUND: what the sum of a bound may lose to rounding
+    constexpr float kUnits = 1.f + (!BOUND ? 0.f : 65535.f * P * 0x1p-25f * (1.f + (float)P / SX));
+    const unsigned t16 = HOME && halves ? t_home : threshold(below, norms(), kUnits);
     const bool undecided = stored(secondE) >= t16;
-    if (t16 == 0x10000u) best = 0;
+    if (t16 == 0x10000u) best = 0;             // a zero signal: block 0 (ties go to the lowest)
+    if constexpr (home_applies<P>(SX))
+        if (!SHARED && g.weak != nullptr && wave == 0 && blockIdx.x % kWeakEvery == 0) {   // uniform over the wavefront
+            const int weak = __popcll(__ballot(t16 < kWeakBelow));
+            if (lane == 0 && weak != 0) atomicAdd(&g.weak[g.turn % 3], weak);
+            if (blockIdx.x == 0 && lane == 0) g.weak[(g.turn + 1) % 3] = 0;
+        }
     if (!SHARED || wave == 0) {
         thr[loc0 + lane] = undecided ? t16 : 0x10000u;
         key[loc0 + lane] = 0ull;
+        if constexpr (HOME) reinterpret_cast<int*>(r2s)[loc0 + lane] = id_own;     // (its own signal's: used above)
     }
     if (__ballot(undecided) != 0ull && lane == 0) *any_flag = 1;
     __syncthreads();
@@ -792,6 +1018,9 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         // (the signals of the next task are on their way while the present one is computed)
         int id_next = -1, j_next = 0;
         ExactRow<P, ARITH> y_next;
+        auto signal = [&](int id) {
+            return id < 0 ? (int64_t)-1 : HOME ? (int64_t)reinterpret_cast<const int*>(r2s)[id] : wg0 + id;
+        };
         auto look_up = [&](int t) {
             id_next = -1;
             if (t < n_task) {                  // uniform
@@ -800,14 +1029,14 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 const int id = (int)E16[task * 32 + n];
                 id_next = id == 0xffff ? -1 : id;
             }
-            y_next.load(g, id_next < 0 ? (int64_t)-1 : wg0 + id_next, h);
+            y_next.load(g, signal(id_next), h);
         };
         look_up(wave);
         for (int t = wave; t < n_task; t += NW) {
             const int id = id_next, j = j_next;
             const ExactRow<P, ARITH> y = y_next;
             look_up(t + NW);
-            const float e = exact_energy<P, S, SX, ARITH>(g, y, id < 0 ? (int64_t)-1 : wg0 + id, j, lane);
+            const float e = exact_energy<P, S, SX, ARITH>(g, y, signal(id), j, lane);
             // the largest energy (bits of a non-negative float), the lower block on a tie
             if (h == 0 && id >= 0)
                 atomicMax(&key[id], ((unsigned long long)__builtin_bit_cast(unsigned, e) << 32) | (unsigned)(~j));
@@ -815,12 +1044,14 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         __syncthreads();
         if (undecided) best = (int)~(unsigned)key[loc0 + lane];
     }
-    if (valid && (!SHARED || wave == 0)) g.blk[wg0 + loc0 + lane] = best;
+    if (valid && (!SHARED || wave == 0)) g.blk[HOME ? (int64_t)id_own : wg0 + loc0 + lane] = best;
 
     // First step of the grouping (Section 3.3), folded in here: chunk_count[c][j] += number of
     // this workgroup's signals that chose block j (chunk is a multiple of SIG; the array is zero on
     // entry).  Integer atomics only: the sums do not depend on the order.
-    if (g.chunk_count != nullptr) {            // uniform
+    if (HOME && by_home) {                     // uniform: of all chunks
+        if (valid) atomicAdd(&g.chunk_count[(unsigned)id_own / (unsigned)g.chunk * (unsigned)K + best], 1);
+    } else if (g.chunk_count != nullptr) {     // uniform
         int* lh = reinterpret_cast<int*>(front);
         __syncthreads();                       // the lists are dead
         for (int j = tid; j < K; j += NTH) lh[j] = 0;
@@ -833,14 +1064,14 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     }
 }
 
-template <int P, int S, int SX, int ARITH, bool SHARED, int W>
+template <int P, int S, int SX, int ARITH, bool SHARED, int W, bool HOME>
 hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t st) {
     constexpr int sig = SHARED ? 64 : 64 * W;
     const size_t lds = scr_lds_bytes<P, SHARED, W>(a.K);
     if (lds > kScrLdsMax || a.chunk % sig != 0) return hipErrorInvalidValue;
-    const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W>);
+    const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W, HOME>);
     if (hipError_t e = raised->ensure(fn, kScrLdsMax); e != hipSuccess) return e;
-    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W>), dim3((unsigned)((a.m + sig - 1) / sig)),
+    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W, HOME>), dim3((unsigned)((a.m + sig - 1) / sig)),
                        dim3(64 * waves), lds, st, a);
     return hipGetLastError();
 }
@@ -859,17 +1090,57 @@ __global__ __launch_bounds__(64) void energy_direct_kernel(ScrArgs g) {
     if (h == 0 && i < g.m) g.E[(int64_t)j * g.m + i] = e;
 }
 
+// Which shape (the rules of sbo_internal.h).
+template <int P>
+bool scr_by_256(const ScrArgs& a) {
+    return P <= 64 && scr_lds_bytes<P, false, kScrWaves / 2>(a.K) <= kScrLdsMax / 2 && screen_by_256(a.m);
+}
+template <int P>
+bool scr_shared(const ScrArgs& a) {
+    return screen_shared(a.m, P == 64 && scr_by_256<P>(a)) || scr_lds_bytes<P, false, kScrWaves>(a.K) > kScrLdsMax;
+}
 template <int P, int S, int SX, int ARITH>
 hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
-    const bool half = P <= 64 && scr_lds_bytes<P, false, kScrWaves / 2>(a.K) <= kScrLdsMax / 2 && screen_by_256(a.m);
-    if (screen_shared(a.m, P == 64 && half) || scr_lds_bytes<P, false, kScrWaves>(a.K) > kScrLdsMax) {
+    if (scr_shared<P>(a)) {
         const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
-        return launch_w<P, S, SX, ARITH, true, kScrWaves>(a, units < kScrWaves ? units : kScrWaves, raised, st);
+        return launch_w<P, S, SX, ARITH, true, kScrWaves, false>(a, units < kScrWaves ? units : kScrWaves, raised, st);
     }
     if constexpr (P <= 64)
-        if (half)
-            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2>(a, kScrWaves / 2, raised, st);
-    return launch_w<P, S, SX, ARITH, false, kScrWaves>(a, kScrWaves, raised, st);
+        if (scr_by_256<P>(a))
+            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2, false>(a, kScrWaves / 2, raised, st);
+    return launch_w<P, S, SX, ARITH, false, kScrWaves, false>(a, kScrWaves, raised, st);
+}
+
+// The signals in the order of the grouping in g.perm, with home blocks.
+template <int P, int SX, int ARITH>
+hipError_t launch_home_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
+    constexpr int S = pow2_at_least(SX);
+    if constexpr (P <= 64)
+        if (scr_by_256<P>(a))
+            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2, true>(a, kScrWaves / 2, raised, st);
+    return launch_w<P, S, SX, ARITH, false, kScrWaves, true>(a, kScrWaves, raised, st);
+}
+template <int P>
+hipError_t launch_home_p(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
+    switch (a.s0) {
+#define SBO_CASE(N) \
+    case N:         \
+        if constexpr (home_applies<P>(N)) { \
+            if (arith == SBO_ARITH_F16X2) return launch_home_a<P, N, 3>(a, raised, st); \
+            if constexpr (P <= 64) return arith == SBO_ARITH_F32 ? launch_home_a<P, N, 0>(a, raised, st) : launch_home_a<P, N, 1>(a, raised, st); \
+        } \
+        break;
+        SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
+        SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
+#undef SBO_CASE
+        default: break;
+    }
+    return hipErrorInvalidValue;
+}
+// Whether launch_home_p has a kernel for these sizes: where workgroups take more than 64 signals.
+template <int P>
+bool home_takes(const ScrArgs& a) {
+    return home_applies<P>(a.s0) && !scr_shared<P>(a);
 }
 
 // s0 is a compile-time constant of the kernels.  It pays where the selection networks take part of the time (width s0

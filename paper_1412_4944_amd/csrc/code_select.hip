@@ -652,7 +652,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
                          bool split, hipStream_t st, int32_t* blk, bool choose, bool by_pos) {
     if ((blk != nullptr ? !group_in_select(p, K, m) : choose) || (by_pos && p != 256)) return hipErrorInvalidValue;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
-        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, st)
+        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, nullptr, st)
                              : launch_dict_swizzle(p, K, D, ws.dsw, st);
         if (e != hipSuccess) return e;
     }

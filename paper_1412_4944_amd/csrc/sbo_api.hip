@@ -36,6 +36,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.offsets = (int32_t*)take((size_t)(K + 1) * 4);
     w.perm = (int32_t*)take((size_t)m_max * 4);
     w.group_done = (int*)take(4);
+    w.weak = (int*)take(3 * 4);
     w.energy = (float*)take((size_t)m_max * 4);
     w.dsw = (float*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dsb = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 6);
@@ -161,28 +162,29 @@ static int run_swizzle(sbo_ctx* c, const float* D) {
     if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, c->stream));
     if (ops & (kOpsBf16 | kOpsF16))
         SBO_HIP(launch_dict_parts(c->p, c->K, D, ops & kOpsBf16 ? c->ws.dsb : nullptr,
-                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm, c->stream));
+                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm, c->ws.weak, c->stream));
     return SBO_OK;
 }
 
-static int run_energy(sbo_ctx* c, const float* Y, int64_t m, int32_t* blk) {
+static int run_energy(sbo_ctx* c, const float* Y, int64_t m, int32_t* blk, int turn = -1) {
     StageTimer t(c, SBO_STAGE_ENERGY);     // also leaves the chunk histograms of the grouping
-    SBO_HIP(launch_energy(c->p, c->K, c->s0, choice_arith(c), Y, m, c->ws, blk, c->ws.chunk_count, c->stream));
+    SBO_HIP(launch_energy(c->p, c->K, c->s0, choice_arith(c), Y, m, c->ws, blk, c->ws.chunk_count, c->stream, turn,
+                          c->svd_method != SBO_SVD_JACOBI));
     return SBO_OK;
 }
 
-// have_ops: the workspace holds D in those orders already.
+// turn: the iteration of sbo_iterate; from the second one on the workspace holds D in those orders already.
 static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32_t* blk,
-                    int32_t* supp, float* coef, float* err, bool have_ops = false) {
+                    int32_t* supp, float* coef, float* err, int turn = -1) {
     int rc = SBO_OK;
     const bool direct = choose_in_select(c->p, c->K, c->s0, m, choice_arith(c));
     if (direct) {
         StageTimer t(c, SBO_STAGE_ENERGY);
         SBO_HIP(launch_energy_direct(c->p, c->K, c->s0, choice_arith(c), Y, m, D, c->ws, c->stream));
     } else {
-        if (!have_ops) rc = run_swizzle(c, D);
+        if (turn <= 0) rc = run_swizzle(c, D);
         if (rc) return rc;
-        rc = run_energy(c, Y, m, blk);
+        rc = run_energy(c, Y, m, blk, turn);
         if (rc) return rc;
     }
     const bool in_select = group_in_select(c->p, c->K, m);
@@ -388,7 +390,7 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
     const bool fused = c->p <= 64;             // select and accumulate share one pass over Y
     for (int it = 0; it < n_iter; ++it) {
         if (!fused) {
-            rc = run_code(c, Y, m, D, blk, supp, coef, err, it > 0);
+            rc = run_code(c, Y, m, D, blk, supp, coef, err, it);
             if (rc) return rc;
             rc = run_update_grouped(c, Y, m, supp, coef, D, code_ops(c), err,      // grouping reused
                                     sqerr_per_iter ? sqerr_per_iter + it : nullptr);
@@ -401,7 +403,7 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
             rc = run_swizzle(c, D);
             if (rc) return rc;
         }
-        rc = run_energy(c, Y, m, blk);
+        rc = run_energy(c, Y, m, blk, it);
         if (rc) return rc;
         const bool in_select = group_in_select(c->p, c->K, m);
         if (!in_select) rc = run_group(c, blk, m, true);

@@ -83,6 +83,7 @@ struct Workspace {
     int32_t* counts;       // [K]
     int32_t* offsets;      // [K+1]
     int32_t* perm;         // [m_max]
+    int* weak;             // [3] signals that the dictionary represents badly, per iteration in turn (code_screen.h)
     int* group_done;       // [1] workgroups of the scatter that have read the histograms (0 between launches)
     // coding
     float* energy;         // [m_max] kept energy in the winning block
@@ -207,14 +208,18 @@ inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
 // dsw = D in the fp32 operand order of the coding kernels.
 hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStream_t st);
 // dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
-// (device_utils.h); dnorm comes with dsh.
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, hipStream_t st);
+// (device_utils.h); dnorm comes with dsh.  weak: nullptr, or ws.weak, whose first count is set to zero.
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, int* weak,
+                             hipStream_t st);
 // The block of every signal, from the operand orders in ws that (p, s0, arith) reads (energy_ops in
 // sbo_api.hip).
 // chunk_count != nullptr: also add the per-chunk histograms of the chosen blocks into it (the
 // first step of launch_group; the array must be zero on entry, launch_group leaves it so).
+// turn: the iteration (0, 1, ...) of sbo_iterate on the same signals, or -1; orthobases: the blocks were updated by Newton-Schulz
+// where ws.sweeps says so.  From turn 1 on the last grouping in ws tells where every signal comes from, and large sets are
+// coded with home blocks (code_screen.h).  The blocks chosen are the same.
 hipError_t launch_energy(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws, int32_t* blk,
-                         int32_t* chunk_count, hipStream_t st);
+                         int32_t* chunk_count, hipStream_t st, int turn = -1, bool orthobases = false);
 
 // Small sets (choose_in_select): ws.part_E[j * m + i] = the energy of signal i in block j, for launch_select.
 hipError_t launch_energy_direct(int p, int K, int s0, int arith, const float* Y, int64_t m, const float* D,

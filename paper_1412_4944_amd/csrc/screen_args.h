@@ -17,6 +17,11 @@ struct ScrArgs {
     int32_t* blk;
     int32_t* chunk_count;      // or nullptr
     int chunk;
+    // iterations of sbo_iterate (home blocks, code_screen.h): three counts of weak signals, in turn, and the iteration
+    int* weak = nullptr;
+    int turn = 0;
+    // ... from the second one on: the last grouping, and the blocks whose last update was by Newton-Schulz (negative)
+    const int32_t *perm = nullptr, *offsets = nullptr, *sweeps = nullptr;
     // energy_direct_kernel only
     const float* D = nullptr;
     float* E = nullptr;        // [K][m]
@@ -27,6 +32,11 @@ hipError_t launch_screen_16(const ScrArgs& a, int arith, LdsRaised* raised, hipS
 hipError_t launch_screen_32(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
 hipError_t launch_screen_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
 hipError_t launch_screen_256(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+// With home blocks (perm, offsets, sweeps given), and whether there is a kernel for it.
+hipError_t launch_home_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+hipError_t launch_home_256(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+bool home_takes_64(const ScrArgs& a);
+bool home_takes_256(const ScrArgs& a);
 // The full-precision energies of every (signal, block), from D itself.
 hipError_t launch_direct_16(const ScrArgs& a, int arith, hipStream_t st);
 hipError_t launch_direct_32(const ScrArgs& a, int arith, hipStream_t st);

@@ -387,6 +387,68 @@ def test_iterate_free_running(name, kw, iters, arith):
         assert np.abs(Q @ Q.T - np.eye(cfg.p)).max() <= 1e-5
 
 
+def _home_case(p, K, s0, m, kind):
+    """Signals planted in K orthobases at 20 dB, the dictionary 8 % off; or what takes the shortcuts of later iterations away."""
+    rng = np.random.default_rng(p * 1000 + K * 10 + s0)
+    base = np.linalg.qr(rng.standard_normal((K, p, p)))[0].transpose(0, 2, 1)
+    if kind == "close":                        # every orthobase has a near twin: contenders for every signal
+        twin = base[0::2][: (K + 1) // 2] + rng.standard_normal(((K + 1) // 2, p, p)) * (0.02 / np.sqrt(p))
+        base = np.concatenate([base[0::2], np.linalg.qr(twin.transpose(0, 2, 1))[0].transpose(0, 2, 1)])[:K]
+    blk = rng.integers(0, K, m)
+    atoms = rng.random((m, p), dtype=np.float32).argpartition(s0, axis=1)[:, :s0]
+    x = rng.uniform(0.5, 2.0, (m, s0)) * rng.choice([-1.0, 1.0], (m, s0))
+    Y = np.zeros((m, p))
+    for t in range(s0):
+        Y += base[blk, atoms[:, t]] * x[:, t:t + 1]
+    Y += rng.standard_normal((m, p)) * (0.1 * np.sqrt((Y ** 2).mean(1, keepdims=True)))
+    Y *= np.exp(0.6 * rng.standard_normal((m, 1)))
+    D = base + rng.standard_normal((K, p, p)) * (0.08 / np.sqrt(p))
+    D = np.linalg.qr(D.transpose(0, 2, 1))[0].transpose(0, 2, 1)
+    D *= np.sign((D * base).sum(2, keepdims=True))
+    if kind == "odd signals":                  # too small to be screened, zero, unlike any orthobase
+        Y[::401] = rng.standard_normal(Y[::401].shape)
+        Y[7::5003] = 0.0
+        Y[11::5003] *= 1e-21
+    elif kind == "random":
+        D = np.linalg.qr(rng.standard_normal((K, p, p)))[0]
+    elif kind == "unused":                     # a block that nobody takes and that is no orthobase
+        D[K - 1] *= 0.25
+    return Y.astype(np.float32), D.astype(np.float32)
+
+
+HOME_CASES = [(64, 5, 8, 60001, "planted", "f16x2"), (64, 32, 6, 100003, "planted", "f16x2"), (64, 1, 3, 90000, "planted", "f16x2"),
+              (64, 9, 4, 131149, "odd signals", "f32"), (64, 6, 8, 100003, "odd signals", "bf16x3"),
+              (64, 8, 8, 100003, "random", "f16x2"), (64, 8, 5, 70001, "close", "f16x2"), (64, 40, 8, 100003, "close", "bf16x3"),
+              (64, 7, 6, 90001, "unused", "f16x2"), (64, 70, 9, 53001, "planted", "f16x2"), (64, 6, 10, 60001, "planted", "f16x2"), (256, 5, 12, 90001, "planted", "f16x2"),
+              (256, 4, 16, 86017, "close", "f16x2"), (256, 3, 5, 131072, "odd signals", "f16x2")]
+
+
+@pytest.mark.parametrize("p,K,s0,m,kind,arith", HOME_CASES)
+def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m, kind, arith):
+    """From the second iteration of a call on, large sets are coded in the order of the last grouping, starting from the
+    block that a signal came from; every bit of the results is that of calls of one iteration, which know no such block."""
+    Y, D = _home_case(p, K, s0, m, kind)
+    n = 3
+    with Sbo(p, K, s0, m, arith=arith) as g:
+        t = g.torch
+        Yd = g.dev_f32(Y)
+        got = []
+        for per_call in (n, 1):
+            Dd, out = g.dev_f32(D), g.outputs(m)
+            sq = t.zeros(n, dtype=t.float64, device=g.dev)
+            for it in range(0, n, per_call):
+                sbo.sbo_iterate(g.ctx, Yd, Dd, per_call, *out, sq[it:it + per_call])
+            t.cuda.synchronize()
+            got.append([a.cpu().numpy() for a in (*out, Dd, sq)])
+        for name, a, b in zip(("blk", "supp", "coef", "err", "D", "sq"), *got):
+            assert np.array_equal(a, b), (name, int((a != b).sum()))
+        again = [a.cpu().numpy() for a in out]                     # and the context is as it was: the same once more
+        Dd = g.dev_f32(D)
+        sbo.sbo_iterate(g.ctx, Yd, Dd, n, *out, sq)
+        t.cuda.synchronize()
+        assert all(np.array_equal(a, b.cpu().numpy()) for a, b in zip(again, out))
+
+
 @pytest.mark.parametrize("name,kw", [("tiny", dict()), ("patch8", dict(m=5000)), ("p32", dict(p=32, K=6, m=3000, s0=4)),
                                      ("p64_s5", dict(p=64, K=7, m=2100, s0=5)),
                                      ("p256", dict(p=256, K=2, m=1500, s0=12, snr_db=25.0))])
