@@ -44,13 +44,10 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
     constexpr int EPS = S0 <= 1 ? 1 : S0 <= 2 ? 2 : S0 <= 4 ? 4 : S0 <= 8 ? 8 : 16;
     constexpr int SPI = 64 / EPS;              // signals covered by one such fetch
     constexpr int NI = (SPS + SPI - 1) / SPI;  // fetches per step
-    // piece_start[K+1] | tmp[16] | pad | ids[kMaxPiece] | buf: xd[NW][SPS][64] while the
+    // ids[kMaxPiece] | buf: xd[NW][SPS][64] while the
     // piece is walked, then [NW/2][ACC_F4] 16-byte units while the wavefronts are summed
-    extern __shared__ int lds[];
-    int* piece_start = lds;
-    int* tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    int* ids = lds + head;
+    extern __shared__ __attribute__((aligned(16))) int lds[];
+    int* ids = lds;
     float* buf = reinterpret_cast<float*>(ids + kMaxPiece);
 
     const int tid = threadIdx.x;
@@ -58,14 +55,10 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
     const int h = lane >> 5, n = lane & 31;
 
     for (int e = tid; e < NW * SPS * 64; e += 64 * NW) buf[e] = 0.f;
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + piece - 1) / piece; }, K,
-                       piece_start, tmp);
     const int id = blockIdx.x;
-    if (id >= piece_start[K]) return;          // uniform over the workgroup
-
-    const int j = upper_slot(piece_start, K, id);
-    const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    if (pc.j < 0) return;                      // uniform over the workgroup
+    const int pos0 = pc.before + pc.rank, cnt = pc.count;          // <= kMaxPiece (launcher)
 
     for (int q = tid; q < cnt; q += 64 * NW) ids[q] = perm[pos0 + q];
     __syncthreads();
@@ -241,11 +234,9 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
                                                          float* __restrict__ partial, int by_pos) {
     constexpr int P = 256;
     constexpr int NTL = 8;                     // 32-wide tiles along the dimensions
-    // piece_start[K+1] | tmp[16] | xd[4][kWidePairs][2][64] | ids[kMaxPiece]
-    extern __shared__ int lds[];
-    int* piece_start = lds;
-    int* tmp = lds + (K + 1);
-    float* xd_all = reinterpret_cast<float*>(tmp + 16);
+    // xd[4][kWidePairs][2][64] | ids[kMaxPiece]
+    extern __shared__ __attribute__((aligned(16))) int lds[];
+    float* xd_all = reinterpret_cast<float*>(lds);
     int* ids = reinterpret_cast<int*>(xd_all + 4 * kWidePairs * 2 * 64);
 
     const int tid = threadIdx.x;
@@ -253,14 +244,10 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
     const int h = lane >> 5, n = lane & 31;
 
     for (int e = tid; e < 4 * kWidePairs * 2 * 64; e += 256) xd_all[e] = 0.f;
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + piece - 1) / piece; }, K,
-                       piece_start, tmp);
     const int id = blockIdx.x;
-    if (id >= piece_start[K]) return;          // uniform over the workgroup
-
-    const int j = upper_slot(piece_start, K, id);
-    const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    if (pc.j < 0) return;                      // uniform over the workgroup
+    const int pos0 = pc.before + pc.rank, cnt = pc.count;          // <= kMaxPiece (launcher)
     for (int q = tid; q < cnt; q += 256) ids[q] = perm[pos0 + q];
     __syncthreads();
 
@@ -379,8 +366,8 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
 // four with 64 atoms each split and multiplied in turn, zero-filled the x tile and met twice a step; 2048 signals 21 -> 19.
 constexpr int kAwsSignals = 16;
 constexpr int kAwsWaves = 8;
-constexpr size_t aws_lds_bytes(int head) {
-    return (size_t)(head + kMaxPiece) * sizeof(int) + (size_t)2 * 3 * 256 * 32 + (size_t)3 * 3 * 257 * 32;
+constexpr size_t aws_lds_bytes() {
+    return (size_t)kMaxPiece * sizeof(int) + (size_t)2 * 3 * 256 * 32 + (size_t)3 * 3 * 257 * 32;
 }
 
 template <int S0>
@@ -396,12 +383,9 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
     constexpr int YPLANE = P * 32;             // bytes of one part of the y tile
     constexpr int XPLANE = (P + 1) * 32;       // bytes of one part of the x tile (+ the extra row)
     static_assert(G * S0 <= NT, "one thread per (signal, entry)");
-    // piece_start[K+1] | tmp[16] | pad | ids[kMaxPiece] | two y tiles | three x tiles
-    extern __shared__ int lds[];
-    int* piece_start = lds;
-    int* tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    int* ids = lds + head;
+    // ids[kMaxPiece] | two y tiles | three x tiles
+    extern __shared__ __attribute__((aligned(16))) int lds[];
+    int* ids = lds;
     unsigned char* ytiles = reinterpret_cast<unsigned char*>(ids + kMaxPiece);
     unsigned char* xtiles = ytiles + 2 * 3 * YPLANE;
 
@@ -409,14 +393,10 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
 
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + piece - 1) / piece; }, K,
-                       piece_start, tmp);
     const int id = blockIdx.x;
-    if (id >= piece_start[K]) return;          // uniform over the workgroup
-
-    const int j = upper_slot(piece_start, K, id);
-    const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);   // <= kMaxPiece (launcher)
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    if (pc.j < 0) return;                      // uniform over the workgroup
+    const int pos0 = pc.before + pc.rank, cnt = pc.count;          // <= kMaxPiece (launcher)
     for (int q = tid; q < cnt; q += NT) ids[q] = perm[pos0 + q];
     for (int e = tid; e < 9 * XPLANE / 16; e += NT) reinterpret_cast<u32x4*>(xtiles)[e] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
@@ -583,10 +563,9 @@ hipError_t launch_ps(int K, const float* Y, int64_t m, const int32_t* supp, cons
     constexpr int MT = P >= 32 ? P / 32 : 1;
     const int piece = accum_piece(m, K);
     const int max_pieces = accum_max_pieces(m, K);
-    const size_t head = ((size_t)(K + 1 + 16) + 3) & ~(size_t)3;
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
-    const size_t lds1 = (head + kMaxPiece + (walk > xch ? walk : xch)) * 4;
+    const size_t lds1 = (kMaxPiece + (walk > xch ? walk : xch)) * 4;
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, S0, false>),
                                          144 * 1024);
         e != hipSuccess)
@@ -606,9 +585,9 @@ hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, 
     constexpr int P = 256;
     const int piece = accum_piece(m, K);
     const int max_pieces = accum_max_pieces(m, K);
-    const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
+    const size_t lds1 = kMaxPiece * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
     if (split) {
-        const size_t lds = aws_lds_bytes(((K + 1 + 16) + 3) & ~3);
+        const size_t lds = aws_lds_bytes();
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_wide_split_kernel<S0>), lds);
             e != hipSuccess)
             return e;
@@ -659,10 +638,9 @@ hipError_t launch_gram_p(int K, const float* Y, int64_t n, const Workspace& ws, 
     constexpr int MT = P >= 32 ? P / 32 : 1;
     const int piece = accum_piece(n, K);
     const int max_pieces = accum_max_pieces(n, K);
-    const size_t head = ((size_t)(K + 1 + 16) + 3) & ~(size_t)3;
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
-    const size_t lds1 = (head + kMaxPiece + (walk > xch ? walk : xch)) * 4;
+    const size_t lds1 = (kMaxPiece + (walk > xch ? walk : xch)) * 4;
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, 1, true>),
                                          144 * 1024);
         e != hipSuccess)
@@ -687,7 +665,7 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
             constexpr int P = 256;
             const int piece = accum_piece(n, K);
             const int max_pieces = accum_max_pieces(n, K);
-            const size_t lds1 = (K + 1 + 16 + kMaxPiece) * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
+            const size_t lds1 = kMaxPiece * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
             hipLaunchKernelGGL((accum_wide_kernel<1, true>), dim3(max_pieces), dim3(256), lds1, st, Y, K,
                                piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial, 0);
             hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256),

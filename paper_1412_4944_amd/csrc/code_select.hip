@@ -37,19 +37,16 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     constexpr int NVL = MT * 16;               // accumulator values per lane
     static_assert(S <= NVL, "sort width exceeds the values of one lane");
 
-    extern __shared__ int lds[];   // tile_start[K+1] | tmp[16] | pad | stage[4][...] | ties[4][...]
-    int* tile_start = lds;
-    int* tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    int* stage_all = lds + head;
+    extern __shared__ __attribute__((aligned(16))) int lds[];      // stage[4][...] | ties[4][...]
+    int* stage_all = lds;
     float* ties_all = reinterpret_cast<float*>(stage_all + 4 * kSelectStageWords<S>);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, n = lane & 31;
 
-    if constexpr (GROUP) {                     // behind the tiles: off[K+1] | run[4][K] | list[m]
-        int* off = reinterpret_cast<int*>(ties_all + 4 * kSelectTieWords);
+    if constexpr (GROUP) {                     // behind the tiles: tmp[16] | off[K+1] | run[4][K] | list[m]
+        int *tmp = reinterpret_cast<int*>(ties_all + 4 * kSelectTieWords), *off = tmp + 16;
         int *run = off + (K + 1), *list = run + 4 * K;
         if (g.E != nullptr) {                  // uniform
             int* choice = list + g.m;
@@ -57,23 +54,16 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
             g.blk = choice;
         }
         group_in_lds<4>(g.blk, g.m, K, off, run, list, [&](auto f) { wg_exclusive_scan4(f, K, off, tmp); });
-        if (blockIdx.x == 0) {
-            __syncthreads();
-            g.leave(K, off, list);
-        }
+        __syncthreads();
+        if (blockIdx.x == 0) g.leave(K, off, list);
         offsets = off;
         perm = list;
     }
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + 31) >> 5; }, K,
-                       tile_start, tmp);
-    const int wt = blockIdx.x * 4 + wave;
-    if (wt >= tile_start[K]) return;           // no workgroup barrier below this line
-
-    const int j = upper_slot(tile_start, K, wt);
-    const int pos0 = offsets[j] + (wt - tile_start[j]) * 32;
-    const int cnt = min(32, offsets[j + 1] - pos0);
-    const bool active = n < cnt;
-    const int64_t i = active ? perm[pos0 + n] : -1;
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, 32, (int)blockIdx.x * 4 + wave);
+    if (pc.j < 0) return;                      // no workgroup barrier below this line
+    const int j = pc.j;
+    const bool active = n < pc.count;
+    const int64_t i = active ? perm[pc.before + pc.rank + n] : -1;
 
     // B operand: this lane's half of the dims of signal i.
     float yb[KS];
@@ -130,20 +120,15 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
                                                                   float* __restrict__ err) {
     constexpr int KS16 = P / 16, MT = P / 32, Q_U = MT * KS16 * 3 * 64;
 
-    extern __shared__ int lds[];               // piece_start[K+1] | tmp[16] | pad | Qs[Q_U] | stage[NW][..] | ties[NW][..]
-    int *piece_start = lds, *tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    u32x4* Qs = reinterpret_cast<u32x4*>(lds + head);
+    extern __shared__ __attribute__((aligned(16))) int lds[];      // Qs[Q_U] | stage[NW][..] | ties[NW][..]
+    u32x4* Qs = reinterpret_cast<u32x4*>(lds);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
 
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + piece - 1) / piece; }, K, piece_start, tmp);
-    const int id = blockIdx.x;
-    if (id >= piece_start[K]) return;          // uniform over the workgroup
-    const int j = upper_slot(piece_start, K, id);
-    const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0), n_tiles = (cnt + 31) >> 5;
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, (int)blockIdx.x);
+    if (pc.j < 0) return;                      // uniform over the workgroup
+    const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count, n_tiles = (cnt + 31) >> 5;
 
     // Ids two tiles ahead, rows one tile ahead (lanes past the end read the row of signal 0 and are zeroed when consumed).
     auto tile_id = [&](int t) -> int { return t * 32 + n < cnt ? perm[pos0 + t * 32 + n] : -1; };
@@ -167,8 +152,8 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
     }
     __syncthreads();
 
-    int* stage = lds + head + Q_U * 4 + wave * kSelectStageWords<S>;
-    float* ties = reinterpret_cast<float*>(lds + head + Q_U * 4 + NW * kSelectStageWords<S>) + wave * kSelectTieWords;
+    int* stage = lds + Q_U * 4 + wave * kSelectStageWords<S>;
+    float* ties = reinterpret_cast<float*>(lds + Q_U * 4 + NW * kSelectStageWords<S>) + wave * kSelectTieWords;
     for (int tile = wave; tile < n_tiles; tile += NW) {
         const int64_t i = i_cur;
         u32x4 yq[KS16][3];
@@ -239,25 +224,18 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
     constexpr int QCH = 8;                     // operand groups loaded ahead of their MFMAs
     static_assert(S <= 16 && QN % QCH == 0, "shape");
 
-    extern __shared__ int lds[];               // tile_start[K+1] | tmp[16] | ctile[4][32][LDC]
-    int* tile_start = lds;
-    int* tmp = lds + (K + 1);
-    float* ctile_all = reinterpret_cast<float*>(tmp + 16);
+    extern __shared__ __attribute__((aligned(16))) int lds[];      // ctile[4][32][LDC]
+    float* ctile_all = reinterpret_cast<float*>(lds);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, n = lane & 31;
 
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + 31) >> 5; }, K,
-                       tile_start, tmp);
-    const int wt = blockIdx.x * 4 + wave;
-    if (wt >= tile_start[K]) return;           // no workgroup barrier below this line
-
-    const int j = upper_slot(tile_start, K, wt);
-    const int pos0 = offsets[j] + (wt - tile_start[j]) * 32;
-    const int cnt = min(32, offsets[j + 1] - pos0);
-    const bool active = n < cnt;
-    const int64_t i = active ? perm[pos0 + n] : -1;
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, 32, (int)blockIdx.x * 4 + wave);
+    if (pc.j < 0) return;                      // no workgroup barrier below this line
+    const int j = pc.j;
+    const bool active = n < pc.count;
+    const int64_t i = active ? perm[pc.before + pc.rank + n] : -1;
 
     float yb[KS];
     if (active) {
@@ -357,7 +335,7 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
         gt_own += a > tau;
         eq_own += a == tau;
     }
-    const int64_t at = by_pos ? pos0 + n : i;
+    const int64_t at = by_pos ? pc.before + pc.rank + n : i;
     const int gt_oth = other_half(gt_own), eq_oth = other_half(eq_own);
     const int need = s0 - (gt_own + gt_oth);   // entries equal to tau to take, lowest index first
     const int gt_lo = h ? gt_oth : gt_own, eq_lo = h ? eq_oth : eq_own;
@@ -410,11 +388,8 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
                                                                  float* __restrict__ err, int by_pos) {
     constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 3, NW = kTileWaves, L = 16;
     constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
-    extern __shared__ int lds[];               // tile_start[K+1] | tmp[16] | pad | parts of y, then coefficients | stage
-    int* tile_start = lds;
-    int* tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    u32x4* ys = reinterpret_cast<u32x4*>(lds + head);          // [KS16][3][64]
+    extern __shared__ __attribute__((aligned(16))) int lds[];  // parts of y, then coefficients | stage
+    u32x4* ys = reinterpret_cast<u32x4*>(lds);                 // [KS16][3][64]
     float* cs = reinterpret_cast<float*>(ys);                  // [32][kTileLd]
     int* stage = reinterpret_cast<int*>(ys + STAGE_U);         // [32][2][16]
     static_assert(32 * kTileLd * 4 <= STAGE_U * 16, "the coefficients fit");
@@ -422,13 +397,11 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + 31) >> 5; }, K, tile_start, tmp);
     const int per_xcd = gridDim.x >> 3;        // the grid is a multiple of 8 (launcher)
     const int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (id >= tile_start[K]) return;           // uniform over the workgroup
-    const int j = upper_slot(tile_start, K, id);
-    const int pos0 = offsets[j] + (id - tile_start[j]) * 32;
-    const int cnt = min(32, offsets[j + 1] - pos0);
+    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, 32, id);
+    if (pc.j < 0) return;                      // uniform over the workgroup
+    const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count;
 
     // A operand: rows of this wavefront's 32 atoms, AHEAD contraction steps on their way
     const u32x4* Qj = Dsb + ((int64_t)j * MT + wave) * STAGE_U + lane;
@@ -566,7 +539,7 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
     if (split) {
         // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every tile
         const int64_t tiles = (((m + 31) / 32 + K) + 7) & ~(int64_t)7;
-        const size_t lds = (((size_t)(K + 1 + 16) + 3) & ~(size_t)3) * sizeof(int) + (size_t)(P / 16) * 3 * 64 * 16 + 32 * 32 * sizeof(int);
+        const size_t lds = (size_t)(P / 16) * 3 * 64 * 16 + 32 * 32 * sizeof(int);
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_split_kernel<S>), 64 * 1024); e != hipSuccess)
             return e;
         hipLaunchKernelGGL((select_wide_split_kernel<S>), dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
@@ -575,7 +548,7 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
     }
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
-    const size_t lds = (K + 1 + 16) * sizeof(int) + 4 * 32 * (P + 1) * sizeof(float);
+    const size_t lds = 4 * 32 * (P + 1) * sizeof(float);
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_kernel<P, S>), lds);
         e != hipSuccess)
         return e;
@@ -609,9 +582,9 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
                      int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
-    size_t lds = ((((K + 1 + 16) + 3) & ~3) + 4 * (kSelectStageWords<S> + kSelectTieWords)) * sizeof(int);
+    size_t lds = 4 * (kSelectStageWords<S> + kSelectTieWords) * sizeof(int);
     if (blk != nullptr) {
-        lds += (5 * K + 1 + (choose ? 2 : 1) * m) * sizeof(int);       // at most 60 KiB in all (choose: K <= 64)
+        lds += (16 + 5 * K + 1 + (choose ? 2 : 1) * m) * sizeof(int);       // at most 60 KiB in all (choose: K <= 64)
         hipLaunchKernelGGL((select_kernel<P, S, true>), grid, dim3(256), lds, st, Y, D, K, s0, nullptr, nullptr, supp,
                            coef, err,
                            GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count, choose ? ws.part_E : nullptr, blk});
@@ -622,7 +595,7 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
         const int64_t resident = 256 * (P == 64 ? 3 : 4) - K / 2;          // less the blocks' unfinished pieces
         const int tiles = (int)std::min<int64_t>(4, (m + 32 * NW * resident - 1) / (32 * NW * resident));
         const int piece = 32 * NW * tiles;
-        lds = ((((K + 1 + 16) + 3) & ~3) + 4 * Q_U + NW * (kSelectStageWords<S> + kSelectTieWords)) * sizeof(int);
+        lds = (4 * Q_U + NW * (kSelectStageWords<S> + kSelectTieWords)) * sizeof(int);
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_split_kernel<P, S, NW>), 160 * 1024);
             e != hipSuccess)
             return e;

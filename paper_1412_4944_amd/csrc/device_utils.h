@@ -242,6 +242,128 @@ __device__ __forceinline__ void wg_exclusive_scan4(F f, int n, int* out, int* tm
     __syncthreads();
 }
 
+// Inclusive sums over the lanes of a wavefront (all lanes active).
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);        // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);        // row_bcast 15, 31
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// Piece `id` of the signal lists of all K blocks, cut into pieces of `piece` signals, block by block (block j has
+// ceil(count_of(j) / piece) of them).  Every wavefront for itself, all lanes active: no LDS, no barrier (a workgroup's scan
+// into LDS and a search there: 3500 cycles of the start of select_accum_kernel, 1400 like this).
+struct Piece {
+    int j;                     // its block, -1: there is no such piece
+    int rank, count;           // its first signal, in the block's list, and how many it has
+    int before;                // signals of the blocks before
+};
+template <class F>
+__device__ __forceinline__ Piece find_piece(F count_of, int K, int piece, int id) {
+    const int lane = threadIdx.x & 63;
+    int pieces = 0, signals = 0;               // of the blocks before
+    for (int j0 = 0; j0 < K; j0 += 256) {
+        int n[4];                              // on their way at once
+#pragma unroll
+        for (int u = 0; u < 4; ++u) n[u] = j0 + 64 * u + lane < K ? count_of(j0 + 64 * u + lane) : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (j0 + 64 * u >= K) break;       // uniform
+            const int np = (int)((unsigned)(n[u] + piece - 1) / (unsigned)piece);
+            const int upto = wave_scan(np), in_list = wave_scan(n[u]), at = id - pieces - (upto - np);
+            const unsigned long long here = __ballot(at >= 0 && at < np);
+            if (here != 0ull) {                // uniform
+                const int l = __builtin_ctzll(here);
+                const int rank = __builtin_amdgcn_readlane(at, l) * piece, all = __builtin_amdgcn_readlane(n[u], l);
+                return {j0 + 64 * u + l, rank, min(piece, all - rank), signals + __builtin_amdgcn_readlane(in_list - n[u], l)};
+            }
+            pieces += __builtin_amdgcn_readlane(upto, 63);
+            signals += __builtin_amdgcn_readlane(in_list, 63);
+        }
+    }
+    return {-1, 0, 0, 0};
+}
+
+// A grouping that has not been carried out: the choices and their histograms per chunk of kListChunk signals (group.hip),
+// from which a workgroup of NW wavefronts lists the signals of its own piece.  Few signals (list_in_kernel): a workgroup
+// reads all histograms, and the choices of the chunks that its piece comes from.  The launch after sets the histograms to zero
+// (a count of the workgroups that have read them costs more than all the rest: 144 of them, one after the other, 4 us).
+constexpr int kListChunk = 512, kListChunks = 64;          // signals of a chunk, chunks at most
+struct ChunkLists {
+    const int32_t* blk;
+    int m, n_chunks;
+    const int32_t* chunk_count;            // [n_chunks][K]
+    int32_t *counts, *offsets; // [K], [K+1]: written by the first workgroup
+
+    static constexpr int lds_ints(int NW, int K, int n_chunks) { return (n_chunks + NW) * K; }
+
+    // Piece `id` and, in ids[piece.count], its signals in order; table: lds_ints ints, dead after the barrier that ends this.
+    template <int NW>
+    __device__ __forceinline__ Piece list(int K, int piece, int id, int* table, int* ids) const {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        int* part = table + n_chunks * K;      // [NW][K] sums over every NW-th chunk
+        for (int j = lane; j < K; j += 64) {
+            int v[kListChunks / NW], s = 0;    // on their way at once
+#pragma unroll
+            for (int u = 0; u < kListChunks / NW; ++u) v[u] = chunk_count[min(wave + u * NW, n_chunks - 1) * K + j];
+#pragma unroll
+            for (int u = 0; u < kListChunks / NW; ++u)
+                if (wave + u * NW < n_chunks) {            // uniform
+                    table[(wave + u * NW) * K + j] = v[u];
+                    s += v[u];
+                }
+            part[wave * K + j] = s;
+        }
+        __syncthreads();
+        auto count_of = [&](int j) {
+            int s = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += part[w * K + j];
+            return s;
+        };
+        if (id == 0 && wave == 0) {            // (uniform)
+            int before = 0;
+            for (int j0 = 0; j0 < K; j0 += 64) {
+                const int j = j0 + lane, n = j < K ? count_of(j) : 0, upto = before + wave_scan(n);
+                if (j < K) {
+                    counts[j] = n;
+                    offsets[j + 1] = upto;
+                }
+                before = __builtin_amdgcn_readlane(upto, 63);
+            }
+            if (lane == 0) offsets[0] = 0;
+        }
+        const Piece pc = find_piece(count_of, K, piece, id);
+        if (pc.j >= 0) {                       // uniform over the workgroup
+            // the chunks that have some of it, a wavefront every NW-th one
+            const int n = lane < n_chunks ? table[lane * K + pc.j] : 0, front = wave_scan(n) - n;
+            unsigned long long mask = __ballot(n > 0 && front < pc.rank + pc.count && front + n > pc.rank);
+            for (int k = 0; mask != 0ull; ++k, mask &= mask - 1) {         // uniform over the wavefront
+                if (k % NW != wave) continue;
+                const int c = __builtin_ctzll(mask);
+                int key[kListChunk / 64];      // on their way at once (a condition would make eight trips of it)
+#pragma unroll
+                for (int u = 0; u < kListChunk / 64; ++u) key[u] = blk[min(c * kListChunk + u * 64 + lane, m - 1)];
+                int at = __builtin_amdgcn_readlane(front, c) - pc.rank;    // of the next one, in the piece
+#pragma unroll
+                for (int u = 0; u < kListChunk / 64; ++u) {
+                    const int i = c * kListChunk + u * 64 + lane;
+                    const bool here = key[u] == pc.j && i < m;
+                    const unsigned long long mine = __ballot(here);
+                    const int to = at + __popcll(mine & ((1ull << lane) - 1ull));
+                    if (here && to >= 0 && to < pc.count) ids[to] = i;
+                    at += __popcll(mine);
+                }
+            }
+        }
+        __syncthreads();
+        return pc;
+    }
+};
+
 // The keys of the 64 A signals from `at` on, A per lane (-1 past the end): all loads are on their way at once, where
 // a loop of one load per 64 signals waits for each (group_scatter_kernel, 512 signals per wavefront, A = 8: 1024
 // signals, K = 4 6.8 -> 5.4 us, 16384, K = 16 9.2 -> 7.4, 262144, K = 32 8.3 -> 6.3, with the load before the scan;

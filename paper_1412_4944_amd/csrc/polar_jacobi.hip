@@ -81,7 +81,7 @@ hipError_t launch_polar(int p, int K, const float* M, const int32_t* counts, flo
 }
 
 hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Workspace& ws, int write_ops,
-                                    const float* err, double* sq_out, hipStream_t st) {
+                                    const float* err, double* sq_out, hipStream_t st, bool clear_lists) {
     SqTotalArgs sq;
     if (err != nullptr && sq_out != nullptr) {
         sq.err = err;
@@ -95,7 +95,8 @@ hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Wor
         return launch_polar_wide(K, nullptr, ws.partial, ws.offsets, accum_piece(m, K), ws.counts, D,
                                  dict_ops(ws, write_ops), true, nullptr, ws, sq, st);
     return launch_polar_ns(p, K, nullptr, ws.partial, ws.offsets, accum_piece(m, K), ws.counts, D,
-                           dict_ops(ws, write_ops), ws.ns_fallback, ws.sweeps, sq, ws.raised, st);
+                           dict_ops(ws, write_ops), ws.ns_fallback, ws.sweeps, sq, ws.raised, st, ws.chunk_count,
+                           clear_lists ? group_geom(m).n_chunks * K : 0);
 }
 
 }  // namespace sbo

@@ -70,6 +70,9 @@ struct NsArgs {
     int* sq_counter;
     double* sq_out;
     int nb;
+    // histograms that this launch sets to zero (ChunkLists), or n_clear == 0
+    int32_t* clear;
+    int n_clear;
 };
 
 // sqrt(3 / (1 + l + l^2)) for l = 0.16 and then the l that the steps leave: 0.16, 0.375, 0.71, 0.96 (a chain of selects: a table
@@ -514,6 +517,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         return;
     }
     const int j = blockIdx.x;
+    for (int e = j * NTH + tid; e < g.n_clear; e += g.K * NTH) g.clear[e] = 0;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int strip = wave & (T - 1), hh = HV > 1 ? wave / T : 0;           // (the two of a strip on one SIMD)
     const int grp = lane >> 4, c16 = lane & 15;
@@ -625,7 +629,7 @@ hipError_t launch_ns_p(const NsArgs& a, LdsRaised* raised, hipStream_t st) {
 hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, const int32_t* offsets,
                            int piece, const int32_t* counts, float* D, const DictOps& ops,
                            int32_t* fallback, int32_t* iters, const SqTotalArgs& sq, LdsRaised* raised,
-                           hipStream_t st) {
+                           hipStream_t st, int32_t* clear, int n_clear) {
     constexpr int kMaxIters = 26;
     NsArgs a;
     a.M = M;
@@ -644,6 +648,8 @@ hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, c
     a.sq_part = sq.part;
     a.sq_counter = sq.counter;
     a.sq_out = sq.out;
+    a.clear = clear;
+    a.n_clear = n_clear;
     a.nb = sq.out != nullptr ? sq.nb : 0;
     if (M == nullptr && (partial == nullptr || offsets == nullptr || piece < 1)) return hipErrorInvalidValue;
     switch (p) {

@@ -202,7 +202,7 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
 // err / sq_out: also the squared-error total of the coding pass.  One launch on the default path;
 // with the Jacobi SVD for every block the pieces are summed by their own launch first.
 static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, const float* err, double* sq_out,
-                            int K = -1) {
+                            int K = -1, bool clear_lists = false) {
     if (K < 0) K = c->K;
     if (c->svd_method == SBO_SVD_JACOBI) {
         {
@@ -214,7 +214,7 @@ static int run_polar_pieces(sbo_ctx* c, int64_t m, float* D, int write_ops, cons
         return SBO_OK;
     }
     StageTimer t(c, SBO_STAGE_SVD);
-    SBO_HIP(launch_polar_from_pieces(c->p, K, m, D, c->ws, write_ops, err, sq_out, c->stream));
+    SBO_HIP(launch_polar_from_pieces(c->p, K, m, D, c->ws, write_ops, err, sq_out, c->stream, clear_lists));
     return SBO_OK;
 }
 
@@ -405,15 +405,15 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
         }
         rc = run_energy(c, Y, m, blk, it);
         if (rc) return rc;
-        const bool in_select = group_in_select(c->p, c->K, m);
-        if (!in_select) rc = run_group(c, blk, m, true);
+        const bool lists = c->svd_method != SBO_SVD_JACOBI && lists_in_round(c->p, c->K, m);
+        if (!lists) rc = run_group(c, blk, m, true);
         if (rc) return rc;
         {
             StageTimer t(c, SBO_STAGE_SELECT);  // includes the per-piece accumulation
             SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, c->stream,
-                                        in_select ? blk : nullptr));
+                                        lists ? blk : nullptr));
         }
-        rc = run_polar_pieces(c, m, D, energy_ops(c), err, sqerr_per_iter ? sqerr_per_iter + it : nullptr);
+        rc = run_polar_pieces(c, m, D, energy_ops(c), err, sqerr_per_iter ? sqerr_per_iter + it : nullptr, -1, lists);
         if (rc) return rc;
     }
     return SBO_OK;

@@ -200,6 +200,11 @@ constexpr bool screen_shared(int64_t m, bool p64_by_256) {
 // 512 not everywhere.
 constexpr int kDirectMaxK = 64;
 constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than group_in_select allows)
+// Which iterations leave the grouping to the select + accumulate kernel, whose workgroups list the signals of their own piece
+// (ChunkLists in device_utils.h).
+inline bool lists_in_round(int p, int K, int64_t m) {
+    return p <= 64 && m <= 32768 && (int64_t)((m + 511) / 512 + 8) * K <= 4096;
+}
 inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
     return group_in_select(p, K, m) && K <= kDirectMaxK && K * m <= kDirectMaxEnergies && screen_applies(p, K, s0, arith);
@@ -251,7 +256,9 @@ hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, co
                              const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos = false);
 
 // Fused select + per-piece accumulation (p <= 64); the piece results land in ws.partial
-// and launch_accum_reduce sums them into M.  blk: as launch_select.
+// and launch_accum_reduce sums them into M.  blk: nullptr, or the choices of signals that have not been grouped, with their
+// histograms in ws.chunk_count (where lists_in_round says so; the launch after sets them to zero); ws.counts and ws.offsets are
+// left as launch_group would leave them, ws.perm is not.
 hipError_t launch_select_accum(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                                const Workspace& ws, int32_t* supp, float* coef, float* err,
                                hipStream_t st, const int32_t* blk = nullptr);
@@ -294,12 +301,13 @@ struct SqTotalArgs {
 hipError_t launch_polar_ns(int p, int K, const float* M, const float* partial, const int32_t* offsets,
                            int piece, const int32_t* counts, float* D, const DictOps& ops,
                            int32_t* fallback, int32_t* iters, const SqTotalArgs& sq, LdsRaised* raised,
-                           hipStream_t st);
+                           hipStream_t st, int32_t* clear = nullptr, int n_clear = 0);
 // The SVD update straight from the piece results (launch_select_accum, or launch_accumulate
 // without its sum; Newton-Schulz path): what launch_accum_reduce + launch_polar do, in one launch.
-// err / sq_out as for launch_accum_reduce.
+// err / sq_out as for launch_accum_reduce.  clear_lists (p <= 64): also sets the histograms to zero that launch_select_accum
+// has read.
 hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Workspace& ws, int write_ops,
-                                    const float* err, double* sq_out, hipStream_t st);
+                                    const float* err, double* sq_out, hipStream_t st, bool clear_lists = false);
 
 // p = 256 (polar_wide.hip): source and squared-error total as launch_polar_ns; newton_schulz_first ==
 // false or eig_sv != nullptr: the Jacobi SVD for every block.  And the sizes of ws.wide, ws.wide_sync.

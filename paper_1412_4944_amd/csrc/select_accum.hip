@@ -43,13 +43,12 @@ constexpr int sa_wave_bytes() {
     return use > copy ? use : copy;
 }
 
-// GROUP: every workgroup groups the (small) set itself, as select_kernel does: no launch for it (1024 signals, K = 4,
-// p = 16: 5.4 + 6.6 us -> 9.2).
+// GROUP: the signals have not been grouped, every workgroup lists those of its own piece (ChunkLists).
 template <int P, int S, bool GROUP>
 __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     const float* __restrict__ Y, const float* __restrict__ D, int K, int s0, int piece,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm, int32_t* __restrict__ supp,
-    float* __restrict__ coef, float* __restrict__ err, float* __restrict__ partial, GroupInKernel grp) {
+    float* __restrict__ coef, float* __restrict__ err, float* __restrict__ partial, ChunkLists lists) {
     constexpr int NW = kSaWaves, NTH = 64 * NW;
     constexpr int KS16 = P / 16;               // projection: steps of 16 dims
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-wide tiles per side of P_j
@@ -65,13 +64,10 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     constexpr int YU = P / 8 - 1 < 7 ? P / 8 - 1 : 7;      // of a signal's 16-byte units
     constexpr int NE = (S + 3) / 4;            // kept entries per lane and half tile
 
-    // piece_start[K+1] | tmp[16] | pad | Qs[Q_U] | per wavefront: stage | region; GROUP: while it groups, off[K+1] |
-    // run[NW][K] | list[m] in the place of the latter, and ids[kMinPiece] behind everything
-    extern __shared__ int lds[];
-    int* piece_start = lds;
-    int* tmp = lds + (K + 1);
-    const int head = ((K + 1 + 16) + 3) & ~3;  // keep the 16-byte units aligned
-    u32x4* Qs = reinterpret_cast<u32x4*>(lds + head);
+    // Qs[Q_U] | per wavefront: stage | region; GROUP: the table of `lists` in the place of the latter first, and
+    // ids[piece] behind everything
+    extern __shared__ __attribute__((aligned(16))) int lds[];
+    u32x4* Qs = reinterpret_cast<u32x4*>(lds);
     unsigned char* waves_base = reinterpret_cast<unsigned char*>(Qs + Q_U);
 
     const int tid = threadIdx.x;
@@ -79,26 +75,12 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     const int h = lane >> 5, n = lane & 31;
 
     int* ids = reinterpret_cast<int*>(waves_base + (size_t)NW * WAVE_B);
-    if constexpr (GROUP) {
-        int *off = reinterpret_cast<int*>(waves_base), *run = off + (K + 1), *list = run + NW * K;
-        group_in_lds<NW>(grp.blk, grp.m, K, off, run, list, [&](auto f) { wg_exclusive_scan4(f, K, off, tmp); });
-        offsets = off;
-        perm = list;
-    }
-    // pieces per block, as every kernel that walks the pieces counts them (K <= 4 * NTH)
-    wg_exclusive_scan4([&](int j) { return (offsets[j + 1] - offsets[j] + piece - 1) / piece; }, K,
-                       piece_start, tmp);
     const int id = blockIdx.x;
-    if (id >= piece_start[K]) return;          // uniform over the workgroup
-
-    const int j = upper_slot(piece_start, K, id);
-    const int pos0 = offsets[j] + (id - piece_start[j]) * piece;
-    const int cnt = min(piece, offsets[j + 1] - pos0);
-    if constexpr (GROUP) {                     // (the scan's barriers: list is there)
-        if (blockIdx.x == 0) grp.leave(K, offsets, perm);
-        if (tid < cnt) ids[tid] = perm[pos0 + tid];        // cnt <= kMinPiece (launcher)
-        __syncthreads();                       // the lists are dead
-    }
+    Piece pc;
+    if constexpr (GROUP) pc = lists.list<NW>(K, piece, id, reinterpret_cast<int*>(waves_base), ids);
+    else pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    if (pc.j < 0) return;                      // uniform over the workgroup
+    const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count;
 
     const int n_tiles = (cnt + 31) >> 5;
     // Signal ids are fetched two tiles ahead and the rows of Y one tile ahead: the loads of
@@ -241,8 +223,8 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
                 for (int t = 0; t < NE; ++t) {
                     const int pos = 4 * t + (lane >> 4);
                     const bool have = row < cnt_t && pos < s0;
-                    const int atom = stage[stage_idx<S>(row, 0, have ? pos : 0)];
-                    const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx<S>(row, 1, have ? pos : 0)]));
+                    const int atom = stage[stage_idx(row, 0, have ? pos : 0)];
+                    const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx(row, 1, have ? pos : 0)]));
                     at_[t] = tr_off(have ? (atom & (ROWS - 1)) : ROWS, sx);   // row ROWS: nobody reads it
                     *reinterpret_cast<unsigned short*>(xt + at_[t]) = (unsigned short)(w.hi >> 16);
                     *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = (unsigned short)(w.mid >> 16);
@@ -337,26 +319,26 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
     constexpr size_t wave_b = sa_wave_bytes<P, S>();
     const int piece = accum_piece(m, K);
     const int max_pieces = accum_max_pieces(m, K);
-    const int head = ((K + 1 + 16) + 3) & ~3;
-    const size_t lds = (size_t)head * sizeof(int) + (size_t)MT * (P / 16) * 3 * 64 * sizeof(u32x4) + kSaWaves * wave_b +
-                       (blk != nullptr ? kMinPiece * sizeof(int) : 0);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    size_t lds = (size_t)MT * (P / 16) * 3 * 64 * sizeof(u32x4) + kSaWaves * wave_b;
     if (blk != nullptr) {
-        static_assert((256 + 1 + kSaWaves * 256 + 1024) * sizeof(int) <= kSaWaves * wave_b, "the lists fit");
-        if (piece > kMinPiece) return hipErrorInvalidValue;
+        const GroupGeom g = group_geom(m);
+        lds += (size_t)piece * sizeof(int);
+        if (g.chunk != kListChunk || g.n_chunks > kListChunks || lds > 160 * 1024 ||
+            ChunkLists::lds_ints(kSaWaves, K, g.n_chunks) * sizeof(int) > kSaWaves * wave_b)
+            return hipErrorInvalidValue;
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S, true>), 160 * 1024);
             e != hipSuccess)
             return e;
         hipLaunchKernelGGL((select_accum_kernel<P, S, true>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K, s0,
                            piece, nullptr, nullptr, supp, coef, err, ws.partial,
-                           GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count});
+                           ChunkLists{blk, (int)m, g.n_chunks, ws.chunk_count, ws.counts, ws.offsets});
         return hipGetLastError();
     }
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S, false>), 160 * 1024);
         e != hipSuccess)
         return e;
     hipLaunchKernelGGL((select_accum_kernel<P, S, false>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K, s0,
-                       piece, ws.offsets, ws.perm, supp, coef, err, ws.partial, GroupInKernel{});
+                       piece, ws.offsets, ws.perm, supp, coef, err, ws.partial, ChunkLists{});
     return hipGetLastError();
 }
 
@@ -378,7 +360,7 @@ hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, co
 hipError_t launch_select_accum(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                                const Workspace& ws, int32_t* supp, float* coef, float* err,
                                hipStream_t st, const int32_t* blk) {
-    if (blk != nullptr && !group_in_select(p, K, m)) return hipErrorInvalidValue;
+    if (blk != nullptr && !lists_in_round(p, K, m)) return hipErrorInvalidValue;
     switch (p) {
         case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, st, blk);
         case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, st, blk);

@@ -13,7 +13,7 @@ namespace sbo {
 // residual (sum of the dropped c^2) of signal i (original index; active = lane has a
 // signal).  Exact magnitude ties beyond the trivial one are resolved by a sequential
 // per-signal pass through the wave-private LDS tile ct, 16 atoms at a time.  The (atom, coefficient)
-// rows are first compacted in the wave-private LDS area stage[2][S][32] (words) and then
+// rows are first compacted in the wave-private LDS area stage[S + 1][2][32] (words) and then
 // written with one or a few wide stores per lane (lane half 0: supp row, half 1: coef row),
 // because scattered 4-byte stores to rows in original signal order are what this step
 // would otherwise wait on.  ct is touched only on the tie path (*used_ct is then set).  On return the compacted rows
@@ -22,11 +22,11 @@ namespace sbo {
 //
 // What bounds it: instruction issue (it was 7500 cycles a tile of 32 signals for a wavefront, most of them for a
 // branch and two swizzled addresses per entry; positions now come from packed counts, and an entry is a
-// comparison, an address and two predicated stores: 100003 signals, p = 64: 32.8 -> 29.4 us).
+// comparison, an address and a store: 100003 signals, p = 64: 32.8 -> 29.4 us).
 // Both areas are as small as that: with 16 entries and all p coefficients of a signal in them (12 KiB a wavefront at
 // p = 64) LDS held three wavefronts of select_kernel on a SIMD, and a few workgroups a second round (29.8 -> 26.3 us).
 template <int S>
-constexpr int kSelectStageWords = 32 * 2 * S;
+constexpr int kSelectStageWords = 32 * 2 * (S + 1);
 constexpr int kSelectTieWords = 32 * (16 + 1);         // [signal][atom], a column of padding
 
 // 8 consecutive values as the three bf16 parts of an operand unit: out[0], out[step], out[2 step].
@@ -38,10 +38,9 @@ __device__ __forceinline__ void split_unit(const f32x4* v, u32x4* out, int step)
     out[2 * step] = u32x4{a.lo, b.lo, c.lo, d.lo};
 }
 
-// Word index of entry `pos` (< S) of signal row n in the stage area; kind 0 = atom, 1 =
-// coefficient bits.  All lanes n of one entry are neighbours.
-template <int S>
-__device__ __forceinline__ int stage_idx(int n, int kind, int pos) { return (kind * S + pos) * 32 + n; }
+// Word index of entry `pos` of signal row n in the stage area; kind 0 = atom, 1 =
+// coefficient bits (one instruction writes both).  All lanes n of one entry are neighbours.  Entry S is nobody's.
+__device__ __forceinline__ int stage_idx(int n, int kind, int pos) { return (2 * pos + kind) * 32 + n; }
 
 // The value in the other lane of the pair (all lanes active).
 __device__ __forceinline__ unsigned pair_other(unsigned x, int h) {
@@ -110,6 +109,8 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
         // Every entry with |c| >= tau is kept.  Emit in ascending atom order.
         unsigned before = 0;                   // entries of earlier words
         float dropped = 0.f;
+        int h4 = h * 4;
+        asm volatile("" : "+v"(h4));           // or the atoms of all entries are kept in registers over the caller's loop
 #pragma unroll
         for (int w = 0; w < NWD; ++w) {
             const unsigned both = own[w] + par[w], upto = both * 0x01010101u;      // inclusive sums, per byte
@@ -121,13 +122,12 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int f = 16 * w + 4 * g + e;
-                    const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + h * 4 + (f & 3);
+                    const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + (f & 3) + h4;
                     const bool keep = mag[f] >= keep_from;
-                    if (keep) {
-                        int* at = stage + stage_idx<S>(n, 0, (int)pos);
-                        at[0] = atom;
-                        at[S * 32] = __builtin_bit_cast(int, c[f]);
-                    }
+                    // (what is not kept goes to entry S: a branch costs more)
+                    int* at = stage + stage_idx(n, 0, keep ? (int)pos : S);
+                    at[0] = atom;
+                    at[32] = __builtin_bit_cast(int, c[f]);
                     pos += keep;
                     const float rest = keep || atom >= P ? 0.f : c[f];
                     dropped = fmaf(rest, rest, dropped);
@@ -165,8 +165,8 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                         ++taken_eq;
                     }
                     if (take && pos < s0) {
-                        stage[stage_idx<S>(n, 0, pos)] = k0 + k;
-                        stage[stage_idx<S>(n, 1, pos)] = __builtin_bit_cast(int, v);
+                        stage[stage_idx(n, 0, pos)] = k0 + k;
+                        stage[stage_idx(n, 1, pos)] = __builtin_bit_cast(int, v);
                         ++pos;
                     } else {
                         dropped += v * v;
@@ -184,16 +184,16 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (active) {
         int* dst = (h ? reinterpret_cast<int*>(coef) : supp) + i * s0;
-        const int* row = stage + stage_idx<S>(n, h, 0);
+        const int* row = stage + stage_idx(n, h, 0);           // an entry every 64 words
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         typedef int i32x2 __attribute__((ext_vector_type(2)));
         if ((s0 & 3) == 0) {
             for (int t = 0; t < s0; t += 4)
-                *reinterpret_cast<i32x4*>(dst + t) = i32x4{row[t * 32], row[t * 32 + 32], row[t * 32 + 64], row[t * 32 + 96]};
+                *reinterpret_cast<i32x4*>(dst + t) = i32x4{row[t * 64], row[t * 64 + 64], row[t * 64 + 128], row[t * 64 + 192]};
         } else if ((s0 & 1) == 0) {
-            for (int t = 0; t < s0; t += 2) *reinterpret_cast<i32x2*>(dst + t) = i32x2{row[t * 32], row[t * 32 + 32]};
+            for (int t = 0; t < s0; t += 2) *reinterpret_cast<i32x2*>(dst + t) = i32x2{row[t * 64], row[t * 64 + 64]};
         } else {
-            for (int t = 0; t < s0; ++t) dst[t] = row[t * 32];
+            for (int t = 0; t < s0; ++t) dst[t] = row[t * 64];
         }
     }
     __builtin_amdgcn_wave_barrier();           // stage is reused by the caller's next tile

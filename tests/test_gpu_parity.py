@@ -305,6 +305,26 @@ def test_iterate_groups_small_sets_in_the_select_kernel(p, K, m):
             np.testing.assert_array_equal(perm, orc.o_group(a[1], K)[2])
 
 
+@pytest.mark.parametrize("p,K,m,s0", [(64, 16, 16384, 6), (64, 56, 32768, 8), (64, 57, 32768, 8), (64, 3, 32769, 5), (64, 2, 32767, 4),
+                                      (32, 24, 511, 4), (32, 7, 513, 3), (32, 70, 20001, 4), (16, 4, 1024, 3), (16, 256, 4096, 2),
+                                      (16, 257, 4000, 2), (16, 400, 1000, 2), (64, 1, 1, 8), (16, 5, 33, 3)])
+@pytest.mark.parametrize("skewed", [False, True], ids=["even", "skewed"])
+def test_iterate_lists_the_signals_of_a_piece_from_the_histograms(p, K, m, s0, skewed):
+    """Small sets (up to 32768 signals and 4096 histogram entries) are not grouped in sbo_iterate.  A round on the blocks that it chose,
+    which groups them, has the same sums in the same order, so every bit is the same; and the histograms are left zero."""
+    pr = synth.generate(synth.custom(f"lists_p{p}_K{K}", p=p, K=K, m=m, s0=s0, snr_db=20.0, zipf_s=2.0 if skewed else None))
+    with Sbo(p, K, s0, m) as g:
+        for _ in range(2):
+            Q, blk, supp, coef, err, _sq = g.iterate(pr.Y, pr.D_init, 1)[:6]
+            Q2, supp2, coef2, err2 = g.train_rounds(pr.Y, blk, pr.D_init, 1)
+            for a, b in ((Q, Q2), (supp, supp2), (coef, coef2), (err, err2)):
+                np.testing.assert_array_equal(a, b)
+        np.testing.assert_array_equal(g.code(pr.Y, pr.D_init)[0], blk)
+        counts, _off, perm = g.group(blk)
+        np.testing.assert_array_equal(counts, np.bincount(blk, minlength=K))
+        np.testing.assert_array_equal(perm, orc.o_group(blk, K)[2])
+
+
 UPDATE_CASES = [
     ("tiny", dict()),
     ("patch8", dict(m=4096 + 77)),
