@@ -19,13 +19,11 @@ namespace sbo {
 
 namespace {
 
-// GROUP: the grouping of a small set (m <= kGroupInSelect) without a launch of its own.  Every workgroup sorts all
-// choices in its own LDS (the stable order of group.hip: each wavefront a quarter, counts, scan, scatter); the
-// first one also leaves counts, offsets and perm in memory and sets the histograms of the block choice back to zero.
-// A launch in a stream costs 4.5 us whatever it does, the sort in LDS less than that.
-template <int P, int S, bool GROUP>
+// GROUP: a small set (group_in_select) without a grouping launch: every workgroup reads all choices and every wavefront finds
+// the signals of its tile among them (225 signals, K = 32, p = 64: 11.8 us with a sort of them all in LDS).
+template <int P, int S0, bool GROUP>
 __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y,
-                                                     const float* __restrict__ D, int K, int s0,
+                                                     const float* __restrict__ D, int K,
                                                      const int32_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ perm,
                                                      int32_t* __restrict__ supp,
@@ -34,36 +32,24 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     constexpr int KS = P / 2;
     constexpr int QN = P / 8;
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-row tiles per block
-    constexpr int NVL = MT * 16;               // accumulator values per lane
-    static_assert(S <= NVL, "sort width exceeds the values of one lane");
-
     extern __shared__ __attribute__((aligned(16))) int lds[];      // stage[4][...] | ties[4][...]
     int* stage_all = lds;
-    float* ties_all = reinterpret_cast<float*>(stage_all + 4 * kSelectStageWords<S>);
+    float* ties_all = reinterpret_cast<float*>(stage_all + 4 * kSelectStageWords<S0>);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, n = lane & 31;
 
-    if constexpr (GROUP) {                     // behind the tiles: tmp[16] | off[K+1] | run[4][K] | list[m]
-        int *tmp = reinterpret_cast<int*>(ties_all + 4 * kSelectTieWords), *off = tmp + 16;
-        int *run = off + (K + 1), *list = run + 4 * K;
-        if (g.E != nullptr) {                  // uniform
-            int* choice = list + g.m;
-            g.choose<256>(K, choice);
-            g.blk = choice;
-        }
-        group_in_lds<4>(g.blk, g.m, K, off, run, list, [&](auto f) { wg_exclusive_scan4(f, K, off, tmp); });
-        __syncthreads();
-        if (blockIdx.x == 0) g.leave(K, off, list);
-        offsets = off;
-        perm = list;
-    }
-    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, 32, (int)blockIdx.x * 4 + wave);
+    // GROUP, behind the tiles: count[K] | ids[4][32] | choice[m]
+    int* count = reinterpret_cast<int*>(ties_all + 4 * kSelectTieWords);
+    int *ids = count + K + wave * 32, *choice = count + K + 4 * 32;
+    if constexpr (GROUP) g.choose<256>(K, choice, count);
+    const Piece pc = find_piece([&](int j) { return GROUP ? count[j] : offsets[j + 1] - offsets[j]; }, K, 32, (int)blockIdx.x * 4 + wave);
     if (pc.j < 0) return;                      // no workgroup barrier below this line
+    if constexpr (GROUP) g.list(choice, pc, ids);
     const int j = pc.j;
     const bool active = n < pc.count;
-    const int64_t i = active ? perm[pc.before + pc.rank + n] : -1;
+    const int64_t i = active ? (GROUP ? ids[n] : perm[pc.before + pc.rank + n]) : -1;
 
     // B operand: this lane's half of the dims of signal i.
     float yb[KS];
@@ -101,8 +87,8 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
         }
     }
 
-    tile_select<P, S>(acc, h, n, active, i, s0, ties_all + wave * kSelectTieWords,
-                             stage_all + wave * kSelectStageWords<S>, supp, coef, err);
+    tile_select<P, S0>(acc, h, n, active, i, ties_all + wave * kSelectTieWords, stage_all + wave * kSelectStageWords<S0>, supp,
+                       coef, err);
 }
 
 // The same with the six bf16 products (every arithmetic but SBO_ARITH_F32), for larger sets.  A workgroup takes a piece of
@@ -111,9 +97,9 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
 // 64 lines an instruction, 16 instructions a tile, and few of them in flight; here a tile reads LDS and has 1500 cycles
 // of matrix work, and what is left is the selection's instructions (select_tile.h).  Coefficients against 64 bits, of
 // |y|: rms 2.3e-8 to 5.5e-8 (select_kernel 3.1e-8 to 8.5e-8), at most 3.1e-7 (4.6e-7).
-template <int P, int S, int NW>
+template <int P, int S0, int NW>
 __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* __restrict__ Y, const float* __restrict__ D,
-                                                                  int K, int s0, int piece,
+                                                                  int K, int piece,
                                                                   const int32_t* __restrict__ offsets,
                                                                   const int32_t* __restrict__ perm,
                                                                   int32_t* __restrict__ supp, float* __restrict__ coef,
@@ -130,11 +116,12 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
     if (pc.j < 0) return;                      // uniform over the workgroup
     const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count, n_tiles = (cnt + 31) >> 5;
 
-    // Ids two tiles ahead, rows one tile ahead (lanes past the end read the row of signal 0 and are zeroed when consumed).
-    auto tile_id = [&](int t) -> int { return t * 32 + n < cnt ? perm[pos0 + t * 32 + n] : -1; };
+    // Ids two tiles ahead, rows one tile ahead (lanes past the end take the last signal of the piece once more and keep
+    // nothing of it).
+    auto tile_id = [&](int t) -> int { return perm[pos0 + min(t * 32 + n, cnt - 1)]; };
     f32x4 raw[KS16][2];                        // this lane's dims ks*16 + h*8 .. +7 of its signal
     auto load_rows = [&](int sid) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)max(sid, 0) * P + h * 8);
+        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)sid * P + h * 8);
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks) {
             raw[ks][0] = src[ks * 4];
@@ -152,16 +139,13 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
     }
     __syncthreads();
 
-    int* stage = lds + Q_U * 4 + wave * kSelectStageWords<S>;
-    float* ties = reinterpret_cast<float*>(lds + Q_U * 4 + NW * kSelectStageWords<S>) + wave * kSelectTieWords;
+    int* stage = lds + Q_U * 4 + wave * kSelectStageWords<S0>;
+    float* ties = reinterpret_cast<float*>(lds + Q_U * 4 + NW * kSelectStageWords<S0>) + wave * kSelectTieWords;
     for (int tile = wave; tile < n_tiles; tile += NW) {
         const int64_t i = i_cur;
         u32x4 yq[KS16][3];
 #pragma unroll
-        for (int ks = 0; ks < KS16; ++ks) {
-            if (i < 0) raw[ks][0] = raw[ks][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-            split_unit(raw[ks], yq[ks], 1);
-        }
+        for (int ks = 0; ks < KS16; ++ks) split_unit(raw[ks], yq[ks], 1);
         i_cur = i_next;
         i_next = tile_id(tile + 2 * NW);
         load_rows(i_cur);
@@ -188,7 +172,7 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
         // An infinite entry has no three parts (infinity less itself): the coefficients of such a signal in fp32.
         const bool bad = acc[0][0] != acc[0][0];
         if (__any(bad)) {                      // uniform, rare
-            const float* row = Y + max(i, (int64_t)0) * P;
+            const float* row = Y + i * P;
 #pragma unroll 1
             for (int d = 0; d < P; ++d) {
                 const float y = row[d];
@@ -200,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
                 }
             }
         }
-        tile_select<P, S>(acc, h, n, i >= 0, i, s0, ties, stage, supp, coef, err);
+        tile_select<P, S0>(acc, h, n, tile * 32 + n < cnt, i, ties, stage, supp, coef, err);
     }
 }
 
@@ -577,17 +561,18 @@ hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int 
 // eight of them (two workgroups on a CU) 36.6 to 43.
 constexpr int64_t kSplitMinSignals = 32768;
 
-template <int P, int S>
-hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws,
+template <int P, int S0>
+hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
                      int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
-    size_t lds = 4 * (kSelectStageWords<S> + kSelectTieWords) * sizeof(int);
+    size_t lds = 4 * (kSelectStageWords<S0> + kSelectTieWords) * sizeof(int);
     if (blk != nullptr) {
-        lds += (16 + 5 * K + 1 + (choose ? 2 : 1) * m) * sizeof(int);       // at most 60 KiB in all (choose: K <= 64)
-        hipLaunchKernelGGL((select_kernel<P, S, true>), grid, dim3(256), lds, st, Y, D, K, s0, nullptr, nullptr, supp,
+        if (K > GroupInKernel::kMostBlocks) return hipErrorInvalidValue;
+        lds += (K + 4 * 32 + m) * sizeof(int);             // less than 60 KiB in all
+        hipLaunchKernelGGL((select_kernel<P, S0, true>), grid, dim3(256), lds, st, Y, D, K, nullptr, nullptr, supp,
                            coef, err,
-                           GroupInKernel{blk, (int)m, ws.counts, ws.offsets, ws.perm, ws.chunk_count, choose ? ws.part_E : nullptr, blk});
+                           GroupInKernel{blk, (int)m, ws.chunk_count, choose ? ws.part_E : nullptr});
         return hipGetLastError();
     }
     if constexpr (P >= 32) if (split && m >= kSplitMinSignals) {
@@ -595,15 +580,15 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
         const int64_t resident = 256 * (P == 64 ? 3 : 4) - K / 2;          // less the blocks' unfinished pieces
         const int tiles = (int)std::min<int64_t>(4, (m + 32 * NW * resident - 1) / (32 * NW * resident));
         const int piece = 32 * NW * tiles;
-        lds = (4 * Q_U + NW * (kSelectStageWords<S> + kSelectTieWords)) * sizeof(int);
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_split_kernel<P, S, NW>), 160 * 1024);
+        lds = (4 * Q_U + NW * (kSelectStageWords<S0> + kSelectTieWords)) * sizeof(int);
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_split_kernel<P, S0, NW>), 160 * 1024);
             e != hipSuccess)
             return e;
-        hipLaunchKernelGGL((select_split_kernel<P, S, NW>), dim3((unsigned)((m + piece - 1) / piece + K)), dim3(64 * NW), lds,
-                           st, Y, D, K, s0, piece, ws.offsets, ws.perm, supp, coef, err);
+        hipLaunchKernelGGL((select_split_kernel<P, S0, NW>), dim3((unsigned)((m + piece - 1) / piece + K)), dim3(64 * NW), lds,
+                           st, Y, D, K, piece, ws.offsets, ws.perm, supp, coef, err);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((select_kernel<P, S, false>), grid, dim3(256), lds, st, Y, D, K, s0, ws.offsets,
+    hipLaunchKernelGGL((select_kernel<P, S0, false>), grid, dim3(256), lds, st, Y, D, K, ws.offsets,
                        ws.perm, supp, coef, err, GroupInKernel{});
     return hipGetLastError();
 }
@@ -611,11 +596,14 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
 template <int P>
 hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
                     int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
-    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
-    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
-    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
-    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
-    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, blk, choose, split, st);
+    switch (s0) {
+#define SBO_CASE(N) \
+    case N: return launch_ps<P, N>(Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
+        SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
+        SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
+#undef SBO_CASE
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace

@@ -417,75 +417,61 @@ __device__ __forceinline__ void scatter_chunk(const int32_t* __restrict__ blk, i
     }
 }
 
-// The grouping of a small set by one workgroup of NW wavefronts, in LDS (the stable order of group.hip: each wavefront
-// its share of the signals, counts, scan, scatter): off[K+1], list[m], run[NW][K], tmp[16].  list is there after the
-// caller's next barrier.
-template <int NW, class Scan>
-__device__ __forceinline__ void group_in_lds(const int32_t* __restrict__ blk, int m, int K, int* off, int* run, int* list,
-                                             Scan scan) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (m + NW - 1) / NW, beg = min(m, wave * per), end = min(m, beg + per);
-    int key[1];
-    load_keys(blk, beg, end, key);
-    for (int j = tid; j < NW * K; j += 64 * NW) run[j] = 0;
-    __syncthreads();
-    for (int i = beg + lane; i < end; i += 64) {
-        const int b = i < beg + 64 ? key[0] : blk[i];
-        if ((unsigned)b < (unsigned)K) atomicAdd(&run[wave * K + b], 1);
-    }
-    __syncthreads();
-    scan([&](int j) {
-        int v = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) v += run[w * K + j];
-        return v;
-    });
-    for (int j = tid; j < K; j += 64 * NW) {   // counts of the wavefronts -> where each one's signals start
-        int at = off[j];
-        for (int w = 0; w < NW; ++w) {
-            const int v = run[w * K + j];
-            run[w * K + j] = at;
-            at += v;
-        }
-    }
-    __syncthreads();
-    scatter_chunk(blk, key, beg, end, K, run + wave * K, list);
-}
-// ... and what launch_group would have left in memory, by one workgroup of the launch (after a barrier).
+// A small set that has not been grouped: every wavefront finds the signals of its own tile among all choices, in LDS.
 struct GroupInKernel {
-    const int32_t* blk;
+    int32_t* blk;              // the choices; written first where E is given
     int m;
-    int32_t *counts, *offsets, *perm, *chunk_count;
-    const float* E = nullptr;                  // [K][m] energies to choose from first
-    int32_t* chosen = nullptr;                 // where the choice goes
-    // The block of largest energy of every signal (the lowest on a tie) -> choice[m] in LDS; N threads.
+    int32_t* chunk_count;      // the choice's histograms, which nobody needs: set to zero
+    const float* E = nullptr;  // [K][m] energies to choose from
+    static constexpr int kMostBlocks = 256;                // K at most (launcher)
+
+    // The block of largest energy of every signal (the lowest on a tie), or the choices as they are -> choice[m]; their numbers ->
+    // count[K]; N threads.
     template <int N>
-    __device__ __forceinline__ void choose(int K, int* choice) const {
-        constexpr int A = 16;                  // energies on their way at a time
-        for (int i = threadIdx.x; i < m; i += N) {
-            float top = -1.f;
+    __device__ __forceinline__ void choose(int K, int* choice, int* count) const {
+        constexpr int A = 32;                  // energies on their way at a time
+        const int tid = threadIdx.x;
+        for (int j = tid; j < K; j += N) count[j] = 0;
+        __syncthreads();
+        for (int i = tid; i < m; i += N) {
             int best = 0;
-            for (int j0 = 0; j0 < K; j0 += A) {
-                float e[A];
+            if (E != nullptr) {                // uniform
+                float top = -1.f;
+                for (int j0 = 0; j0 < K; j0 += A) {
+                    float e[A];
 #pragma unroll
-                for (int a = 0; a < A; ++a) e[a] = j0 + a < K ? E[(int64_t)(j0 + a) * m + i] : -1.f;
+                    for (int a = 0; a < A; ++a) e[a] = E[(int64_t)min(j0 + a, K - 1) * m + i];     // (the last one again: no larger)
 #pragma unroll
-                for (int a = 0; a < A; ++a) {
-                    best = e[a] > top ? j0 + a : best;
-                    top = fmaxf(top, e[a]);
+                    for (int a = 0; a < A; ++a) {
+                        best = e[a] > top ? j0 + a : best;
+                        top = fmaxf(top, e[a]);
+                    }
                 }
+                if (blockIdx.x == 0) blk[i] = best;
+            } else {
+                best = blk[i];
             }
             choice[i] = best;
-            if (blockIdx.x == 0) chosen[i] = best;
+            if ((unsigned)best < (unsigned)K) atomicAdd(&count[best], 1);  // out-of-range ids are dropped
         }
+        if (blockIdx.x == 0)
+            for (int e = tid; e < (m + 511) / 512 * K; e += N) chunk_count[e] = 0;
         __syncthreads();
     }
-    __device__ __forceinline__ void leave(int K, const int* off, const int* list) const {
-        const int tid = threadIdx.x, n = blockDim.x;
-        for (int j = tid; j <= K; j += n) offsets[j] = off[j];
-        for (int j = tid; j < K; j += n) counts[j] = off[j + 1] - off[j];
-        for (int e = tid; e < (m + 511) / 512 * K; e += n) chunk_count[e] = 0;
-        for (int i = tid; i < off[K]; i += n) perm[i] = list[i];
+    // The signals of a piece, in order -> ids[pc.count]; a wavefront.
+    __device__ __forceinline__ void list(const int* choice, const Piece& pc, int* ids) const {
+        const int lane = threadIdx.x & 63;
+        int at = -pc.rank;                     // of the next one, in the piece
+        for (int i0 = 0; i0 < m && at < pc.count; i0 += 64) {              // uniform
+            const bool mine = choice[min(i0 + lane, m - 1)] == pc.j && i0 + lane < m;
+            const unsigned long long mask = __ballot(mine);
+            const int to = at + __popcll(mask & ((1ull << lane) - 1ull));
+            if (mine && to >= 0 && to < pc.count) ids[to] = i0 + lane;
+            at += __popcll(mask);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 };
 

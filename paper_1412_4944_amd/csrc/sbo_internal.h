@@ -241,9 +241,9 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // p = 256 reads Q in operand order: ws.dsb (split: the bf16 matrix cores) or ws.dsw (fp32 matrix
 // instruction).  ops_valid: that buffer already holds this D (launch_dict_swizzle[_split]);
 // otherwise it is rewritten first.  p <= 64 reads D itself and ignores both flags.
-// blk: nullptr, or the choices of the signals, which the kernel then groups itself (where group_in_select says so;
-// launch_group is not called, and what it leaves in ws is left there too).  The line: every workgroup sorts the whole
-// set, so it has to be small, and its lists have to fit 64 KiB of LDS beside the tiles.
+// blk: nullptr, or the choices of signals that have not been grouped (where group_in_select says so; the histograms in
+// ws.chunk_count are set to zero, as launch_group would).  The line: every workgroup reads the whole set, so it has to be
+// small, and has to fit 64 KiB of LDS beside the tiles.
 // choose: blk is written first, from the energies in ws.part_E (launch_energy_direct).
 // by_pos (p = 256): the codes of the signal at position q of ws.perm go to row q, not to the row of the signal: where a
 // signal is in several blocks (sbo_learn's initial sets).  launch_accumulate reads them likewise.

@@ -36,17 +36,17 @@ namespace {
 constexpr int kSaWaves = 8;
 
 // LDS of a wavefront: the stage and the operand tiles (or the scratch for ties); at the end a copy of its accumulators.
-template <int P, int S>
+template <int P, int S0>
 constexpr int sa_wave_bytes() {
     constexpr int MT = P >= 32 ? P / 32 : 1, ops = 6 * (MT * 32 + 1) * 32, ct = kSelectTieWords * 4;
-    constexpr int use = kSelectStageWords<S> * 4 + (ops > ct ? ops : ct), copy = MT * MT * 4 * 64 * 16;
+    constexpr int use = kSelectStageWords<S0> * 4 + (ops > ct ? ops : ct), copy = MT * MT * 4 * 64 * 16;
     return use > copy ? use : copy;
 }
 
 // GROUP: the signals have not been grouped, every workgroup lists those of its own piece (ChunkLists).
-template <int P, int S, bool GROUP>
+template <int P, int S0, bool GROUP>
 __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
-    const float* __restrict__ Y, const float* __restrict__ D, int K, int s0, int piece,
+    const float* __restrict__ Y, const float* __restrict__ D, int K, int piece,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm, int32_t* __restrict__ supp,
     float* __restrict__ coef, float* __restrict__ err, float* __restrict__ partial, ChunkLists lists) {
     constexpr int NW = kSaWaves, NTH = 64 * NW;
@@ -59,10 +59,10 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     constexpr int CT_B = kSelectTieWords * 4;           // tie-breaking scratch of tile_select
     constexpr int OPS_B = 6 * PLANE_B;         // x tile (3 parts) + y tile (3 parts)
     constexpr int REGION_B = (OPS_B > CT_B ? OPS_B : CT_B);
-    constexpr int WAVE_B = sa_wave_bytes<P, S>();
-    static_assert(kSelectStageWords<S> * 4 + REGION_B <= WAVE_B, "stage and region");
+    constexpr int WAVE_B = sa_wave_bytes<P, S0>();
+    static_assert(kSelectStageWords<S0> * 4 + REGION_B <= WAVE_B, "stage and region");
     constexpr int YU = P / 8 - 1 < 7 ? P / 8 - 1 : 7;      // of a signal's 16-byte units
-    constexpr int NE = (S + 3) / 4;            // kept entries per lane and half tile
+    constexpr int NE = (S0 + 3) / 4;            // kept entries per lane and half tile
 
     // Qs[Q_U] | per wavefront: stage | region; GROUP: the table of `lists` in the place of the latter first, and
     // ids[piece] behind everything
@@ -86,15 +86,15 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     // Signal ids are fetched two tiles ahead and the rows of Y one tile ahead: the loads of
     // the next tile are issued as soon as the current rows have been split, and land while
     // the matrix work and the selection run.  The loads are unconditional (lanes past the end
-    // of the piece read the row of signal 0 and are zeroed when consumed).  Those of the first tile are on their way
+    // of the piece take its last signal once more and keep nothing of it).  Those of the first tile are on their way
     // before Q_j is split (50021 signals, K = 24, p = 32: 10.0 -> 9.4 us; 262144, p = 64: no difference).
     auto tile_id = [&](int t) -> int {
-        if (t >= n_tiles || n >= min(32, cnt - t * 32)) return -1;
-        return GROUP ? ids[t * 32 + n] : perm[pos0 + t * 32 + n];
+        const int at = min(t * 32 + n, cnt - 1);
+        return GROUP ? ids[at] : perm[pos0 + at];
     };
     f32x4 raw[KS16][2];                        // this lane's dims ks*16 + h*8 .. +7 of its signal
     auto load_rows = [&](int sid) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)max(sid, 0) * P + h * 8);
+        const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)sid * P + h * 8);
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks) {
             raw[ks][0] = src[ks * 4];
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
         out[128] = u32x4{a.lo, b.lo, c.lo, d.lo};
     }
     int* stage = reinterpret_cast<int*>(waves_base + (size_t)wave * WAVE_B);
-    unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords<S>);
+    unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords<S0>);
     unsigned char* xt = region;                // [3 parts][ROWS atoms][16 signals] bf16
     unsigned char* yt = region + 3 * PLANE_B;  // [3 parts][16 signals][P dims] bf16
     // the x tile starts out zero (and is left zero by every tile)
@@ -143,18 +143,14 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
 
     for (int tile = wave; tile < n_tiles; tile += NW) {
         const int64_t i = i_cur;
-        const bool active = i >= 0;
+        const bool active = tile * 32 + n < cnt;
         const int cnt_t = min(32, cnt - tile * 32);        // signals in this tile (uniform)
 
         // y in three bf16 parts (B operand of the projection)
         u32x4 yq[KS16][3];
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks) {
-            f32x4 v0 = raw[ks][0], v1 = raw[ks][1];
-            if (!active) {
-                v0 = f32x4{0.f, 0.f, 0.f, 0.f};
-                v1 = v0;
-            }
+            const f32x4 v0 = raw[ks][0], v1 = raw[ks][1];
             const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
             const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
             yq[ks][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
@@ -189,8 +185,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
         // product below.
         // The tie-breaking scratch is the operand region: the x tile is zeroed again if it was used.
         bool ties = false;
-        tile_select<P, S>(acc, h, n, active, i, s0, reinterpret_cast<float*>(region), stage, supp, coef,
-                                 err, &ties);
+        tile_select<P, S0>(acc, h, n, active, i, reinterpret_cast<float*>(region), stage, supp, coef, err, &ties);
         if (ties) {                            // uniform (rare): the scratch overwrote the zeroed x tile
             for (int e = lane; e < 3 * PLANE_B / 16; e += 64)
                 reinterpret_cast<u32x4*>(xt)[e] = u32x4{0u, 0u, 0u, 0u};
@@ -222,7 +217,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
 #pragma unroll
                 for (int t = 0; t < NE; ++t) {
                     const int pos = 4 * t + (lane >> 4);
-                    const bool have = row < cnt_t && pos < s0;
+                    const bool have = row < cnt_t && pos < S0;
                     const int atom = stage[stage_idx(row, 0, have ? pos : 0)];
                     const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx(row, 1, have ? pos : 0)]));
                     at_[t] = tr_off(have ? (atom & (ROWS - 1)) : ROWS, sx);   // row ROWS: nobody reads it
@@ -312,11 +307,11 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     }
 }
 
-template <int P, int S>
-hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws,
+template <int P, int S0>
+hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
                      int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    constexpr size_t wave_b = sa_wave_bytes<P, S>();
+    constexpr size_t wave_b = sa_wave_bytes<P, S0>();
     const int piece = accum_piece(m, K);
     const int max_pieces = accum_max_pieces(m, K);
     size_t lds = (size_t)MT * (P / 16) * 3 * 64 * sizeof(u32x4) + kSaWaves * wave_b;
@@ -326,18 +321,18 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
         if (g.chunk != kListChunk || g.n_chunks > kListChunks || lds > 160 * 1024 ||
             ChunkLists::lds_ints(kSaWaves, K, g.n_chunks) * sizeof(int) > kSaWaves * wave_b)
             return hipErrorInvalidValue;
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S, true>), 160 * 1024);
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, true>), 160 * 1024);
             e != hipSuccess)
             return e;
-        hipLaunchKernelGGL((select_accum_kernel<P, S, true>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K, s0,
+        hipLaunchKernelGGL((select_accum_kernel<P, S0, true>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K,
                            piece, nullptr, nullptr, supp, coef, err, ws.partial,
                            ChunkLists{blk, (int)m, g.n_chunks, ws.chunk_count, ws.counts, ws.offsets});
         return hipGetLastError();
     }
-    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S, false>), 160 * 1024);
+    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, false>), 160 * 1024);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((select_accum_kernel<P, S, false>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K, s0,
+    hipLaunchKernelGGL((select_accum_kernel<P, S0, false>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K,
                        piece, ws.offsets, ws.perm, supp, coef, err, ws.partial, ChunkLists{});
     return hipGetLastError();
 }
@@ -345,11 +340,14 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, int s0, c
 template <int P>
 hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
                     int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk) {
-    if (s0 <= 1) return launch_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, st, blk);
-    if (s0 <= 2) return launch_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, st, blk);
-    if (s0 <= 4) return launch_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, st, blk);
-    if (s0 <= 8) return launch_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, st, blk);
-    return launch_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, st, blk);
+    switch (s0) {
+#define SBO_CASE(N) \
+    case N: return launch_ps<P, N>(Y, m, D, K, ws, supp, coef, err, st, blk);
+        SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
+        SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
+#undef SBO_CASE
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "device_utils.h"
+#include "energy_networks.h"
 
 namespace sbo {
 
@@ -25,8 +26,8 @@ namespace sbo {
 // comparison, an address and a store: 100003 signals, p = 64: 32.8 -> 29.4 us).
 // Both areas are as small as that: with 16 entries and all p coefficients of a signal in them (12 KiB a wavefront at
 // p = 64) LDS held three wavefronts of select_kernel on a SIMD, and a few workgroups a second round (29.8 -> 26.3 us).
-template <int S>
-constexpr int kSelectStageWords = 32 * 2 * (S + 1);
+template <int S0>
+constexpr int kSelectStageWords = 32 * 2 * (S0 + 1);
 constexpr int kSelectTieWords = 32 * (16 + 1);         // [signal][atom], a column of padding
 
 // 8 consecutive values as the three bf16 parts of an operand unit: out[0], out[step], out[2 step].
@@ -39,7 +40,7 @@ __device__ __forceinline__ void split_unit(const f32x4* v, u32x4* out, int step)
 }
 
 // Word index of entry `pos` of signal row n in the stage area; kind 0 = atom, 1 =
-// coefficient bits (one instruction writes both).  All lanes n of one entry are neighbours.  Entry S is nobody's.
+// coefficient bits (one instruction writes both).  All lanes n of one entry are neighbours.  Entry s0 is nobody's.
 __device__ __forceinline__ int stage_idx(int n, int kind, int pos) { return (2 * pos + kind) * 32 + n; }
 
 // The value in the other lane of the pair (all lanes active).
@@ -53,13 +54,12 @@ __device__ __forceinline__ float pair_other(float x, int h) {
 }
 __device__ __forceinline__ int pair_other(int x, int h) { return (int)pair_other((unsigned)x, h); }
 
-template <int P, int S>
-__device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, bool active, int64_t i,
-                                            int s0, float* ct, int* stage,
+template <int P, int S0>
+__device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, bool active, int64_t i, float* ct, int* stage,
                                             int32_t* __restrict__ supp, float* __restrict__ coef,
                                             float* __restrict__ err, bool* used_ct = nullptr) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
-    constexpr int NVL = MT * 16;
+    constexpr int NVL = MT * 16, S = pow2_at_least(S0);
     constexpr int LDC = kSelectTieWords / 32;
     static_assert(P <= 64, "p = 256 selects in select_wide_split_kernel");
     static_assert(S <= NVL, "sort width exceeds the values of one lane");
@@ -72,17 +72,11 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
         mag[f] = atom < P ? fabsf(c[f]) : -1.f;
     }
 
-    // tau = s0-th largest magnitude of the signal.
-    float top[S], oth[S], mrg[S];
+    // tau = s0-th largest magnitude of the signal: the s0 largest are max(top_t, oth_{s0-1-t}).
+    float top[S], tau = __builtin_inff();
     top_sorted<NVL, S>(mag, top);
 #pragma unroll
-    for (int t = 0; t < S; ++t) oth[t] = pair_other(top[t], h);
-#pragma unroll
-    for (int t = 0; t < S; ++t) mrg[t] = fmaxf(top[t], oth[S - 1 - t]);
-    bitonic_merge_desc<S>(mrg);
-    float tau = mrg[0];
-#pragma unroll
-    for (int t = 1; t < S; ++t) tau = (t == s0 - 1) ? mrg[t] : tau;
+    for (int t = 0; t < S0; ++t) tau = fminf(tau, fmaxf(top[t], pair_other(top[S0 - 1 - t], h)));
 
     // Entries with |c| >= tau, per group of 4 consecutive atoms (the groups alternate
     // between the two lanes of a signal), four groups to a word.  Exactly s0 of them: no tie at tau to
@@ -103,7 +97,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
         par[w] = pair_other(own[w], h);
         total = __builtin_amdgcn_sad_u8(own[w], 0u, __builtin_amdgcn_sad_u8(par[w], 0u, total));
     }
-    const bool simple = !active || (int)total == s0;
+    const bool simple = !active || (int)total == S0;
 
     if (__all(simple)) {
         // Every entry with |c| >= tau is kept.  Emit in ascending atom order.
@@ -124,8 +118,8 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                     const int f = 16 * w + 4 * g + e;
                     const int atom = (f >> 4) * 32 + ((f & 15) >> 2) * 8 + (f & 3) + h4;
                     const bool keep = mag[f] >= keep_from;
-                    // (what is not kept goes to entry S: a branch costs more)
-                    int* at = stage + stage_idx(n, 0, keep ? (int)pos : S);
+                    // (what is not kept goes to entry s0: a branch costs more)
+                    int* at = stage + stage_idx(n, 0, keep ? (int)pos : S0);
                     at[0] = atom;
                     at[32] = __builtin_bit_cast(int, c[f]);
                     pos += keep;
@@ -143,7 +137,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
 #pragma unroll
         for (int f = 0; f < NVL; ++f) gt += mag[f] > tau;
         gt += pair_other(gt, h);
-        const int need = s0 - gt;              // entries equal to tau still to take (>= 1)
+        const int need = S0 - gt;              // entries equal to tau still to take (>= 1)
         int pos = 0, taken_eq = 0;
         float dropped = 0.f;
 #pragma unroll
@@ -164,7 +158,7 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
                         take = true;
                         ++taken_eq;
                     }
-                    if (take && pos < s0) {
+                    if (take && pos < S0) {
                         stage[stage_idx(n, 0, pos)] = k0 + k;
                         stage[stage_idx(n, 1, pos)] = __builtin_bit_cast(int, v);
                         ++pos;
@@ -183,17 +177,20 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (active) {
-        int* dst = (h ? reinterpret_cast<int*>(coef) : supp) + i * s0;
+        int* dst = (h ? reinterpret_cast<int*>(coef) : supp) + i * S0;
         const int* row = stage + stage_idx(n, h, 0);           // an entry every 64 words
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         typedef int i32x2 __attribute__((ext_vector_type(2)));
-        if ((s0 & 3) == 0) {
-            for (int t = 0; t < s0; t += 4)
+        if constexpr ((S0 & 3) == 0) {
+#pragma unroll
+            for (int t = 0; t < S0; t += 4)
                 *reinterpret_cast<i32x4*>(dst + t) = i32x4{row[t * 64], row[t * 64 + 64], row[t * 64 + 128], row[t * 64 + 192]};
-        } else if ((s0 & 1) == 0) {
-            for (int t = 0; t < s0; t += 2) *reinterpret_cast<i32x2*>(dst + t) = i32x2{row[t * 64], row[t * 64 + 64]};
+        } else if constexpr ((S0 & 1) == 0) {
+#pragma unroll
+            for (int t = 0; t < S0; t += 2) *reinterpret_cast<i32x2*>(dst + t) = i32x2{row[t * 64], row[t * 64 + 64]};
         } else {
-            for (int t = 0; t < s0; ++t) dst[t] = row[t * 64];
+#pragma unroll
+            for (int t = 0; t < S0; ++t) dst[t] = row[t * 64];
         }
     }
     __builtin_amdgcn_wave_barrier();           // stage is reused by the caller's next tile
