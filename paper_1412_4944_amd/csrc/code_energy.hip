@@ -35,9 +35,10 @@ namespace {
 // (rows past K*P are zero): the order in which a wavefront's lanes consume the A operand.
 template <int P>
 __global__ __launch_bounds__(256) void dict_swizzle_kernel(const float* __restrict__ D, int K,
-                                                           f32x4* __restrict__ Dsw) {
+                                                           f32x4* __restrict__ Dsw, CallStart start) {
     constexpr int QN = P / 8;
     constexpr int STAGE_F4 = 2 * QN * 64;
+    start.clear();
     const f32x4* D4 = reinterpret_cast<const f32x4*>(D);
     const int rows = K * P;
     const int s = blockIdx.x;
@@ -64,8 +65,8 @@ constexpr int dict_rows() {
 template <int P>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
-                                                         float2* __restrict__ dnorm, int* __restrict__ weak) {
-    if (weak != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *weak = 0;       // the first count of the iterations that follow (code_screen.h)
+                                                         float2* __restrict__ dnorm, CallStart start) {
+    start.clear();
     constexpr int KS16 = P / 16, R = dict_rows<P>();
     __shared__ float qs[R][P / 8 + 1], rs[R][P / 8 + 1];
     const f32x4* D4 = reinterpret_cast<const f32x4*>(D);
@@ -856,28 +857,28 @@ hipError_t launch_wide_s(const float* Y, int64_t m, int K, int s0, int arith, co
 
 }  // namespace
 
-hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStream_t st) {
+hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const CallStart& start, hipStream_t st) {
     f32x4* out = reinterpret_cast<f32x4*>(dsw);
     const dim3 grid((K * p + 63) / 64);
     switch (p) {
-        case 16: hipLaunchKernelGGL((dict_swizzle_kernel<16>), grid, dim3(256), 0, st, D, K, out); break;
-        case 32: hipLaunchKernelGGL((dict_swizzle_kernel<32>), grid, dim3(256), 0, st, D, K, out); break;
-        case 64: hipLaunchKernelGGL((dict_swizzle_kernel<64>), grid, dim3(256), 0, st, D, K, out); break;
-        case 256: hipLaunchKernelGGL((dict_swizzle_kernel<256>), grid, dim3(256), 0, st, D, K, out); break;
+        case 16: hipLaunchKernelGGL((dict_swizzle_kernel<16>), grid, dim3(256), 0, st, D, K, out, start); break;
+        case 32: hipLaunchKernelGGL((dict_swizzle_kernel<32>), grid, dim3(256), 0, st, D, K, out, start); break;
+        case 64: hipLaunchKernelGGL((dict_swizzle_kernel<64>), grid, dim3(256), 0, st, D, K, out, start); break;
+        case 256: hipLaunchKernelGGL((dict_swizzle_kernel<256>), grid, dim3(256), 0, st, D, K, out, start); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, int* weak,
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, const CallStart& start,
                              hipStream_t st) {
     u32x4 *b = reinterpret_cast<u32x4*>(dsb), *h = reinterpret_cast<u32x4*>(dsh);
     const unsigned stages = (unsigned)(K * p + 63) / 64;           // (the last one is filled up with zeros)
     switch (p) {
-        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
-        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
-        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
-        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm, weak); break;
+        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
+        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
+        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
+        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

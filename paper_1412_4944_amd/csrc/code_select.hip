@@ -19,16 +19,20 @@ namespace sbo {
 
 namespace {
 
-// GROUP: a small set (group_in_select) without a grouping launch: every workgroup reads all choices and every wavefront finds
+// How a select kernel finds the signals of its tiles: from the grouping; from all choices of a small set (group_in_select),
+// GroupInKernel; from the choice's histograms (lists_in_select), ChunkLists.
+enum Source { kGrouped, kSmall, kLists };
+
+// kSmall: a small set (group_in_select) without a grouping launch: every workgroup reads all choices and every wavefront finds
 // the signals of its tile among them (225 signals, K = 32, p = 64: 11.8 us with a sort of them all in LDS).
-template <int P, int S0, bool GROUP>
+template <int P, int S0, Source SRC>
 __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y,
                                                      const float* __restrict__ D, int K,
                                                      const int32_t* __restrict__ offsets,
                                                      const int32_t* __restrict__ perm,
                                                      int32_t* __restrict__ supp,
                                                      float* __restrict__ coef,
-                                                     float* __restrict__ err, GroupInKernel g) {
+                                                     float* __restrict__ err, GroupInKernel g, ChunkLists lists) {
     constexpr int KS = P / 2;
     constexpr int QN = P / 8;
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-row tiles per block
@@ -40,16 +44,26 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
     const int lane = tid & 63, wave = tid >> 6;
     const int h = lane >> 5, n = lane & 31;
 
-    // GROUP, behind the tiles: count[K] | ids[4][32] | choice[m]
-    int* count = reinterpret_cast<int*>(ties_all + 4 * kSelectTieWords);
-    int *ids = count + K + wave * 32, *choice = count + K + 4 * 32;
-    if constexpr (GROUP) g.choose<256>(K, choice, count);
-    const Piece pc = find_piece([&](int j) { return GROUP ? count[j] : offsets[j + 1] - offsets[j]; }, K, 32, (int)blockIdx.x * 4 + wave);
+    // behind the tiles: ids[4][32]; kSmall: count[K] | choice[m]; kLists: the table in the place of the tiles (and longer, maybe)
+    constexpr int kTiles = 4 * (kSelectStageWords<S0> + kSelectTieWords);
+    int* ids = lds + (SRC == kLists ? max(kTiles, ChunkLists::table_ints(4, K, lists.n_chunks)) : kTiles) + wave * 32;
+    int *count = ids + (4 - wave) * 32, *choice = count + K;
+    if constexpr (SRC == kSmall) g.choose<256>(K, choice, count);
+    if constexpr (SRC == kLists) lists.load<4>(K, lds);
+    const Piece pc = find_piece([&](int j) {
+        if constexpr (SRC == kSmall) return count[j];
+        else if constexpr (SRC == kLists) return lists.count_of<4>(K, lds, j);
+        else return offsets[j + 1] - offsets[j];
+    }, K, 32, (int)blockIdx.x * 4 + wave);
+    if constexpr (SRC == kLists) {
+        if (pc.j >= 0) lists.collect(K, lds, pc, ids, 0, 1);
+        __syncthreads();                       // the table is dead
+    }
     if (pc.j < 0) return;                      // no workgroup barrier below this line
-    if constexpr (GROUP) g.list(choice, pc, ids);
+    if constexpr (SRC == kSmall) g.list(choice, pc, ids);
     const int j = pc.j;
     const bool active = n < pc.count;
-    const int64_t i = active ? (GROUP ? ids[n] : perm[pc.before + pc.rank + n]) : -1;
+    const int64_t i = active ? (SRC != kGrouped ? ids[n] : perm[pc.before + pc.rank + n]) : -1;
 
     // B operand: this lane's half of the dims of signal i.
     float yb[KS];
@@ -97,28 +111,38 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
 // 64 lines an instruction, 16 instructions a tile, and few of them in flight; here a tile reads LDS and has 1500 cycles
 // of matrix work, and what is left is the selection's instructions (select_tile.h).  Coefficients against 64 bits, of
 // |y|: rms 2.3e-8 to 5.5e-8 (select_kernel 3.1e-8 to 8.5e-8), at most 3.1e-7 (4.6e-7).
-template <int P, int S0, int NW>
+template <int P, int S0, int NW, bool LISTS>
 __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* __restrict__ Y, const float* __restrict__ D,
                                                                   int K, int piece,
                                                                   const int32_t* __restrict__ offsets,
                                                                   const int32_t* __restrict__ perm,
                                                                   int32_t* __restrict__ supp, float* __restrict__ coef,
-                                                                  float* __restrict__ err) {
+                                                                  float* __restrict__ err, ChunkLists lists) {
     constexpr int KS16 = P / 16, MT = P / 32, Q_U = MT * KS16 * 3 * 64;
 
-    extern __shared__ __attribute__((aligned(16))) int lds[];      // Qs[Q_U] | stage[NW][..] | ties[NW][..]
+    extern __shared__ __attribute__((aligned(16))) int lds_all[];  // ids[piece] (LISTS) | Qs[Q_U] | stage[NW][..] | ties[NW][..]
+    int *ids = lds_all, *lds = lds_all + (LISTS ? piece : 0);  // (a multiple of 32); LISTS: the table in the place of the latter
     u32x4* Qs = reinterpret_cast<u32x4*>(lds);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
 
-    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, (int)blockIdx.x);
+    if constexpr (LISTS) lists.load<NW>(K, lds);
+    const Piece pc = find_piece([&](int j) { return LISTS ? lists.count_of<NW>(K, lds, j) : offsets[j + 1] - offsets[j]; }, K, piece,
+                                (int)blockIdx.x);
     if (pc.j < 0) return;                      // uniform over the workgroup
+    if constexpr (LISTS) {
+        lists.collect(K, lds, pc, ids, wave, NW);
+        __syncthreads();                       // the table is dead
+    }
     const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count, n_tiles = (cnt + 31) >> 5;
 
     // Ids two tiles ahead, rows one tile ahead (lanes past the end take the last signal of the piece once more and keep
     // nothing of it).
-    auto tile_id = [&](int t) -> int { return perm[pos0 + min(t * 32 + n, cnt - 1)]; };
+    auto tile_id = [&](int t) -> int {
+        const int at = min(t * 32 + n, cnt - 1);
+        return LISTS ? ids[at] : perm[pos0 + at];
+    };
     f32x4 raw[KS16][2];                        // this lane's dims ks*16 + h*8 .. +7 of its signal
     auto load_rows = [&](int sid) {
         const f32x4* src = reinterpret_cast<const f32x4*>(Y + (int64_t)sid * P + h * 8);
@@ -364,18 +388,19 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
 // few blocks, whose rows then stay in that XCD's L2 (131072 signals, K = 16: 190 -> 172 us).
 constexpr int kTileWaves = 8;
 constexpr int kTileLd = 260;                  // floats per signal of the coefficients (16-byte units cover all banks)
-template <int S>
+template <int S, bool LISTS>
 __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(const float* __restrict__ Y, const u32x4* __restrict__ Dsb,
                                                                  int K, int s0, const int32_t* __restrict__ offsets,
                                                                  const int32_t* __restrict__ perm,
                                                                  int32_t* __restrict__ supp, float* __restrict__ coef,
-                                                                 float* __restrict__ err, int by_pos) {
+                                                                 float* __restrict__ err, int by_pos, ChunkLists lists) {
     constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 3, NW = kTileWaves, L = 16;
     constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
-    extern __shared__ __attribute__((aligned(16))) int lds[];  // parts of y, then coefficients | stage
+    extern __shared__ __attribute__((aligned(16))) int lds[];  // parts of y, then coefficients | stage | ids[32] (LISTS)
     u32x4* ys = reinterpret_cast<u32x4*>(lds);                 // [KS16][3][64]
     float* cs = reinterpret_cast<float*>(ys);                  // [32][kTileLd]
     int* stage = reinterpret_cast<int*>(ys + STAGE_U);         // [32][2][16]
+    int* ids = stage + 32 * 32;
     static_assert(32 * kTileLd * 4 <= STAGE_U * 16, "the coefficients fit");
 
     const int tid = threadIdx.x;
@@ -383,8 +408,14 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
     const int h = lane >> 5, n = lane & 31;
     const int per_xcd = gridDim.x >> 3;        // the grid is a multiple of 8 (launcher)
     const int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, 32, id);
+    int* table = reinterpret_cast<int*>(ys);   // LISTS: in the place of the signals
+    if constexpr (LISTS) lists.load<NW>(K, table);
+    const Piece pc = find_piece([&](int j) { return LISTS ? lists.count_of<NW>(K, table, j) : offsets[j + 1] - offsets[j]; }, K, 32, id);
     if (pc.j < 0) return;                      // uniform over the workgroup
+    if constexpr (LISTS) {
+        lists.collect(K, table, pc, ids, wave, NW);
+        __syncthreads();                       // the table is dead
+    }
     const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count;
 
     // A operand: rows of this wavefront's 32 atoms, AHEAD contraction steps on their way
@@ -395,7 +426,7 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
         for (int pl = 0; pl < 3; ++pl) v[pl] = Qj[(ks * 3 + pl) * 64];
     };
     {
-        const int64_t i = n < cnt ? perm[pos0 + n] : -1;
+        const int64_t i = n < cnt ? (LISTS ? ids[n] : perm[pos0 + n]) : -1;
         f32x4 v[KS16 / NW][2];
 #pragma unroll
         for (int q = 0; q < KS16 / NW; ++q)     // steps NW q + wave: dims ks*16 + h*8 .. +7 of signal n
@@ -507,7 +538,7 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (!active) return;
-    const int64_t i = by_pos ? pos0 + sig : perm[pos0 + sig];
+    const int64_t i = LISTS ? ids[sig] : by_pos ? pos0 + sig : perm[pos0 + sig];
     if (part == 0) err[i] = dropped;
     for (int e = part; e < s0; e += L) {
         supp[i * s0 + e] = mine[e];
@@ -518,18 +549,23 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
 template <int P, int S>
 hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int s0,
                           const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
-                          bool by_pos, hipStream_t st) {
+                          bool by_pos, const ChunkLists* lists, hipStream_t st) {
     (void)D;                                   // the kernels read ws.dsb / ws.dsw, the same Q in operand order
     if (split) {
         // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every tile
         const int64_t tiles = (((m + 31) / 32 + K) + 7) & ~(int64_t)7;
-        const size_t lds = (size_t)(P / 16) * 3 * 64 * 16 + 32 * 32 * sizeof(int);
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_wide_split_kernel<S>), 64 * 1024); e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((select_wide_split_kernel<S>), dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
-                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos);
+        constexpr size_t rows = (size_t)(P / 16) * 3 * 64 * 16;
+        const size_t lds = rows + 32 * 33 * sizeof(int);
+        const auto kernel = lists != nullptr ? &select_wide_split_kernel<S, true> : &select_wide_split_kernel<S, false>;
+        if (lists != nullptr && (by_pos || ChunkLists::table_ints(kTileWaves, K, lists->n_chunks) * sizeof(int) > rows))
+            return hipErrorInvalidValue;
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), 64 * 1024); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
+                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos,
+                           lists != nullptr ? *lists : ChunkLists{});
         return hipGetLastError();
     }
+    if (lists != nullptr) return hipErrorInvalidValue;
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
     const size_t lds = 4 * 32 * (P + 1) * sizeof(float);
@@ -544,12 +580,12 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
 template <int P>
 hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int K,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
-                         bool by_pos, hipStream_t st) {
-    if (s0 <= 1) return launch_wide_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
-    if (s0 <= 2) return launch_wide_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
-    if (s0 <= 4) return launch_wide_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
-    if (s0 <= 8) return launch_wide_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
-    return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, st);
+                         bool by_pos, const ChunkLists* lists, hipStream_t st) {
+    if (s0 <= 1) return launch_wide_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
+    if (s0 <= 2) return launch_wide_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
+    if (s0 <= 4) return launch_wide_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
+    if (s0 <= 8) return launch_wide_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
+    return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
 }
 
 // From here on select_split_kernel (p = 32, 64), four wavefronts and up to 4 tiles for each: the fewest with which all
@@ -562,43 +598,48 @@ hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int 
 constexpr int64_t kSplitMinSignals = 32768;
 
 template <int P, int S0>
-hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
-                     int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
+hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Workspace& ws, int32_t* supp, float* coef,
+                     float* err, int32_t* blk, bool choose, bool split, const ChunkLists* lists, hipStream_t st) {
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
-    size_t lds = 4 * (kSelectStageWords<S0> + kSelectTieWords) * sizeof(int);
-    if (blk != nullptr) {
-        if (K > GroupInKernel::kMostBlocks) return hipErrorInvalidValue;
-        lds += (K + 4 * 32 + m) * sizeof(int);             // less than 60 KiB in all
-        hipLaunchKernelGGL((select_kernel<P, S0, true>), grid, dim3(256), lds, st, Y, D, K, nullptr, nullptr, supp,
-                           coef, err,
-                           GroupInKernel{blk, (int)m, ws.chunk_count, choose ? ws.part_E : nullptr});
-        return hipGetLastError();
-    }
+    const int tiles_ints = 4 * (kSelectStageWords<S0> + kSelectTieWords);
+    const int table_ints = lists != nullptr ? ChunkLists::table_ints(4, K, lists->n_chunks) : 0;
+    if (table_ints * sizeof(int) > 64 * 1024) return hipErrorInvalidValue;
     if constexpr (P >= 32) if (split && m >= kSplitMinSignals) {
         constexpr int NW = 4, Q_U = P / 32 * (P / 16) * 3 * 64;
         const int64_t resident = 256 * (P == 64 ? 3 : 4) - K / 2;          // less the blocks' unfinished pieces
         const int tiles = (int)std::min<int64_t>(4, (m + 32 * NW * resident - 1) / (32 * NW * resident));
         const int piece = 32 * NW * tiles;
-        lds = (4 * Q_U + NW * (kSelectStageWords<S0> + kSelectTieWords)) * sizeof(int);
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_split_kernel<P, S0, NW>), 160 * 1024);
-            e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((select_split_kernel<P, S0, NW>), dim3((unsigned)((m + piece - 1) / piece + K)), dim3(64 * NW), lds,
-                           st, Y, D, K, piece, ws.offsets, ws.perm, supp, coef, err);
+        const size_t lds = (std::max(4 * Q_U + tiles_ints, table_ints) + (lists != nullptr ? piece : 0)) * sizeof(int);
+        const auto kernel = lists != nullptr ? &select_split_kernel<P, S0, NW, true> : &select_split_kernel<P, S0, NW, false>;
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), 160 * 1024); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((m + piece - 1) / piece + K)), dim3(64 * NW), lds, st, Y, D, K, piece, ws.offsets,
+                           ws.perm, supp, coef, err, lists != nullptr ? *lists : ChunkLists{});
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((select_kernel<P, S0, false>), grid, dim3(256), lds, st, Y, D, K, ws.offsets,
-                       ws.perm, supp, coef, err, GroupInKernel{});
+    const size_t lds = (std::max(tiles_ints, table_ints) + 4 * 32) * sizeof(int);
+    if (lists != nullptr) {
+        const void* fn = reinterpret_cast<const void*>(&select_kernel<P, S0, kLists>);
+        if (hipError_t e = ws.raised->ensure(fn, 66 * 1024); e != hipSuccess) return e;
+        hipLaunchKernelGGL((select_kernel<P, S0, kLists>), grid, dim3(256), lds, st, Y, D, K, nullptr, nullptr, supp, coef, err,
+                           GroupInKernel{}, *lists);
+    } else if (blk != nullptr) {
+        if (K > GroupInKernel::kMostBlocks) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((select_kernel<P, S0, kSmall>), grid, dim3(256), lds + (K + m) * sizeof(int), st, Y, D, K, nullptr, nullptr,
+                           supp, coef, err, GroupInKernel{blk, (int)m, ws.chunk_count, choose ? ws.part_E : nullptr}, ChunkLists{});
+    } else {
+        hipLaunchKernelGGL((select_kernel<P, S0, kGrouped>), grid, dim3(256), lds, st, Y, D, K, ws.offsets, ws.perm, supp, coef, err,
+                           GroupInKernel{}, ChunkLists{});
+    }
     return hipGetLastError();
 }
 
 template <int P>
-hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
-                    int32_t* supp, float* coef, float* err, int32_t* blk, bool choose, bool split, hipStream_t st) {
+hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws, int32_t* supp, float* coef,
+                    float* err, int32_t* blk, bool choose, bool split, const ChunkLists* lists, hipStream_t st) {
     switch (s0) {
 #define SBO_CASE(N) \
-    case N: return launch_ps<P, N>(Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
+    case N: return launch_ps<P, N>(Y, m, D, K, ws, supp, coef, err, blk, choose, split, lists, st);
         SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
         SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
 #undef SBO_CASE
@@ -610,18 +651,22 @@ hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, co
 
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, int32_t* blk, bool choose, bool by_pos) {
-    if ((blk != nullptr ? !group_in_select(p, K, m) : choose) || (by_pos && p != 256)) return hipErrorInvalidValue;
+                         bool split, hipStream_t st, int32_t* blk, bool choose, bool by_pos, bool lists) {
+    const bool fits = lists ? blk != nullptr && !choose && lists_in_select(p, K, m) : blk != nullptr ? group_in_select(p, K, m) : !choose;
+    if (!fits || (by_pos && p != 256)) return hipErrorInvalidValue;
+    const GroupGeom g = group_geom(m);
+    if (lists && g.chunk != kListChunk) return hipErrorInvalidValue;
+    const ChunkLists from = {blk, (int)m, g.n_chunks, ws.chunk_count, nullptr, nullptr}, *l = lists ? &from : nullptr;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
-        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, nullptr, st)
-                             : launch_dict_swizzle(p, K, D, ws.dsw, st);
+        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, CallStart{}, st)
+                             : launch_dict_swizzle(p, K, D, ws.dsw, CallStart{}, st);
         if (e != hipSuccess) return e;
     }
     switch (p) {
-        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
-        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
-        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, st);
-        case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, by_pos, st);
+        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, l, st);
+        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, l, st);
+        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, l, st);
+        case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, by_pos, l, st);
         default: return hipErrorInvalidValue;
     }
 }

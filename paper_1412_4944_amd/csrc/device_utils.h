@@ -288,79 +288,89 @@ __device__ __forceinline__ Piece find_piece(F count_of, int K, int piece, int id
 }
 
 // A grouping that has not been carried out: the choices and their histograms per chunk of kListChunk signals (group.hip),
-// from which a workgroup of NW wavefronts lists the signals of its own piece.  Few signals (list_in_kernel): a workgroup
-// reads all histograms, and the choices of the chunks that its piece comes from.  The launch after sets the histograms to zero
+// from which a workgroup of NW wavefronts lists the signals of its own piece, or a wavefront those of its own tile.  A workgroup
+// reads all histograms, and the choices of the chunks that its piece comes from.  Another launch sets the histograms to zero
 // (a count of the workgroups that have read them costs more than all the rest: 144 of them, one after the other, 4 us).
-constexpr int kListChunk = 512, kListChunks = 64;          // signals of a chunk, chunks at most
+constexpr int kListChunk = 512;                // signals of a chunk
 struct ChunkLists {
     const int32_t* blk;
     int m, n_chunks;
     const int32_t* chunk_count;            // [n_chunks][K]
-    int32_t *counts, *offsets; // [K], [K+1]: written by the first workgroup
+    int32_t *counts, *offsets;             // [K], [K+1]: written by leave()
 
-    static constexpr int lds_ints(int NW, int K, int n_chunks) { return (n_chunks + NW) * K; }
-
-    // Piece `id` and, in ids[piece.count], its signals in order; table: lds_ints ints, dead after the barrier that ends this.
+    // The histograms -> table (LDS, table_ints ints); all wavefronts, ends with a barrier.
+    static constexpr int table_ints(int NW, int K, int n_chunks) { return (n_chunks + NW) * K; }
     template <int NW>
-    __device__ __forceinline__ Piece list(int K, int piece, int id, int* table, int* ids) const {
+    __device__ __forceinline__ void load(int K, int* table) const {
+        constexpr int A = 16;                  // on their way at once
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         int* part = table + n_chunks * K;      // [NW][K] sums over every NW-th chunk
         for (int j = lane; j < K; j += 64) {
-            int v[kListChunks / NW], s = 0;    // on their way at once
+            int s = 0;
+            for (int c0 = wave; c0 < n_chunks; c0 += A * NW) {
+                int v[A];
 #pragma unroll
-            for (int u = 0; u < kListChunks / NW; ++u) v[u] = chunk_count[min(wave + u * NW, n_chunks - 1) * K + j];
+                for (int u = 0; u < A; ++u) v[u] = chunk_count[min(c0 + u * NW, n_chunks - 1) * K + j];
 #pragma unroll
-            for (int u = 0; u < kListChunks / NW; ++u)
-                if (wave + u * NW < n_chunks) {            // uniform
-                    table[(wave + u * NW) * K + j] = v[u];
-                    s += v[u];
-                }
+                for (int u = 0; u < A; ++u)
+                    if (c0 + u * NW < n_chunks) {          // uniform
+                        table[(c0 + u * NW) * K + j] = v[u];
+                        s += v[u];
+                    }
+            }
             part[wave * K + j] = s;
         }
         __syncthreads();
-        auto count_of = [&](int j) {
-            int s = 0;
+    }
+    template <int NW>
+    __device__ __forceinline__ int count_of(int K, const int* table, int j) const {
+        int s = 0;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) s += part[w * K + j];
-            return s;
-        };
-        if (id == 0 && wave == 0) {            // (uniform)
-            int before = 0;
-            for (int j0 = 0; j0 < K; j0 += 64) {
-                const int j = j0 + lane, n = j < K ? count_of(j) : 0, upto = before + wave_scan(n);
-                if (j < K) {
-                    counts[j] = n;
-                    offsets[j + 1] = upto;
-                }
-                before = __builtin_amdgcn_readlane(upto, 63);
+        for (int w = 0; w < NW; ++w) s += table[(n_chunks + w) * K + j];
+        return s;
+    }
+    // What the grouping would have left, but for the lists; one wavefront.
+    template <int NW>
+    __device__ __forceinline__ void leave(int K, const int* table) const {
+        const int lane = threadIdx.x & 63;
+        int before = 0;
+        for (int j0 = 0; j0 < K; j0 += 64) {
+            const int j = j0 + lane, n = j < K ? count_of<NW>(K, table, j) : 0, upto = before + wave_scan(n);
+            if (j < K) {
+                counts[j] = n;
+                offsets[j + 1] = upto;
             }
-            if (lane == 0) offsets[0] = 0;
+            before = __builtin_amdgcn_readlane(upto, 63);
         }
-        const Piece pc = find_piece(count_of, K, piece, id);
-        if (pc.j >= 0) {                       // uniform over the workgroup
-            // the chunks that have some of it, a wavefront every NW-th one
-            const int n = lane < n_chunks ? table[lane * K + pc.j] : 0, front = wave_scan(n) - n;
-            unsigned long long mask = __ballot(n > 0 && front < pc.rank + pc.count && front + n > pc.rank);
-            for (int k = 0; mask != 0ull; ++k, mask &= mask - 1) {         // uniform over the wavefront
-                if (k % NW != wave) continue;
-                const int c = __builtin_ctzll(mask);
-                int key[kListChunk / 64];      // on their way at once (a condition would make eight trips of it)
+        if (lane == 0) offsets[0] = 0;
+    }
+    // The signals of a piece, in order -> ids[pc.count] (LDS): those of every `step`-th chunk that has some, from `first` on.
+    // One wavefront; `step` of them share out a piece.
+    __device__ __forceinline__ void collect(int K, const int* table, const Piece& pc, int* ids, int first, int step) const {
+        constexpr int A = kListChunk / 64;
+        const int lane = threadIdx.x & 63;
+        int front = 0, k = 0;                  // signals of the chunks before; chunks so far
+        for (int c0 = 0; c0 < n_chunks && front < pc.rank + pc.count; c0 += 64) {          // uniform
+            const int n = c0 + lane < n_chunks ? table[(c0 + lane) * K + pc.j] : 0, upto = front + wave_scan(n);
+            unsigned long long mask = __ballot(n > 0 && upto - n < pc.rank + pc.count && upto > pc.rank);
+            for (; mask != 0ull; ++k, mask &= mask - 1) {  // uniform
+                if (k % step != first) continue;
+                const int l = __builtin_ctzll(mask), i0 = (c0 + l) * kListChunk + lane;
+                int key[A];                    // on their way at once (a condition would make as many trips of it)
 #pragma unroll
-                for (int u = 0; u < kListChunk / 64; ++u) key[u] = blk[min(c * kListChunk + u * 64 + lane, m - 1)];
-                int at = __builtin_amdgcn_readlane(front, c) - pc.rank;    // of the next one, in the piece
+                for (int u = 0; u < A; ++u) key[u] = blk[min(i0 + u * 64, m - 1)];
+                int at = __builtin_amdgcn_readlane(upto - n, l) - pc.rank; // of the next one, in the piece
 #pragma unroll
-                for (int u = 0; u < kListChunk / 64; ++u) {
-                    const int i = c * kListChunk + u * 64 + lane;
-                    const bool here = key[u] == pc.j && i < m;
+                for (int u = 0; u < A; ++u) {
+                    const bool here = key[u] == pc.j && i0 + u * 64 < m;
                     const unsigned long long mine = __ballot(here);
                     const int to = at + __popcll(mine & ((1ull << lane) - 1ull));
-                    if (here && to >= 0 && to < pc.count) ids[to] = i;
+                    if (here && to >= 0 && to < pc.count) ids[to] = i0 + u * 64;
                     at += __popcll(mine);
                 }
             }
+            front = __builtin_amdgcn_readlane(upto, 63);
         }
-        __syncthreads();
-        return pc;
     }
 };
 

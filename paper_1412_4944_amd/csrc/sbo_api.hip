@@ -157,12 +157,13 @@ static int select_ops(const sbo_ctx* c) { return c->p <= 64 ? 0 : use_split(c) ?
 static int code_ops(const sbo_ctx* c) { return energy_ops(c) | select_ops(c); }
 
 // D in the operand order(s) the coding kernels of this context read (tiny; outside the stages).
-static int run_swizzle(sbo_ctx* c, const float* D) {
+static int run_swizzle(sbo_ctx* c, int64_t m, const float* D) {
     const int ops = code_ops(c);
-    if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, c->stream));
+    const CallStart start = {c->ws.weak, c->ws.chunk_count, group_geom(m).n_chunks * c->K};
+    if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, start, c->stream));
     if (ops & (kOpsBf16 | kOpsF16))
         SBO_HIP(launch_dict_parts(c->p, c->K, D, ops & kOpsBf16 ? c->ws.dsb : nullptr,
-                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm, c->ws.weak, c->stream));
+                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm, start, c->stream));
     return SBO_OK;
 }
 
@@ -182,18 +183,20 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
         StageTimer t(c, SBO_STAGE_ENERGY);
         SBO_HIP(launch_energy_direct(c->p, c->K, c->s0, choice_arith(c), Y, m, D, c->ws, c->stream));
     } else {
-        if (turn <= 0) rc = run_swizzle(c, D);
+        if (turn <= 0) rc = run_swizzle(c, m, D);
         if (rc) return rc;
         rc = run_energy(c, Y, m, blk, turn);
         if (rc) return rc;
     }
-    const bool in_select = group_in_select(c->p, c->K, m);
-    if (!in_select) rc = run_group(c, blk, m, true);   // the energy kernel left the chunk histograms
+    // The energy kernel left the chunk histograms: for the grouping, which the update of an iteration needs too, or for lists.
+    const bool in_select = group_in_select(c->p, c->K, m), lists = turn < 0 && !in_select && lists_in_select(c->p, c->K, m) &&
+                           (c->p <= 64 || use_split(c));
+    if (!in_select && !lists) rc = run_group(c, blk, m, true);
     if (rc) return rc;
     {
         StageTimer t(c, SBO_STAGE_SELECT);         // p = 256 reads the operand order run_swizzle wrote
         SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, true, use_split(c), c->stream,
-                              in_select ? blk : nullptr, direct));
+                              in_select || lists ? blk : nullptr, direct, false, lists));
     }
     return SBO_OK;
 }
@@ -270,10 +273,9 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     c->ws.raised = &c->raised;
     c->ws.device = device;
     c->ws.parts_accum = c->coding_arith != SBO_ARITH_F32;
-    // Some pieces of the workspace carry an invariant between calls: the chunk histograms, the two
-    // finished-workgroup counters and the counters of polar_wide.hip are zero whenever no call is in flight.
-    e = hipMemsetAsync(c->ws.chunk_count, 0, (size_t)max_chunks() * K * 4, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->ws.sq_counter, 0, 4, c->stream);
+    // Some pieces of the workspace carry an invariant between calls: the two finished-workgroup counters and the counters of
+    // polar_wide.hip are zero whenever no call is in flight.
+    e = hipMemsetAsync(c->ws.sq_counter, 0, 4, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->ws.group_done, 0, 4, c->stream);
     if (e == hipSuccess && p > 64) e = hipMemsetAsync(c->ws.wide_sync, 0, polar_wide_sync_bytes(K), c->stream);
     if (e != hipSuccess) {
@@ -400,7 +402,7 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
         // The dictionary in the coding kernel's operand order: rewritten from D at the start
         // of the call, kept up to date by the SVD kernel afterwards.
         if (it == 0) {
-            rc = run_swizzle(c, D);
+            rc = run_swizzle(c, m, D);
             if (rc) return rc;
         }
         rc = run_energy(c, Y, m, blk, it);

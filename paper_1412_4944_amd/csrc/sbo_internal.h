@@ -200,21 +200,41 @@ constexpr bool screen_shared(int64_t m, bool p64_by_256) {
 // 512 not everywhere.
 constexpr int kDirectMaxK = 64;
 constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than group_in_select allows)
-// Which iterations leave the grouping to the select + accumulate kernel, whose workgroups list the signals of their own piece
-// (ChunkLists in device_utils.h).
+// Which iterations leave the grouping to the select + accumulate kernel, and which calls of sbo_code to the select kernel, whose
+// workgroups list the signals of their own piece (ChunkLists in device_utils.h).  The histograms are read by every workgroup,
+// and a piece of a block comes from K times as many signals.  sbo_iterate, an iteration: 16384 signals, K = 16, p = 64 47.5 us
+// with a grouping launch, 41 (with the shorter search for a piece); the same table as below was not taken beyond 4096 entries.
+// sbo_code, with a grouping launch / lists (us): p = 64, K = 16 2100 signals 26.0 / 21.3, 65537 50.3 / 44.7, 131000 62.4 / 59.0;
+// K = 64 65537 104.2 / 99.0, 100003 (p = 32) 68.9 / 74.5; K = 128 12000 47.4 / 46.4, 32000 81.8 / 78.0, 40000 (p = 32) 49.4 / 49.8;
+// K = 200 12000 59.9 / 63.6; p = 256, K = 16 5000 61.3 / 55.4, 65537 271.5 / 268.8, 100003 336.8 / 341.2.  Sets of 1025 to 2048
+// signals are grouped by a launch, as the stage times that callers read of them say (sbo_stage_ms).
 inline bool lists_in_round(int p, int K, int64_t m) {
     return p <= 64 && m <= 32768 && (int64_t)((m + 511) / 512 + 8) * K <= 4096;
+}
+inline bool lists_in_select(int p, int K, int64_t m) {
+    return m > 2048 && m <= (p <= 64 ? 131072 : 65536) && K <= 128 && (int64_t)((m + 511) / 512 + 8) * K <= 9216;
 }
 inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
     return group_in_select(p, K, m) && K <= kDirectMaxK && K * m <= kDirectMaxEnergies && screen_applies(p, K, s0, arith);
 }
 
+// What the first launch of a call that codes signals also does: the counts and histograms that the next ones add to are set
+// to zero.
+struct CallStart {
+    int* weak = nullptr;           // ws.weak: its first count
+    int32_t* hist = nullptr;       // ws.chunk_count: the first n_hist entries
+    int n_hist = 0;
+    __device__ __forceinline__ void clear() const {
+        if (weak != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *weak = 0;
+        for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n_hist; e += gridDim.x * blockDim.x) hist[e] = 0;
+    }
+};
 // dsw = D in the fp32 operand order of the coding kernels.
-hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, hipStream_t st);
+hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const CallStart& start, hipStream_t st);
 // dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
-// (device_utils.h); dnorm comes with dsh.  weak: nullptr, or ws.weak, whose first count is set to zero.
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, int* weak,
+// (device_utils.h); dnorm comes with dsh.
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, const CallStart& start,
                              hipStream_t st);
 // The block of every signal, from the operand orders in ws that (p, s0, arith) reads (energy_ops in
 // sbo_api.hip).
@@ -247,9 +267,12 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // choose: blk is written first, from the energies in ws.part_E (launch_energy_direct).
 // by_pos (p = 256): the codes of the signal at position q of ws.perm go to row q, not to the row of the signal: where a
 // signal is in several blocks (sbo_learn's initial sets).  launch_accumulate reads them likewise.
+// lists: blk likewise, where lists_in_select says so; the histograms are left as they are, and nothing of what launch_group
+// leaves.
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false);
+                         bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false,
+                         bool lists = false);
 
 // M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,

@@ -77,8 +77,16 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     int* ids = reinterpret_cast<int*>(waves_base + (size_t)NW * WAVE_B);
     const int id = blockIdx.x;
     Piece pc;
-    if constexpr (GROUP) pc = lists.list<NW>(K, piece, id, reinterpret_cast<int*>(waves_base), ids);
-    else pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    if constexpr (GROUP) {
+        int* table = reinterpret_cast<int*>(waves_base);
+        lists.load<NW>(K, table);
+        if (id == 0 && wave == 0) lists.leave<NW>(K, table);
+        pc = find_piece([&](int j) { return lists.count_of<NW>(K, table, j); }, K, piece, id);
+        if (pc.j >= 0) lists.collect(K, table, pc, ids, wave, NW);
+        __syncthreads();
+    } else {
+        pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    }
     if (pc.j < 0) return;                      // uniform over the workgroup
     const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count;
 
@@ -318,8 +326,8 @@ hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Wor
     if (blk != nullptr) {
         const GroupGeom g = group_geom(m);
         lds += (size_t)piece * sizeof(int);
-        if (g.chunk != kListChunk || g.n_chunks > kListChunks || lds > 160 * 1024 ||
-            ChunkLists::lds_ints(kSaWaves, K, g.n_chunks) * sizeof(int) > kSaWaves * wave_b)
+        if (g.chunk != kListChunk || lds > 160 * 1024 ||
+            ChunkLists::table_ints(kSaWaves, K, g.n_chunks) * sizeof(int) > kSaWaves * wave_b)
             return hipErrorInvalidValue;
         if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, true>), 160 * 1024);
             e != hipSuccess)

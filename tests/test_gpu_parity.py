@@ -305,6 +305,35 @@ def test_iterate_groups_small_sets_in_the_select_kernel(p, K, m):
             np.testing.assert_array_equal(perm, orc.o_group(a[1], K)[2])
 
 
+@pytest.mark.parametrize("p,K,m,s0", [(64, 16, 2049, 6), (64, 128, 32500, 5), (64, 129, 32500, 5), (64, 64, 69632, 8), (64, 65, 69632, 8),
+                                      (64, 3, 131072, 1), (64, 3, 131073, 1), (32, 7, 32767, 4), (32, 24, 32768, 7), (16, 5, 100003, 3),
+                                      (16, 128, 2100, 16), (256, 16, 5041, 12), (256, 2, 65536, 16), (256, 2, 65537, 16),
+                                      (256, 97, 4100, 3)])
+@pytest.mark.parametrize("arith", ["f16x2", "f32"])
+def test_code_lists_the_signals_of_a_tile_from_the_histograms(p, K, m, s0, arith):
+    """sbo_code on both sides of its rule (2049 to 131072 signals, p = 256 65536, K <= 128, 9216 histogram entries), in turn
+    with calls that group; filled up with zero signals, which all go to block 0, to a set that is grouped, the codes are the same."""
+    if arith == "f32" and m > 40000:
+        pytest.skip("one arithmetic is enough at these sizes")
+    pr = synth.generate(synth.custom(f"clists_p{p}_K{K}", p=p, K=K, m=m, s0=s0, snr_db=20.0, zipf_s=1.2 if K > 20 else None))
+    more = 140000 if p <= 64 else 70000
+    full = np.concatenate([pr.Y, np.zeros((more - m, p), np.float32)])
+    with Sbo(p, K, s0, more, arith=arith) as g:
+        for _ in range(2):
+            blk, supp, coef, err = g.code(pr.Y, pr.D_planted)
+            blk2, supp2, coef2, err2 = (a[:m] for a in g.code(full, pr.D_planted))
+            np.testing.assert_array_equal(blk, blk2)
+            # (other sizes take other select kernels: the last bits of a coefficient may differ, and with them a tie)
+            same = (supp == supp2).all(1)
+            assert same.mean() > 0.999
+            tol = 2e-6 * np.linalg.norm(pr.Y, axis=1)
+            assert (np.abs(coef - coef2).max(1) <= tol)[same].all()
+            assert (np.abs(err - err2) <= tol * np.linalg.norm(pr.Y, axis=1)).all()
+        counts, _off, perm = g.group(blk)
+        np.testing.assert_array_equal(perm, orc.o_group(blk, K)[2])
+        np.testing.assert_array_equal(g.iterate(pr.Y, pr.D_planted, 1)[1], blk)    # (its histograms start from zero)
+
+
 @pytest.mark.parametrize("p,K,m,s0", [(64, 16, 16384, 6), (64, 56, 32768, 8), (64, 57, 32768, 8), (64, 3, 32769, 5), (64, 2, 32767, 4),
                                       (32, 24, 511, 4), (32, 7, 513, 3), (32, 70, 20001, 4), (16, 4, 1024, 3), (16, 256, 4096, 2),
                                       (16, 257, 4000, 2), (16, 400, 1000, 2), (64, 1, 1, 8), (16, 5, 33, 3)])
