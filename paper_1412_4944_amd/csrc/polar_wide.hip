@@ -10,8 +10,9 @@
 //   workgroup owns a strip of 16 columns of X, in registers.  Per step it multiplies G = X^T X (its 16
 //   columns), then X E (its 16 columns), six bf16 products each; the A operands are ALL of X, by
 //   columns for the first product and by rows for the second, read straight from L2 in operand order,
-//   each exactly once: every workgroup leaves its strip in both orders when it has updated it, and that
-//   is the only exchange, hence one barrier per step (two in the first and the last).  A wavefront
+//   each exactly once: every workgroup leaves its strip in both orders when it has updated it, in fp32 (whoever reads it
+//   makes the parts: two thirds of their bytes), and that is the only exchange, hence one barrier per step (two in the
+//   first and the last).  A wavefront
 //   makes two 16 x 16 tiles of both products; its loads run four contraction steps ahead and through from
 //   the first product into the second.
 //
@@ -22,8 +23,10 @@
 //   pairs of sets in 15 rounds, seven of them keeping one of the two sets in place.  A set is
 //   handed over through memory with a version number; there is no barrier but one per sweep.
 //
-// What bounds it: Newton-Schulz by the 768 KiB of operands per workgroup and step from L2 (40 to 46 bytes a
-// cycle arrive; a step is 25000 cycles, 6600 of them matrix work, 3000 the barrier); Jacobi by the vector ALU
+// What bounds it: Newton-Schulz by the 512 KiB of operands per workgroup and step from L2 (30 bytes a cycle arrive at a CU, no
+// more with one team on an XCD than with two, or with more loads on their way): of 27000 cycles a step 14000 are the first product
+// and the wait for its slowest wavefront, 6300 the second (the splits), 5000 the barrier.  With the three parts in memory (768 KiB)
+// 138 -> 131 us in the same profile, K = 16; K = 4 no difference.  Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  Jacobi is called, not inlined,
 // where a block may need it after Newton-Schulz, whose operands take all registers (inlined: 100 of them spilled, K = 16 147 us
 // instead of 130); the norm and the smallest diagonal entry of a step share a barrier (130 -> 126).
@@ -62,13 +65,14 @@ constexpr int kWaves = kNT / 64;
 constexpr int kMaxSweeps = 24;
 constexpr float kTol = 1e-6f;                  // rotate while |a_i . a_j| > kTol |a_i| |a_j|
 
-constexpr int kImage = 8 * 3 * 1024;           // a strip's operand image: [contraction step][part][64 lanes][16 bytes]
+constexpr int kImage = 8 * 3 * 1024;           // a strip as an operand, LDS: [contraction step][part][64 lanes][16 bytes]
+constexpr int kShared = 8 * 2 * 1024;          // and in memory, in fp32: [contraction step][half][64 lanes][16 bytes]
 constexpr int kLdStrip = P + 4;
 
 // A team's memory
-constexpr size_t kColAt = 0;                                   // [2][16 strips] images by columns
-constexpr size_t kRowAt = kColAt + 2 * (size_t)kTeam * kImage; // [2][16 row tiles][8][part][half][64 lanes][8 bytes]
-constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kImage;   // [16 strips][8][64 lanes][16 bytes] fp16 parts of E
+constexpr size_t kColAt = 0;                                   // [2][16 strips] by columns
+constexpr size_t kRowAt = kColAt + 2 * (size_t)kTeam * kShared;        // [2][16 row tiles] by rows
+constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kShared;  // [16 strips][8][64 lanes][16 bytes] fp16 parts of E
 constexpr size_t kJaAt = kEAt + (size_t)kTeam * 8 * 1024;      // [256 columns][256] A
 constexpr float kEScale = 8192.f;                              // of those: 1e-2 is in the middle of fp16's range
 constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
@@ -373,35 +377,32 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         for (int k = 0; k < 2; ++k)
             xr[k] = *reinterpret_cast<const f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4);
     }
-    // Leaves the strip for the others (buffer buf) and in ximg.  Contraction step s of 32 = tiles 2s and
-    // 2s + 1: a lane holds rows grp * 4 .. of both, which is what an accumulator leaves it; the rows
-    // by ds_read_b64_tr_b16 (see polar_ns.hip), 4 columns of a row per lane.
+    // Leaves the strip for the others (buffer buf), in fp32, and its parts in ximg.  Contraction step s of 32 = tiles 2s and
+    // 2s + 1, its two halves: a lane holds rows grp * 4 .. of both, which is what an accumulator leaves it, and of the rows'
+    // image four columns grp * 4 .. of a row, by way of LDS (the wavefront's own part of `strip`).
     auto publish = [&](int buf) {
         u32x4 part[3];
         split(xr[0], xr[1], part);
-        unsigned char* cols = mem + kColAt + ((size_t)buf * kTeam + t.q) * kImage;
+        unsigned char* cols = mem + kColAt + ((size_t)buf * kTeam + t.q) * kShared;
+        unsigned char* rows = mem + kRowAt + (size_t)buf * kTeam * kShared;
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) {
-            const int at = (wave * 3 + pl) * 1024 + lane * 16;
-            *reinterpret_cast<u32x4*>(ximg + at) = part[pl];
-            *reinterpret_cast<u32x4*>(cols + at) = part[pl];
+        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(ximg + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            *reinterpret_cast<f32x4*>(cols + (wave * 2 + k) * 1024 + lane * 16) = xr[k];
+            *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4) = xr[k];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        typedef short s16x4 __attribute__((ext_vector_type(4)));
-        typedef __attribute__((address_space(3))) s16x4* lds_ptr;
-        unsigned char* rows = mem + kRowAt + (size_t)buf * kTeam * kImage;
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (lds_ptr)(ximg + (wave * 3 + pl) * 1024 + (4 * grp + (c16 >> 2) + 16 * (c16 & 3)) * 16 + k * 8));
-                const int td = 2 * wave + k;
-                *reinterpret_cast<u32x2*>(rows + (size_t)((td * 8 + (t.q >> 1)) * 3 + pl) * 1024 + (t.q & 1) * 512 +
-                                          lane * 8) = __builtin_bit_cast(u32x2, r);
-            }
+        for (int k = 0; k < 2; ++k) {
+            const int td = 2 * wave + k;
+            const float* row = strip + td * 16 + c16;          // of columns 0, 1, ..
+            *reinterpret_cast<f32x4*>(rows + (size_t)((td * 8 + (t.q >> 1)) * 2 + (t.q & 1)) * 1024 + lane * 16) =
+                f32x4{row[(4 * grp) * kLdStrip], row[(4 * grp + 1) * kLdStrip], row[(4 * grp + 2) * kLdStrip],
+                      row[(4 * grp + 3) * kLdStrip]};
+        }
     };
     // Smallest diagonal entry of G in this workgroup's columns (two tiles lie on the diagonal, both in the wavefront of
     // tile t.q, which leaves it in red[kDiagAt]: there after the next barrier).
@@ -425,7 +426,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
                 e[k][r] = ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16 ? 1.f : 0.f) - a2 * gm[k][r];
     };
 
-    // A product: contraction steps S0 .. S0 + 7, their A operands requested kAhead steps before, the B operands
+    // A product: contraction steps S0 .. S0 + 7, their A operands requested kAhead steps before and split here, the B operands
     // from an image in LDS one step before; two sums per tile, so that four matrix instructions are independent.
     auto product = [&](auto& a, auto& request, auto& turn, const unsigned char* img, auto first_step, f32x4 (&out)[2]) {
         constexpr int S0 = decltype(first_step)::value;
@@ -439,11 +440,14 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
 #pragma unroll
         for (int s = S0; s < S0 + 8; ++s) {
             if (s + 1 < S0 + 8) read(s + 1);
+            u32x4 part[2][3];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                split(__builtin_bit_cast(f32x4, a[s % kAhead][k][0]), __builtin_bit_cast(f32x4, a[s % kAhead][k][1]), part[k]);
 #pragma unroll
             for (int q = 0; q < 6; ++q)
 #pragma unroll
-                for (int k = 0; k < 2; ++k)
-                    sum[k][q & 1] = mfma(a[s % kAhead][k][TA[q]], b[s & 1][TB[q]], sum[k][q & 1]);
+                for (int k = 0; k < 2; ++k) sum[k][q & 1] = mfma(part[k][TA[q]], b[s & 1][TB[q]], sum[k][q & 1]);
             if (s + kAhead < 16) request(s + kAhead);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -455,37 +459,42 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
     if (!(first != nullptr ? t.meet(first) : t.sync(0.f))) return Outcome::dead;
     float prev = 3e38f;                        // |I - X^T X|_F^2 before the step before
     NsScale scale;
+    bool look = false;
     for (int it = 0;; ) {
         // A operands, contraction steps 0 .. 7 of X^T X, then 8 .. 15 = 0 .. 7 of X E.  Buffer loads: one
         // descriptor, a scalar offset per load (as pointers the addresses alone take 100 registers).  Every
         // wavefront of the team starts at another step: in step, they would all ask the same L2
         // channels at a time.
-        const int cols = (int)kColAt + ((it & 1) * kTeam + 2 * wave) * kImage;
-        const int rows = (int)kRowAt + ((it & 1) * kTeam + 2 * wave) * kImage;
-        u32x4 a[kAhead][2][3];
+        const int cols = (int)kColAt + ((it & 1) * kTeam + 2 * wave) * kShared;
+        const int rows = (int)kRowAt + ((it & 1) * kTeam + 2 * wave) * kShared;
+        u32x4 a[kAhead][2][2];
         auto turn = [&](int s) { return (s + wave + t.q) & 7; };
         auto request = [&](int s) {
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    const int at = k * kImage + (turn(s) * 3 + pl) * 1024;
-                    if (s < 8) {
-                        a[s % kAhead][k][pl] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, cols + at, 0);
-                    } else {
-                        const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane * 8, rows + at, 0);
-                        const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane * 8 + 512, rows + at, 0);
-                        a[s % kAhead][k][pl] = u32x4{lo.x, lo.y, hi.x, hi.y};
-                    }
-                }
+                for (int e = 0; e < 2; ++e)
+                    a[s % kAhead][k][e] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rsrc, lane * 16, (s < 8 ? cols : rows) + k * kShared + (turn(s) * 2 + e) * 1024, 0);
         };
 #pragma unroll
         for (int s = 0; s < kAhead; ++s) request(s);
+        if (look) {                            // uniform: what the last barrier carried, with the operands on their way
+            prev = group_sum<16>(t.value(0));
+            if (!(prev < 2.f * P)) return Outcome::left;
+            scale.seen(-row16_max(-t.value(1)));
+        }
         f32x4 gm[2];
         product(a, request, turn, ximg, std::integral_constant<int, 0>{}, gm);
 
-        float alpha = 1.f, fr = 0.f, least = 0.f;
+        float alpha = 1.f, fr = 0.f;
         bool last = false, known = false;
+        // |I - G|_F^2 of the workgroup's columns and their smallest diagonal entry: by one thread, after a barrier
+        auto own_norm = [&]() {
+            float v = 0.f;
+            for (int w = 0; w < kWaves; ++w) v += red[(it & 1) * 8 + w];
+            return v;
+        };
         f32x4 e[2];
         if (it == 0) {
             float rs = 0.f, r2 = 0.f;
@@ -518,8 +527,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             if (wave == (t.q >> 1) && lane == 0) red[kDiagAt + 1] = tr;
             least_diag(gm);
             __syncthreads();
-            least = red[kDiagAt];
-            if (!t.sync(row_max_nan(rs), row_max_nan(r2), least, group_sum<16>(r2), red[kDiagAt + 1])) return Outcome::dead;
+            if (!t.sync(row_max_nan(rs), row_max_nan(r2), red[kDiagAt], group_sum<16>(r2), red[kDiagAt + 1])) return Outcome::dead;
             const float rsmax = row_max_nan(t.value(0)), r2max = row_max_nan(t.value(1));
             // zero, infinite, NaN or overflowing input: not for this iteration
             if (!(rsmax > 1e-37f && rsmax < 3e37f)) return Outcome::left;
@@ -534,10 +542,6 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             fr = sum_groups(group_sum<16>(fr));
             if (lane == 0) red[(it & 1) * 8 + wave] = fr;
             least_diag(gm);
-            __syncthreads();
-            fr = 0.f;
-            for (int w = 0; w < kWaves; ++w) fr += red[(it & 1) * 8 + w];
-            least = red[kDiagAt];
             alpha = scale.next();
             // Close to the end the team meets here to learn whether this is the last step, and exchanges the
             // leading fp16 parts of E for its square.
@@ -549,7 +553,8 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
                 *reinterpret_cast<u32x4*>(eimg + wave * 3 * 1024 + lane * 16) = lead;
                 *reinterpret_cast<u32x4*>(eimg + (wave * 3 + 1) * 1024 + lane * 16) = u32x4{a0.lo, a1.lo, a2.lo, a3.lo};
                 *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)t.q * 8 + wave) * 1024 + lane * 16) = lead;
-                if (!t.sync(fr)) return Outcome::dead;
+                __syncthreads();
+                if (!t.sync(own_norm())) return Outcome::dead;
                 prev = group_sum<16>(t.value(0));
                 known = true;
                 if (!(prev < 2.f * P)) return Outcome::left;   // NaN or diverging
@@ -593,18 +598,14 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         product(a, request, turn, eimg, std::integral_constant<int, 8>{}, acc);
 #pragma unroll
         for (int k = 0; k < 2; ++k) xr[k] = alpha * xr[k] + (0.5f * alpha) * acc[k];
-        ++it;
         if (last) {
-            steps = it;
+            steps = it + 1;
             break;
         }
-        publish(it & 1);
-        if (!t.sync(fr, least)) return Outcome::dead;
-        if (!known && it > 1) {
-            prev = group_sum<16>(t.value(0));
-            if (!(prev < 2.f * P)) return Outcome::left;
-            scale.seen(-row16_max(-t.value(1)));
-        }
+        publish((it + 1) & 1);
+        if (!t.sync(it > 0 ? own_norm() : 0.f, red[kDiagAt])) return Outcome::dead;
+        look = !known && it > 0;
+        ++it;
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k)
