@@ -17,7 +17,8 @@ LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libsbo.so")
 
 SOURCES = ["sbo_api.hip", "code_energy.hip", "code_screen_16.hip", "code_screen_32.hip", "code_screen_64.hip",
-           "code_screen_256.hip", "code_home_64.hip", "code_home_256.hip", "code_select.hip", "select_accum.hip", "group.hip", "accumulate.hip",
+           "code_screen_256.hip", "code_home_64.hip", "code_home_256.hip", "code_guess_64.hip", "code_select.hip",
+           "select_accum.hip", "group.hip", "accumulate.hip",
            "polar_jacobi.hip", "polar_ns.hip", "polar_wide.hip", "eigen.hip", "reduce.hip", "worst.hip"]
 # bench.py's achievable-peak probes: a library of their own, not part of libsbo
 PROBE_SOURCE = "bench_probe.hip"
@@ -33,7 +34,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # from min/max, which need no NaN-quieting pre-pass when NaNs are not honoured (signals
 # or atoms holding NaN give unspecified block choices instead of propagating NaN).
 EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"] for f in SOURCES
-         if f.startswith(("code_energy", "code_screen", "code_home"))}
+         if f.startswith(("code_energy", "code_screen", "code_home", "code_guess"))}
 # (the same reason: the accumulators are read by vector instructions after every product)
 EXTRA["eigen.hip"] = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 

@@ -65,10 +65,14 @@ constexpr int dict_rows() {
 template <int P>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
-                                                         float2* __restrict__ dnorm, CallStart start) {
+                                                         float2* __restrict__ dnorm, float* __restrict__ dev, CallStart start) {
     start.clear();
     constexpr int KS16 = P / 16, R = dict_rows<P>();
     __shared__ float qs[R][P / 8 + 1], rs[R][P / 8 + 1];
+    // p = 64, dev: the rows of the whole block, [half, this one's first][ks][hi, lo][lane]
+    constexpr bool GRAM = P == 64;
+    __shared__ u32x4 both[GRAM ? 2 : 1][GRAM ? KS16 : 1][2][GRAM ? 64 : 1];
+    __shared__ float off[2];
     const f32x4* D4 = reinterpret_cast<const f32x4*>(D);
     const int rows = K * P;
     const int row0 = blockIdx.x * R;
@@ -97,6 +101,17 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
             out[64] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
             qs[r][kh] = q2;
             rs[r][kh] = r2;
+            if constexpr (GRAM) {
+                if (dev != nullptr) {          // uniform
+                    const int lane_g = hh * 32 + r;
+                    const f32x4* other = D4 + (int64_t)(grow ^ 32) * (P / 4) + ks * 4 + hh * 2;
+                    const F16x2Quad c = split_f16x2_dict(other[0], q2, r2), d = split_f16x2_dict(other[1], q2, r2);
+                    both[0][ks][0][lane_g] = u32x4{a.hi.x, a.hi.y, b.hi.x, b.hi.y};
+                    both[0][ks][1][lane_g] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
+                    both[1][ks][0][lane_g] = u32x4{c.hi.x, c.hi.y, d.hi.x, d.hi.y};
+                    both[1][ks][1][lane_g] = u32x4{c.lo.x, c.lo.y, d.lo.x, d.lo.y};
+                }
+            }
         }
     }
     if (Dsh != nullptr) {                      // uniform
@@ -111,6 +126,33 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
             r2 = row16_max(r2);
             const int at = (row0 + (int)threadIdx.x) >> 4;
             if ((threadIdx.x & 15) == 0 && at < K * (P / 16)) dnorm[at] = float2{sqrtf(q2), sqrtf(r2)};
+        }
+        if constexpr (GRAM) {
+            // Half of Q Q^T, products to 2^-22: this workgroup's rows with themselves by the third wavefront, with the others by
+            // the last.
+            if (dev == nullptr) return;        // uniform
+            const int lane = threadIdx.x & 63, half = (int)(threadIdx.x >> 6) - 2;
+            if (half >= 0) {                   // uniform over the wavefront
+                f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+#pragma unroll
+                    for (int ks = 0; ks < KS16; ++ks)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, both[0][ks][t == 1][lane]),
+                                                                     __builtin_bit_cast(f16x8, both[half][ks][t == 2][lane]), acc, 0, 0, 0);
+                float sum = 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = (v & 3) + 8 * (v >> 2) + 4 * (lane >> 5);
+                    const float d = acc[v] * (1.f / (kF16DictScale * kF16DictScale)) - (half == 0 && row == (lane & 31) ? 1.f : 0.f);
+                    sum = fmaf(d, d, sum);
+                }
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+                if (lane == 0) off[half] = sum;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) dev[blockIdx.x] = off[0] + off[1];
         }
     }
 }
@@ -870,18 +912,27 @@ hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const C
     return hipGetLastError();
 }
 
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, const CallStart& start,
-                             hipStream_t st) {
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, float2* dev,
+                             const CallStart& start, hipStream_t st) {
     u32x4 *b = reinterpret_cast<u32x4*>(dsb), *h = reinterpret_cast<u32x4*>(dsh);
+    float* dv = p == 64 && dsh != nullptr ? reinterpret_cast<float*>(dev) : nullptr;
     const unsigned stages = (unsigned)(K * p + 63) / 64;           // (the last one is filled up with zeros)
     switch (p) {
-        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
-        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
-        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
-        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm, start); break;
+        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
+        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
+        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
+        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+bool guess_applies(int p, int K, int s0, int64_t m, int arith) {
+    ScrArgs a;
+    a.m = (int)m;
+    a.K = K;
+    a.s0 = s0;
+    return p == 64 && screen_applies(p, K, s0, arith) && guess_takes_64(a);
 }
 
 static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const float* Y, int64_t m, const Workspace& ws,
@@ -907,6 +958,10 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
             a.sweeps = ws.sweeps;
             return p == 64 ? launch_home_64(a, arith, ws.raised, st) : launch_home_256(a, arith, ws.raised, st);
         }
+    }
+    if (turn <= 0 && p == 64 && guess_takes_64(a)) {
+        a.dev = ws.dev;
+        return launch_guess_64(a, arith, ws.raised, st);
     }
     switch (p) {
         case 16: return launch_screen_16(a, arith, ws.raised, st);

@@ -4,7 +4,7 @@
 namespace sbo {
 
 hipError_t launch_home_256(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
-    return launch_home_p<256>(a, arith, raised, st);
+    return launch_home_p<256, kHome>(a, arith, raised, st);
 }
 
 bool home_takes_256(const ScrArgs& a) { return home_takes<256>(a); }

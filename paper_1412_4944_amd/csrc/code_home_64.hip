@@ -4,7 +4,7 @@
 namespace sbo {
 
 hipError_t launch_home_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
-    return launch_home_p<64>(a, arith, raised, st);
+    return launch_home_p<64, kHome>(a, arith, raised, st);
 }
 
 bool home_takes_64(const ScrArgs& a) { return home_takes<64>(a); }

@@ -362,13 +362,35 @@ template <int P>
 constexpr bool home_applies(int s0) {
     return (P == 64 || P == 256) && home_line<P>(s0) < 0.97f;
 }
+// Without a grouping to start from (sbo_code, the first iteration; p = 64): the bounds of all blocks first.  That of a signal's
+// own block is hardly below |y|^2, because half of its large coefficients is not among the atoms looked at, so the block of the
+// largest bound is taken as its home, and only there is it screened in full, in tiles of 32 signals of one block.  That the
+// dictionary consists of orthobases, dict_parts_kernel has measured: |Q Q^T - I|_F at most kOrthobase.  After 4 blocks of every
+// 64 a workgroup with far fewer signals that have found their block (a bound above kGuessFound) than these blocks would get on
+// average goes over to screening everything in full: signals that no block represents cost 3 to 8 % more for the attempt.
+// 100003 signals, K = 64, s0 = 5: 69 -> 52 us, the call 107.5 -> 88.0; 500000 signals, K = 128, s0 = 6: call 645 -> 468; random signals,
+// K = 32, 262144 of them: 167 -> 176.
+constexpr float kOrthobase = 1e-4f;
+constexpr float kGuessFound = 0.99f;
+constexpr int kGuessFew = 4;                   // a quarter of that average, less one
+// A bad guess leaves nearly all blocks to the resolution, K tiles of one signal each.  From kGuessAgain K / wavefronts bad guesses on
+// a second listing is the smaller evil: 100003 signals, K = 128, s0 = 8: call 181 -> 146 us (full 171).  Only in workgroups of 512: those
+// of 256 run where a compute unit may have no other to hide its latencies, and the registers of the second listing cost more than
+// it gives (65537 signals, K = 32, s0 = 8: call 58 -> 62).
+constexpr int kGuessAgain = 8;
+constexpr int kGuessMinK = 16, kGuessMaxK = 160;           // (160: the lists of a workgroup fit where its stages were)
+
 // One signal in kHomeFew may be weak: of a workgroup, and of those counted, which are the first 64 of every kWeakEvery-th
 // workgroup (all of them: 4096 atomic additions to one address, 262144 signals 125 -> 152 us).
 constexpr int kHomeFew = 16, kWeakEvery = 4;
 
-template <int P, int S, int SX, int ARITH, bool SHARED, int W, bool HOME>
+// What a workgroup screens in full: everything; the home blocks of its signals; the block of the largest bound.
+enum Choice { kFull, kHome, kGuess };
+
+template <int P, int S, int SX, int ARITH, bool SHARED, int W, Choice CHOICE>
 __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     using G = ScrGeom<P>;
+    constexpr bool HOME = CHOICE == kHome, GUESS = CHOICE == kGuess;
     constexpr int KS16 = G::KS16, MTS = G::MTS, NB = G::NB, SPB = G::SPB, NV = G::NV, STAGE_U = G::STAGE_U;
     constexpr bool WIDE = G::WIDE, BOUND = scr_bound(P, SX, SHARED);
     constexpr bool YLDS = SHARED && P >= 64;               // B operands from LDS (registers: 32 less at p = 64)
@@ -396,8 +418,14 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
 
     // HOME: whether the dictionary represents the signals well enough (what the coding of the last iteration left in
     // weak, three counts in turn) and all its blocks are orthobases; the signals are then those at positions wg0 .. of perm.
-    bool by_home = false;
+    bool by_home = false, guess = GUESS;
     int id_own = 0, home_lo = 0, home_hi = 0;  // own signal; the home blocks of the workgroup
+    if constexpr (GUESS)
+        for (int j0 = 0; j0 < K; j0 += 64) {
+            const int jj = j0 + lane;
+            const float2 off = jj < K ? g.dev[jj] : float2{0.f, 0.f};
+            guess = guess && __ballot(!(off.x + off.y <= kOrthobase * kOrthobase)) == 0ull;
+        }
     if constexpr (HOME) {
         by_home = g.weak[(g.turn + 2) % 3] * kHomeFew <= (int)((gridDim.x + kWeakEvery - 1) / kWeakEvery) * 64;
         int lo = 0, hi = 0, other = 0;
@@ -719,6 +747,13 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         return !valid || y2_own == 0.f ? 0x10000u : t16;
     };
     constexpr unsigned kWeakBelow = (unsigned)(65535.f * (home_line<P>(SX) < 1.f ? home_line<P>(SX) : 1.f));
+    // Few enough signals whose best block has to be reached by others below the line; every wavefront, with a barrier.
+    auto few_weak = [&](unsigned t16) {
+        const int weak = __popcll(__ballot(t16 < kWeakBelow));
+        if (lane == 0 && weak != 0) atomicAdd(n_weak, weak);
+        __syncthreads();
+        return *n_weak * kHomeFew <= SIG;
+    };
     bool halves = false;                       // HOME: only the home blocks have been screened in full
     unsigned t_home = 0u;
     constexpr int kMatrix = NT * UT * KS16;
@@ -747,8 +782,9 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             if (WIDE && s % SPB == SPB - 1) finish(run, s / SPB);      // uniform
             __syncthreads();
         };
-        if constexpr (HOME) {
-            if (by_home) {                     // uniform
+        if constexpr (HOME || GUESS) {
+            const float2 nrm = norms();
+            if (HOME && by_home) {             // uniform
                 // the home blocks, those of its own signals by every wavefront
                 int lo = 0, hi = 0;
                 const int first = (int)wg0 + loc0, last = min(first + 63, m - 1);
@@ -770,124 +806,274 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     }
                     stash(pre, (s + 1) & 1);
                 }
-                const float2 nrm = norms();
                 t_home = threshold(bestE, nrm, 1.f);
-                const int weak = __popcll(__ballot(t_home < kWeakBelow));
-                if (lane == 0 && weak != 0) atomicAdd(n_weak, weak);
-                __syncthreads();
-                halves = *n_weak * kHomeFew <= SIG;
-
-                // and bounds from kHomeRows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the
-                // atoms of one
-                if (halves) {                  // uniform
-                    u16x2 top[NT];             // sqrt(t), twice
+                halves = few_weak(t_home);
+            }
+            if (GUESS) halves = guess;
+            // Bounds from kHomeRows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the
+            // atoms of one.  GUESS: without home blocks, the block of the largest bound is kept instead.
+            if (halves) {                      // uniform
+                u16x2 top[NT];             // sqrt(t), twice
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const _Float16 t = (_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2s[loc0 + nt * 32 + n], 0.f) * (kHomeT / P)));
-                        top[nt] = __builtin_bit_cast(u16x2, f16x2{t, t});
+                for (int nt = 0; nt < NT; ++nt) {
+                    const _Float16 t = (_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2s[loc0 + nt * 32 + n], 0.f) * (kHomeT / P)));
+                    top[nt] = __builtin_bit_cast(u16x2, f16x2{t, t});
+                }
+                const float t_own = (float)(_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2_own, 0.f) * (kHomeT / P)));
+                // Orthobases to 1e-4, sums to a few 2^-24; and |a - b| <= d gives a^2 >= b^2 - 2 d b for the root of the sum, b <= |y|.
+                constexpr float root = P > 64 ? 8.f : 5.657f;                        // of kHomeRows
+                const float most = 1.0003f + (float)g.s0 * (t_own * t_own) * e_scale + 2.f * root * coef_error(nrm);
+                const int n_step = WIDE ? 2 * K : (K + 1) / 2;
+                auto fetch_home = [&](u32x4 (&q)[FPT], int s) {
+                    s = min(s, n_step - 1);
+                    if constexpr (WIDE) {
+                        fetch(q, (s >> 1) * SPB + (s & 1));
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < FPT; ++r) {
+                            const int u = min(tid + 64 * W * r, STAGE_U - 1), v = u & (STAGE_U / 2 - 1);
+                            const int j = min(2 * s + u / (STAGE_U / 2), K - 1);
+                            q[r] = __builtin_amdgcn_raw_buffer_load_b128(dict, (j * (2 * STAGE_U) + (v >> 6) * 128 + (v & 63)) * 16, 0, 0);
+                        }
                     }
-                    const float t_own = (float)(_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2_own, 0.f) * (kHomeT / P)));
-                    // Orthobases to 1e-4, sums to a few 2^-24; and |a - b| <= d gives a^2 >= b^2 - 2 d b for the root of the sum, b <= |y|.
-                    constexpr float root = P > 64 ? 8.f : 5.657f;                        // of kHomeRows
-                    const float most = 1.0003f + (float)g.s0 * (t_own * t_own) * e_scale + 2.f * root * coef_error(nrm);
-                    const int n_step = WIDE ? 2 * K : (K + 1) / 2;
-                    auto fetch_home = [&](u32x4 (&q)[FPT], int s) {
-                        s = min(s, n_step - 1);
-                        if constexpr (WIDE) {
-                            fetch(q, (s >> 1) * SPB + (s & 1));
+                };
+                int n_left = 0;            // blocks that the bounds leave in, besides the best one, of the own signal
+                int last_block = -1;
+                auto leave = [&](float sum, int j) {
+                    const float e = most - sum * e_scale;
+                    if constexpr (GUESS) {
+                        const bool again = j == last_block;  // (the block past the end of an odd number of them)
+                        last_block = j;
+                        const float v = again ? -1.f : e;
+                        secondE = fmaxf(secondE, fminf(bestE, v));
+                        best = v > bestE ? j : best;
+                        bestE = fmaxf(bestE, v);
+                        E16[j * SIG + loc0 + lane] = (unsigned short)stored(e);
+                        return;
+                    }
+                    const bool other = j != best;
+                    secondE = fmaxf(secondE, other ? e : -1.f);
+                    const unsigned q = stored(e);
+                    E16[j * SIG + loc0 + lane] = (unsigned short)q;
+                    n_left += other && q >= t_home;
+                };
+                float part_sum[NT] = {0.f, 0.f};
+                auto bound = [&](const Acc& acc, int s, auto second_half) {
+#pragma unroll
+                    for (int b = 0; b < UT; ++b) {
+                        float up[NT][2] = {{0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll
+                        for (int v = 0; v < 16; v += 4) {
+                            f16x2 w[NT][2];
+#pragma unroll
+                            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                                for (int nt = 0; nt < NT; ++nt) {
+                                    const auto x = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[nt][b][v + 2 * k]), fabsf(acc[nt][b][v + 2 * k + 1]));
+                                    w[nt][k] = __builtin_bit_cast(f16x2, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x), top[nt]));
+                                }
+#pragma unroll
+                            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                                for (int nt = 0; nt < NT; ++nt) up[nt][k] = __builtin_amdgcn_fdot2(w[nt][k], w[nt][k], up[nt][k], false);
+                        }
+                        float sum[NT];
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) sum[nt] = up[nt][0] + up[nt][1];
+                        if constexpr (WIDE && !decltype(second_half)::value) {
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) part_sum[nt] = sum[nt];
+                        } else if constexpr (WIDE) {
+                            const SwapPair t = swap32(part_sum[0] + sum[0], part_sum[1] + sum[1]);
+                            leave(t.first + t.second, s >> 1);
                         } else {
-#pragma unroll
-                            for (int r = 0; r < FPT; ++r) {
-                                const int u = min(tid + 64 * W * r, STAGE_U - 1), v = u & (STAGE_U / 2 - 1);
-                                const int j = min(2 * s + u / (STAGE_U / 2), K - 1);
-                                q[r] = __builtin_amdgcn_raw_buffer_load_b128(dict, (j * (2 * STAGE_U) + (v >> 6) * 128 + (v & 63)) * 16, 0, 0);
-                            }
+                            const SwapPair t = swap32(sum[0], sum[1]);
+                            leave(t.first + t.second, min(2 * s + b, K - 1));
                         }
-                    };
-                    int n_left = 0;            // blocks that the bounds leave in, besides the best one, of the own signal
-                    auto leave = [&](float sum, int j) {
-                        const float e = most - sum * e_scale;
-                        const bool other = j != best;
-                        secondE = fmaxf(secondE, other ? e : -1.f);
-                        const unsigned q = stored(e);
-                        E16[j * SIG + loc0 + lane] = (unsigned short)q;
-                        n_left += other && q >= t_home;
-                    };
-                    float part_sum[NT] = {0.f, 0.f};
-                    auto bound = [&](const Acc& acc, int s, auto second_half) {
-#pragma unroll
-                        for (int b = 0; b < UT; ++b) {
-                            float up[NT][2] = {{0.f, 0.f}, {0.f, 0.f}};
-#pragma unroll
-                            for (int v = 0; v < 16; v += 4) {
-                                f16x2 w[NT][2];
-#pragma unroll
-                                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                                    for (int nt = 0; nt < NT; ++nt) {
-                                        const auto x = __builtin_amdgcn_cvt_pkrtz(fabsf(acc[nt][b][v + 2 * k]), fabsf(acc[nt][b][v + 2 * k + 1]));
-                                        w[nt][k] = __builtin_bit_cast(f16x2, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x), top[nt]));
-                                    }
-#pragma unroll
-                                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                                    for (int nt = 0; nt < NT; ++nt) up[nt][k] = __builtin_amdgcn_fdot2(w[nt][k], w[nt][k], up[nt][k], false);
-                            }
-                            float sum[NT];
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt) sum[nt] = up[nt][0] + up[nt][1];
-                            if constexpr (WIDE && !decltype(second_half)::value) {
-#pragma unroll
-                                for (int nt = 0; nt < NT; ++nt) part_sum[nt] = sum[nt];
-                            } else if constexpr (WIDE) {
-                                const SwapPair t = swap32(part_sum[0] + sum[0], part_sum[1] + sum[1]);
-                                leave(t.first + t.second, s >> 1);
-                            } else {
-                                const SwapPair t = swap32(sum[0], sum[1]);
-                                leave(t.first + t.second, min(2 * s + b, K - 1));
-                            }
-                        }
-                    };
-                    auto home_step = [&](Acc& now, Acc& next, int s, auto second_half) {
-                        stash(pre, s & 1);     // stage s + 2, requested a step ago (two steps ago: no better)
-                        fetch_home(pre, s + 3);
-                        project(next, (s + 1) & 1);
-                        bound(now, s, second_half);
-                        interleave<kMatrix, UT * 60>();
-                        __syncthreads();
-                    };
-                    fetch_home(pre, 0);
-                    stash(pre, 0);
-                    fetch_home(pre, 1);
-                    stash(pre, 1);
+                    }
+                };
+                auto home_step = [&](Acc& now, Acc& next, int s, auto second_half) {
+                    stash(pre, s & 1);     // stage s + 2, requested a step ago (two steps ago: no better)
+                    fetch_home(pre, s + 3);
+                    project(next, (s + 1) & 1);
+                    bound(now, s, second_half);
+                    interleave<kMatrix, UT * 60>();
+                    __syncthreads();
+                };
+                {
+                    u32x4 pre0[FPT], pre1[FPT];            // (three trips at once)
+                    fetch_home(pre0, 0);
+                    fetch_home(pre1, 1);
                     fetch_home(pre, 2);
+                    stash(pre0, 0);
+                    stash(pre1, 1);
+                }
+                __syncthreads();
+                project(acc0, 0);
+                __syncthreads();
+                for (int s = 0; s < n_step && halves; s += 2) {
+                    home_step(acc0, acc1, s, std::false_type{});
+                    if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});     // uniform
+                    // n blocks: far too few signals have found theirs, whose bound is hardly below one: in full
+                    if (GUESS && s == 2 * ((K - 1) / 64)) {            // uniform
+                        const int found = __popcll(__ballot(bestE >= kGuessFound && y2_own > 0.f));
+                        if (lane == 0 && found != 0) atomicAdd(&n_weak[1], found);
+                        __syncthreads();
+                        halves = (n_weak[1] + 1) * kGuessFew * K >= (int)min((int64_t)SIG, m - wg0) * 2 * (s + 2);
+                        __syncthreads();
+                    }
+                    if (!GUESS && (s & 14) == 14) {        // too many to be resolved one by one: all over again, in full
+                        if (n_left != 0) atomicAdd(&n_weak[1], n_left);
+                        n_left = 0;
+                        __syncthreads();
+                        halves = n_weak[1] <= 2 * SIG;
+                        __syncthreads();
+                    }
+                }
+            }
+            if constexpr (GUESS) {
+                // The kept energy, as far as the leading parts give it, of the wanted signals in their block j_try, in stored energies
+                // (the others: -1): the signals listed by block, in tiles of 32.
+                auto guessed_energy = [&](int j_try, bool wanted) {
+                    int* first = reinterpret_cast<int*>(front);                        // [K] signals of a block, then its first tile
+                    unsigned short* tile_block = reinterpret_cast<unsigned short*>(first + K);         // [most]
+                    const int most = K + SIG / 32;         // tiles
+                    unsigned short* list = tile_block + ((most + 7) & ~7);             // [most][32]
+                    __syncthreads();                       // the stages are dead
+                    for (int j = tid; j < K; j += NTH) first[j] = 0;
+                    for (int e = tid; e < most * 16; e += NTH) reinterpret_cast<unsigned*>(list)[e] = 0xffffffffu;
                     __syncthreads();
-                    project(acc0, 0);
+                    int slot = 0;
+                    if (wanted) slot = atomicAdd(&first[j_try], 1);
                     __syncthreads();
-                    for (int s = 0; s < n_step && halves; s += 2) {
-                        home_step(acc0, acc1, s, std::false_type{});
-                        if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});     // uniform
-                        if ((s & 14) == 14) {  // too many to be resolved one by one: all over again, in full
-                            if (n_left != 0) atomicAdd(&n_weak[1], n_left);
-                            n_left = 0;
-                            __syncthreads();
-                            halves = n_weak[1] <= 2 * SIG;
-                            __syncthreads();
+                    if (wave == 0) {
+                        int tiles = 0;
+                        for (int j0 = 0; j0 < K; j0 += 64) {
+                            const int j = j0 + lane, nt = j < K ? (first[j] + 31) >> 5 : 0, upto = tiles + wave_scan(nt);
+                            for (int t = 0; t < nt; ++t) tile_block[upto - nt + t] = (unsigned short)j;
+                            if (j < K) first[j] = upto - nt;
+                            tiles = __builtin_amdgcn_readlane(upto, 63);
+                        }
+                        if (lane == 0) *n_tasks = tiles;
+                    }
+                    __syncthreads();
+                    if (wanted) list[first[j_try] * 32 + slot] = (unsigned short)(loc0 + lane);
+                    thr[loc0 + lane] = __builtin_bit_cast(unsigned, -1.f);
+                    __syncthreads();
+                    const int tiles = *n_tasks;
+                    // two tiles at a time, so that the networks sort two signals per lane as elsewhere; the operands of the next
+                    // two are on their way meanwhile
+                    int id[2] = {-1, -1}, j_of[2] = {0, 0};
+                    ExactRow<P, 3> y[2];
+                    u32x4 rows[2][UT][KS16];
+                    auto look_up = [&](int t) {
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            id[k] = -1;
+                            if (t + k < tiles) {           // uniform
+                                j_of[k] = __builtin_amdgcn_readfirstlane((int)tile_block[t + k]);
+                                const int at = (int)list[(t + k) * 32 + n];
+                                id[k] = at == 0xffff ? -1 : at;
+                            }
+                            y[k].load(g, id[k] < 0 ? (int64_t)-1 : wg0 + id[k], h);
+                            const u32x4* D = g.Dh + (int64_t)j_of[k] * UT * (KS16 * 128) + lane;
+#pragma unroll
+                            for (int mt = 0; mt < UT; ++mt)
+#pragma unroll
+                                for (int ks = 0; ks < KS16; ++ks) rows[k][mt][ks] = D[(mt * KS16 + ks) * 128];
+                        }
+                    };
+                    look_up(2 * wave);
+                    for (int t = 2 * wave; t < tiles; t += 2 * NW) {
+                        const int id_out = h == 0 ? id[0] : id[1];
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            float vmax = 0.f;
+#pragma unroll
+                            for (int e = 0; e < P / 8; ++e)
+                                vmax = fmaxf(fmaxf(fmaxf(vmax, fabsf(y[k].v[e].x)), fmaxf(fabsf(y[k].v[e].y), fabsf(y[k].v[e].z))),
+                                             fabsf(y[k].v[e].w));
+                            vmax = fmaxf(vmax, other_half(vmax));
+                            const unsigned ex = (__builtin_bit_cast(unsigned, vmax) >> 23) & 0xffu;        // (as convert_group)
+                            const float scale = ex >= 64u && ex <= 240u ? __builtin_bit_cast(float, (253u - ex) << 23) : 0.f;
+#pragma unroll
+                            for (int ks = 0; ks < KS16; ++ks) {
+                                const f32x4 v0 = y[k].v[2 * ks] * scale, v1 = y[k].v[2 * ks + 1] * scale;
+                                const u32x4 b = {pack_f16(v0.x, v0.y), pack_f16(v0.z, v0.w), pack_f16(v1.x, v1.y), pack_f16(v1.z, v1.w)};
+#pragma unroll
+                                for (int mt = 0; mt < UT; ++mt)
+                                    acc0[k][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                                        __builtin_bit_cast(f16x8, rows[k][mt][ks]), __builtin_bit_cast(f16x8, b),
+                                        ks == 0 ? zero : acc0[k][mt], 0, 0, 0);
+                            }
+                        }
+                        u16x2 x[NV], a[SX];
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            const auto q = __builtin_amdgcn_cvt_pkrtz(fabsf(acc0[0][v >> 4][v & 15]), fabsf(acc0[1][v >> 4][v & 15]));
+                            x[v] = __builtin_bit_cast(u16x2, q);
+                        }
+                        look_up(t + 2 * NW);
+                        pk_top_sorted<NV, SX>(x, a);
+                        const float e = pk_pair_energy<SX>(a, h != 0);
+                        if (id_out >= 0) thr[id_out] = __builtin_bit_cast(unsigned, e * 0x1p-26f / y2s[id_out]);
+                    }
+                    __syncthreads();
+                    const float below = __builtin_bit_cast(float, thr[loc0 + lane]);
+                    if (tid == 0) *n_tasks = 0;
+                    __syncthreads();
+                    return below;
+                };
+                // Signals badly represented by their blocks leave most blocks to the resolution.  Where that is more work than a second
+                // listing (tiles of 32 among the wavefronts), and not most are, those try the next best block too.
+                if (halves) {                  // uniform
+                    float kept = -1.f;
+                    int j_try = best;
+                    bool wanted = y2_own > 0.f;
+                    for (int round = 0;; ++round) {
+                        const float e = guessed_energy(j_try, wanted);
+                        if (wanted) {
+                            E16[j_try * SIG + loc0 + lane] = (unsigned short)stored(e);
+                            best = e > kept ? j_try : best;
+                            kept = fmaxf(kept, e);
+                        }
+                        t_home = threshold(kept, nrm, 1.f);
+                        wanted = wanted && t_home < kWeakBelow;
+                        halves = few_weak(t_home);
+                        const int n_bad = *n_weak;
+                        if (W < kScrWaves || (halves && n_bad * K <= kGuessAgain * NW) || round != 0 || 4 * n_bad > SIG) break;   // uniform
+                        __syncthreads();
+                        if (tid == 0) *n_weak = 0;
+                        // its largest bound, and what is second to both
+                        if (__ballot(wanted) != 0ull) {
+                            unsigned q0 = 0, q1 = 0;
+                            int j0 = 0;
+                            for (int j = 0; j < K; ++j) {
+                                const unsigned q = E16[j * SIG + loc0 + lane];
+                                q1 = max(q1, min(q0, q));
+                                j0 = q > q0 ? j : j0;
+                                q0 = max(q0, q);
+                            }
+                            if (wanted) {
+                                j_try = j0;
+                                secondE = (float)q1 * (1.f / 65535.f);
+                            }
                         }
                     }
                 }
-                if (!halves) {                 // uniform
-                    bestE = secondE = -1.f;
-                    best = 0;
-                    fetch(pre, 0);
-                    __syncthreads();
-                }
+            }
+            if ((by_home || guess) && !halves) {               // uniform
+                bestE = secondE = -1.f;
+                best = 0;
+                fetch(pre, 0);
+                __syncthreads();
             }
         }
         if (!halves) {                         // uniform
+            u32x4 pre1[FPT];
+            fetch(pre1, 1);
             stash(pre, 0);
-            fetch(pre, 1);
-            stash(pre, 1);
+            stash(pre1, 1);
             __syncthreads();
             project(acc0, 0);
             __syncthreads();
@@ -967,7 +1153,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     }
     // one unit for the rounding of the table; BOUND: what the sum of a bound may lose to rounding
     constexpr float kUnits = 1.f + (!BOUND ? 0.f : 65535.f * P * 0x1p-25f * (1.f + (float)P / SX));
-    const unsigned t16 = HOME && halves ? t_home : threshold(below, norms(), kUnits);
+    const unsigned t16 = (HOME || GUESS) && halves ? t_home : threshold(below, norms(), kUnits);
     const bool undecided = stored(secondE) >= t16;
     if (t16 == 0x10000u) best = 0;             // a zero signal: block 0 (ties go to the lowest)
     if constexpr (home_applies<P>(SX))
@@ -1064,14 +1250,14 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     }
 }
 
-template <int P, int S, int SX, int ARITH, bool SHARED, int W, bool HOME>
+template <int P, int S, int SX, int ARITH, bool SHARED, int W, Choice CHOICE>
 hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t st) {
     constexpr int sig = SHARED ? 64 : 64 * W;
     const size_t lds = scr_lds_bytes<P, SHARED, W>(a.K);
     if (lds > kScrLdsMax || a.chunk % sig != 0) return hipErrorInvalidValue;
-    const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W, HOME>);
+    const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>);
     if (hipError_t e = raised->ensure(fn, kScrLdsMax); e != hipSuccess) return e;
-    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W, HOME>), dim3((unsigned)((a.m + sig - 1) / sig)),
+    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>), dim3((unsigned)((a.m + sig - 1) / sig)),
                        dim3(64 * waves), lds, st, a);
     return hipGetLastError();
 }
@@ -1103,31 +1289,31 @@ template <int P, int S, int SX, int ARITH>
 hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
     if (scr_shared<P>(a)) {
         const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
-        return launch_w<P, S, SX, ARITH, true, kScrWaves, false>(a, units < kScrWaves ? units : kScrWaves, raised, st);
+        return launch_w<P, S, SX, ARITH, true, kScrWaves, kFull>(a, units < kScrWaves ? units : kScrWaves, raised, st);
     }
     if constexpr (P <= 64)
         if (scr_by_256<P>(a))
-            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2, false>(a, kScrWaves / 2, raised, st);
-    return launch_w<P, S, SX, ARITH, false, kScrWaves, false>(a, kScrWaves, raised, st);
+            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2, kFull>(a, kScrWaves / 2, raised, st);
+    return launch_w<P, S, SX, ARITH, false, kScrWaves, kFull>(a, kScrWaves, raised, st);
 }
 
-// The signals in the order of the grouping in g.perm, with home blocks.
-template <int P, int SX, int ARITH>
+// With home blocks (the signals in the order of the grouping in g.perm), or guessing them.
+template <int P, int SX, int ARITH, Choice CHOICE>
 hipError_t launch_home_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
     constexpr int S = pow2_at_least(SX);
     if constexpr (P <= 64)
         if (scr_by_256<P>(a))
-            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2, true>(a, kScrWaves / 2, raised, st);
-    return launch_w<P, S, SX, ARITH, false, kScrWaves, true>(a, kScrWaves, raised, st);
+            return launch_w<P, S, SX, ARITH, false, kScrWaves / 2, CHOICE>(a, kScrWaves / 2, raised, st);
+    return launch_w<P, S, SX, ARITH, false, kScrWaves, CHOICE>(a, kScrWaves, raised, st);
 }
-template <int P>
+template <int P, Choice CHOICE>
 hipError_t launch_home_p(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st) {
     switch (a.s0) {
 #define SBO_CASE(N) \
     case N:         \
         if constexpr (home_applies<P>(N)) { \
-            if (arith == SBO_ARITH_F16X2) return launch_home_a<P, N, 3>(a, raised, st); \
-            if constexpr (P <= 64) return arith == SBO_ARITH_F32 ? launch_home_a<P, N, 0>(a, raised, st) : launch_home_a<P, N, 1>(a, raised, st); \
+            if (arith == SBO_ARITH_F16X2) return launch_home_a<P, N, 3, CHOICE>(a, raised, st); \
+            if constexpr (P <= 64) return arith == SBO_ARITH_F32 ? launch_home_a<P, N, 0, CHOICE>(a, raised, st) : launch_home_a<P, N, 1, CHOICE>(a, raised, st); \
         } \
         break;
         SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)

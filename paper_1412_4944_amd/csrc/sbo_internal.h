@@ -91,6 +91,7 @@ struct Workspace {
     unsigned* dsb;         // the same rows as three bf16 parts (6 bytes per entry)
     unsigned* dsh;         // the same rows as two fp16 parts (4 bytes per entry)
     float2* dnorm;         // [K*p/16] per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
+    float2* dev;           // [K] p = 64: |Q Q^T - I|_F^2 of a block, in two parts (guess_applies)
     float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row; or
                            // the energies of a small set, [K][m] (at most kDirectMaxEnergies)
     int32_t* part_j;       // same shape: its block
@@ -233,9 +234,11 @@ struct CallStart {
 // dsw = D in the fp32 operand order of the coding kernels.
 hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const CallStart& start, hipStream_t st);
 // dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
-// (device_utils.h); dnorm comes with dsh.
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, const CallStart& start,
-                             hipStream_t st);
+// (device_utils.h); dnorm comes with dsh.  dev (or nullptr; p = 64, dsh given): |Q Q^T - I|_F^2 per block.
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, float2* dev,
+                             const CallStart& start, hipStream_t st);
+// Whether the block choice of a first pass (turn <= 0 of launch_energy) reads ws.dev.
+bool guess_applies(int p, int K, int s0, int64_t m, int arith);
 // The block of every signal, from the operand orders in ws that (p, s0, arith) reads (energy_ops in
 // sbo_api.hip).
 // chunk_count != nullptr: also add the per-chunk histograms of the chosen blocks into it (the

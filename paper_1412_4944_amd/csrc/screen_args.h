@@ -22,6 +22,8 @@ struct ScrArgs {
     int turn = 0;
     // ... from the second one on: the last grouping, and the blocks whose last update was by Newton-Schulz (negative)
     const int32_t *perm = nullptr, *offsets = nullptr, *sweeps = nullptr;
+    // ... in the first one, and in sbo_code: per block |Q Q^T - I|_F^2 in two parts
+    const float2* dev = nullptr;
     // energy_direct_kernel only
     const float* D = nullptr;
     float* E = nullptr;        // [K][m]
@@ -37,6 +39,9 @@ hipError_t launch_home_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStr
 hipError_t launch_home_256(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
 bool home_takes_64(const ScrArgs& a);
 bool home_takes_256(const ScrArgs& a);
+// Guessing them (dev given).
+hipError_t launch_guess_64(const ScrArgs& a, int arith, LdsRaised* raised, hipStream_t st);
+bool guess_takes_64(const ScrArgs& a);
 // The full-precision energies of every (signal, block), from D itself.
 hipError_t launch_direct_16(const ScrArgs& a, int arith, hipStream_t st);
 hipError_t launch_direct_32(const ScrArgs& a, int arith, hipStream_t st);

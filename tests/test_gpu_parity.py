@@ -498,6 +498,23 @@ def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m
         assert all(np.array_equal(a, b.cpu().numpy()) for a, b in zip(again, out))
 
 
+@pytest.mark.parametrize("K,s0,m,kind,arith", [(32, 8, 65537, "planted", "bf16x3"), (16, 3, 70001, "planted", "f32"),
+                                               (31, 6, 90001, "odd signals", "f16x2"), (100, 5, 53001, "close", "f16x2"),
+                                               (64, 5, 131149, "close", "bf16x3"), (127, 8, 100003, "planted", "f16x2"),
+                                               (40, 8, 270001, "odd signals", "f32"), (33, 7, 66000, "random", "f16x2"),
+                                               (159, 4, 210007, "planted", "f16x2")])
+def test_code_starts_from_the_block_of_the_largest_bound(K, s0, m, kind, arith):
+    """sbo_code on many signals guesses their block from bounds, where the dictionary consists of orthobases; with one more
+    block that is none and that nobody takes it screens them all: the same bits."""
+    Y, D = _home_case(64, K, s0, m, kind)
+    got = []
+    for Dk in (D, np.concatenate([D, 0.25 * D[:1]])):
+        with Sbo(64, len(Dk), s0, m, arith=arith) as g:
+            got.append(g.code(Y, Dk))
+    for name, a, b in zip(("blk", "supp", "coef", "err"), *got):
+        assert np.array_equal(a, b), (name, int((a != b).sum()))
+
+
 @pytest.mark.parametrize("name,kw", [("tiny", dict()), ("patch8", dict(m=5000)), ("p32", dict(p=32, K=6, m=3000, s0=4)),
                                      ("p64_s5", dict(p=64, K=7, m=2100, s0=5)),
                                      ("p256", dict(p=256, K=2, m=1500, s0=12, snr_db=25.0))])
