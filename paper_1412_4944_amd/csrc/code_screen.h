@@ -597,6 +597,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     constexpr int UT = SHARED ? (P == 64 ? 2 : 1) : MTS;   // 32-row tiles of a step
     constexpr int UB = WIDE ? 1 : UT * 32 / P;             // blocks of a step
+    const int per_row = ((WIDE ? K : (K + UB - 1) / UB) + g.rows - 1) / g.rows;         // SHARED: units of a row of workgroups
     using Acc = f32x16[NT][UT];
     u16x2 run[SX];                             // p = 256: the pair's sorted top of the block so far
     // of the own signal, in stored units (BOUND: bounds from above)
@@ -1085,11 +1086,12 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     } else {
         // A step = UT row tiles of the dictionary, p = 256: one of the SPB tiles of a block; wavefront w takes
         // the blocks (p < 64: tiles) w, w + NW, .. and reads their rows from L2, one step ahead.
-        const int n_unit = WIDE ? K : (K + UB - 1) / UB;
+        const int unit0 = (int)blockIdx.y * per_row;
+        const int n_unit = min((WIDE ? K : (K + UB - 1) / UB) - unit0, per_row);
         const int n_mine = wave < n_unit ? ((n_unit - 1 - wave) / NW + 1) * SPB : 0;
         auto tile_of = [&](int t) {            // past the end: the last one once more, not used
             t = min(t, n_mine - 1);
-            return WIDE ? (wave + (t / SPB) * NW) * SPB + t % SPB : (wave + t * NW) * UT;
+            return WIDE ? (unit0 + wave + (t / SPB) * NW) * SPB + t % SPB : (unit0 + wave + t * NW) * UT;
         };
         u32x4 rows[UT][KS16];
         auto load = [&](int t) {
@@ -1108,9 +1110,9 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         auto step = [&](Acc& now, Acc& next, int t) {
             project(next);
             load(t + 2);
-            select(now, WIDE ? 0 : (wave + t * NW) * UB, t % SPB == 0);
+            select(now, WIDE ? 0 : (unit0 + wave + t * NW) * UB, t % SPB == 0);
             interleave<kMatrix, kVector>();
-            if (WIDE && t % SPB == SPB - 1) finish(run, wave + (t / SPB) * NW);   // uniform
+            if (WIDE && t % SPB == SPB - 1) finish(run, unit0 + wave + (t / SPB) * NW);           // uniform
         };
         if (n_mine > 0) {                      // uniform over the wavefront
             load(0);
@@ -1149,6 +1151,52 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             best = ahead ? __builtin_bit_cast(int, xb[(3 * NW + w) * 64 + lane]) : best;
             bestE = ahead ? u : bestE;
             below = fmaxf(below, e);
+        }
+        if (g.rows > 1) {                      // uniform
+            // Of a column of workgroups the last one to finish goes on, with what all have found; nobody waits.  All of the exchange
+            // goes past the caches of an XCD (atomics of the agent scope, both ways), and every store has been acknowledged before
+            // the count: the order that a fence would give, without writing the L2 back (a release and an acquire: 1 to 3 us more).
+            const int row = (int)blockIdx.y, col = (int)blockIdx.x;
+            const int j_beg = min(row * per_row * UB, K), j_end = min((row + 1) * per_row * UB, K);
+            unsigned* E_all = g.split_E + (size_t)col * K * 32;
+            unsigned* E_own = reinterpret_cast<unsigned*>(E16);
+            unsigned* x = g.split_x + (size_t)(col * g.rows) * 256;
+            for (int e = j_beg * 32 + tid; e < j_end * 32; e += NTH)
+                __hip_atomic_store(&E_all[e], E_own[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (wave == 0) {
+                const float found[4] = {below, bestE, secondE, __builtin_bit_cast(float, best)};
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    __hip_atomic_store(&x[(row * 4 + k) * 64 + lane], __builtin_bit_cast(unsigned, found[k]), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) {
+                const int before = __hip_atomic_fetch_add(&g.split_done[col], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (before == g.rows - 1) __hip_atomic_store(&g.split_done[col], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                *n_tasks = before;
+            }
+            __syncthreads();
+            const bool last = *n_tasks == g.rows - 1;
+            if (!last) return;                 // uniform
+            __syncthreads();
+            if (tid == 0) *n_tasks = 0;
+            for (int e = tid; e < K * 32; e += NTH)
+                if (e < j_beg * 32 || e >= j_end * 32)
+                    E_own[e] = __hip_atomic_load(&E_all[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            below = bestE = secondE = -1.f;
+            for (int r = 0; r < g.rows; ++r) {
+                float v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    v[k] = __builtin_bit_cast(float, __hip_atomic_load(&x[(r * 4 + k) * 64 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                const bool ahead = v[0] > below;
+                secondE = fmaxf(fmaxf(secondE, v[2]), ahead ? bestE : v[1]);
+                best = ahead ? __builtin_bit_cast(int, v[3]) : best;
+                bestE = ahead ? v[1] : bestE;
+                below = fmaxf(below, v[0]);
+            }
         }
     }
     // one unit for the rounding of the table; BOUND: what the sum of a bound may lose to rounding
@@ -1257,7 +1305,7 @@ hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t 
     if (lds > kScrLdsMax || a.chunk % sig != 0) return hipErrorInvalidValue;
     const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>);
     if (hipError_t e = raised->ensure(fn, kScrLdsMax); e != hipSuccess) return e;
-    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>), dim3((unsigned)((a.m + sig - 1) / sig)),
+    hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>), dim3((unsigned)((a.m + sig - 1) / sig), (unsigned)a.rows),
                        dim3(64 * waves), lds, st, a);
     return hipGetLastError();
 }
@@ -1289,7 +1337,9 @@ template <int P, int S, int SX, int ARITH>
 hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
     if (scr_shared<P>(a)) {
         const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
-        return launch_w<P, S, SX, ARITH, true, kScrWaves, kFull>(a, units < kScrWaves ? units : kScrWaves, raised, st);
+        ScrArgs b = a;
+        b.rows = choice_split(P, a.K, a.m);
+        return launch_w<P, S, SX, ARITH, true, kScrWaves, kFull>(b, units < kScrWaves ? units : kScrWaves, raised, st);
     }
     if constexpr (P <= 64)
         if (scr_by_256<P>(a))

@@ -47,6 +47,9 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     const size_t direct = m_max < kDirectMaxEnergies / K ? (size_t)K * m_max : (size_t)kDirectMaxEnergies;
     w.part_E = (float*)take((direct > kEnergySplitRows * split_m ? direct : kEnergySplitRows * split_m) * 4);
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
+    w.split_E = (unsigned*)take(K <= kSplitMaxK ? (size_t)((m_max < kSplitMaxSignals ? m_max : kSplitMaxSignals) + 63) / 64 * K * 128 : 0);
+    w.split_x = (unsigned*)take((size_t)kNumCU * 4 * 64 * 4);
+    w.split_done = (int*)take((size_t)kNumCU / 2 * 4);
     // The eigenvectors of a Gram matrix are computed when the pieces of that matrix have been summed: same memory.
     size_t partial = (size_t)max_pieces_bound(m_max, K, p) * p * p * 4;
     if (partial < eigen_scratch_bytes(p)) partial = eigen_scratch_bytes(p);
@@ -279,6 +282,7 @@ int sbo_create(sbo_ctx** out, int p, int K, int s0, int64_t m_max, void* hip_str
     // polar_wide.hip are zero whenever no call is in flight.
     e = hipMemsetAsync(c->ws.sq_counter, 0, 4, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->ws.group_done, 0, 4, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws.split_done, 0, (size_t)kNumCU / 2 * 4, c->stream);
     if (e == hipSuccess && p > 64) e = hipMemsetAsync(c->ws.wide_sync, 0, polar_wide_sync_bytes(K), c->stream);
     if (e != hipSuccess) {
         (void)hipFree(c->ws_base);

@@ -95,6 +95,9 @@ struct Workspace {
     float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row; or
                            // the energies of a small set, [K][m] (at most kDirectMaxEnergies)
     int32_t* part_j;       // same shape: its block
+    unsigned* split_E;     // choice_split: [ceil(m / 64)][K][64 signals] 16 bits, the energies of all blocks
+    unsigned* split_x;     // ... [kNumCU][4][64] what a workgroup found
+    int* split_done;       // ... [kNumCU / 2] workgroups of a column that have finished (0 between launches)
     // accumulation
     float* partial;        // [max_pieces][p][p]
     float* M;              // [K][p][p]
@@ -191,6 +194,18 @@ constexpr bool screen_by_256(int64_t m) {
 constexpr bool screen_shared(int64_t m, bool p64_by_256) {
     const int64_t round = (int64_t)kNumCU * 512, rounds = (m + round - 1) / round;
     return p64_by_256 ? 5 * m < 2 * round : 20 * m < 13 * rounds * round;
+}
+
+// Screening by workgroups of 64 signals that leave at least half of the chip idle: the blocks are shared out among rows of
+// workgroups, kSplitAtoms or more to each, and the one that finishes last decides.  The exchange takes 2 to 3 us: calls of
+// sbo_code, 5041 signals, p = 256, s0 = 12, K = 16 59.6 -> 51, K = 32 86 -> 65; p = 64, s0 = 6, K = 64 31.7 -> 30.0, K = 200 60 -> 47; 600
+// signals, p = 64, K = 200 49 -> 32.  (2048 atoms or more: up to 7 % slower where there is room for more rows.)  With p < 64 the steps saved
+// are shorter than that: p = 32, K = 128 29.6 -> 30.5, p = 16, K = 64 18.5 -> 23.
+constexpr int kSplitMaxSignals = kNumCU / 2 * 64, kSplitMaxK = 256, kSplitAtoms = 1024;
+constexpr int choice_split(int p, int K, int64_t m) {
+    const int columns = m <= kSplitMaxSignals ? (int)((m + 63) / 64) : kNumCU, parts = K * p / kSplitAtoms;
+    const int rows = kNumCU / columns < parts ? kNumCU / columns : parts;
+    return p >= 64 && K <= kSplitMaxK && rows > 1 ? rows : 1;
 }
 
 // Which calls of sbo_code leave the choice among full-precision energies to the select kernel (energy_direct_kernel): those

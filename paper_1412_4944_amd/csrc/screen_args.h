@@ -24,6 +24,10 @@ struct ScrArgs {
     const int32_t *perm = nullptr, *offsets = nullptr, *sweeps = nullptr;
     // ... in the first one, and in sbo_code: per block |Q Q^T - I|_F^2 in two parts
     const float2* dev = nullptr;
+    // workgroups of 64 signals, split: rows of workgroups that share out the blocks, and what they exchange (choice_split)
+    int rows = 1;
+    unsigned *split_E = nullptr, *split_x = nullptr;
+    int* split_done = nullptr;
     // energy_direct_kernel only
     const float* D = nullptr;
     float* E = nullptr;        // [K][m]

@@ -515,6 +515,20 @@ def test_code_starts_from_the_block_of_the_largest_bound(K, s0, m, kind, arith):
         assert np.array_equal(a, b), (name, int((a != b).sum()))
 
 
+@pytest.mark.parametrize("p,K,s0,kind,arith", [(256, 16, 12, "close", "f16x2"), (256, 31, 5, "planted", "f16x2"),
+                                               (64, 33, 8, "close", "bf16x3"), (64, 130, 6, "odd signals", "f32"),
+                                               (64, 256, 3, "planted", "f16x2")])
+def test_code_of_few_signals_shares_out_the_blocks(p, K, s0, kind, arith):
+    """Up to 8192 signals the block choice is split among workgroups; a signal gets the same bits as in a larger set
+    (but for the last one of its error, which is rounded by where it stands in a tile of the selection)."""
+    Y, D = _home_case(p, K, s0, 8256, kind)
+    with Sbo(p, K, s0, len(Y), arith=arith) as g:
+        want = g.code(Y, D)
+        for m in (1100, 4097, 5041, 8192, 2111):
+            for name, a, b in zip(("blk", "supp", "coef"), want, g.code(Y[:m], D)):
+                assert np.array_equal(a[:m], b), (m, name, int((a[:m] != b).sum()))
+
+
 @pytest.mark.parametrize("name,kw", [("tiny", dict()), ("patch8", dict(m=5000)), ("p32", dict(p=32, K=6, m=3000, s0=4)),
                                      ("p64_s5", dict(p=64, K=7, m=2100, s0=5)),
                                      ("p256", dict(p=256, K=2, m=1500, s0=12, snr_db=25.0))])
