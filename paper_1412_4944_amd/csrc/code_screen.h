@@ -29,15 +29,17 @@
 //      arithmetic (SBO_ARITH_*), operand by operand and sum by sum what the kernels in
 //      code_energy.hip do, and compared: the largest energy wins, the lower block on a tie.
 // The chosen blocks are therefore those of the full computation, for every dictionary (nothing is
-// assumed about D; the bound is just wide if its atoms are long).
+// assumed about D; the bound is just wide if its atoms are long).  Where a dictionary is known to consist of orthobases
+// most blocks take less (home blocks, guessed blocks: below).
 //
 // Two shapes of the same work:
-//   energy_screen_kernel<..., false, W, HOME>: a workgroup takes 64 W signals, a wavefront 64 of them and all
+//   energy_screen_kernel<..., false, W, Choice>: a workgroup takes 64 W signals, a wavefront 64 of them and all
 //     blocks; dictionary stages go through LDS, double-buffered.  W = 8; W = 4, two workgroups per CU, for a last
 //     round that W = 8 would not fill.
-//   energy_screen_kernel<..., true, 8, false>: a workgroup takes 64 signals, and its wavefronts share out the
+//   energy_screen_kernel<..., true, 8, kFull>: a workgroup takes 64 signals, and its wavefronts share out the
 //     blocks and read their dictionary rows straight from L2: more workgroups, for signal sets that
-//     would not fill the chip otherwise, and for K beyond the LDS table of the other.
+//     would not fill the chip otherwise, and for K beyond the LDS table of the other.  Up to 8192 signals several
+//     workgroups share out the blocks (choice_split).
 //
 // Measured (MI355X, f16x2 results; "before" is the full-precision projection of every block): K = 32, p = 64,
 // s0 = 8, 262144 signals 229 us before, 126 with networks for every block, 100 with bounds; K = 128, s0 = 6, 2^20
@@ -329,8 +331,8 @@ __device__ __forceinline__ void interleave() {
     }
 }
 
-// Home blocks (sbo_iterate from its second iteration on, where it takes more than 64 signals per workgroup): the signals are taken in the order of the previous grouping, so
-// that most of the signals of a workgroup belong to one block, their home.  That block is screened first, in full.  For every other
+// Home blocks (sbo_iterate from its second iteration on, where it takes more than 64 signals per workgroup): the signals are
+// taken in the order of the previous grouping, so that most of the signals of a workgroup belong to one block, their home.  That block is screened first, in full.  For every other
 // one, of which the update has just made an orthobase (sweeps), kHomeRows atoms decide: with R = the part of the signal's energy that
 // they leave, and for any t,
 //     kept energy  <=  R + s0 t + sum over them of (c^2 - min(c^2, t))  =  |y|^2 + s0 t - sum of min(c^2, t),

@@ -219,7 +219,8 @@ constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than 
 // Which iterations leave the grouping to the select + accumulate kernel, and which calls of sbo_code to the select kernel, whose
 // workgroups list the signals of their own piece (ChunkLists in device_utils.h).  The histograms are read by every workgroup,
 // and a piece of a block comes from K times as many signals.  sbo_iterate, an iteration: 16384 signals, K = 16, p = 64 47.5 us
-// with a grouping launch, 41 (with the shorter search for a piece); the same table as below was not taken beyond 4096 entries.
+// with a grouping launch, 41 (with the shorter search for a piece); beyond 4096 entries a launch costs less than reading them
+// in every workgroup, by the figures of sbo_code below and a select+accumulate kernel with one workgroup to a CU.
 // sbo_code, with a grouping launch / lists (us): p = 64, K = 16 2100 signals 26.0 / 21.3, 65537 50.3 / 44.7, 131000 62.4 / 59.0;
 // K = 64 65537 104.2 / 99.0, 100003 (p = 32) 68.9 / 74.5; K = 128 12000 47.4 / 46.4, 32000 81.8 / 78.0, 40000 (p = 32) 49.4 / 49.8;
 // K = 200 12000 59.9 / 63.6; p = 256, K = 16 5000 61.3 / 55.4, 65537 271.5 / 268.8, 100003 336.8 / 341.2.  Sets of 1025 to 2048

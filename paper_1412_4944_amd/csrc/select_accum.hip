@@ -23,7 +23,7 @@
 //
 // What bounds it: instruction issue and LDS round trips of two wavefronts per SIMD, not memory (Y is
 // read once).  Measured, 262144 signals, K = 32, p = 64, s0 = 8: 61 us with y transposed word by word through
-// lane exchanges and the copies of the accumulators stored entry by entry, 49 us as it is (with the shorter
+// lane exchanges and the copies of the accumulators stored entry by entry, 44.6 us as it is (with the shorter
 // selection of select_tile.h); 2^20 signals, K = 128: 265 -> 190 us.
 #include "sbo_internal.h"
 #include "device_utils.h"
