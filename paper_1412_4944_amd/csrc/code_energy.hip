@@ -955,11 +955,16 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
     if (turn >= 0 && (p == 64 ? home_takes_64(a) : p == 256 && home_takes_256(a))) {
         a.weak = ws.weak;
         a.turn = turn;
-        if (turn > 0 && orthobases) {
-            a.perm = ws.perm;
-            a.offsets = ws.offsets;
-            a.sweeps = ws.sweeps;
-            return p == 64 ? launch_home_64(a, arith, ws.raised, st) : launch_home_256(a, arith, ws.raised, st);
+        if (orthobases) {
+            // The first iteration loads the kernel of the next ones (2.3 ms, once in a process: a program that has made one
+            // iteration has made ready for more).
+            ScrArgs home = a;
+            home.load_only = turn == 0;
+            home.perm = ws.perm;
+            home.offsets = ws.offsets;
+            home.sweeps = ws.sweeps;
+            hipError_t e = p == 64 ? launch_home_64(home, arith, ws.raised, st) : launch_home_256(home, arith, ws.raised, st);
+            if (turn > 0 || e != hipSuccess) return e;
         }
     }
     if (turn <= 0 && p == 64 && guess_takes_64(a)) {

@@ -1306,7 +1306,7 @@ hipError_t launch_w(const ScrArgs& a, int waves, LdsRaised* raised, hipStream_t 
     const size_t lds = scr_lds_bytes<P, SHARED, W>(a.K);
     if (lds > kScrLdsMax || a.chunk % sig != 0) return hipErrorInvalidValue;
     const void* fn = reinterpret_cast<const void*>(&energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>);
-    if (hipError_t e = raised->ensure(fn, kScrLdsMax); e != hipSuccess) return e;
+    if (hipError_t e = raised->ensure(fn, kScrLdsMax); e != hipSuccess || a.load_only) return e;
     hipLaunchKernelGGL((energy_screen_kernel<P, S, SX, ARITH, SHARED, W, CHOICE>), dim3((unsigned)((a.m + sig - 1) / sig), (unsigned)a.rows),
                        dim3(64 * waves), lds, st, a);
     return hipGetLastError();

@@ -22,6 +22,7 @@ struct ScrArgs {
     int turn = 0;
     // ... from the second one on: the last grouping, and the blocks whose last update was by Newton-Schulz (negative)
     const int32_t *perm = nullptr, *offsets = nullptr, *sweeps = nullptr;
+    bool load_only = false;    // nothing is launched, but the kernel is there afterwards
     // ... in the first one, and in sbo_code: per block |Q Q^T - I|_F^2 in two parts
     const float2* dev = nullptr;
     // workgroups of 64 signals, split: rows of workgroups that share out the blocks, and what they exchange (choice_split)
