@@ -367,11 +367,11 @@ constexpr bool home_applies(int s0) {
 // Without a grouping to start from (sbo_code, the first iteration; p = 64): the bounds of all blocks first.  That of a signal's
 // own block is hardly below |y|^2, because half of its large coefficients is not among the atoms looked at, so the block of the
 // largest bound is taken as its home, and only there is it screened in full, in tiles of 32 signals of one block.  That the
-// dictionary consists of orthobases, dict_parts_kernel has measured: |Q Q^T - I|_F at most kOrthobase.  After 4 blocks of every
-// 64 a workgroup with far fewer signals that have found their block (a bound above kGuessFound) than these blocks would get on
-// average goes over to screening everything in full: signals that no block represents cost 3 to 8 % more for the attempt.
+// dictionary consists of orthobases, dict_parts_kernel has measured: |Q Q^T - I|_F at most kOrthobase.  After 16 K / signals
+// blocks a workgroup with far fewer signals that have found their block (a bound above kGuessFound) than these blocks would get on
+// average goes over to screening everything in full: signals that no block represents cost 1 to 5 % more for the attempt (workgroups of 256 up to 8).
 // 100003 signals, K = 64, s0 = 5: 69 -> 52 us, the call 107.5 -> 88.0; 500000 signals, K = 128, s0 = 6: call 645 -> 468; random signals,
-// K = 32, 262144 of them: 167 -> 176.
+// K = 32, 262144 of them: call 169 -> 173.
 constexpr float kOrthobase = 1e-4f;
 constexpr float kGuessFound = 0.99f;
 constexpr int kGuessFew = 4;                   // a quarter of that average, less one
@@ -914,17 +914,20 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 __syncthreads();
                 project(acc0, 0);
                 __syncthreads();
+                // Far too few signals have found their block among those so far, whose bound is hardly below one: in full
+                auto found_few = [&](int s) {
+                    if (!GUESS || s != (8 * K - 1) / SIG) return false;            // uniform
+                    const int found = __popcll(__ballot(bestE >= kGuessFound && y2_own > 0.f));
+                    if (lane == 0 && found != 0) atomicAdd(&n_weak[1], found);
+                    __syncthreads();
+                    return (n_weak[1] + 1) * kGuessFew * K < (int)min((int64_t)SIG, m - wg0) * 2 * (s + 1);
+                };
                 for (int s = 0; s < n_step && halves; s += 2) {
                     home_step(acc0, acc1, s, std::false_type{});
-                    if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});     // uniform
-                    // n blocks: far too few signals have found theirs, whose bound is hardly below one: in full
-                    if (GUESS && s == 2 * ((K - 1) / 64)) {            // uniform
-                        const int found = __popcll(__ballot(bestE >= kGuessFound && y2_own > 0.f));
-                        if (lane == 0 && found != 0) atomicAdd(&n_weak[1], found);
-                        __syncthreads();
-                        halves = (n_weak[1] + 1) * kGuessFew * K >= (int)min((int64_t)SIG, m - wg0) * 2 * (s + 2);
-                        __syncthreads();
-                    }
+                    halves = !found_few(s);
+                    if (!halves) break;        // uniform
+                    if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});         // uniform
+                    halves = !found_few(s + 1);
                     if (!GUESS && (s & 14) == 14) {        // too many to be resolved one by one: all over again, in full
                         if (n_left != 0) atomicAdd(&n_weak[1], n_left);
                         n_left = 0;
