@@ -30,11 +30,12 @@ constexpr int kPairs = 4;                      // signal pairs per step of a wav
 constexpr int kDepth = 6;                      // steps whose operands are in flight per wavefront
 
 // GRAM: the A operand is y itself (S0 is not used): the piece's share of sum_i y_i y_i^T.
-template <int P, int S0, bool GRAM>
+// LISTS: the signals have not been grouped, every workgroup lists those of its own piece (ChunkLists).
+template <int P, int S0, bool GRAM, bool LISTS>
 __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
     const float* __restrict__ Y, int K, int piece, const int32_t* __restrict__ offsets,
     const int32_t* __restrict__ perm, const int32_t* __restrict__ supp,
-    const float* __restrict__ coef, float* __restrict__ partial) {
+    const float* __restrict__ coef, float* __restrict__ partial, ChunkLists lists) {
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-wide tiles per side of P_j
     constexpr int PP = P * P;
     constexpr int NW = kTallWaves;
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
     constexpr int EPS = S0 <= 1 ? 1 : S0 <= 2 ? 2 : S0 <= 4 ? 4 : S0 <= 8 ? 8 : 16;
     constexpr int SPI = 64 / EPS;              // signals covered by one such fetch
     constexpr int NI = (SPS + SPI - 1) / SPI;  // fetches per step
-    // ids[kMaxPiece] | buf: xd[NW][SPS][64] while the
+    // ids[kMaxPiece] | buf: the table of `lists`, then xd[NW][SPS][64] while the
     // piece is walked, then [NW/2][ACC_F4] 16-byte units while the wavefronts are summed
     extern __shared__ __attribute__((aligned(16))) int lds[];
     int* ids = lds;
@@ -54,13 +55,24 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, n = lane & 31;
 
-    for (int e = tid; e < NW * SPS * 64; e += 64 * NW) buf[e] = 0.f;
     const int id = blockIdx.x;
-    const Piece pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    Piece pc;
+    if constexpr (LISTS) {
+        int* table = reinterpret_cast<int*>(buf);
+        lists.load<NW>(K, table);
+        if (id == 0 && wave == 0) lists.leave<NW>(K, table);
+        pc = find_piece([&](int j) { return lists.count_of<NW>(K, table, j); }, K, piece, id);
+        if (pc.j >= 0) lists.collect(K, table, pc, ids, wave, NW);
+        __syncthreads();
+    } else {
+        pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);
+    }
     if (pc.j < 0) return;                      // uniform over the workgroup
     const int pos0 = pc.before + pc.rank, cnt = pc.count;          // <= kMaxPiece (launcher)
 
-    for (int q = tid; q < cnt; q += 64 * NW) ids[q] = perm[pos0 + q];
+    for (int e = tid; e < NW * SPS * 64; e += 64 * NW) buf[e] = 0.f;
+    if constexpr (!LISTS)
+        for (int q = tid; q < cnt; q += 64 * NW) ids[q] = perm[pos0 + q];
     __syncthreads();
 
     f32x16 acc[MT][MT];
@@ -559,19 +571,32 @@ __global__ __launch_bounds__(256) void accum_reduce_kernel(int K, int piece,
 
 template <int P, int S0>
 hipError_t launch_ps(int K, const float* Y, int64_t m, const int32_t* supp, const float* coef,
-                     const Workspace& ws, float* M, hipStream_t st) {
+                     const Workspace& ws, float* M, hipStream_t st, const int32_t* blk) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
     const int piece = accum_piece(m, K);
     const int max_pieces = accum_max_pieces(m, K);
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
-    const size_t lds1 = (kMaxPiece + (walk > xch ? walk : xch)) * 4;
-    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, S0, false>),
+    size_t lds1 = (kMaxPiece + (walk > xch ? walk : xch)) * 4;
+    if (blk != nullptr) {
+        const GroupGeom g = group_geom(m);
+        const size_t table = (kMaxPiece + (size_t)ChunkLists::table_ints(kTallWaves, K, g.n_chunks)) * 4;
+        if (table > lds1) lds1 = table;
+        if (g.chunk != kListChunk || lds1 > 144 * 1024 || M != nullptr) return hipErrorInvalidValue;
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, S0, false, true>), 144 * 1024);
+            e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL((accum_piece_kernel<P, S0, false, true>), dim3(max_pieces), dim3(64 * kTallWaves), lds1, st,
+                           Y, K, piece, nullptr, nullptr, supp, coef, ws.partial,
+                           ChunkLists{blk, (int)m, g.n_chunks, ws.chunk_count, ws.counts, ws.offsets});
+        return hipGetLastError();
+    }
+    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, S0, false, false>),
                                          144 * 1024);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((accum_piece_kernel<P, S0, false>), dim3(max_pieces), dim3(64 * kTallWaves), lds1, st,
-                       Y, K, piece, ws.offsets, ws.perm, supp, coef, ws.partial);
+    hipLaunchKernelGGL((accum_piece_kernel<P, S0, false, false>), dim3(max_pieces), dim3(64 * kTallWaves), lds1, st,
+                       Y, K, piece, ws.offsets, ws.perm, supp, coef, ws.partial, ChunkLists{});
     if (M == nullptr) return hipGetLastError();
     const size_t lds2 = (K + 1 + 16) * sizeof(int);
     hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256), lds2, st,
@@ -619,10 +644,10 @@ hipError_t launch_wide(int K, int s0, const float* Y, int64_t m, const int32_t* 
 
 template <int P>
 hipError_t launch_p(int K, int s0, const float* Y, int64_t m, const int32_t* supp,
-                    const float* coef, const Workspace& ws, float* M, hipStream_t st) {
+                    const float* coef, const Workspace& ws, float* M, hipStream_t st, const int32_t* blk) {
     switch (s0) {
 #define SBO_CASE(N) \
-    case N: return launch_ps<P, N>(K, Y, m, supp, coef, ws, M, st);
+    case N: return launch_ps<P, N>(K, Y, m, supp, coef, ws, M, st, blk);
         SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7)
         SBO_CASE(8) SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13)
         SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
@@ -641,12 +666,12 @@ hipError_t launch_gram_p(int K, const float* Y, int64_t n, const Workspace& ws, 
     const size_t walk = (size_t)kTallWaves * 2 * kPairs * 64;
     const size_t xch = (size_t)(kTallWaves / 2) * MT * MT * 16 * 64;
     const size_t lds1 = (kMaxPiece + (walk > xch ? walk : xch)) * 4;
-    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, 1, true>),
+    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_piece_kernel<P, 1, true, false>),
                                          144 * 1024);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((accum_piece_kernel<P, 1, true>), dim3(max_pieces), dim3(64 * kTallWaves), lds1, st,
-                       Y, K, piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial);
+    hipLaunchKernelGGL((accum_piece_kernel<P, 1, true, false>), dim3(max_pieces), dim3(64 * kTallWaves), lds1, st,
+                       Y, K, piece, ws.offsets, ws.perm, nullptr, nullptr, ws.partial, ChunkLists{});
     hipLaunchKernelGGL((accum_reduce_kernel<P>), dim3(K, (P * P + 255) / 256), dim3(256),
                        (K + 1 + 16) * sizeof(int), st, K, piece, ws.offsets, ws.partial, G, nullptr,
                        (int64_t)0, nullptr, nullptr, nullptr, 0);
@@ -702,12 +727,12 @@ hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, flo
 }
 
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
-                             const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos) {
-    if (by_pos && p != 256) return hipErrorInvalidValue;
+                             const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos, const int32_t* blk) {
+    if ((by_pos && p != 256) || (blk != nullptr && !lists_in_update(p, K, m))) return hipErrorInvalidValue;
     switch (p) {
-        case 16: return launch_p<16>(K, s0, Y, m, supp, coef, ws, M, st);
-        case 32: return launch_p<32>(K, s0, Y, m, supp, coef, ws, M, st);
-        case 64: return launch_p<64>(K, s0, Y, m, supp, coef, ws, M, st);
+        case 16: return launch_p<16>(K, s0, Y, m, supp, coef, ws, M, st, blk);
+        case 32: return launch_p<32>(K, s0, Y, m, supp, coef, ws, M, st, blk);
+        case 64: return launch_p<64>(K, s0, Y, m, supp, coef, ws, M, st, blk);
         case 256: return launch_wide(K, s0, Y, m, supp, coef, ws, M, ws.parts_accum, by_pos, st);
         default: return hipErrorInvalidValue;
     }

@@ -189,14 +189,22 @@ hipError_t launch_sort(int K, const int32_t* blk, int64_t m, const GroupGeom& g,
 
 // have_hist: ws.chunk_count already holds the per-chunk histograms (written by the coding
 // kernel); otherwise they are computed from blk here.
+hipError_t launch_group_hist(int K, const int32_t* blk, int64_t m, const Workspace& ws, hipStream_t st) {
+    if (K > kMaxK) return hipErrorInvalidValue;
+    const GroupGeom g = group_geom(m);
+    hipLaunchKernelGGL(group_hist_kernel, dim3((unsigned)((g.n_chunks + 3) / 4)), dim3(256), 4 * K * sizeof(int), st, blk,
+                       (int)m, K, g.chunk, g.n_chunks, ws.chunk_count);
+    return hipGetLastError();
+}
+
 hipError_t launch_group(int K, const int32_t* blk, int64_t m, const Workspace& ws, bool have_hist,
                         hipStream_t st) {
     if (K > kMaxK) return hipErrorInvalidValue;
     const GroupGeom g = group_geom(m);
-    const unsigned wgs = (unsigned)((g.n_chunks + 3) / 4);
-    if (!have_hist)
-        hipLaunchKernelGGL(group_hist_kernel, dim3(wgs), dim3(256), 4 * K * sizeof(int), st, blk,
-                           (int)m, K, g.chunk, g.n_chunks, ws.chunk_count);
+    if (!have_hist) {
+        hipError_t e = launch_group_hist(K, blk, m, ws, st);
+        if (e != hipSuccess) return e;
+    }
     return launch_sort(K, blk, m, g, ws.chunk_count, ws.chunk_base, ws.group_done, ws.counts, ws.offsets, ws.perm, st);
 }
 

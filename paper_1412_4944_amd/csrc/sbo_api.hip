@@ -379,9 +379,21 @@ int sbo_update(sbo_ctx* c, const float* Y, int64_t m, const int32_t* blk, const 
     if (rc) return rc;
     if (!Y || !blk || !supp || !coef || !D) return SBO_EINVAL;
     c->n_spans = 0;
-    rc = run_group(c, blk, m);
-    if (rc) return rc;
-    rc = run_update_grouped(c, Y, m, supp, coef, D);
+    if (lists_in_update(c->p, c->K, m) && c->svd_method != SBO_SVD_JACOBI) {
+        {
+            StageTimer t(c, SBO_STAGE_GROUP);
+            SBO_HIP(launch_group_hist(c->K, blk, m, c->ws, c->stream));
+        }
+        {
+            StageTimer t(c, SBO_STAGE_ACCUM);
+            SBO_HIP(launch_accumulate(c->p, c->K, c->s0, Y, m, supp, coef, c->ws, nullptr, c->stream, false, blk));
+        }
+        rc = run_polar_pieces(c, m, D, 0, nullptr, nullptr);
+    } else {
+        rc = run_group(c, blk, m);
+        if (rc) return rc;
+        rc = run_update_grouped(c, Y, m, supp, coef, D);
+    }
     if (rc) return rc;
     if (counts)
         SBO_HIP(hipMemcpyAsync(counts, c->ws.counts, (size_t)c->K * 4, hipMemcpyDeviceToDevice,

@@ -231,6 +231,11 @@ inline bool lists_in_round(int p, int K, int64_t m) {
 inline bool lists_in_select(int p, int K, int64_t m) {
     return m > 2048 && m <= (p <= 64 ? 131072 : 65536) && K <= 128 && (int64_t)((m + 511) / 512 + 8) * K <= 9216;
 }
+// sbo_update, which calls the histogram kernel (scatter launch / lists, us): p = 64, K = 4 2100 signals 31.5 / 27.5, 131000 54.1 / 50.3;
+// K = 32 32000 36.9 / 30.5, 131000 49.2 / 47.5; K = 64 65537 42.9 / 41.8; p = 16, K = 32 32000 24.4 / 18.1; K = 128 32000 27.8 / 26.4.
+inline bool lists_in_update(int p, int K, int64_t m) {
+    return p <= 64 && K <= 128 && m <= 131072 && (int64_t)((m + 511) / 512 + 8) * K <= 9216;
+}
 inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
     return group_in_select(p, K, m) && K <= kDirectMaxK && K * m <= kDirectMaxEnergies && screen_applies(p, K, s0, arith);
@@ -271,6 +276,8 @@ hipError_t launch_energy_direct(int p, int K, int s0, int arith, const float* Y,
 
 hipError_t launch_group(int K, const int32_t* blk, int64_t m, const Workspace& ws, bool have_hist,
                         hipStream_t st);
+// Its first launch alone: the chunk histograms.
+hipError_t launch_group_hist(int K, const int32_t* blk, int64_t m, const Workspace& ws, hipStream_t st);
 // The grouping with its scratch in a static device array (no workspace, no allocation).
 constexpr int kGroupStaticMaxK = 128;
 constexpr int64_t kGroupStaticMaxM = (int64_t)1 << 20;
@@ -293,9 +300,11 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
                          bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false,
                          bool lists = false);
 
-// M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.
+// M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.  blk (M == nullptr, where
+// lists_in_update says so): as for launch_select_accum.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
-                             const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos = false);
+                             const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos = false,
+                            const int32_t* blk = nullptr);
 
 // Fused select + per-piece accumulation (p <= 64); the piece results land in ws.partial
 // and launch_accum_reduce sums them into M.  blk: nullptr, or the choices of signals that have not been grouped, with their

@@ -498,6 +498,30 @@ def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m
         assert all(np.array_equal(a, b.cpu().numpy()) for a, b in zip(again, out))
 
 
+@pytest.mark.parametrize("p,K,s0,m", [(16, 4, 3, 513), (16, 60, 2, 70001), (32, 16, 4, 131072), (64, 5, 8, 1), (64, 33, 8, 65537),
+                                      (64, 128, 3, 32768)])
+def test_update_lists_the_signals_of_a_piece_from_the_histograms(p, K, s0, m):
+    """sbo_update without a grouping: blocks that nobody takes, one that takes half of the signals, choices that are no block
+    (dropped).  The same bits as by the calls that group first."""
+    rng = np.random.default_rng(m + K)
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    blk = np.where(rng.random(m) < 0.5, 1, rng.integers(-1, K, m)).astype(np.int32)
+    blk[blk == 2] = 3
+    supp = np.sort(rng.random((m, p), dtype=np.float32).argpartition(s0, axis=1)[:, :s0], axis=1).astype(np.int32)
+    coef = rng.standard_normal((m, s0)).astype(np.float32)
+    D = np.linalg.qr(rng.standard_normal((K, p, p)))[0].astype(np.float32)
+    with Sbo(p, K, s0, m) as g:
+        got, counts = g.update(Y, blk, supp, coef, D)
+        again, _ = g.update(Y, blk, supp, coef, D)
+        c, _offsets, _perm = g.group(blk)
+        M = g.accumulate(Y, blk, supp, coef)
+        want = g.polar(M, D, c)
+    assert np.array_equal(counts, np.bincount(blk[blk >= 0], minlength=K)) and np.array_equal(counts, c)
+    assert np.array_equal(got, again)
+    # the same pieces, summed in the same order: the same bits
+    assert np.array_equal(got, want), np.abs(got - want).max()
+
+
 @pytest.mark.parametrize("K,s0,m,kind,arith", [(32, 8, 65537, "planted", "bf16x3"), (16, 3, 70001, "planted", "f32"),
                                                (31, 6, 90001, "odd signals", "f16x2"), (100, 5, 53001, "close", "f16x2"),
                                                (64, 5, 131149, "close", "bf16x3"), (127, 8, 100003, "planted", "f16x2"),
