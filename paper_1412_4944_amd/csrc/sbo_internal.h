@@ -218,15 +218,19 @@ constexpr int kDirectMaxK = 64;
 constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than group_in_select allows)
 // Which iterations leave the grouping to the select + accumulate kernel, and which calls of sbo_code to the select kernel, whose
 // workgroups list the signals of their own piece (ChunkLists in device_utils.h).  The histograms are read by every workgroup,
-// and a piece of a block comes from K times as many signals.  sbo_iterate, an iteration: 16384 signals, K = 16, p = 64 47.5 us
-// with a grouping launch, 41 (with the shorter search for a piece); beyond 4096 entries a launch costs less than reading them
-// in every workgroup, by the figures of sbo_code below and a select+accumulate kernel with one workgroup to a CU.
+// and a piece of a block comes from K times as many signals.  sbo_iterate, an iteration, with a grouping launch / lists (us):
+// p = 64, K = 16 16384 signals 47.5 / 41 (with the shorter search for a piece), 40000 61.6 / 56.6, K = 64 50000 107.2 / 106.0,
+// K = 120 32000 105.4 / 103.9; p = 32, K = 16 65537 42.5 / 38.9, K = 32 131000 56.8 / 56.8; p = 16, K = 16 40000 31.4 / 26.1, K = 32
+// 131000 41.6 / 41.7, K = 64 65537 43.1 / 42.5: even at 8500 to 8800 entries (K > 128: 4096, where it was
+// measured; sbo_code with K = 200 loses beyond).  p = 64: as long as no iteration takes its signals in
+// the order of the grouping (home blocks: workgroups of more than 64 signals).
 // sbo_code, with a grouping launch / lists (us): p = 64, K = 16 2100 signals 26.0 / 21.3, 65537 50.3 / 44.7, 131000 62.4 / 59.0;
 // K = 64 65537 104.2 / 99.0, 100003 (p = 32) 68.9 / 74.5; K = 128 12000 47.4 / 46.4, 32000 81.8 / 78.0, 40000 (p = 32) 49.4 / 49.8;
 // K = 200 12000 59.9 / 63.6; p = 256, K = 16 5000 61.3 / 55.4, 65537 271.5 / 268.8, 100003 336.8 / 341.2.  Sets of 1025 to 2048
 // signals are grouped by a launch, as the stage times that callers read of them say (sbo_stage_ms).
 inline bool lists_in_round(int p, int K, int64_t m) {
-    return p <= 64 && m <= 32768 && (int64_t)((m + 511) / 512 + 8) * K <= 4096;
+    return p <= 64 && m <= 131072 && (p < 64 || screen_shared(m, true)) &&
+           (int64_t)((m + 511) / 512 + 8) * K <= (K <= 128 ? 9216 : 4096);
 }
 inline bool lists_in_select(int p, int K, int64_t m) {
     return m > 2048 && m <= (p <= 64 ? 131072 : 65536) && K <= 128 && (int64_t)((m + 511) / 512 + 8) * K <= 9216;

@@ -336,10 +336,12 @@ def test_code_lists_the_signals_of_a_tile_from_the_histograms(p, K, m, s0, arith
 
 @pytest.mark.parametrize("p,K,m,s0", [(64, 16, 16384, 6), (64, 56, 32768, 8), (64, 57, 32768, 8), (64, 3, 32769, 5), (64, 2, 32767, 4),
                                       (32, 24, 511, 4), (32, 7, 513, 3), (32, 70, 20001, 4), (16, 4, 1024, 3), (16, 256, 4096, 2),
-                                      (16, 257, 4000, 2), (16, 400, 1000, 2), (64, 1, 1, 8), (16, 5, 33, 3)])
+                                      (16, 257, 4000, 2), (16, 400, 1000, 2), (64, 1, 1, 8), (16, 5, 33, 3),
+                                      (64, 32, 52428, 6), (64, 32, 52429, 6), (64, 128, 32768, 16), (32, 34, 131072, 4), (32, 34, 131073, 4),
+                                      (16, 128, 32768, 3), (16, 129, 32767, 2), (16, 241, 4500, 2)])
 @pytest.mark.parametrize("skewed", [False, True], ids=["even", "skewed"])
 def test_iterate_lists_the_signals_of_a_piece_from_the_histograms(p, K, m, s0, skewed):
-    """Small sets (up to 32768 signals and 4096 histogram entries) are not grouped in sbo_iterate.  A round on the blocks that it chose,
+    """Sets with few histogram entries, whose block choice does not need the lists, are not grouped in sbo_iterate.  A round on the blocks that it chose,
     which groups them, has the same sums in the same order, so every bit is the same; and the histograms are left zero."""
     pr = synth.generate(synth.custom(f"lists_p{p}_K{K}", p=p, K=K, m=m, s0=s0, snr_db=20.0, zipf_s=2.0 if skewed else None))
     with Sbo(p, K, s0, m) as g:
