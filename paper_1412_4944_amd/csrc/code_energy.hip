@@ -950,6 +950,7 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
     a.chunk_count = chunk_count;
     a.chunk = group_geom(m).chunk;
     a.split_E = ws.split_E;
+    a.split_room = ws.split_room;
     a.split_x = ws.split_x;
     a.split_done = ws.split_done;
     if (turn >= 0 && (p == 64 ? home_takes_64(a) : p == 256 && home_takes_256(a))) {

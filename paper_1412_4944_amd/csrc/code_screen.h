@@ -1344,6 +1344,7 @@ hipError_t launch_a(const ScrArgs& a, LdsRaised* raised, hipStream_t st) {
         const int units = P == 64 || P > 64 ? a.K : (a.K * P + 31) / 32;
         ScrArgs b = a;
         b.rows = choice_split(P, a.K, a.m);
+        if (b.rows > 1 && (int64_t)((a.m + 63) / 64) * a.K > a.split_room) return hipErrorInvalidValue;
         return launch_w<P, S, SX, ARITH, true, kScrWaves, kFull>(b, units < kScrWaves ? units : kScrWaves, raised, st);
     }
     if constexpr (P <= 64)

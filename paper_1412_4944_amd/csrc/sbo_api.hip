@@ -47,7 +47,9 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     const size_t direct = m_max < kDirectMaxEnergies / K ? (size_t)K * m_max : (size_t)kDirectMaxEnergies;
     w.part_E = (float*)take((direct > kEnergySplitRows * split_m ? direct : kEnergySplitRows * split_m) * 4);
     w.part_j = (int32_t*)take((size_t)kEnergySplitRows * split_m * 4);
-    w.split_E = (unsigned*)take(K <= kSplitMaxK ? (size_t)((m_max < kSplitMaxSignals ? m_max : kSplitMaxSignals) + 63) / 64 * K * 128 : 0);
+    // (a context for more blocks than are ever split may be used with fewer: sbo_set_blocks, sbo_learn)
+    w.split_room = (int)(((m_max < kSplitMaxSignals ? m_max : kSplitMaxSignals) + 63) / 64) * (K < kSplitMaxK ? K : kSplitMaxK);
+    w.split_E = (unsigned*)take((size_t)w.split_room * 128);
     w.split_x = (unsigned*)take((size_t)kNumCU * 4 * 64 * 4);
     w.split_done = (int*)take((size_t)kNumCU / 2 * 4);
     // The eigenvectors of a Gram matrix are computed when the pieces of that matrix have been summed: same memory.

@@ -96,6 +96,7 @@ struct Workspace {
                            // the energies of a small set, [K][m] (at most kDirectMaxEnergies)
     int32_t* part_j;       // same shape: its block
     unsigned* split_E;     // choice_split: [ceil(m / 64)][K][64 signals] 16 bits, the energies of all blocks
+    int split_room;        // ... ceil(m / 64) * K at most
     unsigned* split_x;     // ... [kNumCU][4][64] what a workgroup found
     int* split_done;       // ... [kNumCU / 2] workgroups of a column that have finished (0 between launches)
     // accumulation

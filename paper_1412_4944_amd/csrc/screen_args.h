@@ -28,6 +28,7 @@ struct ScrArgs {
     // workgroups of 64 signals, split: rows of workgroups that share out the blocks, and what they exchange (choice_split)
     int rows = 1;
     unsigned *split_E = nullptr, *split_x = nullptr;
+    int split_room = 0;
     int* split_done = nullptr;
     // energy_direct_kernel only
     const float* D = nullptr;

@@ -47,6 +47,14 @@ def test_workspace_of_an_orthobase(p):
     assert grown <= 512 * (22 * p * p + 2 * 4 * 1025 + p + 64)
 
 
+@pytest.mark.parametrize("p", [64, 256])
+def test_workspace_grows_with_the_orthobases(p):
+    """A context may be used with fewer orthobases than it was made for (sbo_set_blocks, sbo_learn), so it has the memory of
+    every call that fewer orthobases allow: more of them never make it smaller."""
+    sizes = [sbo.sbo_workspace_bytes(p, K, 4, 8192) for K in (64, 128, 255, 256, 257, 300, 512, 1024)]
+    assert sizes == sorted(sizes)
+
+
 def test_strerror_and_null_context():
     assert sbo.sbo_strerror(0) == "success"
     assert "invalid" in sbo.sbo_strerror(-1)

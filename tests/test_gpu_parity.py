@@ -555,6 +555,40 @@ def test_code_of_few_signals_shares_out_the_blocks(p, K, s0, kind, arith):
                 assert np.array_equal(a[:m], b), (m, name, int((a[:m] != b).sum()))
 
 
+@pytest.mark.parametrize("p,K_cap,K,s0", [(64, 257, 64, 6), (64, 512, 256, 4), (256, 260, 16, 12), (256, 300, 8, 5)])
+def test_contexts_for_more_blocks_than_are_in_use_share_them_out(p, K_cap, K, s0):
+    """A context made for more orthobases than the split choice takes, used with fewer: bit for bit what a context made for
+    that many gives, also in the calls that follow."""
+    Y, D = _home_case(p, K, s0, 8192, "planted")
+    with Sbo(p, K_cap, s0, len(Y)) as big, Sbo(p, K, s0, len(Y)) as small:
+        sbo.sbo_set_blocks(big.ctx, K)
+        for m in (5041, 2111, 8192, 5041):
+            print(f"case p={p} K={K} of {K_cap} m={m}", flush=True)
+            for a, b in zip(big.code(Y[:m], D), small.code(Y[:m], D)):
+                assert np.array_equal(a, b)
+        for a, b in zip(big.iterate(Y[:5041], D, 3), small.iterate(Y[:5041], D, 3)):
+            assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("p,K_cap,K0,K_max", [(64, 300, 32, 34), (256, 300, 8, 9)])
+def test_learn_on_a_context_for_more_blocks_than_it_ends_with(p, K_cap, K0, K_max):
+    """Algorithm 2 with a number of orthobases whose block choice is split, on a context with room for many more."""
+    m, s0, P0, W = 4097, 4, 3 * p, 4 * p
+    Y, _D = _home_case(p, K_max, s0, m, "planted")
+    rng = np.random.default_rng(p)
+    sets = np.stack([np.sort(rng.permutation(m)[:P0]) for _ in range(K0)]).astype(np.int32)
+    got = []
+    for cap in (K_cap, K_max):
+        with Sbo(p, cap, s0, m) as g:
+            D = g.torch.zeros((K_max, p, p), dtype=g.torch.float32, device=g.dev)
+            out = g.outputs(m)
+            k, history = sbo.sbo_learn(g.ctx, g.dev_f32(Y), D, g.dev_i32(sets), 2, W, K_max, 0.0, *out)
+            g.torch.cuda.synchronize()
+            got.append([np.array([k]), np.array(history), D.cpu().numpy()] + [a.cpu().numpy() for a in out])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("name,kw", [("tiny", dict()), ("patch8", dict(m=5000)), ("p32", dict(p=32, K=6, m=3000, s0=4)),
                                      ("p64_s5", dict(p=64, K=7, m=2100, s0=5)),
                                      ("p256", dict(p=256, K=2, m=1500, s0=12, snr_db=25.0))])
