@@ -62,7 +62,7 @@ __global__ __launch_bounds__(64 * kTallWaves) void accum_piece_kernel(
         lists.load<NW>(K, table);
         if (id == 0 && wave == 0) lists.leave<NW>(K, table);
         pc = find_piece([&](int j) { return lists.count_of<NW>(K, table, j); }, K, piece, id);
-        if (pc.j >= 0) lists.collect(K, table, pc, ids, wave, NW);
+        if (pc.j >= 0) lists.collect<NW>(K, table, pc, ids, wave);
         __syncthreads();
     } else {
         pc = find_piece([&](int j) { return offsets[j + 1] - offsets[j]; }, K, piece, id);

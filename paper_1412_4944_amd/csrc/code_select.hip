@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ Y
         else return offsets[j + 1] - offsets[j];
     }, K, 32, (int)blockIdx.x * 4 + wave);
     if constexpr (SRC == kLists) {
-        if (pc.j >= 0) lists.collect(K, lds, pc, ids, 0, 1);
+        if (pc.j >= 0) lists.collect<1>(K, lds, pc, ids, 0);
         __syncthreads();                       // the table is dead
     }
     if (pc.j < 0) return;                      // no workgroup barrier below this line
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * NW, 4) void select_split_kernel(const float* _
                                 (int)blockIdx.x);
     if (pc.j < 0) return;                      // uniform over the workgroup
     if constexpr (LISTS) {
-        lists.collect(K, lds, pc, ids, wave, NW);
+        lists.collect<NW>(K, lds, pc, ids, wave);
         __syncthreads();                       // the table is dead
     }
     const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count, n_tiles = (cnt + 31) >> 5;
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
     const Piece pc = find_piece([&](int j) { return LISTS ? lists.count_of<NW>(K, table, j) : offsets[j + 1] - offsets[j]; }, K, 32, id);
     if (pc.j < 0) return;                      // uniform over the workgroup
     if constexpr (LISTS) {
-        lists.collect(K, table, pc, ids, wave, NW);
+        lists.collect<NW>(K, table, pc, ids, wave);
         __syncthreads();                       // the table is dead
     }
     const int j = pc.j, pos0 = pc.before + pc.rank, cnt = pc.count;

@@ -292,6 +292,8 @@ __device__ __forceinline__ Piece find_piece(F count_of, int K, int piece, int id
 // reads all histograms, and the choices of the chunks that its piece comes from.  Another launch sets the histograms to zero
 // (a count of the workgroups that have read them costs more than all the rest: 144 of them, one after the other, 4 us).
 constexpr int kListChunk = 512;                // signals of a chunk
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // (the caller's choices: any alignment of an int)
 struct ChunkLists {
     const int32_t* blk;
     int m, n_chunks;
@@ -344,35 +346,72 @@ struct ChunkLists {
         }
         if (lane == 0) offsets[0] = 0;
     }
-    // The signals of a piece, in order -> ids[pc.count] (LDS): those of every `step`-th chunk that has some, from `first` on.
-    // One wavefront; `step` of them share out a piece.
-    __device__ __forceinline__ void collect(int K, const int* table, const Piece& pc, int* ids, int first, int step) const {
-        constexpr int A = kListChunk / 64;
+    // The signals of a piece, in order -> ids[pc.count] (LDS): those of the chunks c with c % STEP == first, four of them on
+    // their way at a time.  One wavefront; STEP of them share out a piece.  A piece of a rare block comes from as many chunks as it
+    // has signals, so that what a chunk costs decides: a trip to memory, eight loads and eight ballots each made it 0.4 us (sbo_code,
+    // 131000 signals, all but 900 of them in one of four blocks, p = 32: 31 us by a grouping launch, 61 so, 45 as it is; loads
+    // of eight neighbours by words 62: the lines that an instruction touches).
+    template <int STEP>
+    __device__ __forceinline__ void collect(int K, const int* table, const Piece& pc, int* ids, int first) const {
+        constexpr int H = kListChunk / 256, G = 4;         // a lane's four neighbours at a time
+        static_assert(64 % STEP == 0, "c0 is a multiple of STEP");
+        const unsigned long long every = STEP == 1 ? ~0ull : ~0ull / ((1ull << (STEP & 63)) - 1) << first;
         const int lane = threadIdx.x & 63;
-        int front = 0, k = 0;                  // signals of the chunks before; chunks so far
+        int front = 0;                         // signals of the chunks before
         for (int c0 = 0; c0 < n_chunks && front < pc.rank + pc.count; c0 += 64) {          // uniform
             const int n = c0 + lane < n_chunks ? table[(c0 + lane) * K + pc.j] : 0, upto = front + wave_scan(n);
-            unsigned long long mask = __ballot(n > 0 && upto - n < pc.rank + pc.count && upto > pc.rank);
-            for (; mask != 0ull; ++k, mask &= mask - 1) {  // uniform
-                if (k % step != first) continue;
-                const int l = __builtin_ctzll(mask), i0 = (c0 + l) * kListChunk + lane;
-                int key[A];                    // on their way at once (a condition would make as many trips of it)
+            unsigned long long mask = __ballot(n > 0 && upto - n < pc.rank + pc.count && upto > pc.rank) & every;
+            while (mask != 0ull) {             // uniform
+                i32x4 key[G][H];
+                int i0[G], at[G];              // at: of the next one, in the piece
 #pragma unroll
-                for (int u = 0; u < A; ++u) key[u] = blk[min(i0 + u * 64, m - 1)];
-                int at = __builtin_amdgcn_readlane(upto - n, l) - pc.rank; // of the next one, in the piece
+                for (int q = 0; q < G; ++q) {
+                    i0[q] = -1;
+                    if (mask == 0ull) continue;            // uniform
+                    const int l = __builtin_ctzll(mask);
+                    mask &= mask - 1;
+                    i0[q] = (c0 + l) * kListChunk;
+                    at[q] = __builtin_amdgcn_readlane(upto - n, l) - pc.rank;
+                    const int own = i0[q] + lane * 4;
+                    if (i0[q] + kListChunk <= m) {         // uniform
 #pragma unroll
-                for (int u = 0; u < A; ++u) {
-                    const bool here = key[u] == pc.j && i0 + u * 64 < m;
-                    const unsigned long long mine = __ballot(here);
-                    const int to = at + __popcll(mine & ((1ull << lane) - 1ull));
-                    if (here && to >= 0 && to < pc.count) ids[to] = i0 + u * 64;
-                    at += __popcll(mine);
+                        for (int u = 0; u < H; ++u) key[q][u] = *reinterpret_cast<const i32x4_any*>(blk + own + u * 256);
+                    } else {                               // the last chunk
+#pragma unroll
+                        for (int u = 0; u < H; ++u)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const int i = own + u * 256 + e, k = blk[min(i, m - 1)];
+                                key[q][u][e] = i < m ? k : -1;
+                            }
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    if (i0[q] < 0) break;                  // uniform
+                    unsigned here[H], count = 0u;          // which of the lane's own; how many, 16 bits each
+#pragma unroll
+                    for (int u = 0; u < H; ++u) {
+                        here[u] = 0u;
+#pragma unroll
+                        for (int e = 3; e >= 0; --e) here[u] = here[u] * 2 + (key[q][u][e] == pc.j);
+                        count |= (unsigned)__popc(here[u]) << (16 * u);
+                    }
+                    const unsigned all = (unsigned)wave_scan((int)count), before = all - count;
+                    int to = at[q] + (int)(before & 0xffffu);
+#pragma unroll
+                    for (int u = 0; u < H; ++u) {
+                        for (; here[u] != 0u; ++to, here[u] &= here[u] - 1)
+                            if ((unsigned)to < (unsigned)pc.count) ids[to] = i0[q] + u * 256 + lane * 4 + __builtin_ctz(here[u]);
+                        to = at[q] + (__builtin_amdgcn_readlane((int)all, 63) & 0xffff) + (int)(before >> 16);
+                    }
                 }
             }
             front = __builtin_amdgcn_readlane(upto, 63);
         }
     }
 };
+static_assert(kListChunk == 512, "collect: two halves");
 
 // The keys of the 64 A signals from `at` on, A per lane (-1 past the end): all loads are on their way at once, where
 // a loop of one load per 64 signals waits for each (group_scatter_kernel, 512 signals per wavefront, A = 8: 1024

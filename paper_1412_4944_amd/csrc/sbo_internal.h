@@ -217,30 +217,33 @@ constexpr int choice_split(int p, int K, int64_t m) {
 // 512 not everywhere.
 constexpr int kDirectMaxK = 64;
 constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than group_in_select allows)
-// Which iterations leave the grouping to the select + accumulate kernel, and which calls of sbo_code to the select kernel, whose
-// workgroups list the signals of their own piece (ChunkLists in device_utils.h).  The histograms are read by every workgroup,
-// and a piece of a block comes from K times as many signals.  sbo_iterate, an iteration, with a grouping launch / lists (us):
-// p = 64, K = 16 16384 signals 47.5 / 41 (with the shorter search for a piece), 40000 61.6 / 56.6, K = 64 50000 107.2 / 106.0,
-// K = 120 32000 105.4 / 103.9; p = 32, K = 16 65537 42.5 / 38.9, K = 32 131000 56.8 / 56.8; p = 16, K = 16 40000 31.4 / 26.1, K = 32
-// 131000 41.6 / 41.7, K = 64 65537 43.1 / 42.5: even at 8500 to 8800 entries (K > 128: 4096, where it was
-// measured; sbo_code with K = 200 loses beyond).  p = 64: as long as no iteration takes its signals in
-// the order of the grouping (home blocks: workgroups of more than 64 signals).
-// sbo_code, with a grouping launch / lists (us): p = 64, K = 16 2100 signals 26.0 / 21.3, 65537 50.3 / 44.7, 131000 62.4 / 59.0;
-// K = 64 65537 104.2 / 99.0, 100003 (p = 32) 68.9 / 74.5; K = 128 12000 47.4 / 46.4, 32000 81.8 / 78.0, 40000 (p = 32) 49.4 / 49.8;
-// K = 200 12000 59.9 / 63.6; p = 256, K = 16 5000 61.3 / 55.4, 65537 271.5 / 268.8, 100003 336.8 / 341.2.  Sets of 1025 to 2048
-// signals are grouped by a launch, as the stage times that callers read of them say (sbo_stage_ms).
+// Which iterations leave the grouping to the select + accumulate kernel, which calls of sbo_code to the select kernel and which of
+// sbo_update (after the histogram kernel) to the accumulation, whose workgroups list the signals of their own piece (ChunkLists in
+// device_utils.h).  The histograms are read by every workgroup, a piece of a block comes from K times as many signals, and that of a
+// rare block from as many chunks as it has signals: the gain depends on how even the blocks are.  With a grouping launch / lists (us),
+// blocks taken evenly, by Zipf(1.1), by Zipf(2):
+//   sbo_code     p = 64, K = 32 32000 signals 44 / 37, 45 / 40, 45 / 44, 65000 60 / 52, 59 / 55, 62 / 60, 81000 73 / 66, 71 / 68, 71 / 71, 131000
+//                79 / 75, 81 / 81, 81 / 87; K = 16 65000 45 / 40, 45 / 41, 46 / 48, 131000 64 / 60, 64 / 63, 63 / 72; p = 16, K = 16 65000 27 / 23, 27 / 24,
+//                27 / 28, 81000 31 / 28, 31 / 29, 30 / 33, 131000 29 / 32, 29 / 33, 29 / 37; p = 32, K = 64 65000 47 / 39
+//   sbo_update   p = 64, K = 32 65000 48 / 41, 54 / 49; p = 32, K = 16 65000 29 / 25, 33 / 29, 38 / 38, 81000 31 / 28, 36 / 33, 40 / 43, 131000
+//                35 / 32, 38 / 37, 41 / 48; p = 16, K = 32 81000 30 / 25, 32 / 32, 36 / 37, 98000 32 / 28, 33 / 35, 36 / 39
+//   an iteration p = 64, K = 32 48000 77 / 71, 84 / 81; p = 32, K = 32 81000 51 / 47, 55 / 54, 63 / 64, 98000 57 / 54, 62 / 63, 68 / 71; p = 16,
+//                K = 64 65000 45 / 39
+// and where all blocks but one have 300 signals at most 5 more up to 81000, 8 to 13 at 131000: up to 160 chunks what even blocks gain is
+// at least what the most uneven ones lose.  More entries than 9216: K = 64 100003 signals (p = 32) 68.9 / 74.5 evenly, K = 128 40000 49.4 /
+// 49.8; iterations with K > 128: 4096, where it was measured (sbo_code with K = 200 loses beyond).  p = 256, sbo_code, K = 16
+// 16000 signals 94 / 87, 65000 264 / 262, 100003 337 / 341.  Iterations at p = 64: as long as none takes its signals in the
+// order of the grouping (home blocks: workgroups of more than 64 signals).  sbo_code of 1025 to 2048 signals would gain 4 to 7 us
+// (K = 4 to 128, every p), but the time of the grouping stage there is one that callers get to read.
+constexpr int64_t kListSignals = 160 * 512;
+inline bool few_entries(int K, int64_t m) { return (int64_t)((m + 511) / 512 + 8) * K <= (K <= 128 ? 9216 : 4096); }
 inline bool lists_in_round(int p, int K, int64_t m) {
-    return p <= 64 && m <= 131072 && (p < 64 || screen_shared(m, true)) &&
-           (int64_t)((m + 511) / 512 + 8) * K <= (K <= 128 ? 9216 : 4096);
+    return p <= 64 && m <= kListSignals && (p < 64 || screen_shared(m, true)) && few_entries(K, m);
 }
 inline bool lists_in_select(int p, int K, int64_t m) {
-    return m > 2048 && m <= (p <= 64 ? 131072 : 65536) && K <= 128 && (int64_t)((m + 511) / 512 + 8) * K <= 9216;
+    return m > 2048 && m <= (p <= 64 ? kListSignals : 65536) && K <= 128 && few_entries(K, m);
 }
-// sbo_update, which calls the histogram kernel (scatter launch / lists, us): p = 64, K = 4 2100 signals 31.5 / 27.5, 131000 54.1 / 50.3;
-// K = 32 32000 36.9 / 30.5, 131000 49.2 / 47.5; K = 64 65537 42.9 / 41.8; p = 16, K = 32 32000 24.4 / 18.1; K = 128 32000 27.8 / 26.4.
-inline bool lists_in_update(int p, int K, int64_t m) {
-    return p <= 64 && K <= 128 && m <= 131072 && (int64_t)((m + 511) / 512 + 8) * K <= 9216;
-}
+inline bool lists_in_update(int p, int K, int64_t m) { return p <= 64 && K <= 128 && m <= kListSignals && few_entries(K, m); }
 inline bool group_in_select(int p, int K, int64_t m) { return p <= 64 && K <= 256 && m <= 1024; }
 inline bool choose_in_select(int p, int K, int s0, int64_t m, int arith) {
     return group_in_select(p, K, m) && K <= kDirectMaxK && K * m <= kDirectMaxEnergies && screen_applies(p, K, s0, arith);

@@ -306,12 +306,13 @@ def test_iterate_groups_small_sets_in_the_select_kernel(p, K, m):
 
 
 @pytest.mark.parametrize("p,K,m,s0", [(64, 16, 2049, 6), (64, 128, 32500, 5), (64, 129, 32500, 5), (64, 64, 69632, 8), (64, 65, 69632, 8),
-                                      (64, 3, 131072, 1), (64, 3, 131073, 1), (32, 7, 32767, 4), (32, 24, 32768, 7), (16, 5, 100003, 3),
+                                      (64, 3, 131072, 1), (64, 3, 131073, 1), (64, 5, 81920, 3), (64, 5, 81921, 3), (16, 51, 81920, 2),
+                                      (32, 7, 32767, 4), (32, 24, 32768, 7), (16, 5, 100003, 3),
                                       (16, 128, 2100, 16), (256, 16, 5041, 12), (256, 2, 65536, 16), (256, 2, 65537, 16),
                                       (256, 97, 4100, 3)])
 @pytest.mark.parametrize("arith", ["f16x2", "f32"])
 def test_code_lists_the_signals_of_a_tile_from_the_histograms(p, K, m, s0, arith):
-    """sbo_code on both sides of its rule (2049 to 131072 signals, p = 256 65536, K <= 128, 9216 histogram entries), in turn
+    """sbo_code on both sides of its rule (2049 to 81920 signals, p = 256 65536, K <= 128, 9216 histogram entries), in turn
     with calls that group; filled up with zero signals, which all go to block 0, to a set that is grouped, the codes are the same."""
     if arith == "f32" and m > 40000:
         pytest.skip("one arithmetic is enough at these sizes")
@@ -338,7 +339,7 @@ def test_code_lists_the_signals_of_a_tile_from_the_histograms(p, K, m, s0, arith
                                       (32, 24, 511, 4), (32, 7, 513, 3), (32, 70, 20001, 4), (16, 4, 1024, 3), (16, 256, 4096, 2),
                                       (16, 257, 4000, 2), (16, 400, 1000, 2), (64, 1, 1, 8), (16, 5, 33, 3),
                                       (64, 32, 52428, 6), (64, 32, 52429, 6), (64, 128, 32768, 16), (32, 34, 131072, 4), (32, 34, 131073, 4),
-                                      (16, 128, 32768, 3), (16, 129, 32767, 2), (16, 241, 4500, 2)])
+                                      (16, 128, 32768, 3), (16, 129, 32767, 2), (16, 241, 4500, 2), (32, 5, 81920, 3), (16, 54, 81921, 3)])
 @pytest.mark.parametrize("skewed", [False, True], ids=["even", "skewed"])
 def test_iterate_lists_the_signals_of_a_piece_from_the_histograms(p, K, m, s0, skewed):
     """Sets with few histogram entries, whose block choice does not need the lists, are not grouped in sbo_iterate.  A round on the blocks that it chose,
@@ -522,6 +523,38 @@ def test_update_lists_the_signals_of_a_piece_from_the_histograms(p, K, s0, m):
     assert np.array_equal(got, again)
     # the same pieces, summed in the same order: the same bits
     assert np.array_equal(got, want), np.abs(got - want).max()
+
+
+@pytest.mark.parametrize("p,K,m", [(16, 4, 81920), (32, 7, 66047), (64, 9, 51713), (64, 3, 33279), (16, 6, 515), (32, 5, 2559)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_pieces_of_rare_blocks_come_from_many_chunks(p, K, m, shift):
+    """Blocks with a signal in every chunk, in every other one, in the last ones only or with three neighbours now and then, listed by
+    chunks; the choices stand anywhere in memory.  The same bits as by the calls that group first."""
+    rng = np.random.default_rng(m + K)
+    blk = np.zeros(m, np.int32)
+    blk[3::509] = 1
+    blk[511::1024] = 2
+    for j in range(3, K):
+        blk[j * 40:: 300 + 213 * j] = j
+        blk[j * 40 + 1:: 300 + 213 * j] = j
+        blk[j * 40 + 2:: 300 + 213 * j] = j
+    blk[m - 5:] = [K - 1, 0, 1, K - 1, 1]
+    s0 = 4
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    supp = np.sort(rng.random((m, p), dtype=np.float32).argpartition(s0, axis=1)[:, :s0], axis=1).astype(np.int32)
+    coef = rng.standard_normal((m, s0)).astype(np.float32)
+    D = np.linalg.qr(rng.standard_normal((K, p, p)))[0].astype(np.float32)
+    with Sbo(p, K, s0, m) as g:
+        t = g.torch
+        c, _offsets, _perm = g.group(blk)
+        want = g.polar(g.accumulate(Y, blk, supp, coef), D, c)
+        at = t.zeros(m + 4, dtype=t.int32, device=g.dev)[shift:shift + m]
+        at.copy_(g.dev_i32(blk))
+        Dd, counts = g.dev_f32(D), t.zeros(K, dtype=t.int32, device=g.dev)
+        sbo.sbo_update(g.ctx, g.dev_f32(Y), at, g.dev_i32(supp), g.dev_f32(coef), Dd, counts)
+        t.cuda.synchronize()
+        assert np.array_equal(counts.cpu().numpy(), np.bincount(blk, minlength=K)) and np.array_equal(counts.cpu().numpy(), c)
+        assert np.array_equal(Dd.cpu().numpy(), want)
 
 
 @pytest.mark.parametrize("K,s0,m,kind,arith", [(32, 8, 65537, "planted", "bf16x3"), (16, 3, 70001, "planted", "f32"),
