@@ -949,6 +949,7 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
     a.blk = blk;
     a.chunk_count = chunk_count;
     a.chunk = group_geom(m).chunk;
+    a.short_cut = ws.short_cut;
     a.split_E = ws.split_E;
     a.split_room = ws.split_room;
     a.split_x = ws.split_x;

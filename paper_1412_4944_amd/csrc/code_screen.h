@@ -1207,6 +1207,8 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     // one unit for the rounding of the table; BOUND: what the sum of a bound may lose to rounding
     constexpr float kUnits = 1.f + (!BOUND ? 0.f : 65535.f * P * 0x1p-25f * (1.f + (float)P / SX));
     const unsigned t16 = (HOME || GUESS) && halves ? t_home : threshold(below, norms(), kUnits);
+    if constexpr (HOME || GUESS)
+        if (tid == 0) g.short_cut[blockIdx.x] = halves;
     const bool undecided = stored(secondE) >= t16;
     if (t16 == 0x10000u) best = 0;             // a zero signal: block 0 (ties go to the lowest)
     if constexpr (home_applies<P>(SX))

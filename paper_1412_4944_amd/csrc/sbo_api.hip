@@ -37,6 +37,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.perm = (int32_t*)take((size_t)m_max * 4);
     w.group_done = (int*)take(4);
     w.weak = (int*)take(3 * 4);
+    w.short_cut = (int*)take((size_t)((m_max + 255) / 256) * 4);
     w.energy = (float*)take((size_t)m_max * 4);
     w.dsw = (float*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dsb = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 6);
@@ -672,6 +673,18 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
 int sbo_svd_sweeps(sbo_ctx* c, int32_t* sweeps) {
     if (!c || !sweeps) return SBO_EINVAL;
     SBO_HIP(hipMemcpyAsync(sweeps, c->ws.sweeps, (size_t)c->K * 4, hipMemcpyDeviceToHost, c->stream));
+    SBO_HIP(hipStreamSynchronize(c->stream));
+    return SBO_OK;
+}
+
+// For tests, not in the header: sets the first n entries of ws.short_cut to -1 (read == nullptr), or reads them after a call: 1 where a
+// workgroup decided by home or guessed blocks, 0 where it screened everything, -1 where another kernel chose.
+int sbo_test_short_cuts(sbo_ctx* c, int32_t* read, int n) {
+    if (!c || n < 0 || n > (int)((c->m_max + 255) / 256)) return SBO_EINVAL;
+    if (read == nullptr)
+        SBO_HIP(hipMemsetAsync(c->ws.short_cut, 0xff, (size_t)n * 4, c->stream));
+    else
+        SBO_HIP(hipMemcpyAsync(read, c->ws.short_cut, (size_t)n * 4, hipMemcpyDeviceToHost, c->stream));
     SBO_HIP(hipStreamSynchronize(c->stream));
     return SBO_OK;
 }

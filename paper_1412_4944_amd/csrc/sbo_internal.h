@@ -84,6 +84,7 @@ struct Workspace {
     int32_t* offsets;      // [K+1]
     int32_t* perm;         // [m_max]
     int* weak;             // [3] signals that the dictionary represents badly, per iteration in turn (code_screen.h)
+    int* short_cut;        // [ceil(m_max / 256)] per workgroup of a choice with home or guessed blocks: 1 where these decided
     int* group_done;       // [1] workgroups of the scatter that have read the histograms (0 between launches)
     // coding
     float* energy;         // [m_max] kept energy in the winning block

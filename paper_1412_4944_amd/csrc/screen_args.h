@@ -20,6 +20,7 @@ struct ScrArgs {
     // iterations of sbo_iterate (home blocks, code_screen.h): three counts of weak signals, in turn, and the iteration
     int* weak = nullptr;
     int turn = 0;
+    int* short_cut = nullptr;  // home and guessed blocks: whether a workgroup got by with them
     // ... from the second one on: the last grouping, and the blocks whose last update was by Newton-Schulz (negative)
     const int32_t *perm = nullptr, *offsets = nullptr, *sweeps = nullptr;
     bool load_only = false;    // nothing is launched, but the kernel is there afterwards

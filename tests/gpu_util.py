@@ -35,6 +35,19 @@ class Sbo:
                            {"f32": sbo.SBO_ARITH_F32, "bf16x3": sbo.SBO_ARITH_BF16X3,
                             "screen": sbo.SBO_ARITH_BF16X3_SCREEN, "f16x2": sbo.SBO_ARITH_F16X2}[name])
 
+    def short_cuts(self, m, run):
+        """run(), and of the workgroups of its (last) block choice how many there were in a kernel with home or guessed blocks, and how
+        many of them decided by these."""
+        import ctypes
+        n = (m + 255) // 256
+        buf = (ctypes.c_int32 * n)()
+        fn = sbo.lib().sbo_test_short_cuts
+        fn.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32), ctypes.c_int]
+        assert fn(self.ctx, None, n) == 0
+        out = run()
+        assert fn(self.ctx, buf, n) == 0
+        return out, sum(x >= 0 for x in buf), sum(x == 1 for x in buf)
+
     def svd_jacobi(self, on):
         """Jacobi SVD for every orthobase (on) or the default Newton-Schulz + Jacobi fallback."""
         sbo.sbo_set_option(self.ctx, sbo.SBO_OPT_SVD_METHOD, sbo.SBO_SVD_JACOBI if on else sbo.SBO_SVD_AUTO)

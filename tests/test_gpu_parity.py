@@ -461,6 +461,8 @@ def _home_case(p, K, s0, m, kind):
         Y[::401] = rng.standard_normal(Y[::401].shape)
         Y[7::5003] = 0.0
         Y[11::5003] *= 1e-21
+    elif kind.startswith("noise"):             # every so many signals
+        Y[::int(kind[5:])] = rng.standard_normal(Y[::int(kind[5:])].shape)
     elif kind == "random":
         D = np.linalg.qr(rng.standard_normal((K, p, p)))[0]
     elif kind == "unused":                     # a block that nobody takes and that is no orthobase
@@ -499,6 +501,21 @@ def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m
         sbo.sbo_iterate(g.ctx, Yd, Dd, n, *out, sq)
         t.cuda.synchronize()
         assert all(np.array_equal(a, b.cpu().numpy()) for a, b in zip(again, out))
+
+
+@pytest.mark.parametrize("op,p,K,s0,m,kind,taken", [
+    ("code", 64, 32, 8, 65537, "planted", "most"), ("code", 64, 64, 5, 100003, "planted", "most"), ("code", 64, 127, 8, 100003, "planted", "most"),
+    ("code", 64, 33, 7, 66000, "random", "none"), ("code", 64, 32, 8, 53001, "planted", "no kernel"),
+    ("iterate", 64, 32, 6, 100003, "planted", "most"), ("iterate", 64, 70, 9, 53001, "planted", "most"), ("iterate", 64, 8, 8, 100003, "random", "none"),
+    ("iterate", 64, 7, 6, 90001, "unused", "none"), ("iterate", 64, 6, 10, 60001, "planted", "no kernel"), ("iterate", 256, 5, 12, 90001, "planted", "most")])
+def test_short_cuts_of_the_block_choice_are_taken(op, p, K, s0, m, kind, taken):
+    """Whether the workgroups decide by guessed blocks (sbo_code) and home blocks (the last iteration), which no result shows."""
+    Y, D = _home_case(p, K, s0, m, kind)
+    with Sbo(p, K, s0, m) as g:
+        _out, n, n_taken = g.short_cuts(m, (lambda: g.code(Y, D)) if op == "code" else (lambda: g.iterate(Y, D, 3)))
+    print(n, n_taken)
+    assert (n == 0) == (taken == "no kernel")
+    assert n_taken >= 0.9 * n if taken == "most" else n_taken == 0
 
 
 @pytest.mark.parametrize("p,K,s0,m", [(16, 4, 3, 513), (16, 60, 2, 70001), (32, 16, 4, 131072), (64, 5, 8, 1), (64, 33, 8, 65537),
