@@ -56,26 +56,67 @@ __global__ __launch_bounds__(256) void dict_swizzle_kernel(const float* __restri
 // device_utils.h): three bf16 (Dsb) and / or two fp16 (Dsh; then also dnorm, per 16 atoms the largest
 // norm of an atom and of what its leading fp16 part leaves).  One launch for both orders.  Latency is all it is
 // (a trip to memory each way), so a thread takes one or two units: p = 256, K = 16 13.3 us with 64 rows to
-// a workgroup, 9.4 with 16.
+// a workgroup, 9.4 with 16.  GUESS (p = 64): also |Q Q^T - I|_F^2 of every block, and which of the sample of the signals it represents;
+// K = 64 4.5 -> 5.4 us with the sample (in workgroups of its own, that read D once more, 8.2).
 template <int P>
 constexpr int dict_rows() {
     return P == 256 ? 16 : P == 64 ? 32 : 64;
 }
 
-template <int P>
+// Which of 32 signals a block of 64 atoms represents (kSample): rows = the leading parts of its atoms in operand order, LDS,
+// [atom / 32][ks][.][lane]; y: this lane's half of the dims of signal lane % 32.  One wavefront.
+__device__ __forceinline__ unsigned represented(const u32x4 (&rows)[2][4][2][64], const f32x4 (&y)[4][2]) {
+    const int lane = threadIdx.x & 63;
+    float vmax = 0.f, y2 = 0.f;                // scaled to [1/2, 1) as in code_screen.h; zero, or too small for that: represented
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vmax = fmaxf(vmax, fabsf(y[ks][e >> 2][e & 3]));
+    vmax = fmaxf(vmax, other_half(vmax));
+    const unsigned ex = (__builtin_bit_cast(unsigned, vmax) >> 23) & 0xffu;
+    const float scale = ex >= 64u && ex <= 240u ? __builtin_bit_cast(float, (253u - ex) << 23) : 0.f;
+    f32x16 acc[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) acc[mt] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const f32x4 v0 = y[ks][0] * scale, v1 = y[ks][1] * scale;
+        const u32x4 b = {pack_f16(v0.x, v0.y), pack_f16(v0.z, v0.w), pack_f16(v1.x, v1.y), pack_f16(v1.z, v1.w)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y2 = fmaf(v0[e], v0[e], fmaf(v1[e], v1[e], y2));
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, rows[mt][ks][0][lane]),
+                                                             __builtin_bit_cast(f16x8, b), acc[mt], 0, 0, 0);
+    }
+    y2 = (y2 + other_half(y2)) * (kF16DictScale * kF16DictScale);
+    const float top = y2 * (kHomeT / 64);
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) sum[2 * mt + (v & 1)] += fminf(acc[mt][v] * acc[mt][v], top);
+    const float half = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    return (unsigned)__ballot(half + other_half(half) <= y2 * home_rest(64));
+}
+
+template <int P, bool GUESS>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
-                                                         float2* __restrict__ dnorm, float* __restrict__ dev, CallStart start) {
+                                                         float2* __restrict__ dnorm, float* __restrict__ dev, CallStart start,
+                                                         SignalSample sample) {
     start.clear();
     constexpr int KS16 = P / 16, R = dict_rows<P>();
     __shared__ float qs[R][P / 8 + 1], rs[R][P / 8 + 1];
-    // p = 64, dev: the rows of the whole block, [half, this one's first][ks][hi, lo][lane]
-    constexpr bool GRAM = P == 64;
-    __shared__ u32x4 both[GRAM ? 2 : 1][GRAM ? KS16 : 1][2][GRAM ? 64 : 1];
+    // GUESS (p = 64): the rows of the whole block, [half, this one's first][ks][hi, lo][lane]
+    __shared__ u32x4 both[GUESS ? 2 : 1][GUESS ? KS16 : 1][2][GUESS ? 64 : 1];
     __shared__ float off[2];
     const f32x4* D4 = reinterpret_cast<const f32x4*>(D);
     const int rows = K * P;
     const int row0 = blockIdx.x * R;
+    // the sample of the signals: half of its tiles for each of the two workgroups of a block, one for each wavefront
+    f32x4 y[GUESS ? 4 : 1][2];
+    const int tile = (blockIdx.x & 1) * 4 + (int)(threadIdx.x >> 6);
     for (int g = threadIdx.x; g < R * (P / 8); g += 256) {         // (ks, hh, row)
         const int r = g % R, kh = g / R, ks = kh >> 1, hh = kh & 1;
         const int grow = row0 + r, lane = hh * 32 + (grow & 31);
@@ -84,6 +125,20 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
         if (grow < rows) {
             v0 = D4[(int64_t)grow * (P / 4) + ks * 4 + hh * 2];
             v1 = D4[(int64_t)grow * (P / 4) + ks * 4 + hh * 2 + 1];
+        }
+        f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0;
+        if constexpr (GUESS) {
+            static_assert(P == 64 && R * (P / 8) == 256 && kSample == 8 * 32, "once; two workgroups of four wavefronts");
+            const f32x4* other = D4 + (int64_t)(grow ^ 32) * (P / 4) + ks * 4 + hh * 2;
+            o0 = other[0];
+            o1 = other[1];
+            // (last: loads return in order, and these come from further away)
+            const int64_t i = (int64_t)(tile * 32 + (threadIdx.x & 31)) * sample.m / kSample;
+            const f32x4* y4 = reinterpret_cast<const f32x4*>(sample.Y + i * P) + ((threadIdx.x >> 5) & 1) * 2;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) y[k][e] = y4[k * 4 + e];
         }
         if (Dsb != nullptr) {
             const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
@@ -101,16 +156,13 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
             out[64] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
             qs[r][kh] = q2;
             rs[r][kh] = r2;
-            if constexpr (GRAM) {
-                if (dev != nullptr) {          // uniform
-                    const int lane_g = hh * 32 + r;
-                    const f32x4* other = D4 + (int64_t)(grow ^ 32) * (P / 4) + ks * 4 + hh * 2;
-                    const F16x2Quad c = split_f16x2_dict(other[0], q2, r2), d = split_f16x2_dict(other[1], q2, r2);
-                    both[0][ks][0][lane_g] = u32x4{a.hi.x, a.hi.y, b.hi.x, b.hi.y};
-                    both[0][ks][1][lane_g] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
-                    both[1][ks][0][lane_g] = u32x4{c.hi.x, c.hi.y, d.hi.x, d.hi.y};
-                    both[1][ks][1][lane_g] = u32x4{c.lo.x, c.lo.y, d.lo.x, d.lo.y};
-                }
+            if constexpr (GUESS) {
+                const int lane_g = hh * 32 + r;
+                const F16x2Quad c = split_f16x2_dict(o0, q2, r2), d = split_f16x2_dict(o1, q2, r2);
+                both[0][ks][0][lane_g] = u32x4{a.hi.x, a.hi.y, b.hi.x, b.hi.y};
+                both[0][ks][1][lane_g] = u32x4{a.lo.x, a.lo.y, b.lo.x, b.lo.y};
+                both[1][ks][0][lane_g] = u32x4{c.hi.x, c.hi.y, d.hi.x, d.hi.y};
+                both[1][ks][1][lane_g] = u32x4{c.lo.x, c.lo.y, d.lo.x, d.lo.y};
             }
         }
     }
@@ -127,10 +179,9 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
             const int at = (row0 + (int)threadIdx.x) >> 4;
             if ((threadIdx.x & 15) == 0 && at < K * (P / 16)) dnorm[at] = float2{sqrtf(q2), sqrtf(r2)};
         }
-        if constexpr (GRAM) {
+        if constexpr (GUESS) {
             // Half of Q Q^T, products to 2^-22: this workgroup's rows with themselves by the third wavefront, with the others by
             // the last.
-            if (dev == nullptr) return;        // uniform
             const int lane = threadIdx.x & 63, half = (int)(threadIdx.x >> 6) - 2;
             if (half >= 0) {                   // uniform over the wavefront
                 f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -151,6 +202,8 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
                 for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
                 if (lane == 0) off[half] = sum;
             }
+            const unsigned mask = represented(both, y);
+            if (lane == 0) sample.mask[(blockIdx.x >> 1) * (kSample / 32) + tile] = mask;
             __syncthreads();
             if (threadIdx.x == 0) dev[blockIdx.x] = off[0] + off[1];
         }
@@ -913,15 +966,21 @@ hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const C
 }
 
 hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, float2* dev,
-                             const CallStart& start, hipStream_t st) {
+                             const SignalSample& sample, const CallStart& start, hipStream_t st) {
     u32x4 *b = reinterpret_cast<u32x4*>(dsb), *h = reinterpret_cast<u32x4*>(dsh);
-    float* dv = p == 64 && dsh != nullptr ? reinterpret_cast<float*>(dev) : nullptr;
+    float* dv = reinterpret_cast<float*>(dev);
+    if (dev != nullptr && (p != 64 || dsh == nullptr)) return hipErrorInvalidValue;
     const unsigned stages = (unsigned)(K * p + 63) / 64;           // (the last one is filled up with zeros)
     switch (p) {
-        case 16: hipLaunchKernelGGL((dict_parts_kernel<16>), dim3(stages * (64 / dict_rows<16>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
-        case 32: hipLaunchKernelGGL((dict_parts_kernel<32>), dim3(stages * (64 / dict_rows<32>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
-        case 64: hipLaunchKernelGGL((dict_parts_kernel<64>), dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
-        case 256: hipLaunchKernelGGL((dict_parts_kernel<256>), dim3(stages * (64 / dict_rows<256>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start); break;
+#define SBO_CASE(N) \
+    case N: hipLaunchKernelGGL((dict_parts_kernel<N, false>), dim3(stages * (64 / dict_rows<N>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start, sample); break;
+        SBO_CASE(16) SBO_CASE(32) SBO_CASE(256)
+#undef SBO_CASE
+        case 64: {
+            const auto kernel = dev != nullptr ? &dict_parts_kernel<64, true> : &dict_parts_kernel<64, false>;
+            hipLaunchKernelGGL(kernel, dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start, sample);
+            break;
+        }
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -971,6 +1030,7 @@ static hipError_t launch_energy_screen(int p, int K, int s0, int arith, const fl
     }
     if (turn <= 0 && p == 64 && guess_takes_64(a)) {
         a.dev = ws.dev;
+        a.sample = ws.sample;
         return launch_guess_64(a, arith, ws.raised, st);
     }
     switch (p) {

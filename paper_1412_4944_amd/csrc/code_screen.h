@@ -333,7 +333,7 @@ __device__ __forceinline__ void interleave() {
 
 // Home blocks (sbo_iterate from its second iteration on, where it takes more than 64 signals per workgroup): the signals are
 // taken in the order of the previous grouping, so that most of the signals of a workgroup belong to one block, their home.  That block is screened first, in full.  For every other
-// one, of which the update has just made an orthobase (sweeps), kHomeRows atoms decide: with R = the part of the signal's energy that
+// one, of which the update has just made an orthobase (sweeps), home_rows atoms decide: with R = the part of the signal's energy that
 // they leave, and for any t,
 //     kept energy  <=  R + s0 t + sum over them of (c^2 - min(c^2, t))  =  |y|^2 + s0 t - sum of min(c^2, t),
 // which a block that has nothing to do with the signal does not bring near the kept energy of the home block of a signal that the
@@ -346,18 +346,8 @@ __device__ __forceinline__ void interleave() {
 // instructions and 130 vector instructions a wavefront), the load of the signals (7 us a workgroup of 512, p = 256 21: HBM), p = 256
 // the home block (16 us).
 template <int P>
-constexpr int kHomeRows = P > 64 ? 64 : 32;
-// t, in units of |y|^2 / P, and mean and spread of the sum over kHomeRows<P> of the P coefficients of a random direction.
-constexpr float kHomeT = 0.8f;
-template <int P>
-constexpr float kHomeSum = 0.447f * kHomeRows<P> / P;
-template <int P>
-constexpr float kHomeSpread = P > 64 ? 0.010f : 0.026f;
-// A signal is weak if the kept energy of its best block, relative to its own, is below this line: there such bounds leave
-// one block in 160 in (mean + 2.5 spreads, and what the arithmetic may lose).
-template <int P>
-constexpr float home_line(int s0) {
-    return 1.f + kHomeT * s0 / P - kHomeSum<P> + 2.5f * kHomeSpread<P> + 0.006f;
+constexpr float home_line(int s0) {            // weak signals (home_rest)
+    return 1.f + kHomeT * s0 / P - home_rest(P);
 }
 // Which sizes have a kernel for home blocks: where signals at 20 dB are above the line (p = 64: s0 <= 9, p = 256: all).
 template <int P>
@@ -367,14 +357,14 @@ constexpr bool home_applies(int s0) {
 // Without a grouping to start from (sbo_code, the first iteration; p = 64): the bounds of all blocks first.  That of a signal's
 // own block is hardly below |y|^2, because half of its large coefficients is not among the atoms looked at, so the block of the
 // largest bound is taken as its home, and only there is it screened in full, in tiles of 32 signals of one block.  That the
-// dictionary consists of orthobases, dict_parts_kernel has measured: |Q Q^T - I|_F at most kOrthobase.  After 16 K / signals
-// blocks a workgroup with far fewer signals that have found their block (a bound above kGuessFound) than these blocks would get on
-// average goes over to screening everything in full: signals that no block represents cost 1 to 5 % more for the attempt (workgroups of 256 up to 8).
-// 100003 signals, K = 64, s0 = 5: 69 -> 52 us, the call 107.5 -> 88.0; 500000 signals, K = 128, s0 = 6: call 645 -> 468; random signals,
-// K = 32, 262144 of them: call 169 -> 173.
+// dictionary consists of orthobases, dict_parts_kernel has measured: |Q Q^T - I|_F at most kOrthobase.  So it has that at most
+// kGuessWeak of a sample of kSample signals are weak: a workgroup sees it only when the bounds are made, and has then half as much work
+// behind it as full screening takes, or K tiles for a few weak signals before it.  262144 signals, K = 32, s0 = 8: full 106 us, guesses 97;
+// with 2 of the 32 blocks random full 125, guesses 199, as it is 129; random dictionary 139, 142.  (The bounds of the first blocks, seen by
+// every workgroup for itself, tell only that no signal at all is represented: 199 and 149.)
+// 100003 signals, K = 64, s0 = 5: call 107.5 -> 88.0; 500000 signals, K = 128, s0 = 6: call 645 -> 468.
 constexpr float kOrthobase = 1e-4f;
-constexpr float kGuessFound = 0.99f;
-constexpr int kGuessFew = 4;                   // a quarter of that average, less one
+constexpr int kGuessWeak = 3;
 // A bad guess leaves nearly all blocks to the resolution, K tiles of one signal each.  From kGuessAgain K / wavefronts bad guesses on
 // a second listing is the smaller evil: 100003 signals, K = 128, s0 = 8: call 181 -> 146 us (full 171).  Only in workgroups of 512: those
 // of 256 run where a compute unit may have no other to hide its latencies, and the registers of the second listing cost more than
@@ -420,14 +410,19 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
 
     // HOME: whether the dictionary represents the signals well enough (what the coding of the last iteration left in
     // weak, three counts in turn) and all its blocks are orthobases; the signals are then those at positions wg0 .. of perm.
-    bool by_home = false, guess = GUESS;
+    bool by_home = false, guess = false;
     int id_own = 0, home_lo = 0, home_hi = 0;  // own signal; the home blocks of the workgroup
-    if constexpr (GUESS)
-        for (int j0 = 0; j0 < K; j0 += 64) {
-            const int jj = j0 + lane;
-            const float2 off = jj < K ? g.dev[jj] : float2{0.f, 0.f};
-            guess = guess && __ballot(!(off.x + off.y <= kOrthobase * kOrthobase)) == 0ull;
-        }
+    // GUESS: on their way, how far the blocks are from orthobases and which signals of the sample they represent
+    constexpr int DEVS = GUESS ? (kGuessMaxK + 63) / 64 : 1, WORDS = kSample / 32, MASKS = GUESS ? 8 : 1;
+    float2 dev[DEVS];
+    unsigned seen[MASKS];                      // words lane % WORDS, of the last block once more past the end
+    auto sample_word = [&](int w) { return g.sample[min(w + lane, (K - 1) * WORDS + lane % WORDS)]; };
+    if constexpr (GUESS) {
+#pragma unroll
+        for (int e = 0; e < DEVS; ++e) dev[e] = g.dev[min(lane + 64 * e, K - 1)];
+#pragma unroll
+        for (int e = 0; e < MASKS; ++e) seen[e] = sample_word(64 * e);
+    }
     if constexpr (HOME) {
         by_home = g.weak[(g.turn + 2) % 3] * kHomeFew <= (int)((gridDim.x + kWeakEvery - 1) / kWeakEvery) * 64;
         int lo = 0, hi = 0, other = 0;
@@ -812,8 +807,27 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 t_home = threshold(bestE, nrm, 1.f);
                 halves = few_weak(t_home);
             }
-            if (GUESS) halves = guess;
-            // Bounds from kHomeRows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the
+            if constexpr (GUESS) {
+                unsigned mask = 0u;
+#pragma unroll
+                for (int e = 0; e < MASKS; ++e) mask |= seen[e];
+                for (int w = 64 * MASKS; w < K * WORDS; w += 64 * MASKS) {     // uniform
+#pragma unroll
+                    for (int e = 0; e < MASKS; ++e) seen[e] = sample_word(w + 64 * e);
+#pragma unroll
+                    for (int e = 0; e < MASKS; ++e) mask |= seen[e];
+                }
+#pragma unroll
+                for (int o = WORDS; o < 64; o <<= 1) mask |= (unsigned)__shfl_xor((int)mask, o, 64);
+                int weak = 32 - __popc(mask);
+#pragma unroll
+                for (int o = 1; o < WORDS; o <<= 1) weak += __shfl_xor(weak, o, 64);
+                bool close = true;
+#pragma unroll
+                for (int e = 0; e < DEVS; ++e) close = close && dev[e].x + dev[e].y <= kOrthobase * kOrthobase;
+                halves = guess = __ballot(!close) == 0ull && __builtin_amdgcn_readfirstlane(weak) <= kGuessWeak;
+            }
+            // Bounds from home_rows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the
             // atoms of one.  GUESS: without home blocks, the block of the largest bound is kept instead.
             if (halves) {                      // uniform
                 u16x2 top[NT];             // sqrt(t), twice
@@ -824,7 +838,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 }
                 const float t_own = (float)(_Float16)(8192.f * __builtin_amdgcn_sqrtf(fmaxf(y2_own, 0.f) * (kHomeT / P)));
                 // Orthobases to 1e-4, sums to a few 2^-24; and |a - b| <= d gives a^2 >= b^2 - 2 d b for the root of the sum, b <= |y|.
-                constexpr float root = P > 64 ? 8.f : 5.657f;                        // of kHomeRows
+                constexpr float root = P > 64 ? 8.f : 5.657f;                        // of home_rows
                 const float most = 1.0003f + (float)g.s0 * (t_own * t_own) * e_scale + 2.f * root * coef_error(nrm);
                 const int n_step = WIDE ? 2 * K : (K + 1) / 2;
                 auto fetch_home = [&](u32x4 (&q)[FPT], int s) {
@@ -914,20 +928,9 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 __syncthreads();
                 project(acc0, 0);
                 __syncthreads();
-                // Far too few signals have found their block among those so far, whose bound is hardly below one: in full
-                auto found_few = [&](int s) {
-                    if (!GUESS || s != (8 * K - 1) / SIG) return false;            // uniform
-                    const int found = __popcll(__ballot(bestE >= kGuessFound && y2_own > 0.f));
-                    if (lane == 0 && found != 0) atomicAdd(&n_weak[1], found);
-                    __syncthreads();
-                    return (n_weak[1] + 1) * kGuessFew * K < (int)min((int64_t)SIG, m - wg0) * 2 * (s + 1);
-                };
                 for (int s = 0; s < n_step && halves; s += 2) {
                     home_step(acc0, acc1, s, std::false_type{});
-                    halves = !found_few(s);
-                    if (!halves) break;        // uniform
                     if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});         // uniform
-                    halves = !found_few(s + 1);
                     if (!GUESS && (s & 14) == 14) {        // too many to be resolved one by one: all over again, in full
                         if (n_left != 0) atomicAdd(&n_weak[1], n_left);
                         n_left = 0;

@@ -658,7 +658,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
     if (lists && g.chunk != kListChunk) return hipErrorInvalidValue;
     const ChunkLists from = {blk, (int)m, g.n_chunks, ws.chunk_count, nullptr, nullptr}, *l = lists ? &from : nullptr;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
-        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, nullptr, CallStart{}, st)
+        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, nullptr, SignalSample{}, CallStart{}, st)
                              : launch_dict_swizzle(p, K, D, ws.dsw, CallStart{}, st);
         if (e != hipSuccess) return e;
     }

@@ -44,6 +44,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.dsh = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dnorm = (float2*)take((size_t)K * (p / 16) * 8);
     w.dev = (float2*)take(p == 64 ? (size_t)K * 8 : 0);
+    w.sample = (unsigned*)take(p == 64 ? (size_t)K * (kSample / 8) : 0);
     const size_t split_m = (size_t)(m_max < kEnergySplitSignals ? m_max : kEnergySplitSignals);
     const size_t direct = m_max < kDirectMaxEnergies / K ? (size_t)K * m_max : (size_t)kDirectMaxEnergies;
     w.part_E = (float*)take((direct > kEnergySplitRows * split_m ? direct : kEnergySplitRows * split_m) * 4);
@@ -164,14 +165,15 @@ static int select_ops(const sbo_ctx* c) { return c->p <= 64 ? 0 : use_split(c) ?
 static int code_ops(const sbo_ctx* c) { return energy_ops(c) | select_ops(c); }
 
 // D in the operand order(s) the coding kernels of this context read (tiny; outside the stages).
-static int run_swizzle(sbo_ctx* c, int64_t m, const float* D) {
+static int run_swizzle(sbo_ctx* c, const float* Y, int64_t m, const float* D) {
     const int ops = code_ops(c);
     const CallStart start = {c->ws.weak, c->ws.chunk_count, group_geom(m).n_chunks * c->K};
     if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, start, c->stream));
     if (ops & (kOpsBf16 | kOpsF16))
         SBO_HIP(launch_dict_parts(c->p, c->K, D, ops & kOpsBf16 ? c->ws.dsb : nullptr,
                                   ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm,
-                                  guess_applies(c->p, c->K, c->s0, m, choice_arith(c)) ? c->ws.dev : nullptr, start, c->stream));
+                                  guess_applies(c->p, c->K, c->s0, m, choice_arith(c)) ? c->ws.dev : nullptr,
+                                  SignalSample{Y, (int)m, c->ws.sample}, start, c->stream));
     return SBO_OK;
 }
 
@@ -191,7 +193,7 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
         StageTimer t(c, SBO_STAGE_ENERGY);
         SBO_HIP(launch_energy_direct(c->p, c->K, c->s0, choice_arith(c), Y, m, D, c->ws, c->stream));
     } else {
-        if (turn <= 0) rc = run_swizzle(c, m, D);
+        if (turn <= 0) rc = run_swizzle(c, Y, m, D);
         if (rc) return rc;
         rc = run_energy(c, Y, m, blk, turn);
         if (rc) return rc;
@@ -423,7 +425,7 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
         // The dictionary in the coding kernel's operand order: rewritten from D at the start
         // of the call, kept up to date by the SVD kernel afterwards.
         if (it == 0) {
-            rc = run_swizzle(c, m, D);
+            rc = run_swizzle(c, Y, m, D);
             if (rc) return rc;
         }
         rc = run_energy(c, Y, m, blk, it);

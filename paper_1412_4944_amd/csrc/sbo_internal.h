@@ -93,6 +93,7 @@ struct Workspace {
     unsigned* dsh;         // the same rows as two fp16 parts (4 bytes per entry)
     float2* dnorm;         // [K*p/16] per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
     float2* dev;           // [K] p = 64: |Q Q^T - I|_F^2 of a block, in two parts (guess_applies)
+    unsigned* sample;      // [K][kSample / 32] p = 64: which of a sample of the signals a block represents
     float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row; or
                            // the energies of a small set, [K][m] (at most kDirectMaxEnergies)
     int32_t* part_j;       // same shape: its block
@@ -256,18 +257,28 @@ struct CallStart {
     int* weak = nullptr;           // ws.weak: its first count
     int32_t* hist = nullptr;       // ws.chunk_count: the first n_hist entries
     int n_hist = 0;
+    // 256 threads (blockDim would be a trip to memory before everything else)
     __device__ __forceinline__ void clear() const {
         if (weak != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *weak = 0;
-        for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n_hist; e += gridDim.x * blockDim.x) hist[e] = 0;
+        for (int e = blockIdx.x * 256 + threadIdx.x; e < n_hist; e += gridDim.x * 256) hist[e] = 0;
     }
 };
 // dsw = D in the fp32 operand order of the coding kernels.
 hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const CallStart& start, hipStream_t st);
+// A sample of the signals tells whether it is worth guessing blocks: kSample of them, evenly spaced, and per block which of them it
+// represents (code_screen.h), a bit each.  The launch that writes the dictionary's operand order finds out.
+constexpr int kSample = 256;
+struct SignalSample {
+    const float* Y = nullptr;
+    int m = 0;
+    unsigned* mask = nullptr;      // ws.sample
+};
 // dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
-// (device_utils.h); dnorm comes with dsh.  dev (or nullptr; p = 64, dsh given): |Q Q^T - I|_F^2 per block.
+// (device_utils.h); dnorm comes with dsh.  dev (or nullptr; p = 64, dsh given): |Q Q^T - I|_F^2 per block, and the
+// sample of the m signals of Y (m >= kSample).
 hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, float2* dev,
-                             const CallStart& start, hipStream_t st);
-// Whether the block choice of a first pass (turn <= 0 of launch_energy) reads ws.dev.
+                             const SignalSample& sample, const CallStart& start, hipStream_t st);
+// Whether the block choice of a first pass (turn <= 0 of launch_energy) reads ws.dev and ws.sample.
 bool guess_applies(int p, int K, int s0, int64_t m, int arith);
 // The block of every signal, from the operand orders in ws that (p, s0, arith) reads (energy_ops in
 // sbo_api.hip).

@@ -6,6 +6,17 @@
 
 namespace sbo {
 
+// Bounds of home and guessed blocks (code_screen.h): t, in units of |y|^2 / P; of the sum of min(c^2, t) over kHomeRows of the P
+// coefficients of a random direction, in units of |y|^2, mean and spread.
+constexpr float kHomeT = 0.8f;
+constexpr int home_rows(int P) { return P > 64 ? 64 : 32; }
+constexpr float home_sum(int P) { return 0.447f * home_rows(P) / P; }
+constexpr float home_spread(int P) { return P > 64 ? 0.010f : 0.026f; }
+// A signal is weak if its best block keeps less than 1 + s0 t - home_rest: there such bounds leave one block in 160 in (mean + 2.5
+// spreads, and what the arithmetic may lose).  A block that represents a signal keeps 1 + s0 t - (the sum over all atoms): s0 t of it are
+// the kept ones.
+constexpr float home_rest(int P) { return home_sum(P) - 2.5f * home_spread(P) - 0.006f; }
+
 // What the resolution reads, besides Dh: Dx = the dictionary in the exact arithmetic's operand order.
 struct ScrArgs {
     const float* Y;
@@ -26,6 +37,7 @@ struct ScrArgs {
     bool load_only = false;    // nothing is launched, but the kernel is there afterwards
     // ... in the first one, and in sbo_code: per block |Q Q^T - I|_F^2 in two parts
     const float2* dev = nullptr;
+    const unsigned* sample = nullptr;        // ... and the signals of the sample that it represents, [K][kSample / 32]
     // workgroups of 64 signals, split: rows of workgroups that share out the blocks, and what they exchange (choice_split)
     int rows = 1;
     unsigned *split_E = nullptr, *split_x = nullptr;

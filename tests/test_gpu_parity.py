@@ -505,7 +505,7 @@ def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m
 
 @pytest.mark.parametrize("op,p,K,s0,m,kind,taken", [
     ("code", 64, 32, 8, 65537, "planted", "most"), ("code", 64, 64, 5, 100003, "planted", "most"), ("code", 64, 127, 8, 100003, "planted", "most"),
-    ("code", 64, 33, 7, 66000, "random", "none"), ("code", 64, 32, 8, 53001, "planted", "no kernel"),
+    ("code", 64, 33, 7, 66000, "random", "none"), ("code", 64, 64, 5, 100003, "noise17", "none"), ("code", 64, 32, 8, 53001, "planted", "no kernel"),
     ("iterate", 64, 32, 6, 100003, "planted", "most"), ("iterate", 64, 70, 9, 53001, "planted", "most"), ("iterate", 64, 8, 8, 100003, "random", "none"),
     ("iterate", 64, 7, 6, 90001, "unused", "none"), ("iterate", 64, 6, 10, 60001, "planted", "no kernel"), ("iterate", 256, 5, 12, 90001, "planted", "most")])
 def test_short_cuts_of_the_block_choice_are_taken(op, p, K, s0, m, kind, taken):
