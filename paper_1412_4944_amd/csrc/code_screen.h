@@ -338,7 +338,7 @@ __device__ __forceinline__ void interleave() {
 //     kept energy  <=  R + s0 t + sum over them of (c^2 - min(c^2, t))  =  |y|^2 + s0 t - sum of min(c^2, t),
 // which a block that has nothing to do with the signal does not bring near the kept energy of the home block of a signal that the
 // dictionary represents well.  What comes near is resolved like all other candidates, so that the chosen blocks remain those of the
-// full computation.  Where more than one signal in kHomeFew is not represented well (kept energy below home_line), or a block
+// full computation.  Where more than one signal in kHomeFew<P> is not represented well (kept energy below home_line), or a block
 // is no orthobase, everything is screened in full: in the order of the signals if the last iteration says so, or by the workgroup that
 // finds it.  Half of the products and of the selection (p = 64; p = 256: a quarter of the products, and no networks), with
 // trained dictionaries: K = 32, s0 = 8, 262144 signals 104 -> 78 us, K = 128, s0 = 6, 2^20 signals 1380 -> 760, p = 256,
@@ -358,23 +358,30 @@ constexpr bool home_applies(int s0) {
 // own block is hardly below |y|^2, because half of its large coefficients is not among the atoms looked at, so the block of the
 // largest bound is taken as its home, and only there is it screened in full, in tiles of 32 signals of one block.  That the
 // dictionary consists of orthobases, dict_parts_kernel has measured: |Q Q^T - I|_F at most kOrthobase.  So it has that at most
-// kGuessWeak of a sample of kSample signals are weak: a workgroup sees it only when the bounds are made, and has then half as much work
-// behind it as full screening takes, or K tiles for a few weak signals before it.  262144 signals, K = 32, s0 = 8: full 106 us, guesses 97;
-// with 2 of the 32 blocks random full 125, guesses 199, as it is 129; random dictionary 139, 142.  (The bounds of the first blocks, seen by
-// every workgroup for itself, tell only that no signal at all is represented: 199 and 149.)
-// 100003 signals, K = 64, s0 = 5: call 107.5 -> 88.0; 500000 signals, K = 128, s0 = 6: call 645 -> 468.
+// guess_weak(K) of a sample of kSample signals are weak: a workgroup sees it only when the bounds are made, and has then half as much
+// work behind it as full screening takes.  262144 signals, K = 32, s0 = 8: full 106 us, guesses 95; with 2 of the 32 blocks random full 125,
+// guesses anyway 199, as it is 129; random dictionary 139, 142.  (The bounds of the first blocks, seen by every workgroup for itself, tell
+// only that no signal at all is represented: 199 and 149.)
+// 100003 signals, K = 64, s0 = 5: call 125 -> 100; 10^6, K = 128, s0 = 6: choice 1220 -> 855.
 constexpr float kOrthobase = 1e-4f;
-constexpr int kGuessWeak = 3;
-// A bad guess leaves nearly all blocks to the resolution, K tiles of one signal each.  From kGuessAgain K / wavefronts bad guesses on
-// a second listing is the smaller evil: 100003 signals, K = 128, s0 = 8: call 181 -> 146 us (full 171).  Only in workgroups of 512: those
-// of 256 run where a compute unit may have no other to hide its latencies, and the registers of the second listing cost more than
-// it gives (65537 signals, K = 32, s0 = 8: call 58 -> 62).
-constexpr int kGuessAgain = 8;
-constexpr int kGuessMinK = 16, kGuessMaxK = 160;           // (160: the lists of a workgroup fit where its stages were)
+constexpr int kGuessMinK = 20, kGuessMaxK = 160;           // (160: the lists of a workgroup fit where its stages were)
 
-// One signal in kHomeFew may be weak: of a workgroup, and of those counted, which are the first 64 of every kWeakEvery-th
-// workgroup (all of them: 4096 atomic additions to one address, 262144 signals 125 -> 152 us).
-constexpr int kHomeFew = 16, kWeakEvery = 4;
+// Weak signals.  Such bounds leave them with most blocks, and a tile of one signal is as much work as one of 32: K tiles for the first
+// weak signal of a workgroup (3.3 us each, a wavefront).  So all of them in a workgroup are listed and screened in all blocks, by all atoms
+// (p = 64; at p = 256 a tile is a small part of the work).  262144 signals, K = 32, s0 = 8, 1 % of them noise, full / so / left to the
+// resolution: sbo_code 113 / 109 / 128, six iterations 614 / 555 / 638; 100003, K = 64, 3 % 99 / 84 / 107.  Bad guesses too: 100003, K = 128,
+// s0 = 8 164 / 125, left to the resolution 165.
+// Where it pays: iterations, of the signals counted, which are the first 64 of every kWeakEvery-th workgroup (all of them: 4096 atomic
+// additions to one address, 262144 signals 125 -> 152 us), one in kHomeFew (K = 32, 9 % noise, full 675, home blocks 653; K = 128 10 % 3870,
+// 3160; p = 256, whose weak signals go to the resolution, less); of a workgroup one in kWeakFew.  Guesses, of the sample, guess_weak(K): the
+// gain grows with K, choice of 262144 signals, K = 24, s0 = 6, full / guesses: 1 % noise 94 / 92, K = 32, s0 = 8 1 % 113 / 109, 2 % 117 / 114, 6 %
+// 125 / 144; 100003, K = 64, s0 = 5 3 % 100 / 86, 6 % 104 / 104, 10 % 108 / 118; 10^6, K = 128, s0 = 6 6 % 1330 / 1230.
+template <int P>
+constexpr int kHomeFew = P > 64 ? 16 : 8;
+template <int P>
+constexpr int kWeakFew = P > 64 ? 16 : 4;
+constexpr int kWeakEvery = 4;
+constexpr int guess_weak(int K) { return K < 96 ? (K - 16) / 4 : 20; }
 
 // What a workgroup screens in full: everything; the home blocks of its signals; the block of the largest bound.
 enum Choice { kFull, kHome, kGuess };
@@ -424,7 +431,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         for (int e = 0; e < MASKS; ++e) seen[e] = sample_word(64 * e);
     }
     if constexpr (HOME) {
-        by_home = g.weak[(g.turn + 2) % 3] * kHomeFew <= (int)((gridDim.x + kWeakEvery - 1) / kWeakEvery) * 64;
+        by_home = g.weak[(g.turn + 2) % 3] * kHomeFew<P> <= (int)((gridDim.x + kWeakEvery - 1) / kWeakEvery) * 64;
         int lo = 0, hi = 0, other = 0;
         const int last = (int)min(wg0 + SIG, (int64_t)m) - 1;
         for (int j0 = 0; j0 < K; j0 += 64) {
@@ -750,7 +757,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         const int weak = __popcll(__ballot(t16 < kWeakBelow));
         if (lane == 0 && weak != 0) atomicAdd(n_weak, weak);
         __syncthreads();
-        return *n_weak * kHomeFew <= SIG;
+        return *n_weak * kWeakFew<P> <= SIG;
     };
     bool halves = false;                       // HOME: only the home blocks have been screened in full
     unsigned t_home = 0u;
@@ -782,6 +789,21 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         };
         if constexpr (HOME || GUESS) {
             const float2 nrm = norms();
+            // the leading parts of a signal, scaled (as convert_group), as a B operand
+            auto leading_parts = [](const ExactRow<P, 3>& y, u32x4 (&b)[KS16]) {
+                float vmax = 0.f;
+#pragma unroll
+                for (int e = 0; e < P / 8; ++e)
+                    vmax = fmaxf(fmaxf(fmaxf(vmax, fabsf(y.v[e].x)), fmaxf(fabsf(y.v[e].y), fabsf(y.v[e].z))), fabsf(y.v[e].w));
+                vmax = fmaxf(vmax, other_half(vmax));
+                const unsigned ex = (__builtin_bit_cast(unsigned, vmax) >> 23) & 0xffu;
+                const float scale = ex >= 64u && ex <= 240u ? __builtin_bit_cast(float, (253u - ex) << 23) : 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS16; ++ks) {
+                    const f32x4 v0 = y.v[2 * ks] * scale, v1 = y.v[2 * ks + 1] * scale;
+                    b[ks] = u32x4{pack_f16(v0.x, v0.y), pack_f16(v0.z, v0.w), pack_f16(v1.x, v1.y), pack_f16(v1.z, v1.w)};
+                }
+            };
             if (HOME && by_home) {             // uniform
                 // the home blocks, those of its own signals by every wavefront
                 int lo = 0, hi = 0;
@@ -825,7 +847,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 bool close = true;
 #pragma unroll
                 for (int e = 0; e < DEVS; ++e) close = close && dev[e].x + dev[e].y <= kOrthobase * kOrthobase;
-                halves = guess = __ballot(!close) == 0ull && __builtin_amdgcn_readfirstlane(weak) <= kGuessWeak;
+                halves = guess = __ballot(!close) == 0ull && __builtin_amdgcn_readfirstlane(weak) <= guess_weak(K);
             }
             // Bounds from home_rows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the
             // atoms of one.  GUESS: without home blocks, the block of the largest bound is kept instead.
@@ -854,7 +876,8 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                         }
                     }
                 };
-                int n_left = 0;            // blocks that the bounds leave in, besides the best one, of the own signal
+                int n_left = 0;            // blocks that the bounds leave in, besides the best one, of the own signal (weak, p = 64: below)
+                const unsigned t_left = !WIDE && t_home < kWeakBelow ? 0x10000u : t_home;
                 int last_block = -1;
                 auto leave = [&](float sum, int j) {
                     const float e = most - sum * e_scale;
@@ -872,7 +895,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     secondE = fmaxf(secondE, other ? e : -1.f);
                     const unsigned q = stored(e);
                     E16[j * SIG + loc0 + lane] = (unsigned short)q;
-                    n_left += other && q >= t_home;
+                    n_left += other && q >= t_left;
                 };
                 float part_sum[NT] = {0.f, 0.f};
                 auto bound = [&](const Acc& acc, int s, auto second_half) {
@@ -940,10 +963,85 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     }
                 }
             }
+            // p = 64: the weak signals, whom such bounds leave with most blocks, are screened in all of them: listed, in tiles of 32, two blocks
+            // at a time by every wavefront (a tile of one signal is as much work as one of 32).
+            auto screen_weak = [&]() {
+                const bool wanted = t_home < kWeakBelow;
+                unsigned short* list = reinterpret_cast<unsigned short*>(front);
+                const unsigned long long mask = __ballot(wanted);
+                __syncthreads();               // the stages are dead
+                int at = 0;
+                if (lane == 0 && mask != 0ull) at = atomicAdd(n_tasks, __popcll(mask));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (wanted) list[at + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)(loc0 + lane);
+                if constexpr (HOME) reinterpret_cast<int*>(key)[loc0 + lane] = id_own;
+                __syncthreads();
+                const int n_list = *n_tasks, n_pair = (K + 1) / 2;
+                u32x4 rows[2][UT][KS16];
+                auto look_up = [&](int pair) {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const u32x4* D = g.Dh + (int64_t)min(2 * pair + k, K - 1) * UT * (KS16 * 128) + lane;
+#pragma unroll
+                        for (int mt = 0; mt < UT; ++mt)
+#pragma unroll
+                            for (int ks = 0; ks < KS16; ++ks) rows[k][mt][ks] = D[(mt * KS16 + ks) * 128];
+                    }
+                };
+                for (int t0 = 0; t0 < n_list; t0 += 32) {          // uniform
+                    const int id = t0 + n < n_list ? (int)list[t0 + n] : -1;
+                    ExactRow<P, 3> y;
+                    y.load(g, id < 0 ? (int64_t)-1 : HOME ? (int64_t)reinterpret_cast<const int*>(key)[id] : wg0 + id, h);
+                    if (wave < n_pair) look_up(wave);
+                    u32x4 yb[KS16];
+                    leading_parts(y, yb);
+                    const float to_stored = id < 0 ? 0.f : 0x1p-26f / y2s[id];
+                    for (int pair = wave; pair < n_pair; pair += NW) {
+#pragma unroll
+                        for (int k = 0; k < 2; ++k)
+#pragma unroll
+                            for (int ks = 0; ks < KS16; ++ks)
+#pragma unroll
+                                for (int mt = 0; mt < UT; ++mt)
+                                    acc0[k][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                                        __builtin_bit_cast(f16x8, rows[k][mt][ks]), __builtin_bit_cast(f16x8, yb[ks]),
+                                        ks == 0 ? zero : acc0[k][mt], 0, 0, 0);
+                        u16x2 x[NV], a[SX];
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            const auto q = __builtin_amdgcn_cvt_pkrtz(fabsf(acc0[0][v >> 4][v & 15]), fabsf(acc0[1][v >> 4][v & 15]));
+                            x[v] = __builtin_bit_cast(u16x2, q);
+                        }
+                        look_up(min(pair + NW, n_pair - 1));
+                        pk_top_sorted<NV, SX>(x, a);
+                        const float e = pk_pair_energy<SX>(a, h != 0);
+                        if (id >= 0) E16[min(2 * pair + h, K - 1) * SIG + id] = (unsigned short)stored(e * to_stored);
+                    }
+                }
+                __syncthreads();
+                if (tid == 0) *n_tasks = 0;
+                if (mask != 0ull) {            // uniform over the wavefront
+                    unsigned q0 = 0, q1 = 0;
+                    int j0 = 0;
+                    for (int j = 0; j < K; ++j) {
+                        const unsigned q = E16[j * SIG + loc0 + lane];
+                        q1 = max(q1, min(q0, q));
+                        j0 = q > q0 ? j : j0;
+                        q0 = max(q0, q);
+                    }
+                    const unsigned t16 = threshold((float)q0 * (1.f / 65535.f), nrm, 1.f);
+                    if (wanted) {
+                        best = j0;
+                        secondE = (float)q1 * (1.f / 65535.f);
+                        t_home = t16;
+                    }
+                }
+            };
             if constexpr (GUESS) {
-                // The kept energy, as far as the leading parts give it, of the wanted signals in their block j_try, in stored energies
-                // (the others: -1): the signals listed by block, in tiles of 32.
-                auto guessed_energy = [&](int j_try, bool wanted) {
+                // The kept energy of the signals in the blocks of their largest bounds, as far as the leading parts give it (a zero
+                // signal: -1): the signals listed by block, in tiles of 32.
+                auto guessed_energy = [&]() {
+                    const bool wanted = y2_own > 0.f;
                     int* first = reinterpret_cast<int*>(front);                        // [K] signals of a block, then its first tile
                     unsigned short* tile_block = reinterpret_cast<unsigned short*>(first + K);         // [most]
                     const int most = K + SIG / 32;         // tiles
@@ -953,7 +1051,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     for (int e = tid; e < most * 16; e += NTH) reinterpret_cast<unsigned*>(list)[e] = 0xffffffffu;
                     __syncthreads();
                     int slot = 0;
-                    if (wanted) slot = atomicAdd(&first[j_try], 1);
+                    if (wanted) slot = atomicAdd(&first[best], 1);
                     __syncthreads();
                     if (wave == 0) {
                         int tiles = 0;
@@ -966,7 +1064,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                         if (lane == 0) *n_tasks = tiles;
                     }
                     __syncthreads();
-                    if (wanted) list[first[j_try] * 32 + slot] = (unsigned short)(loc0 + lane);
+                    if (wanted) list[first[best] * 32 + slot] = (unsigned short)(loc0 + lane);
                     thr[loc0 + lane] = __builtin_bit_cast(unsigned, -1.f);
                     __syncthreads();
                     const int tiles = *n_tasks;
@@ -997,22 +1095,14 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                         const int id_out = h == 0 ? id[0] : id[1];
 #pragma unroll
                         for (int k = 0; k < 2; ++k) {
-                            float vmax = 0.f;
-#pragma unroll
-                            for (int e = 0; e < P / 8; ++e)
-                                vmax = fmaxf(fmaxf(fmaxf(vmax, fabsf(y[k].v[e].x)), fmaxf(fabsf(y[k].v[e].y), fabsf(y[k].v[e].z))),
-                                             fabsf(y[k].v[e].w));
-                            vmax = fmaxf(vmax, other_half(vmax));
-                            const unsigned ex = (__builtin_bit_cast(unsigned, vmax) >> 23) & 0xffu;        // (as convert_group)
-                            const float scale = ex >= 64u && ex <= 240u ? __builtin_bit_cast(float, (253u - ex) << 23) : 0.f;
+                            u32x4 yb[KS16];
+                            leading_parts(y[k], yb);
 #pragma unroll
                             for (int ks = 0; ks < KS16; ++ks) {
-                                const f32x4 v0 = y[k].v[2 * ks] * scale, v1 = y[k].v[2 * ks + 1] * scale;
-                                const u32x4 b = {pack_f16(v0.x, v0.y), pack_f16(v0.z, v0.w), pack_f16(v1.x, v1.y), pack_f16(v1.z, v1.w)};
 #pragma unroll
                                 for (int mt = 0; mt < UT; ++mt)
                                     acc0[k][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                                        __builtin_bit_cast(f16x8, rows[k][mt][ks]), __builtin_bit_cast(f16x8, b),
+                                        __builtin_bit_cast(f16x8, rows[k][mt][ks]), __builtin_bit_cast(f16x8, yb[ks]),
                                         ks == 0 ? zero : acc0[k][mt], 0, 0, 0);
                             }
                         }
@@ -1033,44 +1123,15 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     __syncthreads();
                     return below;
                 };
-                // Signals badly represented by their blocks leave most blocks to the resolution.  Where that is more work than a second
-                // listing (tiles of 32 among the wavefronts), and not most are, those try the next best block too.
                 if (halves) {                  // uniform
-                    float kept = -1.f;
-                    int j_try = best;
-                    bool wanted = y2_own > 0.f;
-                    for (int round = 0;; ++round) {
-                        const float e = guessed_energy(j_try, wanted);
-                        if (wanted) {
-                            E16[j_try * SIG + loc0 + lane] = (unsigned short)stored(e);
-                            best = e > kept ? j_try : best;
-                            kept = fmaxf(kept, e);
-                        }
-                        t_home = threshold(kept, nrm, 1.f);
-                        wanted = wanted && t_home < kWeakBelow;
-                        halves = few_weak(t_home);
-                        const int n_bad = *n_weak;
-                        if (W < kScrWaves || (halves && n_bad * K <= kGuessAgain * NW) || round != 0 || 4 * n_bad > SIG) break;   // uniform
-                        __syncthreads();
-                        if (tid == 0) *n_weak = 0;
-                        // its largest bound, and what is second to both
-                        if (__ballot(wanted) != 0ull) {
-                            unsigned q0 = 0, q1 = 0;
-                            int j0 = 0;
-                            for (int j = 0; j < K; ++j) {
-                                const unsigned q = E16[j * SIG + loc0 + lane];
-                                q1 = max(q1, min(q0, q));
-                                j0 = q > q0 ? j : j0;
-                                q0 = max(q0, q);
-                            }
-                            if (wanted) {
-                                j_try = j0;
-                                secondE = (float)q1 * (1.f / 65535.f);
-                            }
-                        }
-                    }
+                    const float e = guessed_energy();
+                    if (y2_own > 0.f) E16[best * SIG + loc0 + lane] = (unsigned short)stored(e);
+                    t_home = threshold(e, nrm, 1.f);
+                    halves = few_weak(t_home);
                 }
             }
+            if constexpr (!WIDE)
+                if (halves && *n_weak != 0) screen_weak();         // uniform
             if ((by_home || guess) && !halves) {               // uniform
                 bestE = secondE = -1.f;
                 best = 0;

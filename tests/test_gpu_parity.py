@@ -474,6 +474,7 @@ HOME_CASES = [(64, 5, 8, 60001, "planted", "f16x2"), (64, 32, 6, 100003, "plante
               (64, 9, 4, 131149, "odd signals", "f32"), (64, 6, 8, 100003, "odd signals", "bf16x3"),
               (64, 8, 8, 100003, "random", "f16x2"), (64, 8, 5, 70001, "close", "f16x2"), (64, 40, 8, 100003, "close", "bf16x3"),
               (64, 7, 6, 90001, "unused", "f16x2"), (64, 70, 9, 53001, "planted", "f16x2"), (64, 6, 10, 60001, "planted", "f16x2"), (256, 5, 12, 90001, "planted", "f16x2"),
+              (64, 33, 5, 100003, "noise40", "f16x2"), (64, 32, 8, 66001, "noise9", "bf16x3"), (64, 70, 3, 53001, "noise15", "f32"),
               (256, 4, 16, 86017, "close", "f16x2"), (256, 3, 5, 131072, "odd signals", "f16x2")]
 
 
@@ -505,7 +506,8 @@ def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m
 
 @pytest.mark.parametrize("op,p,K,s0,m,kind,taken", [
     ("code", 64, 32, 8, 65537, "planted", "most"), ("code", 64, 64, 5, 100003, "planted", "most"), ("code", 64, 127, 8, 100003, "planted", "most"),
-    ("code", 64, 33, 7, 66000, "random", "none"), ("code", 64, 64, 5, 100003, "noise17", "none"), ("code", 64, 32, 8, 53001, "planted", "no kernel"),
+    ("code", 64, 33, 7, 66000, "random", "none"), ("code", 64, 64, 5, 100003, "noise10", "none"), ("code", 64, 64, 5, 100003, "noise33", "most"),
+    ("iterate", 64, 32, 6, 100003, "noise12", "most"), ("code", 64, 32, 8, 53001, "planted", "no kernel"),
     ("iterate", 64, 32, 6, 100003, "planted", "most"), ("iterate", 64, 70, 9, 53001, "planted", "most"), ("iterate", 64, 8, 8, 100003, "random", "none"),
     ("iterate", 64, 7, 6, 90001, "unused", "none"), ("iterate", 64, 6, 10, 60001, "planted", "no kernel"), ("iterate", 256, 5, 12, 90001, "planted", "most")])
 def test_short_cuts_of_the_block_choice_are_taken(op, p, K, s0, m, kind, taken):
@@ -578,7 +580,9 @@ def test_pieces_of_rare_blocks_come_from_many_chunks(p, K, m, shift):
                                                (31, 6, 90001, "odd signals", "f16x2"), (100, 5, 53001, "close", "f16x2"),
                                                (64, 5, 131149, "close", "bf16x3"), (127, 8, 100003, "planted", "f16x2"),
                                                (40, 8, 270001, "odd signals", "f32"), (33, 7, 66000, "random", "f16x2"),
-                                               (159, 4, 210007, "planted", "f16x2")])
+                                               (159, 4, 210007, "planted", "f16x2"), (64, 5, 100003, "noise33", "f16x2"),
+                                               (97, 3, 70001, "noise40", "f32"), (32, 8, 66001, "noise130", "bf16x3"),
+                                               (127, 7, 200003, "noise15", "f16x2")])
 def test_code_starts_from_the_block_of_the_largest_bound(K, s0, m, kind, arith):
     """sbo_code on many signals guesses their block from bounds, where the dictionary consists of orthobases; with one more
     block that is none and that nobody takes it screens them all: the same bits."""
