@@ -13,7 +13,7 @@ hipError_t launch_guess_64(const ScrArgs& a, int arith, LdsRaised* raised, hipSt
 // chain of latencies, and the added steps are most of them: 53000 signals, s0 = 8, K = 32 50 -> 54 us, 64 74 -> 75; s0 = 5, 64 75 -> 66.
 bool guess_takes_64(const ScrArgs& a) {
     const int least = (a.m <= kNumCU * 256 ? 10 : 4) * a.s0;
-    return home_takes<64>(a) && a.s0 <= 8 && a.K >= (least > kGuessMinK ? least : kGuessMinK) && a.K <= kGuessMaxK;
+    return home_takes<64>(a) && a.s0 <= kGuessMaxS0 && a.K >= (least > kGuessMinK ? least : kGuessMinK) && a.K <= kGuessMaxK;
 }
 
 }  // namespace sbo

@@ -364,7 +364,7 @@ constexpr bool home_applies(int s0) {
 // only that no signal at all is represented: 199 and 149.)
 // 100003 signals, K = 64, s0 = 5: call 125 -> 100; 10^6, K = 128, s0 = 6: choice 1220 -> 855.
 constexpr float kOrthobase = 1e-4f;
-constexpr int kGuessMinK = 20, kGuessMaxK = 160;           // (160: the lists of a workgroup fit where its stages were)
+constexpr int kGuessMaxS0 = 8, kGuessMinK = 20, kGuessMaxK = 160;           // (160: the lists of a workgroup fit where its stages were)
 
 // Weak signals.  Such bounds leave them with most blocks, and a tile of one signal is as much work as one of 32: K tiles for the first
 // weak signal of a workgroup (3.3 us each, a wavefront).  So all of them in a workgroup are listed and screened in all blocks, by all atoms
@@ -1433,7 +1433,7 @@ hipError_t launch_home_p(const ScrArgs& a, int arith, LdsRaised* raised, hipStre
     switch (a.s0) {
 #define SBO_CASE(N) \
     case N:         \
-        if constexpr (home_applies<P>(N)) { \
+        if constexpr (home_applies<P>(N) && (CHOICE != kGuess || N <= kGuessMaxS0)) { \
             if (arith == SBO_ARITH_F16X2) return launch_home_a<P, N, 3, CHOICE>(a, raised, st); \
             if constexpr (P <= 64) return arith == SBO_ARITH_F32 ? launch_home_a<P, N, 0, CHOICE>(a, raised, st) : launch_home_a<P, N, 1, CHOICE>(a, raised, st); \
         } \

@@ -2,8 +2,8 @@
 // block that won the energy comparison (Section 2: x = Q_j^T y hard-thresholded to the
 // s0 entries of largest magnitude; Algorithm 1, steps 3-4).
 //
-// Signals arrive grouped by block (perm/offsets).  One wavefront takes a tile of up to
-// 32 signals of ONE block, so the projection is again one fp32 MFMA tile product with
+// Signals arrive grouped by block (perm/offsets), or every workgroup lists those of its own tiles (Source).  One wavefront
+// takes a tile of up to 32 signals of ONE block, so the projection is again one fp32 MFMA tile product with
 // atoms on M and signals on N; every signal's p coefficients then sit in two lanes.
 // The s0-th largest magnitude tau is found with the same compare-exchange networks as
 // in stage 1, and the support {|c| > tau} plus the lowest-index entries equal to tau is

@@ -187,8 +187,6 @@ hipError_t launch_sort(int K, const int32_t* blk, int64_t m, const GroupGeom& g,
 
 }  // namespace
 
-// have_hist: ws.chunk_count already holds the per-chunk histograms (written by the coding
-// kernel); otherwise they are computed from blk here.
 hipError_t launch_group_hist(int K, const int32_t* blk, int64_t m, const Workspace& ws, hipStream_t st) {
     if (K > kMaxK) return hipErrorInvalidValue;
     const GroupGeom g = group_geom(m);
@@ -197,6 +195,8 @@ hipError_t launch_group_hist(int K, const int32_t* blk, int64_t m, const Workspa
     return hipGetLastError();
 }
 
+// have_hist: ws.chunk_count already holds the per-chunk histograms (written by the coding
+// kernel); otherwise they are computed from blk here.
 hipError_t launch_group(int K, const int32_t* blk, int64_t m, const Workspace& ws, bool have_hist,
                         hipStream_t st) {
     if (K > kMaxK) return hipErrorInvalidValue;
