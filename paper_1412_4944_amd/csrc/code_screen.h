@@ -421,12 +421,16 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     int id_own = 0, home_lo = 0, home_hi = 0;  // own signal; the home blocks of the workgroup
     // GUESS: on their way, how far the blocks are from orthobases and which signals of the sample they represent
     constexpr int DEVS = GUESS ? (kGuessMaxK + 63) / 64 : 1, WORDS = kSample / 32, MASKS = GUESS ? 8 : 1;
-    float2 dev[DEVS];
+    unsigned dev[DEVS][2];
     unsigned seen[MASKS];                      // words lane % WORDS, of the last block once more past the end
     auto sample_word = [&](int w) { return g.sample[min(w + lane, (K - 1) * WORDS + lane % WORDS)]; };
     if constexpr (GUESS) {
 #pragma unroll
-        for (int e = 0; e < DEVS; ++e) dev[e] = g.dev[min(lane + 64 * e, K - 1)];
+        for (int e = 0; e < DEVS; ++e) {
+            const float2 d = g.dev[min(lane + 64 * e, K - 1)];
+            dev[e][0] = __builtin_bit_cast(unsigned, d.x);
+            dev[e][1] = __builtin_bit_cast(unsigned, d.y);
+        }
 #pragma unroll
         for (int e = 0; e < MASKS; ++e) seen[e] = sample_word(64 * e);
     }
@@ -844,9 +848,10 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 int weak = 32 - __popc(mask);
 #pragma unroll
                 for (int o = 1; o < WORDS; o <<= 1) weak += __shfl_xor(weak, o, 64);
+                constexpr unsigned line = __builtin_bit_cast(unsigned, kOrthobase * kOrthobase * 0.5f);       // of half of a block
                 bool close = true;
 #pragma unroll
-                for (int e = 0; e < DEVS; ++e) close = close && dev[e].x + dev[e].y <= kOrthobase * kOrthobase;
+                for (int e = 0; e < DEVS; ++e) close = close && max(dev[e][0], dev[e][1]) <= line;         // (bits: a NaN is above it)
                 halves = guess = __ballot(!close) == 0ull && __builtin_amdgcn_readfirstlane(weak) <= guess_weak(K);
             }
             // Bounds from home_rows atoms for all: a step takes the first 32 atoms of two blocks, or (p = 256) half of the

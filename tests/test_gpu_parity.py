@@ -520,6 +520,18 @@ def test_short_cuts_of_the_block_choice_are_taken(op, p, K, s0, m, kind, taken):
     assert n_taken >= 0.9 * n if taken == "most" else n_taken == 0
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.nan])
+def test_a_block_that_is_not_finite_is_no_orthobase(bad):
+    """Which block a signal gets is then anybody's guess, but not by bounds that hold for orthobases only."""
+    K, s0, m = 33, 5, 100003
+    Y, D = _home_case(64, K, s0, m, "planted")
+    D[7, 40, 3] = bad
+    with Sbo(64, K, s0, m) as g:
+        out, n, n_taken = g.short_cuts(m, lambda: g.code(Y, D))
+    assert n > 0 and n_taken == 0
+    assert (out[0] >= 0).all() and (out[0] < K).all()
+
+
 @pytest.mark.parametrize("p,K,s0,m", [(16, 4, 3, 513), (16, 60, 2, 70001), (32, 16, 4, 131072), (64, 5, 8, 1), (64, 33, 8, 65537),
                                       (64, 128, 3, 32768)])
 def test_update_lists_the_signals_of_a_piece_from_the_histograms(p, K, s0, m):
