@@ -380,7 +380,7 @@ template <int P>
 constexpr int kHomeFew = P > 64 ? 16 : 8;
 template <int P>
 constexpr int kWeakFew = P > 64 ? 16 : 4;
-constexpr int kWeakEvery = 4;
+constexpr int kWeakEvery = 4, kSameCounts = 8;
 constexpr int guess_weak(int K) { return K < 96 ? (K - 16) / 4 : 20; }
 
 // What a workgroup screens in full: everything; the home blocks of its signals; the block of the largest bound.
@@ -1360,7 +1360,18 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     // this workgroup's signals that chose block j (chunk is a multiple of SIG; the array is zero on
     // entry).  Integer atomics only: the sums do not depend on the order.
     if (HOME && by_home) {                     // uniform: of all chunks
-        if (valid) atomicAdd(&g.chunk_count[(unsigned)id_own / (unsigned)g.chunk * (unsigned)K + best], 1);
+        // Neighbours in a block's list are neighbours in the set where blocks are few: one addition for all signals of a wavefront that
+        // are of the same chunk and chose the same block (an addition for each, 64 to one address: six iterations on 262144 signals, p = 64,
+        // choice, K = 4 388 us, so 210; K = 16 387, 342; K = 32 493, 473; p = 256, 131072 signals, K = 8 669, 557).
+        const unsigned at = (unsigned)id_own / (unsigned)g.chunk * (unsigned)K + (unsigned)best;
+        unsigned long long left = __ballot(valid);
+        for (int t = 0; t < kSameCounts && left != 0ull; ++t) {
+            const int l = __builtin_ctzll(left);
+            const unsigned long long same = __ballot(valid && at == (unsigned)__builtin_amdgcn_readlane((int)at, l));
+            if (lane == l) atomicAdd(&g.chunk_count[at], __popcll(same));
+            left &= ~same;
+        }
+        if ((left >> lane & 1ull) != 0ull) atomicAdd(&g.chunk_count[at], 1);
     } else if (g.chunk_count != nullptr) {     // uniform
         int* lh = reinterpret_cast<int*>(front);
         __syncthreads();                       // the lists are dead
