@@ -1461,10 +1461,12 @@ hipError_t launch_home_p(const ScrArgs& a, int arith, LdsRaised* raised, hipStre
     }
     return hipErrorInvalidValue;
 }
-// Whether launch_home_p has a kernel for these sizes: where workgroups take more than 64 signals.
+// Whether launch_home_p has a kernel for these sizes: where workgroups take more than 64 signals, and there are steps to save.  p = 64, six
+// iterations, full / home blocks: K = 3 262144 signals 649 / 649 us, s0 = 8, 3 % noise 676 / 704, K = 5 641 / 637, 682 / 702, K = 7 665 / 656,
+// 713 / 724, K = 8 679 / 639, 711 / 710; 60001, K = 3 371 / 371, 389 / 401, K = 8 355 / 341, 378 / 375; p = 256, 131072, K = 2 2557 / 2502.
 template <int P>
 bool home_takes(const ScrArgs& a) {
-    return home_applies<P>(a.s0) && !scr_shared<P>(a);
+    return home_applies<P>(a.s0) && !scr_shared<P>(a) && a.K >= (P > 64 ? 1 : 8);
 }
 
 // s0 is a compile-time constant of the kernels.  It pays where the selection networks take part of the time (width s0

@@ -509,7 +509,8 @@ def test_iterations_in_one_call_are_iterations_in_calls_of_their_own(p, K, s0, m
     ("code", 64, 33, 7, 66000, "random", "none"), ("code", 64, 64, 5, 100003, "noise10", "none"), ("code", 64, 64, 5, 100003, "noise33", "most"),
     ("iterate", 64, 32, 6, 100003, "noise12", "most"), ("code", 64, 32, 8, 53001, "planted", "no kernel"),
     ("iterate", 64, 32, 6, 100003, "planted", "most"), ("iterate", 64, 70, 9, 53001, "planted", "most"), ("iterate", 64, 8, 8, 100003, "random", "none"),
-    ("iterate", 64, 7, 6, 90001, "unused", "none"), ("iterate", 64, 6, 10, 60001, "planted", "no kernel"), ("iterate", 256, 5, 12, 90001, "planted", "most")])
+    ("iterate", 64, 9, 6, 90001, "unused", "none"), ("iterate", 64, 6, 10, 60001, "planted", "no kernel"),
+    ("iterate", 64, 8, 6, 90001, "planted", "most"), ("iterate", 64, 7, 6, 90001, "planted", "no kernel"), ("iterate", 256, 2, 5, 90001, "planted", "most"), ("iterate", 256, 5, 12, 90001, "planted", "most")])
 def test_short_cuts_of_the_block_choice_are_taken(op, p, K, s0, m, kind, taken):
     """Whether the workgroups decide by guessed blocks (sbo_code) and home blocks (the last iteration), which no result shows."""
     Y, D = _home_case(p, K, s0, m, kind)
