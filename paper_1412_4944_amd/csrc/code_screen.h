@@ -408,6 +408,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
     int* any_flag = reinterpret_cast<int*>(wred + 2 * W);
     int* n_tasks = any_flag + 1;
     int* n_weak = n_tasks + 1;                 // HOME: weak signals, then blocks left in
+    int* ids = reinterpret_cast<int*>(thr);    // HOME, until the decision: the signals themselves
 
     const int tid = threadIdx.x, NTH = blockDim.x, NW = NTH >> 6;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -450,6 +451,8 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
         home_hi = min(hi, K - 1);
         const int64_t pos = wg0 + loc0 + lane;
         id_own = pos < m ? (by_home ? g.perm[pos] : (int)pos) : -1;
+        // (kept there: the loops have no register for it, and a register spilled makes the first launch wait 0.1 ms for scratch memory)
+        ids[loc0 + lane] = id_own;
     }
 
     // the dictionary's norms (most of the time one entry per thread; consumed below)
@@ -882,7 +885,6 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     }
                 };
                 int n_left = 0;            // blocks that the bounds leave in, besides the best one, of the own signal (weak, p = 64: below)
-                const unsigned t_left = !WIDE && t_home < kWeakBelow ? 0x10000u : t_home;
                 int last_block = -1;
                 auto leave = [&](float sum, int j) {
                     const float e = most - sum * e_scale;
@@ -900,7 +902,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     secondE = fmaxf(secondE, other ? e : -1.f);
                     const unsigned q = stored(e);
                     E16[j * SIG + loc0 + lane] = (unsigned short)q;
-                    n_left += other && q >= t_left;
+                    n_left += other && q >= t_home;
                 };
                 float part_sum[NT] = {0.f, 0.f};
                 auto bound = [&](const Acc& acc, int s, auto second_half) {
@@ -960,7 +962,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                     home_step(acc0, acc1, s, std::false_type{});
                     if (s + 1 < n_step) home_step(acc1, acc0, s + 1, std::true_type{});         // uniform
                     if (!GUESS && (s & 14) == 14) {        // too many to be resolved one by one: all over again, in full
-                        if (n_left != 0) atomicAdd(&n_weak[1], n_left);
+                        if (n_left != 0 && (WIDE || t_home >= kWeakBelow)) atomicAdd(&n_weak[1], n_left);
                         n_left = 0;
                         __syncthreads();
                         halves = n_weak[1] <= 2 * SIG;
@@ -979,7 +981,6 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 if (lane == 0 && mask != 0ull) at = atomicAdd(n_tasks, __popcll(mask));
                 at = __builtin_amdgcn_readfirstlane(at);
                 if (wanted) list[at + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)(loc0 + lane);
-                if constexpr (HOME) reinterpret_cast<int*>(key)[loc0 + lane] = id_own;
                 __syncthreads();
                 const int n_list = *n_tasks, n_pair = (K + 1) / 2;
                 u32x4 rows[2][UT][KS16];
@@ -996,7 +997,7 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
                 for (int t0 = 0; t0 < n_list; t0 += 32) {          // uniform
                     const int id = t0 + n < n_list ? (int)list[t0 + n] : -1;
                     ExactRow<P, 3> y;
-                    y.load(g, id < 0 ? (int64_t)-1 : HOME ? (int64_t)reinterpret_cast<const int*>(key)[id] : wg0 + id, h);
+                    y.load(g, id < 0 ? (int64_t)-1 : HOME ? (int64_t)ids[id] : wg0 + id, h);
                     if (wave < n_pair) look_up(wave);
                     u32x4 yb[KS16];
                     leading_parts(y, yb);
@@ -1287,9 +1288,12 @@ __global__ __launch_bounds__(64 * W, 2) void energy_screen_kernel(ScrArgs g) {
             if (blockIdx.x == 0 && lane == 0) g.weak[(g.turn + 1) % 3] = 0;
         }
     if (!SHARED || wave == 0) {
+        if constexpr (HOME) {
+            id_own = ids[loc0 + lane];
+            reinterpret_cast<int*>(r2s)[loc0 + lane] = id_own;                     // (its own signal's: used above)
+        }
         thr[loc0 + lane] = undecided ? t16 : 0x10000u;
         key[loc0 + lane] = 0ull;
-        if constexpr (HOME) reinterpret_cast<int*>(r2s)[loc0 + lane] = id_own;     // (its own signal's: used above)
     }
     if (__ballot(undecided) != 0ull && lane == 0) *any_flag = 1;
     __syncthreads();
