@@ -232,16 +232,17 @@ constexpr int64_t kDirectMaxEnergies = 32768;  // K m (and no more signals than 
 //   an iteration p = 64, K = 32 48000 77 / 71, 84 / 81; p = 32, K = 32 81000 51 / 47, 55 / 54, 63 / 64, 98000 57 / 54, 62 / 63, 68 / 71; p = 16,
 //                K = 64 65000 45 / 39
 // and where all blocks but one have 300 signals at most 5 more up to 81000, 8 to 13 at 131000: up to 160 chunks what even blocks gain is
-// at least what the most uneven ones lose.  With up to 5 blocks, of which it takes more to make one rare, 256 chunks
-// (the largest sets measured): 126800 signals, K = 5, evenly, Zipf(1.1), (2), (3), (5) sbo_code p = 32 36 / 34, 36 / 34, 36 / 34, 36 / 37,
-// 35 / 42, p = 64 50 / 46, 49 / 46, 49 / 47, 49 / 50, 48 / 56, sbo_update p = 16 32 / 28, 35 / 32, 39 / 36, 40 / 41, 43 / 48, an iteration p = 32 47 / 43, 52 / 47,
-// 54 / 51, 56 / 60; K = 8 sbo_code p = 64 56 / 52, 55 / 53, 56 / 54, 53 / 61, sbo_update p = 32 35 / 30, 40 / 36, 43 / 45, 47 / 54.
+// at least what the most uneven ones lose.  With up to 8 blocks it takes more than Zipf(2) to make one
+// so rare: 256 chunks (the largest sets measured).  126800 signals, evenly, Zipf(1.1), (2), (3): K = 5 sbo_code p = 32 36 / 34, 36 / 34, 36 / 34, 36 / 37,
+// sbo_update p = 16 32 / 28, 35 / 32, 39 / 36, 40 / 41, an iteration p = 32 47 / 43, 52 / 47, 54 / 51, 56 / 60; K = 8 sbo_code p = 64 56 / 52, 55 / 53,
+// 56 / 54, 53 / 61, sbo_update p = 16 32 / 28, 35 / 31, 39 / 40, 40 / 47, an iteration p = 16 39 / 36, 42 / 39, 47 / 47, 49 / 55; K = 12 sbo_code p = 64
+// 60 / 57, 60 / 57, 60 / 63, sbo_update p = 16 33 / 29, 34 / 31, 38 / 44.
 // More entries than 9216: K = 64 100003 signals (p = 32) 68.9 / 74.5 evenly, K = 128 40000 49.4 /
 // 49.8; iterations with K > 128: 4096, where it was measured (sbo_code with K = 200 loses beyond).  p = 256, sbo_code, K = 16
 // 16000 signals 94 / 87, 65000 264 / 262, 100003 337 / 341.  Iterations at p = 64: as long as none takes its signals in the
 // order of the grouping (home blocks: workgroups of more than 64 signals).  sbo_code of 1025 to 2048 signals would gain 4 to 7 us
 // (K = 4 to 128, every p), but the time of the grouping stage there is one that callers get to read.
-constexpr int64_t list_signals(int K) { return (K <= 5 ? 256 : 160) * 512; }
+constexpr int64_t list_signals(int K) { return (K <= 8 ? 256 : 160) * 512; }
 inline bool few_entries(int K, int64_t m) { return (int64_t)((m + 511) / 512 + 8) * K <= (K <= 128 ? 9216 : 4096); }
 inline bool lists_in_round(int p, int K, int64_t m) {
     return p <= 64 && m <= list_signals(K) && (p < 64 || screen_shared(m, true)) && few_entries(K, m);
