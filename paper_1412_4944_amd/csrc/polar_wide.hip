@@ -1,5 +1,5 @@
 // Batched SVD update Q_j = U V^T (Algorithm 1, steps 6-7) for p = 256: a team of 16 workgroups per
-// block, one launch for everything.
+// block (32 where there are eight blocks or fewer), one launch for everything.
 //
 // A 256 x 256 matrix in the three bf16 parts that fp32 accuracy takes is 384 KiB: more than the LDS of
 // a CU, and one CU alone would need 80 us of matrix time for a block.  So 16 workgroups share a block
@@ -16,6 +16,13 @@
 //   makes two 16 x 16 tiles of both products; its loads run four contraction steps ahead and through from
 //   the first product into the second.
 //
+//   Up to eight blocks, a team on each XCD: two workgroups to a strip, one for the upper and one for the lower half of its rows,
+//   which halves the operands that each of them reads.  They need each other's half of X, which comes with the barrier, and of E:
+//   a number in memory says when it is there, and half of the contraction runs meanwhile.  The second workgroups are helpers: if
+//   they have not come when the first are all there and have waited a little, these go on without (meet_pairs), so that a
+//   launch needs no more of the chip at a time than one with teams of 16.  Sums are made in the same order in every case:
+//   the same bits.
+//
 //   A block on which that does not converge (rank-deficient, zero, NaN), every block under
 //   SBO_SVD_JACOBI, and the eigenvectors of a Gram matrix: one-sided Jacobi with eight of the
 //   workgroups.  Columns in 16 sets of 16; a workgroup rotates all pairs of two sets (one set's columns of A
@@ -24,18 +31,22 @@
 //   handed over through memory with a version number; there is no barrier but one per sweep.
 //
 // What bounds it: Newton-Schulz by the 512 KiB of operands per workgroup and step from L2 (30 bytes a cycle arrive at a CU, no
-// more with one team on an XCD than with two, or with more loads on their way): of 27000 cycles a step 14000 are the first product
-// and the wait for its slowest wavefront, 6300 the second (the splits), 5000 the barrier.  With the three parts in memory (768 KiB)
-// 138 -> 131 us in the same profile, K = 16; K = 4 no difference.  Jacobi by the vector ALU
+// more with one team on an XCD than with two, or with more loads on their way; pairs 256 KiB): of 25500 cycles a step 10900 are the
+// first product and the wait for its slowest wavefront, 9500 the second (the splits), 3400 the barrier; with pairs, of 21000 7500, 7000 and
+// 5000.  K = 4 114 -> 88 us, K = 16 131 -> 124 (9 steps from a finished matrix): 103 with pairs alone, the rest because the compiler
+// took the operands' descriptor and offsets for different ones in every lane (a loop around every load) and a flat load among
+// them waited for all of them.  Eight steps of operands on their way instead of four: 91 us (registers spilled, and half of
+// the wavefronts get theirs late).  With the three parts in memory (768 KiB) 138 -> 131 us in the same profile,
+// K = 16; K = 4 no difference.  Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  Jacobi is called, not inlined,
 // where a block may need it after Newton-Schulz, whose operands take all registers (inlined: 100 of them spilled, K = 16 147 us
-// instead of 130); the norm and the smallest diagonal entry of a step share a barrier (130 -> 126).
+// instead of 130; so is a pair team's way on without its helpers); the norm and the smallest diagonal entry of a step share a barrier (130 -> 126).
 // Measured: K = 16 inside sbo_iterate 347 us (a launch per product and step, fp32 matrix instruction,
 // 20 steps enqueued, plus launches for the sum of the pieces, the Jacobi SVD that has nothing to do,
 // the operand order and the squared error: 46 launches, 400 us) -> 126 us and nothing else; K = 1 in a
 // first training round 300 -> 125 us; eigenvectors of a Gram matrix (10 sweeps) 12.1 -> 1.8 ms.
 //
-// Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups, one per CU, and workgroups
+// Waiting on other workgroups: a launch has at most 16 teams of 16 workgroups (helpers not counted), one per CU, and workgroups
 // start in order.  A launch that does not have the chip to itself can hold at most 15 workgroups of an
 // incomplete team on an XCD (32 CUs), so two launches at a time always leave room for one to complete a
 // team.  With contexts of this size on more than two streams the teams lie in consecutive workgroups instead
@@ -57,9 +68,12 @@ namespace sbo {
 namespace {
 
 constexpr int P = 256;
-constexpr int kTeam = 16;                      // workgroups per block
+constexpr int kTeam = 16;                      // workgroups per block, of as many columns each,
+constexpr int kPairs = 32;                     // or two for each of these strips
 constexpr int kJacTeam = 8;
 constexpr int kMaxTeams = 16;                  // blocks at a time
+constexpr int kMaxPairTeams = 8;               // with pairs: one team on each XCD
+constexpr int kHelperPolls = 64;               // for the second workgroups of the pairs, when the first are all there (60 us)
 constexpr int kNT = 512;
 constexpr int kWaves = kNT / 64;
 constexpr int kMaxSweeps = 24;
@@ -76,16 +90,20 @@ constexpr size_t kEAt = kRowAt + 2 * (size_t)kTeam * kShared;  // [16 strips][8]
 constexpr size_t kJaAt = kEAt + (size_t)kTeam * 8 * 1024;      // [256 columns][256] A
 constexpr float kEScale = 8192.f;                              // of those: 1e-2 is in the middle of fp16's range
 constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
-constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;         // red[2][4][kCarried][16] | sigma[256] | 1/|v|[256]
+// red[2][4][kCarried][32] | sigma[256] | 1/|v|[256] | pairs: sums of each half of the columns [2 halves][2][256]
+constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;
 constexpr int kCarried = 5;                                    // floats of each workgroup that a barrier carries
-constexpr int kRedSize = 4 * kCarried * 16;
-constexpr size_t kTeamBytes = kSmallAt + 5120;
-static_assert((2 * kRedSize + 2 * P) * 4 <= 5120, "the team's small memory");
+constexpr int kRedSize = 4 * kCarried * kPairs;
+constexpr int kSmallFloats = 2 * kRedSize + 2 * P + 4 * P;
+constexpr size_t kELoAt = (kSmallAt + kSmallFloats * 4 + 255) / 256 * 256;     // pairs: second fp16 parts of E, as the first at kEAt,
+constexpr size_t kEHalfAt = kELoAt + (size_t)kTeam * 8 * 1024;                 // and E in fp32, [16 strips][16 tiles][64 lanes][16 bytes]
+constexpr size_t kTeamBytes = kEHalfAt + (size_t)kTeam * kShared;
 // and its counters (ints, zero between launches), each on a cache line of its own
-constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kUndoneAt = 129, kVersionAt = 160, kMeetAt = 192, kSyncInts = 224;
+constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kUndoneAt = 129, kVersionAt = 160, kMeetAt = 192, kPairAt = 224, kPairInts = 16,
+              kSyncInts = kPairAt + kPairs * kPairInts;
 // Added to a barrier's counter by a workgroup that gives up (no barrier counts as far, and 16 times it fits an int).
 constexpr int kGone = 1 << 24;
-constexpr unsigned long long kGoneMeet = 1ull << 62;
+constexpr unsigned long long kGoneMeet = 1ull << 62, kNoHelpers = 1ull << 61;
 
 // LDS
 constexpr int kEimgAt = kImage;
@@ -108,13 +126,14 @@ struct WideArgs {
     int max_iters, K, teams;
     int spread;
     int polls;                 // of one wait, at most
+    int helper_polls;          // for the second workgroups of the pairs (-1: they leave at once)
     unsigned char* data;       // [teams][kTeamBytes]
     int* sync;                 // [teams][kSyncInts]
     SqTotalArgs sq;
 };
 
-__host__ __device__ inline int wide_team_wgs(int teams, int spread) {
-    return spread ? teams * kTeam : (teams + 7) / 8 * 128;
+__host__ __device__ inline int wide_team_wgs(int teams, int spread, bool pairs) {
+    return pairs ? 8 * kPairs : spread ? teams * kTeam : (teams + 7) / 8 * 128;
 }
 
 __device__ __forceinline__ float half_sum(float x) {           // over 32 lanes
@@ -164,7 +183,7 @@ __device__ __forceinline__ void raise_to(int* p, int v, bool near) {
 // A barrier of `size` workgroups that carries kCarried floats of each of them.
 struct Team {
     int* arrive;               // the counters: of the agent scope, then (a cache line on) near ones
-    float* red;                // [4][kCarried][16]
+    float* red;                // [4][kCarried][32]
     int* ok;                   // LDS
     int size, q, polls;
     int epoch, arrived;        // barriers so far; of this kind
@@ -181,12 +200,12 @@ struct Team {
         ++epoch;
         ++arrived;
         if (threadIdx.x == 0) {
-            float* slot = red + (epoch & 3) * (16 * kCarried) + q;
+            float* slot = red + (epoch & 3) * (kPairs * kCarried) + q;
             slot[0] = a;
-            slot[16] = b;
-            slot[32] = c;
-            slot[48] = d;
-            slot[64] = e;
+            slot[kPairs] = b;
+            slot[2 * kPairs] = c;
+            slot[3 * kPairs] = d;
+            slot[4 * kPairs] = e;
         }
         stores_done();
         if (threadIdx.x == 0) {
@@ -201,24 +220,22 @@ struct Team {
         __syncthreads();
         return *ok != 0;
     }
-    // The first barrier of a launch, which finds out whether the team is near: a counter of five bits per XCD.
+    // The first barrier of a launch, which finds out whether the team is near: a counter of six bits per XCD.
     // If it is, what was stored before is where the others look; if not, a barrier of the other kind follows.
     __device__ __forceinline__ bool meet(unsigned long long* count) {
         stores_done();
         if (threadIdx.x == 0) {
             int xcc;
             asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
-            const int field = 5 * (xcc < 8 ? xcc : 8);
+            const int field = 6 * (xcc < 8 ? xcc : 8);
             __hip_atomic_fetch_add(count, 1ull << field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             unsigned long long v = 0;
             const bool here = poll(polls, true, [&]() {
                 v = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                int n = 0;
-                for (int f = 0; f <= 40; f += 5) n += (int)(v >> f) & 31;
-                return n == size || v >= kGoneMeet;
+                return met(v) == size || v >= kGoneMeet;
             });
             if (!here) __hip_atomic_fetch_or(count, kGoneMeet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *ok = !here || v >= kGoneMeet ? 0 : xcc < 8 && (int)(v >> field & 31) == size ? 2 : 1;
+            *ok = !here || v >= kGoneMeet ? 0 : xcc < 8 && (int)(v >> field & 63) == size ? 2 : 1;
         }
         __syncthreads();
         const int how = *ok;
@@ -226,10 +243,59 @@ struct Team {
         if (how == 1) return sync(0.f);        // (begins with a barrier: *ok has been read)
         return how != 0;
     }
+    __device__ __forceinline__ static int met(unsigned long long v) {
+        int n = 0;
+        for (int f = 0; f <= 48; f += 6) n += (int)(v >> f) & 63;
+        return n;
+    }
+    // The same for a team of pairs: 1 all are there, 0 a wait has ended, -1 without the helpers (the second half of the
+    // workgroups): one of the first half saw these complete, waited helper_polls times and put kNoHelpers into the counter
+    // before the last helper came.  A counter that has all of them and not that bit never gets it, so all read the same.
+    // first (bits 54 ..): of the first half.
+    __device__ __forceinline__ int meet_pairs(unsigned long long* count, int helper_polls) {
+        stores_done();
+        if (threadIdx.x == 0) {
+            int xcc;
+            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
+            const int field = 6 * (xcc < 8 ? xcc : 8);
+            const bool helper = q >= kTeam;
+            __hip_atomic_fetch_add(count, (1ull << field) + (helper ? 0 : 1ull << 54), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int how = -2;
+            for (int k = 0, waited = 0; how == -2; ++k) {
+                unsigned long long v = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int first = (int)(v >> 54) & 31;
+                const bool without = (v & kNoHelpers) != 0;
+                if (v >= kGoneMeet) {
+                    how = 0;
+                } else if (!without && met(v) == kPairs) {
+                    how = xcc < 8 && (int)(v >> field & 63) == kPairs ? 2 : 1;
+                } else if (without && (helper || first == kTeam)) {
+                    how = -1;
+                } else if (k >= polls && !helper && first < kTeam) {
+                    __hip_atomic_fetch_or(count, kGoneMeet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    how = 0;
+                } else if (k >= polls || (!helper && first == kTeam && ++waited > helper_polls)) {
+                    __hip_atomic_compare_exchange_strong(count, &v, v | kNoHelpers, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);      // (fails: look again)
+                }
+                if (how == -2) __builtin_amdgcn_s_sleep(1);
+            }
+            if (how > 0) asm volatile("buffer_inv sc0" ::: "memory");
+            *ok = how;
+        }
+        __syncthreads();
+        const int how = *ok;
+        near = how == 2;
+        if (how == 1) return sync(0.f) ? 1 : 0;
+        if (how == -1) __syncthreads();        // *ok has been read
+        return how > 0 ? 1 : how;
+    }
     // value k of workgroup lane % size, from the last sync
     __device__ __forceinline__ float value(int k) const {
-        return __hip_atomic_load(red + (epoch & 3) * (16 * kCarried) + k * 16 + (threadIdx.x & (size - 1)), __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+        // (a flat load would have to be waited for with all loads before and after it)
+        typedef __attribute__((address_space(1))) float* global_ptr;
+        return __hip_atomic_load((global_ptr)(red + (epoch & 3) * (kPairs * kCarried) + k * kPairs + (threadIdx.x & (size - 1))),
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
 
@@ -252,6 +318,15 @@ __device__ __forceinline__ float wave_max(float x) {
     auto q = __builtin_amdgcn_permlane32_swap(w, w, false, false);
     const unsigned b0 = q[0], b1 = q[1];
     return fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
+}
+__device__ __forceinline__ float wave_max_nan(float x) {
+    unsigned u = __builtin_bit_cast(unsigned, row_max_nan(x));
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned a0 = r[0], a1 = r[1];
+    u = max(a0, a1);
+    auto q = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const unsigned b0 = q[0], b1 = q[1];
+    return __builtin_bit_cast(float, max(b0, b1));
 }
 // Sums over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (bitwise the same in all of them).
 __device__ __forceinline__ float sum_groups(float x) {
@@ -290,6 +365,24 @@ __device__ __forceinline__ void load_strip(const Source& src, int s, f32x4 (&v)[
                 for (int u = 0; u < 2; ++u) v[u] += w[k][u];
             }
     }
+}
+
+// 16-byte unit (tid % 32) + 32 h of column tid / 32 of strip s: half h of its rows
+__device__ __forceinline__ f32x4 load_half_strip(const Source& src, int s, int h) {
+    constexpr int kInFlight = 16;
+    const f32x4* b = reinterpret_cast<const f32x4*>(src.base) + s * (16 * P / 4) + (threadIdx.x >> 5) * (P / 4) + 32 * h +
+                     (threadIdx.x & 31);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int pc = 0; pc < src.n; pc += kInFlight) {
+        f32x4 w[kInFlight];
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+            if (pc + k < src.n) w[k] = b[(int64_t)(pc + k) * (P * P / 4)];         // uniform
+#pragma unroll
+        for (int k = 0; k < kInFlight; ++k)
+            if (pc + k < src.n) v += w[k];
+    }
+    return v;
 }
 
 // D[j] rows of strip s from LDS ([16][kLdStrip]), and the same rows in the operand orders.  dn: 256 floats of LDS.
@@ -332,15 +425,33 @@ __device__ __forceinline__ void emit_strip(const WideArgs& g, int j, int s, cons
     __syncthreads();
 }
 
-enum class Outcome { done, left, dead };       // left: to the Jacobi SVD; dead: a wait has ended
+__device__ __forceinline__ unsigned char* uniform(unsigned char* p) {
+    const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    // (of the global address space: flat accesses are counted with those of LDS)
+    return (unsigned char*)(__attribute__((address_space(1))) unsigned char*)((unsigned long long)hi << 32 | lo);
+}
 
-// Newton-Schulz for a block; strip `t.q` of the result is left in LDS at kStripAt.  first != nullptr: the team
-// has not met yet.
-__device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source& src, Team& t,
+enum class Outcome { done, left, dead, alone };        // left: to the Jacobi SVD; dead: a wait has ended; alone: without helpers
+
+// Newton-Schulz for block j.  H = 1: strip `t.q` of the result is left in LDS at kStripAt; first != nullptr: the team has not met yet.
+// H = 2, a team of pairs, which meets here: workgroups s and s + 16 have the upper and the lower half of strip s's rows, a
+// wavefront one tile of both products, and write their halves of D[j].  The B operand of a product is the whole strip: the
+// contraction starts with the own half, and the other one comes by memory meanwhile, X with the team's barrier, E with a
+// number in `pair`.
+template <int H>
+__device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const Source& src, Team& t,
                                                  unsigned long long* first, unsigned char* mem, unsigned char* lds,
-                                                 float* red, int& steps) {
+                                                 float* red, int* pair, int& steps) {
+    constexpr int NT = 2 / H;                  // tiles of a wavefront
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = lane >> 4, c16 = lane & 15;
+    // (Uniform, which the compiler does not see of what has been through a call or a wait: every operand load was a loop over
+    // the lanes' descriptors and offsets.)
+    const int tq = __builtin_amdgcn_readfirstlane(t.q);
+    mem = uniform(mem);
+    const int sn = H == 1 ? tq : tq & (kTeam - 1), half = H == 1 ? 0 : tq / kTeam;         // the strip, which half
+    const int t0 = H == 1 ? 2 * wave : half * 8 + wave, tp = (1 - half) * 8 + wave;        // the first tile; one of the other half
     unsigned char* ximg = lds;
     unsigned char* eimg = lds + kEimgAt;
     float* strip = reinterpret_cast<float*>(lds + kStripAt);
@@ -362,75 +473,125 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         out[1] = u32x4{a.mid, b.mid, c.mid, d.mid};
         out[2] = u32x4{a.lo, b.lo, c.lo, d.lo};
     };
-    // xr[k]: rows (2 wave + k) * 16 + grp * 4 .. +3 of column t.q * 16 + c16
-    f32x4 xr[2];
-    {
-        f32x4 v[2];
-        load_strip(src, t.q, v);
+    // The parts of the tiles t0 .. (or of one tile) in an image of the strip: contraction step of 32 = two tiles, a half unit each.
+    auto put_tile = [&](unsigned char* img, int tile, f32x4 v) {
+        const Bf16x3Pair a = split_bf16x3(v.x, v.y), b = split_bf16x3(v.z, v.w);
+        u32x2* at = reinterpret_cast<u32x2*>(img + (tile >> 1) * 3 * 1024 + lane * 16 + (tile & 1) * 8);
+        at[0] = u32x2{a.hi, b.hi};
+        at[128] = u32x2{a.mid, b.mid};
+        at[256] = u32x2{a.lo, b.lo};
+    };
+    auto put_parts = [&](unsigned char* img, const f32x4 (&v)[NT]) {
+        if constexpr (H == 1) {
+            u32x4 part[3];
+            split(v[0], v[NT - 1], part);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int e = tid + u * kNT;
-            *reinterpret_cast<f32x4*>(strip + (e >> 6) * kLdStrip + 4 * (e & 63)) = v[u];
+            for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(img + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
+        } else {
+            put_tile(img, t0, v[0]);
+        }
+    };
+    // over the values that a barrier carried (H = 2: the two of a pair first)
+    auto all_sum = [](float v) {
+        if constexpr (H == 2) {
+            const unsigned u = __builtin_bit_cast(unsigned, v);
+            auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+            const unsigned a0 = r[0], a1 = r[1];
+            v = __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
+        }
+        return group_sum<16>(v);
+    };
+    auto all_max = [](float v) {
+        v = row16_max(v);
+        if constexpr (H == 2) {
+            const unsigned u = __builtin_bit_cast(unsigned, v);
+            auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+            const unsigned a0 = r[0], a1 = r[1];
+            v = fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1));
+        }
+        return v;
+    };
+    // xr[k]: rows (t0 + k) * 16 + grp * 4 .. +3 of column sn * 16 + c16
+    f32x4 xr[NT];
+    {
+        if constexpr (H == 1) {
+            f32x4 v[2];
+            load_strip(src, sn, v);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int e = tid + u * kNT;
+                *reinterpret_cast<f32x4*>(strip + (e >> 6) * kLdStrip + 4 * (e & 63)) = v[u];
+            }
+        } else {
+            const f32x4 v = load_half_strip(src, sn, half);
+            *reinterpret_cast<f32x4*>(strip + (tid >> 5) * kLdStrip + 128 * half + 4 * (tid & 31)) = v;
+            if (tid == 0) {                    // what workgroups without a tile on the diagonal say of it
+                red[kDiagAt] = 3e38f;
+                red[kDiagAt + 1] = 0.f;
+            }
         }
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            xr[k] = *reinterpret_cast<const f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4);
+        for (int k = 0; k < NT; ++k)
+            xr[k] = *reinterpret_cast<const f32x4*>(strip + c16 * kLdStrip + (t0 + k) * 16 + grp * 4);
     }
     // Leaves the strip for the others (buffer buf), in fp32, and its parts in ximg.  Contraction step s of 32 = tiles 2s and
     // 2s + 1, its two halves: a lane holds rows grp * 4 .. of both, which is what an accumulator leaves it, and of the rows'
     // image four columns grp * 4 .. of a row, by way of LDS (the wavefront's own part of `strip`).
     auto publish = [&](int buf) {
-        u32x4 part[3];
-        split(xr[0], xr[1], part);
-        unsigned char* cols = mem + kColAt + ((size_t)buf * kTeam + t.q) * kShared;
+        unsigned char* cols = mem + kColAt + ((size_t)buf * kTeam + sn) * kShared;
         unsigned char* rows = mem + kRowAt + (size_t)buf * kTeam * kShared;
+        put_parts(ximg, xr);
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(ximg + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            *reinterpret_cast<f32x4*>(cols + (wave * 2 + k) * 1024 + lane * 16) = xr[k];
-            *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4) = xr[k];
+        for (int k = 0; k < NT; ++k) {
+            *reinterpret_cast<f32x4*>(cols + (t0 + k) * 1024 + lane * 16) = xr[k];
+            *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (t0 + k) * 16 + grp * 4) = xr[k];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int td = 2 * wave + k;
+        for (int k = 0; k < NT; ++k) {
+            const int td = t0 + k;
             const float* row = strip + td * 16 + c16;          // of columns 0, 1, ..
-            *reinterpret_cast<f32x4*>(rows + (size_t)((td * 8 + (t.q >> 1)) * 2 + (t.q & 1)) * 1024 + lane * 16) =
+            *reinterpret_cast<f32x4*>(rows + (size_t)((td * 8 + (sn >> 1)) * 2 + (sn & 1)) * 1024 + lane * 16) =
                 f32x4{row[(4 * grp) * kLdStrip], row[(4 * grp + 1) * kLdStrip], row[(4 * grp + 2) * kLdStrip],
                       row[(4 * grp + 3) * kLdStrip]};
         }
     };
-    // Smallest diagonal entry of G in this workgroup's columns (two tiles lie on the diagonal, both in the wavefront of
-    // tile t.q, which leaves it in red[kDiagAt]: there after the next barrier).
-    auto least_diag = [&](const f32x4 (&gm)[2]) {
-        if (wave != (t.q >> 1)) return;        // uniform
+    auto on_diagonal = [&](int k, int r) { return (t0 + k) * 16 + grp * 4 + r == sn * 16 + c16; };
+    const bool diagonal = sn >= t0 && sn < t0 + NT;            // uniform: this wavefront has the tile on the diagonal
+    // Smallest diagonal entry of G in this workgroup's columns (left in red[kDiagAt]: there after the next barrier).
+    auto least_diag = [&](const f32x4 (&gm)[NT]) {
+        if (!diagonal) return;
         float v = 3e38f;
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < NT; ++k)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) v = gm[k][r];
+                if (on_diagonal(k, r)) v = gm[k][r];
         v = -wave_max(-v);
         if (lane == 0) red[kDiagAt] = v;
     };
     // E = I - a2 G
-    auto make_e = [&](const f32x4 (&gm)[2], float a2, f32x4 (&e)[2]) {
+    auto make_e = [&](const f32x4 (&gm)[NT], float a2, f32x4 (&e)[NT]) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < NT; ++k)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                e[k][r] = ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16 ? 1.f : 0.f) - a2 * gm[k][r];
+            for (int r = 0; r < 4; ++r) e[k][r] = (on_diagonal(k, r) ? 1.f : 0.f) - a2 * gm[k][r];
     };
 
     // A product: contraction steps S0 .. S0 + 7, their A operands requested kAhead steps before and split here, the B operands
-    // from an image in LDS one step before; two sums per tile, so that four matrix instructions are independent.
-    auto product = [&](auto& a, auto& request, auto& turn, const unsigned char* img, auto first_step, f32x4 (&out)[2]) {
-        constexpr int S0 = decltype(first_step)::value;
-        f32x4 sum[2][2] = {{zero4, zero4}, {zero4, zero4}};
+    // from an image in LDS one step before; sums apart, so that matrix instructions are independent.  H = 2: ask() before the last
+    // step of the own half, have() before the first of the other one.
+    auto product = [&](auto& a, auto& request, auto& turn, const unsigned char* img, auto first_step, f32x4 (&out)[NT], auto&& ask,
+                       auto&& have) {
+        constexpr int S0 = decltype(first_step)::value, NS = 4;
+        f32x4 sum[NT][NS];
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+#pragma unroll
+            for (int c = 0; c < NS; ++c) sum[k][c] = zero4;
         u32x4 b[2][3];
         auto read = [&](int s) {
 #pragma unroll
@@ -439,24 +600,48 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         read(S0);
 #pragma unroll
         for (int s = S0; s < S0 + 8; ++s) {
-            if (s + 1 < S0 + 8) read(s + 1);
-            u32x4 part[2][3];
+            if (H == 2 && s == S0 + 3) ask();
+            if (H == 2 && s == S0 + 4) {
+                have();
+                read(s);
+            }
+            if (s + 1 < S0 + 8 && !(H == 2 && s == S0 + 3)) read(s + 1);
+            u32x4 part[NT][3];
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int k = 0; k < NT; ++k)
                 split(__builtin_bit_cast(f32x4, a[s % kAhead][k][0]), __builtin_bit_cast(f32x4, a[s % kAhead][k][1]), part[k]);
 #pragma unroll
             for (int q = 0; q < 6; ++q)
 #pragma unroll
-                for (int k = 0; k < 2; ++k) sum[k][q & 1] = mfma(part[k][TA[q]], b[s & 1][TB[q]], sum[k][q & 1]);
+                for (int k = 0; k < NT; ++k) sum[k][q % NS] = mfma(part[k][TA[q]], b[s & 1][TB[q]], sum[k][q % NS]);
             if (s + kAhead < 16) request(s + kAhead);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int k = 0; k < 2; ++k) out[k] = sum[k][0] + sum[k][1];
+        for (int k = 0; k < NT; ++k) out[k] = (sum[k][0] + sum[k][1]) + (sum[k][2] + sum[k][3]);
     };
 
     publish(0);
-    if (!(first != nullptr ? t.meet(first) : t.sync(0.f))) return Outcome::dead;
+    if constexpr (H == 2) {
+        const int how = t.meet_pairs(first, g.helper_polls);
+        if (how <= 0) return how < 0 ? Outcome::alone : Outcome::dead;
+    } else {
+        if (!(first != nullptr ? t.meet(first) : t.sync(0.f))) return Outcome::dead;
+    }
+    // H = 2, handing something to the other workgroup of the pair
+    int handed = 0;
+    auto hand = [&]() {
+        stores_done();
+        ++handed;
+        if (tid == 0) raise_to(pair + t.q * kPairInts, handed, t.near);
+    };
+    auto taken = [&]() {                       // the same number of hands from there (uniform)
+        int* flag = t.ok + 1;
+        if (tid == 0)
+            *flag = poll(t.polls, t.near, [&]() { return peek(pair + (t.q ^ kTeam) * kPairInts, t.near) >= handed; });
+        __syncthreads();
+        return *flag != 0;
+    };
     float prev = 3e38f;                        // |I - X^T X|_F^2 before the step before
     NsScale scale;
     bool look = false;
@@ -465,78 +650,128 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         // descriptor, a scalar offset per load (as pointers the addresses alone take 100 registers).  Every
         // wavefront of the team starts at another step: in step, they would all ask the same L2
         // channels at a time.
-        const int cols = (int)kColAt + ((it & 1) * kTeam + 2 * wave) * kShared;
-        const int rows = (int)kRowAt + ((it & 1) * kTeam + 2 * wave) * kShared;
-        u32x4 a[kAhead][2][2];
-        auto turn = [&](int s) { return (s + wave + t.q) & 7; };
+        const int buf = __builtin_amdgcn_readfirstlane(it & 1);
+        const int cols = (int)kColAt + (buf * kTeam + t0) * kShared;
+        const int rows = (int)kRowAt + (buf * kTeam + t0) * kShared;
+        u32x4 a[kAhead][NT][2], other = {0u, 0u, 0u, 0u};
+        // The steps of the tile's half first (H = 2 has the others later), in an order that is the same for both H: so are the sums.
+        const int own4 = (t0 >> 3) * 4;
+        auto turn = [&](int s) { return ((s & 4) ^ own4) | ((s + (t0 >> 1) + sn) & 3); };
         auto request = [&](int s) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int k = 0; k < NT; ++k)
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
                     a[s % kAhead][k][e] = __builtin_amdgcn_raw_buffer_load_b128(
                         rsrc, lane * 16, (s < 8 ? cols : rows) + k * kShared + (turn(s) * 2 + e) * 1024, 0);
         };
+        // What the last barrier carried: asked for before the operands, which it would otherwise wait for (loads return in order).
+        const float carried0 = look ? t.value(0) : 0.f, carried1 = look ? t.value(1) : 0.f;    // uniform
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (H == 2)                  // a tile of the strip's other half
+            other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)kColAt + (buf * kTeam + sn) * kShared + tp * 1024, 0);
 #pragma unroll
         for (int s = 0; s < kAhead; ++s) request(s);
-        if (look) {                            // uniform: what the last barrier carried, with the operands on their way
-            prev = group_sum<16>(t.value(0));
+        __builtin_amdgcn_sched_barrier(0);
+        if (look) {                            // uniform
+            prev = all_sum(carried0);
             if (!(prev < 2.f * P)) return Outcome::left;
-            scale.seen(-row16_max(-t.value(1)));
+            scale.seen(-all_max(-carried1));
         }
-        f32x4 gm[2];
-        product(a, request, turn, ximg, std::integral_constant<int, 0>{}, gm);
+        f32x4 gm[NT];
+        product(a, request, turn, ximg, std::integral_constant<int, 0>{}, gm, []() {},
+                [&]() {
+                    put_tile(ximg, tp, __builtin_bit_cast(f32x4, other));
+                    __syncthreads();
+                });
 
         float alpha = 1.f, fr = 0.f;
         bool last = false, known = false;
-        // |I - G|_F^2 of the workgroup's columns and their smallest diagonal entry: by one thread, after a barrier
+        // |I - G|_F^2 of the workgroup's part of G: by one thread, after a barrier
         auto own_norm = [&]() {
             float v = 0.f;
             for (int w = 0; w < kWaves; ++w) v += red[(it & 1) * 8 + w];
             return v;
         };
-        f32x4 e[2];
+        f32x4 e[NT];
         if (it == 0) {
-            float rs = 0.f, r2 = 0.f;
+            // row sums and squares by columns: of a tile, then of half a column, then of a column (the same order for both H)
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int k = 0; k < NT; ++k) {
+                float rs = 0.f, r2 = 0.f;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     rs += fabsf(gm[k][r]);
                     r2 = fmaf(gm[k][r], gm[k][r], r2);
                 }
-            rs = sum_groups(rs);
-            r2 = sum_groups(r2);
-            if (lane < 16) {
-                red[wave * 16 + lane] = rs;
-                red[128 + wave * 16 + lane] = r2;
+                rs = sum_groups(rs);
+                r2 = sum_groups(r2);
+                if (lane < 16) {
+                    red[(NT * wave + k) * 16 + lane] = rs;
+                    red[256 + (NT * wave + k) * 16 + lane] = r2;
+                }
             }
             __syncthreads();
-            rs = r2 = 0.f;
-            for (int w = 0; w < kWaves; ++w) {
-                rs += red[w * 16 + c16];
-                r2 += red[128 + w * 16 + c16];
+            float rs[NT], r2[NT];
+#pragma unroll
+            for (int k = 0; k < NT; ++k) {
+                rs[k] = r2[k] = 0.f;
+                for (int w = 8 * k; w < 8 * k + 8; ++w) {
+                    rs[k] += red[w * 16 + c16];
+                    r2[k] += red[256 + w * 16 + c16];
+                }
             }
             float tr = 0.f;
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int k = 0; k < NT; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if ((2 * wave + k) * 16 + grp * 4 + r == t.q * 16 + c16) tr = gm[k][r];
+                    if (on_diagonal(k, r)) tr = gm[k][r];
             tr = sum_groups(group_sum<16>(tr));
-            if (wave == (t.q >> 1) && lane == 0) red[kDiagAt + 1] = tr;
+            if (diagonal && lane == 0) red[kDiagAt + 1] = tr;
             least_diag(gm);
+            float rsmax, r2max, sum2;
             __syncthreads();
-            if (!t.sync(row_max_nan(rs), row_max_nan(r2), red[kDiagAt], group_sum<16>(r2), red[kDiagAt + 1])) return Outcome::dead;
-            const float rsmax = row_max_nan(t.value(0)), r2max = row_max_nan(t.value(1));
+            if constexpr (H == 1) {
+                const float rc = rs[0] + rs[NT - 1], r2c = r2[0] + r2[NT - 1];
+                if (!t.sync(row_max_nan(rc), row_max_nan(r2c), red[kDiagAt], group_sum<16>(r2c), red[kDiagAt + 1])) return Outcome::dead;
+                rsmax = row_max_nan(t.value(0));
+                r2max = row_max_nan(t.value(1));
+                sum2 = t.value(3);
+            } else {                           // added up by everybody
+                typedef __attribute__((address_space(1))) float* global_ptr;
+                const global_ptr sums = (global_ptr)(reinterpret_cast<float*>(mem + kSmallAt) + 2 * kRedSize + 2 * P);
+                if (tid < 16) {
+                    sums[(half * 2) * P + sn * 16 + tid] = rs[0];
+                    sums[(half * 2 + 1) * P + sn * 16 + tid] = r2[0];
+                }
+                if (!t.sync(0.f, 0.f, red[kDiagAt], 0.f, red[kDiagAt + 1])) return Outcome::dead;
+                float v[4][4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        v[k][c] = __hip_atomic_load(sums + k * P + c * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                unsigned m1 = 0, m2 = 0;       // (a NaN wins: its bits are the largest)
+                sum2 = 0.f;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float w = v[1][c] + v[3][c], of = __shfl(group_sum<16>(w), (lane & 3) * 16, 64);     // of strip 4 c + lane % 4
+                    m1 = max(m1, __builtin_bit_cast(unsigned, v[0][c] + v[2][c]));
+                    m2 = max(m2, __builtin_bit_cast(unsigned, w));
+                    if ((c16 >> 2) == c) sum2 = of;
+                }
+                rsmax = wave_max_nan(__builtin_bit_cast(float, m1));
+                r2max = wave_max_nan(__builtin_bit_cast(float, m2));
+            }
+            sum2 = group_sum<16>(sum2);
             // zero, infinite, NaN or overflowing input: not for this iteration
             if (!(rsmax > 1e-37f && rsmax < 3e37f)) return Outcome::left;
-            alpha = scale.first(rsmax, r2max, -row16_max(-t.value(2)), group_sum<16>(t.value(3)),
-                                group_sum<16>(t.value(4)) * (1.f / P));
+            alpha = scale.first(rsmax, r2max, -all_max(-t.value(2)), sum2, all_sum(t.value(4)) * (1.f / P));
         } else {
             make_e(gm, 1.f, e);
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int k = 0; k < NT; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) fr = fmaf(e[k][r], e[k][r], fr);
             fr = sum_groups(group_sum<16>(fr));
@@ -544,34 +779,51 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             least_diag(gm);
             alpha = scale.next();
             // Close to the end the team meets here to learn whether this is the last step, and exchanges the
-            // leading fp16 parts of E for its square.
+            // leading fp16 parts of E for its square (H = 2: the second ones too, for the other half of the strip).
             if (prev < 4.f || it >= g.max_iters) {           // uniform over the team
-                const f32x4 lo = kEScale * e[0], hi = kEScale * e[1];
+                const f32x4 lo = kEScale * e[0], hi = kEScale * e[NT - 1];
                 const F16x2Pair a0 = split_f16x2(lo.x, lo.y), a1 = split_f16x2(lo.z, lo.w);
                 const F16x2Pair a2 = split_f16x2(hi.x, hi.y), a3 = split_f16x2(hi.z, hi.w);
-                const u32x4 lead = {a0.hi, a1.hi, a2.hi, a3.hi};
-                *reinterpret_cast<u32x4*>(eimg + wave * 3 * 1024 + lane * 16) = lead;
-                *reinterpret_cast<u32x4*>(eimg + (wave * 3 + 1) * 1024 + lane * 16) = u32x4{a0.lo, a1.lo, a2.lo, a3.lo};
-                *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)t.q * 8 + wave) * 1024 + lane * 16) = lead;
+                if constexpr (H == 1) {
+                    const u32x4 lead = {a0.hi, a1.hi, a2.hi, a3.hi};
+                    *reinterpret_cast<u32x4*>(eimg + wave * 3 * 1024 + lane * 16) = lead;
+                    *reinterpret_cast<u32x4*>(eimg + (wave * 3 + 1) * 1024 + lane * 16) = u32x4{a0.lo, a1.lo, a2.lo, a3.lo};
+                    *reinterpret_cast<u32x4*>(mem + kEAt + ((size_t)sn * 8 + wave) * 1024 + lane * 16) = lead;
+                } else {
+                    const u32x2 lead = {a0.hi, a1.hi}, rest = {a0.lo, a1.lo};
+                    const size_t at = ((size_t)sn * 8 + (t0 >> 1)) * 1024 + lane * 16 + (t0 & 1) * 8;
+                    *reinterpret_cast<u32x2*>(eimg + (t0 >> 1) * 3 * 1024 + lane * 16 + (t0 & 1) * 8) = lead;
+                    *reinterpret_cast<u32x2*>(eimg + ((t0 >> 1) * 3 + 1) * 1024 + lane * 16 + (t0 & 1) * 8) = rest;
+                    *reinterpret_cast<u32x2*>(mem + kEAt + at) = lead;
+                    *reinterpret_cast<u32x2*>(mem + kELoAt + at) = rest;
+                }
                 __syncthreads();
                 if (!t.sync(own_norm())) return Outcome::dead;
-                prev = group_sum<16>(t.value(0));
+                prev = all_sum(t.value(0));
                 known = true;
                 if (!(prev < 2.f * P)) return Outcome::left;   // NaN or diverging
                 last = prev < kLastEps * kLastEps;
                 if (!last && it >= g.max_iters) return Outcome::left;
             }
         }
-        u32x4 eq[3];
         // uniform.  E^2: one operand in its leading fp16 part (off by 2^-11, of a term below 4e-5: 2e-8 at most, as
         // the polynomial), the other in two.  As three bf16 products it takes a second exchange and two more rounds
         // of loads, 3 us of 97 at K = 16, for an error that is the same in all digits measured.
         if (last) {
             alpha = 1.f;
-            f32x4 e2[2] = {zero4, zero4};
-            const int er = (int)kEAt + 2 * wave * 8 * 1024;
+            if constexpr (H == 2) {            // the other half
+                const int at = (sn * 8 + (tp >> 1)) * 1024 + lane * 16 + (tp & 1) * 8;
+                const u32x2 lead = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (int)kEAt, 0));
+                const u32x2 rest = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (int)kELoAt, 0));
+                *reinterpret_cast<u32x2*>(eimg + (tp >> 1) * 3 * 1024 + lane * 16 + (tp & 1) * 8) = lead;
+                *reinterpret_cast<u32x2*>(eimg + ((tp >> 1) * 3 + 1) * 1024 + lane * 16 + (tp & 1) * 8) = rest;
+                __syncthreads();
+            }
+            f32x4 e2[NT];
+            const int er = (int)kEAt + t0 * 8 * 1024;
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < NT; ++k) {
+                e2[k] = zero4;
                 u32x4 ea[8];
 #pragma unroll
                 for (int s = 0; s < 8; ++s) ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + (k * 8 + s) * 1024, 0);
@@ -586,18 +838,32 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
             }
             __syncthreads();                   // eimg is rewritten
 #pragma unroll
-            for (int k = 0; k < 2; ++k) e[k] = kLastLinear * e[k] + (kLastSquare / (kEScale * kEScale)) * e2[k];
+            for (int k = 0; k < NT; ++k) e[k] = kLastLinear * e[k] + (kLastSquare / (kEScale * kEScale)) * e2[k];
         } else {
             make_e(gm, alpha * alpha, e);
         }
-        split(e[0], e[1], eq);
+        put_parts(eimg, e);
+        const int eh = (int)kEHalfAt + sn * kShared;
+        if constexpr (H == 1) {
+            __syncthreads();
+        } else {
+            *reinterpret_cast<f32x4*>(mem + eh + t0 * 1024 + lane * 16) = e[0];
+            hand();
+        }
+        f32x4 acc[NT];
+        bool here = true;
+        product(a, request, turn, eimg, std::integral_constant<int, 8>{}, acc,
+                [&]() {
+                    here = taken();
+                    other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, eh + tp * 1024, 0);
+                },
+                [&]() {
+                    put_tile(eimg, tp, __builtin_bit_cast(f32x4, other));
+                    __syncthreads();
+                });
+        if (H == 2 && !here) return Outcome::dead;
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(eimg + (wave * 3 + pl) * 1024 + lane * 16) = eq[pl];
-        __syncthreads();
-        f32x4 acc[2];
-        product(a, request, turn, eimg, std::integral_constant<int, 8>{}, acc);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) xr[k] = alpha * xr[k] + (0.5f * alpha) * acc[k];
+        for (int k = 0; k < NT; ++k) xr[k] = alpha * xr[k] + (0.5f * alpha) * acc[k];
         if (last) {
             steps = it + 1;
             break;
@@ -608,9 +874,49 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, const Source
         ++it;
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-        *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (2 * wave + k) * 16 + grp * 4) = xr[k];
+    for (int k = 0; k < NT; ++k)
+        *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (t0 + k) * 16 + grp * 4) = xr[k];
     __syncthreads();
+    if constexpr (H == 2) {                    // D[j] rows of the strip, as emit_strip; the norms of whole atoms by the first of the pair
+        {
+            const int c = tid >> 5, d4 = 32 * half + (tid & 31);
+            reinterpret_cast<f32x4*>(g.D + ((int64_t)j * P + sn * 16 + c) * P)[d4] =
+                *reinterpret_cast<const f32x4*>(strip + c * kLdStrip + 4 * d4);
+        }
+        if (g.ops.f32 == nullptr && g.ops.bf16 == nullptr && g.ops.f16 == nullptr) return Outcome::done;       // uniform
+        const int c = tid & 15, d4 = 32 * half + (tid >> 4), grow = j * P + sn * 16 + c;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(strip + c * kLdStrip + 4 * d4);
+        float q2 = 0.f, r2 = 0.f;
+        if (g.ops.f32 != nullptr) store_operand_f32<P>(g.ops.f32, grow, d4, v);
+        if (g.ops.bf16 != nullptr) store_operand_split<P>(g.ops.bf16, grow, d4, v);
+        if (g.ops.f16 == nullptr) return Outcome::done;        // uniform
+        store_operand_f16x2<P>(g.ops.f16, grow, d4, split_f16x2_dict(v, q2, r2));
+        q2 = sum_groups(q2);
+        r2 = sum_groups(r2);
+        if (lane < 16) {
+            red[wave * 16 + lane] = q2;
+            red[128 + wave * 16 + lane] = r2;
+        }
+        __syncthreads();
+        q2 = r2 = 0.f;
+        for (int w = 0; w < kWaves; ++w) {
+            q2 += red[w * 16 + c16];
+            r2 += red[128 + w * 16 + c16];
+        }
+        float* sums = reinterpret_cast<float*>(mem + kSmallAt) + 2 * kRedSize + 2 * P + sn * 32;    // (last read in the first step)
+        if (half == 1 && tid < 16) {
+            sums[tid] = q2;
+            sums[16 + tid] = r2;
+        }
+        hand();
+        if (half == 1) return Outcome::done;
+        if (!taken()) return Outcome::dead;
+        q2 += __hip_atomic_load(sums + c16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        r2 += __hip_atomic_load(sums + 16 + c16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        q2 = row16_max(q2);
+        r2 = row16_max(r2);
+        if (tid == 0) g.ops.dnorm[j * (P / 16) + sn] = float2{sqrtf(q2), sqrtf(r2)};
+    }
     return Outcome::done;
 }
 
@@ -1082,27 +1388,39 @@ __device__ __forceinline__ void jacobi_alone(const WideArgs& g, int j, const Sou
 // Everything by value (what a call could change through a pointer would live in memory from the start).
 struct JacobiResult {
     Outcome how;
-    Team t;
+    int epoch, arrived;        // of the barrier
     int tbase;
 };
 __device__ __attribute__((noinline)) JacobiResult jacobi_called(WideArgs g, int j, Source src, Team t, int* version, int tbase,
                                                                 unsigned char* mem, unsigned char* lds, float* red, int* flag) {
     const Outcome how = jacobi(g, j, src, t, version, tbase, mem, lds, red, flag);
-    return {how, t, tbase};
+    return {how, t.epoch, t.arrived, tbase};
 }
 __device__ __attribute__((noinline)) void jacobi_alone_called(WideArgs g, int j, Source src, unsigned char* mem,
                                                               unsigned char* lds, float* red, int* flag) {
     jacobi_alone(g, j, src, mem, lds, red, flag);
 }
 
-// NS: Newton-Schulz first; otherwise Jacobi for every block.
-template <bool NS>
+// A team of pairs without its helpers: called for the same reason.
+struct NewtonSchulzResult {
+    Outcome how;
+    int steps;
+};
+__device__ __attribute__((noinline)) NewtonSchulzResult newton_schulz_called(WideArgs g, int j, Source src, Team t, unsigned char* mem,
+                                                                             unsigned char* lds, float* red) {
+    int steps = 0;
+    const Outcome how = newton_schulz<1>(g, j, src, t, nullptr, mem, lds, red, nullptr, steps);
+    return {how, steps};
+}
+
+// NS: Newton-Schulz first; otherwise Jacobi for every block.  PAIRS: teams of 32, which have one block each.
+template <bool NS, bool PAIRS>
 __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     // The 16 workgroups of a team lie eight apart: workgroups go round the eight XCDs, so a team shares an L2
     // (spread: next to each other).
-    const int team_wgs = wide_team_wgs(g.teams, g.spread);
+    const int team_wgs = wide_team_wgs(g.teams, g.spread, PAIRS);
     if ((int)blockIdx.x >= team_wgs) {         // uniform: the workgroups of the squared-error total
         const int b = (int)blockIdx.x - team_wgs;
         if (g.sq.out != nullptr && b < g.sq.nb)
@@ -1110,15 +1428,16 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
                                reinterpret_cast<double*>(lds));
         return;
     }
-    const int team = g.spread ? (int)blockIdx.x / 16 : (int)blockIdx.x / 128 * 8 + (int)blockIdx.x % 8;
-    const int q = g.spread ? (int)blockIdx.x % 16 : (int)blockIdx.x % 128 / 8;
+    const int team = PAIRS ? (int)blockIdx.x % 8 : g.spread ? (int)blockIdx.x / 16 : (int)blockIdx.x / 128 * 8 + (int)blockIdx.x % 8;
+    const int q = PAIRS ? (int)blockIdx.x / 8 : g.spread ? (int)blockIdx.x % 16 : (int)blockIdx.x % 128 / 8;
+    constexpr int kSize = PAIRS ? kPairs : kTeam;
     if (team >= g.teams) return;               // uniform
     float* red = reinterpret_cast<float*>(lds + kSmallLds);
     int* flag = reinterpret_cast<int*>(red + 1280);
     unsigned char* mem = g.data + (size_t)team * kTeamBytes;
     int* sync = g.sync + team * kSyncInts;
     float* small = reinterpret_cast<float*>(mem + kSmallAt);
-    Team all = {sync + kArriveAt, small, flag, kTeam, q, g.polls, 0, 0, false};
+    Team all = {sync + kArriveAt, small, flag, kSize, q, g.polls, 0, 0, false};
     Team eight = {sync + kArriveJacAt, small + kRedSize, flag + 1, kJacTeam, q, g.polls, 0, 0, false};
     int tbase = 0;
     const int blocks = (g.K - 1 - team) / g.teams + 1;         // of this team
@@ -1158,14 +1477,29 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
         Outcome how = Outcome::left;
         if constexpr (NS) {
             int steps = 0;
-            how = newton_schulz(g, src, all, met ? nullptr : count, mem, lds, red, steps);
+            if constexpr (PAIRS) {
+                how = g.helper_polls < 0 && q >= kTeam ? Outcome::alone
+                                                       : newton_schulz<2>(g, j, src, all, count, mem, lds, red, sync + kPairAt, steps);
+                if (how == Outcome::alone) {   // uniform over the team
+                    if (q >= kTeam) {          // nobody waits for this workgroup
+                        --undone;
+                        break;
+                    }
+                    all.size = kTeam;
+                    const NewtonSchulzResult r = newton_schulz_called(g, j, src, all, mem, lds, red);
+                    how = (Outcome)__builtin_amdgcn_readfirstlane((int)r.how);
+                    steps = __builtin_amdgcn_readfirstlane(r.steps);
+                }
+            } else {
+                how = newton_schulz<1>(g, j, src, all, met ? nullptr : count, mem, lds, red, nullptr, steps);
+            }
             met = true;
             eight.near = all.near;
             if (q == 0 && tid == 0) {
                 g.fallback[j] = how == Outcome::left;
                 if (g.iters_out != nullptr && how == Outcome::done) g.iters_out[j] = -steps;
             }
-            if (how == Outcome::done) emit_strip(g, j, q, reinterpret_cast<const float*>(lds + kStripAt), red);
+            if (how == Outcome::done && all.size == kTeam) emit_strip(g, j, q, reinterpret_cast<const float*>(lds + kStripAt), red);
         }
         if (how == Outcome::left) {
             __syncthreads();
@@ -1173,9 +1507,10 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
             if (q < kJacTeam) {
                 if constexpr (NS) {
                     const JacobiResult r = jacobi_called(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag);
-                    how = r.how;
-                    eight = r.t;
-                    tbase = r.tbase;
+                    how = (Outcome)__builtin_amdgcn_readfirstlane((int)r.how);
+                    eight.epoch = __builtin_amdgcn_readfirstlane(r.epoch);
+                    eight.arrived = __builtin_amdgcn_readfirstlane(r.arrived);
+                    tbase = __builtin_amdgcn_readfirstlane(r.tbase);
                 } else
                     how = jacobi(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag);
             }
@@ -1194,7 +1529,7 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
     stores_done();
     if (tid == 0) {
         if (undone > 0) __hip_atomic_fetch_max(sync + kUndoneAt, undone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        flag[0] = __hip_atomic_fetch_add(sync + kExitAt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == kTeam - 1;
+        flag[0] = __hip_atomic_fetch_add(sync + kExitAt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == kSize - 1;
         flag[1] = flag[0] ? __hip_atomic_load(sync + kUndoneAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     }
     __syncthreads();
@@ -1212,13 +1547,14 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
             if (g.iters_out != nullptr) g.iters_out[j] = 0;
         }
     }
-    if (tid >= kSyncInts) return;
-    const bool in_l2 = all.near && tid != kArriveAt && tid < kMeetAt && tid != kExitAt && tid != kUndoneAt;
-    if (in_l2 || rest > 0) {                   // (rest > 0: this workgroup may have left without knowing that it is near)
-        __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int e = tid; e < (PAIRS ? kSyncInts : kPairAt); e += kNT) {
+        const bool in_l2 = all.near && e != kArriveAt && (e < kMeetAt || e >= kPairAt) && e != kExitAt && e != kUndoneAt;
+        if (in_l2 || rest > 0) {               // (rest > 0: this workgroup may have left without knowing that it is near)
+            __hip_atomic_store(sync + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        if (!in_l2 || rest > 0) __hip_atomic_store(sync + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (!in_l2 || rest > 0) __hip_atomic_store(sync + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
@@ -1250,12 +1586,13 @@ hipError_t launch_polar_wide(int K, const float* M, const float* partial, const 
     a.sq = sq;
     a.spread = wide_streams(ws.device) > 2;
     a.polls = ws.wide_polls;
-    const unsigned grid = (unsigned)(wide_team_wgs(a.teams, a.spread) + (sq.out != nullptr ? sq.nb : 0));
-    const void* fn = newton_schulz_first ? reinterpret_cast<const void*>(&wide_polar_kernel<true>)
-                                         : reinterpret_cast<const void*>(&wide_polar_kernel<false>);
-    if (hipError_t e = ws.raised->ensure(fn, kLds); e != hipSuccess) return e;
-    if (newton_schulz_first) hipLaunchKernelGGL(wide_polar_kernel<true>, dim3(grid), dim3(kNT), kLds, st, a);
-    else hipLaunchKernelGGL(wide_polar_kernel<false>, dim3(grid), dim3(kNT), kLds, st, a);
+    a.helper_polls = ws.wide_helpers ? (a.polls < kHelperPolls ? a.polls : kHelperPolls) : -1;
+    const bool pairs = newton_schulz_first && !a.spread && K <= kMaxPairTeams;
+    const unsigned grid = (unsigned)(wide_team_wgs(a.teams, a.spread, pairs) + (sq.out != nullptr ? sq.nb : 0));
+    auto* kernel = pairs ? &wide_polar_kernel<true, true> : newton_schulz_first ? &wide_polar_kernel<true, false>
+                                                                                : &wide_polar_kernel<false, false>;
+    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), kLds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNT), kLds, st, a);
     return hipGetLastError();
 }
 

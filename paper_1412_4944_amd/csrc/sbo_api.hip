@@ -691,6 +691,13 @@ int sbo_test_short_cuts(sbo_ctx* c, int32_t* read, int n) {
     return SBO_OK;
 }
 
+// For tests, not in the header: p = 256, few orthobases: the SVD by teams whose second workgroups stay away (on = 0).
+int sbo_test_wide_helpers(sbo_ctx* c, int on) {
+    if (!c) return SBO_EINVAL;
+    c->ws.wide_helpers = on != 0;
+    return SBO_OK;
+}
+
 int sbo_set_option(sbo_ctx* c, int option, int value) {
     if (!c) return SBO_EINVAL;
     switch (option) {

@@ -127,6 +127,7 @@ struct Workspace {
     LdsRaised* raised;
     int device;                            // that was current when the context was created
     int wide_polls = kWidePolls;           // p > 64: how long the workgroups of an SVD team wait for one another
+    bool wide_helpers = true;              // p > 64: false (tests) = the second workgroups of pairs leave at once
 };
 constexpr int kSqBlocks = 256;
 constexpr int kEnergySplitBelow = 192;       // coding launches with fewer workgroups split the blocks

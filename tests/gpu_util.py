@@ -48,6 +48,13 @@ class Sbo:
         assert fn(self.ctx, buf, n) == 0
         return out, sum(x >= 0 for x in buf), sum(x == 1 for x in buf)
 
+    def wide_helpers(self, on):
+        """p = 256, few orthobases: whether the second workgroups of the pairs of an SVD team take part (as they do)."""
+        import ctypes
+        fn = sbo.lib().sbo_test_wide_helpers
+        fn.argtypes = [ctypes.c_void_p, ctypes.c_int]
+        assert fn(self.ctx, int(on)) == 0
+
     def svd_jacobi(self, on):
         """Jacobi SVD for every orthobase (on) or the default Newton-Schulz + Jacobi fallback."""
         sbo.sbo_set_option(self.ctx, sbo.SBO_OPT_SVD_METHOD, sbo.SBO_SVD_JACOBI if on else sbo.SBO_SVD_AUTO)

@@ -919,6 +919,52 @@ def test_polar_p256_teams_of_workgroups(K, jacobi_only):
     print(f"  K={K} jacobi={jacobi_only}: worst |Q - Q_oracle| {w:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("K", [1, 8])
+@pytest.mark.parametrize("polls", [1 << 22, 40, 3, 0])
+def test_polar_p256_teams_of_pairs(K, polls):
+    """p = 256, up to eight orthobases: two workgroups to a strip of columns.  The same bits as without the second
+    ones, and as by the teams that more orthobases have, for every kind of block; with waits that end early every
+    block is finished all the same, and the next call finds the counters set back."""
+    p = 256
+    rng = np.random.default_rng(61 + K)
+    M = np.stack([(synth.random_onb(rng, p) * np.geomspace(1, 10.0 ** -(j % 4), p)) @ synth.random_onb(rng, p)
+                  for j in range(9)])
+    M[2] = np.diag(rng.uniform(0.98, 1, p))[rng.permutation(p)]                    # a narrow spectrum
+    if K > 1:
+        M[5][:, 200:] = M[5][:, :56]                     # rank 200: left to the Jacobi SVD
+        M[6] = 0
+        M[7][3, 5] = np.nan
+    M32 = M.astype(np.float32)
+    counts = np.ones(9, np.int32)
+    counts[4] = 0
+    D_old = synth.random_dictionary(rng, 9, p).astype(np.float32)
+    good = [j for j in range(K) if K == 1 or j not in (4, 5, 6, 7)]
+    with Sbo(p, 9, 4, 256) as g:                         # nine orthobases: teams of 16
+        teams = g.polar(M32, D_old, counts)[:K]
+        few = lambda: g.polar(M32[:K], D_old[:K], counts[:K])
+        sbo.sbo_set_blocks(g.ctx, K)
+        pairs = few()
+        steps = np.array(sbo.sbo_svd_sweeps(g.ctx, K))
+        g.wide_helpers(False)
+        alone = few()
+        g.wide_helpers(True)
+        sbo.sbo_set_option(g.ctx, sbo.SBO_OPT_SVD_WAIT, polls)
+        print(f"case K={K} polls={polls} steps {steps}", flush=True)
+        ended = few()
+        sbo.sbo_set_option(g.ctx, sbo.SBO_OPT_SVD_WAIT, 1 << 22)
+        again = few()
+    assert (steps[good] < 0).all()
+    np.testing.assert_array_equal(pairs, teams)
+    np.testing.assert_array_equal(pairs, alone)
+    np.testing.assert_array_equal(pairs, again)
+    for j in good:
+        Q = orc.o_polar(M32[j].astype(np.float64))
+        assert np.abs(pairs[j] - Q).max() <= 2e-6
+        compare_Q(ended[j:j + 1], Q[None], M32[j:j + 1].astype(np.float64), np.ones(1, bool))
+    if K > 1:
+        np.testing.assert_array_equal(ended[4], D_old[4])
+
+
 def test_polar_p256_on_three_streams():
     """Contexts on more than two streams: the teams take the other workgroup order; their launches overlap."""
     import torch
