@@ -376,13 +376,17 @@ __global__ __launch_bounds__(256) void accum_wide_kernel(const float* __restrict
 // What bounds it: the products, 1270 TFLOP/s while they run (the chip sustains 1530 on such operands), and the 256 KiB that a piece
 // leaves (15 us of it).  131072 signals, K = 16, s0 = 12: 110 -> 98 us with eight wavefronts, two on a SIMD, where
 // four with 64 atoms each split and multiplied in turn, zero-filled the x tile and met twice a step; 2048 signals 21 -> 19.
+// Small sets (accum_geom): the dims in four slices.  Four sums are taken in turn, so that the error is no larger (|M - M64|_F / |M64|_F at
+// K = 1 to 16, 600 to 16384 signals 0.74 to 1.05 of what it was, 0.9 on average; with one sum up to 1.6).  K = 1, 2048 signals 19.8 -> 13.0 us,
+// 16384, K = 4 29.8 -> 27.0.
 constexpr int kAwsSignals = 16;
 constexpr int kAwsWaves = 8;
-constexpr size_t aws_lds_bytes() {
-    return (size_t)kMaxPiece * sizeof(int) + (size_t)2 * 3 * 256 * 32 + (size_t)3 * 3 * 257 * 32;
+constexpr size_t aws_lds_bytes(int slices) {
+    return (size_t)kMaxPiece * sizeof(int) + (size_t)2 * 3 * (256 / slices) * 32 + (size_t)3 * 3 * 257 * 32;
 }
 
-template <int S0>
+// SLICES (blockIdx.y): a workgroup has 256 / SLICES of the dims, of a piece that is longer by as much.
+template <int S0, int SLICES>
 __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const float* __restrict__ Y, int K, int piece,
                                                                           const int32_t* __restrict__ offsets,
                                                                           const int32_t* __restrict__ perm,
@@ -390,11 +394,16 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
                                                                           const float* __restrict__ coef,
                                                                           float* __restrict__ partial, int by_pos) {
     constexpr int P = 256, NT = 64 * kAwsWaves;
-    constexpr int NTL = 8;                     // 32-wide tiles along the dimensions
+    constexpr int DIMS = P / SLICES;
+    constexpr int NTL = DIMS / 32;             // 32-wide tiles along the dimensions
     constexpr int G = kAwsSignals, GH = G / 2;
-    constexpr int YPLANE = P * 32;             // bytes of one part of the y tile
+    constexpr int YPLANE = DIMS * 32;          // bytes of one part of the y tile
+    constexpr int YT = 2 * DIMS;               // threads that build it; the entries of x: by the others, where there are enough
+    constexpr int XT = YT + G * 16 <= NT ? YT : 0;
+    constexpr int AHEAD = SLICES == 1 ? 2 : 4; // steps whose loads are on their way
+    constexpr int SUMS = SLICES;               // taken in turn: none gets longer than in a piece that is not sliced
     constexpr int XPLANE = (P + 1) * 32;       // bytes of one part of the x tile (+ the extra row)
-    static_assert(G * S0 <= NT, "one thread per (signal, entry)");
+    static_assert(XT + G * S0 <= NT, "one thread per (signal, entry)");
     // ids[kMaxPiece] | two y tiles | three x tiles
     extern __shared__ __attribute__((aligned(16))) int lds[];
     int* ids = lds;
@@ -413,11 +422,13 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
     for (int e = tid; e < 9 * XPLANE / 16; e += NT) reinterpret_cast<u32x4*>(xtiles)[e] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
 
-    f32x16 acc[NTL];
+    f32x16 acc[SUMS][NTL];
 #pragma unroll
-    for (int b = 0; b < NTL; ++b)
+    for (int a = 0; a < SUMS; ++a)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+        for (int b = 0; b < NTL; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
     const int atom0 = 32 * wave;               // this wavefront's atoms: atom0 .. atom0+31
     const int n_steps = (cnt + G - 1) / G;
@@ -430,21 +441,26 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
         int k;
         float c;
     };
-    const int dim = tid & (P - 1), u0 = __builtin_amdgcn_readfirstlane(tid / P) * GH;
-    const int e_sig = tid / S0, e_ent = tid % S0;
+    const int dim = tid & (DIMS - 1), u0 = __builtin_amdgcn_readfirstlane(tid / DIMS % 2) * GH, dim0 = (int)blockIdx.y * DIMS;
+    const bool has_y = XT == 0 || tid < YT, has_x = tid >= XT && tid < XT + G * S0;    // (the first uniform over a wavefront)
+    const int e_sig = (unsigned)(tid - XT) / S0, e_ent = (unsigned)(tid - XT) % S0;
     auto fetch = [&](Fetched& f, int g) {
+        if (has_y) {
 #pragma unroll
-        for (int u = 0; u < GH; ++u) {
-            const int64_t i = ids[min(g * G + u0 + u, cnt - 1)];
-            f.y[u] = Y[i * P + dim];
+            for (int u = 0; u < GH; ++u) {
+                const int64_t i = ids[min(g * G + u0 + u, cnt - 1)];
+                f.y[u] = Y[i * P + dim0 + dim];
+            }
         }
-        const int e = min(g * G + min(e_sig, G - 1), cnt - 1);
-        const int64_t i = by_pos ? pos0 + e : ids[e];
-        f.k = supp[i * S0 + e_ent];
-        f.c = coef[i * S0 + e_ent];
+        if (SLICES == 1 || has_x) {
+            const int e = min(g * G + min(e_sig, G - 1), cnt - 1);
+            const int64_t i = by_pos ? pos0 + e : ids[e];
+            f.k = supp[i * S0 + e_ent];
+            f.c = coef[i * S0 + e_ent];
+        }
     };
     auto scatter = [&](unsigned char* xt, int at, TriWord t) {
-        if (tid < G * S0) {
+        if (has_x) {
             *reinterpret_cast<unsigned short*>(xt + at) = (unsigned short)(t.hi >> 16);
             *reinterpret_cast<unsigned short*>(xt + XPLANE + at) = (unsigned short)(t.mid >> 16);
             *reinterpret_cast<unsigned short*>(xt + 2 * XPLANE + at) = (unsigned short)(t.lo >> 16);
@@ -453,18 +469,20 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
     auto build = [&](const Fetched& f, int g) {            // returns where this thread's entry went
         unsigned char* yt = ytiles + (g & 1) * (3 * YPLANE);
         const int left = cnt - g * G;          // signals of this step (uniform)
-        unsigned w[3][GH / 2];
+        if (has_y) {
+            unsigned w[3][GH / 2];
 #pragma unroll
-        for (int u = 0; u < GH; u += 2) {
-            const Bf16x3Pair s = split_bf16x3(u0 + u < left ? f.y[u] : 0.f, u0 + u + 1 < left ? f.y[u + 1] : 0.f);
-            w[0][u >> 1] = s.hi;
-            w[1][u >> 1] = s.mid;
-            w[2][u >> 1] = s.lo;
+            for (int u = 0; u < GH; u += 2) {
+                const Bf16x3Pair s = split_bf16x3(u0 + u < left ? f.y[u] : 0.f, u0 + u + 1 < left ? f.y[u + 1] : 0.f);
+                w[0][u >> 1] = s.hi;
+                w[1][u >> 1] = s.mid;
+                w[2][u >> 1] = s.lo;
+            }
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                *reinterpret_cast<u32x4*>(yt + pl * YPLANE + tr_off(dim, u0)) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
         }
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl)
-            *reinterpret_cast<u32x4*>(yt + pl * YPLANE + tr_off(dim, u0)) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
-        const bool have = tid < G * S0 && e_sig < left && (unsigned)f.k < (unsigned)P;
+        const bool have = has_x && e_sig < left && (unsigned)f.k < (unsigned)P;
         const int at = tr_off(have ? f.k : P, e_sig & (G - 1));
         scatter(xtiles + (g % 3) * (3 * XPLANE), at, split_trunc(f.c));
         return at;
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
     // the six partial products, smallest first: (A part, B part)
     constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
     constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
-    auto multiply = [&](int g) {
+    auto multiply = [&](int g, int turn) {
         const unsigned char* yt = ytiles + (g & 1) * (3 * YPLANE);
         const unsigned char* xt = xtiles + (g % 3) * (3 * XPLANE);
         // operands: lane (h, n) takes signals 8h .. 8h+7 of atom resp. dim tile*32 + n
@@ -487,43 +505,45 @@ __global__ __launch_bounds__(64 * kAwsWaves) void accum_wide_split_kernel(const 
                 yb[pl] = *reinterpret_cast<const u32x4*>(yt + pl * YPLANE + tr_off(nt * 32 + n, 8 * h));
 #pragma unroll
             for (int t = 0; t < 6; ++t)
-                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[TA[t]]),
-                                                                  __builtin_bit_cast(bf16x8, yb[TB[t]]), acc[nt], 0, 0, 0);
+                acc[turn][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[TA[t]]),
+                                                                        __builtin_bit_cast(bf16x8, yb[TB[t]]), acc[turn][nt], 0, 0, 0);
         }
     };
 
-    // phase g: the products of step g; the tiles of step g + 1 are built (their loads were issued two phases ago), and the
+    // phase g: the products of step g; the tiles of step g + 1 are built (their loads were issued AHEAD phases ago), and the
     // entries of step g - 1 wiped, whose x tile is that of step g + 2
-    Fetched fa, fb;
-    fetch(fa, 0);
-    fetch(fb, 1);
-    int now = build(fa, 0), old = tr_off(P, 0);
-    fetch(fa, 2);
+    Fetched f[AHEAD];
+#pragma unroll
+    for (int g = 0; g < AHEAD; ++g) fetch(f[g], g);
+    int now = build(f[0], 0), old = tr_off(P, 0);
+    fetch(f[0], AHEAD);
     __syncthreads();
-    auto phase = [&](Fetched& f, int g) {
+    auto phase = [&](Fetched& f, int g, int turn) {
         // one wavefront of a SIMD builds first, the other multiplies first: between two barriers they would otherwise
         // want the vector ALU together, and then the matrix cores
-        if (wave >= kAwsWaves / 2) multiply(g);
+        if (wave >= kAwsWaves / 2) multiply(g, turn);
         const int next = build(f, g + 1);
-        fetch(f, g + 3);
+        fetch(f, g + 1 + AHEAD);
         scatter(xtiles + ((g + 2) % 3) * (3 * XPLANE), old, TriWord{0u, 0u, 0u});
-        if (wave < kAwsWaves / 2) multiply(g);
+        if (wave < kAwsWaves / 2) multiply(g, turn);
         old = now;
         now = next;
         __syncthreads();
     };
-    for (int g = 0; g < n_steps; g += 2) {
-        phase(fb, g);
-        if (g + 1 < n_steps) phase(fa, g + 1); // uniform
-    }
+    for (int g = 0; g < n_steps; g += AHEAD)
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (g + u < n_steps) phase(f[(u + 1) % AHEAD], g + u, u % SUMS);       // uniform
 
-    float* out = partial + (int64_t)id * P * P;
+    float* out = partial + (int64_t)id * P * P + dim0;
 #pragma unroll
     for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int atom = atom0 + (r >> 2) * 8 + h * 4 + (r & 3);
-            out[atom * P + nt * 32 + n] = acc[nt][r];
+            float sum = acc[0][nt][r];
+            if constexpr (SUMS == 4) sum = (sum + acc[1][nt][r]) + (acc[2][nt][r] + acc[3][nt][r]);
+            out[atom * P + nt * 32 + n] = sum;
         }
 }
 
@@ -608,16 +628,15 @@ template <int S0>
 hipError_t launch_wide_s(int K, const float* Y, int64_t m, const int32_t* supp, const float* coef,
                          const Workspace& ws, float* M, bool split, bool by_pos, hipStream_t st) {
     constexpr int P = 256;
-    const int piece = accum_piece(m, K);
-    const int max_pieces = accum_max_pieces(m, K);
+    const AccumGeom geom = accum_geom(P, m, K, split);
+    const int piece = geom.piece, max_pieces = geom.max_pieces;
     const size_t lds1 = kMaxPiece * sizeof(int) + (size_t)4 * kWidePairs * 2 * 64 * sizeof(float);
     if (split) {
-        const size_t lds = aws_lds_bytes();
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&accum_wide_split_kernel<S0>), lds);
-            e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((accum_wide_split_kernel<S0>), dim3(max_pieces), dim3(64 * kAwsWaves), lds, st, Y, K, piece,
-                           ws.offsets, ws.perm, supp, coef, ws.partial, (int)by_pos);
+        const size_t lds = aws_lds_bytes(geom.slices);
+        auto* kernel = geom.slices == 1 ? &accum_wide_split_kernel<S0, 1> : &accum_wide_split_kernel<S0, kAccumSlices>;
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(max_pieces, geom.slices), dim3(64 * kAwsWaves), lds, st, Y, K, piece, ws.offsets,
+                           ws.perm, supp, coef, ws.partial, (int)by_pos);
     } else {
         hipLaunchKernelGGL((accum_wide_kernel<S0, false>), dim3(max_pieces), dim3(256), lds1, st, Y, K, piece,
                            ws.offsets, ws.perm, supp, coef, ws.partial, (int)by_pos);
@@ -706,7 +725,7 @@ hipError_t launch_gram(int p, int K, const float* Y, int64_t n, const Workspace&
 // *sq_out = sum of err[0..m) (same launch, extra workgroups).
 hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, float* M,
                                const float* err, double* sq_out, hipStream_t st) {
-    const int piece = accum_piece(m, K);
+    const int piece = accum_geom(p, m, K, ws.parts_accum).piece;
     const size_t lds = (K + 1 + 16) * sizeof(int);
     const int gy = (p * p + 255) / 256;
     const bool sq = err != nullptr && sq_out != nullptr;

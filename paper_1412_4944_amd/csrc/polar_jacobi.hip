@@ -92,7 +92,7 @@ hipError_t launch_polar_from_pieces(int p, int K, int64_t m, float* D, const Wor
         sq.nb = (int)(m / 2048 < 1 ? 1 : m / 2048 < 128 ? m / 2048 : 128);   // <= kSqBlocks shares of err
     }
     if (p == 256)
-        return launch_polar_wide(K, nullptr, ws.partial, ws.offsets, accum_piece(m, K), ws.counts, D,
+        return launch_polar_wide(K, nullptr, ws.partial, ws.offsets, accum_geom(p, m, K, ws.parts_accum).piece, ws.counts, D,
                                  dict_ops(ws, write_ops), true, nullptr, ws, sq, st);
     return launch_polar_ns(p, K, nullptr, ws.partial, ws.offsets, accum_piece(m, K), ws.counts, D,
                            dict_ops(ws, write_ops), ws.ns_fallback, ws.sweeps, sq, ws.raised, st, ws.chunk_count,

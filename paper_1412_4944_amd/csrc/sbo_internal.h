@@ -53,6 +53,22 @@ inline int accum_max_pieces(int64_t m, int K) {
     int piece = accum_piece(m, K);
     return (int)((m + piece - 1) / piece) + K;
 }
+// The pieces of launch_accumulate.  p = 256 on the bf16 matrix cores, small sets: slices of 64 dims, a workgroup each, of
+// pieces that are up to four times as long; a quarter of the results to write and for the SVD to add up.  A step of a
+// slice takes two thirds of a whole one's time, so it does not pay for long.  sbo_update, whole / sliced (us): K = 1, 600
+// signals 251 / 245, 2048 180 / 173, 8192 207 / 187; K = 2, 8192 230 / 219; K = 4, 4096 232 / 227, 16384 235 / 228; K = 16, 5041 321 / 317,
+// 16384 316 / 315, 32768 358 / 358; K = 32, 20000 3028 / 2933 (accumulation 31 / 42), 32768 582 / 602.
+struct AccumGeom {
+    int piece, max_pieces, slices;
+};
+constexpr int kAccumSlices = 4, kAccumSliceMaxK = 16;
+constexpr int64_t kAccumSliceMaxSignals = 16384;
+inline AccumGeom accum_geom(int p, int64_t m, int K, bool parts) {
+    if (p != 256 || !parts || K > kAccumSliceMaxK || m > kAccumSliceMaxSignals) return {accum_piece(m, K), accum_max_pieces(m, K), 1};
+    const int target = kNumCU / kAccumSlices - K;      // (a piece more per block, at most: all resident in one round)
+    const int64_t c = ((m + target - 1) / target + 63) / 64 * 64;
+    return {(int)c, (int)((m + c - 1) / c) + K, kAccumSlices};
+}
 
 // ---- Jacobi stopping threshold ---------------------------------------------------
 // A sweep in which every pair already had a cosine below this is the last one.

@@ -811,6 +811,35 @@ def test_largest_K_at_p256(K):
             np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("K,m,s0", [(1, 1, 1), (1, 79, 16), (1, 16384, 12), (1, 16385, 12), (3, 8191, 1), (16, 5041, 12),
+                                    (16, 16384, 16), (17, 5041, 12)])
+def test_accumulate_p256_in_slices(K, m, s0):
+    """p = 256, small sets: the dims of a piece in slices, at the edges of that rule and of pieces and steps; an empty block, ids
+    out of range (ignored) and the sum over the pieces.  Bound: the fp32 sums of at most 64 products and of the pieces, each
+    rounding 2^-24 of a partial sum, which random signs keep near the square root of their number."""
+    p = 256
+    rng = np.random.default_rng(71 + m + K)
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    blk = rng.integers(0, K, m).astype(np.int32)
+    if K > 2:
+        blk[blk == 1] = 0
+    supp = np.sort(np.argsort(rng.random((m, p)), axis=1)[:, :s0], axis=1).astype(np.int32)
+    coef = rng.standard_normal((m, s0)).astype(np.float32)
+    x = np.zeros((m, p))
+    np.put_along_axis(x, supp.astype(np.int64), coef.astype(np.float64), axis=1)
+    if m > 10:
+        x[3, supp[3, -1]] = 0.0
+        supp[3, -1] = 256
+    ref = np.stack([x[blk == j].T @ Y[blk == j].astype(np.float64) for j in range(K)])
+    with Sbo(p, K, s0, m) as g:
+        M = g.accumulate(Y, blk, supp, coef)
+        np.testing.assert_array_equal(M, g.accumulate(Y, blk, supp, coef))
+    for j in range(K):
+        n = np.linalg.norm(ref[j])
+        assert np.linalg.norm(M[j] - ref[j]) <= 4e-7 * n, j
+        assert np.abs(M[j] - ref[j]).max() <= 4e-6 * max(np.abs(ref[j]).max(), 1e-30), j
+
+
 @pytest.mark.parametrize("p", [16, 32, 64, 256])
 def test_polar_condition_sweep_and_both_paths(p):
     """The SVD update over a range of condition numbers, once with the default path
