@@ -31,11 +31,12 @@
 //   handed over through memory with a version number; there is no barrier but one per sweep.
 //
 // What bounds it: Newton-Schulz by the 512 KiB of operands per workgroup and step from L2 (30 bytes a cycle arrive at a CU, no
-// more with one team on an XCD than with two, or with more loads on their way; pairs 256 KiB): of 25500 cycles a step 10900 are the
-// first product and the wait for its slowest wavefront, 9500 the second (the splits), 3400 the barrier; with pairs, of 21000 7500, 7000 and
-// 5000.  K = 4 114 -> 88 us, K = 16 131 -> 124 (9 steps from a finished matrix): 103 with pairs alone, the rest because the compiler
+// more with one team on an XCD than with two, or with more loads on their way; pairs 256 KiB): of 25000 cycles a step 11300 are the
+// first product and the wait for its slowest wavefront, 9000 the second (the splits), 2300 the barrier; with pairs, of 18000 7200, 6700 and
+// 2500.  K = 4 114 -> 80 us, K = 16 131 -> 120 (9 steps from a finished matrix): 103 with pairs alone; 88, 124 because the compiler
 // took the operands' descriptor and offsets for different ones in every lane (a loop around every load) and a flat load among
-// them waited for all of them.  Eight steps of operands on their way instead of four: 91 us (registers spilled, and half of
+// them waited for all of them; the rest by a barrier of flags that a wavefront reads at once, by loads that pass L1 by,
+// instead of a counter, polled by atomics (5000 cycles with pairs).  Eight steps of operands on their way instead of four: 91 us (registers spilled, and half of
 // the wavefronts get theirs late).  With the three parts in memory (768 KiB) 138 -> 131 us in the same profile,
 // K = 16; K = 4 no difference.  Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  Jacobi is called, not inlined,
@@ -99,9 +100,9 @@ constexpr size_t kELoAt = (kSmallAt + kSmallFloats * 4 + 255) / 256 * 256;     /
 constexpr size_t kEHalfAt = kELoAt + (size_t)kTeam * 8 * 1024;                 // and E in fp32, [16 strips][16 tiles][64 lanes][16 bytes]
 constexpr size_t kTeamBytes = kEHalfAt + (size_t)kTeam * kShared;
 // and its counters (ints, zero between launches), each on a cache line of its own
-constexpr int kArriveAt = 0, kArriveJacAt = 64, kExitAt = 128, kUndoneAt = 129, kVersionAt = 160, kMeetAt = 192, kPairAt = 224, kPairInts = 16,
+constexpr int kFlagsAt = 0, kFlagsJacAt = 64, kExitAt = 128, kUndoneAt = 129, kVersionAt = 160, kMeetAt = 192, kPairAt = 224, kPairInts = 16,
               kSyncInts = kPairAt + kPairs * kPairInts;
-// Added to a barrier's counter by a workgroup that gives up (no barrier counts as far, and 16 times it fits an int).
+// Flag of a workgroup that has given up.
 constexpr int kGone = 1 << 24;
 constexpr unsigned long long kGoneMeet = 1ull << 62, kNoHelpers = 1ull << 61;
 
@@ -148,27 +149,26 @@ __device__ __forceinline__ float half_sum(float x) {           // over 32 lanes
 // releases for all; the other side polls, acquires and lets its workgroup go on.
 //
 // near: both workgroups run on the same XCD (HW_REG_XCC_ID, compared when the team first meets), so
-// its L2 is where they meet: a store that has been waited for is in it (L1 writes through), and a load
-// finds it there once L1 is invalidated; counters are atomics without a scope bit, which L2
-// executes.  That is how the workgroup scope works for a workgroup spread over several CUs.  Otherwise the
-// fences of the agent scope, which write L2 back and invalidate it: 3 us a barrier, 5 to 10 when all
-// CUs do it, against 1.
+// its L2 is where they meet: a store that has been waited for is in it (L1 writes through), and a load of the
+// agent scope passes L1 by and finds it there.  Otherwise the fences of the agent scope, which write L2 back and
+// invalidate it: 3 us a barrier, 5 to 10 when all CUs do it, against 1.
+constexpr int kPastL1 = 16;                    // buffer loads: the bit of the agent scope (the same time as without)
 __device__ __forceinline__ void stores_done() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 }
-__device__ __forceinline__ int peek(int* p, bool near) {
-    if (!near) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int v = -1;                                // (an atomic that changes nothing: a load could be served by L1)
-    __hip_atomic_compare_exchange_strong(p, &v, -1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    return v;
+__device__ __forceinline__ int peek(int* p) {
+    return __hip_atomic_load((__attribute__((address_space(1))) int*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void acquire(bool near) {
+    if (near) asm volatile("" ::: "memory");
+    else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 template <class F>
 __device__ __forceinline__ bool poll(int polls, bool near, F ready) {
     for (int k = 0; k < polls; ++k) {
         if (ready()) {
-            if (near) asm volatile("buffer_inv sc0" ::: "memory");
-            else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            acquire(near);
             return true;
         }
         __builtin_amdgcn_s_sleep(1);
@@ -181,24 +181,29 @@ __device__ __forceinline__ void raise_to(int* p, int v, bool near) {
 }
 
 // A barrier of `size` workgroups that carries kCarried floats of each of them.
+// (a flat load would have to be waited for with all loads before and after it)
+__device__ __forceinline__ float far_load(const float* p) {
+    return __hip_atomic_load((const __attribute__((address_space(1))) float*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 struct Team {
-    int* arrive;               // the counters: of the agent scope, then (a cache line on) near ones
+    int* flags;                // [size] of each workgroup how many barriers it has come to
     float* red;                // [4][kCarried][32]
     int* ok;                   // LDS
     int size, q, polls;
-    int epoch, arrived;        // barriers so far; of this kind
+    int epoch;                 // barriers so far
     bool near;
 
-    // So that the others need not wait for as long.
-    __device__ __forceinline__ void gone() const {             // thread 0
-        if (near) __hip_atomic_fetch_add(arrive + 32, kGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else __hip_atomic_fetch_add(arrive, kGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __device__ __forceinline__ void raise(int v) const {       // one thread
+        if (near) __hip_atomic_store(flags + q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else __hip_atomic_store(flags + q, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
+    // So that the others need not wait for as long.
+    __device__ __forceinline__ void gone() const { raise(kGone); }             // thread 0
 
     // a .. e: of thread 0
     __device__ __forceinline__ bool sync(float a, float b = 0.f, float c = 0.f, float d = 0.f, float e = 0.f) {
         ++epoch;
-        ++arrived;
         if (threadIdx.x == 0) {
             float* slot = red + (epoch & 3) * (kPairs * kCarried) + q;
             slot[0] = a;
@@ -208,14 +213,18 @@ struct Team {
             slot[4 * kPairs] = e;
         }
         stores_done();
-        if (threadIdx.x == 0) {
-            int* count = arrive + (near ? 32 : 0);
-            if (near) __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            else __hip_atomic_fetch_add(count, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            const int target = size * arrived;
-            int v = 0;
-            const bool here = poll(polls, near, [&]() { return (v = peek(count, near)) >= target; });
-            *ok = here && v < kGone;
+        if (threadIdx.x < 64) {                // a wavefront reads all flags at once (a counter: 32 additions, and as many
+            if (threadIdx.x == 0) raise(epoch);            // polls, one after the other)
+            const int at = (int)threadIdx.x < size ? (int)threadIdx.x : 0;
+            bool here = false, gone = false;
+            for (int k = 0; k < polls && !here && !gone; ++k) {
+                const int v = peek(flags + at);
+                here = __all(v >= epoch);
+                gone = __any(v >= kGone);
+                if (!here && !gone) __builtin_amdgcn_s_sleep(1);
+            }
+            acquire(near);
+            if (threadIdx.x == 0) *ok = here && !gone;
         }
         __syncthreads();
         return *ok != 0;
@@ -280,7 +289,6 @@ struct Team {
                 }
                 if (how == -2) __builtin_amdgcn_s_sleep(1);
             }
-            if (how > 0) asm volatile("buffer_inv sc0" ::: "memory");
             *ok = how;
         }
         __syncthreads();
@@ -292,10 +300,7 @@ struct Team {
     }
     // value k of workgroup lane % size, from the last sync
     __device__ __forceinline__ float value(int k) const {
-        // (a flat load would have to be waited for with all loads before and after it)
-        typedef __attribute__((address_space(1))) float* global_ptr;
-        return __hip_atomic_load((global_ptr)(red + (epoch & 3) * (kPairs * kCarried) + k * kPairs + (threadIdx.x & (size - 1))),
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return far_load(red + (epoch & 3) * (kPairs * kCarried) + k * kPairs + (threadIdx.x & (size - 1)));
     }
 };
 
@@ -638,7 +643,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
     auto taken = [&]() {                       // the same number of hands from there (uniform)
         int* flag = t.ok + 1;
         if (tid == 0)
-            *flag = poll(t.polls, t.near, [&]() { return peek(pair + (t.q ^ kTeam) * kPairInts, t.near) >= handed; });
+            *flag = poll(t.polls, t.near, [&]() { return peek(pair + (t.q ^ kTeam) * kPairInts) >= handed; });
         __syncthreads();
         return *flag != 0;
     };
@@ -663,13 +668,13 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
                     a[s % kAhead][k][e] = __builtin_amdgcn_raw_buffer_load_b128(
-                        rsrc, lane * 16, (s < 8 ? cols : rows) + k * kShared + (turn(s) * 2 + e) * 1024, 0);
+                        rsrc, lane * 16, (s < 8 ? cols : rows) + k * kShared + (turn(s) * 2 + e) * 1024, kPastL1);
         };
         // What the last barrier carried: asked for before the operands, which it would otherwise wait for (loads return in order).
         const float carried0 = look ? t.value(0) : 0.f, carried1 = look ? t.value(1) : 0.f;    // uniform
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (H == 2)                  // a tile of the strip's other half
-            other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)kColAt + (buf * kTeam + sn) * kShared + tp * 1024, 0);
+            other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, (int)kColAt + (buf * kTeam + sn) * kShared + tp * 1024, kPastL1);
 #pragma unroll
         for (int s = 0; s < kAhead; ++s) request(s);
         __builtin_amdgcn_sched_barrier(0);
@@ -739,8 +744,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
                 r2max = row_max_nan(t.value(1));
                 sum2 = t.value(3);
             } else {                           // added up by everybody
-                typedef __attribute__((address_space(1))) float* global_ptr;
-                const global_ptr sums = (global_ptr)(reinterpret_cast<float*>(mem + kSmallAt) + 2 * kRedSize + 2 * P);
+                float* sums = reinterpret_cast<float*>(mem + kSmallAt) + 2 * kRedSize + 2 * P;
                 if (tid < 16) {
                     sums[(half * 2) * P + sn * 16 + tid] = rs[0];
                     sums[(half * 2 + 1) * P + sn * 16 + tid] = r2[0];
@@ -751,7 +755,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
                 for (int k = 0; k < 4; ++k)
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        v[k][c] = __hip_atomic_load(sums + k * P + c * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        v[k][c] = far_load(sums + k * P + c * 64 + lane);
                 unsigned m1 = 0, m2 = 0;       // (a NaN wins: its bits are the largest)
                 sum2 = 0.f;
 #pragma unroll
@@ -813,8 +817,8 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
             alpha = 1.f;
             if constexpr (H == 2) {            // the other half
                 const int at = (sn * 8 + (tp >> 1)) * 1024 + lane * 16 + (tp & 1) * 8;
-                const u32x2 lead = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (int)kEAt, 0));
-                const u32x2 rest = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (int)kELoAt, 0));
+                const u32x2 lead = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (int)kEAt, kPastL1));
+                const u32x2 rest = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, (int)kELoAt, kPastL1));
                 *reinterpret_cast<u32x2*>(eimg + (tp >> 1) * 3 * 1024 + lane * 16 + (tp & 1) * 8) = lead;
                 *reinterpret_cast<u32x2*>(eimg + ((tp >> 1) * 3 + 1) * 1024 + lane * 16 + (tp & 1) * 8) = rest;
                 __syncthreads();
@@ -826,7 +830,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
                 e2[k] = zero4;
                 u32x4 ea[8];
 #pragma unroll
-                for (int s = 0; s < 8; ++s) ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + (k * 8 + s) * 1024, 0);
+                for (int s = 0; s < 8; ++s) ea[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, er + (k * 8 + s) * 1024, kPastL1);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int s = 0; s < 8; ++s)
@@ -855,7 +859,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         product(a, request, turn, eimg, std::integral_constant<int, 8>{}, acc,
                 [&]() {
                     here = taken();
-                    other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, eh + tp * 1024, 0);
+                    other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, eh + tp * 1024, kPastL1);
                 },
                 [&]() {
                     put_tile(eimg, tp, __builtin_bit_cast(f32x4, other));
@@ -911,8 +915,8 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         hand();
         if (half == 1) return Outcome::done;
         if (!taken()) return Outcome::dead;
-        q2 += __hip_atomic_load(sums + c16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        r2 += __hip_atomic_load(sums + 16 + c16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        q2 += far_load(sums + c16);
+        r2 += far_load(sums + 16 + c16);
         q2 = row16_max(q2);
         r2 = row16_max(r2);
         if (tid == 0) g.ops.dnorm[j * (P / 16) + sn] = float2{sqrtf(q2), sqrtf(r2)};
@@ -1093,10 +1097,25 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
     float* GV = reinterpret_cast<float*>(mem + kJvAt);
     float* Gsig = reinterpret_cast<float*>(mem + kSmallAt) + 2 * kRedSize;
     float* Gvinv = Gsig + P;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(uniform(mem), 0, (int)kTeamBytes, 0x00027000);
     auto copy4 = [&](float* dst, const float* from) {          // 16 columns
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             reinterpret_cast<f32x4*>(dst)[tid + u * kNT] = reinterpret_cast<const f32x4*>(from)[tid + u * kNT];
+    };
+    // what another workgroup has left, past L1: 16 columns to LDS, or one to registers; at: bytes into the team's memory
+    auto fetch4 = [&](float* dst, int at) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            reinterpret_cast<u32x4*>(dst)[tid + u * kNT] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (tid + u * kNT) * 16, at, kPastL1);
+    };
+    auto fetch_column = [&](int at, float (&v)[8]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float2 w = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (hw * P + 2 * l32 + 64 * k) * 4, at, kPastL1));
+            v[2 * k] = w.x;
+            v[2 * k + 1] = w.y;
+        }
     };
 
     // scale by 1 / max|entry| (the orthogonal factor does not depend on scale)
@@ -1165,18 +1184,19 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
             if (sweep > 0 || r > 0) {
                 if (tid == 0)
                     *flag = poll(t.polls, t.near, [&]() {
-                        return peek(version + sj, t.near) >= now && (!moves(r) || peek(version + si, t.near) >= now);
+                        return peek(version + sj) >= now && (!moves(r) || peek(version + si) >= now);
                     });
                 __syncthreads();
                 if (*flag == 0) return Outcome::dead;
-                copy4(YA, GA + sj * 16 * P);
-                copy4(YV, GV + sj * 16 * P);
+                const int aj = __builtin_amdgcn_readfirstlane(sj) * (16 * P * 4), ai = __builtin_amdgcn_readfirstlane(si) * (16 * P * 4);
+                fetch4(YA, (int)kJaAt + aj);
+                fetch4(YV, (int)kJvAt + aj);
                 if (r == 0) {
-                    copy4(XA, GA + si * 16 * P);
-                    copy4(XV, GV + si * 16 * P);
+                    fetch4(XA, (int)kJaAt + ai);
+                    fetch4(XV, (int)kJvAt + ai);
                 } else if (moves(r)) {
-                    get_column(GA + (si * 16 + hw) * P, x);
-                    get_column(GV + (si * 16 + hw) * P, u);
+                    fetch_column((int)kJaAt + ai, x);
+                    fetch_column((int)kJvAt + ai, u);
                 }
             }
             __syncthreads();
@@ -1263,7 +1283,7 @@ __device__ __forceinline__ Outcome jacobi(const WideArgs& g, int j, const Source
     }
     if (!t.sync(0.f)) return Outcome::dead;
     float* sig = red + 256;
-    if (tid < P) sig[tid] = Gsig[tid];
+    if (tid < P) sig[tid] = far_load(Gsig + tid);
     __syncthreads();
     if (eig) {
         // atoms = eigenvectors (columns of V) by descending eigenvalue, eig_sv = square roots of the
@@ -1388,13 +1408,13 @@ __device__ __forceinline__ void jacobi_alone(const WideArgs& g, int j, const Sou
 // Everything by value (what a call could change through a pointer would live in memory from the start).
 struct JacobiResult {
     Outcome how;
-    int epoch, arrived;        // of the barrier
+    int epoch;                 // of the barrier
     int tbase;
 };
 __device__ __attribute__((noinline)) JacobiResult jacobi_called(WideArgs g, int j, Source src, Team t, int* version, int tbase,
                                                                 unsigned char* mem, unsigned char* lds, float* red, int* flag) {
     const Outcome how = jacobi(g, j, src, t, version, tbase, mem, lds, red, flag);
-    return {how, t.epoch, t.arrived, tbase};
+    return {how, t.epoch, tbase};
 }
 __device__ __attribute__((noinline)) void jacobi_alone_called(WideArgs g, int j, Source src, unsigned char* mem,
                                                               unsigned char* lds, float* red, int* flag) {
@@ -1437,8 +1457,8 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
     unsigned char* mem = g.data + (size_t)team * kTeamBytes;
     int* sync = g.sync + team * kSyncInts;
     float* small = reinterpret_cast<float*>(mem + kSmallAt);
-    Team all = {sync + kArriveAt, small, flag, kSize, q, g.polls, 0, 0, false};
-    Team eight = {sync + kArriveJacAt, small + kRedSize, flag + 1, kJacTeam, q, g.polls, 0, 0, false};
+    Team all = {sync + kFlagsAt, small, flag, kSize, q, g.polls, 0, false};
+    Team eight = {sync + kFlagsJacAt, small + kRedSize, flag + 1, kJacTeam, q, g.polls, 0, false};
     int tbase = 0;
     const int blocks = (g.K - 1 - team) / g.teams + 1;         // of this team
     int undone = blocks;
@@ -1509,7 +1529,6 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
                     const JacobiResult r = jacobi_called(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag);
                     how = (Outcome)__builtin_amdgcn_readfirstlane((int)r.how);
                     eight.epoch = __builtin_amdgcn_readfirstlane(r.epoch);
-                    eight.arrived = __builtin_amdgcn_readfirstlane(r.arrived);
                     tbase = __builtin_amdgcn_readfirstlane(r.tbase);
                 } else
                     how = jacobi(g, j, src, eight, sync + kVersionAt, tbase, mem, lds, red, flag);
@@ -1548,7 +1567,7 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
         }
     }
     for (int e = tid; e < (PAIRS ? kSyncInts : kPairAt); e += kNT) {
-        const bool in_l2 = all.near && e != kArriveAt && (e < kMeetAt || e >= kPairAt) && e != kExitAt && e != kUndoneAt;
+        const bool in_l2 = all.near && (e < kMeetAt || e >= kPairAt) && e != kExitAt && e != kUndoneAt;
         if (in_l2 || rest > 0) {               // (rest > 0: this workgroup may have left without knowing that it is near)
             __hip_atomic_store(sync + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
