@@ -113,8 +113,15 @@ __device__ __forceinline__ F16x2Pair split_f16x2(float v0, float v1) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     F16x2Pair r;
     r.hi = pack_f16(v0, v1);
-    const f16x2 h = __builtin_bit_cast(f16x2, r.hi);
-    r.lo = pack_f16(v0 - (float)h[0], v1 - (float)h[1]);
+    // v - 1 * hi with a one and a packed hi that the compiler does not see through: v_fma_mix_f32 reads the halves as they
+    // are, four instructions a pair (eight: both values rounded apart, unpacked and subtracted)
+    float one = 1.f;
+    asm("" : "+s"(one));
+    unsigned hi = r.hi;
+    asm("" : "+v"(hi));
+    const f16x2 h = __builtin_bit_cast(f16x2, hi);
+    r.hi = hi;
+    r.lo = pack_f16(fmaf(-(float)h[0], one, v0), fmaf(-(float)h[1], one, v1));
     return r;
 }
 // Dictionary entries (|q| <= 1 for orthonormal atoms; anything below 8 is representable) are

@@ -13,10 +13,12 @@
 //   * Steps.  The singular values are pulled towards one by scaling X before a step: with all of
 //     them in [l, 1], X sqrt(3 / (1 + l + l^2)) makes the step's polynomial map [l, 1] to the
 //     smallest possible interval [l', 1].  A smaller singular value is safe (the polynomial never
-//     exceeds one and is positive on (0, sqrt(3))), it only takes longer; l starts at 0.16 (block
-//     matrices of this method have condition numbers of 2 to 10).  The last step is quintic, X (I + c1 E + c2 E^2),
-//     E = I - X^T X (ns_scale.h).  Five steps where the plain iteration takes seven.
-//   * The step.  Two wavefronts have a strip of 16 columns of X (v_mfma_f32_16x16x32_bf16 tiles, four
+//     exceeds one and is positive on (0, sqrt(3))), it only takes longer; a larger l than the guess costs steps and rounding (the
+//     largest values are sent down to l' first, where an error weighs 1 / l' as much).  l starts at a guess from the spread of
+//     the squared singular values, |G|_F^2 / (p mu^2) - 1 with mu = tr G / p, which the first product shows (kSpread).  The last step
+//     is quintic, X (I + c1 E + c2 E^2), E = I - X^T X (ns_scale.h).  Four to seven steps where the plain iteration takes seven
+//     to ten.
+//   * The step.  Two wavefronts have a strip of 16 columns of X (16x16x32 MFMA tiles, four
 //     consecutive rows of one column per lane and tile), half of its row tiles each; a wavefront alone on its SIMD issues
 //     a vector instruction every 8 cycles, and its LDS reads, products and splits then follow one another.
 //     An accumulator tile is at the same time
@@ -25,14 +27,20 @@
 //     the registers that hold E (each with the other wavefront's half from LDS), and the A operands (the other strips'
 //     columns of X, and, transposed by ds_read_b64_tr_b16 on the way out, its rows) go through LDS.  G and E are symmetric:
 //     at p = 64 ten of their sixteen tiles are computed and the others read transposed.
-//   * The products run at fp32 accuracy: every entry is the exact sum of three bf16 parts
+//   * The products run at fp32 accuracy.  p < 64: every entry is the exact sum of three bf16 parts
 //     (device_utils.h), six partial products with fp32 accumulation; three for E^2 in the last step, which is
-//     below 1e-4 and added to E.  (With its leading parts alone, three products for X E and the plain series, a
-//     signed permutation with one late singular value came out up to 4.2e-7 off; now exactly, in the same time.)
-// Measured (p = 64, launch to launch): inside sbo_iterate 22.4 us with a wavefront per strip, 19.5 as it is (K = 16), a new
-// orthobase 20.8 -> 17.6; p = 32 8.6 us, p = 16 7.2.  Of 36000 cycles at p = 64, five steps take 22000 (matrix work 6000 of
-// them), the last product and its E^2 2500, the scale of the input 2000, the sum of the pieces 2500, offsets, exchange and
-// output 5000.
+//     below 1e-4 and added to E.  p = 64, where LDS moves 240 KB a step with three parts: two fp16 parts, three partial
+//     products.  They leave 2^-22 of an entry.  In G that is a symmetric error, which the next step takes out; for the last
+//     step the products that were left out are added.  What is left in X E is made up for by three roundings less: E is scaled by the
+//     mantissa of alpha, so that the products are added to X without one, and the two steps of a contraction are summed apart.
+//     |Q - Q64|_F / sqrt(p) on block matrices of training rounds (96 to 65536 signals, condition 1.3 to 700) 0.54 to 1.05 of that with three
+//     parts and l = 0.16, on average 0.81 (p = 32 0.91, p = 16 0.94: the guess alone); p = 32, 16 with two parts 1.3 and 1.5, in the same time.
+//   * The steps' branches are those of scalars: as the sum that decides comes out of lanes, the compiler would take every one of
+//     them for divergent (p = 16: 2 % of an iteration).
+// Measured (p = 64, launch to launch): inside sbo_iterate 22.4 us with a wavefront per strip, 19.5 with two (K = 16, 16384 signals), 17.4 with two
+// parts, 15.6 with the guess (a step less: 1.4 us); a new orthobase 20.8, 17.6, 15.9, 14.5.  p = 32 8.6 us, p = 16 7.2.  Of 37000 cycles
+// at p = 64, K = 16 (seven steps, before the guess): the sum of the pieces 8000 (a CU takes 25 to 40 bytes a cycle of what others have just
+// written), the scale of the input 2000, a step 3500, the last one's E^2 1300, output 2200.
 //
 // The same launch can (a) sum the per-piece partial matrices of the fused select + accumulate
 // kernel on the way in, in piece order, which saves the separate reduction launch, and (b) form
@@ -75,11 +83,51 @@ struct NsArgs {
     int n_clear;
 };
 
-// sqrt(3 / (1 + l + l^2)) for l = 0.16 and then the l that the steps leave: 0.16, 0.375, 0.71, 0.96 (a chain of selects: a table
-// would be read from memory in every step)
-constexpr float kAlpha0 = 1.5907f;
-__device__ __forceinline__ float step_alpha(int it) {
-    return it == 0 ? kAlpha0 : it == 1 ? 1.4081f : it == 2 ? 1.1601f : it == 3 ? 1.0206f : 1.f;
+// sqrt(3 / (1 + l + l^2)) for a first l and then the l that the steps leave: from k = 1 on 0.064, 0.16 (k = 2), 0.37, 0.72, 0.96; from 8 on
+// 0.45, 0.80, 0.98; from 14 on 0.09, 0.22, 0.49, 0.83, 0.99; one elsewhere (a chain of selects: a table would be read from memory in
+// every step).
+__device__ __forceinline__ float step_alpha(int k) {
+    float a = 1.f;
+    a = k == 1 ? 1.67603f : a;
+    a = k == 2 ? 1.5907f : a;
+    a = k == 3 ? 1.4081f : a;
+    a = k == 4 ? 1.1601f : a;
+    a = k == 5 ? 1.0206f : a;
+    a = k == 14 ? 1.65287f : a;
+    a = k == 15 ? 1.53661f : a;
+    a = k == 16 ? 1.31621f : a;
+    a = k == 17 ? 1.0889f : a;
+    a = k == 18 ? 1.00613f : a;
+    a = k == 8 ? 1.34738f : a;
+    a = k == 9 ? 1.11f : a;
+    return k == 10 ? 1.00948f : a;
+}
+
+// Where l starts, by the spread of the squared singular values: 0.45, 0.16, 0.09, 0.064.  Steps simulated in 64 bits on block matrices of
+// training rounds, with 0.45 / 0.16: spread 0.13 to 0.15 4 / 5, 0.2 to 0.3 5 / 5, beyond 0.3 5.2 to 7 / 5; with 0.16 / 0.064 0.45 to
+// 0.6 5 / 6, 0.75 to 0.9 11.3 / 10.5, 1.1 to 1.4 10 / 9.2, beyond 1.4 11.8 / 10.3 and more.  0.09 between 0.6 and 1.4: with 0.064 the
+// error was up to 1.15 of what it was with 0.16, now 0.95 to 1.05, in as many steps.  Lower l lose accuracy (0.025 beyond
+// 1.4: up to 1.5 of the error), and so do 0.09 and 0.064 for p < 64, which stays with 0.16 there (1.28).
+constexpr float kSpread[3] = {0.18f, 0.6f, 1.4f};
+// X and E are split in two fp16 parts each (device_utils.h), times this: no singular value is above one after a step, no
+// entry of E above 1.9.
+template <int P>
+constexpr int ns_parts() { return P == 64 ? 2 : 3; }
+template <int P>
+constexpr float ns_scale() { return ns_parts<P>() == 2 ? 16384.f : 1.f; }
+// alpha = mantissa (in [1, 2)) times power of two, for normal numbers above zero
+__device__ __forceinline__ float mantissa(float alpha) {
+    return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, alpha) & 0x007fffffu) | 0x3f800000u);
+}
+__device__ __forceinline__ float power_of_two(float alpha) {
+    return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, alpha) & 0x7f800000u);
+}
+// Power of two that brings entries of at most this magnitude (its bits) below kScale; zero, so that the block goes to the Jacobi
+// SVD, where sums of their squares leave the range of fp32.
+__device__ __forceinline__ float input_scale(unsigned mx) {
+    const unsigned e = mx >> 23;               // biased exponent
+    if (e < 64u || e > 190u) return 0.f;
+    return __builtin_bit_cast(float, (unsigned)(127 + 13 + 127 - (int)e) << 23);
 }
 
 // wavefronts per strip of 16 columns: they share out its row tiles
@@ -94,12 +142,13 @@ constexpr int ns_threads() {
 // bytes of one LDS image of X or E: per strip and contraction step of 32, three parts of 64 lanes x 16 bytes
 template <int P>
 constexpr int ns_image_bytes() {
-    return (P / 16) * ((P / 16 + 1) / 2) * 3 * 1024;
+    return (P / 16) * ((P / 16 + 1) / 2) * ns_parts<P>() * 1024;
 }
 // dynamic LDS: two images (the Jacobi routine reuses this part) | red[2][8 wavefronts] | cols[6][P] floats
 template <int P>
 constexpr size_t ns_front_bytes() {
-    const size_t img = (size_t)2 * ns_image_bytes<P>(), jac = (size_t)jacobi_lds_floats<P>() * 4;
+    const size_t rest = ns_parts<P>() == 2 ? ns_image_bytes<P>() / 2 : 0;      // what two parts leave, in the last step
+    const size_t img = (size_t)2 * ns_image_bytes<P>() + rest, jac = (size_t)jacobi_lds_floats<P>() * 4;
     const size_t sq = (size_t)(ns_threads<P>() + 2) * 8;
     const size_t a = img > jac ? img : jac;
     return ((a > sq ? a : sq) + 15) / 16 * 16;
@@ -143,6 +192,12 @@ __device__ __forceinline__ float wave_max_nan(float x) {
     return __builtin_bit_cast(float, max(b0, b1));
 }
 
+// What all lanes agree on, as the compiler is to know it: the steps and their branches then are those of scalars.
+__device__ __forceinline__ float uniform(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+__device__ __forceinline__ bool uniform(bool x) { return __builtin_amdgcn_readfirstlane((int)x) != 0; }
+
 // The iteration and the output, for the wavefronts that have the first (HH = 0) or the second half of a strip's row tiles
 // (the branch between the two is what a choice of registers per lane costs otherwise: 48 selects a step); barriers are the
 // same in both.  Returns the steps, or 0: not converged.  xr[a][r] = X[t*16 + grp*4 + r][col], t = HH*TH + a.
@@ -152,26 +207,42 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
     constexpr int T = P / 16, S = (T + 1) / 2, HV = ns_halves<P>(), TH = T / HV, NW = T * HV, hh = HH;
     // G and E are symmetric: at p = 64 the fourth tile of a strip is the transpose of the second of another one
     constexpr bool SYM = T == 4;
+    constexpr float kScale = ns_scale<P>();
     constexpr int NE = SYM && hh == 1 ? 1 : TH;          // tiles of E of this wavefront
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = lane >> 4, c16 = lane & 15, col = strip * 16 + c16;
 
-    // Three bf16 parts of a row tile, two words each: lane (grp, c16) holds rows grp*4 .. +3 of column c16.
+    // The parts of a row tile, two words each: lane (grp, c16) holds rows grp*4 .. +3 of column c16.
+    constexpr int NPT = ns_parts<P>();
     struct Parts {
-        u32x2 p[3];
+        u32x2 p[NPT];
     };
     auto split_tile = [](f32x4 v) {
-        const Bf16x3Pair a = split_bf16x3(v.x, v.y), b = split_bf16x3(v.z, v.w);
-        return Parts{{u32x2{a.hi, b.hi}, u32x2{a.mid, b.mid}, u32x2{a.lo, b.lo}}};
+        if constexpr (NPT == 2) {
+            const F16x2Pair a = split_f16x2(v.x, v.y), b = split_f16x2(v.z, v.w);
+            return Parts{{u32x2{a.hi, b.hi}, u32x2{a.lo, b.lo}}};
+        } else {
+            const Bf16x3Pair a = split_bf16x3(v.x, v.y), b = split_bf16x3(v.z, v.w);
+            return Parts{{u32x2{a.hi, b.hi}, u32x2{a.mid, b.mid}, u32x2{a.lo, b.lo}}};
+        }
+    };
+    auto remainder = [](f32x4 v, const Parts& w) {             // what two parts leave of a tile, as fp16
+        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+        const unsigned u0 = w.p[0].x, u1 = w.p[0].y, v0 = w.p[1].x, v1 = w.p[1].y;
+        const f16x2 h0 = __builtin_bit_cast(f16x2, u0), h1 = __builtin_bit_cast(f16x2, u1);
+        const f16x2 l0 = __builtin_bit_cast(f16x2, v0), l1 = __builtin_bit_cast(f16x2, v1);
+        return u32x2{pack_f16(v.x - (float)h0[0] - (float)l0[0], v.y - (float)h0[1] - (float)l0[1]),
+                     pack_f16(v.z - (float)h1[0] - (float)l1[0], v.w - (float)h1[1] - (float)l1[1])};
     };
     // The LDS image: per (strip, step, part) 1 KiB, tile 2s in the first half, tile 2s+1 in the
     // second, 8 bytes per (grp, c16), the upper two groups with their columns exchanged by eights:
     // 32 consecutive lanes of a write, of a straight and of a transposing read each cover all banks.
     const int lane_at = (grp * 16 + (c16 ^ ((grp >> 1) * 8))) * 8;
-    auto unit = [&](unsigned char* img, int st, int t, int pl) { return img + ((st * S + (t >> 1)) * 3 + pl) * 1024 + (t & 1) * 512; };
+    auto unit = [&](unsigned char* img, int st, int t, int pl) { return img + ((st * S + (t >> 1)) * NPT + pl) * 1024 + (t & 1) * 512; };
+    auto rest = [&](int st, int t) { return lds_raw + 2 * ns_image_bytes<P>() + (st * S + (t >> 1)) * 1024 + (t & 1) * 512; };
     auto write_tile = [&](unsigned char* img, int t, const Parts& w) {       // of the own strip
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x2*>(unit(img, strip, t, pl) + lane_at) = w.p[pl];
+        for (int pl = 0; pl < NPT; ++pl) *reinterpret_cast<u32x2*>(unit(img, strip, t, pl) + lane_at) = w.p[pl];
     };
     auto read_tile = [&](unsigned char* img, int st, int t, int pl) {
         return *reinterpret_cast<const u32x2*>(unit(img, st, t, pl) + lane_at);
@@ -192,13 +263,17 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
         return SYM && i == 3 ? read_rows(img, (st + 3) & 3, 1, pl) : read_tile(img, st, i, pl);
     };
     auto mfma = [](u32x2 a0, u32x2 a1, u32x2 b0, u32x2 b1, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{a0.x, a0.y, a1.x, a1.y}),
-                                                       __builtin_bit_cast(bf16x8, u32x4{b0.x, b0.y, b1.x, b1.y}), c, 0, 0, 0);
+        const u32x4 a = {a0.x, a0.y, a1.x, a1.y}, b = {b0.x, b0.y, b1.x, b1.y};
+        if constexpr (NPT == 2)
+            return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     };
-    // the six partial products, smallest first: (A part, B part)
-    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
-    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
-    constexpr int kOrder[3] = {2, 0, 1};       // in which they first use the parts
+    // the partial products, smallest first: (A part, B part)
+    constexpr int NP = NPT == 2 ? 3 : 6;
+    constexpr int TA[6] = {NPT == 2 ? 1 : 2, 0, NPT == 2 ? 0 : 1, 1, 0, 0};
+    constexpr int TB[6] = {0, NPT == 2 ? 1 : 2, NPT == 2 ? 0 : 1, 0, 1, 0};
+    constexpr int kOrder[3] = {NPT - 1, 0, 1}; // in which they first use the parts
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
     const u32x2 none = {0u, 0u};
     // Row tiles of G and E are kept in the order strip, strip + 1, ... (mod T); this wavefront has numbers
@@ -218,7 +293,7 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
             all[0] = own[0];
         } else {
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
+            for (int k = 0; k < NPT; ++k)
 #pragma unroll
                 for (int a = 0; a < TH; ++a) {
                     all[hh * TH + a].p[kOrder[k]] = own[a].p[kOrder[k]];
@@ -228,7 +303,7 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
     };
     auto whole_e = [&](unsigned char* img, const Parts (&own)[NE], Parts (&all)[T]) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
+        for (int k = 0; k < NPT; ++k)
 #pragma unroll
             for (int i = 0; i < T; ++i)
                 all[i].p[kOrder[k]] = i >= hh * TH && i < hh * TH + NE ? own[(i - hh * TH) % NE].p[kOrder[k]] : read_e(img, strip, i, kOrder[k]);
@@ -241,7 +316,7 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
     unsigned char* const ximg = lds_raw;
     unsigned char* const eimg = lds_raw + ns_image_bytes<P>();
     int it = 0;
-    bool narrow = false;
+    int first = 0, first_test = 1;             // the step's place in step_alpha's order; the first one that can be the last
     while (true) {
         Parts xo[TH], xq[T];
 #pragma unroll
@@ -253,45 +328,62 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
 
         // this wavefront's tiles of G = X^T X
         f32x4 ge[NE];
+        u32x2 rows[T][NPT][TH];
         {
-            u32x2 a[T][3][NE];                 // requested in the order in which the products use them
+            u32x2 a[T][NPT][NE];                 // requested in the order in which the products use them
             whole(ximg, xo, xq);
 #pragma unroll
-            for (int s = 0; s < S; ++s)
+            for (int k = 0; k < NPT; ++k)
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
+                for (int s = 0; s < S; ++s)
 #pragma unroll
                     for (int i = 0; i < NE; ++i) {
                         if (hh == 0 && i == 0) continue;       // the diagonal tile: the own strip
                         a[2 * s][kOrder[k]][i] = read_tile(ximg, mine(i), 2 * s, kOrder[k]);
                         if (2 * s + 1 < T) a[2 * s + 1][kOrder[k]][i] = read_tile(ximg, mine(i), 2 * s + 1, kOrder[k]);
                     }
+            // The A operands of X E: on their way during the products of G.
+#pragma unroll
+            for (int k = 0; k < NPT; ++k)
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int i = 0; i < TH; ++i) {
+                        rows[2 * s][kOrder[k]][i] = read_rows(ximg, strip_of[2 * s], hh * TH + i, kOrder[k]);
+                        if (2 * s + 1 < T)
+                            rows[2 * s + 1][kOrder[k]][i] = read_rows(ximg, strip_of[2 * s + 1 < T ? 2 * s + 1 : 0], hh * TH + i, kOrder[k]);
+                    }
 #pragma unroll
             for (int i = 0; i < NE; ++i) ge[i] = zero4;
-            f32x4 g0 = zero4;                  // the diagonal tile's steps are summed apart: its entries are near one
+            f32x4 g1[NE];                      // the second step's: two shorter chains, and less is rounded
 #pragma unroll
-            for (int s = 0; s < S; ++s)
+            for (int i = 0; i < NE; ++i) g1[i] = zero4;
 #pragma unroll
-                for (int q = 0; q < 6; ++q)
+            for (int q = 0; q < NP; ++q)
+#pragma unroll
+                for (int s = 0; s < S; ++s)
 #pragma unroll
                     for (int i = 0; i < NE; ++i) {
                         constexpr int last = T - 1;
                         const int t1 = 2 * s + 1 < T ? 2 * s + 1 : last;
                         const bool own = hh == 0 && i == 0;
-                        f32x4& sum = own && s > 0 ? g0 : ge[i];
+                        f32x4& sum = s > 0 ? g1[i] : ge[i];
                         sum = mfma(own ? xq[2 * s].p[TA[q]] : a[2 * s][TA[q]][i],
                                    T == 1 ? none : own ? xq[t1].p[TA[q]] : a[t1][TA[q]][i], xq[2 * s].p[TB[q]],
                                    T > 1 ? xq[t1].p[TB[q]] : none, sum);
                     }
-            if constexpr (S > 1 && hh == 0) ge[0] += g0;
+            if constexpr (S > 1) {
+#pragma unroll
+                for (int i = 0; i < NE; ++i) ge[i] += g1[i];
+            }
         }
 
-        float alpha = narrow ? 1.f : step_alpha(it);               // X is scaled by this before the step
+        float alpha = step_alpha(first + min(it, 5)) / kScale;               // xr times this is X, scaled as the step wants it
         bool last = false;
         float fr_own = 0.f;
         // Whether this can be the last step.  Not the second and the third of a spectrum that is not narrow: two scaled steps
         // leave values that were more than a tenth apart further from one than the line allows.  (NaN stays NaN.)
-        const bool test = it > 2 || (it > 0 && narrow);
+        const bool test = it >= first_test;
         if (it == 0) {
             // The scale of the input.  The iteration sends every singular value in (0, sqrt(3)) to
             // +1, one in (sqrt(3), sqrt(5)) to -1 (an orthogonal matrix that is NOT U V^T, and
@@ -350,21 +442,26 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
             }
             mu *= 1.f / P;
             // zero, infinite, NaN or overflowing input: not for this iteration
-            if (!(rsmax > 1e-37f && rsmax < 3e37f)) return 0;
+            if (!uniform(rsmax > 1e-37f && rsmax < 3e37f)) return 0;
             float b2 = 2.9f * __builtin_amdgcn_rcpf(rsmax);
-            narrow = narrow_spectrum<P>(sum2, mu);
-            if (narrow)
+            const float r = __builtin_amdgcn_rcpf(mu), spread = uniform((sum2 * r) * (r * (1.f / P))) - 1.f;
+            if (spread < kNarrow<P> * kNarrow<P>) {
                 b2 = fminf(b2, __builtin_amdgcn_rcpf(mu));
-            else if (r2max > 1e-37f && r2max < 3e37f)
-                b2 = fminf(b2, kAlpha0 * kAlpha0 / 1.04f * __builtin_amdgcn_rsqf(r2max));
-            alpha = __builtin_amdgcn_sqrtf(b2);
+                first = 20;                    // as it is
+            } else {
+                first = spread < kSpread[0] ? 8 : spread < kSpread[1] || P < 64 ? 2 : spread < kSpread[2] ? 14 : 1;
+                first_test = spread < kSpread[1] || P < 64 ? 3 : 4;
+                const float a0 = step_alpha(first);
+                if (r2max > 1e-37f && r2max < 3e37f) b2 = fminf(b2, a0 * a0 * (1.f / 1.04f) * __builtin_amdgcn_rsqf(r2max));
+            }
+            alpha = uniform(__builtin_amdgcn_sqrtf(b2));
         } else if (test) {
             float fr = 0.f;
 #pragma unroll
             for (int i = NE - 1; i >= 0; --i) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float e = diag[i][r] - ge[i][r];
+                    const float e = fmaf(-1.f / (kScale * kScale), ge[i][r], diag[i][r]);
                     fr = fmaf(e, e, fr);
                 }
                 if (SYM && hh == 0 && i == 1) fr *= 2.f;       // and its transpose
@@ -372,14 +469,20 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
             fr_own = sum_groups(group_sum<16>(fr));
             if constexpr (NW > 1) publish(it & 1, fr_own);
         }
-        // E = I - alpha^2 G, then X <- alpha (X + X E / 2)
+        // E = I - alpha^2 G (times kScale), then X <- alpha (X + X E / 2)
         f32x4 eo[NE];
         Parts ep[NE], eq[T];
-        auto make_e = [&](float a2) {
+        // (times the mantissa of alpha: what the products add to X is then scaled by a power of two, without a rounding)
+        auto make_e = [&]() {
+            const float beta = NPT == 2 ? mantissa(alpha) : 1.f, a2 = beta * kScale * alpha * alpha;
 #pragma unroll
             for (int i = 0; i < NE; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) eo[i][r] = diag[i][r] - a2 * ge[i][r];
+                for (int r = 0; r < 4; ++r) {
+                    float e = (beta * kScale) * diag[i][r] - a2 * ge[i][r];
+                    asm("" : "+v"(e));         // (or it is rounded to fp16 in a second such instruction, twice)
+                    eo[i][r] = e;
+                }
         };
         auto share_e = [&](bool image) {       // its parts, and to the image
 #pragma unroll
@@ -388,37 +491,32 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
                 if (image) write_tile(eimg, hh * TH + i, ep[i]);
             }
         };
-        // The A operands of X E, requested in the order in which the products use them.
-        u32x2 rows[T][3][TH];
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int i = 0; i < TH; ++i) {
-                    rows[2 * s][kOrder[k]][i] = read_rows(ximg, strip_of[2 * s], hh * TH + i, kOrder[k]);
-                    if (2 * s + 1 < T)
-                        rows[2 * s + 1][kOrder[k]][i] = read_rows(ximg, strip_of[2 * s + 1 < T ? 2 * s + 1 : 0], hh * TH + i, kOrder[k]);
-                }
-        make_e(alpha * alpha);
+        make_e();
         share_e(HV > 1);
         if (NW > 1) __syncthreads();           // (and the last reads of X's image)
+        whole_e(eimg, ep, eq);
         if (test) {                            // has this been the last but one step?
             float fr = NW > 1 ? red[(it & 1) * 8] : fr_own;
 #pragma unroll
             for (int w = 1; w < NW; ++w) fr += red[(it & 1) * 8 + w];
+            fr = uniform(fr);
             if (!(fr < 2.f * P)) return 0;     // NaN or diverging: leave it to the Jacobi SVD
             last = fr < kLastEps * kLastEps;   // |E|_F, a bound on the spectral norm of E
             if (!last && it >= g.max_iters) return 0;
         }
         if (last) {                            // uniform
-            if (HV == 1 || alpha != 1.f) {     // uniform: E without the scaling
-                alpha = 1.f;
-                make_e(1.f);
-                share_e(true);                 // (the own tiles of the image, which nobody has read yet)
-                __syncthreads();
+            if constexpr (NPT == 2) {
+#pragma unroll
+                for (int a = 0; a < TH; ++a) *reinterpret_cast<u32x2*>(rest(strip, hh * TH + a) + lane_at) = remainder(xr[a], xo[a]);
             }
-            whole_e(eimg, ep, eq);
+            if (HV == 1 || alpha != 1.f / kScale) {            // uniform: E without the scaling
+                __syncthreads();               // (E's image has been read)
+                alpha = 1.f / kScale;
+                make_e();
+                share_e(true);
+                __syncthreads();
+                whole_e(eimg, ep, eq);
+            }
             // E^2 from the three largest partial products: 2^-16 of something below 1e-4
             f32x4 e2[NE];
 #pragma unroll
@@ -441,32 +539,62 @@ __device__ __forceinline__ int iterate(const NsArgs& g, int j, int strip, f32x4 
                     e2[i] = mfma(lo[0], hi[0], eq[2 * s].p[1], b(1), e2[i]);
                     e2[i] = mfma(lo[0], hi[0], eq[2 * s].p[0], b(0), e2[i]);
                 }
-#pragma unroll
-            for (int i = 0; i < NE; ++i) eo[i] = kLastLinear * eo[i] + kLastSquare * e2[i];
             __syncthreads();                   // E's image has been read
+            if constexpr (NPT == 2) {
+                // What the two parts have left out of G, where it decides the rounding of the result: the products of
+                // what they leave of X, and on the diagonal, where they add up, those of the second parts.
+                f32x4 c[NE];
+#pragma unroll
+                for (int i = 0; i < NE; ++i) c[i] = zero4;
+                auto rest_tile = [&](int st, int t) { return *reinterpret_cast<const u32x2*>(rest(st, t) + lane_at); };
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const u32x2 x0 = read_tile(ximg, strip, 2 * s, 0), x1 = read_tile(ximg, strip, 2 * s + 1, 0);
+                    const u32x2 d0 = rest_tile(strip, 2 * s), d1 = rest_tile(strip, 2 * s + 1);
+#pragma unroll
+                    for (int i = 0; i < NE; ++i) {
+                        c[i] = mfma(read_tile(ximg, mine(i), 2 * s, 0), read_tile(ximg, mine(i), 2 * s + 1, 0), d0, d1, c[i]);
+                        c[i] = mfma(rest_tile(mine(i), 2 * s), rest_tile(mine(i), 2 * s + 1), x0, x1, c[i]);
+                    }
+                    if (hh == 0) {
+                        const u32x2 l0 = read_tile(ximg, strip, 2 * s, 1), l1 = read_tile(ximg, strip, 2 * s + 1, 1);
+                        c[0] = mfma(l0, l1, l0, l1, c[0]);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < NE; ++i) eo[i] -= (1.f / kScale) * c[i];
+            }
+#pragma unroll
+            for (int i = 0; i < NE; ++i) eo[i] = kLastLinear * eo[i] + (kLastSquare / kScale) * e2[i];
             share_e(HV > 1);
             if (HV > 1) __syncthreads();
+            whole_e(eimg, ep, eq);
         }
-        whole_e(eimg, ep, eq);
         // row tiles of X E
-        f32x4 acc[TH];
+        f32x4 acc[TH], acc1[TH];
 #pragma unroll
-        for (int i = 0; i < TH; ++i) acc[i] = zero4;
+        for (int i = 0; i < TH; ++i) acc[i] = acc1[i] = zero4;
 #pragma unroll
-        for (int s = 0; s < S; ++s)
+        for (int q = 0; q < NP; ++q)
 #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int s = 0; s < S; ++s)
 #pragma unroll
                 for (int i = 0; i < TH; ++i) {
                     const int t1 = T > 1 ? 2 * s + 1 : 0;
-                    acc[i] = mfma(rows[2 * s][TA[q]][i], T > 1 ? rows[t1][TA[q]][i] : none, eq[2 * s].p[TB[q]],
-                                  T > 1 ? eq[t1].p[TB[q]] : none, acc[i]);
+                    f32x4& sum = s > 0 ? acc1[i] : acc[i];
+                    sum = mfma(rows[2 * s][TA[q]][i], T > 1 ? rows[t1][TA[q]][i] : none, eq[2 * s].p[TB[q]],
+                               T > 1 ? eq[t1].p[TB[q]] : none, sum);
                 }
 #pragma unroll
-        for (int i = 0; i < TH; ++i) xr[i] = alpha * xr[i] + (0.5f * alpha) * acc[i];
+        for (int i = 0; i < TH; ++i) {
+            if constexpr (S > 1) acc[i] += acc1[i];
+            xr[i] = (kScale * alpha) * xr[i] + (0.5f * (NPT == 2 ? power_of_two(alpha) : alpha)) * acc[i];
+        }
         ++it;
         if (last) break;
     }
+#pragma unroll
+    for (int a = 0; a < TH; ++a) xr[a] *= 1.f / kScale;
 
     // D[j][k][:] = column k of X; the same values in the coding kernels' operand orders
     f32x4* Dj = reinterpret_cast<f32x4*>(g.D + (int64_t)j * P * P);
@@ -576,6 +704,13 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
                     for (int t = 0; t < TH; ++t) sum[t] += v[k][t];
                 }
         }
+        unsigned mx = 0;                       // largest magnitude (a NaN wins)
+#pragma unroll
+        for (int t = 0; t < TH; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = max(mx, __builtin_bit_cast(unsigned, fabsf(sum[t][r])));
+        mx = __builtin_bit_cast(unsigned, wave_max_nan(__builtin_bit_cast(float, mx)));
+        if (lane == 0) red[wave] = __builtin_bit_cast(float, mx);
         f32x4* rows = reinterpret_cast<f32x4*>(lds_raw) + strip * (16 * LD);
 #pragma unroll
         for (int t = 0; t < TH; ++t) {
@@ -584,7 +719,10 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         }
         __syncthreads();
 #pragma unroll
-        for (int a = 0; a < TH; ++a) xr[a] = rows[c16 * LD + (hh * TH + a) * 4 + grp];
+        for (int w = 0; w < T * HV; ++w) mx = max(mx, __builtin_bit_cast(unsigned, red[w]));
+        const float scale = ns_parts<P>() == 2 ? input_scale(mx) : 1.f;
+#pragma unroll
+        for (int a = 0; a < TH; ++a) xr[a] = scale * rows[c16 * LD + (hh * TH + a) * 4 + grp];
         __syncthreads();                       // the strips become the images
     }
 

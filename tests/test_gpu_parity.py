@@ -925,6 +925,34 @@ def test_polar_of_narrow_spectra_is_accurate(p, kind):
     assert err.max() <= 1e-6
 
 
+@pytest.mark.parametrize("p", [16, 32, 64])
+@pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
+def test_polar_on_both_sides_of_the_lines_of_the_spread(p, scale):
+    """The first guess of the smallest singular value hangs on the spread of the squared ones (0.01, 0.18, 0.6, 1.4: kSpread in
+    polar_ns.hip).  An eighth of the values lies above the others, so that the spread is 1 % below and above each line.
+    Bound: a rounding of 2^-24 in every step, where singular values of 1 / cond weigh it cond times as much."""
+    rng = np.random.default_rng(47 + p)
+    h, mats, conds = p // 8, [], []
+    for line in (0.01, 0.18, 0.6, 1.4):
+        for want in (0.99 * line, 1.01 * line):
+            lo, hi = 1.0, 1e3
+            for _ in range(80):
+                x = (lo + hi) / 2
+                s2 = np.r_[np.full(h, x), np.ones(p - h)]
+                lo, hi = (x, hi) if (s2 ** 2).mean() / s2.mean() ** 2 - 1 < want else (lo, x)
+            mats.append((synth.random_onb(rng, p) * np.sqrt(s2)) @ synth.random_onb(rng, p) * scale)
+            conds.append(np.sqrt(x))
+    M32 = np.stack(mats).astype(np.float32)
+    with Sbo(p, len(mats), 4, 256) as g:
+        D = g.polar(M32, np.zeros_like(M32), None)
+        steps = -np.array(sbo.sbo_svd_sweeps(g.ctx, len(mats)))
+    Q = np.stack([orc.o_polar(m.astype(np.float64)) for m in M32])
+    err = np.sqrt(((D - Q) ** 2).sum((1, 2)) / p)
+    print(f"  p={p} scale={scale}: |Q - Q64| {err}, steps {steps}", flush=True)
+    assert (steps > 0).all() and (steps <= 7).all()
+    assert (err <= steps * np.array(conds) * 2.0 ** -24).all()
+
+
 @pytest.mark.parametrize("K", [1, 9, 33])               # one team; two groups of eight; teams with three blocks in turn
 @pytest.mark.parametrize("jacobi_only", [False, True], ids=["auto", "jacobi"])
 def test_polar_p256_teams_of_workgroups(K, jacobi_only):
