@@ -8,8 +8,8 @@
 // wrong: the smallest column norm is an upper bound of the smallest singular value, and where atoms are
 // rarely used it is close to it.  From 0.5 on the values have met and it is left alone.  (Simulated on block
 // matrices of first training rounds, condition 60 to 5000: 9 to 15 steps instead of 11 to 22; condition
-// below 7: as without it.  p <= 64, condition 3 to 14, keeps the fixed scalings for l = 0.16 of
-// polar_ns.hip: a step less in some rounds was what the bookkeeping cost.)
+// below 7: as without it.  p <= 64, condition 3 to 14, has fixed scalings for a first l by the spread alone
+// (polar_ns.hip): a step less in some rounds was what the bookkeeping cost.)
 //
 // A narrow spectrum (atoms used equally often, over many signals) is the exception, for every p: alpha(0.16) would send
 // singular values that are all near one down to 0.375 first, where the rounding of the step weighs 1 / 0.375 as
@@ -41,6 +41,12 @@ template <int P>
 __device__ __forceinline__ bool narrow_spectrum(float sum2, float mu) {
     return sum2 < P * (1.f + kNarrow<P> * kNarrow<P>) * (mu * mu);
 }
+
+// p = 256: the first l by the spread of the squared singular values (sum2 / (p mu^2) - 1), 0.16 between the lines.  Below the lower
+// one 0.45 takes a step less (condition 1.5 to 2), and the error falls by a third; above the other one 0.064 takes up to two
+// less (sets of 2048 signals, 12 atoms a signal: 8.5 -> 7 on average; Algorithm 2 to K = 4, 16384 signals 5646 -> 5587 us), with
+// an error of 1.0 to 1.09.  With that line at 1.4, 8192 signals of 5 atoms took 7 steps instead of 6.
+constexpr float kHighSpread = 2.5f, kHighL = 0.064f, kLowSpread = 0.18f, kLowL = 0.45f;
 
 struct NsScale {
     float l = 0.16f;           // before the present step
@@ -77,6 +83,9 @@ struct NsScale {
         if (col2 > 1e-37f && col2 < 3e37f) {
             est = 1.04f * __builtin_amdgcn_sqrtf(col2);
             const float r = diag > 0.f ? __builtin_amdgcn_sqrtf(diag * __builtin_amdgcn_rcpf(est)) : 0.f;
+            const float even = 256 * (mu * mu);
+            if (sum2 > (1.f + kHighSpread) * even) l = kHighL;
+            else if (sum2 < (1.f + kLowSpread) * even) l = kLowL;
             l = fmaxf(fminf(l, r), 1e-3f);
             const float a = best(l);
             b2 = fminf(b2, a * a * __builtin_amdgcn_rcpf(est));

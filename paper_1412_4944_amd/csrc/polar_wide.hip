@@ -8,13 +8,18 @@
 //
 //   Newton-Schulz (polar_ns.hip has the iteration and its last step, ns_scale.h the scaling).  A
 //   workgroup owns a strip of 16 columns of X, in registers.  Per step it multiplies G = X^T X (its 16
-//   columns), then X E (its 16 columns), six bf16 products each; the A operands are ALL of X, by
+//   columns), then X E (its 16 columns), at fp32 accuracy; the A operands are ALL of X, by
 //   columns for the first product and by rows for the second, read straight from L2 in operand order,
 //   each exactly once: every workgroup leaves its strip in both orders when it has updated it, in fp32 (whoever reads it
 //   makes the parts: two thirds of their bytes), and that is the only exchange, hence one barrier per step (two in the
 //   first and the last).  A wavefront
 //   makes two 16 x 16 tiles of both products; its loads run four contraction steps ahead and through from
 //   the first product into the second.
+//
+//   The products: three bf16 parts of an operand, six partial products, in the first step (whose input has no scale yet) and for
+//   the G of a step that may be the last one; elsewhere two fp16 parts, scaled, and three.  What these leave out of G (2^-22 of an entry)
+//   is symmetric and goes with the next step; in X E it is made up for by a rounding less, E being scaled by alpha.  |Q - Q64|_F / sqrt(p)
+//   0.85 to 0.95 of what it was (block matrices of training rounds, 384 to 16384 signals); splits and matrix work of a step are halved.
 //
 //   Up to eight blocks, a team on each XCD: two workgroups to a strip, one for the upper and one for the lower half of its rows,
 //   which halves the operands that each of them reads.  They need each other's half of X, which comes with the barrier, and of E:
@@ -37,7 +42,9 @@
 // took the operands' descriptor and offsets for different ones in every lane (a loop around every load) and a flat load among
 // them waited for all of them; the rest by a barrier of flags that a wavefront reads at once, by loads that pass L1 by,
 // instead of a counter, polled by atomics (5000 cycles with pairs).  Eight steps of operands on their way instead of four: 91 us (registers spilled, and half of
-// the wavefronts get theirs late).  With the three parts in memory (768 KiB) 138 -> 131 us in the same profile,
+// the wavefronts get theirs late).  With two fp16 parts in most products
+// K = 4 80 -> 70, K = 16 120 -> 91 (a step 5.6 and 6.9 us), so that the cycles above are of three parts in all of them.
+// With the three parts in memory (768 KiB) 138 -> 131 us in the same profile,
 // K = 16; K = 4 no difference.  Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  Jacobi is called, not inlined,
 // where a block may need it after Newton-Schulz, whose operands take all registers (inlined: 100 of them spilled, K = 16 147 us
@@ -93,6 +100,7 @@ constexpr float kEScale = 8192.f;                              // of those: 1e-2
 constexpr size_t kJvAt = kJaAt + (size_t)P * P * 4;            // V
 // red[2][4][kCarried][32] | sigma[256] | 1/|v|[256] | pairs: sums of each half of the columns [2 halves][2][256]
 constexpr size_t kSmallAt = kJvAt + (size_t)P * P * 4;
+constexpr float kXScale = 16384.f;                             // of X after the first step, and of E for its product with X
 constexpr int kCarried = 5;                                    // floats of each workgroup that a barrier carries
 constexpr int kRedSize = 4 * kCarried * kPairs;
 constexpr int kSmallFloats = 2 * kRedSize + 2 * P + 4 * P;
@@ -108,7 +116,8 @@ constexpr unsigned long long kGoneMeet = 1ull << 62, kNoHelpers = 1ull << 61;
 
 // LDS
 constexpr int kEimgAt = kImage;
-constexpr int kStripAt = 2 * kImage;                           // [16][kLdStrip] floats
+constexpr int kXimg16At = 2 * kImage;                          // X in fp16 parts: two of three KiB a contraction step
+constexpr int kStripAt = 3 * kImage;                           // [16][kLdStrip] floats
 constexpr int kSmallLds = 4 * P * 16 * 4 > kStripAt + 16 * kLdStrip * 4 ? 4 * P * 16 * 4 : kStripAt + 16 * kLdStrip * 4;
 constexpr size_t kLds = kSmallLds + 6144;                      // 256 floats of reductions, 4 x 256 words, two flags, ..
 constexpr int kDiagAt = 1282;                                  // .. and two words beside the reductions
@@ -459,19 +468,30 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
     const int t0 = H == 1 ? 2 * wave : half * 8 + wave, tp = (1 - half) * 8 + wave;        // the first tile; one of the other half
     unsigned char* ximg = lds;
     unsigned char* eimg = lds + kEimgAt;
+    unsigned char* ximg16 = lds + kXimg16At;
     float* strip = reinterpret_cast<float*>(lds + kStripAt);
 
-    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};  // the six partial products, smallest first
-    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
     constexpr int kAhead = 4;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(mem, 0, (int)kTeamBytes, 0x00027000);
-    auto mfma = [](u32x4 a, u32x4 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                       0, 0, 0);
+    // Two ways for the products: three bf16 parts, six partial products, or two fp16 parts and three (`two`).
+    typedef std::true_type Two;
+    typedef std::false_type Three;
+    auto mfma = [](auto two, u32x4 a, u32x4 b, f32x4 c) {
+        if constexpr (decltype(two)::value)
+            return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     };
     auto at16 = [](const unsigned char* p) { return *reinterpret_cast<const u32x4*>(p); };
-    auto split = [](f32x4 lo, f32x4 hi, u32x4 (&out)[3]) {
+    auto split = [](auto two, f32x4 lo, f32x4 hi, u32x4 (&out)[3]) {
+        if constexpr (decltype(two)::value) {
+            const F16x2Pair a = split_f16x2(lo.x, lo.y), b = split_f16x2(lo.z, lo.w);
+            const F16x2Pair c = split_f16x2(hi.x, hi.y), d = split_f16x2(hi.z, hi.w);
+            out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+            out[1] = u32x4{a.lo, b.lo, c.lo, d.lo};
+            return;
+        }
         const Bf16x3Pair a = split_bf16x3(lo.x, lo.y), b = split_bf16x3(lo.z, lo.w);
         const Bf16x3Pair c = split_bf16x3(hi.x, hi.y), d = split_bf16x3(hi.z, hi.w);
         out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
@@ -479,21 +499,28 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         out[2] = u32x4{a.lo, b.lo, c.lo, d.lo};
     };
     // The parts of the tiles t0 .. (or of one tile) in an image of the strip: contraction step of 32 = two tiles, a half unit each.
-    auto put_tile = [&](unsigned char* img, int tile, f32x4 v) {
+    auto put_tile = [&](auto two, unsigned char* img, int tile, f32x4 v) {
+        if constexpr (decltype(two)::value) {
+            const F16x2Pair a = split_f16x2(v.x, v.y), b = split_f16x2(v.z, v.w);
+            u32x2* at = reinterpret_cast<u32x2*>(img + (tile >> 1) * 3 * 1024 + lane * 16 + (tile & 1) * 8);
+            at[0] = u32x2{a.hi, b.hi};
+            at[128] = u32x2{a.lo, b.lo};
+            return;
+        }
         const Bf16x3Pair a = split_bf16x3(v.x, v.y), b = split_bf16x3(v.z, v.w);
         u32x2* at = reinterpret_cast<u32x2*>(img + (tile >> 1) * 3 * 1024 + lane * 16 + (tile & 1) * 8);
         at[0] = u32x2{a.hi, b.hi};
         at[128] = u32x2{a.mid, b.mid};
         at[256] = u32x2{a.lo, b.lo};
     };
-    auto put_parts = [&](unsigned char* img, const f32x4 (&v)[NT]) {
+    auto put_parts = [&](auto two, unsigned char* img, const f32x4 (&v)[NT]) {
         if constexpr (H == 1) {
             u32x4 part[3];
-            split(v[0], v[NT - 1], part);
+            split(two, v[0], v[NT - 1], part);
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(img + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
+            for (int pl = 0; pl < (decltype(two)::value ? 2 : 3); ++pl) *reinterpret_cast<u32x4*>(img + (wave * 3 + pl) * 1024 + lane * 16) = part[pl];
         } else {
-            put_tile(img, t0, v[0]);
+            put_tile(two, img, t0, v[0]);
         }
     };
     // over the values that a barrier carried (H = 2: the two of a pair first)
@@ -543,10 +570,11 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
     // Leaves the strip for the others (buffer buf), in fp32, and its parts in ximg.  Contraction step s of 32 = tiles 2s and
     // 2s + 1, its two halves: a lane holds rows grp * 4 .. of both, which is what an accumulator leaves it, and of the rows'
     // image four columns grp * 4 .. of a row, by way of LDS (the wavefront's own part of `strip`).
-    auto publish = [&](int buf) {
+    auto publish = [&](int buf, bool scaled) {
         unsigned char* cols = mem + kColAt + ((size_t)buf * kTeam + sn) * kShared;
         unsigned char* rows = mem + kRowAt + (size_t)buf * kTeam * kShared;
-        put_parts(ximg, xr);
+        put_parts(Three{}, ximg, xr);
+        if (scaled) put_parts(Two{}, ximg16, xr);              // (which of them the next step takes is known after the barrier)
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
             *reinterpret_cast<f32x4*>(cols + (t0 + k) * 1024 + lane * 16) = xr[k];
@@ -578,20 +606,25 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         v = -wave_max(-v);
         if (lane == 0) red[kDiagAt] = v;
     };
-    // E = I - a2 G
-    auto make_e = [&](const f32x4 (&gm)[NT], float a2, f32x4 (&e)[NT]) {
+    // E = I - a2 G, times a scale
+    auto make_e = [&](const f32x4 (&gm)[NT], float a2, f32x4 (&e)[NT], float by = 1.f) {
+        a2 *= by;
 #pragma unroll
         for (int k = 0; k < NT; ++k)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) e[k][r] = (on_diagonal(k, r) ? 1.f : 0.f) - a2 * gm[k][r];
+            for (int r = 0; r < 4; ++r) e[k][r] = (on_diagonal(k, r) ? by : 0.f) - a2 * gm[k][r];
     };
 
     // A product: contraction steps S0 .. S0 + 7, their A operands requested kAhead steps before and split here, the B operands
     // from an image in LDS one step before; sums apart, so that matrix instructions are independent.  H = 2: ask() before the last
     // step of the own half, have() before the first of the other one.
-    auto product = [&](auto& a, auto& request, auto& turn, const unsigned char* img, auto first_step, f32x4 (&out)[NT], auto&& ask,
-                       auto&& have) {
+    auto product = [&](auto two, auto& a, auto& request, auto& turn, const unsigned char* img, auto first_step, f32x4 (&out)[NT],
+                       auto&& ask, auto&& have) {
         constexpr int S0 = decltype(first_step)::value, NS = 4;
+        constexpr bool kTwo = decltype(two)::value;
+        constexpr int NPT = kTwo ? 2 : 3, NP = kTwo ? 3 : 6;
+        constexpr int TA[6] = {kTwo ? 1 : 2, 0, kTwo ? 0 : 1, 1, 0, 0};        // the partial products, smallest first
+        constexpr int TB[6] = {0, kTwo ? 1 : 2, kTwo ? 0 : 1, 0, 1, 0};
         f32x4 sum[NT][NS];
 #pragma unroll
         for (int k = 0; k < NT; ++k)
@@ -600,7 +633,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         u32x4 b[2][3];
         auto read = [&](int s) {
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl) b[s & 1][pl] = at16(img + (turn(s) * 3 + pl) * 1024 + lane * 16);
+            for (int pl = 0; pl < NPT; ++pl) b[s & 1][pl] = at16(img + (turn(s) * 3 + pl) * 1024 + lane * 16);
         };
         read(S0);
 #pragma unroll
@@ -614,11 +647,14 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
             u32x4 part[NT][3];
 #pragma unroll
             for (int k = 0; k < NT; ++k)
-                split(__builtin_bit_cast(f32x4, a[s % kAhead][k][0]), __builtin_bit_cast(f32x4, a[s % kAhead][k][1]), part[k]);
+                split(two, __builtin_bit_cast(f32x4, a[s % kAhead][k][0]), __builtin_bit_cast(f32x4, a[s % kAhead][k][1]), part[k]);
 #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int q = 0; q < NP; ++q)
 #pragma unroll
-                for (int k = 0; k < NT; ++k) sum[k][q % NS] = mfma(part[k][TA[q]], b[s & 1][TB[q]], sum[k][q % NS]);
+                for (int k = 0; k < NT; ++k) {
+                    f32x4& to = sum[k][kTwo && q == 2 ? 2 + (s & 1) : q % NS];
+                    to = mfma(two, part[k][TA[q]], b[s & 1][TB[q]], to);
+                }
             if (s + kAhead < 16) request(s + kAhead);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -626,7 +662,7 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         for (int k = 0; k < NT; ++k) out[k] = (sum[k][0] + sum[k][1]) + (sum[k][2] + sum[k][3]);
     };
 
-    publish(0);
+    publish(0, false);
     if constexpr (H == 2) {
         const int how = t.meet_pairs(first, g.helper_polls);
         if (how <= 0) return how < 0 ? Outcome::alone : Outcome::dead;
@@ -684,11 +720,22 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
             scale.seen(-all_max(-carried1));
         }
         f32x4 gm[NT];
-        product(a, request, turn, ximg, std::integral_constant<int, 0>{}, gm, []() {},
-                [&]() {
-                    put_tile(ximg, tp, __builtin_bit_cast(f32x4, other));
-                    __syncthreads();
-                });
+        auto gram = [&](auto two, unsigned char* img) {
+            product(two, a, request, turn, img, std::integral_constant<int, 0>{}, gm, []() {},
+                    [&]() {
+                        put_tile(two, img, tp, __builtin_bit_cast(f32x4, other));
+                        __syncthreads();
+                    });
+        };
+        // Three parts where the input has no scale yet, and where this may be the last step (below): then the rounding of G is
+        // that of the result.  Elsewhere what two parts leave out is a symmetric error of G, which the next step takes out.
+        const bool exact = __builtin_amdgcn_readfirstlane((int)(it == 0 || prev < 4.f || it >= g.max_iters)) != 0;
+        if (exact) gram(Three{}, ximg);
+        else gram(Two{}, ximg16);
+        if (it > 0) {                          // uniform
+#pragma unroll
+            for (int k = 0; k < NT; ++k) gm[k] *= 1.f / (kXScale * kXScale);
+        }
 
         float alpha = 1.f, fr = 0.f;
         bool last = false, known = false;
@@ -842,11 +889,13 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
             }
             __syncthreads();                   // eimg is rewritten
 #pragma unroll
-            for (int k = 0; k < NT; ++k) e[k] = kLastLinear * e[k] + (kLastSquare / (kEScale * kEScale)) * e2[k];
+            for (int k = 0; k < NT; ++k) e[k] = kXScale * (kLastLinear * e[k] + (kLastSquare / (kEScale * kEScale)) * e2[k]);
         } else {
-            make_e(gm, alpha * alpha, e);
+            // (times alpha, at least one: the products are then added to X without another rounding)
+            make_e(gm, alpha * alpha, e, it == 0 ? 1.f : kXScale * alpha);
         }
-        put_parts(eimg, e);
+        if (it == 0) put_parts(Three{}, eimg, e);
+        else put_parts(Two{}, eimg, e);
         const int eh = (int)kEHalfAt + sn * kShared;
         if constexpr (H == 1) {
             __syncthreads();
@@ -856,30 +905,35 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         }
         f32x4 acc[NT];
         bool here = true;
-        product(a, request, turn, eimg, std::integral_constant<int, 8>{}, acc,
-                [&]() {
-                    here = taken();
-                    other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, eh + tp * 1024, kPastL1);
-                },
-                [&]() {
-                    put_tile(eimg, tp, __builtin_bit_cast(f32x4, other));
-                    __syncthreads();
-                });
+        auto turned = [&](auto two) {
+            product(two, a, request, turn, eimg, std::integral_constant<int, 8>{}, acc,
+                    [&]() {
+                        here = taken();
+                        other = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, eh + tp * 1024, kPastL1);
+                    },
+                    [&]() {
+                        put_tile(two, eimg, tp, __builtin_bit_cast(f32x4, other));
+                        __syncthreads();
+                    });
+        };
+        if (it == 0) turned(Three{});
+        else turned(Two{});
         if (H == 2 && !here) return Outcome::dead;
 #pragma unroll
-        for (int k = 0; k < NT; ++k) xr[k] = alpha * xr[k] + (0.5f * alpha) * acc[k];
+        for (int k = 0; k < NT; ++k)
+            xr[k] = it == 0 ? (kXScale * alpha) * xr[k] + (0.5f * kXScale * alpha) * acc[k] : alpha * xr[k] + (0.5f / kXScale) * acc[k];
         if (last) {
             steps = it + 1;
             break;
         }
-        publish((it + 1) & 1);
+        publish((it + 1) & 1, true);
         if (!t.sync(it > 0 ? own_norm() : 0.f, red[kDiagAt])) return Outcome::dead;
         look = !known && it > 0;
         ++it;
     }
 #pragma unroll
     for (int k = 0; k < NT; ++k)
-        *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (t0 + k) * 16 + grp * 4) = xr[k];
+        *reinterpret_cast<f32x4*>(strip + c16 * kLdStrip + (t0 + k) * 16 + grp * 4) = xr[k] * (1.f / kXScale);
     __syncthreads();
     if constexpr (H == 2) {                    // D[j] rows of the strip, as emit_strip; the norms of whole atoms by the first of the pair
         {
