@@ -226,8 +226,8 @@ enum {
                                   Q_j up to rounding, in tens of milliseconds. */
 };
 enum {
-    SBO_SVD_AUTO   = 0,  /* default: Newton-Schulz polar factor on the matrix cores (six bf16 partial products of exact
-                            three-part splits, rounding at the fp32 level, whatever SBO_OPT_CODING_ARITH is), the
+    SBO_SVD_AUTO   = 0,  /* default: Newton-Schulz polar factor on the matrix cores (three-part bf16 or two-part fp16
+                            splits, rounding at the fp32 level, whatever SBO_OPT_CODING_ARITH is), the
                             one-sided Jacobi SVD for the orthobases it flags (rank-deficient P_j) */
     SBO_SVD_JACOBI = 1   /* the one-sided Jacobi SVD for every orthobase (one workgroup each, p = 256: eight) */
 };
@@ -243,8 +243,11 @@ enum {
                               hi + lo in fp16 (22 significand bits), three partial products with fp32
                               accumulation: per-term error 3 * 2^-22 |a||b|, below the p * 2^-24 sum |a||b|
                               an fp32 dot product of p terms guarantees; half the matrix work of
-                              SBO_ARITH_BF16X3.  Supports and coefficients still come from the six bf16
-                              products.  (For s0 <= p/2 the choice is screened, under every arithmetic: one
+                              SBO_ARITH_BF16X3.  Supports and coefficients come from the six bf16
+                              products; at p = 256, in the calls that choose orthobases and for those that
+                              the library has made itself (sbo_learn, sbo_new_base with have_q0 = 0), from the
+                              three fp16 ones (measured against 64 bits: half of the error of the
+                              six).  (For s0 <= p/2 the choice is screened, under every arithmetic: one
                               fp16 product and its guaranteed error bound rule out the blocks that cannot
                               win, only the others are computed as described here; the chosen blocks are
                               the same.  p = 256: under this arithmetic only, and for K <= 1013; with more

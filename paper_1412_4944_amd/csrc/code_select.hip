@@ -384,24 +384,32 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
 // through LDS) a tile took 38 us however few there were, and nothing hid its selection.  Before and now: 2048 signals, K = 1
 // 43.2 -> 17 us, 5041, K = 16 42.4 -> 19, 16384 46 -> 33, 32768 86 -> 55, 131072 212 -> 159 (two workgroups per CU, six steps
 // ahead 172).
+// F16: two fp16 parts and three partial products (device_utils.h), every signal scaled by a power of two, where the dictionary has them
+// (select_arith in sbo_api.hip): half of the chain of products that the wavefronts of a tile go through, two thirds of the rows'
+// bytes (a tile reads all of its block's: 384 KiB, now 256).  131072 signals, K = 16 143 -> 116 us, 5041, K = 16 17.2 -> 14.4.  The products with a second part are
+// summed apart: the coefficients are off those in 64 bits by 0.9e-7 of theirs on average, by six bf16 products 2.0e-7 (rms; s0 = 2 to 12).
 // Workgroup ids are dealt out so that the workgroups of one XCD (ids equal modulo 8) take a contiguous run of tiles, that is,
 // few blocks, whose rows then stay in that XCD's L2 (131072 signals, K = 16: 190 -> 172 us).
 constexpr int kTileWaves = 8;
 constexpr int kTileLd = 260;                  // floats per signal of the coefficients (16-byte units cover all banks)
-template <int S, bool LISTS>
+// Bytes of the parts of y, of the coefficients, and of the table of `lists`, in one place (the table of few_entries takes most).
+template <bool LISTS, bool F16>
+constexpr size_t kTileRoom = LISTS || !F16 ? 256 / 16 * 3 * 64 * 16 : 32 * kTileLd * 4;
+template <int S, bool LISTS, bool F16>
 __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(const float* __restrict__ Y, const u32x4* __restrict__ Dsb,
                                                                  int K, int s0, const int32_t* __restrict__ offsets,
                                                                  const int32_t* __restrict__ perm,
                                                                  int32_t* __restrict__ supp, float* __restrict__ coef,
                                                                  float* __restrict__ err, int by_pos, ChunkLists lists) {
     constexpr int P = 256, KS16 = P / 16, MT = P / 32, AHEAD = 3, NW = kTileWaves, L = 16;
-    constexpr int STAGE_U = KS16 * 3 * 64;     // 16-byte units of 32 rows
+    constexpr int NPT = F16 ? 2 : 3;           // parts
+    constexpr int STAGE_U = KS16 * NPT * 64;   // 16-byte units of 32 rows
     extern __shared__ __attribute__((aligned(16))) int lds[];  // parts of y, then coefficients | stage | ids[32] (LISTS)
-    u32x4* ys = reinterpret_cast<u32x4*>(lds);                 // [KS16][3][64]
+    u32x4* ys = reinterpret_cast<u32x4*>(lds);                 // [KS16][NPT][64]
     float* cs = reinterpret_cast<float*>(ys);                  // [32][kTileLd]
-    int* stage = reinterpret_cast<int*>(ys + STAGE_U);         // [32][2][16]
+    int* stage = lds + kTileRoom<LISTS, F16> / 4;              // [32][2][16]; before that, largest magnitudes [8][32] (F16)
     int* ids = stage + 32 * 32;
-    static_assert(32 * kTileLd * 4 <= STAGE_U * 16, "the coefficients fit");
+    static_assert(32 * kTileLd * 4 <= kTileRoom<LISTS, F16> && STAGE_U * 16 <= kTileRoom<LISTS, F16>, "parts and coefficients fit");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -420,11 +428,12 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
 
     // A operand: rows of this wavefront's 32 atoms, AHEAD contraction steps on their way
     const u32x4* Qj = Dsb + ((int64_t)j * MT + wave) * STAGE_U + lane;
-    u32x4 a[AHEAD][3];
-    auto fetch = [&](u32x4 (&v)[3], int ks) {
+    u32x4 a[AHEAD][NPT];
+    auto fetch = [&](u32x4 (&v)[NPT], int ks) {
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) v[pl] = Qj[(ks * 3 + pl) * 64];
+        for (int pl = 0; pl < NPT; ++pl) v[pl] = Qj[(ks * NPT + pl) * 64];
     };
+    int shift = 0;                             // F16: signal n is scaled by 2^shift, its largest magnitude then in [2^13, 2^14)
     {
         const int64_t i = n < cnt ? (LISTS ? ids[n] : perm[pos0 + n]) : -1;
         f32x4 v[KS16 / NW][2];
@@ -437,6 +446,38 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
             }
 #pragma unroll
         for (int t = 0; t < AHEAD; ++t) fetch(a[t], t);
+        if constexpr (F16) {
+            unsigned mx = 0;
+#pragma unroll
+            for (int q = 0; q < KS16 / NW; ++q)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float m = fabsf(v[q][e][c]);
+                        mx = max(mx, __builtin_bit_cast(unsigned, m));
+                    }
+            mx = max(mx, pair_other(mx, h));
+            if (h == 0) stage[wave * 32 + n] = (int)mx;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < NW; ++w) mx = max(mx, (unsigned)stage[w * 32 + n]);
+            const int e = (int)(mx >> 23);
+            shift = e == 0xff ? 0 : 140 - max(e, 1);
+#pragma unroll
+            for (int q = 0; q < KS16 / NW; ++q) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[q][e][c] = __builtin_amdgcn_ldexpf(v[q][e][c], shift);
+                const F16x2Pair x = split_f16x2(v[q][0].x, v[q][0].y), y = split_f16x2(v[q][0].z, v[q][0].w);
+                const F16x2Pair z = split_f16x2(v[q][1].x, v[q][1].y), w = split_f16x2(v[q][1].z, v[q][1].w);
+                u32x4* out = ys + ((NW * q + wave) * 2) * 64 + lane;
+                out[0] = u32x4{x.hi, y.hi, z.hi, w.hi};
+                out[64] = u32x4{x.lo, y.lo, z.lo, w.lo};
+            }
+        }
+        if constexpr (!F16)
 #pragma unroll
         for (int q = 0; q < KS16 / NW; ++q) {
             const Bf16x3Pair x = split_bf16x3(v[q][0].x, v[q][0].y), y = split_bf16x3(v[q][0].z, v[q][0].w);
@@ -448,22 +489,40 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
         }
     }
     __syncthreads();
-    // the six partial products, smallest first: (A part, B part)
-    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
-    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 acc;
+    f32x16 acc = zero;
+    if constexpr (F16) {
+        f32x16 rest = zero;                    // the products with a second part: apart, so that less is rounded at the size of the sum
+        auto mfma = [](u32x4 x, u32x4 y, f32x16 z) {
+            return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), z, 0, 0, 0);
+        };
 #pragma unroll
-    for (int ks = 0; ks < KS16; ++ks) {
-        u32x4 b[3];
+        for (int ks = 0; ks < KS16; ++ks) {
+            const u32x4 hi = ys[ks * 2 * 64 + lane], lo = ys[(ks * 2 + 1) * 64 + lane];
+            rest = mfma(a[ks % AHEAD][NPT - 1], hi, rest);
+            acc = mfma(a[ks % AHEAD][0], hi, acc);
+            rest = mfma(a[ks % AHEAD][0], lo, rest);
+            if (ks + AHEAD < KS16) fetch(a[ks % AHEAD], ks + AHEAD);
+        }
+        acc += rest;
+        static_assert(kF16DictScale == 8192.f, "2^13");
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) b[pl] = ys[(ks * 3 + pl) * 64 + lane];
+        for (int r = 0; r < 16; ++r) acc[r] = __builtin_amdgcn_ldexpf(acc[r], -13 - shift);
+    } else {
+        // the six partial products, smallest first: (A part, B part)
+        constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
+        constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-        for (int t = 0; t < 6; ++t)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[ks % AHEAD][TA[t]]),
-                                                          __builtin_bit_cast(bf16x8, b[TB[t]]),
-                                                          (ks == 0 && t == 0) ? zero : acc, 0, 0, 0);
-        if (ks + AHEAD < KS16) fetch(a[ks % AHEAD], ks + AHEAD);
+        for (int ks = 0; ks < KS16; ++ks) {
+            u32x4 b[3];
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) b[pl] = ys[(ks * 3 + pl) * 64 + lane];
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[ks % AHEAD][TA[t] % NPT]),
+                                                              __builtin_bit_cast(bf16x8, b[TB[t]]), acc, 0, 0, 0);
+            if (ks + AHEAD < KS16) fetch(a[ks % AHEAD], ks + AHEAD);
+        }
     }
     __syncthreads();                           // the parts are dead
 #pragma unroll
@@ -546,25 +605,28 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
     }
 }
 
+template <int S, bool F16>
+hipError_t launch_wide_parts(const float* Y, int64_t m, int K, int s0, const Workspace& ws, int32_t* supp, float* coef, float* err,
+                             bool by_pos, const ChunkLists* lists, hipStream_t st) {
+    // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every tile
+    const int64_t tiles = (((m + 31) / 32 + K) + 7) & ~(int64_t)7;
+    const size_t room = lists != nullptr ? kTileRoom<true, F16> : kTileRoom<false, F16>, lds = room + 32 * 33 * sizeof(int);
+    const auto kernel = lists != nullptr ? &select_wide_split_kernel<S, true, F16> : &select_wide_split_kernel<S, false, F16>;
+    if (lists != nullptr && (by_pos || ChunkLists::table_ints(kTileWaves, K, lists->n_chunks) * sizeof(int) > room))
+        return hipErrorInvalidValue;
+    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), 64 * 1024); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
+                       reinterpret_cast<const u32x4*>(F16 ? ws.dsh : ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos,
+                       lists != nullptr ? *lists : ChunkLists{});
+    return hipGetLastError();
+}
 template <int P, int S>
 hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int s0,
-                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
+                          const Workspace& ws, int32_t* supp, float* coef, float* err, int ops,
                           bool by_pos, const ChunkLists* lists, hipStream_t st) {
-    (void)D;                                   // the kernels read ws.dsb / ws.dsw, the same Q in operand order
-    if (split) {
-        // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every tile
-        const int64_t tiles = (((m + 31) / 32 + K) + 7) & ~(int64_t)7;
-        constexpr size_t rows = (size_t)(P / 16) * 3 * 64 * 16;
-        const size_t lds = rows + 32 * 33 * sizeof(int);
-        const auto kernel = lists != nullptr ? &select_wide_split_kernel<S, true> : &select_wide_split_kernel<S, false>;
-        if (lists != nullptr && (by_pos || ChunkLists::table_ints(kTileWaves, K, lists->n_chunks) * sizeof(int) > rows))
-            return hipErrorInvalidValue;
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), 64 * 1024); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
-                           reinterpret_cast<const u32x4*>(ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos,
-                           lists != nullptr ? *lists : ChunkLists{});
-        return hipGetLastError();
-    }
+    (void)D;                                   // the kernels read ws.dsh / ws.dsb / ws.dsw, the same Q in operand order
+    if (ops == kOpsF16) return launch_wide_parts<S, true>(Y, m, K, s0, ws, supp, coef, err, by_pos, lists, st);
+    if (ops == kOpsBf16) return launch_wide_parts<S, false>(Y, m, K, s0, ws, supp, coef, err, by_pos, lists, st);
     if (lists != nullptr) return hipErrorInvalidValue;
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
@@ -579,13 +641,13 @@ hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int 
 
 template <int P>
 hipError_t launch_wide_p(int s0, const float* Y, int64_t m, const float* D, int K,
-                         const Workspace& ws, int32_t* supp, float* coef, float* err, bool split,
+                         const Workspace& ws, int32_t* supp, float* coef, float* err, int ops,
                          bool by_pos, const ChunkLists* lists, hipStream_t st) {
-    if (s0 <= 1) return launch_wide_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
-    if (s0 <= 2) return launch_wide_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
-    if (s0 <= 4) return launch_wide_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
-    if (s0 <= 8) return launch_wide_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
-    return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, split, by_pos, lists, st);
+    if (s0 <= 1) return launch_wide_ps<P, 1>(Y, m, D, K, s0, ws, supp, coef, err, ops, by_pos, lists, st);
+    if (s0 <= 2) return launch_wide_ps<P, 2>(Y, m, D, K, s0, ws, supp, coef, err, ops, by_pos, lists, st);
+    if (s0 <= 4) return launch_wide_ps<P, 4>(Y, m, D, K, s0, ws, supp, coef, err, ops, by_pos, lists, st);
+    if (s0 <= 8) return launch_wide_ps<P, 8>(Y, m, D, K, s0, ws, supp, coef, err, ops, by_pos, lists, st);
+    return launch_wide_ps<P, 16>(Y, m, D, K, s0, ws, supp, coef, err, ops, by_pos, lists, st);
 }
 
 // From here on select_split_kernel (p = 32, 64), four wavefronts and up to 4 tiles for each: the fewest with which all
@@ -651,22 +713,24 @@ hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, co
 
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, int32_t* blk, bool choose, bool by_pos, bool lists) {
+                         int ops, hipStream_t st, int32_t* blk, bool choose, bool by_pos, bool lists) {
     const bool fits = lists ? blk != nullptr && !choose && lists_in_select(p, K, m) : blk != nullptr ? group_in_select(p, K, m) : !choose;
     if (!fits || (by_pos && p != 256)) return hipErrorInvalidValue;
     const GroupGeom g = group_geom(m);
     if (lists && g.chunk != kListChunk) return hipErrorInvalidValue;
     const ChunkLists from = {blk, (int)m, g.n_chunks, ws.chunk_count, nullptr, nullptr}, *l = lists ? &from : nullptr;
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
-        hipError_t e = split ? launch_dict_parts(p, K, D, ws.dsb, nullptr, nullptr, nullptr, SignalSample{}, CallStart{}, st)
-                             : launch_dict_swizzle(p, K, D, ws.dsw, CallStart{}, st);
+        hipError_t e = ops == kOpsF32 ? launch_dict_swizzle(p, K, D, ws.dsw, CallStart{}, st)
+                                      : launch_dict_parts(p, K, D, ops == kOpsBf16 ? ws.dsb : nullptr, ops == kOpsF16 ? ws.dsh : nullptr,
+                                                          ws.dnorm, nullptr, SignalSample{}, CallStart{}, st);
         if (e != hipSuccess) return e;
     }
+    const bool split = ops != kOpsF32;
     switch (p) {
         case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, l, st);
         case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, l, st);
         case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, blk, choose, split, l, st);
-        case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, split, by_pos, l, st);
+        case 256: return launch_wide_p<256>(s0, Y, m, D, K, ws, supp, coef, err, ops, by_pos, l, st);
         default: return hipErrorInvalidValue;
     }
 }

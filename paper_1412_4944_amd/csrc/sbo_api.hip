@@ -161,8 +161,15 @@ static int energy_ops(const sbo_ctx* c) {
 }
 
 // ... that its select kernel reads (p <= 64: D itself), and both.
-static int select_ops(const sbo_ctx* c) { return c->p <= 64 ? 0 : use_split(c) ? kOpsBf16 : kOpsF32; }
-static int code_ops(const sbo_ctx* c) { return energy_ops(c) | select_ops(c); }
+// Two fp16 parts after a choice that has them as well, and where the library has made the orthobases itself (own); a caller's
+// dictionary without a choice may have entries beyond their range.
+static int select_arith(const sbo_ctx* c, bool own) {
+    const int a = c->coding_arith;
+    return a == SBO_ARITH_F32 ? kOpsF32 : a == SBO_ARITH_F16X2 && own ? kOpsF16 : kOpsBf16;
+}
+static int code_arith(const sbo_ctx* c) { return select_arith(c, choice_arith(c) == SBO_ARITH_F16X2); }
+static int select_ops(const sbo_ctx* c, bool own) { return c->p <= 64 ? 0 : select_arith(c, own); }
+static int code_ops(const sbo_ctx* c) { return energy_ops(c) | (c->p <= 64 ? 0 : code_arith(c)); }
 
 // D in the operand order(s) the coding kernels of this context read (tiny; outside the stages).
 static int run_swizzle(sbo_ctx* c, const float* Y, int64_t m, const float* D) {
@@ -205,7 +212,7 @@ static int run_code(sbo_ctx* c, const float* Y, int64_t m, const float* D, int32
     if (rc) return rc;
     {
         StageTimer t(c, SBO_STAGE_SELECT);         // p = 256 reads the operand order run_swizzle wrote
-        SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, true, use_split(c), c->stream,
+        SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, true, code_arith(c), c->stream,
                               in_select || lists ? blk : nullptr, direct, false, lists));
     }
     return SBO_OK;
@@ -444,8 +451,9 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
     return SBO_OK;
 }
 
+// own: D holds orthobases that the library has made.
 static int run_train_rounds(sbo_ctx* c, const float* Y, int64_t m, const int32_t* blk, float* D, int R,
-                            int32_t* supp, float* coef, float* err) {
+                            int32_t* supp, float* coef, float* err, bool own = false) {
     int rc = run_group(c, blk, m);             // the assignment, hence the grouping, is fixed
     if (rc) return rc;
     for (int r = 0; r < R; ++r) {
@@ -462,9 +470,9 @@ static int run_train_rounds(sbo_ctx* c, const float* Y, int64_t m, const int32_t
             {
                 StageTimer t(c, SBO_STAGE_SELECT);
                 SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, r > 0,
-                                      use_split(c), c->stream));
+                                      select_arith(c, own), c->stream));
             }
-            rc = run_update_grouped(c, Y, m, supp, coef, D, select_ops(c));
+            rc = run_update_grouped(c, Y, m, supp, coef, D, select_ops(c, own));
             if (rc) return rc;
         }
     }
@@ -524,6 +532,7 @@ int sbo_init_base(sbo_ctx* c, const float* Y, int64_t m, const int32_t* ids, int
 // ws.perm etc. already hold the set (launch_single_block).
 static int run_new_base(sbo_ctx* c, const float* Y, int64_t n, int R, int have_q0, float* Q,
                         int32_t* supp, float* coef, float* err, double* sqerr_per_round, bool have_gram = false) {
+    const bool own = !have_q0;
     if (!have_q0) {
         int rc = run_init_base(c, Y, n, Q, nullptr, have_gram);
         if (rc) return rc;
@@ -532,12 +541,12 @@ static int run_new_base(sbo_ctx* c, const float* Y, int64_t n, int R, int have_q
         if (c->p <= 64) {
             SBO_HIP(launch_select_accum(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, c->stream));
         } else {
-            SBO_HIP(launch_select(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, r > 0, use_split(c), c->stream));
+            SBO_HIP(launch_select(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, r > 0, select_arith(c, own), c->stream));
         }
         if (sqerr_per_round)
             SBO_HIP(launch_sqerr(err, c->ws.perm, n, c->ws, sqerr_per_round + r, c->stream));
         int rc = c->p <= 64 ? run_polar_pieces(c, n, Q, 0, nullptr, nullptr, 1)
-                            : run_update_grouped(c, Y, n, supp, coef, Q, select_ops(c), nullptr, nullptr, 1);
+                            : run_update_grouped(c, Y, n, supp, coef, Q, select_ops(c, own), nullptr, nullptr, 1);
         if (rc) return rc;
     }
     return SBO_OK;
@@ -618,9 +627,9 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
                 SBO_HIP(launch_select_accum(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, c->stream));
                 rc = run_polar_pieces(c, n_init, D, 0, nullptr, nullptr, K0);
             } else {
-                SBO_HIP(launch_select(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, r > 0, use_split(c), c->stream,
+                SBO_HIP(launch_select(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, r > 0, select_arith(c, true), c->stream,
                                       nullptr, false, true));
-                rc = run_update_grouped(c, Y, n_init, supp, coef, D, select_ops(c), nullptr, nullptr, K0, true);
+                rc = run_update_grouped(c, Y, n_init, supp, coef, D, select_ops(c, true), nullptr, nullptr, K0, true);
             }
             if (rc) return fail(rc);
         }
@@ -657,7 +666,7 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
         c->K = K;
         rc = run_code(c, Y, m, D, blk, supp, coef, err);
         if (rc) return fail(rc);
-        rc = run_train_rounds(c, Y, m, blk, D, R, supp, coef, err);
+        rc = run_train_rounds(c, Y, m, blk, D, R, supp, coef, err, true);
         if (rc) return fail(rc);
         rc = next_error();
         if (rc) return fail(rc);

@@ -326,9 +326,10 @@ constexpr int64_t kGroupStaticMaxM = (int64_t)1 << 20;
 hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* counts, int32_t* offsets,
                                int32_t* perm, hipStream_t st);
 
-// p = 256 reads Q in operand order: ws.dsb (split: the bf16 matrix cores) or ws.dsw (fp32 matrix
-// instruction).  ops_valid: that buffer already holds this D (launch_dict_swizzle[_split]);
-// otherwise it is rewritten first.  p <= 64 reads D itself and ignores both flags.
+// p = 256 reads Q in operand order, `ops`: ws.dsh (kOpsF16), ws.dsb (kOpsBf16) or ws.dsw (kOpsF32: the fp32 matrix
+// instruction).  ops_valid: that buffer already holds this D (launch_dict_parts, launch_dict_swizzle, the SVD update);
+// otherwise it is rewritten first.  kOpsF16: for entries below 8 (device_utils.h).  p <= 64 reads D itself; of `ops` it only takes
+// whether it is kOpsF32.
 // blk: nullptr, or the choices of signals that have not been grouped (where group_in_select says so; the histograms in
 // ws.chunk_count are set to zero, as launch_group would).  The line: every workgroup reads the whole set, so it has to be
 // small, and has to fit 64 KiB of LDS beside the tiles.
@@ -339,7 +340,7 @@ hipError_t launch_group_static(int K, const int32_t* blk, int64_t m, int32_t* co
 // leaves.
 hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                          const Workspace& ws, int32_t* supp, float* coef, float* err, bool ops_valid,
-                         bool split, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false,
+                         int ops, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false,
                          bool lists = false);
 
 // M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.  blk (M == nullptr, where

@@ -925,6 +925,27 @@ def test_polar_of_narrow_spectra_is_accurate(p, kind):
     assert err.max() <= 1e-6
 
 
+@pytest.mark.parametrize("m", [33, 2048, 2100])         # an unfinished tile; grouped; listed from the histograms
+def test_select_p256_two_parts_over_magnitudes(m):
+    """Signals of 1e-36 to 1e30, zeros among them: the two fp16 parts are those of a signal scaled by a power of two.
+    Bound per coefficient: 3 * 2^-22 |y||q| for the parts, and sums of 48 products, 2^-24 each, of at most |y||q|."""
+    p, s0 = 256, 12
+    rng = np.random.default_rng(53 + m)
+    D = synth.random_onb(rng, p)[None].astype(np.float32)
+    scale = rng.choice([1e-36, 1e-30, 1e-18, 1e-3, 1.0, 1e18, 1e30, 0.0], m)
+    x = np.zeros((m, p))
+    np.put_along_axis(x, np.argsort(rng.random((m, p)), 1)[:, :s0], rng.uniform(0.5, 2, (m, s0)), 1)
+    Y = ((x @ D[0] + 0.01 * rng.standard_normal((m, p))) * scale[:, None]).astype(np.float32)
+    with Sbo(p, 1, s0, m) as g:
+        _blk, supp, coef, _err = g.code(Y, D)
+    c64 = Y.astype(np.float64) @ D[0].astype(np.float64).T
+    norm = np.linalg.norm(Y.astype(np.float64), axis=1, keepdims=True)
+    assert (np.abs(coef - np.take_along_axis(c64, supp, 1)) <= (3 * 2.0 ** -22 + 48 * 2.0 ** -24) * norm + 2.0 ** -149).all()
+    some = scale > 0
+    assert np.array_equal(supp[some], np.sort(np.argsort(-np.abs(c64[some]), 1)[:, :s0], 1))
+    assert (coef[~some] == 0).all()
+
+
 @pytest.mark.parametrize("p", [16, 32, 64])
 @pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
 def test_polar_on_both_sides_of_the_lines_of_the_spread(p, scale):
