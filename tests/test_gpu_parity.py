@@ -946,6 +946,52 @@ def test_select_p256_two_parts_over_magnitudes(m):
     assert (coef[~some] == 0).all()
 
 
+@pytest.mark.parametrize("m,s0", [(1500, 8), (6000, 5), (140000, 2)])      # a tile per wavefront; a few; many, grouped first
+@pytest.mark.parametrize("order", ["rising", "falling", "mixed"])
+def test_select_accum_two_parts_over_magnitudes(m, s0, order):
+    """Signals of 1e-9 to 1, zeros among them, in one block: the sums of a piece are kept at a power of two that leaves its
+    largest coefficients in fp16's range, lowered whenever a larger one comes (rising: in most tiles).  Coefficients:
+    4 * 2^-22 |y||q| for the parts, and sums of 24 products, 2^-24 each, of at most |y||q|.  The update from the call's own codes."""
+    p, K = 64, 2
+    rng = np.random.default_rng(59 + m)
+    D = np.stack([synth.random_onb(rng, p) for _ in range(K)]).astype(np.float32)
+    scale = np.sort(np.r_[10.0 ** rng.uniform(-9, 0, m // 2), np.ones(m - m // 2 - 5), np.zeros(5)])
+    scale = {"rising": scale, "falling": scale[::-1], "mixed": rng.permutation(scale)}[order]
+    of, x = rng.integers(0, K, m), np.zeros((m, p))
+    np.put_along_axis(x, np.argsort(rng.random((m, p)), 1)[:, :s0], rng.uniform(0.5, 2, (m, s0)), 1)
+    Y = np.where(of[:, None] == 0, x @ D[0], x @ D[1]) + 0.01 * rng.standard_normal((m, p))
+    Y = (Y * scale[:, None]).astype(np.float32)
+    with Sbo(p, K, s0, m) as g:
+        Dg, blk, supp, coef, err, _sq = g.iterate(Y, D, 1)
+    Y64 = Y.astype(np.float64)
+    c64 = np.where(blk[:, None] == 0, Y64 @ D[0].astype(np.float64).T, Y64 @ D[1].astype(np.float64).T)
+    norm = np.linalg.norm(Y64, axis=1)
+    kept = np.take_along_axis(c64, supp, 1)
+    assert (np.abs(coef - kept) <= (4 * 2.0 ** -22 + 24 * 2.0 ** -24) * norm[:, None]).all()
+    assert (np.abs(err - ((c64 ** 2).sum(1) - (kept ** 2).sum(1))) <= 1e-5 * norm ** 2).all()
+    Dn, M = orc.o_update(Y, blk, supp, coef, D)
+    print(f"  m={m} {order}: worst dQ {compare_Q(Dg, Dn, M, np.bincount(blk, minlength=K) > 0):.2e}", flush=True)
+
+
+@pytest.mark.parametrize("largest", [7.9, 8.1, 3e4, 1e20])
+def test_train_rounds_with_large_dictionary_entries(largest):
+    """sbo_train_rounds takes any dictionary: entries of 8 and more leave fp16's range with the usual scale."""
+    p, K, m, s0 = 64, 2, 3000, 6
+    rng = np.random.default_rng(67)
+    D = np.stack([synth.random_onb(rng, p) for _ in range(K)])
+    D[1] *= largest / np.abs(D[1]).max()
+    D = D.astype(np.float32)
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    blk = rng.integers(0, K, m).astype(np.int32)
+    with Sbo(p, K, s0, m) as g:
+        Q, supp, coef, _err = g.train_rounds(Y, blk, D, 1)
+    c64 = np.where(blk[:, None] == 0, Y.astype(np.float64) @ D[0].astype(np.float64).T, Y.astype(np.float64) @ D[1].astype(np.float64).T)
+    size = np.linalg.norm(Y, axis=1) * np.where(blk == 0, 1.0, np.linalg.norm(D[1].astype(np.float64), axis=1).max())
+    assert (np.abs(coef - np.take_along_axis(c64, supp, 1)) <= (4 * 2.0 ** -22 + 24 * 2.0 ** -24) * size[:, None]).all()
+    Dn, M = orc.o_update(Y, blk, supp, coef, D)
+    compare_Q(Q, Dn, M, np.ones(K, bool))
+
+
 @pytest.mark.parametrize("p", [16, 32, 64])
 @pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
 def test_polar_on_both_sides_of_the_lines_of_the_spread(p, scale):
