@@ -69,7 +69,6 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.sel_state = (int32_t*)take((size_t)4 * 2 * 4);
     w.sel_cnt = (int32_t*)take(sel_chunks * 2 * 4);
     w.sel_base = (int32_t*)take(sel_chunks * 2 * 4);
-    w.sq_out = (double*)take(8);
     w.sq_counter = (int32_t*)take(4);
     w.sweeps = (int32_t*)take((size_t)K * 4);
     w.ns_fallback = (int32_t*)take((size_t)K * 4);
@@ -453,19 +452,21 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
     return SBO_OK;
 }
 
-// own: D holds orthobases that the library has made.
+// own: D holds orthobases that the library has made.  sq_out: the squared-error total of the last round.
 static int run_train_rounds(sbo_ctx* c, const float* Y, int64_t m, const int32_t* blk, float* D, int R,
-                            int32_t* supp, float* coef, float* err, bool own = false) {
+                            int32_t* supp, float* coef, float* err, bool own = false, double* sq_out = nullptr) {
     int rc = run_group(c, blk, m);             // the assignment, hence the grouping, is fixed
     if (rc) return rc;
     for (int r = 0; r < R; ++r) {
+        double* const sq = r == R - 1 ? sq_out : nullptr;
+        const float* const sq_err = sq != nullptr ? err : nullptr;
         if (c->p <= 64) {
             {
                 StageTimer t(c, SBO_STAGE_SELECT);
                 SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err,
                                             c->stream, nullptr, fused_f16(c)));
             }
-            rc = run_polar_pieces(c, m, D, 0, nullptr, nullptr);
+            rc = run_polar_pieces(c, m, D, 0, sq_err, sq);
             if (rc) return rc;
             continue;
         } else {
@@ -474,7 +475,7 @@ static int run_train_rounds(sbo_ctx* c, const float* Y, int64_t m, const int32_t
                 SBO_HIP(launch_select(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, r > 0,
                                       select_arith(c, own), c->stream));
             }
-            rc = run_update_grouped(c, Y, m, supp, coef, D, select_ops(c, own));
+            rc = run_update_grouped(c, Y, m, supp, coef, D, select_ops(c, own), sq_err, sq);
             if (rc) return rc;
         }
     }
@@ -566,13 +567,16 @@ int sbo_new_base(sbo_ctx* c, const float* Y, int64_t m, const int32_t* ids, int6
     return run_new_base(c, Y, n, R, have_q0, Q, supp, coef, err, sqerr_per_round);
 }
 
-// RMSE of the codes in err (Section 4) on its way to the host ...
-static int send_sq(sbo_ctx* c, const float* err, int64_t m) {
+// RMSE of the codes in err (Section 4) on its way to the host: written there by the kernel that adds it up (a copy is a launch of
+// its own), which is that of the last SVD update where there has been one (`added`) ...
+static int prepare_sq(sbo_ctx* c) {
     if (c->host_sq == nullptr)
         SBO_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->host_sq), sizeof(double), hipHostMallocDefault));
     if (c->sq_here == nullptr) SBO_HIP(hipEventCreateWithFlags(&c->sq_here, hipEventDisableTiming));
-    SBO_HIP(launch_sqerr(err, nullptr, m, c->ws, c->ws.sq_out, c->stream));
-    SBO_HIP(hipMemcpyAsync(c->host_sq, c->ws.sq_out, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    return SBO_OK;
+}
+static int send_sq(sbo_ctx* c, const float* err, int64_t m, bool added) {
+    if (!added) SBO_HIP(launch_sqerr(err, nullptr, m, c->ws, c->host_sq, c->stream));
     SBO_HIP(hipEventRecord(c->sq_here, c->stream));
     return SBO_OK;
 }
@@ -649,13 +653,15 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
     // The GPU goes on with the next growth step's worst-W set while the error travels to the host, which decides whether
     // there is to be one.  p = 64, m = 32768, K = 5 to 16: 6958 -> 6408 us (the host's answer, and the launches after
     // it, were waited for once per orthobase); a call that stops on the error pays some 40 us for a set it does not use.
+    rc = prepare_sq(c);
+    if (rc) return fail(rc);
     int n = 0;
-    auto next_error = [&]() {
-        int e = send_sq(c, err, m);
+    auto next_error = [&](bool added) {
+        int e = send_sq(c, err, m, added);
         if (e == SBO_OK && K < K_max) e = prepare_growth(c, Y, err, m, W);
         return e != SBO_OK ? e : wait_rmse(c, m, &rmse_hist[n]);
     };
-    rc = next_error();
+    rc = next_error(false);
     if (rc) return fail(rc);
     ++n;
 
@@ -668,9 +674,9 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
         c->K = K;
         rc = run_code(c, Y, m, D, blk, supp, coef, err);
         if (rc) return fail(rc);
-        rc = run_train_rounds(c, Y, m, blk, D, R, supp, coef, err, true);
+        rc = run_train_rounds(c, Y, m, blk, D, R, supp, coef, err, true, c->host_sq);
         if (rc) return fail(rc);
-        rc = next_error();
+        rc = next_error(true);
         if (rc) return fail(rc);
         ++n;
     }

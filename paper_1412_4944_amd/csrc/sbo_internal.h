@@ -131,7 +131,6 @@ struct Workspace {
     int32_t* sel_state;    // [4][2] (key prefix, entries still to take) after each pass
     int32_t* sel_cnt;      // [ceil(m_max / kSelChunk)][2] entries above / equal to the threshold
     int32_t* sel_base;     // same shape: exclusive sums of sel_cnt over the chunks
-    double* sq_out;        // [1] squared-error total inside sbo_learn
     int32_t* sweeps;       // [K] most recent SVD stage: Jacobi sweeps, or minus the Newton-Schulz steps
     int32_t* ns_fallback;  // [K] 1 = Newton-Schulz left the block to the Jacobi kernel
     int32_t* sq_counter;   // [1] workgroups of the fused squared-error sum that have finished (0 between launches)
