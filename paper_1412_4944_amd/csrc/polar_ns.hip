@@ -37,8 +37,8 @@
 //     parts and l = 0.16, on average 0.81 (p = 32 0.91, p = 16 0.94: the guess alone); p = 32, 16 with two parts 1.3 and 1.5, in the same time.
 //   * The steps' branches are those of scalars: as the sum that decides comes out of lanes, the compiler would take every one of
 //     them for divergent (p = 16: 2 % of an iteration).
-// Measured (p = 64, launch to launch): inside sbo_iterate 22.4 us with a wavefront per strip, 19.5 with two (K = 16, 16384 signals), 17.4 with two
-// parts, 15.6 with the guess (a step less: 1.4 us); a new orthobase 20.8, 17.6, 15.9, 14.5.  p = 32 8.6 us, p = 16 7.2.  Of 37000 cycles
+// Measured (p = 64, launch to launch): inside sbo_iterate (K = 16, 16384 signals) 22.4 us with a wavefront per strip, 19.5 with two; the kernel
+// alone 18.4 there, 16.4 with two parts, 14.6 with the guess (seven steps -> six); on average in sbo_learn (K = 1 to 16) 17.8, 16.0, 14.7.  p = 32 8.8 -> 8.0 us, p = 16 6.8.  Of 37000 cycles
 // at p = 64, K = 16 (seven steps, before the guess): the sum of the pieces 8000 (a CU takes 25 to 40 bytes a cycle of what others have just
 // written), the scale of the input 2000, a step 3500, the last one's E^2 1300, output 2200.
 //
