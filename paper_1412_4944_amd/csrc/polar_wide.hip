@@ -1047,7 +1047,6 @@ __device__ __forceinline__ void write_factor(const WideArgs& g, int j, unsigned 
                                              int* flag, int q, bool alone) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float* GA = reinterpret_cast<float*>(mem + kJaAt);
-    const float* GV = reinterpret_cast<const float*>(mem + kJvAt);
     float* sig = red + 256;                    // [256] words each
     int* isbad = reinterpret_cast<int*>(red + 512);
     float* vec = red + 768;
@@ -1064,8 +1063,12 @@ __device__ __forceinline__ void write_factor(const WideArgs& g, int j, unsigned 
     __syncthreads();
     const bool bad = *flag != 0;               // uniform over the team
     if (bad && q != 0) return;
-    if (bad) {                                 // one workgroup completes the vanished columns
-        for (int e = tid; e < P * P; e += kNT) GA[e] = isbad[e / P] ? 0.f : GA[e] / sig[e / P];
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(uniform(mem), 0, (int)kTeamBytes, 0x00027000);
+    if (bad) {                                 // one workgroup completes the vanished columns, all of A rewritten by itself
+        for (int e = tid; e < P * P; e += kNT) {
+            const float a = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, e * 4, (int)kJaAt, kPastL1));
+            GA[e] = isbad[e / P] ? 0.f : a / sig[e / P];
+        }
         __syncthreads();
         for (int c = 0; c < P; ++c) {
             if (!isbad[c]) continue;           // uniform
@@ -1111,21 +1114,40 @@ __device__ __forceinline__ void write_factor(const WideArgs& g, int j, unsigned 
             __syncthreads();
         }
     }
-    // Q = U V^T, atom-major: D[j][k][r] = sum_c U[r][c] V[k][c]; 32 rows k at a time
+    // Q = U V^T, atom-major: D[j][k][r] = sum_c U[r][c] V[k][c]; 32 rows k at a time.  What the other workgroups have left is
+    // read past L1, which may still hold the same memory as an earlier block of this launch left it (no barrier of a near team
+    // invalidates it); 16 columns at a time through LDS, once for all wavefronts.
+    if (bad) stores_done();
     if (tid < P) sig[tid] = bad ? 1.f : 1.f / sig[tid];
     __syncthreads();
     float* strip = reinterpret_cast<float*>(lds);              // [2][16][kLdStrip] (X and Y are dead)
+    float* cu = reinterpret_cast<float*>(lds);                 // [16 columns][256], before that
+    float* cv = cu + 16 * P;                   // [16 columns][32 rows]
     alone = alone || bad;
     for (int sl = alone ? 0 : q; sl < (alone ? kJacTeam : q + 1); ++sl) {
         const int q0 = 4 * lane, k0 = 4 * wave;
         float o[4][4] = {};
-        for (int c = 0; c < P; ++c) {
-            const f32x4 uu = *reinterpret_cast<const f32x4*>(GA + c * P + q0) * sig[c];
-            const f32x4 vv = *reinterpret_cast<const f32x4*>(GV + c * P + 32 * sl + k0);
+        for (int c0 = 0; c0 < P; c0 += 16) {
+            u32x4 u[2], v = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int t = 0; t < 2; ++t)
+                u[t] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (tid + t * kNT) * 16, (int)kJaAt + c0 * (P * 4), kPastL1);
+            if (tid < 128)                     // 8 units of 16 bytes a column
+                v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (tid >> 3) * (P * 4) + 128 * sl + (tid & 7) * 16,
+                                                          (int)kJvAt + c0 * (P * 4), kPastL1);
+            __syncthreads();                   // the columns before these, or the strip, have been read
 #pragma unroll
-                for (int b = 0; b < 4; ++b) o[a][b] += vv[a] * uu[b];
+            for (int t = 0; t < 2; ++t) reinterpret_cast<u32x4*>(cu)[tid + t * kNT] = u[t];
+            if (tid < 128) reinterpret_cast<u32x4*>(cv)[tid] = v;
+            __syncthreads();
+            for (int c = 0; c < 16; ++c) {
+                const f32x4 uu = *reinterpret_cast<const f32x4*>(cu + c * P + q0) * sig[c0 + c];
+                const f32x4 vv = *reinterpret_cast<const f32x4*>(cv + c * 32 + k0);
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) o[a][b] += vv[a] * uu[b];
+            }
         }
         __syncthreads();
 #pragma unroll

@@ -1043,6 +1043,35 @@ def test_polar_p256_teams_of_workgroups(K, jacobi_only):
     print(f"  K={K} jacobi={jacobi_only}: worst |Q - Q_oracle| {w:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("jacobi_only", [False, True], ids=["auto", "jacobi"])
+def test_polar_p256_blocks_in_turn_are_those_of_a_team_of_their_own(jacobi_only):
+    """p = 256, 40 orthobases: a team has up to three in turn, in the same memory.  By the Jacobi SVD (full and deficient ranks in
+    every order, Newton-Schulz between them) each comes out with the bits that it has where every team has one."""
+    p, K = 256, 40
+    rng = np.random.default_rng(83)
+    M = np.stack([synth.random_onb(rng, p) * np.geomspace(1, 1e-3, p) @ synth.random_onb(rng, p) for _ in range(K)])
+    for j in range(K):
+        if (j % 16 + j // 16) % 3 == 0:                  # rank 216: one workgroup completes it
+            M[j][:, 216:] = M[j][:, :40]
+        elif not jacobi_only and (j % 16 + j // 16) % 3 == 1:
+            M[j] += synth.random_onb(rng, p)             # well conditioned: Newton-Schulz
+    M = M.astype(np.float32)
+    old = np.zeros_like(M)
+    with Sbo(p, K, 4, 256) as g:
+        g.svd_jacobi(jacobi_only)
+        print(f"case jacobi={jacobi_only}", flush=True)
+        D = g.polar(M, old, None)
+        parts = []
+        for at in range(0, K, 16):
+            n = min(16, K - at)
+            sbo.sbo_set_blocks(g.ctx, n)
+            parts.append(g.polar(M[at:at + n], old[at:at + n], None))
+    # the same teams (16 workgroups) in all of them but the last eight, whose teams may be of pairs: the same bits too
+    np.testing.assert_array_equal(D, np.concatenate(parts))
+    for j in range(K):
+        assert np.abs(D[j] @ D[j].T - np.eye(p)).max() <= 1e-5, j
+
+
 @pytest.mark.parametrize("K", [1, 8])
 @pytest.mark.parametrize("polls", [1 << 22, 40, 3, 0])
 def test_polar_p256_teams_of_pairs(K, polls):
