@@ -1,5 +1,5 @@
 // Batched SVD update Q_j = U V^T (Algorithm 1, steps 6-7) for p = 256: a team of 16 workgroups per
-// block (32 where there are eight blocks or fewer), one launch for everything.
+// block (32 where there are eight blocks or fewer and no second stream, wide_pairs), one launch for everything.
 //
 // A 256 x 256 matrix in the three bf16 parts that fp32 accuracy takes is 384 KiB: more than the LDS of
 // a CU, and one CU alone would need 80 us of matrix time for a block.  So 16 workgroups share a block
@@ -21,7 +21,7 @@
 //   is symmetric and goes with the next step; in X E it is made up for by a rounding less, E being scaled by alpha.  |Q - Q64|_F / sqrt(p)
 //   0.85 to 0.95 of what it was (block matrices of training rounds, 384 to 16384 signals); splits and matrix work of a step are halved.
 //
-//   Up to eight blocks, a team on each XCD: two workgroups to a strip, one for the upper and one for the lower half of its rows,
+//   Up to eight blocks on one stream, a team on each XCD: two workgroups to a strip, one for the upper and one for the lower half of its rows,
 //   which halves the operands that each of them reads.  They need each other's half of X, which comes with the barrier, and of E:
 //   a number in memory says when it is there, and half of the contraction runs meanwhile.  The second workgroups are helpers: if
 //   they have not come when the first are all there and have waited a little, these go on without (meet_pairs), so that a
@@ -1654,6 +1654,12 @@ __global__ __launch_bounds__(kNT) void wide_polar_kernel(WideArgs g) {
 
 }  // namespace
 
+// Pairs take a whole XCD for a team, so they are for launches that have the chip to themselves: with contexts of this size on a second
+// stream, a team of one launch and a team of the other one, which share an XCD otherwise, would follow one another.  Two SVDs on two
+// streams, 2 to 8 blocks of a training round: 73 to 75 us together, in pairs 110 to 118.  One alone, 1 to 8 blocks: 58 to 60 us in
+// pairs, 9 blocks, by teams of 16, 72.
+bool wide_pairs(int K, int device) { return K <= kMaxPairTeams && wide_streams(device) < 2; }
+
 size_t polar_wide_scratch_bytes(int K) { return (size_t)(K < kMaxTeams ? K : kMaxTeams) * kTeamBytes; }
 size_t polar_wide_sync_bytes(int K) { return (size_t)(K < kMaxTeams ? K : kMaxTeams) * kSyncInts * sizeof(int); }
 
@@ -1682,7 +1688,7 @@ hipError_t launch_polar_wide(int K, const float* M, const float* partial, const 
     a.spread = wide_streams(ws.device) > 2;
     a.polls = ws.wide_polls;
     a.helper_polls = ws.wide_helpers ? (a.polls < kHelperPolls ? a.polls : kHelperPolls) : -1;
-    const bool pairs = newton_schulz_first && !a.spread && K <= kMaxPairTeams;
+    const bool pairs = newton_schulz_first && wide_pairs(K, ws.device);
     const unsigned grid = (unsigned)(wide_team_wgs(a.teams, a.spread, pairs) + (sq.out != nullptr ? sq.nb : 0));
     auto* kernel = pairs ? &wide_polar_kernel<true, true> : newton_schulz_first ? &wide_polar_kernel<true, false>
                                                                                 : &wide_polar_kernel<false, false>;

@@ -715,6 +715,9 @@ int sbo_test_wide_helpers(sbo_ctx* c, int on) {
     return SBO_OK;
 }
 
+// For tests, not in the header: 1 = the next SVD of this context (p = 256) is made by teams of pairs.
+int sbo_test_wide_pairs(sbo_ctx* c) { return c && c->p == 256 && wide_pairs(c->K, c->ws.device); }
+
 int sbo_set_option(sbo_ctx* c, int option, int value) {
     if (!c) return SBO_EINVAL;
     switch (option) {

@@ -408,6 +408,8 @@ size_t polar_wide_scratch_bytes(int K);
 size_t polar_wide_sync_bytes(int K);
 // Streams of a GPU with live contexts of p = 256 (how many of these launches may run at a time there).
 int wide_streams(int device);
+// Whether the SVD of K orthobases is made by teams of pairs (SBO_SVD_AUTO).
+bool wide_pairs(int K, int device);
 hipError_t launch_polar_wide(int K, const float* M, const float* partial, const int32_t* offsets, int piece,
                              const int32_t* counts, float* D, const DictOps& ops, bool newton_schulz_first,
                              float* eig_sv, const Workspace& ws, const SqTotalArgs& sq, hipStream_t st);

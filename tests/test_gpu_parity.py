@@ -1147,6 +1147,38 @@ def test_polar_p256_on_three_streams():
         assert torch.equal(d, D[0])
 
 
+def test_polar_p256_pairs_have_the_gpu_to_themselves():
+    """Teams of pairs take a whole XCD each, so they are for contexts on one stream; on two streams teams of 16, whose launches
+    overlap, and the same bits."""
+    import torch
+    p, K = 256, 8
+    rng = np.random.default_rng(97)
+    M = torch.from_numpy(np.stack([(synth.random_onb(rng, p) * np.geomspace(1, 0.1, p)) @ synth.random_onb(rng, p)
+                                   for _ in range(K)]).astype(np.float32)).cuda()
+    pairs = sbo.lib().sbo_test_wide_pairs
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    a = sbo.sbo_create(p, K, 4, 256, streams[0].cuda_stream)
+    same = sbo.sbo_create(p, 9, 4, 256, streams[0].cuda_stream)
+    assert pairs(a) == 1 and pairs(same) == 0            # nine orthobases: teams of 16
+    with torch.cuda.stream(streams[0]):
+        alone = torch.zeros_like(M)
+        sbo.sbo_polar(a, M, None, alone)
+    b = sbo.sbo_create(p, K, 4, 256, streams[1].cuda_stream)
+    assert pairs(a) == 0 and pairs(b) == 0
+    D = [torch.zeros_like(M) for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for c, d in zip((a, b), D):
+            sbo.sbo_polar(c, M, None, d)
+    torch.cuda.synchronize()
+    assert torch.equal(D[0], alone) and torch.equal(D[1], alone)
+    sbo.sbo_destroy(b)
+    assert pairs(a) == 1
+    sbo.sbo_destroy(a)
+    sbo.sbo_destroy(same)
+
+
 @pytest.mark.parametrize("polls", [0, 1, 8, 60, 400])
 @pytest.mark.parametrize("K", [1, 9, 33])
 def test_polar_p256_teams_that_give_up(K, polls):
