@@ -244,10 +244,10 @@ enum {
                               accumulation: per-term error 3 * 2^-22 |a||b|, below the p * 2^-24 sum |a||b|
                               an fp32 dot product of p terms guarantees; half the matrix work of
                               SBO_ARITH_BF16X3.  Supports and coefficients come from the six bf16
-                              products, or from fp16 ones of the same error against 64 bits or less: at p = 64
-                              where the update follows at once (sbo_iterate, sbo_train_rounds, sbo_new_base,
-                              sbo_learn), at p = 256 where orthobases are chosen and for those that the library has
-                              made itself (sbo_learn, sbo_new_base with have_q0 = 0).  (For s0 <= p/2 the choice is screened, under every arithmetic: one
+                              products; at p = 256, in the calls that choose orthobases and for those that
+                              the library has made itself (sbo_learn, sbo_new_base with have_q0 = 0), from the
+                              three fp16 ones (measured against 64 bits: half of the error of the
+                              six).  (For s0 <= p/2 the choice is screened, under every arithmetic: one
                               fp16 product and its guaranteed error bound rule out the blocks that cannot
                               win, only the others are computed as described here; the chosen blocks are
                               the same.  p = 256: under this arithmetic only, and for K <= 1013; with more

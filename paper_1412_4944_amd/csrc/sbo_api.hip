@@ -167,8 +167,6 @@ static int select_arith(const sbo_ctx* c, bool own) {
     return a == SBO_ARITH_F32 ? kOpsF32 : a == SBO_ARITH_F16X2 && own ? kOpsF16 : kOpsBf16;
 }
 static int code_arith(const sbo_ctx* c) { return select_arith(c, choice_arith(c) == SBO_ARITH_F16X2); }
-// p <= 64, selection and update in one kernel, which scales the dictionary by itself.
-static bool fused_f16(const sbo_ctx* c) { return c->coding_arith == SBO_ARITH_F16X2; }
 static int select_ops(const sbo_ctx* c, bool own) { return c->p <= 64 ? 0 : select_arith(c, own); }
 static int code_ops(const sbo_ctx* c) { return energy_ops(c) | (c->p <= 64 ? 0 : code_arith(c)); }
 
@@ -444,7 +442,7 @@ int sbo_iterate(sbo_ctx* c, const float* Y, int64_t m, float* D, int n_iter, int
         {
             StageTimer t(c, SBO_STAGE_SELECT);  // includes the per-piece accumulation
             SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err, c->stream,
-                                        lists ? blk : nullptr, fused_f16(c)));
+                                        lists ? blk : nullptr));
         }
         rc = run_polar_pieces(c, m, D, energy_ops(c), err, sqerr_per_iter ? sqerr_per_iter + it : nullptr, -1, lists);
         if (rc) return rc;
@@ -464,7 +462,7 @@ static int run_train_rounds(sbo_ctx* c, const float* Y, int64_t m, const int32_t
             {
                 StageTimer t(c, SBO_STAGE_SELECT);
                 SBO_HIP(launch_select_accum(c->p, c->K, c->s0, Y, m, D, c->ws, supp, coef, err,
-                                            c->stream, nullptr, fused_f16(c)));
+                                            c->stream));
             }
             rc = run_polar_pieces(c, m, D, 0, sq_err, sq);
             if (rc) return rc;
@@ -542,7 +540,7 @@ static int run_new_base(sbo_ctx* c, const float* Y, int64_t n, int R, int have_q
     }
     for (int r = 0; r < R; ++r) {
         if (c->p <= 64) {
-            SBO_HIP(launch_select_accum(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, c->stream, nullptr, fused_f16(c)));
+            SBO_HIP(launch_select_accum(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, c->stream));
         } else {
             SBO_HIP(launch_select(c->p, 1, c->s0, Y, n, Q, c->ws, supp, coef, err, r > 0, select_arith(c, own), c->stream));
         }
@@ -630,7 +628,7 @@ int sbo_learn(sbo_ctx* c, const float* Y, int64_t m, float* D, const int32_t* in
                              c->stream));
         for (int r = 0; r < R; ++r) {
             if (c->p <= 64) {
-                SBO_HIP(launch_select_accum(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, c->stream, nullptr, fused_f16(c)));
+                SBO_HIP(launch_select_accum(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, c->stream));
                 rc = run_polar_pieces(c, n_init, D, 0, nullptr, nullptr, K0);
             } else {
                 SBO_HIP(launch_select(c->p, K0, c->s0, Y, n_init, D, c->ws, supp, coef, err, r > 0, select_arith(c, true), c->stream,

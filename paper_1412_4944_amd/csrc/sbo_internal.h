@@ -354,7 +354,7 @@ hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, co
 // left as launch_group would leave them, ws.perm is not.
 hipError_t launch_select_accum(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                                const Workspace& ws, int32_t* supp, float* coef, float* err,
-                               hipStream_t st, const int32_t* blk = nullptr, bool f16 = false);
+                               hipStream_t st, const int32_t* blk = nullptr);
 // err, sq_out != nullptr: the same launch also forms *sq_out = sum of err[0..m).
 hipError_t launch_accum_reduce(int p, int K, int64_t m, const Workspace& ws, float* M,
                                const float* err, double* sq_out, hipStream_t st);

@@ -6,9 +6,9 @@
 // memory.
 //
 // A workgroup (8 wavefronts, one workgroup per CU) owns one piece of one block's grouped signal
-// list.  Both contractions run on the bf16 or fp16 matrix cores at fp32 accuracy: every fp32 operand
+// list.  Both contractions run on the bf16 matrix cores at fp32 accuracy: every fp32 operand
 // entry is the exact sum of three bf16 parts and the six partial products above 2^-24 are
-// accumulated in fp32, or (F16, p = 64) two fp16 parts of scaled operands and three or four products (device_utils.h).  Q_j is split once per workgroup into LDS in MFMA
+// accumulated in fp32 (device_utils.h).  Q_j is split once per workgroup into LDS in MFMA
 // operand order.  Each wavefront walks tiles of 32 signals:
 //   projection  c = Q_j^T y : atoms on M, signals on N, dims contracted; y is split in registers
 //                             (a lane holds its own signal's dims);
@@ -24,9 +24,10 @@
 // What bounds it: instruction issue and LDS round trips of two wavefronts per SIMD, not memory (Y is
 // read once).  Measured, 262144 signals, K = 32, p = 64, s0 = 8: 61 us with y transposed word by word through
 // lane exchanges and the copies of the accumulators stored entry by entry, 44.6 us as it is (with the shorter
-// selection of select_tile.h); 2^20 signals, K = 128: 265 -> 190 us.  F16 (half of the matrix work, two thirds of the tiles' bytes): 44.3 -> 40.9 and 183 -> 164 us.  Against 64 bits, rms:
-// coefficients 9.0e-8 -> 5.9e-8 of theirs, residuals 1.65e-7 -> 1.57e-7 (1.82e-7 without the product of the second parts), Q after
-// an iteration 0.77 to 1.01 of what it was.  p = 32 with two parts: residuals 1.5e-7 -> 2.4e-7, so that it stays with three.
+// selection of select_tile.h); 2^20 signals, K = 128: 265 -> 186 us.  Taken back: two fp16 parts, three products (40.4 and 166 us, and
+// coefficients closer to 64 bits, 5.9e-8 of theirs instead of 9.0e-8): the range of fp16 asks for a scale of every atom and of every
+// signal, and what one scale of P_j leaves of signals 2^-8 as strong as others is short of fp32.  The small products summed apart: 4.9e-8,
+// but 49.3 us.
 #include "sbo_internal.h"
 #include "device_utils.h"
 #include "select_tile.h"
@@ -36,24 +37,6 @@ namespace sbo {
 namespace {
 
 constexpr int kSaWaves = 8;
-constexpr int kNoScale = 1 << 20;
-
-// 8 consecutive values in NPT parts: two fp16 or three bf16.
-template <int NPT>
-__device__ __forceinline__ void parts_of(f32x4 v0, f32x4 v1, u32x4 (&out)[NPT]) {
-    if constexpr (NPT == 2) {
-        const F16x2Pair a = split_f16x2(v0.x, v0.y), b = split_f16x2(v0.z, v0.w);
-        const F16x2Pair c = split_f16x2(v1.x, v1.y), d = split_f16x2(v1.z, v1.w);
-        out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
-        out[1] = u32x4{a.lo, b.lo, c.lo, d.lo};
-    } else {
-        const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
-        const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
-        out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
-        out[1] = u32x4{a.mid, b.mid, c.mid, d.mid};
-        out[2] = u32x4{a.lo, b.lo, c.lo, d.lo};
-    }
-}
 
 // LDS of a wavefront: the stage and the operand tiles (or the scratch for ties); at the end a copy of its accumulators.
 template <int P, int S0>
@@ -64,8 +47,7 @@ constexpr int sa_wave_bytes() {
 }
 
 // GROUP: the signals have not been grouped, every workgroup lists those of its own piece (ChunkLists).
-// F16: two fp16 parts instead of three bf16 ones.
-template <int P, int S0, bool GROUP, bool F16>
+template <int P, int S0, bool GROUP>
 __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     const float* __restrict__ Y, const float* __restrict__ D, int K, int piece,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm, int32_t* __restrict__ supp,
@@ -75,23 +57,21 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     constexpr int MT = P >= 32 ? P / 32 : 1;   // 32-wide tiles per side of P_j
     constexpr int ROWS = MT * 32;              // operand tile rows (atoms resp. dims; rows >= P are not used)
     constexpr int PP = P * P;
-    constexpr int NPT = F16 ? 2 : 3;           // parts
-    constexpr int Q_U = MT * KS16 * NPT * 64;  // Q_j in split operand order, 16-byte units
+    constexpr int Q_U = MT * KS16 * 3 * 64;    // Q_j in split operand order, 16-byte units
     constexpr int PLANE_B = (ROWS + 1) * 32;   // bytes of one part of a transposed operand tile (+ a dummy row)
     constexpr int CT_B = kSelectTieWords * 4;           // tie-breaking scratch of tile_select
-    constexpr int OPS_B = 2 * NPT * PLANE_B;   // x tile (all parts) + y tile
+    constexpr int OPS_B = 6 * PLANE_B;         // x tile (3 parts) + y tile (3 parts)
     constexpr int REGION_B = (OPS_B > CT_B ? OPS_B : CT_B);
     constexpr int WAVE_B = sa_wave_bytes<P, S0>();
     static_assert(kSelectStageWords<S0> * 4 + REGION_B <= WAVE_B, "stage and region");
     constexpr int YU = P / 8 - 1 < 7 ? P / 8 - 1 : 7;      // of a signal's 16-byte units
     constexpr int NE = (S0 + 3) / 4;            // kept entries per lane and half tile
 
-    // Qs[Q_U] | flags[8] (F16) | per wavefront: stage | region; GROUP: the table of `lists` in the place of the latter first, and
+    // Qs[Q_U] | per wavefront: stage | region; GROUP: the table of `lists` in the place of the latter first, and
     // ids[piece] behind everything
     extern __shared__ __attribute__((aligned(16))) int lds[];
     u32x4* Qs = reinterpret_cast<u32x4*>(lds);
-    int* flags = reinterpret_cast<int*>(Qs + Q_U);
-    unsigned char* waves_base = reinterpret_cast<unsigned char*>(Qs + Q_U + (F16 ? NW * 4 / 16 : 0));      // (the launcher allows for three parts)
+    unsigned char* waves_base = reinterpret_cast<unsigned char*>(Qs + Q_U);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -145,58 +125,21 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
         q1 = D4[q_atom * (P / 4) + q_ks * 4 + h * 2 + 1];
     }
     load_rows(i_cur);
-    int q_shift = 13;                          // F16: Q_j is scaled by 2^q_shift
-    auto put_q = [&]() {
-        if (q_mt >= MT) return;
-        u32x4 part[NPT];
-        f32x4 v0 = q0, v1 = q1;
-        if constexpr (F16) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v0[e] = __builtin_amdgcn_ldexpf(q0[e], q_shift);
-                v1[e] = __builtin_amdgcn_ldexpf(q1[e], q_shift);
-            }
-        }
-        parts_of<NPT>(v0, v1, part);
-#pragma unroll
-        for (int pl = 0; pl < NPT; ++pl) Qs[((tid >> 6) * NPT + pl) * 64 + lane] = part[pl];
-    };
-    put_q();
-    unsigned q_mx = 0;                         // largest magnitude of this thread's entries
-    if constexpr (F16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float a = fabsf(q0[e]), b = fabsf(q1[e]);
-            q_mx = max(q_mx, max(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b)));
-        }
-        const bool big = __any(q_mx >= 0x41000000u);           // 8 and more: not below 2^16
-        if (lane == 0) flags[wave] = big;
+    if (q_mt < MT) {
+        const Bf16x3Pair a = split_bf16x3(q0.x, q0.y), b = split_bf16x3(q0.z, q0.w);
+        const Bf16x3Pair c = split_bf16x3(q1.x, q1.y), d = split_bf16x3(q1.z, q1.w);
+        u32x4* out = Qs + ((tid >> 6) * 3) * 64 + lane;
+        out[0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+        out[64] = u32x4{a.mid, b.mid, c.mid, d.mid};
+        out[128] = u32x4{a.lo, b.lo, c.lo, d.lo};
     }
     int* stage = reinterpret_cast<int*>(waves_base + (size_t)wave * WAVE_B);
     unsigned char* region = reinterpret_cast<unsigned char*>(stage + kSelectStageWords<S0>);
-    unsigned char* xt = region;                // [parts][ROWS atoms][16 signals] in 16 bits
-    unsigned char* yt = region + NPT * PLANE_B;            // [parts][16 signals][P dims]
+    unsigned char* xt = region;                // [3 parts][ROWS atoms][16 signals] bf16
+    unsigned char* yt = region + 3 * PLANE_B;  // [3 parts][16 signals][P dims] bf16
     // the x tile starts out zero (and is left zero by every tile)
-    for (int e = lane; e < NPT * PLANE_B / 16; e += 64) reinterpret_cast<u32x4*>(xt)[e] = u32x4{0u, 0u, 0u, 0u};
+    for (int e = lane; e < 3 * PLANE_B / 16; e += 64) reinterpret_cast<u32x4*>(xt)[e] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
-    if constexpr (F16) {
-        int any = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) any |= flags[w];
-        if (__builtin_amdgcn_readfirstlane(any)) {             // uniform, rare: a caller's dictionary, which need not be an orthobase
-            int e = (int)(q_mx >> 23);
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) e = max(e, __shfl_xor(e, o, 64));
-            __syncthreads();                   // the flags have been read
-            if (lane == 0) flags[wave] = e;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < NW; ++w) e = max(e, flags[w]);
-            if (e != 0xff) q_shift = min(13, 142 - __builtin_amdgcn_readfirstlane(e));
-            put_q();
-            __syncthreads();
-        }
-    }
 
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                          0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -205,119 +148,59 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int b = 0; b < MT; ++b) accM[a][b] = zero;
-    // the partial products, smallest first: (A part, B part)
-    constexpr int NP = F16 ? 3 : 6;
-    constexpr int TA[6] = {F16 ? 1 : 2, 0, F16 ? 0 : 1, 1, 0, 0};
-    constexpr int TB[6] = {0, F16 ? 1 : 2, F16 ? 0 : 1, 0, 1, 0};
-    auto mfma = [](u32x4 a, u32x4 b, f32x16 c) {
-        if constexpr (F16)
-            return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-        else
-            return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    };
-    int up = kNoScale;                         // F16: accM is P_j's share times 2^up (uniform)
+    // the six partial products, smallest first: (A part, B part)
+    constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
+    constexpr int TB[6] = {0, 2, 1, 0, 1, 0};
 
     for (int tile = wave; tile < n_tiles; tile += NW) {
         const int64_t i = i_cur;
         const bool active = tile * 32 + n < cnt;
         const int cnt_t = min(32, cnt - tile * 32);        // signals in this tile (uniform)
 
-        // the parts of y (B operand of the projection); F16: of the signal times 2^shift, its largest magnitude in [2^13, 2^14)
-        u32x4 yq[KS16][NPT];
-        int shift = 0;
-        if constexpr (F16) {
-            unsigned mx = 0;
+        // y in three bf16 parts (B operand of the projection)
+        u32x4 yq[KS16][3];
 #pragma unroll
-            for (int ks = 0; ks < KS16; ++ks)
-#pragma unroll
-                for (int e = 0; e < 2; ++e)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float m = fabsf(raw[ks][e][c]);
-                        mx = max(mx, __builtin_bit_cast(unsigned, m));
-                    }
-            mx = max(mx, pair_other(mx, h));
-            const int e = (int)(mx >> 23);
-            shift = e == 0xff ? 0 : 140 - max(e, 1);
-#pragma unroll
-            for (int ks = 0; ks < KS16; ++ks)
-#pragma unroll
-                for (int e = 0; e < 2; ++e)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) raw[ks][e][c] = __builtin_amdgcn_ldexpf(raw[ks][e][c], shift);
+        for (int ks = 0; ks < KS16; ++ks) {
+            const f32x4 v0 = raw[ks][0], v1 = raw[ks][1];
+            const Bf16x3Pair a = split_bf16x3(v0.x, v0.y), b = split_bf16x3(v0.z, v0.w);
+            const Bf16x3Pair c = split_bf16x3(v1.x, v1.y), d = split_bf16x3(v1.z, v1.w);
+            yq[ks][0] = u32x4{a.hi, b.hi, c.hi, d.hi};
+            yq[ks][1] = u32x4{a.mid, b.mid, c.mid, d.mid};
+            yq[ks][2] = u32x4{a.lo, b.lo, c.lo, d.lo};
         }
-#pragma unroll
-        for (int ks = 0; ks < KS16; ++ks) parts_of<NPT>(raw[ks][0], raw[ks][1], yq[ks]);
         i_cur = i_next;
         i_next = tile_id(tile + 2 * NW);
         load_rows(i_cur);                      // rows of the next tile
 
         // projection c = Q_j^T y
-        f32x16 acc[MT], rest[MT];              // F16: the products with a second part apart, less is rounded at the size of the sum
+        f32x16 acc[MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = rest[mt] = zero;
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = zero;
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks) {
-            u32x4 a[MT][NPT];
+            u32x4 a[MT][3];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int pl = 0; pl < NPT; ++pl) a[mt][pl] = Qs[((mt * KS16 + ks) * NPT + pl) * 64 + lane];
-            if constexpr (F16) {               // the product of the second parts too: small coefficients are a fifth more exact for it
+                for (int pl = 0; pl < 3; ++pl) a[mt][pl] = Qs[((mt * KS16 + ks) * 3 + pl) * 64 + lane];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) rest[mt] = mfma(a[mt][1], yq[ks][1], rest[mt]);
-            }
+            for (int t = 0; t < 6; ++t)
 #pragma unroll
-            for (int t = 0; t < NP; ++t)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    f32x16& to = F16 && t < 2 ? rest[mt] : acc[mt];
-                    to = mfma(a[mt][TA[t]], yq[ks][TB[t]], to);
-                }
-        }
-        if constexpr (F16) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc[mt] += rest[mt];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mt][r] = __builtin_amdgcn_ldexpf(acc[mt][r], -q_shift - shift);
-            }
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[mt][TA[t]]),
+                                                                      __builtin_bit_cast(bf16x8, yq[ks][TB[t]]),
+                                                                      acc[mt], 0, 0, 0);
         }
 
         // support, coefficients, residual; the (atom, coefficient) rows stay in `stage` for the
         // product below.
         // The tie-breaking scratch is the operand region: the x tile is zeroed again if it was used.
         bool ties = false;
-        float largest = 0.f;                   // of this lane's magnitudes
-        tile_select<P, S0>(acc, h, n, active, i, reinterpret_cast<float*>(region), stage, supp, coef, err, &ties, &largest);
+        tile_select<P, S0>(acc, h, n, active, i, reinterpret_cast<float*>(region), stage, supp, coef, err, &ties);
         if (ties) {                            // uniform (rare): the scratch overwrote the zeroed x tile
-            for (int e = lane; e < NPT * PLANE_B / 16; e += 64)
+            for (int e = lane; e < 3 * PLANE_B / 16; e += 64)
                 reinterpret_cast<u32x4*>(xt)[e] = u32x4{0u, 0u, 0u, 0u};
         }
-
-        // F16: x y^T is made of y 2^shift and x 2^(up - shift).  `up` has to leave every x below 2^15; where it does not yet, it is
-        // lowered, with 2^6 to spare, and what has been added up is scaled.  (What is lost of a signal that is 2^k smaller than the
-        // largest one, 2^-25 of x, is 2^-(k + 30) of what that one adds.)
-        if constexpr (F16) {
-            const int e = (int)(__builtin_bit_cast(unsigned, fmaxf(largest, pair_other(largest, h))) >> 23);
-            const int room = active && e != 0xff ? shift + 141 - max(e, 1) : kNoScale;
-            if (__any(room < up)) {
-                int least = room;
-#pragma unroll
-                for (int o = 16; o >= 1; o >>= 1) least = min(least, __shfl_xor(least, o, 64));
-                const int to = __builtin_amdgcn_readfirstlane(least) - 6;
-                if (up != kNoScale) {          // uniform
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int nt = 0; nt < MT; ++nt)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) accM[mt][nt][r] = __builtin_amdgcn_ldexpf(accM[mt][nt][r], to - up);
-                }
-                up = to;
-            }
-        }
-        const int x_shift = F16 ? up - shift : 0;              // of signal n
 
         // P_j += sum over the tile's signals of x y^T, 16 signals at a time
 #pragma unroll
@@ -334,32 +217,24 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
 #pragma unroll
                 for (int ks = 0; ks < KS16; ++ks)
 #pragma unroll
-                    for (int pl = 0; pl < NPT; ++pl)
+                    for (int pl = 0; pl < 3; ++pl)
                         *reinterpret_cast<u32x4*>(yt + pl * PLANE_B + sc * (P * 2) + (((ks * 2 + h) ^ (sc & YU)) << 4)) = yq[ks][pl];
             }
             // kept coefficients -> [atom][signal]; four lanes of a signal share its entries
             // (entries that do not exist go to the dummy row instead of a branch)
             int at_[NE];
             {
-                const int sx = lane & 15, row = 16 * half + sx, by = F16 ? __shfl(x_shift, row, 64) : 0;
+                const int sx = lane & 15, row = 16 * half + sx;
 #pragma unroll
                 for (int t = 0; t < NE; ++t) {
                     const int pos = 4 * t + (lane >> 4);
                     const bool have = row < cnt_t && pos < S0;
                     const int atom = stage[stage_idx(row, 0, have ? pos : 0)];
-                    const float x = __builtin_bit_cast(float, stage[stage_idx(row, 1, have ? pos : 0)]);
+                    const TriWord w = split_trunc(__builtin_bit_cast(float, stage[stage_idx(row, 1, have ? pos : 0)]));
                     at_[t] = tr_off(have ? (atom & (ROWS - 1)) : ROWS, sx);   // row ROWS: nobody reads it
-                    if constexpr (F16) {
-                        const float v = __builtin_amdgcn_ldexpf(x, by);
-                        const _Float16 hi = (_Float16)v, lo = (_Float16)(v - (float)hi);
-                        *reinterpret_cast<_Float16*>(xt + at_[t]) = hi;
-                        *reinterpret_cast<_Float16*>(xt + PLANE_B + at_[t]) = lo;
-                    } else {
-                        const TriWord w = split_trunc(x);
-                        *reinterpret_cast<unsigned short*>(xt + at_[t]) = (unsigned short)(w.hi >> 16);
-                        *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = (unsigned short)(w.mid >> 16);
-                        *reinterpret_cast<unsigned short*>(xt + 2 * PLANE_B + at_[t]) = (unsigned short)(w.lo >> 16);
-                    }
+                    *reinterpret_cast<unsigned short*>(xt + at_[t]) = (unsigned short)(w.hi >> 16);
+                    *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = (unsigned short)(w.mid >> 16);
+                    *reinterpret_cast<unsigned short*>(xt + 2 * PLANE_B + at_[t]) = (unsigned short)(w.lo >> 16);
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -368,7 +243,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
             // operands: lane (h, n) takes signals 8h .. 8h+7 of atom resp. dim t*32 + n; the dims by
             // ds_read_b64_tr_b16 (of 16 lanes, lane i addresses four dims, 4 (i & 3) .., of signal i >> 2 and
             // receives dim i of the four signals)
-            u32x4 xa[MT][NPT], yb[MT][NPT];
+            u32x4 xa[MT][3], yb[MT][3];
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 int ya[2];
@@ -378,7 +253,7 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
                     ya[k] = sig * (P * 2) + (((d >> 3) ^ (sig & YU)) << 4) + (d & 4) * 2;
                 }
 #pragma unroll
-                for (int pl = 0; pl < NPT; ++pl) {
+                for (int pl = 0; pl < 3; ++pl) {
                     typedef short s16x4 __attribute__((ext_vector_type(4)));
                     typedef __attribute__((address_space(3))) s16x4* lds_ptr;
                     xa[t][pl] = *reinterpret_cast<const u32x4*>(xt + pl * PLANE_B + tr_off(t * 32 + n, 8 * h));
@@ -389,31 +264,25 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
                 }
             }
 #pragma unroll
-            for (int t = 0; t < NP; ++t)
+            for (int t = 0; t < 6; ++t)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                    for (int nt = 0; nt < MT; ++nt) accM[mt][nt] = mfma(xa[mt][TA[t]], yb[nt][TB[t]], accM[mt][nt]);
+                    for (int nt = 0; nt < MT; ++nt)
+                        accM[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8, xa[mt][TA[t]]), __builtin_bit_cast(bf16x8, yb[nt][TB[t]]),
+                            accM[mt][nt], 0, 0, 0);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();   // the operands have been read: wipe the x entries again
 #pragma unroll
             for (int t = 0; t < NE; ++t) {
-#pragma unroll
-                for (int pl = 0; pl < NPT; ++pl) *reinterpret_cast<unsigned short*>(xt + pl * PLANE_B + at_[t]) = 0;
+                *reinterpret_cast<unsigned short*>(xt + at_[t]) = 0;
+                *reinterpret_cast<unsigned short*>(xt + PLANE_B + at_[t]) = 0;
+                *reinterpret_cast<unsigned short*>(xt + 2 * PLANE_B + at_[t]) = 0;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();       // stage and the region are rewritten by the next tile
-    }
-    if constexpr (F16) {
-        if (up != kNoScale) {                  // uniform
-#pragma unroll
-            for (int a = 0; a < MT; ++a)
-#pragma unroll
-                for (int b = 0; b < MT; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) accM[a][b][r] = __builtin_amdgcn_ldexpf(accM[a][b][r], -up);
-        }
     }
     __syncthreads();                           // all tiles done: their LDS becomes the exchange area
 
@@ -449,8 +318,8 @@ __global__ __launch_bounds__(64 * kSaWaves) void select_accum_kernel(
     }
 }
 
-template <int P, int S0, bool F16>
-hipError_t launch_psf(const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
+template <int P, int S0>
+hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
                      int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
     constexpr size_t wave_b = sa_wave_bytes<P, S0>();
@@ -463,36 +332,28 @@ hipError_t launch_psf(const float* Y, int64_t m, const float* D, int K, const Wo
         if (g.chunk != kListChunk || lds > 160 * 1024 ||
             ChunkLists::table_ints(kSaWaves, K, g.n_chunks) * sizeof(int) > kSaWaves * wave_b)
             return hipErrorInvalidValue;
-        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, true, F16>), 160 * 1024);
+        if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, true>), 160 * 1024);
             e != hipSuccess)
             return e;
-        hipLaunchKernelGGL((select_accum_kernel<P, S0, true, F16>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K,
+        hipLaunchKernelGGL((select_accum_kernel<P, S0, true>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K,
                            piece, nullptr, nullptr, supp, coef, err, ws.partial,
                            ChunkLists{blk, (int)m, g.n_chunks, ws.chunk_count, ws.counts, ws.offsets});
         return hipGetLastError();
     }
-    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, false, F16>), 160 * 1024);
+    if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(&select_accum_kernel<P, S0, false>), 160 * 1024);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((select_accum_kernel<P, S0, false, F16>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K,
+    hipLaunchKernelGGL((select_accum_kernel<P, S0, false>), dim3(max_pieces), dim3(64 * kSaWaves), lds, st, Y, D, K,
                        piece, ws.offsets, ws.perm, supp, coef, err, ws.partial, ChunkLists{});
     return hipGetLastError();
 }
 
-template <int P, int S0>
-hipError_t launch_ps(const float* Y, int64_t m, const float* D, int K, const Workspace& ws, int32_t* supp, float* coef, float* err,
-                     hipStream_t st, const int32_t* blk, bool f16) {
-    if constexpr (P == 64)
-        if (f16) return launch_psf<P, S0, true>(Y, m, D, K, ws, supp, coef, err, st, blk);
-    return launch_psf<P, S0, false>(Y, m, D, K, ws, supp, coef, err, st, blk);
-}
-
 template <int P>
 hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, const Workspace& ws,
-                    int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk, bool f16) {
+                    int32_t* supp, float* coef, float* err, hipStream_t st, const int32_t* blk) {
     switch (s0) {
 #define SBO_CASE(N) \
-    case N: return launch_ps<P, N>(Y, m, D, K, ws, supp, coef, err, st, blk, f16);
+    case N: return launch_ps<P, N>(Y, m, D, K, ws, supp, coef, err, st, blk);
         SBO_CASE(1) SBO_CASE(2) SBO_CASE(3) SBO_CASE(4) SBO_CASE(5) SBO_CASE(6) SBO_CASE(7) SBO_CASE(8)
         SBO_CASE(9) SBO_CASE(10) SBO_CASE(11) SBO_CASE(12) SBO_CASE(13) SBO_CASE(14) SBO_CASE(15) SBO_CASE(16)
 #undef SBO_CASE
@@ -507,12 +368,12 @@ hipError_t launch_p(int s0, const float* Y, int64_t m, const float* D, int K, co
 // p <= 64 only.
 hipError_t launch_select_accum(int p, int K, int s0, const float* Y, int64_t m, const float* D,
                                const Workspace& ws, int32_t* supp, float* coef, float* err,
-                               hipStream_t st, const int32_t* blk, bool f16) {
+                               hipStream_t st, const int32_t* blk) {
     if (blk != nullptr && !lists_in_round(p, K, m)) return hipErrorInvalidValue;
     switch (p) {
-        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, st, blk, f16);
-        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, st, blk, f16);
-        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, st, blk, f16);
+        case 16: return launch_p<16>(s0, Y, m, D, K, ws, supp, coef, err, st, blk);
+        case 32: return launch_p<32>(s0, Y, m, D, K, ws, supp, coef, err, st, blk);
+        case 64: return launch_p<64>(s0, Y, m, D, K, ws, supp, coef, err, st, blk);
         default: return hipErrorInvalidValue;
     }
 }

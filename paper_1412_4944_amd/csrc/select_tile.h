@@ -57,7 +57,7 @@ __device__ __forceinline__ int pair_other(int x, int h) { return (int)pair_other
 template <int P, int S0>
 __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, bool active, int64_t i, float* ct, int* stage,
                                             int32_t* __restrict__ supp, float* __restrict__ coef,
-                                            float* __restrict__ err, bool* used_ct = nullptr, float* largest = nullptr) {
+                                            float* __restrict__ err, bool* used_ct = nullptr) {
     constexpr int MT = P >= 32 ? P / 32 : 1;
     constexpr int NVL = MT * 16, S = pow2_at_least(S0);
     constexpr int LDC = kSelectTieWords / 32;
@@ -75,7 +75,6 @@ __device__ __forceinline__ void tile_select(const f32x16* acc, int h, int n, boo
     // tau = s0-th largest magnitude of the signal: the s0 largest are max(top_t, oth_{s0-1-t}).
     float top[S], tau = __builtin_inff();
     top_sorted<NVL, S>(mag, top);
-    if (largest != nullptr) *largest = top[0];
 #pragma unroll
     for (int t = 0; t < S0; ++t) tau = fminf(tau, fmaxf(top[t], pair_other(top[S0 - 1 - t], h)));
 

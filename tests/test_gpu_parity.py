@@ -949,9 +949,8 @@ def test_select_p256_two_parts_over_magnitudes(m):
 @pytest.mark.parametrize("m,s0", [(1500, 8), (6000, 5), (140000, 2)])      # a tile per wavefront; a few; many, grouped first
 @pytest.mark.parametrize("order", ["rising", "falling", "mixed"])
 def test_select_accum_two_parts_over_magnitudes(m, s0, order):
-    """Signals of 1e-9 to 1, zeros among them, in one block: the sums of a piece are kept at a power of two that leaves its
-    largest coefficients in fp16's range, lowered whenever a larger one comes (rising: in most tiles).  Coefficients:
-    4 * 2^-22 |y||q| for the parts, and sums of 24 products, 2^-24 each, of at most |y||q|.  The update from the call's own codes."""
+    """Signals of 1e-9 to 1, zeros among them, in one block and in every order: wherever parts of operands are scaled, no scale may fit
+    the strong signals of a tile or piece alone.  Coefficients: 4 * 2^-22 |y||q| for the parts (two in fp16; three in bf16 leave less), and sums of 24 products, 2^-24 each, of at most |y||q|.  The update from the call's own codes."""
     p, K = 64, 2
     rng = np.random.default_rng(59 + m)
     D = np.stack([synth.random_onb(rng, p) for _ in range(K)]).astype(np.float32)
@@ -975,7 +974,7 @@ def test_select_accum_two_parts_over_magnitudes(m, s0, order):
 
 @pytest.mark.parametrize("largest", [7.9, 8.1, 3e4, 1e20])
 def test_train_rounds_with_large_dictionary_entries(largest):
-    """sbo_train_rounds takes any dictionary: entries of 8 and more leave fp16's range with the usual scale."""
+    """sbo_train_rounds takes any dictionary; entries of 8 and more are beyond fp16's range with the usual scale."""
     p, K, m, s0 = 64, 2, 3000, 6
     rng = np.random.default_rng(67)
     D = np.stack([synth.random_onb(rng, p) for _ in range(K)])
@@ -990,6 +989,65 @@ def test_train_rounds_with_large_dictionary_entries(largest):
     assert (np.abs(coef - np.take_along_axis(c64, supp, 1)) <= (4 * 2.0 ** -22 + 24 * 2.0 ** -24) * size[:, None]).all()
     Dn, M = orc.o_update(Y, blk, supp, coef, D)
     compare_Q(Q, Dn, M, np.ones(K, bool))
+
+
+@pytest.mark.parametrize("p", [16, 32, 64])
+@pytest.mark.parametrize("kind,size", [("largest", 7.999), ("largest", 15.999), ("largest", 1.9999 * 2.0 ** 40), ("scale", 1e-6),
+                                       ("scale", 1e-8), ("scale", 1e-12), ("atom", 1e6), ("atom", 1e8), ("atom", 1e-8)])
+def test_train_rounds_with_any_dictionary(p, kind, size):
+    """Orthobases by any factor, largest entries just below a power of two, and one atom of another size than the others: the
+    coefficient of an atom is as exact as its own norm allows (bound as above)."""
+    K, m, s0 = 2, 3000, 4
+    rng = np.random.default_rng(71)
+    D = np.stack([synth.random_onb(rng, p) for _ in range(K)])
+    if kind == "largest":
+        D[1] *= size / np.abs(D[1]).max()
+    elif kind == "scale":
+        D[1] *= size
+    else:
+        D[1][5] *= size
+    D = D.astype(np.float32)
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    blk = rng.integers(0, K, m).astype(np.int32)
+    with Sbo(p, K, s0, m) as g:
+        Q, supp, coef, _err = g.train_rounds(Y, blk, D, 1)
+    D64, Y64 = D.astype(np.float64), Y.astype(np.float64)
+    c64 = np.where(blk[:, None] == 0, Y64 @ D64[0].T, Y64 @ D64[1].T)
+    bound = (4 * 2.0 ** -22 + 24 * 2.0 ** -24) * np.linalg.norm(Y64, axis=1)[:, None] * np.linalg.norm(D64, axis=2)[blk]
+    assert (np.abs(coef - np.take_along_axis(c64, supp, 1)) <= np.take_along_axis(bound, supp, 1)).all()
+    kept = np.zeros((m, p), bool)
+    np.put_along_axis(kept, supp, True, 1)
+    mag = np.abs(c64)
+    assert (np.where(kept, mag + bound, np.inf).min(1) >= np.where(kept, 0, mag - bound).max(1)).all()
+    Dn, M = orc.o_update(Y, blk, supp, coef, D)
+    compare_Q(Q, Dn, M, np.ones(K, bool))
+
+
+@pytest.mark.parametrize("p", [16, 32, 64])
+@pytest.mark.parametrize("seed", [1, 2, 3])
+def test_update_of_an_atom_that_only_weak_signals_use(p, seed):
+    """Signals 2^-10 as strong as the others use the last atom, and nobody else does: its row of P_j, some 1e-5 of the largest one (from
+    1e-6 on the SVD takes a row for zero), is a sum of its own, as exact as that row's size allows.  Bound: the sums of 16 products and
+    the rotations of the SVD, a rounding of 2^-24 in each of some 100."""
+    s0, weak, strong = 4, 16, 105 * p // 64
+    rng = np.random.default_rng(73 + seed)
+    D = synth.random_onb(rng, p)
+    x = np.zeros((weak + strong, p))
+    for i in range(weak + strong):
+        x[i, rng.permutation(p - 1)[:s0]] = rng.uniform(0.5, 2, s0) * rng.choice([-1, 1], s0)
+    x[:weak, p - 1] = rng.uniform(2, 3, weak)            # (the fifth: the smallest of the others goes)
+    Y = x @ D + 0.02 * rng.standard_normal((weak + strong, p))
+    Y[:weak] *= 2.0 ** -10
+    Y = Y[rng.permutation(weak + strong)].astype(np.float32)
+    blk = np.zeros(weak + strong, np.int32)
+    with Sbo(p, 1, s0, weak + strong) as g:
+        Q, supp, coef, _err = g.train_rounds(Y, blk, D[None].astype(np.float32), 1)
+    used = (supp == p - 1).any(1)
+    assert used.sum() == weak and np.abs(coef[used]).max() < 2.0 ** -7
+    Dn, _M = orc.o_update(Y, blk, supp, coef, D[None])
+    off = np.linalg.norm(Q[0, p - 1] - Dn[0, p - 1])
+    print(f"  p={p}: last atom off by {off:.2e}", flush=True)
+    assert off <= 100 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("p", [16, 32, 64])
