@@ -247,7 +247,7 @@ enum {
                               products; at p = 256, in the calls that choose orthobases and for those that
                               the library has made itself (sbo_learn, sbo_new_base with have_q0 = 0), from the
                               three fp16 ones (measured against 64 bits: half of the error of the
-                              six).  (For s0 <= p/2 the choice is screened, under every arithmetic: one
+                              six; an atom of norm below 1/16 or from 4 on is scaled by itself).  (For s0 <= p/2 the choice is screened, under every arithmetic: one
                               fp16 product and its guaranteed error bound rule out the blocks that cannot
                               win, only the others are computed as described here; the chosen blocks are
                               the same.  p = 256: under this arithmetic only, and for K <= 1013; with more

@@ -103,7 +103,8 @@ __device__ __forceinline__ unsigned represented(const u32x4 (&rows)[2][4][2][64]
 template <int P, bool GUESS>
 __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict__ D, int K,
                                                          u32x4* __restrict__ Dsb, u32x4* __restrict__ Dsh,
-                                                         float2* __restrict__ dnorm, float* __restrict__ dev, CallStart start,
+                                                         float2* __restrict__ dnorm, int* __restrict__ dodd,
+                                                         float* __restrict__ dev, CallStart start,
                                                          SignalSample sample) {
     start.clear();
     constexpr int KS16 = P / 16, R = dict_rows<P>();
@@ -174,10 +175,15 @@ __global__ __launch_bounds__(256) void dict_parts_kernel(const float* __restrict
                 q2 += qs[threadIdx.x][e];
                 r2 += rs[threadIdx.x][e];
             }
+            const bool odd = odd_norm2(q2);
             q2 = row16_max(q2);
             r2 = row16_max(r2);
             const int at = (row0 + (int)threadIdx.x) >> 4;
             if ((threadIdx.x & 15) == 0 && at < K * (P / 16)) dnorm[at] = float2{sqrtf(q2), sqrtf(r2)};
+            if constexpr (P == 256) {          // (before the shuffle, or lanes of other sixteens)
+                const unsigned long long mask = __ballot(odd);
+                if ((threadIdx.x & 15) == 0 && at < K * (P / 16)) dodd[at] = (int)(mask >> (threadIdx.x & 48) & 0xffff) != 0;
+            }
         }
         if constexpr (GUESS) {
             // Half of Q Q^T, products to 2^-22: this workgroup's rows with themselves by the third wavefront, with the others by
@@ -965,7 +971,7 @@ hipError_t launch_dict_swizzle(int p, int K, const float* D, float* dsw, const C
     return hipGetLastError();
 }
 
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, float2* dev,
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, int* dodd, float2* dev,
                              const SignalSample& sample, const CallStart& start, hipStream_t st) {
     u32x4 *b = reinterpret_cast<u32x4*>(dsb), *h = reinterpret_cast<u32x4*>(dsh);
     float* dv = reinterpret_cast<float*>(dev);
@@ -973,12 +979,12 @@ hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsign
     const unsigned stages = (unsigned)(K * p + 63) / 64;           // (the last one is filled up with zeros)
     switch (p) {
 #define SBO_CASE(N) \
-    case N: hipLaunchKernelGGL((dict_parts_kernel<N, false>), dim3(stages * (64 / dict_rows<N>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start, sample); break;
+    case N: hipLaunchKernelGGL((dict_parts_kernel<N, false>), dim3(stages * (64 / dict_rows<N>())), dim3(256), 0, st, D, K, b, h, dnorm, dodd, dv, start, sample); break;
         SBO_CASE(16) SBO_CASE(32) SBO_CASE(256)
 #undef SBO_CASE
         case 64: {
             const auto kernel = dev != nullptr ? &dict_parts_kernel<64, true> : &dict_parts_kernel<64, false>;
-            hipLaunchKernelGGL(kernel, dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, dv, start, sample);
+            hipLaunchKernelGGL(kernel, dim3(stages * (64 / dict_rows<64>())), dim3(256), 0, st, D, K, b, h, dnorm, dodd, dv, start, sample);
             break;
         }
         default: return hipErrorInvalidValue;

@@ -387,7 +387,8 @@ __global__ __launch_bounds__(256) void select_wide_kernel(const float* __restric
 // F16: two fp16 parts and three partial products (device_utils.h), every signal scaled by a power of two, where the dictionary has them
 // (select_arith in sbo_api.hip): half of the chain of products that the wavefronts of a tile go through, two thirds of the rows'
 // bytes (a tile reads all of its block's: 384 KiB, now 256).  131072 signals, K = 16 143 -> 116 us, 5041, K = 16 17.2 -> 14.4.  The products with a second part are
-// summed apart: the coefficients are off those in 64 bits by 0.9e-7 of theirs on average, by six bf16 products 2.0e-7 (rms; s0 = 2 to 12).
+// summed apart: the coefficients are off those in 64 bits by 0.9e-7 of theirs on average, by six bf16 products 2.0e-7 (rms; s0 = 2 to 12).  A caller's dictionary may have atoms of any size: a
+// wavefront with one that these parts do not represent well (dodd) makes them of its rows of D, each scaled by itself.
 // Workgroup ids are dealt out so that the workgroups of one XCD (ids equal modulo 8) take a contiguous run of tiles, that is,
 // few blocks, whose rows then stay in that XCD's L2 (131072 signals, K = 16: 190 -> 172 us).
 constexpr int kTileWaves = 8;
@@ -396,7 +397,8 @@ constexpr int kTileLd = 260;                  // floats per signal of the coeffi
 template <bool LISTS, bool F16>
 constexpr size_t kTileRoom = LISTS || !F16 ? 256 / 16 * 3 * 64 * 16 : 32 * kTileLd * 4;
 template <int S, bool LISTS, bool F16>
-__global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(const float* __restrict__ Y, const u32x4* __restrict__ Dsb,
+__global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(const float* __restrict__ Y, const float* __restrict__ D,
+                                                                 const u32x4* __restrict__ Dsb, const int* __restrict__ dodd,
                                                                  int K, int s0, const int32_t* __restrict__ offsets,
                                                                  const int32_t* __restrict__ perm,
                                                                  int32_t* __restrict__ supp, float* __restrict__ coef,
@@ -433,6 +435,11 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
 #pragma unroll
         for (int pl = 0; pl < NPT; ++pl) v[pl] = Qj[(ks * NPT + pl) * 64];
     };
+    int odd = 0;                               // F16: of this wavefront's atoms (uniform)
+    if constexpr (F16) {
+        const int at = __builtin_amdgcn_readfirstlane(j) * (P / 16) + 2 * wave;
+        odd = dodd[at] | dodd[at + 1];
+    }
     int shift = 0;                             // F16: signal n is scaled by 2^shift, its largest magnitude then in [2^13, 2^14)
     {
         const int64_t i = n < cnt ? (LISTS ? ids[n] : perm[pos0 + n]) : -1;
@@ -496,18 +503,53 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
         auto mfma = [](u32x4 x, u32x4 y, f32x16 z) {
             return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), z, 0, 0, 0);
         };
+        if (odd != 0) {                        // a caller's dictionary, not an orthobase: rows from D, each scaled to its own largest magnitude
+            const f32x4* row = reinterpret_cast<const f32x4*>(D + ((int64_t)__builtin_amdgcn_readfirstlane(j) * P + wave * 32 + n) * P) + h * 2;
+            unsigned mx = 0;
+#pragma unroll 1
+            for (int ks = 0; ks < KS16; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < KS16; ++ks) {
-            const u32x4 hi = ys[ks * 2 * 64 + lane], lo = ys[(ks * 2 + 1) * 64 + lane];
-            rest = mfma(a[ks % AHEAD][NPT - 1], hi, rest);
-            acc = mfma(a[ks % AHEAD][0], hi, acc);
-            rest = mfma(a[ks % AHEAD][0], lo, rest);
-            if (ks + AHEAD < KS16) fetch(a[ks % AHEAD], ks + AHEAD);
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float m = fabsf(row[ks * 4 + e][c]);
+                        mx = max(mx, __builtin_bit_cast(unsigned, m));
+                    }
+            mx = max(mx, pair_other(mx, h));
+            const int ex = (int)(mx >> 23);
+            const int q_shift = ex == 0xff ? 0 : 140 - max(ex, 1);         // of atom n
+#pragma unroll 1
+            for (int ks = 0; ks < KS16; ++ks) {
+                f32x4 v[2] = {row[ks * 4], row[ks * 4 + 1]};
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[e][c] = __builtin_amdgcn_ldexpf(v[e][c], q_shift);
+                const F16x2Pair x = split_f16x2(v[0].x, v[0].y), y = split_f16x2(v[0].z, v[0].w);
+                const F16x2Pair z = split_f16x2(v[1].x, v[1].y), w = split_f16x2(v[1].z, v[1].w);
+                const u32x4 first = {x.hi, y.hi, z.hi, w.hi}, second = {x.lo, y.lo, z.lo, w.lo};
+                const u32x4 hi = ys[ks * 2 * 64 + lane], lo = ys[(ks * 2 + 1) * 64 + lane];
+                acc = mfma(second, hi, acc);
+                acc = mfma(first, lo, acc);
+                acc = mfma(first, hi, acc);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r)       // atom (r / 4) * 8 + h * 4 + r % 4
+                acc[r] = __builtin_amdgcn_ldexpf(acc[r], -__shfl(q_shift, (r >> 2) * 8 + h * 4 + (r & 3), 64) - shift);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS16; ++ks) {
+                const u32x4 hi = ys[ks * 2 * 64 + lane], lo = ys[(ks * 2 + 1) * 64 + lane];
+                rest = mfma(a[ks % AHEAD][NPT - 1], hi, rest);
+                acc = mfma(a[ks % AHEAD][0], hi, acc);
+                rest = mfma(a[ks % AHEAD][0], lo, rest);
+                if (ks + AHEAD < KS16) fetch(a[ks % AHEAD], ks + AHEAD);
+            }
+            acc += rest;
+            static_assert(kF16DictScale == 8192.f, "2^13");
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = __builtin_amdgcn_ldexpf(acc[r], -13 - shift);
         }
-        acc += rest;
-        static_assert(kF16DictScale == 8192.f, "2^13");
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = __builtin_amdgcn_ldexpf(acc[r], -13 - shift);
     } else {
         // the six partial products, smallest first: (A part, B part)
         constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
@@ -606,7 +648,7 @@ __global__ __launch_bounds__(64 * kTileWaves, 6) void select_wide_split_kernel(c
 }
 
 template <int S, bool F16>
-hipError_t launch_wide_parts(const float* Y, int64_t m, int K, int s0, const Workspace& ws, int32_t* supp, float* coef, float* err,
+hipError_t launch_wide_parts(const float* Y, int64_t m, const float* D, int K, int s0, const Workspace& ws, int32_t* supp, float* coef, float* err,
                              bool by_pos, const ChunkLists* lists, hipStream_t st) {
     // a multiple of 8, so that the kernel's dealing of ids over the XCDs covers every tile
     const int64_t tiles = (((m + 31) / 32 + K) + 7) & ~(int64_t)7;
@@ -615,8 +657,8 @@ hipError_t launch_wide_parts(const float* Y, int64_t m, int K, int s0, const Wor
     if (lists != nullptr && (by_pos || ChunkLists::table_ints(kTileWaves, K, lists->n_chunks) * sizeof(int) > room))
         return hipErrorInvalidValue;
     if (hipError_t e = ws.raised->ensure(reinterpret_cast<const void*>(kernel), 64 * 1024); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y,
-                       reinterpret_cast<const u32x4*>(F16 ? ws.dsh : ws.dsb), K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kTileWaves), lds, st, Y, D,
+                       reinterpret_cast<const u32x4*>(F16 ? ws.dsh : ws.dsb), ws.dodd, K, s0, ws.offsets, ws.perm, supp, coef, err, (int)by_pos,
                        lists != nullptr ? *lists : ChunkLists{});
     return hipGetLastError();
 }
@@ -624,9 +666,9 @@ template <int P, int S>
 hipError_t launch_wide_ps(const float* Y, int64_t m, const float* D, int K, int s0,
                           const Workspace& ws, int32_t* supp, float* coef, float* err, int ops,
                           bool by_pos, const ChunkLists* lists, hipStream_t st) {
-    (void)D;                                   // the kernels read ws.dsh / ws.dsb / ws.dsw, the same Q in operand order
-    if (ops == kOpsF16) return launch_wide_parts<S, true>(Y, m, K, s0, ws, supp, coef, err, by_pos, lists, st);
-    if (ops == kOpsBf16) return launch_wide_parts<S, false>(Y, m, K, s0, ws, supp, coef, err, by_pos, lists, st);
+    // the kernels read ws.dsh / ws.dsb / ws.dsw, the same Q in operand order (kOpsF16: or D, see there)
+    if (ops == kOpsF16) return launch_wide_parts<S, true>(Y, m, D, K, s0, ws, supp, coef, err, by_pos, lists, st);
+    if (ops == kOpsBf16) return launch_wide_parts<S, false>(Y, m, D, K, s0, ws, supp, coef, err, by_pos, lists, st);
     if (lists != nullptr) return hipErrorInvalidValue;
     const int64_t max_tiles = (m + 31) / 32 + K;
     dim3 grid((unsigned)((max_tiles + 3) / 4));
@@ -722,7 +764,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
     if (p == 256 && !ops_valid) {              // the p = 256 kernels read Q in operand order
         hipError_t e = ops == kOpsF32 ? launch_dict_swizzle(p, K, D, ws.dsw, CallStart{}, st)
                                       : launch_dict_parts(p, K, D, ops == kOpsBf16 ? ws.dsb : nullptr, ops == kOpsF16 ? ws.dsh : nullptr,
-                                                          ws.dnorm, nullptr, SignalSample{}, CallStart{}, st);
+                                                          ws.dnorm, ws.dodd, nullptr, SignalSample{}, CallStart{}, st);
         if (e != hipSuccess) return e;
     }
     const bool split = ops != kOpsF32;

@@ -182,6 +182,9 @@ __device__ __forceinline__ F16x2Quad split_f16x2_dict(f32x4 row, float& q2, floa
     r2 += rem.x * rem.x + rem.y * rem.y + rem.z * rem.z + rem.w * rem.w;
     return {u32x2{a.hi, b.hi}, u32x2{a.lo, b.lo}};
 }
+// An atom of this squared norm is not well represented by those parts: below 1/16 its entries reach into fp16's smallest numbers (above,
+// these cost 2^-34 of the norm at most), from 4 on they may leave its range.
+__device__ __forceinline__ bool odd_norm2(float q2) { return !(q2 >= 1.f / 256 && q2 < 16.f); }
 template <int P>
 __device__ __forceinline__ void store_operand_f16x2(unsigned* __restrict__ dsh, int grow, int d4, F16x2Quad q) {
     constexpr int KS16 = P / 16;
@@ -199,6 +202,7 @@ struct DictOps {
     unsigned* bf16 = nullptr;   // three bf16 parts
     unsigned* f16 = nullptr;    // two fp16 parts, and with them
     float2* dnorm = nullptr;    // per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
+    int* dodd = nullptr;        // per 16 atoms (p = 256): one has a norm far from an orthobase's (odd_norm2)
 };
 // Maximum over the 16 lanes of a row, in all of them.
 __device__ __forceinline__ float row16_max(float x) {

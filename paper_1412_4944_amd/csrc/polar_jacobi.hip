@@ -42,6 +42,7 @@ static DictOps dict_ops(const Workspace& ws, int write_ops) {
     if (write_ops & kOpsF16) {
         ops.f16 = ws.dsh;
         ops.dnorm = ws.dnorm;
+        ops.dodd = ws.dodd;
     }
     return ops;
 }

@@ -434,7 +434,10 @@ __device__ __forceinline__ void emit_strip(const WideArgs& g, int j, int s, cons
         }
         q2 = row16_max(q2);
         r2 = row16_max(r2);
-        if (lane == 0) g.ops.dnorm[j * (P / 16) + s] = float2{sqrtf(q2), sqrtf(r2)};
+        if (lane == 0) {
+            g.ops.dnorm[j * (P / 16) + s] = float2{sqrtf(q2), sqrtf(r2)};
+            g.ops.dodd[j * (P / 16) + s] = 0;  // (an orthobase)
+        }
     }
     __syncthreads();
 }
@@ -973,7 +976,10 @@ __device__ __forceinline__ Outcome newton_schulz(const WideArgs& g, int j, const
         r2 += far_load(sums + 16 + c16);
         q2 = row16_max(q2);
         r2 = row16_max(r2);
-        if (tid == 0) g.ops.dnorm[j * (P / 16) + sn] = float2{sqrtf(q2), sqrtf(r2)};
+        if (tid == 0) {
+            g.ops.dnorm[j * (P / 16) + sn] = float2{sqrtf(q2), sqrtf(r2)};
+            g.ops.dodd[j * (P / 16) + sn] = 0;
+        }
     }
     return Outcome::done;
 }

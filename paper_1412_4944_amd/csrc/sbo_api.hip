@@ -43,6 +43,7 @@ size_t workspace_layout(int p, int K, int s0, int64_t m_max, Workspace* ws, char
     w.dsb = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 6);
     w.dsh = (unsigned*)take((size_t)((K * p + 63) / 64) * 64 * p * 4);
     w.dnorm = (float2*)take((size_t)K * (p / 16) * 8);
+    w.dodd = (int*)take(p == 256 ? (size_t)K * (p / 16) * 4 : 0);
     w.dev = (float2*)take(p == 64 ? (size_t)K * 8 : 0);
     w.sample = (unsigned*)take(p == 64 ? (size_t)K * (kSample / 8) : 0);
     const size_t split_m = (size_t)(m_max < kEnergySplitSignals ? m_max : kEnergySplitSignals);
@@ -177,7 +178,7 @@ static int run_swizzle(sbo_ctx* c, const float* Y, int64_t m, const float* D) {
     if (ops & kOpsF32) SBO_HIP(launch_dict_swizzle(c->p, c->K, D, c->ws.dsw, start, c->stream));
     if (ops & (kOpsBf16 | kOpsF16))
         SBO_HIP(launch_dict_parts(c->p, c->K, D, ops & kOpsBf16 ? c->ws.dsb : nullptr,
-                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm,
+                                  ops & kOpsF16 ? c->ws.dsh : nullptr, c->ws.dnorm, c->ws.dodd,
                                   guess_applies(c->p, c->K, c->s0, m, choice_arith(c)) ? c->ws.dev : nullptr,
                                   SignalSample{Y, (int)m, c->ws.sample}, start, c->stream));
     return SBO_OK;

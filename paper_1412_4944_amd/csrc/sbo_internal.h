@@ -108,6 +108,7 @@ struct Workspace {
     unsigned* dsb;         // the same rows as three bf16 parts (6 bytes per entry)
     unsigned* dsh;         // the same rows as two fp16 parts (4 bytes per entry)
     float2* dnorm;         // [K*p/16] per 16 atoms: largest norm, largest norm of what the leading fp16 part leaves
+    int* dodd;             // [K*p/16] p = 256: per 16 atoms, whether one is not well represented by fp16 parts (odd_norm2)
     float2* dev;           // [K] p = 64: |Q Q^T - I|_F^2 of a block, in two parts (guess_applies)
     unsigned* sample;      // [K][kSample / 32] p = 64: which of a sample of the signals a block represents
     float* part_E;         // [kEnergySplitRows][<= kEnergySplitSignals] split coding: best energy per row; or
@@ -295,9 +296,9 @@ struct SignalSample {
     unsigned* mask = nullptr;      // ws.sample
 };
 // dsb / dsh (either may be nullptr) = D as three bf16 / two fp16 parts per entry in operand order
-// (device_utils.h); dnorm comes with dsh.  dev (or nullptr; p = 64, dsh given): |Q Q^T - I|_F^2 per block, and the
+// (device_utils.h); dnorm, and at p = 256 dodd, come with dsh.  dev (or nullptr; p = 64, dsh given): |Q Q^T - I|_F^2 per block, and the
 // sample of the m signals of Y (m >= kSample).
-hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, float2* dev,
+hipError_t launch_dict_parts(int p, int K, const float* D, unsigned* dsb, unsigned* dsh, float2* dnorm, int* dodd, float2* dev,
                              const SignalSample& sample, const CallStart& start, hipStream_t st);
 // Whether the block choice of a first pass (turn <= 0 of launch_energy) reads ws.dev and ws.sample.
 bool guess_applies(int p, int K, int s0, int64_t m, int arith);

@@ -946,6 +946,32 @@ def test_select_p256_two_parts_over_magnitudes(m):
     assert (coef[~some] == 0).all()
 
 
+@pytest.mark.parametrize("m", [79, 2048, 2100])         # as above
+@pytest.mark.parametrize("kind,size", [("scale", 1.01 / 16), ("scale", 0.99 / 16), ("scale", 1e-6), ("scale", 1e-8), ("scale", 1e-12),
+                                       ("scale", 1e-20), ("atoms", 1e-3), ("atoms", 1e-8), ("atoms", 0.0), ("last", 5.0)])
+def test_select_p256_takes_any_dictionary(m, kind, size):
+    """sbo_code, one orthobase by any factor, or some of its atoms: the coefficient of an atom is as exact as its own norm allows (bound
+    as above), on both sides of the line (1/16) from which on rows are read from D itself."""
+    p, s0 = 256, 12
+    rng = np.random.default_rng(89)
+    D = synth.random_onb(rng, p)[None]
+    at = {"scale": slice(None), "atoms": [0, 31, 32, 200], "last": [255]}[kind]
+    D[0][at] *= size
+    D = D.astype(np.float32)
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    with Sbo(p, 1, s0, m) as g:
+        blk, supp, coef, _err = g.code(Y, D)
+    assert (blk == 0).all()
+    D64, Y64 = D[0].astype(np.float64), Y.astype(np.float64)
+    c64 = Y64 @ D64.T
+    bound = (3 * 2.0 ** -22 + 48 * 2.0 ** -24) * np.linalg.norm(Y64, axis=1)[:, None] * np.linalg.norm(D64, axis=1)
+    assert (np.abs(coef - np.take_along_axis(c64, supp, 1)) <= np.take_along_axis(bound, supp, 1)).all()
+    kept = np.zeros((m, p), bool)
+    np.put_along_axis(kept, supp, True, 1)
+    mag = np.abs(c64)
+    assert (np.where(kept, mag + bound, np.inf).min(1) >= np.where(kept, 0, mag - bound).max(1)).all()
+
+
 @pytest.mark.parametrize("m,s0", [(1500, 8), (6000, 5), (140000, 2)])      # a tile per wavefront; a few; many, grouped first
 @pytest.mark.parametrize("order", ["rising", "falling", "mixed"])
 def test_select_accum_two_parts_over_magnitudes(m, s0, order):
