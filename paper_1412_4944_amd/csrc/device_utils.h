@@ -109,10 +109,18 @@ __device__ __forceinline__ unsigned pack_f16(float v0, float v1) {
     const f16x2 t = {(_Float16)v0, (_Float16)v1};        // round to nearest even
     return __builtin_bit_cast(unsigned, t);
 }
+// FINITE: magnitudes from 65520 on, which round to infinity, have the largest number as their first part; the second one takes the rest
+// (below 32 for magnitudes below 65536).
+template <bool FINITE = false>
 __device__ __forceinline__ F16x2Pair split_f16x2(float v0, float v1) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     F16x2Pair r;
     r.hi = pack_f16(v0, v1);
+    if constexpr (FINITE) {
+        const f16x2 largest = {(_Float16)65504.f, (_Float16)65504.f};
+        const f16x2 t = __builtin_elementwise_max(__builtin_elementwise_min(__builtin_bit_cast(f16x2, r.hi), largest), -largest);
+        r.hi = __builtin_bit_cast(unsigned, t);
+    }
     // v - 1 * hi with a one and a packed hi that the compiler does not see through: v_fma_mix_f32 reads the halves as they
     // are, four instructions a pair (eight: both values rounded apart, unpacked and subtracted)
     float one = 1.f;
@@ -174,7 +182,7 @@ struct F16x2Quad {
 __device__ __forceinline__ F16x2Quad split_f16x2_dict(f32x4 row, float& q2, float& r2) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     constexpr float sc = kF16DictScale, inv = 1.f / kF16DictScale;
-    const F16x2Pair a = split_f16x2(row.x * sc, row.y * sc), b = split_f16x2(row.z * sc, row.w * sc);
+    const F16x2Pair a = split_f16x2<true>(row.x * sc, row.y * sc), b = split_f16x2<true>(row.z * sc, row.w * sc);
     const f16x2 ha = __builtin_bit_cast(f16x2, a.hi), hb = __builtin_bit_cast(f16x2, b.hi);
     const f32x4 rem = {row.x - (float)ha[0] * inv, row.y - (float)ha[1] * inv, row.z - (float)hb[0] * inv,
                        row.w - (float)hb[1] * inv};

@@ -946,6 +946,37 @@ def test_select_p256_two_parts_over_magnitudes(m):
     assert (coef[~some] == 0).all()
 
 
+@pytest.mark.parametrize("p", [16, 32, 64, 256])
+@pytest.mark.parametrize("s0", [1, 4])
+@pytest.mark.parametrize("m", [100, 5000])
+def test_code_with_dictionary_entries_up_to_8(p, s0, m):
+    """The default arithmetic takes dictionary entries below 8: up to the next number below, where fp16 parts scaled by 2^13 end.
+    Energies: 3 * 2^-22 |y||q| for the parts of a coefficient, and a rounding of 2^-24 |y||q| for each of its p products."""
+    K = 4
+    rng = np.random.default_rng(101 + p)
+    D = np.stack([synth.random_onb(rng, p) for _ in range(K)])
+    for j, largest in ((1, np.nextafter(np.float32(8), np.float32(0))), (3, 7.9985)):
+        D[j] *= largest / np.abs(D[j]).max()
+    D = D.astype(np.float32)
+    D[1][np.unravel_index(np.abs(D[1]).argmax(), (p, p))] = np.nextafter(np.float32(8), np.float32(0))
+    Y = rng.standard_normal((m, p)).astype(np.float32)
+    with Sbo(p, K, s0, m) as g:
+        blk, supp, coef, _err = g.code(Y, D)
+    D64, Y64 = D.astype(np.float64), Y.astype(np.float64)
+    c64 = np.einsum("mp,kap->mka", Y64, D64)
+    E = np.sort(c64 ** 2, axis=2)[:, :, -s0:].sum(2)
+    norm = np.linalg.norm(Y64, axis=1)
+    rel = 3 * 2.0 ** -22 + p * 2.0 ** -24
+    bound = rel * norm * np.linalg.norm(D64, axis=2).max()
+    assert (E[np.arange(m), blk] >= E.max(1) - 4 * np.sqrt(s0 * E.max(1)) * bound).all()
+    own = c64[np.arange(m), blk]
+    assert (np.abs(coef - np.take_along_axis(own, supp, 1)) <= bound[:, None]).all()
+    kept = np.zeros((m, p), bool)
+    np.put_along_axis(kept, supp, True, 1)
+    mag = np.abs(own)
+    assert (np.where(kept, mag, np.inf).min(1) >= np.where(kept, 0, mag).max(1) - 2 * bound).all()
+
+
 @pytest.mark.parametrize("m", [79, 2048, 2100])         # as above
 @pytest.mark.parametrize("kind,size", [("scale", 1.01 / 16), ("scale", 0.99 / 16), ("scale", 1e-6), ("scale", 1e-8), ("scale", 1e-12),
                                        ("scale", 1e-20), ("atoms", 1e-3), ("atoms", 1e-8), ("atoms", 0.0), ("last", 5.0)])
