@@ -122,12 +122,14 @@ __device__ __forceinline__ float mantissa(float alpha) {
 __device__ __forceinline__ float power_of_two(float alpha) {
     return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, alpha) & 0x7f800000u);
 }
-// Power of two that brings entries of at most this magnitude (its bits) below kScale; zero, so that the block goes to the Jacobi
-// SVD, where sums of their squares leave the range of fp32.
+// Power of two that brings entries of at most this magnitude (its bits) below kScale (three parts: 2), so that neither the parts nor the
+// sums of fourth powers that show the spread leave their range; zero, so that the block goes to the Jacobi SVD, where sums of
+// squares would.
+template <int P>
 __device__ __forceinline__ float input_scale(unsigned mx) {
     const unsigned e = mx >> 23;               // biased exponent
     if (e < 64u || e > 190u) return 0.f;
-    return __builtin_bit_cast(float, (unsigned)(127 + 13 + 127 - (int)e) << 23);
+    return __builtin_bit_cast(float, (unsigned)(127 + (ns_parts<P>() == 2 ? 13 : 0) + 127 - (int)e) << 23);
 }
 
 // wavefronts per strip of 16 columns: they share out its row tiles
@@ -720,7 +722,7 @@ __global__ __launch_bounds__(ns_threads<P>()) void polar_ns_kernel(NsArgs g) {
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < T * HV; ++w) mx = max(mx, __builtin_bit_cast(unsigned, red[w]));
-        const float scale = ns_parts<P>() == 2 ? input_scale(mx) : 1.f;
+        const float scale = input_scale<P>(mx);
 #pragma unroll
         for (int a = 0; a < TH; ++a) xr[a] = scale * rows[c16 * LD + (hh * TH + a) * 4 + grp];
         __syncthreads();                       // the strips become the images

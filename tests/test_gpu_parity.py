@@ -1135,6 +1135,23 @@ def test_polar_on_both_sides_of_the_lines_of_the_spread(p, scale):
     assert (err <= steps * np.array(conds) * 2.0 ** -24).all()
 
 
+@pytest.mark.parametrize("p", [16, 32, 64])
+def test_polar_does_not_depend_on_a_power_of_two(p):
+    """U V^T has no scale: the steps and the bits are those of the same matrix times 2^k, as long as its squares and its entries are
+    fp32 numbers (the spread, by which the steps are chosen, is made of fourth powers)."""
+    rng = np.random.default_rng(103 + p)
+    mats = [(synth.random_onb(rng, p) * np.geomspace(1, 1 / c, p)) @ synth.random_onb(rng, p) for c in (1.05, 1.5, 3, 10, 100)]
+    M = np.stack(mats).astype(np.float32)
+    M[np.abs(M) < 2.0 ** -40] = 0
+    with Sbo(p, len(M), 4, 256) as g:
+        D = g.polar(M, np.zeros_like(M), None)
+        steps = sbo.sbo_svd_sweeps(g.ctx, len(M))
+        assert all(x < 0 for x in steps)
+        for k in (-58, -40, -30, 25, 58):
+            np.testing.assert_array_equal(g.polar(M * np.float32(2.0 ** k), np.zeros_like(M), None), D)
+            assert sbo.sbo_svd_sweeps(g.ctx, len(M)) == steps, k
+
+
 @pytest.mark.parametrize("K", [1, 9, 33])               # one team; two groups of eight; teams with three blocks in turn
 @pytest.mark.parametrize("jacobi_only", [False, True], ids=["auto", "jacobi"])
 def test_polar_p256_teams_of_workgroups(K, jacobi_only):
