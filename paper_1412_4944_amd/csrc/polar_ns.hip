@@ -104,11 +104,13 @@ __device__ __forceinline__ float step_alpha(int k) {
 }
 
 // Where l starts, by the spread of the squared singular values: 0.45, 0.16, 0.09, 0.064.  Steps simulated in 64 bits on block matrices of
-// training rounds, with 0.45 / 0.16: spread 0.13 to 0.15 4 / 5, 0.2 to 0.3 5 / 5, beyond 0.3 5.2 to 7 / 5; with 0.16 / 0.064 0.45 to
-// 0.6 5 / 6, 0.75 to 0.9 11.3 / 10.5, 1.1 to 1.4 10 / 9.2, beyond 1.4 11.8 / 10.3 and more.  0.09 between 0.6 and 1.4: with 0.064 the
-// error was up to 1.15 of what it was with 0.16, now 0.95 to 1.05, in as many steps.  Lower l lose accuracy (0.025 beyond
+// training rounds, with 0.45 / 0.16: spread 0.13 to 0.15 4 / 5, 0.2 to 0.3 5 / 5, beyond 0.3 5.2 to 7 / 5; with 0.16 / 0.09: up to 0.7
+// 5.0 / 6, 0.7 to 0.9 5.8 / 6, 0.9 to 1 6.1 / 6, 1 to 1.4 6.7 / 6.1; with 0.09 / 0.064 beyond 1.4 7.8 / 7.2.  Error against 64 bits (rms over 128
+// block matrices each of 1024 to 2896 signals, s0 = 2 to 8, of that with three parts and 0.16 throughout): with the second line at 0.6
+// 0.92 to 1.02, at 0.75 0.91 to 1.005, at 0.9 0.90 to 0.995, where the slowest block of a launch is one of seven steps more often (ten iterations,
+// 16384 signals, K = 16 366 -> 370 us, sbo_learn 5645 -> 5710); 0.064 instead of 0.09 up to 1.15.  Lower l lose accuracy (0.025 beyond
 // 1.4: up to 1.5 of the error), and so do 0.09 and 0.064 for p < 64, which stays with 0.16 there (1.28).
-constexpr float kSpread[3] = {0.18f, 0.6f, 1.4f};
+constexpr float kSpread[3] = {0.18f, 0.75f, 1.4f};
 // X and E are split in two fp16 parts each (device_utils.h), times this: no singular value is above one after a step, no
 // entry of E above 1.9.
 template <int P>

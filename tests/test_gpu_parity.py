@@ -1110,12 +1110,12 @@ def test_update_of_an_atom_that_only_weak_signals_use(p, seed):
 @pytest.mark.parametrize("p", [16, 32, 64])
 @pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])
 def test_polar_on_both_sides_of_the_lines_of_the_spread(p, scale):
-    """The first guess of the smallest singular value hangs on the spread of the squared ones (0.01, 0.18, 0.6, 1.4: kSpread in
+    """The first guess of the smallest singular value hangs on the spread of the squared ones (0.01, 0.18, 0.75, 1.4: kSpread in
     polar_ns.hip).  An eighth of the values lies above the others, so that the spread is 1 % below and above each line.
     Bound: a rounding of 2^-24 in every step, where singular values of 1 / cond weigh it cond times as much."""
     rng = np.random.default_rng(47 + p)
     h, mats, conds = p // 8, [], []
-    for line in (0.01, 0.18, 0.6, 1.4):
+    for line in (0.01, 0.18, 0.6, 0.75, 1.4):
         for want in (0.99 * line, 1.01 * line):
             lo, hi = 1.0, 1e3
             for _ in range(80):
