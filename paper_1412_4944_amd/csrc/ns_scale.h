@@ -3,8 +3,8 @@
 // With all singular values in [l, 1], X scaled by alpha(l) = sqrt(3 / (1 + l + l^2)) before a step makes the
 // step's polynomial f(s) = alpha s (3 - (alpha s)^2) / 2 map [l, 1] to the smallest possible interval
 // [l', 1], l' = f(l).  A smaller singular value is safe (f is positive and at most one on
-// (0, sqrt(3))), but it grows by only 3/2 a step once alpha is 1: so l starts at 0.16 (block matrices of a trained
-// dictionary have condition numbers of 2 to 10) and is lowered when a column of X shows it to be
+// (0, sqrt(3))), but it grows by only 3/2 a step once alpha is 1: so l starts at a guess by the spread of the
+// singular values (0.45, 0.16 or 0.064, below; block matrices of a trained dictionary have condition numbers of 2 to 10) and is lowered when a column of X shows it to be
 // wrong: the smallest column norm is an upper bound of the smallest singular value, and where atoms are
 // rarely used it is close to it.  From 0.5 on the values have met and it is left alone.  (Simulated on block
 // matrices of first training rounds, condition 60 to 5000: 9 to 15 steps instead of 11 to 22; condition

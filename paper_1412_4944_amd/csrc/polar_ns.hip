@@ -34,7 +34,7 @@
 //     step the products that were left out are added.  What is left in X E is made up for by three roundings less: E is scaled by the
 //     mantissa of alpha, so that the products are added to X without one, and the two steps of a contraction are summed apart.
 //     |Q - Q64|_F / sqrt(p) on block matrices of training rounds (96 to 65536 signals, condition 1.3 to 700) 0.54 to 1.05 of that with three
-//     parts and l = 0.16, on average 0.81 (p = 32 0.91, p = 16 0.94: the guess alone); p = 32, 16 with two parts 1.3 and 1.5, in the same time.
+//     parts and l = 0.16, on average 0.81 (p = 32 0.91, p = 16 0.94: the guess alone; more at kSpread); p = 32, 16 with two parts 1.3 and 1.5, in the same time.
 //   * The steps' branches are those of scalars: as the sum that decides comes out of lanes, the compiler would take every one of
 //     them for divergent (p = 16: 2 % of an iteration).
 // Measured (p = 64, launch to launch): inside sbo_iterate (K = 16, 16384 signals) 22.4 us with a wavefront per strip, 19.5 with two; the kernel

@@ -20,6 +20,8 @@
 //   the G of a step that may be the last one; elsewhere two fp16 parts, scaled, and three.  What these leave out of G (2^-22 of an entry)
 //   is symmetric and goes with the next step; in X E it is made up for by a rounding less, E being scaled by alpha.  |Q - Q64|_F / sqrt(p)
 //   0.85 to 0.95 of what it was (block matrices of training rounds, 384 to 16384 signals); splits and matrix work of a step are halved.
+//   (Together with the sums in teams and the first l of ns_scale.h 0.69 to 0.78; nearly axis-aligned singular vectors, where the
+//   result's own rounding is most of it, 1.06 to 1.15.)
 //
 //   Up to eight blocks on one stream, a team on each XCD: two workgroups to a strip, one for the upper and one for the lower half of its rows,
 //   which halves the operands that each of them reads.  They need each other's half of X, which comes with the barrier, and of E:
@@ -36,19 +38,21 @@
 //   handed over through memory with a version number; there is no barrier but one per sweep.
 //
 // What bounds it: Newton-Schulz by the 512 KiB of operands per workgroup and step from L2 (30 bytes a cycle arrive at a CU, no
-// more with one team on an XCD than with two, or with more loads on their way; pairs 256 KiB): of 25000 cycles a step 11300 are the
-// first product and the wait for its slowest wavefront, 9000 the second (the splits), 2300 the barrier; with pairs, of 18000 7200, 6700 and
-// 2500.  K = 4 114 -> 80 us, K = 16 131 -> 120 (9 steps from a finished matrix): 103 with pairs alone; 88, 124 because the compiler
+// more with one team on an XCD than with two, or with more loads on their way; pairs 256 KiB): of 17000 cycles a step 6500 are the
+// first product, 4000 the second, 1250 E, 2400 what is left for others and the parts in LDS, 2600 the barrier; with pairs, of 12900 4500,
+// 3500, 900, 1550 and 2000; a step that may be the last one 22700 and 17600.  (With three parts in all products 25000 and 18000: 11300, 9000
+// and 2300 of them the products and the barrier, with pairs 7200, 6700 and 2500.)  K = 4 114 -> 80 us, K = 16 131 -> 120 (9 steps from a finished matrix): 103 with pairs alone; 88, 124 because the compiler
 // took the operands' descriptor and offsets for different ones in every lane (a loop around every load) and a flat load among
 // them waited for all of them; the rest by a barrier of flags that a wavefront reads at once, by loads that pass L1 by,
 // instead of a counter, polled by atomics (5000 cycles with pairs).  Eight steps of operands on their way instead of four: 91 us (registers spilled, and half of
 // the wavefronts get theirs late).  With two fp16 parts in most products
-// K = 4 80 -> 70, K = 16 120 -> 91 (a step 5.6 and 6.9 us), so that the cycles above are of three parts in all of them.
+// K = 4 80 -> 70, K = 16 120 -> 91 (a step 5.6 and 6.9 us).
 // With the three parts in memory (768 KiB) 138 -> 131 us in the same profile,
 // K = 16; K = 4 no difference.  Jacobi by the vector ALU
 // of eight CUs (16 rotations of 256 + 256 rows per workgroup at a time) and 15 hand-overs a sweep.  Jacobi is called, not inlined,
 // where a block may need it after Newton-Schulz, whose operands take all registers (inlined: 100 of them spilled, K = 16 147 us
-// instead of 130; so is a pair team's way on without its helpers); the norm and the smallest diagonal entry of a step share a barrier (130 -> 126).
+// instead of 130, with three parts; so is a pair team's way on without its helpers).  Since every product has a body for three parts and one for
+// two, 17 registers a lane are spilled all the same, with pairs 61 (488 and 860 bytes of scratch, 400 of them the called Jacobi's); the norm and the smallest diagonal entry of a step share a barrier (130 -> 126).
 // Measured: K = 16 inside sbo_iterate 347 us (a launch per product and step, fp32 matrix instruction,
 // 20 steps enqueued, plus launches for the sum of the pieces, the Jacobi SVD that has nothing to do,
 // the operand order and the squared error: 46 launches, 400 us) -> 126 us and nothing else; K = 1 in a

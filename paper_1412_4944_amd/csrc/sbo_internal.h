@@ -56,8 +56,11 @@ inline int accum_max_pieces(int64_t m, int K) {
 // The pieces of launch_accumulate.  p = 256 on the bf16 matrix cores, small sets: slices of 64 dims, a workgroup each, of
 // pieces that are up to four times as long; a quarter of the results to write and for the SVD to add up.  A step of a
 // slice takes two thirds of a whole one's time, so it does not pay for long.  sbo_update, whole / sliced (us): K = 1, 600
-// signals 251 / 245, 2048 180 / 173, 8192 207 / 187; K = 2, 8192 230 / 219; K = 4, 4096 232 / 227, 16384 235 / 228; K = 16, 5041 321 / 317,
-// 16384 316 / 315, 32768 358 / 358; K = 32, 20000 3028 / 2933 (accumulation 31 / 42), 32768 582 / 602.
+// signals 119 / 112, 2048 96 / 90, 8192 113 / 93, 16384 119 / 102, 32768 136 / 114, 65536 157 / 136; K = 2, 16384 115 / 103, 49152 133 / 124; K = 4,
+// 4096 115 / 110, 16384 112 / 103, 32768 123 / 117, 49152 133 / 130; K = 8, 16384 115 / 110, 32768 120 / 119; K = 16, 5041 219 / 214, 16384
+// 154 / 152, 24576 152 / 150, 32768 151 / 152; K = 24, 16384 256 / 255, 24576 243 / 247; K = 32, 16384 290 / 290, 32768 257 / 267.
+// So the line in K is where it stops to pay, and the one in m is on the safe side: with few blocks it would pay up to three or four times
+// as many signals, for which the error of the longer sums has not been measured.
 struct AccumGeom {
     int piece, max_pieces, slices;
 };
@@ -343,7 +346,7 @@ hipError_t launch_select(int p, int K, int s0, const float* Y, int64_t m, const 
                          int ops, hipStream_t st, int32_t* blk = nullptr, bool choose = false, bool by_pos = false,
                          bool lists = false);
 
-// M == nullptr: the pieces stay in ws.partial (cut as accum_piece says), for launch_polar_from_pieces.  blk (M == nullptr, where
+// M == nullptr: the pieces stay in ws.partial (cut as accum_geom(p, m, K, ws.parts_accum) says), for launch_polar_from_pieces.  blk (M == nullptr, where
 // lists_in_update says so): as for launch_select_accum.
 hipError_t launch_accumulate(int p, int K, int s0, const float* Y, int64_t m, const int32_t* supp,
                              const float* coef, const Workspace& ws, float* M, hipStream_t st, bool by_pos = false,
