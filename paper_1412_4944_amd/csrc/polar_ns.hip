@@ -108,7 +108,9 @@ __device__ __forceinline__ float step_alpha(int k) {
 // 5.0 / 6, 0.7 to 0.9 5.8 / 6, 0.9 to 1 6.1 / 6, 1 to 1.4 6.7 / 6.1; with 0.09 / 0.064 beyond 1.4 7.8 / 7.2.  Error against 64 bits (rms over 128
 // block matrices each of 1024 to 2896 signals, s0 = 2 to 8, of that with three parts and 0.16 throughout): with the second line at 0.6
 // 0.92 to 1.02, at 0.75 0.91 to 1.005, at 0.9 0.90 to 0.995, where the slowest block of a launch is one of seven steps more often (ten iterations,
-// 16384 signals, K = 16 366 -> 370 us, sbo_learn 5645 -> 5710); 0.064 instead of 0.09 up to 1.15.  Lower l lose accuracy (0.025 beyond
+// 16384 signals, K = 16 366 -> 370 us, sbo_learn 5645 -> 5710); 0.064 instead of 0.09 up to 1.15.  What the spread does not show is a
+// single late value among equal ones (an atom that hardly any signal uses): with 0.45 a step more than with 0.16 (condition 100: 13 instead of 12).
+// Lower l lose accuracy (0.025 beyond
 // 1.4: up to 1.5 of the error), and so do 0.09 and 0.064 for p < 64, which stays with 0.16 there (1.28).
 constexpr float kSpread[3] = {0.18f, 0.75f, 1.4f};
 // X and E are split in two fp16 parts each (device_utils.h), times this: no singular value is above one after a step, no
